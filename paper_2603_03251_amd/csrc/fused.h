@@ -15,6 +15,7 @@ constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxRows = 48;   // rows of one narrow pass (three 16-row MFMA tiles)
 constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles): contexts with more than kFusedMaxRows rows
 constexpr int kFusedWideQueryTiles = 3;   // wide passes: query tiles per attention unit (n_attn_units counts such units)
+constexpr int kFusedWideFreshKeys = 192;  // wide passes: tokens of one sequence an extend pass takes (LDS room of the attention unit)
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())
 constexpr int kFusedMaxSlices = 4;   // most k-slices of a linear layer
 constexpr unsigned kFusedSpinLimit = 4000000u;   // polls of a bounded wait (seconds of wall time) before it gives up

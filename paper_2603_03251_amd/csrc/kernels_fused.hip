@@ -1100,7 +1100,7 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
 // pull the same trunk once per tile, and what bounds them is that pull, not their arithmetic).  Same method and same
 // layouts as attn_unit; the qkv projections arrive with the norm's row scale applied.  Fresh keys: those of all the
 // unit's query tiles (branch rows) or the pass's tokens (extend rows), staged once, NFI items per thread.
-constexpr int kMultiFreshKeys = 192;   // LDS room: NQ x (rows per tile x slots per row) for NQ = 3, or the tokens of an extend
+constexpr int kMultiFreshKeys = kFusedWideFreshKeys;   // LDS room: NQ x (rows per tile x slots per row) for NQ = 3, or the tokens of an extend
 template <int MT, int MP, int NPQ, int NPP, int NQ, bool PG>
 __device__ __forceinline__ void attn_unit_multi(const FusedParams& p, const FusedLayer& L, const float* qkv, int unit, f32x4* lds,
                                                 bf16_t* att_out, float* part_o, float* part_ml, int ph) {
@@ -1966,16 +1966,10 @@ __global__ __launch_bounds__(kFusedThreads) void wide_kernel(FusedParams p, int 
   extern __shared__ f32x4 red[];
   __shared__ float r_s[MP];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t h_stride = (int64_t)MP * p.d;
-  const int64_t ssq_stride = (int64_t)(p.d >> 4) * MP;
   const int lm_phase = fused_last_phase(p.L);
   const int l = ph == 0 ? 0 : (ph == lm_phase ? p.L - 1 : (ph - 1) / 6);
   const int sub = ph == 0 ? -1 : (ph == lm_phase ? 6 : (ph - 1) % 6);
   const FusedLayer L = p.layers[l];
-  float* qkv = p.qkv + (int64_t)l * MP * p.qkvd;
-  bf16_t* att = p.att + (int64_t)l * 2 * MP * p.qd;
-  float* part_o = p.part_o + (int64_t)l * p.part_layer_stride * 64;
-  float* part_ml = p.part_ml + (int64_t)l * p.part_layer_stride * 2;
   stamp(p, ph, 0);
   if (sub == -1) {
     // embedding gather: residual stream version 0, (h * gain) as one fp16 plane, sums of squares per 64 features
@@ -2012,14 +2006,13 @@ __global__ __launch_bounds__(kFusedThreads) void wide_kernel(FusedParams p, int 
     }
   } else if (sub == 1) {
     for (int u = blockIdx.x; u < p.n_attn_units; u += gridDim.x)
-      attn_unit_multi<MTOT, MP, PL::q, PL::p, kWideQueryTiles, PG>(p, L, qkv, u, red, att, part_o, part_ml, ph);
+      attn_unit_multi<MTOT, MP, PL::q, PL::p, kWideQueryTiles, PG>(p, L, p.qkv, u, red, p.att, p.part_o, p.part_ml, ph);
   } else if (sub == 2) {
-    for (int u = blockIdx.x; u < p.n_pair_units; u += gridDim.x) attn_merge_unit<MTOT, MP, 1>(p, u, part_o, part_ml, att);
+    for (int u = blockIdx.x; u < p.n_pair_units; u += gridDim.x) attn_merge_unit<MTOT, MP, 1>(p, u, p.part_o, p.part_ml, p.att);
   } else if (sub == 6 && p.hidden) {
     // final-norm hidden states: workgroup per row, the row's scale from the tile sums
-    const int v = 2 * p.L;
-    const gfloat* hv = (const gfloat*)(p.h + (int64_t)v * h_stride);
-    const gfloat* sq = (const gfloat*)(p.ssq + (int64_t)v * ssq_stride);
+    const gfloat* hv = (const gfloat*)p.h;
+    const gfloat* sq = (const gfloat*)p.ssq;
     float* tmp = (float*)red;
     for (int m = blockIdx.x; m < p.M; m += gridDim.x) {
       float s = 0.f;
@@ -2472,45 +2465,36 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
     SSD_HIP(hipFuncSetAttribute((const void*)wide_kernel<PL, PG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes));
     configured = true;
   }
-  constexpr int64_t MP = kFusedWideRows;
-  const int64_t h_stride = MP * p.d, ssq_stride = (int64_t)(p.d >> 4) * MP;
   const int lm_phase = fused_last_phase(p.L);
   for (int ph = first; ph <= last; ++ph) {
     const int l = ph == 0 ? 0 : (ph == lm_phase ? p.L - 1 : (ph - 1) / 6);
     const int sub = ph == 0 ? -1 : (ph == lm_phase ? 6 : (ph - 1) % 6);
     if (sub == 2 && p.NS == 1) continue;             // no merge phase with one key split
     const FusedLayer& L = layers_host[l];
-    float* qkv = p.qkv + (int64_t)l * MP * p.qkvd;
-    bf16_t* att = p.att + (int64_t)l * 2 * MP * p.qd;
-    bf16_t* act = p.act + (int64_t)l * 2 * MP * p.ffn;
     WideEpi e{};
     e.ph = ph;
     if (sub == 0) {
-      e.out = qkv; e.ld = p.qkvd; e.ssq_in = p.ssq + (int64_t)(2 * l) * ssq_stride;
-      SSD_TRY((launch_wide_gemm<2, FE_QKV>(p, L.qkv, p.xn + (int64_t)(2 * l) * 2 * h_stride, e, s)));
+      e.out = p.qkv; e.ld = p.qkvd; e.ssq_in = p.ssq;
+      SSD_TRY((launch_wide_gemm<2, FE_QKV>(p, L.qkv, p.xn, e, s)));
     } else if (sub == 3 || sub == 5) {
-      const int v = sub == 3 ? 2 * l + 1 : 2 * l + 2;
-      e.h_in = p.h + (int64_t)(v - 1) * h_stride;
-      e.h_out = p.h + (int64_t)v * h_stride;
+      e.h_in = e.h_out = p.h;     // every element is read and rewritten by one lane
       e.gain = sub == 3 ? L.mlp_norm : (l + 1 < p.L ? layers_host[l + 1].attn_norm : p.final_norm);
-      e.xn_out = p.xn + (int64_t)v * 2 * h_stride;
-      e.ssq_out = p.ssq + (int64_t)v * ssq_stride;
-      SSD_TRY((launch_wide_gemm<2, FE_RESID>(p, sub == 3 ? L.o : L.down, sub == 3 ? att : act, e, s)));
+      e.xn_out = p.xn;
+      e.ssq_out = p.ssq;
+      SSD_TRY((launch_wide_gemm<2, FE_RESID>(p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s)));
     } else if (sub == 4) {
-      const int v = 2 * l + 1;
-      e.act_out = act; e.ssq_in = p.ssq + (int64_t)v * ssq_stride;
+      e.act_out = p.act; e.ssq_in = p.ssq;
       // one row group (up to 96 rows): a workgroup per unit of 4 feature tiles, the reduction dimension over its
       // wavefronts, instead of 16 feature tiles per workgroup on a quarter of the grid
       if (((p.M + 15) >> 4) <= kWideGroup && L.gu.n_units <= p.nwg) {
-        SSD_TRY((launch_wide_gemm<4, FE_SWIGLU>(p, L.gu, p.xn + (int64_t)v * 2 * h_stride, e, s)));
+        SSD_TRY((launch_wide_gemm<4, FE_SWIGLU>(p, L.gu, p.xn, e, s)));
       } else {
-        SSD_TRY((launch_wide_gemm_lds<FE_SWIGLU>(p, L.gu, p.xn + (int64_t)v * 2 * h_stride, e, s)));
+        SSD_TRY((launch_wide_gemm_lds<FE_SWIGLU>(p, L.gu, p.xn, e, s)));
       }
     } else {
       if (sub == 6 && p.logits) {
-        const int v = 2 * p.L;
-        e.out = p.logits; e.ld = p.logits_ld; e.ssq_in = p.ssq + (int64_t)v * ssq_stride;
-        SSD_TRY((launch_wide_gemm_lds<FE_LOGITS>(p, p.lm, p.xn + (int64_t)v * 2 * h_stride, e, s)));
+        e.out = p.logits; e.ld = p.logits_ld; e.ssq_in = p.ssq;
+        SSD_TRY((launch_wide_gemm_lds<FE_LOGITS>(p, p.lm, p.xn, e, s)));
       }
       if (sub == 6 && !p.hidden) continue;
       int grid = p.nwg;

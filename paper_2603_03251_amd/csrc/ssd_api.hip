@@ -5,9 +5,11 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -147,10 +149,12 @@ struct ssd_ctx {
   std::vector<int> blocks_of;            // blocks a sequence holds pages for
   std::vector<int> ub_of;                // host upper bound of trunk_len per sequence (trunk_ub = their maximum)
   int fused_mode = 0;
-  bool fused_wide = false;     // passes of up to kFusedWideRows rows through the wide kernel
-  int fused_cap = 0;           // rows of one pass: kFusedMaxRows or kFusedWideRows
+  bool fused_wide = false;     // rounds and extends run as wide passes (up to kFusedWideRows rows, one launch per phase)
+  bool wide_prefill = false;   // prompts are prefilled in wide passes (also in contexts whose rounds are narrow passes)
+  int fused_cap = 0;           // rows of one pass of a round: kFusedMaxRows or kFusedWideRows
   int vt_stride = 0;
-  FusedParams fp{};            // everything that does not change between passes
+  FusedParams fp{};            // everything that does not change between passes: of narrow passes,
+  FusedParams fpw{};           // of wide passes
   FusedLayer* fused_layers_dev = nullptr;
   std::vector<FusedLayer> fused_layers_host;   // the same tables in host memory (wide passes launch phase by phase)
   unsigned* fused_bar = nullptr;
@@ -158,8 +162,10 @@ struct ssd_ctx {
   hipEvent_t fused_done = nullptr;       // recorded behind every persistent launch of this context
   int flags = 0;
   int64_t fused_sync_words = 0; // barrier words, zeroed once (the barrier's epoch carries over from launch to launch)
-  int64_t part_entries = 0;    // per-layer capacity of the attention partial buffers, in query rows
-  int part_ns_max = 1;         // key splits they were sized for
+  struct PartCap {             // attention partial buffers: capacity (of a layer) in query rows, key splits they were sized for
+    int64_t entries = 0;
+    int ns_max = 1;
+  } part, part_wide;
   unsigned long long* phase_clocks = nullptr;
   const int32_t* forced_keys = nullptr;
   const int32_t* forced_tokens = nullptr;
@@ -420,9 +426,12 @@ void set_bounds(ssd_ctx* c, const int32_t* lens) {
 // whole sequences that fits kFusedMaxRows rows (one launch for the few-row workloads the kernel is built for; a batch
 // with more rows streams the weights once per group).
 // seq_base: the pass's rows belong to sequences seq_base, seq_base + 1, .. (rows, tokens and outputs are indexed from 0)
-int fused_forward(ssd_ctx* c, int M, const int32_t* tokens, int rows_per_seq, int max_vis, int branch_depth, float* logits,
+// wide: the pass runs as wide passes of up to kFusedWideRows rows.
+int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_per_seq, int max_vis, int branch_depth, float* logits,
                   int64_t logits_ld, float* hidden, int64_t hidden_ld, int seq_base, hipStream_t s) {
-  FusedParams p = c->fp;
+  FusedParams p = wide ? c->fpw : c->fp;
+  const ssd_ctx::PartCap& part = wide ? c->part_wide : c->part;
+  const int cap = wide ? kFusedWideRows : kFusedMaxRows;
   p.R = rows_per_seq;
   p.is_branch = branch_depth >= 0;
   p.suffix_len = branch_depth >= 0 ? branch_depth + 1 : 0;
@@ -432,18 +441,18 @@ int fused_forward(ssd_ctx* c, int M, const int32_t* tokens, int rows_per_seq, in
   p.SL = c->K + 1 <= 8 ? 8 : 16;
   const int p_ub = max_vis > 1 ? max_vis : 1;
   const int n_seq = M / rows_per_seq;
-  const int per_pass = c->fused_cap / rows_per_seq;
+  const int per_pass = cap / rows_per_seq;
   // Key splits of the stored trunk: the attention phase lasts (rounds of units over the grid) x (a unit's 32-key blocks
   // per wavefront + its fixed part), and more than one split adds a merge (a phase of its own in wide passes, the last
   // unit of a tile to arrive in narrow ones).  Costs in microseconds as measured
   // on the 1B shape; the choice only affects speed.
   {
     const int seqs = n_seq < per_pass ? n_seq : (per_pass > 0 ? per_pass : 1);
-    const int pairs = seqs * p.Hkv * (c->fused_wide ? (p.QT + kFusedWideQueryTiles - 1) / kFusedWideQueryTiles : p.QT);
+    const int pairs = seqs * p.Hkv * (wide ? (p.QT + kFusedWideQueryTiles - 1) / kFusedWideQueryTiles : p.QT);
     int best = 1;
     float best_cost = 0.f;
-    const int ns_cap = c->part_ns_max;                     // what the partial-softmax buffers were sized for
-    const float merge_cost = c->fused_wide ? 5.0f : 4.0f;  // a phase of its own / the last unit of a tile to arrive (its arrival
+    const int ns_cap = part.ns_max;                     // what the partial-softmax buffers were sized for
+    const float merge_cost = wide ? 5.0f : 4.0f;  // a phase of its own / the last unit of a tile to arrive (its arrival
                                                            // count and the other splits' partial results each cost a memory round trip)
     for (int ns = 1; ns <= ns_cap && ns <= 16; ++ns) {
       const int keys = (p_ub + ns - 1) / ns;
@@ -456,12 +465,13 @@ int fused_forward(ssd_ctx* c, int M, const int32_t* tokens, int rows_per_seq, in
     p.NS = (p_ub + p.KPU - 1) / p.KPU;
   }
   if (per_pass < 1 || n_seq * rows_per_seq != M) {
-    set_error("fused pass: %d rows of %d per sequence do not fit passes of %d rows", M, rows_per_seq, c->fused_cap);
+    set_error("fused pass: %d rows of %d per sequence do not fit passes of %d rows", M, rows_per_seq, cap);
     return SSD_ESTATE;
   }
-  const int last = (logits || hidden) ? fused_last_phase(p.L) : fused_last_phase(p.L) - 1;
+  // without outputs (a prefill) the pass ends where the last layer's keys and values are stored: its attention phase
+  const int last = (logits || hidden) ? fused_last_phase(p.L) : fused_last_phase(p.L) - 5;
   const bool timed = c->timing && branch_depth >= 0 && 2 * branch_depth + 1 < (int)c->kernel_events.size();
-  const bool persistent = c->fused_mode == 2;
+  const bool persistent = !wide && c->fused_mode == 2;
   std::unique_lock<std::mutex> serial(g_fused_mu, std::defer_lock);
   if (persistent) {
     serial.lock();
@@ -483,13 +493,13 @@ int fused_forward(ssd_ctx* c, int M, const int32_t* tokens, int rows_per_seq, in
     p.logits_ld = logits_ld;
     p.hidden = hidden ? hidden + row0 * hidden_ld : nullptr;
     p.hidden_ld = hidden_ld;
-    p.n_attn_units = p.B * p.Hkv * (c->fused_wide ? (p.QT + kFusedWideQueryTiles - 1) / kFusedWideQueryTiles : p.QT) * p.NS;
+    p.n_attn_units = p.B * p.Hkv * (wide ? (p.QT + kFusedWideQueryTiles - 1) / kFusedWideQueryTiles : p.QT) * p.NS;
     p.n_pair_units = (p.M * p.Hq + kFusedWaves - 1) / kFusedWaves;
-    if (p.NS > 1 && (int64_t)p.B * p.Hkv * p.NS * p.QT * 16 > c->part_entries) {
+    if (p.NS > 1 && (int64_t)p.B * p.Hkv * p.NS * p.QT * 16 > part.entries) {
       set_error("fused pass: attention partial buffer too small (%d splits, %d query tiles)", p.NS, p.QT);
       return SSD_ESTATE;
     }
-    if (c->fused_wide) SSD_TRY(launch_fused_wide(p, c->fused_layers_host.data() + (size_t)(seq_base + s0) * p.L, 0, last, s));
+    if (wide) SSD_TRY(launch_fused_wide(p, c->fused_layers_host.data() + (size_t)(seq_base + s0) * p.L, 0, last, s));
     else SSD_TRY(launch_fused(p, 0, last, persistent, s));
   }
   if (timed) SSD_HIP(hipEventRecord(c->kernel_events[2 * branch_depth + 1], s));
@@ -505,12 +515,13 @@ int fused_forward(ssd_ctx* c, int M, const int32_t* tokens, int rows_per_seq, in
 // One batched pass of the decoder over `M` rows whose descriptors and rotary tables are already in ctx->rows /
 // ctx->cos_sin.  Logits (fp32, row stride logits_ld) and final-norm hidden states are optional.
 // max_vis: host bound of the stored trunk positions any row sees; branch_depth: decode step of branch rows, -1 for an extend.
-int forward_rows(ssd_ctx* c, int M, const int32_t* tokens, int rows_per_seq, int max_vis, int branch_depth, float* logits,
+// wide: fused contexts run the pass as wide passes.
+int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_per_seq, int max_vis, int branch_depth, float* logits,
                  int64_t logits_ld, float* hidden, int64_t hidden_ld, int seq_base, hipStream_t s) {
   const ssd_model* m = c->model;
   const Dims& d = m->dims;
   if (c->fused_mode)
-    return fused_forward(c, M, tokens, rows_per_seq, max_vis, branch_depth, logits, logits_ld, hidden, hidden_ld, seq_base, s);
+    return fused_forward(c, wide, M, tokens, rows_per_seq, max_vis, branch_depth, logits, logits_ld, hidden, hidden_ld, seq_base, s);
   const int dt = d.dtype;
   const int64_t R = c->max_rows;     // plane stride of an activation buffer = R * columns
   SSD_TRY(launch_embed(dt, m->embed, tokens, c->h, M, d.d_model, d.vocab, s));
@@ -546,13 +557,48 @@ int forward_rows(ssd_ctx* c, int M, const int32_t* tokens, int rows_per_seq, int
 }
 
 // Extend of sequences [b0, b0 + nb): tokens [nb][T], outputs [nb][T][..]
-int extend_rows(ssd_ctx* c, const int32_t* tokens, int T, int offset, float* logits, float* hidden, int b0, int nb, hipStream_t s) {
+int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset, float* logits, float* hidden, int b0, int nb, hipStream_t s) {
   const Dims& d = c->model->dims;
   SSD_TRY(pages_for_pass(c, b0, nb, offset + T, s));
   SSD_TRY(launch_setup_extend_rows(c->rows, c->cos_sin, c->trunk_len, nb, T, offset, d.head_dim / 2, d.rope_theta, b0, s));
   int ub = 0;
   for (int b = b0; b < b0 + nb; ++b) ub = c->ub_of[b] > ub ? c->ub_of[b] : ub;
-  return forward_rows(c, nb * T, tokens, T, ub + offset, -1, logits, d.vocab, hidden, d.d_model, b0, s);
+  return forward_rows(c, wide, nb * T, tokens, T, ub + offset, -1, logits, d.vocab, hidden, d.d_model, b0, s);
+}
+
+// KV of positions 0 .. max(len)-1 of sequences [b0, b0 + nb) (their trunk_len is 0): extend passes over d_tokens
+// [nb][stride].  In contexts that prefill in wide passes a pass takes as many tokens of a sequence as a wide pass has room
+// for, and several sequences where their prompts are short: a pass streams every weight once, so what a prompt costs is its
+// number of passes (a 1020-token prompt of the 1B shape: 6 passes of 170 rows instead of 170 passes of K+1 = 6 rows).
+// Otherwise chunks of K+1 tokens of all sequences.
+int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t* lens, int b0, int nb, hipStream_t s) {
+  const int K1 = c->K + 1;
+  for (int g0 = 0, gn = 0; g0 < nb; g0 += gn) {
+    int max_len = 0, T = K1;
+    gn = nb;
+    if (c->wide_prefill) {
+      // a group: the next sequences that fit one pass with the whole chunk of each
+      T = 0;
+      for (gn = 0; g0 + gn < nb; ++gn) {
+        const int want = std::max(T, std::min<int>(lens[g0 + gn], kFusedWideFreshKeys));
+        if (gn > 0 && want * (gn + 1) > kFusedWideRows) break;
+        T = want;
+      }
+    }
+    for (int b = g0; b < g0 + gn; ++b) max_len = std::max<int>(max_len, lens[b]);
+    if (c->wide_prefill) {
+      const int chunks = (max_len + T - 1) / T;       // of equal size: a short last chunk would cost as much as a full one
+      T = (max_len + chunks - 1) / chunks;
+    }
+    for (int start = 0; start < max_len; start += T) {
+      const int Tn = c->wide_prefill ? std::min(T, max_len - start) : T;
+      const int n = gn * Tn;
+      gather_chunk_tokens_kernel<<<(n + 255) / 256, 256, 0, s>>>(c->step_tokens, d_tokens + (int64_t)g0 * stride, stride, gn, Tn, start);
+      SSD_HIP(hipGetLastError());
+      SSD_TRY(extend_rows(c, c->fused_wide || c->wide_prefill, c->step_tokens, Tn, start, nullptr, nullptr, b0 + g0, gn, s));
+    }
+  }
+  return SSD_OK;
 }
 
 // Workspace and constant parameters of the fused pass.
@@ -573,26 +619,28 @@ int fused_setup(ssd_ctx* c) {
   p.max_trunk = c->max_trunk;
   p.vt_stride = c->vt_stride;
   p.suffix_cap = c->K;
-  const size_t MPr = (size_t)c->fused_cap;
+  // ---- narrow passes: every exchange buffer once per (layer, phase), written at most once per launch
+  const size_t MPr = c->fused_wide ? 0 : (size_t)kFusedMaxRows;
   const size_t nv = 2 * (size_t)L + 1;
   int st = SSD_OK;
-  auto A = [&](void** q, size_t bytes) { if (st == SSD_OK) st = c->arena.alloc(q, bytes); };
+  auto A = [&](void** q, size_t bytes) { if (st == SSD_OK && bytes) st = c->arena.alloc(q, bytes); };
   A((void**)&p.h, nv * MPr * p.d * 4);
   A((void**)&p.xn, nv * 2 * MPr * p.d * 2);
   A((void**)&p.ssq, nv * (p.d / 16) * MPr * 4);
   A((void**)&p.qkv, (size_t)L * MPr * p.qkvd * 4);
   A((void**)&p.att, (size_t)L * 2 * MPr * p.qd * 2);
   A((void**)&p.act, (size_t)L * 2 * MPr * p.ffn * 2);
-  // attention partials (used only when the trunk is split over several units: more than 2048 visible keys)
+  // attention partials (used only when the trunk is split over several units)
   const int r_max = c->rows_per_seq > c->K + 1 ? c->rows_per_seq : c->K + 1;
   const int qt_max = (r_max * p.G + 15) / 16;
-  // narrow passes split shorter trunks too (their units merge the splits themselves, at no barrier)
-  const int ns_max = c->fused_wide ? (c->max_trunk + 2047) / 2048 + 1 : std::max((c->max_trunk + 2047) / 2048 + 1, 8);
-  c->part_ns_max = ns_max;
-  c->part_entries = (int64_t)p.B * p.Hkv * ns_max * qt_max * 16;
-  p.part_layer_stride = c->part_entries;
-  A((void**)&p.part_o, (size_t)L * c->part_entries * 64 * 4);
-  A((void**)&p.part_ml, (size_t)L * c->part_entries * 2 * 4);
+  if (!c->fused_wide) {
+    // narrow passes split short trunks too (their units merge the splits themselves, at no barrier)
+    c->part.ns_max = std::max((c->max_trunk + 2047) / 2048 + 1, 8);
+    c->part.entries = (int64_t)p.B * p.Hkv * c->part.ns_max * qt_max * 16;
+    p.part_layer_stride = c->part.entries;
+    A((void**)&p.part_o, (size_t)L * c->part.entries * 64 * 4);
+    A((void**)&p.part_ml, (size_t)L * c->part.entries * 2 * 4);
+  }
   p.arrivals_stride = (int64_t)p.B * p.Hkv * qt_max;
   A((void**)&p.arrivals, (size_t)L * p.arrivals_stride * 4);
   A((void**)&p.qkv_flags, (size_t)L * 128 * 4);
@@ -669,6 +717,34 @@ int fused_setup(ssd_ctx* c) {
   }
   SSD_HIP(hipMemcpy(c->fused_layers_dev, host.data(), sizeof(FusedLayer) * host.size(), hipMemcpyHostToDevice));
   p.layers = c->fused_layers_dev;
+  // ---- wide passes: one launch per phase, so one set of exchange buffers serves all layers (and stays in the caches)
+  if (c->fused_wide || c->wide_prefill) {
+    FusedParams& w = c->fpw;
+    w = p;
+    const size_t MW = (size_t)kFusedWideRows;
+    // query rows of a pass: whole 16-row tiles per sequence
+    c->part_wide.ns_max = (c->max_trunk + 2047) / 2048 + 1;
+    c->part_wide.entries = (int64_t)p.Hkv * c->part_wide.ns_max * (kFusedWideRows * p.G + 16 * std::min(c->B, kFusedWideRows));
+    // one allocation, carved up
+    char* base = nullptr;
+    size_t used = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+      used = 0;
+      auto carve = [&](auto** q, size_t bytes) {
+        if (pass) *q = (std::remove_reference_t<decltype(*q)>)(base + used);
+        used += (bytes + 255) & ~(size_t)255;
+      };
+      carve(&w.h, MW * p.d * 4);
+      carve(&w.xn, MW * p.d * 2);
+      carve(&w.ssq, (size_t)(p.d / 64) * MW * 4);
+      carve(&w.qkv, MW * p.qkvd * 4);
+      carve(&w.att, MW * p.qd * 2);
+      carve(&w.act, MW * p.ffn * 2);
+      carve(&w.part_o, (size_t)c->part_wide.entries * 64 * 4);
+      carve(&w.part_ml, (size_t)c->part_wide.entries * 2 * 4);
+      if (!pass) SSD_TRY(c->arena.alloc((void**)&base, used));
+    }
+  }
   return SSD_OK;
 }
 
@@ -790,7 +866,6 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
   c->max_rows = c->M > c->B * (c->K + 1) ? c->M : c->B * (c->K + 1);
   const size_t es = elem_size(d.dtype);
   const size_t kvd = (size_t)d.kv_dim();
-  const int R = c->max_rows;
   int st = SSD_OK;
   auto A = [&](void** p, size_t bytes) { if (st == SSD_OK) st = c->arena.alloc(p, bytes); };
   A((void**)&c->trunk_len, sizeof(int32_t) * c->B);
@@ -816,7 +891,12 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
     } else if (narrow_ok) {
       c->fused_mode = (cfg->flags & SSD_CTX_FUSED_PHASES) ? 1 : 2;
     }
+    // (wide passes carry one fp16 plane per activation: not where the configuration asks for two)
+    c->wide_prefill = c->fused_mode != 0 && model->wide_ok && attn_ok &&
+                      !(cfg->flags & (SSD_CTX_NARROW_PASSES | SSD_CTX_TWO_PLANES | SSD_CTX_ONE_PLANE_ALL));
+    if (c->wide_prefill) c->max_rows = std::max(c->max_rows, kFusedWideRows);
   }
+  const int R = c->max_rows;
   if (!c->fused_mode) {
     if (!model->operator_weights) {
       set_error("this context would run the per-operator kernels (flags, or a shape the fused passes do not take), whose "
@@ -878,16 +958,18 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
   A((void**)&c->cos_sin, sizeof(float) * (size_t)R * d.head_dim);
   A((void**)&c->step_tokens, sizeof(int32_t) * R);
   A((void**)&c->exclude, sizeof(int32_t) * c->B * (c->K + 1));
-  A((void**)&c->h, sizeof(float) * (size_t)R * d.d_model);
-  A(&c->xn, sizeof(float) * (size_t)R * d.d_model);
-  A((void**)&c->qkv, sizeof(float) * (size_t)R * d.qkv_dim());
-  A((void**)&c->q, sizeof(float) * (size_t)R * d.q_dim());
-  A(&c->attn_out, sizeof(float) * (size_t)R * d.q_dim());
-  A(&c->act, sizeof(float) * (size_t)R * d.d_ffn);
-  c->attn_partial_floats = attention_partial_floats(R, d.n_q_heads, d.head_dim, c->max_trunk + c->K);
-  A((void**)&c->attn_partial, (size_t)c->attn_partial_floats * sizeof(float));
+  if (!c->fused_mode) {   // exchange buffers of the per-operator kernels (fused contexts: fused_setup)
+    A((void**)&c->h, sizeof(float) * (size_t)R * d.d_model);
+    A(&c->xn, sizeof(float) * (size_t)R * d.d_model);
+    A((void**)&c->qkv, sizeof(float) * (size_t)R * d.qkv_dim());
+    A((void**)&c->q, sizeof(float) * (size_t)R * d.q_dim());
+    A(&c->attn_out, sizeof(float) * (size_t)R * d.q_dim());
+    A(&c->act, sizeof(float) * (size_t)R * d.d_ffn);
+    c->attn_partial_floats = attention_partial_floats(R, d.n_q_heads, d.head_dim, c->max_trunk + c->K);
+    A((void**)&c->attn_partial, (size_t)c->attn_partial_floats * sizeof(float));
+  }
   A(&c->sample_scratch, sample_scratch_bytes(c->M));
-  A(&c->top_f_scratch, top_f_scratch_bytes(R));
+  A(&c->top_f_scratch, top_f_scratch_bytes(std::max(c->M, c->B * (c->K + 1))));
   A((void**)&c->sigma_ids, sizeof(int32_t) * (size_t)c->M * c->F);
   if (st == SSD_OK && c->fused_mode) st = fused_setup(c);
   if (st == SSD_OK) {
@@ -1000,7 +1082,6 @@ int ssd_ctx_prefill(ssd_ctx* c, const int32_t* d_tokens, int32_t stride, const i
   SSD_CHECK_ARG(max_len + 2 * c->K + 2 <= c->max_trunk, "prefill of %d tokens does not leave room for a round (max_trunk %d)",
                 max_len, c->max_trunk);
   SSD_TRY(launch_fill_i32(c->trunk_len, 0, c->B, s));
-  const int T = c->K + 1;
   {
     std::vector<int32_t> zero(c->B, 0);
     set_bounds(c, zero.data());
@@ -1010,12 +1091,7 @@ int ssd_ctx_prefill(ssd_ctx* c, const int32_t* d_tokens, int32_t stride, const i
       for (int b = 0; b < c->B; ++b) pages_release_beyond(c, b, 0, &dirty);
     }
   }
-  for (int start = 0; start < max_len; start += T) {
-    int n = c->B * T;
-    gather_chunk_tokens_kernel<<<(n + 255) / 256, 256, 0, s>>>(c->step_tokens, d_tokens, stride, c->B, T, start);
-    SSD_HIP(hipGetLastError());
-    SSD_TRY(extend_rows(c, c->step_tokens, T, start, nullptr, nullptr, 0, c->B, s));
-  }
+  SSD_TRY(prefill_rows(c, d_tokens, stride, h_lens, 0, c->B, s));
   SSD_HIP(hipMemcpyAsync(c->trunk_len, h_lens, sizeof(int32_t) * c->B, hipMemcpyHostToDevice, s));
   SSD_HIP(hipStreamSynchronize(s));   // h_lens is caller-owned pageable memory
   set_bounds(c, h_lens);
@@ -1043,12 +1119,7 @@ int ssd_ctx_prefill_sequence(ssd_ctx* c, int32_t b, const int32_t* d_tokens, int
   }
   SSD_TRY(launch_fill_i32(c->trunk_len + b, 0, 1, s));
   c->ub_of[b] = 0;
-  const int T = c->K + 1;
-  for (int start = 0; start < len; start += T) {
-    gather_chunk_tokens_kernel<<<1, 256, 0, s>>>(c->step_tokens, d_tokens, len, 1, T, start);
-    SSD_HIP(hipGetLastError());
-    SSD_TRY(extend_rows(c, c->step_tokens, T, start, nullptr, nullptr, b, 1, s));
-  }
+  SSD_TRY(prefill_rows(c, d_tokens, len, &len, b, 1, s));
   SSD_TRY(launch_fill_i32(c->trunk_len + b, len, 1, s));
   c->ub_of[b] = len;
   if (c->kv_pages) {
@@ -1184,7 +1255,7 @@ int ssd_ctx_extend(ssd_ctx* c, const int32_t* d_tokens, int32_t T, int32_t offse
     set_error("extend would pass max_trunk (%d + %d + %d > %d)", c->trunk_ub, offset, T, c->max_trunk);
     return SSD_ESTATE;
   }
-  return extend_rows(c, d_tokens, T, offset, d_logits, nullptr, 0, c->B, (hipStream_t)stream);
+  return extend_rows(c, c->fused_wide, d_tokens, T, offset, d_logits, nullptr, 0, c->B, (hipStream_t)stream);
 }
 
 int ssd_prespeculate(ssd_ctx* c, const int32_t* d_pending, const float* d_temperature, uint64_t round_seed, void* stream) {
@@ -1207,7 +1278,7 @@ int ssd_prespeculate(ssd_ctx* c, const int32_t* d_pending, const float* d_temper
   };
   SSD_TRY(mark());
   // a0: glue extend of {last verified token, s_1..s_K}
-  SSD_TRY(extend_rows(c, d_pending, K + 1, 0, c->glue_logits, c->glue_hidden, 0, B, s));
+  SSD_TRY(extend_rows(c, c->fused_wide, d_pending, K + 1, 0, c->glue_logits, c->glue_hidden, 0, B, s));
   SSD_TRY(mark());
   // a1: fan-out
   SSD_TRY(launch_pending_exclude(c->exclude, d_pending, B, K, s));
@@ -1217,7 +1288,7 @@ int ssd_prespeculate(ssd_ctx* c, const int32_t* d_pending, const float* d_temper
   for (int i = 0; i < K; ++i) {
     SSD_TRY(launch_setup_branch_rows(c->rows, c->cos_sin, c->trunk_len, B, K, c->fan, i, d.head_dim / 2, d.rope_theta, c->step_tokens,
                                      c->keys, c->tokens, c->forced_keys, c->forced_tokens, s));
-    SSD_TRY(forward_rows(c, M, c->step_tokens, RB, c->trunk_ub + K + 1, i, c->logits + (size_t)i * V, (int64_t)K * V,
+    SSD_TRY(forward_rows(c, c->fused_wide, M, c->step_tokens, RB, c->trunk_ub + K + 1, i, c->logits + (size_t)i * V, (int64_t)K * V,
                          c->hidden + (size_t)i * d.d_model, (int64_t)K * d.d_model, 0, s));
     if (c->saguaro_c < 1.0f) {
       // sigma_{F,C}: lower the step's own top-F logits before the draw; the cache keeps the lowered logits, the
@@ -1338,7 +1409,7 @@ int ssd_ctx_enable_phase_clocks(ssd_ctx* c, int32_t on) {
     SSD_TRY(c->arena.alloc((void**)&c->phase_clocks, n * sizeof(unsigned long long)));
     SSD_HIP(hipMemset(c->phase_clocks, 0, n * sizeof(unsigned long long)));
   }
-  c->fp.prof = on ? c->phase_clocks : nullptr;
+  c->fp.prof = c->fpw.prof = on ? c->phase_clocks : nullptr;
   return SSD_OK;
 }
 

@@ -1,0 +1,95 @@
+"""Prompts prefilled in wide passes (many tokens of a sequence per pass) against the same prompts prefilled in chunks of K+1
+tokens through narrow passes, and against the float64 oracle.  Sizes: one token, one chunk, the edges of what a pass takes of a
+sequence, several passes, several short prompts in one pass."""
+import numpy as np
+import pytest
+import torch
+
+import ssd_inputs as I
+from oracle import ssd_oracle as O
+from tests.gpu_util import TOL_BF16_OWN_PREFILL, dev_f32, dev_i32, row_rel_err
+
+pytestmark = pytest.mark.gpu
+
+SHAPE = I.ModelShape(n_layers=2, d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=64, d_ffn=1024, vocab=4112, dtype="bf16",
+                     rope_theta=500000.0, tie_embeddings=True)
+K, F = 3, 2
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2603_03251_amd import binding
+    return binding
+
+
+def _trunk(B, ctx, lens, max_trunk):
+    """Keys and values of the verified positions, [layer][sequence] arrays [len][Hkv][64]."""
+    v = B.ssd_ctx_views(ctx)
+    T, hkv = (max_trunk + 63) // 64 * 64, SHAPE.n_kv_heads
+    ks, vs = [], []
+    for l in range(SHAPE.n_layers):
+        k = B.device_copy(v.h_trunk_k[l], (len(lens), hkv, T, 64), torch.bfloat16).float().cpu().numpy()
+        vt = B.device_copy(v.h_trunk_v[l], (len(lens), hkv, T // 32, 64, 32), torch.bfloat16).float().cpu().numpy()
+        vt = vt.transpose(0, 1, 2, 4, 3).reshape(len(lens), hkv, T, 64)
+        ks.append([k[b, :, :n].transpose(1, 0, 2) for b, n in enumerate(lens)])
+        vs.append([vt[b, :, :n].transpose(1, 0, 2) for b, n in enumerate(lens)])
+    return ks, vs
+
+
+@pytest.mark.parametrize("lens", [[1], [6], [191], [192], [193], [385], [700], [40, 300, 7], [33] * 15],
+                         ids=lambda x: "-".join(map(str, x[:3])) + ("x%d" % len(x) if len(x) > 3 else ""))
+def test_wide_prefill_equals_narrow_chunks(B, lens):
+    nb, max_trunk, seed = len(lens), max(lens) + 2 * K + 8, 7 + sum(lens)
+    print(f"[case] prefill of {lens}", flush=True)
+    model = B.ssd_model_create(SHAPE, I.make_weights(SHAPE, 11))
+    prompt = dev_i32(I.make_prompt(SHAPE, nb, max(lens), seed))
+    pending, temps = dev_i32(I.make_pending(SHAPE, nb, K, seed)), dev_f32(np.zeros(nb))
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
+    try:
+        got = []
+        for ctx in ctxs:
+            B.ssd_ctx_prefill(ctx, prompt, lens)
+            kv = _trunk(B, ctx, lens, max_trunk)
+            B.ssd_prespeculate(ctx, pending, temps, 1)
+            got.append((kv, B.read_cache(ctx)["glue_logits"].cpu().numpy()))
+        # each side is within TOL_BF16_OWN_PREFILL of the exact keys, values and logits
+        for part in (0, 1):
+            for l in range(SHAPE.n_layers):
+                for b in range(nb):
+                    assert row_rel_err(got[0][0][part][l][b], got[1][0][part][l][b]) < 2 * TOL_BF16_OWN_PREFILL, (part, l, b)
+        assert row_rel_err(got[0][1], got[1][1]) < 2 * TOL_BF16_OWN_PREFILL
+        # one slot prefilled alone gives what it gets beside the others
+        b = nb - 1
+        B.ssd_ctx_prefill_sequence(ctxs[0], b, prompt[b, :lens[b]].contiguous())
+        again = _trunk(B, ctxs[0], lens, max_trunk)
+        for part in (0, 1):
+            for l in range(SHAPE.n_layers):
+                assert row_rel_err(again[part][l][b], got[0][0][part][l][b]) < 2 * TOL_BF16_OWN_PREFILL
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
+@pytest.mark.parametrize("pages", [0, 16])
+def test_wide_prefill_against_the_oracle(B, pages):
+    lens, max_trunk, seed = [210, 60], 240, 5
+    w = I.make_weights(SHAPE, seed)
+    om = O.Model.from_weights(SHAPE, w)
+    model = B.ssd_model_create(SHAPE, w)
+    prompt = I.make_prompt(SHAPE, 2, max(lens), seed)
+    pending = I.make_pending(SHAPE, 2, K, seed)
+    ctx = B.ssd_ctx_create(model, 2, K, F, max_trunk, 0, pages)
+    try:
+        B.ssd_ctx_prefill(ctx, dev_i32(prompt), lens)
+        B.ssd_prespeculate(ctx, dev_i32(pending), dev_f32(np.zeros(2)), 1)
+        got = B.read_cache(ctx)["glue_logits"].cpu().numpy()
+        for b, n in enumerate(lens):
+            _, trunk = O.prefill(om, prompt[b, :n])
+            want, _, _ = O.glue_extend(om, trunk, pending[b])
+            err = row_rel_err(got[b], want)
+            print(f"[parity] prefill of {n} tokens, glue logits {err:.2e}", flush=True)
+            assert err < TOL_BF16_OWN_PREFILL
+    finally:
+        B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
