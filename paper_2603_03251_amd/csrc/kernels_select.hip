@@ -167,16 +167,6 @@ __device__ __forceinline__ ScoreId block_argmax(ScoreId v, ScoreId* smem) {
   __syncthreads();
   return r;
 }
-__device__ __forceinline__ double block_sum_f64(double v, double* smem) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (lane == 0) smem[wave] = v;
-  __syncthreads();
-  double r = 0.0;
-  for (int i = 0; i < kSelWaves; ++i) r += smem[i];
-  __syncthreads();
-  return r;
-}
 __device__ __forceinline__ double score_of(float z) { return z != z ? -INFINITY : (double)z; }
 
 // Branch sampler: greedy argmax or Gumbel-max sample of softmax(z / T).  grid = (rows, parts): a block scans one
@@ -291,246 +281,327 @@ __global__ __launch_bounds__(64) void sample_merge_kernel(const ScoreId* __restr
   if (threadIdx.x == 0) out[(int64_t)row * out_stride] = best.id;
 }
 
-struct RowStats {
-  double max;     // max of the row's logits
-  double sum;     // sum exp((z - max)/T), T > 0 only
-  int32_t argmax;
-  int32_t pad;
+// ---- lossless verification (Sec. 2.1) in two launches.  What bounds a verification is not its bytes (11 rows of 128256 logits
+// are 5.6 MB) but the chain of dependent passes: maximum of a row -> softmax denominator -> accept decisions -> residual mass
+// -> bonus token, five kernels of 4 to 20 us each when every pass is a launch that re-reads and re-merges the one before.
+// Here a row is read once for maximum and denominator together (a running maximum per thread, the partial sums rescaled when
+// they meet), and the second kernel does everything behind them: every block merges the rows' partial results for itself,
+// decides, and scores its share of the bonus row for the residual; the block of a sequence that finishes last merges the
+// shares.  A row and the bonus row are shared among `parts` blocks, so that the few rows of one verification occupy the chip;
+// partial results are merged in a fixed order (the result does not depend on timing).  Measured (V = 128256, K = 5,
+// temperature 1): B = 1 55.0 -> 18.6 us a call (rows 7.2, decisions 12.3: six dependent memory round trips and three
+// reductions), B = 16 half of it greedy 104.9 -> 48.6 us (28.6 + 24.4).
+constexpr int kVerifyBlock = 256, kVerifyWaves = kVerifyBlock / 64;
+constexpr int kVerifyMaxParts = 32;     // blocks that share a row (one lane of a wavefront merges one of them)
+constexpr int kVerifyMaxBonusParts = 64;
+struct VerifyPart {       // one part of a row: best logit and its token, sum exp((z - max) / T) relative to that logit
+  float max;
+  int32_t id;
+  double sum;
 };
-
-// ---- lossless verification (Sec. 2.1).  Every pass over a row of logits is shared among `parts` blocks, so that
-// the few rows of one verification occupy the whole chip; partial results meet in the workspace and are merged in a
-// fixed order (the result does not depend on timing).
-constexpr int kVerifyMaxParts = 32;
+struct VerifyCand {       // one part of the bonus row: best candidate of the exponential race, residual mass
+  uint64_t score, id, mass;
+};
 struct VerifyWs {
-  RowStats* stats;        // [B (2K+1)]: target rows 0..K, then draft rows 0..K-1 of each sequence
-  ScoreId* part_best;     // [rows][parts]
-  double* part_sum;       // [rows][parts]
-  double* part_mass;      // [B][parts]  residual mass of the bonus position
-  ScoreId* part_bonus;    // [B][parts]
-  int32_t* accept;        // [B]
+  VerifyPart* part;       // [B rows_per_seq][parts]: target rows 0..K, then draft rows 0..K-1 of each sequence
+  VerifyCand* cand;       // [B][kVerifyMaxBonusParts]
+  uint32_t* done;         // [B] blocks of the second kernel that have stored their candidate
 };
-__host__ __device__ inline size_t verify_ws_align(size_t x) { return (x + 15) & ~(size_t)15; }
 __host__ inline VerifyWs verify_ws_carve(void* base, int B, int K) {
   const size_t rows = (size_t)B * (2 * K + 1);
   char* p = (char*)base;
   VerifyWs w;
-  w.stats = (RowStats*)p;      p += verify_ws_align(rows * sizeof(RowStats));
-  w.part_best = (ScoreId*)p;   p += verify_ws_align(rows * kVerifyMaxParts * sizeof(ScoreId));
-  w.part_sum = (double*)p;     p += verify_ws_align(rows * kVerifyMaxParts * sizeof(double));
-  w.part_mass = (double*)p;    p += verify_ws_align((size_t)B * kVerifyMaxParts * sizeof(double));
-  w.part_bonus = (ScoreId*)p;  p += verify_ws_align((size_t)B * kVerifyMaxParts * sizeof(ScoreId));
-  w.accept = (int32_t*)p;
+  w.part = (VerifyPart*)p;   p += rows * kVerifyMaxParts * sizeof(VerifyPart);
+  w.cand = (VerifyCand*)p;   p += (size_t)B * kVerifyMaxBonusParts * sizeof(VerifyCand);
+  w.done = (uint32_t*)p;
   return w;
 }
 
-// the logit row of workspace row r of sequence b (nullptr: a draft row of a greedy sequence, nothing to do)
-__device__ __forceinline__ const float* verify_row(const float* zt, const float* zd, int b, int r, int K, int V, double T) {
-  if (r <= K) return zt + ((int64_t)b * (K + 1) + r) * V;
-  if (T <= 0.0) return nullptr;
-  return zd + ((int64_t)b * K + (r - K - 1)) * V;
-}
 // this block's share [lo, hi) of a vocabulary of V tokens
 __device__ __forceinline__ void verify_share(int V, int& lo, int& hi) {
   const int chunk = (V + (int)gridDim.y - 1) / (int)gridDim.y;
   lo = (int)blockIdx.y * chunk;
   hi = lo + chunk < V ? lo + chunk : V;
 }
+__device__ __forceinline__ bool better_logit(float v, int t, float m, int id) { return v > m || (v == m && t < id); }
+// exp((x - m) / T) of scores where -infinity is "no probability" (also against a maximum of -infinity), in fp64 to about an ulp.
+// A verification evaluates one exponential per logit and two per token of the bonus row.  Table-driven after P. T. P. Tang, "Table-driven implementation of the
+// exponential function in IEEE floating-point arithmetic" (1989): with n = round(32 a / ln 2), a = n ln 2 / 32 + r, |r| <=
+// ln 2 / 64, exp(a) = 2^(n >> 5) 2^((n & 31) / 32) (1 + r + .. + r^6 / 720) (next term 4e-18): 19 instructions, none of them a
+// conversion or ldexp (a batch of 16 50.7 -> 48.6 us against the library's exp).  No branch, so that several run side by side.
+__device__ __forceinline__ void exp_table_init(double* table) {
+  if (threadIdx.x < 32) table[threadIdx.x] = exp2((double)threadIdx.x * (1.0 / 32.0));
+}
+__device__ __forceinline__ double exp_rel(float x, float m, double inv_t, const double* table) {
+  constexpr double kMagic = 6755399441055744.0;            // 1.5 2^52: adding it leaves round(a 32 / ln 2) in the low bits
+  constexpr double kLn2 = 0.693147180559945309417232121458;
+  constexpr double kStepHi = (float)(kLn2 / 32.0);         // 24 bits: n kStepHi is exact
+  constexpr double kStepLo = kLn2 / 32.0 - kStepHi;
+  const double a = ((double)x - (double)m) * inv_t;
+  const double biased = fma(a, 32.0 / kLn2, kMagic);
+  const int n = (int)(uint32_t)__double_as_longlong(biased);
+  const double nd = biased - kMagic;
+  const double r = fma(nd, -kStepLo, fma(nd, -kStepHi, a));
+  double q = fma(r, 1.0 / 720.0, 1.0 / 120.0);
+  q = fma(r, q, 1.0 / 24.0);
+  q = fma(r, q, 1.0 / 6.0);
+  q = fma(r, q, 0.5);
+  q = fma(r, q, 1.0);
+  const double t = table[n & 31];
+  const double y = fma(t * r, q, t);                       // in [1, 2] (1 + 2^-6)
+  const double scaled = __hiloint2double(__double2hiint(y) + ((n >> 5) << 20), __double2loint(y));
+  // below e^-700 (and for "no probability"): 0; NaN (an infinite maximum) stays NaN
+  return x == -INFINITY || a < -700.0 ? 0.0 : (a == a ? scaled : a);
+}
+__device__ __forceinline__ float logit_score(float z) { return z != z ? -INFINITY : z; }
 
-// Pass 1: per logit row and part, the best (logit, token).  grid (B (2K+1), parts).
-__global__ __launch_bounds__(kSelBlock) void verify_max_kernel(const float* __restrict__ zt, const float* __restrict__ zd,
-                                                               const float* __restrict__ temperature, int K, int V,
-                                                               VerifyWs ws) {
-  __shared__ ScoreId smem[kSelWaves];
-  const int b = blockIdx.x / (2 * K + 1), r = blockIdx.x % (2 * K + 1);
-  const double T = zd ? (double)temperature[b] : 0.0;   // without draft logits every sequence is greedy
-  const float* z = verify_row(zt, zd, b, r, K, V, T);
-  if (!z) return;
+// max(ep / sum_p - eq / sum_q, 0) without contraction: where p and q are equal the two products must round alike and cancel
+// exactly (a fused multiply-add would leave a residue of 1e-17 of the mass and draw the token from rounding noise)
+__device__ __forceinline__ double residual_of(double ep, double pinv, double eq, double qinv) {
+#pragma clang fp contract(off)
+  const double p = ep * pinv, q = eq * qinv;
+  return fmax(p - q, 0.0);
+}
+
+// (best logit, its token, sum relative to it) over groups of W lanes; every lane returns its group's result
+template <int W>
+__device__ __forceinline__ VerifyPart lanes_merge(VerifyPart v, double inv_t, bool sampled, const double* table) {
+  const float own = v.max;
+#pragma unroll
+  for (int o = W / 2; o > 0; o >>= 1) {
+    const float m = __shfl_xor(v.max, o);
+    const int id = __shfl_xor(v.id, o);
+    if (better_logit(m, id, v.max, v.id)) { v.max = m; v.id = id; }
+  }
+  if (sampled) {
+    v.sum *= exp_rel(own, v.max, inv_t, table);
+#pragma unroll
+    for (int o = W / 2; o > 0; o >>= 1) v.sum += __shfl_xor(v.sum, o);
+  }
+  return v;
+}
+
+// Kernel 1: per logit row and part, the best (logit, token) and the partial softmax denominator.  grid (B rows_per_seq, parts);
+// rows_per_seq = 2K+1, or K+1 without draft logits (then every sequence is greedy).
+__global__ __launch_bounds__(kVerifyBlock) void verify_rows_kernel(const float* __restrict__ zt, const float* __restrict__ zd,
+                                                                   const float* __restrict__ temperature, int K, int V,
+                                                                   int rows_per_seq, VerifyWs ws) {
+  constexpr int U = 16;   // loads in flight per thread
+  __shared__ VerifyPart wave_part[kVerifyWaves];
+  __shared__ double table[32];
+  const int b = blockIdx.x / rows_per_seq, r = blockIdx.x % rows_per_seq;
+  if (r == 0 && blockIdx.y == 0 && threadIdx.x == 0) ws.done[b] = 0;    // for the next kernel
+  const double T = zd ? (double)temperature[b] : 0.0;
+  const bool sampled = T > 0.0;
+  if (r > K && !sampled) return;                                        // a draft row of a greedy sequence
+  const float* z = r <= K ? zt + ((int64_t)b * (K + 1) + r) * V : zd + ((int64_t)b * K + (r - K - 1)) * V;
+  const double inv_t = sampled ? 1.0 / T : 0.0;
+  if (sampled) {
+    exp_table_init(table);
+    __syncthreads();
+  }
   int lo, hi;
   verify_share(V, lo, hi);
-  ScoreId best = {-INFINITY, 0x7fffffff};
-  constexpr int U = 8;   // loads in flight per thread
-  for (int t0 = lo + threadIdx.x; t0 < hi; t0 += kSelBlock * U) {
+  VerifyPart best = {-INFINITY, 0x7fffffff, 0.0};
+  for (int t0 = lo + threadIdx.x; t0 < hi; t0 += kVerifyBlock * U) {
     float v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * kSelBlock;
+      const int t = t0 + u * kVerifyBlock;
       v[u] = z[t < hi ? t : t0];
     }
+    // (a thread's tokens come in rising order: an equal logit later on does not replace the one found first)
+    const float before = best.max;
+    float top = -INFINITY;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * kSelBlock;
-      ScoreId c = {score_of(v[u]), t};
-      if (t < hi && better(c, best)) best = c;
+      v[u] = t0 + u * kVerifyBlock < hi ? logit_score(v[u]) : -INFINITY;
+      top = fmaxf(top, v[u]);
+    }
+    if (top > before || best.id == 0x7fffffff) {
+      best.max = top;
+#pragma unroll
+      for (int u = U - 1; u >= 0; --u) best.id = v[u] == top && t0 + u * kVerifyBlock < hi ? t0 + u * kVerifyBlock : best.id;
+      if (sampled) best.sum *= exp_rel(before, top, inv_t, table);
+    }
+    if (sampled) {
+      double part[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < U; ++u) part[u & 3] += exp_rel(v[u], best.max, inv_t, table);
+      best.sum += (part[0] + part[1]) + (part[2] + part[3]);
     }
   }
-  best = block_argmax(best, smem);
-  if (threadIdx.x == 0) ws.part_best[(int64_t)blockIdx.x * gridDim.y + blockIdx.y] = best;
-}
-
-// the row's best over the parts of pass 1 (every thread of the block computes the same)
-__device__ __forceinline__ ScoreId verify_row_best(const VerifyWs& ws, int64_t row, int parts) {
-  ScoreId best = ws.part_best[row * parts];
-  for (int i = 1; i < parts; ++i) {
-    const ScoreId c = ws.part_best[row * parts + i];
-    if (better(c, best)) best = c;
+  best = lanes_merge<64>(best, inv_t, sampled, table);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane == 0) wave_part[wave] = best;
+  __syncthreads();
+  if (wave == 0) {
+    best = lane < kVerifyWaves ? wave_part[lane] : VerifyPart{-INFINITY, 0x7fffffff, 0.0};
+    best = lanes_merge<kVerifyWaves>(best, inv_t, sampled, table);
+    if (lane == 0) ws.part[(int64_t)blockIdx.x * gridDim.y + blockIdx.y] = best;
   }
-  return best;
 }
 
-// Pass 2: per row and part, the partial softmax denominator sum exp((z - max) / T); part 0 also records the row's
-// max and argmax.  grid (B (2K+1), parts).
-__global__ __launch_bounds__(kSelBlock) void verify_sum_kernel(const float* __restrict__ zt, const float* __restrict__ zd,
-                                                               const float* __restrict__ temperature, int K, int V,
-                                                               VerifyWs ws) {
-  __shared__ double dsm[kSelWaves];
-  const int b = blockIdx.x / (2 * K + 1), r = blockIdx.x % (2 * K + 1);
+// Kernel 2.  grid (B, parts): every block of a sequence merges the partial results of its rows, takes the sequential accept
+// decisions (one lane per position, the first rejection by ballot) and, for sampled sequences, finds this part's candidate for
+// the bonus token at position k: from the residual max(p - q, 0), or from p at k = K and where the residual has no mass.
+// The candidate is the winner of an exponential race, r / -log(u): log(r) + (-log(-log u)), the Gumbel-max score, is its
+// logarithm, so the order is the same at one logarithm per token instead of three.
+__global__ __launch_bounds__(kVerifyBlock) void verify_decide_kernel(const float* __restrict__ zt, const float* __restrict__ zd,
+                                                                     const int32_t* __restrict__ spec,
+                                                                     const float* __restrict__ temperature, int K, int V,
+                                                                     uint64_t seed, int rows_per_seq, int row_parts, VerifyWs ws,
+                                                                     int32_t* __restrict__ accept_len, int32_t* __restrict__ bonus) {
+  constexpr int U = 8;    // tokens in flight per thread
+  __shared__ double table[32];
+  __shared__ VerifyPart row_s[2 * SSD_MAX_K + 1];
+  __shared__ int k_s, last_s;
+  __shared__ double mass_s[kVerifyWaves];
+  __shared__ ScoreId best_s[kVerifyWaves];
+  const int b = blockIdx.x, parts = gridDim.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const double T = zd ? (double)temperature[b] : 0.0;
-  const float* z = verify_row(zt, zd, b, r, K, V, T);
-  if (!z) return;
-  const ScoreId best = verify_row_best(ws, blockIdx.x, gridDim.y);
-  if (blockIdx.y == 0 && threadIdx.x == 0) {
-    ws.stats[blockIdx.x].max = best.s;
-    ws.stats[blockIdx.x].argmax = best.id;
-    ws.stats[blockIdx.x].pad = 0;
+  const bool sampled = T > 0.0;
+  if (!sampled && blockIdx.y > 0) return;
+  const double inv_t = sampled ? 1.0 / T : 0.0;
+  if (sampled) exp_table_init(table);
+  // ---- the drafted tokens' logits, requested ahead of the merge
+  int tok = -1;
+  float zt_s = 0.f, zd_s = 0.f;
+  if ((int)threadIdx.x < K) {
+    tok = spec[(int64_t)b * K + threadIdx.x];
+    if (sampled && tok >= 0 && tok < V) {
+      zt_s = zt[((int64_t)b * (K + 1) + threadIdx.x) * V + tok];
+      zd_s = zd[((int64_t)b * K + threadIdx.x) * V + tok];
+    }
   }
-  if (T <= 0.0) return;
-  int lo, hi;
-  verify_share(V, lo, hi);
-  double sum = 0.0;
-  constexpr int U = 8;
-  for (int t0 = lo + threadIdx.x; t0 < hi; t0 += kSelBlock * U) {
-    float v[U];
+  // ---- the rows' maxima and denominators: half a wavefront per row, a lane per part, two rows' chains side by side
+  const int n_rows = sampled ? 2 * K + 1 : K + 1;
+  __syncthreads();
+  static_assert(kVerifyMaxParts <= 32, "half a wavefront merges a row");
+  for (int r0 = 2 * wave + (lane >> 5); r0 < n_rows; r0 += 4 * kVerifyWaves) {
+    VerifyPart v[2];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * kSelBlock;
-      v[u] = z[t < hi ? t : t0];
+    for (int i = 0; i < 2; ++i) {
+      const int r = r0 + 2 * kVerifyWaves * i;
+      v[i] = {-INFINITY, 0x7fffffff, 0.0};
+      if (r < n_rows && (lane & 31) < row_parts) v[i] = ws.part[((int64_t)b * rows_per_seq + r) * row_parts + (lane & 31)];
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (t0 + u * kSelBlock < hi) sum += exp((score_of(v[u]) - best.s) / T);
-  }
-  sum = block_sum_f64(sum, dsm);
-  if (threadIdx.x == 0) ws.part_sum[(int64_t)blockIdx.x * gridDim.y + blockIdx.y] = sum;
-}
-
-// Pass 3: the sequential acceptance (one thread per sequence of work, done by every block of the sequence so that
-// all of them know the bonus position k), then this part's share of the residual mass at position k.  Part 0
-// publishes k, and the bonus token itself if the sequence is greedy.  grid (B, parts).
-__global__ __launch_bounds__(kSelBlock) void verify_accept_kernel(const float* __restrict__ zt, const float* __restrict__ zd,
-                                                                  const int32_t* __restrict__ spec,
-                                                                  const float* __restrict__ temperature, int K, int V,
-                                                                  uint64_t seed, VerifyWs ws, int row_parts,
-                                                                  int32_t* __restrict__ accept_len,
-                                                                  int32_t* __restrict__ bonus) {
-  __shared__ double dsm[kSelWaves];
-  __shared__ int k_s;
-  const int b = blockIdx.x, parts = gridDim.y;   // row_parts: the parts passes 1 and 2 cut a row into (may differ)
-  const double T = zd ? (double)temperature[b] : 0.0;
-  RowStats* st = ws.stats + (int64_t)b * (2 * K + 1);
-  // the rows' softmax denominators: the parts' sums in part order (threads 0 .. 2K merge one row each; part 0 keeps them)
-  __shared__ double sums[2 * SSD_MAX_K + 1];
-  if (T > 0.0 && (int)threadIdx.x <= 2 * K) {
-    const int64_t row = (int64_t)b * (2 * K + 1) + threadIdx.x;
-    double sum = 0.0;
-    for (int i = 0; i < row_parts; ++i) sum += ws.part_sum[row * row_parts + i];
-    sums[threadIdx.x] = sum;
-    if (blockIdx.y == 0) st[threadIdx.x].sum = sum;
+    for (int i = 0; i < 2; ++i) {
+      const int r = r0 + 2 * kVerifyWaves * i;
+      v[i] = lanes_merge<32>(v[i], inv_t, sampled, table);
+      if (r < n_rows && (lane & 31) == 0) row_s[r] = v[i];
+    }
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int k = K;
-    for (int i = 0; i < K; ++i) {
-      int s = spec[(int64_t)b * K + i];
-      bool ok;
-      if (T <= 0.0) ok = st[i].argmax == s;
-      else if (s < 0 || s >= V) ok = false;
+  // ---- accept s_{i+1} while u q(s) < p(s) (greedy: while it is the target's argmax)
+  if (wave == 0) {
+    bool ok = true;
+    if (lane < K) {
+      if (!sampled) ok = row_s[lane].id == tok;
+      else if (tok < 0 || tok >= V) ok = false;
       else {
-        double p = exp((score_of(zt[((int64_t)b * (K + 1) + i) * V + s]) - st[i].max) / T) / sums[i];
-        double q = exp((score_of(zd[((int64_t)b * K + i) * V + s]) - st[K + 1 + i].max) / T) / sums[K + 1 + i];
-        double u = draw_u(draw_prefix(seed, STREAM_ACCEPT, (uint64_t)b, (uint64_t)i), 0ull);
-        ok = u * q < p;
+        const double p = exp_rel(logit_score(zt_s), row_s[lane].max, inv_t, table) / row_s[lane].sum;
+        const double q = exp_rel(logit_score(zd_s), row_s[K + 1 + lane].max, inv_t, table) / row_s[K + 1 + lane].sum;
+        ok = draw_u(draw_prefix(seed, STREAM_ACCEPT, (uint64_t)b, (uint64_t)lane), 0ull) * q < p;
       }
-      if (!ok) { k = i; break; }
     }
-    k_s = k;
+    const unsigned long long rejected = __ballot(!ok);
+    if (lane == 0) k_s = rejected ? __ffsll((long long)rejected) - 1 : K;
   }
   __syncthreads();
   const int k = k_s;
   if (blockIdx.y == 0 && threadIdx.x == 0) {
-    ws.accept[b] = k;
     accept_len[b] = k;
-    if (T <= 0.0) bonus[b] = st[k].argmax;
+    if (!sampled) bonus[b] = row_s[k].id;
   }
-  if (T <= 0.0) return;
-  double mass = 0.0;
-  if (k < K) {
-    const float* zp = zt + ((int64_t)b * (K + 1) + k) * V;
-    const float* zq = zd + ((int64_t)b * K + k) * V;
-    const double pmax = st[k].max, psum = sums[k], qmax = st[K + 1 + k].max, qsum = sums[K + 1 + k];
-    int lo, hi;
-    verify_share(V, lo, hi);
-    for (int t = lo + threadIdx.x; t < hi; t += kSelBlock) {
-      double p = exp((score_of(zp[t]) - pmax) / T) / psum;
-      double q = exp((score_of(zq[t]) - qmax) / T) / qsum;
-      mass += fmax(p - q, 0.0);
-    }
-    mass = block_sum_f64(mass, dsm);
-  }
-  if (threadIdx.x == 0) ws.part_mass[(int64_t)b * parts + blockIdx.y] = mass;
-}
+  if (!sampled) return;
 
-// Pass 4: this part's best Gumbel-max candidate for the bonus token at position k: from the residual max(p - q, 0)
-// if it has mass (k < K), else from p.  grid (B, parts); greedy sequences are done already.
-__global__ __launch_bounds__(kSelBlock) void verify_bonus_kernel(const float* __restrict__ zt, const float* __restrict__ zd,
-                                                                 const float* __restrict__ temperature, int K, int V,
-                                                                 uint64_t seed, VerifyWs ws) {
-  __shared__ ScoreId smem[kSelWaves];
-  const int b = blockIdx.x, parts = gridDim.y;
-  const double T = zd ? (double)temperature[b] : 0.0;
-  if (T <= 0.0) return;
-  const RowStats* st = ws.stats + (int64_t)b * (2 * K + 1);
-  const int k = ws.accept[b];
-  double total = 0.0;
-  for (int i = 0; i < parts; ++i) total += ws.part_mass[(int64_t)b * parts + i];
-  const bool use_residual = k < K && total > 0.0;
+  // ---- this part's share of the bonus row
   const float* zp = zt + ((int64_t)b * (K + 1) + k) * V;
-  const float* zq = k < K ? zd + ((int64_t)b * K + k) * V : nullptr;
-  const double pmax = st[k].max, psum = st[k].sum;
-  const double qmax = k < K ? st[K + 1 + k].max : 0.0, qsum = k < K ? st[K + 1 + k].sum : 1.0;
+  const float* zq = zd + ((int64_t)b * K + (k < K ? k : 0)) * V;
+  const float pmax = row_s[k].max, qmax = k < K ? row_s[K + 1 + k].max : 0.f;
+  const double pinv = 1.0 / row_s[k].sum, qinv = k < K ? 1.0 / row_s[K + 1 + k].sum : 0.0;
   const uint64_t prefix = draw_prefix(seed, STREAM_BONUS, (uint64_t)b, (uint64_t)k);
   int lo, hi;
   verify_share(V, lo, hi);
-  ScoreId best = {-INFINITY, 0x7fffffff};
-  for (int t = lo + threadIdx.x; t < hi; t += kSelBlock) {
-    double r = exp((score_of(zp[t]) - pmax) / T) / psum;
-    if (use_residual) r = fmax(r - exp((score_of(zq[t]) - qmax) / T) / qsum, 0.0);
-    ScoreId c;
-    c.id = t;
-    c.s = r > 0.0 ? log(r) + gumbel_from_u(draw_u(prefix, (uint64_t)t)) : -INFINITY;
-    if (better(c, best)) best = c;
+  ScoreId best;
+  double mass;
+  // once for the residual and, where this part of it has no mass (its candidate counts only if no part has any, and is then
+  // p's), once more for p
+  for (bool residual = k < K;; residual = false) {
+    best = {-1.0, 0x7fffffff};
+    mass = 0.0;
+    for (int t0 = lo + threadIdx.x; t0 < hi; t0 += kVerifyBlock * U) {
+      float vp[U], vq[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = t0 + u * kVerifyBlock;
+        vp[u] = zp[t < hi ? t : t0];
+        vq[u] = zq[t < hi ? t : t0];
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = t0 + u * kVerifyBlock;
+        double r = residual_of(exp_rel(logit_score(vp[u]), pmax, inv_t, table), pinv,
+                               residual ? exp_rel(logit_score(vq[u]), qmax, inv_t, table) : 0.0, qinv);
+        r = t < hi && r > 0.0 ? r : 0.0;
+        mass += r;
+        const ScoreId c = {t < hi ? r / -log(draw_u(prefix, (uint64_t)t)) : -1.0, t};
+        if (better(c, best)) best = c;
+      }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      mass += __shfl_xor(mass, o);
+      ScoreId t;
+      t.s = __shfl_xor(best.s, o);
+      t.id = __shfl_xor(best.id, o);
+      if (better(t, best)) best = t;
+    }
+    __syncthreads();
+    if (lane == 0) { mass_s[wave] = mass; best_s[wave] = best; }
+    __syncthreads();
+    mass = 0.0;
+    best = best_s[0];
+    for (int w = 0; w < kVerifyWaves; ++w) {
+      mass += mass_s[w];
+      if (better(best_s[w], best)) best = best_s[w];
+    }
+    if (!residual) {
+      if (k < K) mass = 0.0;
+      break;
+    }
+    if (mass > 0.0) break;
   }
-  best = block_argmax(best, smem);
-  if (threadIdx.x == 0) ws.part_bonus[(int64_t)b * parts + blockIdx.y] = best;
-}
-
-// Pass 5: the bonus token of every sampled sequence among its parts' candidates.  One wavefront per sequence.
-__global__ __launch_bounds__(64) void verify_bonus_merge_kernel(const float* __restrict__ zd, const float* __restrict__ temperature,
-                                                                int parts, VerifyWs ws, int32_t* __restrict__ bonus) {
-  const int b = blockIdx.x;
-  if (!(zd && temperature[b] > 0.f)) return;
-  ScoreId best = {-INFINITY, 0x7fffffff};
-  for (int i = threadIdx.x; i < parts; i += 64) {
-    const ScoreId c = ws.part_bonus[(int64_t)b * parts + i];
-    if (better(c, best)) best = c;
+  // ---- the part's candidate goes out with agent-scope stores (visible to every compute unit once vmcnt is zero); the block
+  // that counts last of the sequence's parts reads them all back and picks the token
+  if (threadIdx.x == 0) {
+    VerifyCand* c = ws.cand + (int64_t)b * kVerifyMaxBonusParts + blockIdx.y;
+    __hip_atomic_store(&c->score, (uint64_t)__double_as_longlong(best.s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&c->id, (uint64_t)(uint32_t)best.id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&c->mass, (uint64_t)__double_as_longlong(mass), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    last_s = __hip_atomic_fetch_add(ws.done + b, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (uint32_t)parts;
   }
+  __syncthreads();
+  if (!last_s || wave != 0) return;
+  ScoreId mine = {-1.0, 0x7fffffff};
+  double m = 0.0;
+  if (lane < parts) {
+    const VerifyCand* c = ws.cand + (int64_t)b * kVerifyMaxBonusParts + lane;
+    mine.s = __longlong_as_double((long long)__hip_atomic_load(&c->score, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    mine.id = (int)__hip_atomic_load(&c->id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    m = __longlong_as_double((long long)__hip_atomic_load(&c->mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  }
+  if (k < K && __any(m > 0.0) && !(m > 0.0)) mine = {-1.0, 0x7fffffff};
   for (int o = 32; o > 0; o >>= 1) {
     ScoreId t;
-    t.s = __shfl_xor(best.s, o);
-    t.id = __shfl_xor(best.id, o);
-    if (better(t, best)) best = t;
+    t.s = __shfl_xor(mine.s, o);
+    t.id = __shfl_xor(mine.id, o);
+    if (better(t, mine)) mine = t;
   }
-  if (threadIdx.x == 0) bonus[b] = best.id;
+  if (lane == 0) bonus[b] = mine.id;
 }
 
 }  // namespace
@@ -646,23 +717,20 @@ int launch_sample(const float* logits, int64_t ld, const float* temperature, int
 int launch_verify(const float* zt, const float* zd, const int32_t* spec, const float* temperature, int B, int K, int V,
                   uint64_t seed, int32_t* accept_len, int32_t* bonus, void* workspace, hipStream_t s) {
   const VerifyWs ws = verify_ws_carve(workspace, B, K);
-  const int rows = B * (2 * K + 1);
-  // enough blocks to occupy the chip, at least 4096 tokens per part
-  int parts = 1024 / rows;
-  parts = parts > kVerifyMaxParts ? kVerifyMaxParts : parts;
-  while (parts > 1 && V / parts < 4096) --parts;
-  parts = parts < 1 ? 1 : parts;
-  int parts_b = 512 / B;
-  parts_b = parts_b > kVerifyMaxParts ? kVerifyMaxParts : parts_b;
-  while (parts_b > 1 && V / parts_b < 4096) --parts_b;
-  parts_b = parts_b < 1 ? 1 : parts_b;
-  verify_max_kernel<<<dim3(rows, parts), kSelBlock, 0, s>>>(zt, zd, temperature, K, V, ws);
-  verify_sum_kernel<<<dim3(rows, parts), kSelBlock, 0, s>>>(zt, zd, temperature, K, V, ws);
-  verify_accept_kernel<<<dim3(B, parts_b), kSelBlock, 0, s>>>(zt, zd, spec, temperature, K, V, seed, ws, parts, accept_len, bonus);
-  if (zd) {   // without draft logits every sequence is greedy and done
-    verify_bonus_kernel<<<dim3(B, parts_b), kSelBlock, 0, s>>>(zt, zd, temperature, K, V, seed, ws);
-    verify_bonus_merge_kernel<<<B, 64, 0, s>>>(zd, temperature, parts_b, ws, bonus);
-  }
+  const int rows_per_seq = zd ? 2 * K + 1 : K + 1;    // without draft logits every sequence is greedy
+  const int rows = B * rows_per_seq;
+  // enough blocks to occupy the chip, at least 1024 tokens (4 per thread) to each
+  auto cut = [&](int blocks, int n, int most) {
+    int parts = blocks / n;
+    parts = parts > most ? most : parts;
+    parts = parts > V / 1024 ? V / 1024 : parts;
+    return parts < 1 ? 1 : parts;
+  };
+  const int parts = cut(2048, rows, kVerifyMaxParts);
+  const int parts_b = zd ? cut(1024, B, kVerifyMaxBonusParts) : 1;
+  verify_rows_kernel<<<dim3(rows, parts), kVerifyBlock, 0, s>>>(zt, zd, temperature, K, V, rows_per_seq, ws);
+  verify_decide_kernel<<<dim3(B, parts_b), kVerifyBlock, 0, s>>>(zt, zd, spec, temperature, K, V, seed, rows_per_seq, parts, ws,
+                                                                 accept_len, bonus);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }
@@ -703,9 +771,8 @@ int launch_verify_static(const float* zt, const float* zd, const int32_t* spec, 
 
 size_t verify_workspace_bytes(int B, int K) {
   const size_t rows = (size_t)B * (2 * K + 1);
-  return verify_ws_align(rows * sizeof(RowStats)) + verify_ws_align(rows * kVerifyMaxParts * sizeof(ScoreId)) +
-         verify_ws_align(rows * kVerifyMaxParts * sizeof(double)) + verify_ws_align((size_t)B * kVerifyMaxParts * sizeof(double)) +
-         verify_ws_align((size_t)B * kVerifyMaxParts * sizeof(ScoreId)) + verify_ws_align((size_t)B * sizeof(int32_t));
+  return rows * kVerifyMaxParts * sizeof(VerifyPart) + (size_t)B * kVerifyMaxBonusParts * sizeof(VerifyCand) +
+         (((size_t)B * sizeof(uint32_t) + 15) & ~(size_t)15);
 }
 
 }  // namespace ssd

@@ -1,0 +1,65 @@
+"""The two verification kernels where their cuts can go wrong: vocabularies around the sizes at which a row is cut into one more
+part, parts of the bonus row whose residual has no mass, a residual without any mass, infinite and NaN logits."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ssd_oracle as O
+from tests.gpu_util import MARGIN, dev_f32, dev_i32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2603_03251_amd import binding
+    return binding
+
+
+def _verify(B, zt, zd, spec, temps, seed):
+    nb, K = spec.shape
+    k = torch.full((nb,), -9, dtype=torch.int32, device="cuda")
+    t = torch.full((nb,), -9, dtype=torch.int32, device="cuda")
+    ws = torch.randint(0, 255, (B.ssd_verify_workspace_bytes(nb, K),), dtype=torch.uint8, device="cuda")   # its contents do not matter
+    for _ in range(2):                                        # the second call runs over what the first left
+        B.ssd_verify(dev_f32(zt), dev_f32(zd), dev_i32(spec), dev_f32(temps), seed, k, t, ws)
+    torch.cuda.synchronize()
+    return k.cpu().numpy(), t.cpu().numpy()
+
+
+@pytest.mark.parametrize("V", [2, 1023, 1024, 2047, 2049, 4097, 32771, 65536])
+@pytest.mark.parametrize("nb,K", [(1, 1), (1, 15), (7, 3), (70, 2)])
+def test_verify_at_the_edges_of_its_parts(B, V, nb, K):
+    if nb * V > 2 ** 20 and K > 2:
+        pytest.skip("covered by the smaller batch")
+    print(f"[case] verify B={nb} K={K} V={V}", flush=True)
+    g = np.random.default_rng(V + nb + K)
+    zd = (g.standard_normal((nb, K, V)) * 2).astype(np.float32)
+    zt = (g.standard_normal((nb, K + 1, V)) * 2).astype(np.float32)
+    # the target gives the lower half less than the draft does: those parts have no residual mass
+    zt[:, :K, : V // 2] = zd[:, :, : V // 2] - 1.0
+    zt[:, :K, V // 2:] = zd[:, :, V // 2:] + g.uniform(0.2, 0.6, (nb, K, V - V // 2)).astype(np.float32)
+    if V > 8:
+        zt[:, :, 3], zt[:, :, 5] = np.nan, -np.inf            # no probability
+    spec = g.integers(0, V, (nb, K)).astype(np.int32)
+    temps = np.where(np.arange(nb) % 4 == 3, 0.0, 0.9).astype(np.float32)
+    k, t = _verify(B, zt, zd, spec, temps, 99 + V)
+    zt[np.isnan(zt)] = -np.inf
+    checked = 0
+    for b in range(nb):
+        want = O.verify(zt[b], zd[b], spec[b], float(temps[b]), 99 + V, seq=b)
+        if all(m > MARGIN for m in want.accept_margin):
+            assert k[b] == want.accept_len, b
+            if want.bonus_margin > MARGIN:
+                assert t[b] == want.bonus, b
+                checked += 1
+    assert checked > 0 or nb < 7
+
+
+def test_verify_residual_without_mass_falls_back_to_the_target(B):
+    V, K = 5000, 2
+    g = np.random.default_rng(3)
+    zt = g.standard_normal((1, K + 1, V)).astype(np.float32)
+    k, t = _verify(B, zt, zt[:, :K].copy(), np.array([[-1, 5]], np.int32), np.ones(1, np.float32), 7)   # a token outside: rejected
+    score = np.log(O.softmax_T(zt[0, 0], 1.0)) + O.gumbel(7, O.STREAM_BONUS, 0, 0, V)
+    assert k[0] == 0 and t[0] == int(np.argmax(score))
