@@ -141,6 +141,14 @@ int launch_tile_weights_bf16(const bf16_t* src, bf16_t* dst, int N, int Kd, hipS
 // (ld elements); for EPI_SWIGLU out is an activation [M][N] = silu(x.w^T) * (x.w2^T) (planes `out_plane` apart).
 int launch_gemm(int dtype, int epi, const void* x, int64_t x_plane, const void* w, const void* w2, void* out, int64_t ld,
                 int64_t out_plane, int M, int N, int Kd, hipStream_t s);
+// fp32 models: RMSNorm of the residual stream h [M][d_model] together with the linear layer that reads it.
+// act = silu(xn w_gate^T) * (xn w_up^T); and q (rotated), keys (rotated) and values of xn wqkv^T, the latter two straight
+// into the rows' KV slots.
+int launch_norm_swiglu_f32(const float* h, const float* gain, const float* w_gate, const float* w_up, float* act, int M, int d_ffn,
+                           int d_model, float eps, hipStream_t s);
+int launch_norm_qkv_rope_f32(const float* h, const float* gain, const float* wqkv, float* q, float* trunk_k, float* trunk_v,
+                             float* suffix_k, float* suffix_v, const RowDesc* rows, const float* cos_sin, int M, const Dims& d,
+                             int max_trunk, int suffix_cap, hipStream_t s);
 
 // ---------------------------------------------------------------- kernels_attn.hip
 struct AttnArgs {

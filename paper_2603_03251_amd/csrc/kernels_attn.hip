@@ -112,37 +112,40 @@ constexpr int kSplitKeys = 256;         // most keys of a split: one per thread
 constexpr int kSplitMaxRows = 64;       // rows up to which the scratch allows the most splits
 constexpr int kSplitMaxGroup = 8;       // query heads per KV head the split kernel holds
 
-template <typename T, int NE> struct LoadElems;
-template <> struct LoadElems<bf16_t, 1> { static __device__ __forceinline__ void load(const bf16_t* p, float* o) { o[0] = bf16_to_f32(p[0]); } };
-template <> struct LoadElems<bf16_t, 2> {
-  static __device__ __forceinline__ void load(const bf16_t* p, float* o) {
+// VEC consecutive elements: 16 bytes, or (bf16) 4, (either type) one
+template <typename T, int VEC>
+__device__ __forceinline__ void load_elems(const T* p, float* o) {
+  if constexpr (VEC == Vec16<T>::N) Vec16<T>::load(p, o);
+  else if constexpr (VEC == 2 && sizeof(T) == 2) {
     const uint32_t w = *(const uint32_t*)p;
     o[0] = __uint_as_float(w << 16);
     o[1] = __uint_as_float(w & 0xffff0000u);
+  } else {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) o[e] = Elem<T>::load(p + e);
   }
-};
-template <> struct LoadElems<float, 1> { static __device__ __forceinline__ void load(const float* p, float* o) { o[0] = p[0]; } };
-template <> struct LoadElems<float, 2> {
-  static __device__ __forceinline__ void load(const float* p, float* o) {
-    const float2 v = *(const float2*)p;
-    o[0] = v.x;
-    o[1] = v.y;
-  }
-};
+}
 
 // Passes with few rows (an extend, a verification forward, a small decode batch): one block per (row, KV head, split
-// of at most 256 keys), all query heads of the group at once.  Scores: one key per thread against the group's queries
-// (in LDS); softmax over the block; weighted values: thread = (quarter of the keys, D/64 head dimensions), so every
-// value row is read with consecutive threads on consecutive dimensions.  Writes the split's partial softmax
-// (max, sum, unnormalised output) to `partial` [row][query head][split][D + 2]; attention_merge_kernel adds the
-// splits up in split order.
-template <typename T, int D>
+// of at most 256 keys), all query heads of the group (at most G) at once.  Scores: one key per thread against the group's
+// queries (in LDS); softmax over the block; weighted values: every wavefront takes a quarter of the keys the split really
+// has, 16 bytes per lane and kPvBatch loads together (a load covers KPI keys), so
+// a split of 64 keys is one memory round trip there, where 64 fixed keys per wavefront and one row per load made it eight.
+// Writes the split's partial softmax (max, sum, unnormalised output) to `partial` [row][query head][split][D + 2];
+// attention_merge_kernel adds the splits up in split order.  A single split is the result (partial == nullptr).
+// 10 rows x 4 heads x 138 keys, fp32: 7.0 us (18.5 us and 4.7 us of merge before).
+template <typename T, int D, int G>
 __global__ __launch_bounds__(256) void attention_split_kernel(const float* __restrict__ q, const T* __restrict__ trunk_k,
                                                                const T* __restrict__ trunk_v, const T* __restrict__ suffix_k,
                                                                const T* __restrict__ suffix_v, const RowDesc* __restrict__ rows,
                                                                int n_q_heads, int n_kv_heads, int max_trunk, int suffix_cap,
-                                                               float* __restrict__ partial, int keys_per_split) {
-  constexpr int G = kSplitMaxGroup, NE = D / 64;
+                                                               float* __restrict__ partial, int keys_per_split,
+                                                               void* __restrict__ out, int64_t out_plane) {
+  // head dimensions per lane: 16 bytes, or with a large group one consecutive share of a whole-wavefront row per key (8
+  // heads x 8 dimensions of accumulators and their exchange across lanes cost a 70B-shaped row more than they saved:
+  // 55 -> 70 us for 6 rows x 8 heads x 4096 keys)
+  constexpr int KV = Vec16<T>::N, VEC = G * KV <= 32 ? KV : D / 64, LPR = D / VEC, KPI = 64 / LPR;
+  constexpr int kPvBatch = 8;
   __shared__ float q_s[G][D];
   __shared__ float p_s[G][kSplitKeys];
   __shared__ float red_s[4][G][D];
@@ -178,14 +181,14 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
     // (fully unrolled: the key row's loads all go out before the first product; in groups of 4 a row of 128 bf16
     // cost four memory round trips)
 #pragma unroll
-    for (int d0 = 0; d0 < D; d0 += Vec16<T>::N) {
-      float kk[Vec16<T>::N];
+    for (int d0 = 0; d0 < D; d0 += KV) {
+      float kk[KV];
       Vec16<T>::load(kp + d0, kk);
 #pragma unroll
       for (int g = 0; g < G; ++g)
         if (g < group) {
 #pragma unroll
-          for (int e = 0; e < Vec16<T>::N; ++e) sc[g] = fmaf(q_s[g][d0 + e], kk[e], sc[g]);
+          for (int e = 0; e < KV; ++e) sc[g] = fmaf(q_s[g][d0 + e], kk[e], sc[g]);
         }
     }
   }
@@ -197,11 +200,10 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
     if (lane == 0) mx_s[g][wave] = v;
   }
   __syncthreads();
-  float mg[G];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    mg[g] = fmaxf(fmaxf(mx_s[g][0], mx_s[g][1]), fmaxf(mx_s[g][2], mx_s[g][3]));
-    const float m_use = mg[g] == -INFINITY ? 0.f : mg[g];
+    const float mg = fmaxf(fmaxf(mx_s[g][0], mx_s[g][1]), fmaxf(mx_s[g][2], mx_s[g][3]));
+    const float m_use = mg == -INFINITY ? 0.f : mg;
     const float pe = have ? expf(sc[g] - m_use) : 0.f;
     p_s[g][tid] = pe;
     float v = pe;
@@ -209,50 +211,56 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
     if (lane == 0) sum_s[g][wave] = v;
   }
   __syncthreads();
-  // ---- weighted values: wavefront = quarter of the split's keys, lane = NE consecutive head dimensions
-  float acc[G][NE];
+  // ---- weighted values: lane = (key sub of a load's KPI, VEC consecutive head dimensions)
+  float acc[G][VEC];
 #pragma unroll
   for (int g = 0; g < G; ++g)
 #pragma unroll
-    for (int e = 0; e < NE; ++e) acc[g][e] = 0.f;
-  const int jq0 = wave * (kSplitKeys / 4);
-  const int jq1 = min(jq0 + kSplitKeys / 4, j_end - j_begin);
-  // value rows in batches of kPvBatch whose loads go out together (one row per iteration, used at once, made the loop
-  // a chain of memory latencies: 64 of them per wavefront); rows past the quarter's end re-read its last row
-  constexpr int kPvBatch = 8;
-  for (int jj0 = jq0; jj0 < jq1; jj0 += kPvBatch) {
-    float vv[kPvBatch][NE];
+    for (int e = 0; e < VEC; ++e) acc[g][e] = 0.f;
+  const int n_here = max(j_end - j_begin, 0), quarter = (n_here + 3) >> 2;
+  const int jq0 = wave * quarter, jq1 = min(jq0 + quarter, n_here);
+  const int sub = lane / LPR, d0 = (lane & (LPR - 1)) * VEC;
+  for (int jj0 = jq0; jj0 < jq1; jj0 += KPI * kPvBatch) {
+    float vv[kPvBatch][VEC], pe[kPvBatch][G];
 #pragma unroll
     for (int u = 0; u < kPvBatch; ++u) {
-      const int jk = j_begin + min(jj0 + u, jq1 - 1);
-      const T* vp = (jk < r.vis ? tv + (int64_t)jk * kv_stride : sv + (int64_t)(jk - r.vis) * kv_stride) + lane * NE;
-      LoadElems<T, NE>::load(vp, vv[u]);
+      const int jj = jj0 + u * KPI + sub, jc = min(jj, jq1 - 1);   // past the end: the last row again, with weight 0
+      const int jk = j_begin + jc;
+      load_elems<T, VEC>((jk < r.vis ? tv + (int64_t)jk * kv_stride : sv + (int64_t)(jk - r.vis) * kv_stride) + d0, vv[u]);
+#pragma unroll
+      for (int g = 0; g < G; ++g) pe[u][g] = jj < jq1 ? p_s[g][jc] : 0.f;
     }
 #pragma unroll
-    for (int u = 0; u < kPvBatch; ++u) {
-      if (jj0 + u < jq1) {
+    for (int u = 0; u < kPvBatch; ++u)
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-          if (g < group) {
-            const float pe = p_s[g][jj0 + u];
+      for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int e = 0; e < NE; ++e) acc[g][e] = fmaf(pe, vv[u][e], acc[g][e]);
-          }
-      }
-    }
+        for (int e = 0; e < VEC; ++e) acc[g][e] = fmaf(pe[u][g], vv[u][e], acc[g][e]);
   }
 #pragma unroll
   for (int g = 0; g < G; ++g)
 #pragma unroll
-    for (int e = 0; e < NE; ++e) red_s[wave][g][lane * NE + e] = acc[g][e];
+    for (int e = 0; e < VEC; ++e) {
+      float v = acc[g][e];
+#pragma unroll
+      for (int o = LPR; o < 64; o <<= 1) v += __shfl_xor(v, o);
+      if (lane < LPR) red_s[wave][g][d0 + e] = v;
+    }
   __syncthreads();
   for (int i = tid; i < group * D; i += 256) {
     const int g = i / D, d = i - g * D;
-    float* pp = partial + (((int64_t)m * n_q_heads + hk * group + g) * n_splits + split) * (D + 2);
-    pp[2 + d] = (red_s[0][g][d] + red_s[1][g][d]) + (red_s[2][g][d] + red_s[3][g][d]);
-    if (d == 0) {
-      pp[0] = fmaxf(fmaxf(mx_s[g][0], mx_s[g][1]), fmaxf(mx_s[g][2], mx_s[g][3]));   // -inf for a split without keys
-      pp[1] = (sum_s[g][0] + sum_s[g][1]) + (sum_s[g][2] + sum_s[g][3]);
+    const float o = (red_s[0][g][d] + red_s[1][g][d]) + (red_s[2][g][d] + red_s[3][g][d]);
+    const float l = (sum_s[g][0] + sum_s[g][1]) + (sum_s[g][2] + sum_s[g][3]);
+    const int64_t pair = (int64_t)m * n_q_heads + hk * group + g;
+    if (!partial) {
+      Act<T>::store(out, out_plane, pair * D + d, o / l);
+    } else {
+      float* pp = partial + (pair * n_splits + split) * (D + 2);
+      pp[2 + d] = o;
+      if (d == 0) {
+        pp[0] = fmaxf(fmaxf(mx_s[g][0], mx_s[g][1]), fmaxf(mx_s[g][2], mx_s[g][3]));   // -inf for a split without keys
+        pp[1] = l;
+      }
     }
   }
 }
@@ -286,7 +294,8 @@ int choose_splits(const AttnArgs& a, int* keys_per_split) {
   *keys_per_split = 0;
   if (!a.partial || a.n_q_heads / a.n_kv_heads > kSplitMaxGroup) return 1;
   int n = (max_keys + kSplitKeys - 1) / kSplitKeys;
-  int fill = (1024 + pairs - 1) / pairs;
+  // (keys that fit one split: a single block per pair is done before the merge of several would have started)
+  int fill = max_keys <= kSplitKeys ? 1 : (1024 + pairs - 1) / pairs;
   const int by_len = (max_keys + 63) / 64;
   fill = fill < by_len ? fill : by_len;
   n = n > fill ? n : fill;
@@ -307,11 +316,18 @@ int launch_rowwise_d(const AttnArgs& a, hipStream_t s) {
                                                         a.n_kv_heads, a.max_trunk, a.suffix_cap);
   } else {
     dim3 grid(a.M, a.n_kv_heads, n_splits);
-    attention_split_kernel<T, D><<<grid, 256, 0, s>>>(a.q, (const T*)a.trunk_k, (const T*)a.trunk_v, (const T*)a.suffix_k,
-                                                      (const T*)a.suffix_v, a.rows, a.n_q_heads, a.n_kv_heads, a.max_trunk,
-                                                      a.suffix_cap, a.partial, keys_per_split);
+    float* partial = n_splits > 1 ? a.partial : nullptr;
+    const int group = a.n_q_heads / a.n_kv_heads;
+#define SSD_SPLIT_LAUNCH(GV)                                                                                              \
+  attention_split_kernel<T, D, GV><<<grid, 256, 0, s>>>(a.q, (const T*)a.trunk_k, (const T*)a.trunk_v, (const T*)a.suffix_k, \
+                                                        (const T*)a.suffix_v, a.rows, a.n_q_heads, a.n_kv_heads, a.max_trunk, \
+                                                        a.suffix_cap, partial, keys_per_split, a.out, a.out_plane)
+    if (group == 1) SSD_SPLIT_LAUNCH(1);
+    else if (group <= 4) SSD_SPLIT_LAUNCH(4);
+    else SSD_SPLIT_LAUNCH(kSplitMaxGroup);
+#undef SSD_SPLIT_LAUNCH
     SSD_HIP(hipGetLastError());
-    attention_merge_kernel<T, D><<<a.M * a.n_q_heads, D, 0, s>>>(a.partial, a.out, a.out_plane, n_splits);
+    if (n_splits > 1) attention_merge_kernel<T, D><<<a.M * a.n_q_heads, D, 0, s>>>(a.partial, a.out, a.out_plane, n_splits);
   }
   SSD_HIP(hipGetLastError());
   return SSD_OK;

@@ -9,7 +9,7 @@
 // Activations arrive as two bf16 planes, head and remainder (x = hi + lo, written by the producing kernel), and
 // take two MFMAs per weight tile, so the only bf16 rounding left in a layer is that of the weights themselves
 // and of the KV cache.  With a handful of rows the extra MFMAs are free: the kernel is bound by the weight stream.
-// fp32 models (the small correctness configuration): plain FMA dot products, one wavefront per output feature.
+// fp32 models (the small correctness configuration): plain FMA dot products.
 #include "common.h"
 
 namespace ssd {
@@ -137,46 +137,147 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_kernel(const bf16_t* __
   }
 }
 
-// fp32: one wavefront per output feature, lanes stride over the inputs, up to 16 rows per pass.
-constexpr int kRowsF32 = 16;
-template <int EPI>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ x, const float* __restrict__ w,
-                                                        const float* __restrict__ w2, float* __restrict__ out, int64_t ld,
-                                                        int M, int N, int Kd) {
+// fp32 models.  A pass is a handful of rows over matrices of a few hundred KiB that sit in L2, so a layer costs its memory
+// round trips, not its bytes: a wavefront takes one output feature (or, PAIR, two: gate and up of SwiGLU, or the two
+// members of a rotary pair) over 1 / WPF of the reduction dimension and up to kRowsF32 rows, requests 16 bytes per lane of
+// the weights and of every row at a time, kStepsF32 such steps together, and adds the lanes up with a butterfly that
+// halves the number of rows it carries at each step (10 exchanges for 8 rows instead of 48).  WPF = 4 (few features, long
+// reduction dimension): the four wavefronts of a block share a feature.  NORM: the input is the residual stream, the RMSNorm
+// runs along in the same loads (y = 1/rms(x) * sum x gain w): no kernel of its own.  A round of the 2-layer, 256-wide
+// configuration (10 rows, prefix 128): 4.2 (o), 4.6 (down), 6.4 (qkv) and 6.8 us (gate/up); 12.3, 12.3, 7.1 and 9.4 with one 4-byte element
+// per lane and step, behind separate norm (4.2 us) and rotary (3.3 us) kernels.
+constexpr int kRowsF32 = 8;
+constexpr int kStepsF32 = 4;
+enum F32Epilogue { F32_STORE = 0, F32_RESIDUAL = 1, F32_SWIGLU = 2, F32_ROPE = 3 };
+
+// v[r] summed over the 64 lanes; lane l ends up with the sum of row l >> 3.
+__device__ __forceinline__ float rows_sum(float v[kRowsF32]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int half = kRowsF32 / 2, o = 32; half >= 1; half >>= 1, o >>= 1) {
+#pragma unroll
+    for (int i = 0; i < kRowsF32 / 2; ++i)
+      if (i < half) {
+        const bool hi = (lane & o) != 0;
+        const float send = hi ? v[i] : v[i + half], keep = hi ? v[i + half] : v[i];
+        v[i] = keep + __shfl_xor(send, o);
+      }
+  }
+  float s = v[0];
+#pragma unroll
+  for (int o = 4; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+  return s;
+}
+static_assert(kRowsF32 == 8, "rows_sum leaves row lane >> 3 in a lane");
+
+struct GemmF32 {
+  const float* x;       // [M][Kd]
+  const float* gain;    // NORM: [Kd]
+  const float* w;       // [N][Kd]
+  const float* w2;      // SWIGLU: the up matrix
+  float* out;           // STORE, RESIDUAL, SWIGLU: [M][ld]
+  int64_t ld;
+  int M, N, Kd;
+  int m_base, rows;     // first row of this launch, rows per block (<= kRowsF32)
+  float eps;
+  // ROPE: out = the rotated queries [M][qd]; rotated keys and values go to the row's KV slot
+  const RowDesc* desc;
+  const float* cos_sin;
+  float *trunk_k, *trunk_v, *suffix_k, *suffix_v;
+  int qd, kvd, half, max_trunk, suffix_cap;
+};
+
+template <int EPI, bool NORM, int WPF>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 a) {
+  constexpr bool PAIR = EPI == F32_SWIGLU || EPI == F32_ROPE;
+  __shared__ float part[3][4][kRowsF32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = blockIdx.x * 4 + wave;
-  const int m0 = blockIdx.y * kRowsF32;
-  if (n >= N) return;
-  float acc[kRowsF32], acc2[kRowsF32];
+  const int u = WPF == 4 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;   // feature, or feature pair (ROPE)
+  const int n_units = EPI == F32_ROPE ? a.N >> 1 : a.N;
+  if (WPF == 1 && u >= n_units) return;
+  int n = u, n2 = u;
+  if (EPI == F32_ROPE) {
+    const int head = u / a.half;
+    n = head * 2 * a.half + (u - head * a.half);
+    n2 = n + a.half;
+  }
+  const int m0 = a.m_base + (int)blockIdx.y * a.rows, rows = min(a.rows, a.M - m0);
+  const float* w1 = a.w + (int64_t)n * a.Kd;
+  const float* w2 = EPI == F32_SWIGLU ? a.w2 + (int64_t)n * a.Kd : a.w + (int64_t)n2 * a.Kd;
+  const int kq = (a.Kd / 4 + WPF - 1) / WPF * 4;                    // inputs per wavefront
+  const int k_begin = WPF == 4 ? wave * kq : 0, k_end = min(a.Kd, k_begin + kq);
+  float acc[kRowsF32], acc2[kRowsF32], ssq[kRowsF32];
 #pragma unroll
-  for (int r = 0; r < kRowsF32; ++r) { acc[r] = 0.f; acc2[r] = 0.f; }
-  const float* wrow = w + (int64_t)n * Kd;
-  const float* wrow2 = EPI == EPI_SWIGLU ? w2 + (int64_t)n * Kd : nullptr;
-  for (int k = lane; k < Kd; k += 64) {
-    float wv = wrow[k];
-    float wv2 = EPI == EPI_SWIGLU ? wrow2[k] : 0.f;
+  for (int r = 0; r < kRowsF32; ++r) { acc[r] = 0.f; acc2[r] = 0.f; ssq[r] = 0.f; }
+  for (int k0 = k_begin; k0 < k_end; k0 += 256 * kStepsF32) {
 #pragma unroll
-    for (int r = 0; r < kRowsF32; ++r) {
-      int m = m0 + r;
-      float xv = m < M ? x[(int64_t)m * Kd + k] : 0.f;
-      acc[r] = fmaf(xv, wv, acc[r]);
-      if (EPI == EPI_SWIGLU) acc2[r] = fmaf(xv, wv2, acc2[r]);
+    for (int st = 0; st < kStepsF32; ++st) {
+      const int k = k0 + st * 256 + lane * 4;
+      const bool in = k < k_end;                                     // (Kd is a multiple of 4)
+      if (k0 + st * 256 >= k_end) break;
+      const int kc = in ? k : k_begin;
+      const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+      float4 wv = *(const float4*)(w1 + kc), wv2 = zero, g = zero;
+      if (PAIR) wv2 = *(const float4*)(w2 + kc);
+      if (NORM) g = *(const float4*)(a.gain + kc);
+      if (!in) { wv = zero; wv2 = zero; }
+#pragma unroll
+      for (int r = 0; r < kRowsF32; ++r) {
+        const float4 x = *(const float4*)(a.x + (int64_t)(m0 + (r < rows ? r : 0)) * a.Kd + kc);
+        float v[4] = {in ? x.x : 0.f, in ? x.y : 0.f, in ? x.z : 0.f, in ? x.w : 0.f};
+        if (NORM) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ssq[r] = fmaf(v[e], v[e], ssq[r]);
+          v[0] *= g.x; v[1] *= g.y; v[2] *= g.z; v[3] *= g.w;
+        }
+        acc[r] = fmaf(v[0], wv.x, fmaf(v[1], wv.y, fmaf(v[2], wv.z, fmaf(v[3], wv.w, acc[r]))));
+        if (PAIR) acc2[r] = fmaf(v[0], wv2.x, fmaf(v[1], wv2.y, fmaf(v[2], wv2.z, fmaf(v[3], wv2.w, acc2[r]))));
+      }
     }
   }
-#pragma unroll
-  for (int r = 0; r < kRowsF32; ++r) {
-    float v = acc[r], v2 = acc2[r];
-    for (int o = 32; o > 0; o >>= 1) {
-      v += __shfl_xor(v, o);
-      if (EPI == EPI_SWIGLU) v2 += __shfl_xor(v2, o);
+  float y = rows_sum(acc), y2 = 0.f, ss = 0.f;
+  if (PAIR) y2 = rows_sum(acc2);
+  if (NORM) ss = rows_sum(ssq);
+  const int r = lane >> 3, m = m0 + r;
+  if (WPF == 4) {
+    if ((lane & 7) == 0) {
+      part[0][wave][r] = y;
+      if (PAIR) part[1][wave][r] = y2;
+      if (NORM) part[2][wave][r] = ss;
     }
-    int m = m0 + r;
-    if (lane == 0 && m < M) {
-      float* p = out + (int64_t)m * ld + n;
-      if (EPI == EPI_STORE_F32) *p = v;
-      else if (EPI == EPI_RESIDUAL_ADD) *p += v;
-      else *p = (v / (1.0f + expf(-v))) * v2;
+    __syncthreads();
+    if (wave != 0) return;
+    auto total = [&](int i) { return (part[i][0][r] + part[i][1][r]) + (part[i][2][r] + part[i][3][r]); };
+    y = total(0);
+    if (PAIR) y2 = total(1);
+    if (NORM) ss = total(2);
+  }
+  if ((lane & 7) != 0 || r >= rows) return;
+  if (NORM) {
+    const float rs = 1.0f / sqrtf(ss / (float)a.Kd + a.eps);
+    y *= rs;
+    if (PAIR) y2 *= rs;
+  }
+  if (EPI == F32_STORE) a.out[(int64_t)m * a.ld + n] = y;
+  else if (EPI == F32_RESIDUAL) a.out[(int64_t)m * a.ld + n] += y;
+  else if (EPI == F32_SWIGLU) a.out[(int64_t)m * a.ld + n] = (y / (1.0f + expf(-y))) * y2;
+  else {
+    const int i = u % a.half;
+    if (n < a.qd + a.kvd) {
+      const float c = a.cos_sin[((int64_t)m * a.half + i) * 2], sn = a.cos_sin[((int64_t)m * a.half + i) * 2 + 1];
+      const float ra = y * c - y2 * sn, rb = y2 * c + y * sn;
+      y = ra;
+      y2 = rb;
     }
+    float* dst = a.out + (int64_t)m * a.qd + n;
+    if (n >= a.qd) {
+      const RowDesc d = a.desc[m];
+      const int64_t row = (d.is_branch ? ((int64_t)m * a.suffix_cap + d.kv_slot) : ((int64_t)d.seq * a.max_trunk + d.kv_slot)) * a.kvd;
+      if (n < a.qd + a.kvd) dst = (d.is_branch ? a.suffix_k : a.trunk_k) + row + (n - a.qd);
+      else dst = (d.is_branch ? a.suffix_v : a.trunk_v) + row + (n - a.qd - a.kvd);
+    }
+    dst[0] = y;
+    dst[a.half] = y2;
   }
 }
 
@@ -204,11 +305,22 @@ int launch_bf16(const void* x, int64_t x_plane, const void* w, const void* w2, v
   return SSD_OK;
 }
 
-template <int EPI>
-int launch_f32(const void* x, const void* w, const void* w2, void* out, int64_t ld, int M, int N, int Kd, hipStream_t s) {
-  dim3 grid((N + 3) / 4, (M + kRowsF32 - 1) / kRowsF32);
-  gemm_f32_kernel<EPI><<<grid, 256, 0, s>>>((const float*)x, (const float*)w, (const float*)w2, (float*)out, ld, M, N, Kd);
-  SSD_HIP(hipGetLastError());
+// Four wavefronts per feature where that still leaves at most four blocks per compute unit and a wavefront has at least
+// one full step of 256 inputs: down of the 256-wide configuration (K = 1024) takes 4.6 us in 256 blocks, hardly more than
+// o (K = 256, 64 blocks of one wavefront per feature, 4.2 us), where its reduction would be four steps in a row.
+template <int EPI, bool NORM>
+int launch_f32(GemmF32 a, hipStream_t s) {
+  const int n_units = EPI == F32_ROPE ? a.N / 2 : a.N;
+  const int gy = (a.M + kRowsF32 - 1) / kRowsF32;
+  a.rows = (a.M + gy - 1) / gy;
+  constexpr int kMaxGridY = 65535;
+  for (int y0 = 0; y0 < gy; y0 += kMaxGridY) {
+    const int ny = gy - y0 < kMaxGridY ? gy - y0 : kMaxGridY;
+    if ((a.m_base = y0 * a.rows) >= a.M) break;
+    if (n_units <= 1024 && a.Kd >= 1024) gemm_f32_kernel<EPI, NORM, 4><<<dim3(n_units, ny), 256, 0, s>>>(a);
+    else gemm_f32_kernel<EPI, NORM, 1><<<dim3((n_units + 3) / 4, ny), 256, 0, s>>>(a);
+    SSD_HIP(hipGetLastError());
+  }
   return SSD_OK;
 }
 
@@ -233,11 +345,32 @@ int launch_gemm(int dtype, int epi, const void* x, int64_t x_plane, const void* 
       default: return launch_bf16<EPI_SWIGLU>(x, x_plane, w, w2, out, ld, out_plane, M, N, Kd, s);
     }
   }
+  GemmF32 a{};
+  a.x = (const float*)x; a.w = (const float*)w; a.w2 = (const float*)w2; a.out = (float*)out; a.ld = ld; a.M = M; a.N = N; a.Kd = Kd;
   switch (epi) {
-    case EPI_STORE_F32: return launch_f32<EPI_STORE_F32>(x, w, w2, out, ld, M, N, Kd, s);
-    case EPI_RESIDUAL_ADD: return launch_f32<EPI_RESIDUAL_ADD>(x, w, w2, out, ld, M, N, Kd, s);
-    default: return launch_f32<EPI_SWIGLU>(x, w, w2, out, ld, M, N, Kd, s);
+    case EPI_STORE_F32: return launch_f32<F32_STORE, false>(a, s);
+    case EPI_RESIDUAL_ADD: return launch_f32<F32_RESIDUAL, false>(a, s);
+    default: return launch_f32<F32_SWIGLU, false>(a, s);
   }
+}
+
+int launch_norm_swiglu_f32(const float* h, const float* gain, const float* w_gate, const float* w_up, float* act, int M, int d_ffn,
+                           int d_model, float eps, hipStream_t s) {
+  if (M <= 0) return SSD_OK;
+  GemmF32 a{};
+  a.x = h; a.gain = gain; a.w = w_gate; a.w2 = w_up; a.out = act; a.ld = d_ffn; a.M = M; a.N = d_ffn; a.Kd = d_model; a.eps = eps;
+  return launch_f32<F32_SWIGLU, true>(a, s);
+}
+
+int launch_norm_qkv_rope_f32(const float* h, const float* gain, const float* wqkv, float* q, float* trunk_k, float* trunk_v,
+                             float* suffix_k, float* suffix_v, const RowDesc* rows, const float* cos_sin, int M, const Dims& d,
+                             int max_trunk, int suffix_cap, hipStream_t s) {
+  if (M <= 0) return SSD_OK;
+  GemmF32 a{};
+  a.x = h; a.gain = gain; a.w = wqkv; a.out = q; a.M = M; a.N = d.qkv_dim(); a.Kd = d.d_model; a.eps = d.rms_eps;
+  a.desc = rows; a.cos_sin = cos_sin; a.trunk_k = trunk_k; a.trunk_v = trunk_v; a.suffix_k = suffix_k; a.suffix_v = suffix_v;
+  a.qd = d.q_dim(); a.kvd = d.kv_dim(); a.half = d.head_dim / 2; a.max_trunk = max_trunk; a.suffix_cap = suffix_cap;
+  return launch_f32<F32_ROPE, true>(a, s);
 }
 
 }  // namespace ssd

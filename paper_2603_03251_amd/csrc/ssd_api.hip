@@ -527,11 +527,17 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
   SSD_TRY(launch_embed(dt, m->embed, tokens, c->h, M, d.d_model, d.vocab, s));
   for (int l = 0; l < d.n_layers; ++l) {
     const ssd_model::Layer& L = m->layers[l];
-    SSD_TRY(launch_rmsnorm(dt, c->h, L.attn_norm, c->xn, R * d.d_model, nullptr, 0, M, d.d_model, d.rms_eps, s));
-    SSD_TRY(launch_gemm(dt, EPI_STORE_F32, c->xn, R * d.d_model, L.wqkv, nullptr, c->qkv, d.qkv_dim(), 0, M, d.qkv_dim(),
-                        d.d_model, s));
-    SSD_TRY(launch_rope_append(dt, c->qkv, c->rows, c->cos_sin, c->q, c->trunk_k[l], c->trunk_v[l], c->suffix_k[l],
-                               c->suffix_v[l], M, d.n_q_heads, d.n_kv_heads, d.head_dim, c->max_trunk, c->K, s));
+    if (dt == SSD_F32) {
+      SSD_TRY(launch_norm_qkv_rope_f32(c->h, (const float*)L.attn_norm, (const float*)L.wqkv, c->q, (float*)c->trunk_k[l],
+                                       (float*)c->trunk_v[l], (float*)c->suffix_k[l], (float*)c->suffix_v[l], c->rows, c->cos_sin,
+                                       M, d, c->max_trunk, c->K, s));
+    } else {
+      SSD_TRY(launch_rmsnorm(dt, c->h, L.attn_norm, c->xn, R * d.d_model, nullptr, 0, M, d.d_model, d.rms_eps, s));
+      SSD_TRY(launch_gemm(dt, EPI_STORE_F32, c->xn, R * d.d_model, L.wqkv, nullptr, c->qkv, d.qkv_dim(), 0, M, d.qkv_dim(),
+                          d.d_model, s));
+      SSD_TRY(launch_rope_append(dt, c->qkv, c->rows, c->cos_sin, c->q, c->trunk_k[l], c->trunk_v[l], c->suffix_k[l],
+                                 c->suffix_v[l], M, d.n_q_heads, d.n_kv_heads, d.head_dim, c->max_trunk, c->K, s));
+    }
     AttnArgs a;
     a.q = c->q; a.trunk_k = c->trunk_k[l]; a.trunk_v = c->trunk_v[l]; a.suffix_k = c->suffix_k[l];
     a.suffix_v = c->suffix_v[l]; a.out = c->attn_out; a.out_plane = R * d.q_dim(); a.rows = c->rows; a.partial = c->attn_partial; a.partial_floats = c->attn_partial_floats; a.M = M;
@@ -542,9 +548,14 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
     SSD_TRY(launch_attention(dt, a, s));
     SSD_TRY(launch_gemm(dt, EPI_RESIDUAL_ADD, c->attn_out, R * d.q_dim(), L.wo, nullptr, c->h, d.d_model, 0, M, d.d_model,
                         d.q_dim(), s));
-    SSD_TRY(launch_rmsnorm(dt, c->h, L.mlp_norm, c->xn, R * d.d_model, nullptr, 0, M, d.d_model, d.rms_eps, s));
-    SSD_TRY(launch_gemm(dt, EPI_SWIGLU, c->xn, R * d.d_model, L.w_gate, L.w_up, c->act, d.d_ffn, R * d.d_ffn, M, d.d_ffn,
-                        d.d_model, s));
+    if (dt == SSD_F32) {
+      SSD_TRY(launch_norm_swiglu_f32(c->h, (const float*)L.mlp_norm, (const float*)L.w_gate, (const float*)L.w_up, (float*)c->act, M,
+                                     d.d_ffn, d.d_model, d.rms_eps, s));
+    } else {
+      SSD_TRY(launch_rmsnorm(dt, c->h, L.mlp_norm, c->xn, R * d.d_model, nullptr, 0, M, d.d_model, d.rms_eps, s));
+      SSD_TRY(launch_gemm(dt, EPI_SWIGLU, c->xn, R * d.d_model, L.w_gate, L.w_up, c->act, d.d_ffn, R * d.d_ffn, M, d.d_ffn,
+                          d.d_model, s));
+    }
     SSD_TRY(launch_gemm(dt, EPI_RESIDUAL_ADD, c->act, R * d.d_ffn, L.w_down, nullptr, c->h, d.d_model, 0, M, d.d_model,
                         d.d_ffn, s));
   }
