@@ -111,9 +111,9 @@ int launch_setup_extend_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk
 int launch_embed(int dtype, const void* embed, const int32_t* tokens, float* h, int M, int d, int vocab, hipStream_t s);
 int launch_rmsnorm(int dtype, const float* h, const void* gain, void* xn, int64_t xn_plane, float* copy_out,
                    int64_t copy_ld, int M, int d, float eps, hipStream_t s);
-// Rotary embedding of q and k (fp32 [M][qkv_dim]) + write of q (activation dtype) and of the row's K/V
-// into the trunk or its private suffix.
-int launch_rope_append(int dtype, const float* qkv, const RowDesc* rows, const float* cos_sin, float* q_out,
+// bf16 models: rotary embedding of q and k (fp32 [M][qkv_dim]) + write of q (fp32) and of the row's K/V into the trunk or
+// its private suffix.
+int launch_rope_append(const float* qkv, const RowDesc* rows, const float* cos_sin, float* q_out,
                        void* trunk_k, void* trunk_v, void* suffix_k, void* suffix_v, int M, int n_q_heads,
                        int n_kv_heads, int head_dim, int max_trunk, int suffix_cap, hipStream_t s);
 int launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
@@ -164,6 +164,7 @@ struct AttnArgs {
   int64_t partial_floats;
   int M, n_q_heads, n_kv_heads, head_dim, max_trunk, suffix_cap;
   int rows_per_seq;      // rows of one sequence are consecutive
+  int extend;            // 1: rows of an extend (all keys in the trunk, every row sees one key more than the one before)
   int max_vis;           // host upper bound of any row's visible trunk length (grid sizing only)
 };
 int launch_attention(int dtype, const AttnArgs& a, hipStream_t s);

@@ -265,25 +265,225 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
   }
 }
 
-// One block per (row, query head), one thread per head dimension: the splits' partial softmaxes in split order.
+// One block per (row, query head), one thread per head dimension: the splits' partial softmaxes in split order.  The
+// splits' maxima and sums are one load of a wavefront (at most 64 splits), their weights go round through the lanes; the
+// outputs are requested 16 splits at a time (33 splits of 6 rows x 64 heads: 6.0 us, 7.0 before).
 template <typename T, int D>
 __global__ __launch_bounds__(D) void attention_merge_kernel(const float* __restrict__ partial, void* __restrict__ out,
                                                             int64_t out_plane, int n_splits) {
+  static_assert(kMaxSplits == 64, "a wavefront holds one split per lane");
   const int64_t pair = blockIdx.x;
-  const int d = threadIdx.x;
+  const int d = threadIdx.x, lane = threadIdx.x & 63;
   const float* pp = partial + pair * n_splits * (D + 2);
-  float m_max = -INFINITY;
-#pragma unroll 8
-  for (int s = 0; s < n_splits; ++s) m_max = fmaxf(m_max, pp[s * (D + 2)]);
+  const float ms = lane < n_splits ? pp[lane * (D + 2)] : -INFINITY, ls = lane < n_splits ? pp[lane * (D + 2) + 1] : 0.f;
+  float m_max = ms;
+  for (int o = 32; o > 0; o >>= 1) m_max = fmaxf(m_max, __shfl_xor(m_max, o));
+  const float w = ms == -INFINITY ? 0.f : expf(ms - m_max);
   float l = 0.f, o = 0.f;
-#pragma unroll 8
-  for (int s = 0; s < n_splits; ++s) {
-    const float ms = pp[s * (D + 2)];
-    const float w = ms == -INFINITY ? 0.f : expf(ms - m_max);
-    l += w * pp[s * (D + 2) + 1];
-    o += w * pp[s * (D + 2) + 2 + d];
+  for (int s0 = 0; s0 < n_splits; s0 += 16) {
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = pp[min(s0 + i, n_splits - 1) * (D + 2) + 2 + d];
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (s0 + i < n_splits) {
+        const float ws = __shfl(w, s0 + i);
+        l += ws * __shfl(ls, s0 + i);
+        o += ws * v[i];
+      }
   }
   Act<T>::store(out, out_plane, pair * D + d, o / l);
+}
+
+// Extends of bf16 models (the target's verification forward, a prefill chunk, a glue extend): every row of a sequence sees
+// the same trunk up to a point of its own, so a block serves 16 query rows (rows x query heads of the group) of (sequence, KV
+// head, split of the keys), 32 keys per wavefront and step, scores and outputs on MFMA (S^T = K Q^T, O^T = V^T P^T: a query row keeps its lane, and with the key rows of
+// the two 16-key score tiles interleaved a lane ends up with 8 consecutive keys, the B operand of the second product).
+// Queries and probabilities are three bf16 planes each, which is all 24 bits of their fp32 values: the products lose
+// nothing against fp32 arithmetic, the sums are fp32.  Values are read row by row, a lane the same D / 64 dimensions of
+// all 32 keys, and pass through LDS as V^T.  Keys past the last row any query row sees are not read (the last visible one
+// is, again, with weight 0).
+// What bounds it is latency, not bytes (16.8 MB of a 4096-token prefix of the 70B shape): everything a step loads is
+// requested before the queries are staged, and the planner gives a block one step where the chip has room.  6 rows x 64
+// heads x 4096 keys: 17.5 us (55.1 with a block per row, keys and values through the vector units).  One block for three
+// query tiles, which pulls the trunk once, took 27: twice the code, run once by every wavefront, and a third of the
+// wavefronts to hide its latencies behind.
+constexpr int kExtWaves = 4, kExtKeys = 32 * kExtWaves;   // keys of a block's step
+constexpr int kExtVt = 40;                                // V^T row in LDS: 32 keys + padding, 16-byte aligned
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+union Bf8 { bf16x8 v; __bf16 e[8]; u32x4 w; };
+
+// x = p[0] + p[1] + p[2], exactly (8 + 8 + 8 bits)
+__device__ __forceinline__ void split3(float x, __bf16& p0, __bf16& p1, __bf16& p2) {
+  p0 = (__bf16)x;
+  const float r = x - (float)p0;
+  p1 = (__bf16)r;
+  p2 = (__bf16)(r - (float)p1);
+}
+
+template <int D>
+constexpr size_t extend_lds_bytes() {
+  return (size_t)(D / 32) * 3 * 1024 + (size_t)kExtWaves * D * kExtVt * 2 + kExtWaves * 16 * 2 * sizeof(float);
+}
+
+template <int D>
+__global__ __launch_bounds__(256) void attention_extend_kernel(const float* __restrict__ q, const bf16_t* __restrict__ trunk_k,
+                                                                const bf16_t* __restrict__ trunk_v, void* __restrict__ out,
+                                                                int64_t out_plane, const RowDesc* __restrict__ rows, int n_q_heads,
+                                                                int n_kv_heads, int R, int max_trunk, float* __restrict__ partial,
+                                                                int keys_per_split, int n_splits) {
+  constexpr int KS = D / 32, DT = D / 16, NE = D / 64;
+  extern __shared__ char lds[];
+  bf16x8* q_s = (bf16x8*)lds;                                            // [KS][3][64]
+  bf16_t* vt_all = (bf16_t*)(lds + (size_t)KS * 3 * 1024);          // [wave][D][kExtVt]
+  float* ml = (float*)((char*)vt_all + (size_t)kExtWaves * D * kExtVt * 2);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, g4 = lane >> 4;
+  const int hk = blockIdx.x % n_kv_heads, split = blockIdx.x / n_kv_heads;
+  const int qt = blockIdx.y, row0 = blockIdx.z * R;
+  const int group = n_q_heads / n_kv_heads, RG = R * group;
+  const int64_t kv_stride = (int64_t)n_kv_heads * D;
+  const RowDesc last = rows[row0 + R - 1];                               // an extend's rows are causal: the last sees most
+  const bf16_t* tk = trunk_k + (int64_t)last.seq * max_trunk * kv_stride + hk * D;
+  const bf16_t* tv = trunk_v + (int64_t)last.seq * max_trunk * kv_stride + hk * D;
+  const int j_end = min(last.vis, (split + 1) * keys_per_split);
+  bf16_t* vt_s = vt_all + wave * D * kExtVt;
+
+  const int vis = qt * 16 + li < RG ? rows[row0 + (qt * 16 + li) / group].vis : 0;   // keys this lane's query row sees
+  bf16x8 kr[2][KS];
+  uint32_t vr[32];                                                       // this lane's NE dimensions of 32 keys
+  const int krow = (li >> 2) * 8 + (li & 3);
+  auto load_kv = [&](int kb) {
+#pragma unroll
+    for (int tile = 0; tile < 2; ++tile) {
+      const bf16_t* kp = tk + (int64_t)min(kb + krow + tile * 4, last.vis - 1) * kv_stride + g4 * 8;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) kr[tile][ks] = *(const bf16x8*)(kp + ks * 32);
+    }
+#pragma unroll
+    for (int k = 0; k < 32; ++k) {
+      const bf16_t* vp = tv + (int64_t)min(kb + k, last.vis - 1) * kv_stride + lane * NE;
+      vr[k] = NE == 2 ? *(const uint32_t*)vp : (uint32_t)*vp;
+    }
+  };
+  int kb = split * keys_per_split + wave * 32;
+  if (kb < j_end) load_kv(kb);
+
+  // ---- queries: scaled, three planes, in B-operand order
+  const float scale = rsqrtf((float)D);
+  for (int it = threadIdx.x; it < KS * 64; it += 256) {
+    const int l = it & 63, ks = it >> 6;
+    const int qr = min(qt * 16 + (l & 15), RG - 1);
+    const int rr = qr / group;
+    const float* src = q + ((int64_t)(row0 + rr) * n_q_heads + hk * group + (qr - rr * group)) * D + ks * 32 + (l >> 4) * 8;
+    const f32x4 x0 = *(const f32x4*)src, x1 = *(const f32x4*)(src + 4);
+    Bf8 p[3];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) split3((e < 4 ? x0[e & 3] : x1[e & 3]) * scale, p[0].e[e], p[1].e[e], p[2].e[e]);
+#pragma unroll
+    for (int pl = 0; pl < 3; ++pl) q_s[(ks * 3 + pl) * 64 + l] = p[pl].v;
+  }
+  __syncthreads();
+
+  f32x4 acc[DT];
+  float m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) acc[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (; kb < j_end; kb += kExtKeys) {
+    // V^T of the wavefront's 32 keys through LDS (its own part: no barrier)
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+#pragma unroll
+      for (int k8 = 0; k8 < 4; ++k8) {
+        u32x4 w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const uint32_t a = vr[k8 * 8 + 2 * i] >> (16 * e), b = vr[k8 * 8 + 2 * i + 1] >> (16 * e);
+          w[i] = (a & 0xffffu) | (b << 16);
+        }
+        *(u32x4*)(vt_s + (lane * NE + e) * kExtVt + k8 * 8) = w;
+      }
+    Bf8 pp[3];
+    f32x4 S[2] = {(f32x4){0.f, 0.f, 0.f, 0.f}, (f32x4){0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int pl = 2; pl >= 0; --pl)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        const bf16x8 qb = q_s[(ks * 3 + pl) * 64 + lane];
+#pragma unroll
+        for (int tile = 0; tile < 2; ++tile) S[tile] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[tile][ks], qb, S[tile], 0, 0, 0);
+      }
+    float sv[8], mx = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int key = kb + g4 * 8 + e;
+      sv[e] = key < min(vis, j_end) ? (e < 4 ? S[0][e & 3] : S[1][e & 3]) : -INFINITY;
+      mx = fmaxf(mx, sv[e]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m_run, mx), m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float corr = expf(m_run - m_use);
+    m_run = m_new;
+    l_run *= corr;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) acc[dt] = acc[dt] * corr;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float pe = expf(sv[e] - m_use);
+      l_run += pe;
+      split3(pe, pp[0].e[e], pp[1].e[e], pp[2].e[e]);
+    }
+    if (kb + kExtKeys < j_end) load_kv(kb + kExtKeys);
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const bf16x8 vt = *(const bf16x8*)(vt_s + (dt * 16 + li) * kExtVt + g4 * 8);
+#pragma unroll
+      for (int pl = 2; pl >= 0; --pl) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pp[pl].v, acc[dt], 0, 0, 0);
+    }
+  }
+  // ---- the wavefronts' partial softmaxes meet in LDS, where V^T was
+  f32x4* mrg = (f32x4*)vt_all;                                           // [wave][DT][64]
+  static_assert((size_t)DT * 64 * 16 <= (size_t)D * kExtVt * 2, "a wavefront's tile fits where its V^T was");
+  l_run += __shfl_xor(l_run, 16);
+  l_run += __shfl_xor(l_run, 32);
+  __syncthreads();
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) mrg[(wave * DT + dt) * 64 + lane] = acc[dt];
+  if (g4 == 0) {
+    ml[(wave * 16 + li) * 2] = m_run;
+    ml[(wave * 16 + li) * 2 + 1] = l_run;
+  }
+  __syncthreads();
+  const int qi = threadIdx.x & 15, qr = qt * 16 + qi;
+  float mmax = -INFINITY, lsum = 0.f, wgt[kExtWaves];
+#pragma unroll
+  for (int w = 0; w < kExtWaves; ++w) mmax = fmaxf(mmax, ml[(w * 16 + qi) * 2]);
+#pragma unroll
+  for (int w = 0; w < kExtWaves; ++w) {
+    wgt[w] = mmax == -INFINITY ? 0.f : expf(ml[(w * 16 + qi) * 2] - mmax);
+    lsum += wgt[w] * ml[(w * 16 + qi) * 2 + 1];
+  }
+  if (qr < RG) {
+    const int rr = qr / group;
+    const int64_t pair = (int64_t)(row0 + rr) * n_q_heads + hk * group + (qr - rr * group);
+    float* pp = partial + (pair * n_splits + split) * (D + 2);
+    for (int dq = threadIdx.x >> 4; dq < D / 4; dq += 16) {
+      f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kExtWaves; ++w) o += mrg[(w * DT + (dq >> 2)) * 64 + qi + 16 * (dq & 3)] * wgt[w];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (n_splits > 1) pp[2 + dq * 4 + e] = o[e];
+        else Act<bf16_t>::store(out, out_plane, pair * D + dq * 4 + e, o[e] / lsum);
+      }
+    }
+    if (n_splits > 1 && (threadIdx.x >> 4) == 0) {
+      pp[0] = mmax;                                                    // -inf for a split without keys
+      pp[1] = lsum;
+    }
+  }
 }
 
 // Splits of at most kSplitKeys keys, and with few rows enough of them for about 1024 blocks (none shorter than 64
@@ -303,6 +503,30 @@ int choose_splits(const AttnArgs& a, int* keys_per_split) {
   if (n > kMaxSplits || (int64_t)a.M * a.n_q_heads * n * (a.head_dim + 2) > a.partial_floats) return 1;
   *keys_per_split = ((max_keys + n - 1) / n + 63) / 64 * 64;
   return n;
+}
+
+// The extend kernel's launch: splits of whole steps, as many as give the chip four blocks per compute unit (6 rows x 64
+// heads x 4096 keys: 33 splits of one step, 17.5 us), no more than the merge and the scratch hold.
+template <int D>
+int launch_extend(const AttnArgs& a, hipStream_t s) {
+  const int group = a.n_q_heads / a.n_kv_heads, n_seq = a.M / a.rows_per_seq;
+  const int qt = (a.rows_per_seq * group + 15) / 16;
+  const int64_t blocks = (int64_t)n_seq * a.n_kv_heads * qt;
+  const int steps = ((a.max_vis > 1 ? a.max_vis : 1) + kExtKeys - 1) / kExtKeys;
+  int64_t n = blocks < 1024 ? 1024 / blocks : 1;
+  if (n > steps) n = steps;
+  if (n > kMaxSplits) n = kMaxSplits;
+  while (n > 1 && (!a.partial || (int64_t)a.M * a.n_q_heads * n * (D + 2) > a.partial_floats)) --n;
+  const int keys_per_split = (int)((steps + n - 1) / n) * kExtKeys;
+  const int n_splits = (steps * kExtKeys + keys_per_split - 1) / keys_per_split;
+  static_assert(extend_lds_bytes<D>() <= 64 * 1024, "within the LDS a kernel gets without asking");
+  attention_extend_kernel<D><<<dim3(a.n_kv_heads * n_splits, qt, n_seq), 256, extend_lds_bytes<D>(), s>>>(
+      a.q, (const bf16_t*)a.trunk_k, (const bf16_t*)a.trunk_v, a.out, a.out_plane, a.rows, a.n_q_heads, a.n_kv_heads, a.rows_per_seq,
+      a.max_trunk, a.partial, keys_per_split, n_splits);
+  SSD_HIP(hipGetLastError());
+  if (n_splits > 1) attention_merge_kernel<bf16_t, D><<<a.M * a.n_q_heads, D, 0, s>>>(a.partial, a.out, a.out_plane, n_splits);
+  SSD_HIP(hipGetLastError());
+  return SSD_OK;
 }
 
 template <typename T, int D>
@@ -335,6 +559,13 @@ int launch_rowwise_d(const AttnArgs& a, hipStream_t s) {
 
 template <typename T>
 int launch_rowwise(const AttnArgs& a, hipStream_t s) {
+  if constexpr (sizeof(T) == 2) {
+    // bf16 extends; the grid's second and third dimensions count query tiles and sequences
+    if (a.extend && a.M / a.rows_per_seq <= 65535 && (int64_t)a.rows_per_seq * (a.n_q_heads / a.n_kv_heads) <= 16 * 65535) {
+      if (a.head_dim == 64) return launch_extend<64>(a, s);
+      if (a.head_dim == 128) return launch_extend<128>(a, s);
+    }
+  }
   if (a.head_dim == 64) return launch_rowwise_d<T, 64>(a, s);
   if (a.head_dim == 128) return launch_rowwise_d<T, 128>(a, s);
   set_error("head_dim %d not supported (64 or 128)", a.head_dim);

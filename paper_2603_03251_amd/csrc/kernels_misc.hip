@@ -65,11 +65,20 @@ __global__ void setup_extend_rows_kernel(RowDesc* rows, float* cos_sin, const in
 
 template <typename T>
 __global__ void embed_kernel(const T* embed, const int32_t* tokens, float* h, int M, int d, int vocab) {
-  int m = blockIdx.x;
+  const int m = blockIdx.x, c = ((int)blockIdx.y * kBlock + (int)threadIdx.x) * 4;   // (d is a multiple of 4)
+  if (c >= d) return;
   int tok = tokens[m];
   tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);
-  const T* src = embed + (int64_t)tok * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) h[(int64_t)m * d + c] = Elem<T>::load(src + c);
+  const T* src = embed + (int64_t)tok * d + c;
+  float4 v;
+  if constexpr (sizeof(T) == 2) {
+    const uint2 w = *(const uint2*)src;
+    v = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
+                    __uint_as_float(w.y & 0xffff0000u));
+  } else {
+    v = *(const float4*)src;
+  }
+  *(float4*)(h + (int64_t)m * d + c) = v;
 }
 
 __device__ __forceinline__ float block_sum(float v, float* smem) {
@@ -83,12 +92,14 @@ __device__ __forceinline__ float block_sum(float v, float* smem) {
   return t;
 }
 
-// x / sqrt(mean(x^2) + eps) * gain, one block per row.  The row is read once, four elements per thread and step,
+// x / sqrt(mean(x^2) + eps) * gain, one block per row (of 1024 threads where that is at most one step of four elements each:
+// 6 rows of 8192 take 5.5 us, 7.5 with 256 threads).  The row is read once, four elements per thread and step,
 // with the loads of up to 8 steps issued together (a row of 8192 is then one memory latency, not 32).
+constexpr int kNormBlock = 1024;
 template <typename T>
-__global__ void rmsnorm_kernel(const float* __restrict__ h, const T* __restrict__ gain, void* __restrict__ xn, int64_t xn_plane,
+__global__ __launch_bounds__(kNormBlock) void rmsnorm_kernel(const float* __restrict__ h, const T* __restrict__ gain, void* __restrict__ xn, int64_t xn_plane,
                                float* __restrict__ copy_out, int64_t copy_ld, int d, float eps) {
-  __shared__ float smem[kBlock / 64];
+  __shared__ float smem[kNormBlock / 64];
   const int m = blockIdx.x;
   const float* row = h + (int64_t)m * d;
   constexpr int kHeld = 8;                      // float4 per thread kept in registers
@@ -163,56 +174,42 @@ __global__ void rmsnorm_kernel(const float* __restrict__ h, const T* __restrict_
   }
 }
 
-// Rotary embedding (pair (i, i + D/2)) of the q and k heads of one row; q goes out in the activation type,
-// k and v go to the row's KV slot (trunk position or private suffix depth).
-template <typename T>
-__global__ void rope_append_kernel(const float* __restrict__ qkv, const RowDesc* __restrict__ rows, const float* __restrict__ cos_sin,
-                                   float* __restrict__ q_out, T* __restrict__ trunk_k, T* __restrict__ trunk_v,
-                                   T* __restrict__ suffix_k, T* __restrict__ suffix_v, int n_q_heads, int n_kv_heads, int head_dim,
-                                   int max_trunk, int suffix_cap) {
-  int m = blockIdx.x;
-  RowDesc r = rows[m];
-  int half = head_dim >> 1;
-  int qd = n_q_heads * head_dim, kvd = n_kv_heads * head_dim;
+// bf16 models: rotary embedding (pair (i, i + D/2)) of the q and k heads; q goes out in fp32, k and v to the row's KV slot
+// (trunk position or private suffix depth).  grid = (row, share of the row's pairs and value elements), one item per
+// thread: a row of the 70B shape is 5632 items, which in one block of 256 threads were a chain of batches (6 rows: 8.2 us, 4.8 now).
+__global__ __launch_bounds__(kBlock) void rope_append_kernel(const float* __restrict__ qkv, const RowDesc* __restrict__ rows,
+                                                              const float* __restrict__ cos_sin, float* __restrict__ q_out,
+                                                              bf16_t* __restrict__ trunk_k, bf16_t* __restrict__ trunk_v,
+                                                              bf16_t* __restrict__ suffix_k, bf16_t* __restrict__ suffix_v,
+                                                              int n_q_heads, int n_kv_heads, int head_dim, int max_trunk,
+                                                              int suffix_cap) {
+  const int m = blockIdx.x, half = head_dim >> 1;
+  const int qd = n_q_heads * head_dim, kvd = n_kv_heads * head_dim;
+  const int n_rot = (n_q_heads + n_kv_heads) * half;
+  const int idx = blockIdx.y * kBlock + threadIdx.x;
+  if (idx >= n_rot + kvd) return;
+  const RowDesc r = rows[m];
   const float* src = qkv + (int64_t)m * (qd + 2 * kvd);
-  int64_t kv_row = r.is_branch ? ((int64_t)m * suffix_cap + r.kv_slot) : ((int64_t)r.seq * max_trunk + r.kv_slot);
-  T* kdst = (r.is_branch ? suffix_k : trunk_k) + kv_row * kvd;
-  T* vdst = (r.is_branch ? suffix_v : trunk_v) + kv_row * kvd;
-  const float* cs = cos_sin + (int64_t)m * half * 2;
-  int n_rot = (n_q_heads + n_kv_heads) * half;
-  // items in batches whose loads go out together (a 70B-shaped row has 18 items per thread: one at a time they were 18
-  // memory round trips); the input and the outputs never overlap, which the qualifiers above tell the compiler
-  constexpr int kBatch = 6;
-  for (int idx0 = threadIdx.x; idx0 < n_rot; idx0 += blockDim.x * kBatch) {
-    float a[kBatch], b[kBatch], c[kBatch], sn[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int idx = min(idx0 + u * (int)blockDim.x, n_rot - 1);
-      const int head = idx / half, i = idx % half;
-      const float* hsrc = src + head * head_dim;   // q heads then k heads are contiguous in qkv
-      c[u] = cs[i * 2];
-      sn[u] = cs[i * 2 + 1];
-      a[u] = hsrc[i];
-      b[u] = hsrc[i + half];
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int idx = idx0 + u * (int)blockDim.x;
-      if (idx >= n_rot) break;
-      const int head = idx / half, i = idx % half;
-      const float ra = a[u] * c[u] - b[u] * sn[u], rb = b[u] * c[u] + a[u] * sn[u];
-      if (head < n_q_heads) {
-        float* dst = q_out + (int64_t)m * qd + head * head_dim;
-        dst[i] = ra;
-        dst[i + half] = rb;
-      } else {
-        T* dst = kdst + (head - n_q_heads) * head_dim;
-        Elem<T>::store(dst + i, ra);
-        Elem<T>::store(dst + i + half, rb);
-      }
-    }
+  const int64_t kv_row = r.is_branch ? ((int64_t)m * suffix_cap + r.kv_slot) : ((int64_t)r.seq * max_trunk + r.kv_slot);
+  if (idx >= n_rot) {
+    const int c = idx - n_rot;
+    Elem<bf16_t>::store((r.is_branch ? suffix_v : trunk_v) + kv_row * kvd + c, src[qd + kvd + c]);
+    return;
   }
-  for (int c = threadIdx.x; c < kvd; c += blockDim.x) Elem<T>::store(vdst + c, src[qd + kvd + c]);
+  const int head = idx / half, i = idx % half;
+  const float* hsrc = src + head * head_dim;   // q heads then k heads are contiguous in qkv
+  const float c = cos_sin[((int64_t)m * half + i) * 2], sn = cos_sin[((int64_t)m * half + i) * 2 + 1];
+  const float a = hsrc[i], b = hsrc[i + half];
+  const float ra = a * c - b * sn, rb = b * c + a * sn;
+  if (head < n_q_heads) {
+    float* dst = q_out + (int64_t)m * qd + head * head_dim;
+    dst[i] = ra;
+    dst[i + half] = rb;
+  } else {
+    bf16_t* dst = (r.is_branch ? suffix_k : trunk_k) + kv_row * kvd + (head - n_q_heads) * head_dim;
+    Elem<bf16_t>::store(dst + i, ra);
+    Elem<bf16_t>::store(dst + i + half, rb);
+  }
 }
 
 // p[0 .. n-1] = v
@@ -292,33 +289,31 @@ int launch_setup_extend_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk
 }
 
 int launch_embed(int dtype, const void* embed, const int32_t* tokens, float* h, int M, int d, int vocab, hipStream_t s) {
-  if (dtype == SSD_BF16) embed_kernel<bf16_t><<<M, kBlock, 0, s>>>((const bf16_t*)embed, tokens, h, M, d, vocab);
-  else embed_kernel<float><<<M, kBlock, 0, s>>>((const float*)embed, tokens, h, M, d, vocab);
+  const dim3 grid(M, (d / 4 + kBlock - 1) / kBlock);
+  if (dtype == SSD_BF16) embed_kernel<bf16_t><<<grid, kBlock, 0, s>>>((const bf16_t*)embed, tokens, h, M, d, vocab);
+  else embed_kernel<float><<<grid, kBlock, 0, s>>>((const float*)embed, tokens, h, M, d, vocab);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }
 
 int launch_rmsnorm(int dtype, const float* h, const void* gain, void* xn, int64_t xn_plane, float* copy_out,
                    int64_t copy_ld, int M, int d, float eps, hipStream_t s) {
+  const int block = d >= 4 * kNormBlock ? kNormBlock : kBlock;
   if (dtype == SSD_BF16)
-    rmsnorm_kernel<bf16_t><<<M, kBlock, 0, s>>>(h, (const bf16_t*)gain, xn, xn_plane, copy_out, copy_ld, d, eps);
+    rmsnorm_kernel<bf16_t><<<M, block, 0, s>>>(h, (const bf16_t*)gain, xn, xn_plane, copy_out, copy_ld, d, eps);
   else
-    rmsnorm_kernel<float><<<M, kBlock, 0, s>>>(h, (const float*)gain, xn, xn_plane, copy_out, copy_ld, d, eps);
+    rmsnorm_kernel<float><<<M, block, 0, s>>>(h, (const float*)gain, xn, xn_plane, copy_out, copy_ld, d, eps);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }
 
-int launch_rope_append(int dtype, const float* qkv, const RowDesc* rows, const float* cos_sin, float* q_out,
+int launch_rope_append(const float* qkv, const RowDesc* rows, const float* cos_sin, float* q_out,
                        void* trunk_k, void* trunk_v, void* suffix_k, void* suffix_v, int M, int n_q_heads,
                        int n_kv_heads, int head_dim, int max_trunk, int suffix_cap, hipStream_t s) {
-  if (dtype == SSD_BF16)
-    rope_append_kernel<bf16_t><<<M, kBlock, 0, s>>>(qkv, rows, cos_sin, q_out, (bf16_t*)trunk_k,
-                                                    (bf16_t*)trunk_v, (bf16_t*)suffix_k, (bf16_t*)suffix_v, n_q_heads,
-                                                    n_kv_heads, head_dim, max_trunk, suffix_cap);
-  else
-    rope_append_kernel<float><<<M, kBlock, 0, s>>>(qkv, rows, cos_sin, q_out, (float*)trunk_k, (float*)trunk_v,
-                                                   (float*)suffix_k, (float*)suffix_v, n_q_heads, n_kv_heads, head_dim,
-                                                   max_trunk, suffix_cap);
+  const int items = (n_q_heads + n_kv_heads) * (head_dim / 2) + n_kv_heads * head_dim;
+  rope_append_kernel<<<dim3(M, (items + kBlock - 1) / kBlock), kBlock, 0, s>>>(
+      qkv, rows, cos_sin, q_out, (bf16_t*)trunk_k, (bf16_t*)trunk_v, (bf16_t*)suffix_k, (bf16_t*)suffix_v, n_q_heads, n_kv_heads,
+      head_dim, max_trunk, suffix_cap);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }

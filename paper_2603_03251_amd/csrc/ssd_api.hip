@@ -535,14 +535,14 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
       SSD_TRY(launch_rmsnorm(dt, c->h, L.attn_norm, c->xn, R * d.d_model, nullptr, 0, M, d.d_model, d.rms_eps, s));
       SSD_TRY(launch_gemm(dt, EPI_STORE_F32, c->xn, R * d.d_model, L.wqkv, nullptr, c->qkv, d.qkv_dim(), 0, M, d.qkv_dim(),
                           d.d_model, s));
-      SSD_TRY(launch_rope_append(dt, c->qkv, c->rows, c->cos_sin, c->q, c->trunk_k[l], c->trunk_v[l], c->suffix_k[l],
+      SSD_TRY(launch_rope_append(c->qkv, c->rows, c->cos_sin, c->q, c->trunk_k[l], c->trunk_v[l], c->suffix_k[l],
                                  c->suffix_v[l], M, d.n_q_heads, d.n_kv_heads, d.head_dim, c->max_trunk, c->K, s));
     }
     AttnArgs a;
     a.q = c->q; a.trunk_k = c->trunk_k[l]; a.trunk_v = c->trunk_v[l]; a.suffix_k = c->suffix_k[l];
     a.suffix_v = c->suffix_v[l]; a.out = c->attn_out; a.out_plane = R * d.q_dim(); a.rows = c->rows; a.partial = c->attn_partial; a.partial_floats = c->attn_partial_floats; a.M = M;
     a.n_q_heads = d.n_q_heads; a.n_kv_heads = d.n_kv_heads; a.head_dim = d.head_dim; a.max_trunk = c->max_trunk;
-    a.suffix_cap = c->K; a.rows_per_seq = rows_per_seq;
+    a.suffix_cap = c->K; a.rows_per_seq = rows_per_seq; a.extend = branch_depth < 0;
     // here the tokens of an extend are trunk positions too (they are appended before the attention runs)
     a.max_vis = max_vis + (branch_depth < 0 ? rows_per_seq : 0);
     SSD_TRY(launch_attention(dt, a, s));

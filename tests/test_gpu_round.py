@@ -385,6 +385,20 @@ def test_small_bf16_head_dim_128_untied(B):
     _run_round_parity(B, SMALL_BF16_D128, batch=1, P=70, K=2, F=2, seed=9, synthetic_kv=True)
 
 
+@pytest.mark.parametrize("shape,batch,P,K", [
+    # head_dim 128, group 8: 2 and 4 query tiles of a block, one split; keys that end inside a wavefront's first block
+    (SMALL_BF16_D128, 1, 3, 2), (SMALL_BF16_D128, 2, 125, 6),
+    # head_dim 64: groups of query tiles (16 rows x group 8 = 8 tiles in two groups), several splits, ragged end
+    (_small(n_kv_heads=1), 1, 1001, 15),
+    # two KV heads, three sequences, more splits than 16; 3 x 5 = 15 rows in a full-precision 16-row tile
+    (_small(), 3, 2083, 4),
+])
+def test_bf16_extends_of_the_per_operator_path(B, shape, batch, P, K):
+    """The attention of an extend (all rows of a sequence share the stored keys) and linear layers of at most 8 and of more
+    rows, through the round's glue logits and K/V appended by it, which the branch rows read."""
+    _run_round_parity(B, shape, batch=batch, P=P, K=K, F=1, seed=41, synthetic_kv=True, flags=B.SSD_CTX_PER_OPERATOR)
+
+
 def test_small_bf16_geometric_cache_shape(B):
     """Sec. 4.1.2: a round whose fan-out follows the theorem's geometric shape; the library's integer shape equals the
     oracle's, the rows run accept length by accept length, and the fused pass serves the 13 rows per sequence."""
