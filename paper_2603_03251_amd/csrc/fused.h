@@ -16,6 +16,7 @@ constexpr int kFusedMaxRows = 48;   // rows of one narrow pass (three 16-row MFM
 constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles): contexts with more than kFusedMaxRows rows
 constexpr int kFusedWideQueryTiles = 3;   // wide passes: query tiles per attention unit (n_attn_units counts such units)
 constexpr int kFusedWideFreshKeys = 192;  // wide passes: tokens of one sequence an extend pass takes (LDS room of the attention unit)
+constexpr int kFusedWideSlices = 8;       // wide passes: most k-slices of the o- and down-projections (one per XCD)
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())
 constexpr int kFusedMaxSlices = 4;   // most k-slices of a linear layer
 constexpr unsigned kFusedSpinLimit = 4000000u;   // polls of a bounded wait (seconds of wall time) before it gives up
@@ -77,7 +78,8 @@ struct FusedParams {
   bf16_t* att;     // [L][2][48*qd]    attention output planes, B-operand order
   bf16_t* act;     // [L][planes][48*ffn]
   float* fix_buf;  // [L][3][fix_stride]  partial tiles of K-split linear layers (qkv, o, down); every word holds
-                   // 0xffffffff ("not written yet") between launches: the reader of a tile puts that value back
+                   // 0xffffffff ("not written yet") between launches: the reader of a tile puts that value back.
+                   // Wide passes: [kFusedWideSlices][M][d] partial sums of the o- and down-projections' k-slices
   int64_t fix_stride;
   float* part_o;   // [L][B][Hkv][NS][QT*16][64]  partial softmaxes of the key splits (NS > 1 only)
   float* part_ml;  // [L][B][Hkv][NS][QT*16][2]

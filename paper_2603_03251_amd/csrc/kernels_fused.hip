@@ -296,7 +296,7 @@ __device__ __forceinline__ void resid_store(const FusedParams& p, f32x4 hn, int 
 }
 
 // ---------------------------------------------------------------------------------------------- linear layers
-enum { FE_QKV = 0, FE_RESID = 1, FE_SWIGLU = 2, FE_LOGITS = 3 };
+enum { FE_QKV = 0, FE_RESID = 1, FE_SWIGLU = 2, FE_LOGITS = 3, FE_PART = 4 };   // FE_PART: wide passes only
 
 struct EpiArgs {
   float* out;          // QKV: [M][ld] raw projections; LOGITS: [M][ld] logits
@@ -1095,339 +1095,6 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
   return true;
 }
 
-// The attention unit of the wide passes: NQ query tiles of one (sequence, KV head, key split) share every stored key
-// and value block the unit pulls (a wide pass has 6 and more query tiles per sequence and head: units of one tile would
-// pull the same trunk once per tile, and what bounds them is that pull, not their arithmetic).  Same method and same
-// layouts as attn_unit; the qkv projections arrive with the norm's row scale applied.  Fresh keys: those of all the
-// unit's query tiles (branch rows) or the pass's tokens (extend rows), staged once, NFI items per thread.
-constexpr int kMultiFreshKeys = kFusedWideFreshKeys;   // LDS room: NQ x (rows per tile x slots per row) for NQ = 3, or the tokens of an extend
-template <int MT, int MP, int NPQ, int NPP, int NQ, bool PG>
-__device__ __forceinline__ void attn_unit_multi(const FusedParams& p, const FusedLayer& L, const float* qkv, int unit, f32x4* lds,
-                                                bf16_t* att_out, float* part_o, float* part_ml, int ph) {
-  const ThreadIds ids = fresh_thread_ids();
-  const int lane = ids.lane, wave = ids.wave;
-  const int li = lane & 15, g4 = lane >> 4;
-  const int QG = (p.QT + NQ - 1) / NQ;        // groups of query tiles per (sequence, KV head)
-  const int hk = unit % p.Hkv;
-  int rem = unit / p.Hkv;
-  const int qg = rem % QG;
-  rem /= QG;
-  const int s = rem % p.NS, b = rem / p.NS;
-  const int g_log = 31 - __builtin_clz(p.G), sl_log = p.SL == 8 ? 3 : 4;   // G and SL are powers of two
-  const int RG = p.R << g_log;
-  const bool is_branch = p.is_branch != 0;
-  const gfloat* gq = (const gfloat*)qkv;
-  const gfloat* gcs = (const gfloat*)p.cos_sin;
-  int qt[NQ], m[NQ], rloc[NQ];
-  bool vq[NQ];
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    qt[i] = qg * NQ + i;
-    const int qr = qt[i] * 16 + li;
-    vq[i] = qr < RG;
-    const int qrc = vq[i] ? qr : RG - 1;
-    rloc[i] = qrc >> g_log;
-    m[i] = b * p.R + rloc[i];
-  }
-
-  // ---- issue: the first trunk blocks of this wavefront (block counts from the host's bound)
-  const int kb0 = s * p.KPU;
-  const int kend_ub = min(kb0 + p.KPU, p.tv_ub);
-  const int n_tb = kend_ub > kb0 ? (kend_ub - kb0 + 31) >> 5 : 0;
-  const int n_mine = n_tb > wave ? (n_tb - wave + kFusedWaves - 1) / kFusedWaves : 0;
-  const int rpt = 16 >> g_log;                                // rows per query tile
-  const int n_fresh_keys = is_branch ? (NQ * rpt) << sl_log : p.R;
-  const int n_fb = s == 0 ? (n_fresh_keys + 31) >> 5 : 0;
-  const int krow = (li >> 2) * 8 + (li & 3);                  // key of this lane's A-operand row in a block (tile 0)
-  // PG (paged trunk, App. B "PagedAttention"): block j of sequence b is page p.pages[b][j] of a pool shared by all
-  // sequences, a page = the same 4 KiB per head and operand as a block of the contiguous layouts.  Lane i of a wavefront
-  // fetches the page of the wavefront's i-th block up front (one load), so the block loop itself stays free of
-  // dependent loads; entries behind a sequence's allocation name page 0, which exists and holds zeros.
-  const int64_t head0 = PG ? 0 : ((int64_t)(b * p.Hkv + hk) * p.vt_stride) * 64;
-  const gbf16* kbase = (const gbf16*)L.trunk_k + head0 + g4 * 8;
-  const gbf16* vbase = (const gbf16*)L.trunk_vt + head0 + li * 32 + g4 * 8;
-  int pgs = 0;
-  if constexpr (PG) pgs = p.pages[(int64_t)b * p.page_stride + min((kb0 >> 5) + wave + kFusedWaves * lane, p.page_stride - 1)];
-  struct TrunkBlock {
-    bf16x8 k[2][2];
-    bf16x8 vt[4];
-  };
-  constexpr int RING = 2;
-  TrunkBlock ring[RING];
-  auto load_trunk = [&](TrunkBlock& tb, int i) {   // i-th block of this wavefront, clamped to its last one
-    const int ic = max(min(i, n_mine - 1), 0);
-    const int blk = wave + kFusedWaves * ic;
-    const int kb = min(kb0 + blk * 32, p.vt_stride - 32);
-    const int64_t bo = PG ? ((int64_t)__builtin_amdgcn_readlane(pgs, ic) * p.Hkv + hk) * 2048 : (int64_t)kb * 64;
-#pragma unroll
-    for (int tile = 0; tile < 2; ++tile) {
-      const gbf16* kp = kbase + bo + (krow + tile * 4) * 64;
-      tb.k[tile][0] = *(const gbf16x8*)kp;
-      tb.k[tile][1] = *(const gbf16x8*)(kp + 32);
-    }
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) tb.vt[dt] = *(const gbf16x8*)(vbase + bo + dt * 16 * 32);
-  };
-#pragma unroll
-  for (int i = 0; i < RING; ++i) load_trunk(ring[i], i);   // unconditional (a wavefront without blocks re-reads block 0)
-  stamp(p, ph, 3);
-
-  // ---- Q operands of the NQ tiles: dims g4*8..+7 (k-step 0) and 32+g4*8..+7 (k-step 1) of this lane's query rows,
-  // rotated and scaled
-  // (the loads of all NQ tiles go out before the first is used: one memory round trip instead of one per tile; the
-  // scheduling barrier keeps the compiler from sinking them back next to their uses)
-  int tv[NQ];
-  Bf8 qh[NQ][2], ql[NQ][2];
-  RowDesc rdv[NQ];
-  f32x4 qraw[NQ][4], qcsv[NQ][4];
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    rdv[i] = p.rows[m[i]];
-    const int qrc = vq[i] ? qt[i] * 16 + li : RG - 1;
-    const int hq = hk * p.G + (qrc & (p.G - 1));
-    const gfloat* qp = gq + (int64_t)m[i] * p.qkvd + hq * 64 + g4 * 8;
-    qraw[i][0] = *(const gf32x4*)qp;
-    qraw[i][1] = *(const gf32x4*)(qp + 4);
-    qraw[i][2] = *(const gf32x4*)(qp + 32);
-    qraw[i][3] = *(const gf32x4*)(qp + 36);
-    const gfloat* qcs = gcs + ((int64_t)m[i] * 32 + g4 * 8) * 2;
-#pragma unroll
-    for (int c4 = 0; c4 < 4; ++c4) qcsv[i][c4] = *(const gf32x4*)(qcs + 4 * c4);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    const RowDesc rd = rdv[i];
-    const f32x4 qa0 = qraw[i][0], qa1 = qraw[i][1], qb0 = qraw[i][2], qb1 = qraw[i][3];
-    const f32x4 qc0 = qcsv[i][0], qc1 = qcsv[i][1], qc2 = qcsv[i][2], qc3 = qcsv[i][3];
-    tv[i] = vq[i] ? trunk_visible(rd, m[i], p.R) : 0;
-    const float a[8] = {qa0[0], qa0[1], qa0[2], qa0[3], qa1[0], qa1[1], qa1[2], qa1[3]};
-    const float bb[8] = {qb0[0], qb0[1], qb0[2], qb0[3], qb1[0], qb1[1], qb1[2], qb1[3]};
-    const float cc[16] = {qc0[0], qc0[1], qc0[2], qc0[3], qc1[0], qc1[1], qc1[2], qc1[3],
-                          qc2[0], qc2[1], qc2[2], qc2[3], qc3[0], qc3[1], qc3[2], qc3[3]};
-    const float scale = 0.125f * kLog2e;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float c = cc[2 * e], sn = cc[2 * e + 1];
-      const float x0 = (a[e] * c - bb[e] * sn) * scale, x1 = (bb[e] * c + a[e] * sn) * scale;
-      qh[i][0].u[e] = to_bf16(x0);
-      qh[i][1].u[e] = to_bf16(x1);
-      ql[i][0].u[e] = to_bf16(x0 - bf16_to_f32(qh[i][0].u[e]));
-      ql[i][1].u[e] = to_bf16(x1 - bf16_to_f32(qh[i][1].u[e]));
-    }
-  }
-
-  stamp(p, ph, 4);
-  // ---- stage the fresh keys in LDS: K rows [kMultiFreshKeys][72] (row padding against bank conflicts), V^T columns
-  // [64][kMultiFreshKeys + 8]; item = (key f, rotary quad / 8-dim group q8), one after the other per thread
-  constexpr int VS = kMultiFreshKeys + 8;
-  bf16_t* kf_s = (bf16_t*)(lds + kFusedWaves * 4 * 64 + 64);
-  bf16_t* vf_s = kf_s + kMultiFreshKeys * 72;
-  const int nf8 = n_fb * 32 * 8;
-  auto fresh_row = [&](int f, int& m_o, bool& valid, bool& stored) {
-    if (is_branch) {
-      const int rt = qg * NQ * rpt + (f >> sl_log), j = f & (p.SL - 1);
-      m_o = b * p.R + min(rt, p.R - 1);
-      valid = rt < p.R && j < p.suffix_len;
-      stored = j < p.suffix_len - 1;
-    } else {
-      m_o = b * p.R + min(f, p.R - 1);
-      valid = f < p.R;
-      stored = false;
-    }
-  };
-  if (n_fb > 0) {
-    for (int it = threadIdx.x; it < nf8; it += kFusedThreads) {
-      const int f = it >> 3, q8 = it & 7;
-      int m_o;
-      bool valid, stored;
-      fresh_row(f, m_o, valid, stored);
-      u32x2 k_lo = (u32x2){0u, 0u}, k_hi = (u32x2){0u, 0u};
-      Bf8 vv;
-      vv.w = (u32x4){0u, 0u, 0u, 0u};
-      if (valid && stored) {
-        const int64_t row = (((int64_t)m_o * p.suffix_cap + (f & (p.SL - 1))) * p.Hkv + hk) * 64;
-        k_lo = *(const gu32x2*)(L.suffix_k + row + q8 * 4);
-        k_hi = *(const gu32x2*)(L.suffix_k + row + 32 + q8 * 4);
-        vv.v = *(const gbf16x8*)(L.suffix_v + row + q8 * 8);
-      } else if (valid) {
-        const gfloat* kp = gq + (int64_t)m_o * p.qkvd + p.qd + hk * 64 + q8 * 4;
-        const f32x4 a = *(const gf32x4*)kp, bb = *(const gf32x4*)(kp + 32);
-        const gfloat* cs = gcs + ((int64_t)m_o * 32 + q8 * 4) * 2;
-        const f32x4 c0 = *(const gf32x4*)cs, c1 = *(const gf32x4*)(cs + 4);
-        const gfloat* vp = gq + (int64_t)m_o * p.qkvd + p.qd + p.kvd + hk * 64 + q8 * 8;
-        const f32x4 v0 = *(const gf32x4*)vp, v1 = *(const gf32x4*)(vp + 4);
-        const float cc[8] = {c0[0], c0[1], c0[2], c0[3], c1[0], c1[1], c1[2], c1[3]};
-        bf16_t x0[4], x1[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float c = cc[2 * e], sn = cc[2 * e + 1];
-          x0[e] = to_bf16(a[e] * c - bb[e] * sn);
-          x1[e] = to_bf16(bb[e] * c + a[e] * sn);
-        }
-        const uint64_t p0 = pack_bf16x4(x0[0], x0[1], x0[2], x0[3]), p1 = pack_bf16x4(x1[0], x1[1], x1[2], x1[3]);
-        k_lo = (u32x2){(uint32_t)p0, (uint32_t)(p0 >> 32)};
-        k_hi = (u32x2){(uint32_t)p1, (uint32_t)(p1 >> 32)};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          vv.u[e] = to_bf16(v0[e]);
-          vv.u[4 + e] = to_bf16(v1[e]);
-        }
-      }
-      *(u32x2*)(kf_s + f * 72 + q8 * 4) = k_lo;
-      *(u32x2*)(kf_s + f * 72 + 32 + q8 * 4) = k_hi;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vf_s[(q8 * 8 + e) * VS + f] = vv.u[e];
-    }
-    wg_barrier();
-  }
-  stamp(p, ph, 5);
-
-  OnlineSoftmax st[NQ];
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    st[i].m_run = -INFINITY;
-    st[i].l_run = 0.f;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) st[i].acc[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  }
-
-  // ---- stored trunk keys: RING blocks in flight, every block scored against all NQ query tiles
-  auto trunk_block = [&](const TrunkBlock& tb, int i) {
-    const int kb = kb0 + (wave + kFusedWaves * i) * 32;
-#pragma unroll
-    for (int t = 0; t < NQ; ++t) {
-      f32x4 S[2];
-      bool vis[8];
-#pragma unroll
-      for (int tile = 0; tile < 2; ++tile) S[tile] = score_tile<NPQ>(tb.k[tile][0], tb.k[tile][1], qh[t], ql[t]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vis[e] = i < n_mine && kb + g4 * 8 + e < tv[t];
-      softmax_block<NPP>(st[t], S, vis, tb.vt);
-    }
-  };
-  int i0 = 0;
-  for (; i0 + RING < n_mine; i0 += RING) {
-#pragma unroll
-    for (int r = 0; r < RING; ++r) {
-      trunk_block(ring[r], i0 + r);
-      load_trunk(ring[r], i0 + r + RING);
-    }
-  }
-  if (n_mine > 0) {
-#pragma unroll
-    for (int r = 0; r < RING; ++r) trunk_block(ring[r], i0 + r);
-  }
-  stamp(p, ph, 6);
-  // ---- fresh blocks continue the round-robin after the trunk blocks
-  for (int blk = n_tb + ((wave - n_tb) & (kFusedWaves - 1)); blk < n_tb + n_fb; blk += kFusedWaves) {
-    const int f0 = (blk - n_tb) * 32;
-    bf16x8 kk[2][2], vt[4];
-#pragma unroll
-    for (int tile = 0; tile < 2; ++tile) {
-      const bf16_t* kp = kf_s + (f0 + krow + tile * 4) * 72 + g4 * 8;
-      kk[tile][0] = *(const bf16x8*)kp;
-      kk[tile][1] = *(const bf16x8*)(kp + 32);
-    }
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) vt[dt] = *(const bf16x8*)(vf_s + (dt * 16 + li) * VS + f0 + g4 * 8);
-#pragma unroll
-    for (int t = 0; t < NQ; ++t) {
-      f32x4 S[2];
-      bool vis[8];
-#pragma unroll
-      for (int tile = 0; tile < 2; ++tile) S[tile] = score_tile<NPQ>(kk[tile][0], kk[tile][1], qh[t], ql[t]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int f = f0 + g4 * 8 + e;
-        vis[e] = vq[t] && (is_branch ? ((f >> sl_log) == t * rpt + (li >> g_log) && (f & (p.SL - 1)) < p.suffix_len) : f <= rloc[t]);
-      }
-      softmax_block<NPP>(st[t], S, vis, vt);
-    }
-  }
-
-  stamp(p, ph, 7);
-  // ---- the 8 wavefronts' partial softmaxes meet in LDS, one query tile after the other: acc [wave][dt][lane],
-  // (m, l) [wave][16]
-  float* ml = (float*)(lds + kFusedWaves * 4 * 64);
-#pragma unroll
-  for (int t = 0; t < NQ; ++t) {
-    st[t].l_run = sum_over_rows(st[t].l_run);
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt) lds[(wave * 4 + dt) * 64 + lane] = st[t].acc[dt];
-    if (g4 == 0) {
-      ml[(wave * 16 + li) * 2] = st[t].m_run;
-      ml[(wave * 16 + li) * 2 + 1] = st[t].l_run;
-    }
-    wg_barrier();
-    if (threadIdx.x < 256) {
-      const int q = threadIdx.x & 15, dq = threadIdx.x >> 4;       // query row of the tile, dims 4 dq .. 4 dq + 3
-      float mmax = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < kFusedWaves; ++w) mmax = fmaxf(mmax, ml[(w * 16 + q) * 2]);
-      const float m_use = mmax == -INFINITY ? 0.f : mmax;
-      float lsum = 0.f;
-      f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int w = 0; w < kFusedWaves; ++w) {
-        const float wgt = exp2_fast(ml[(w * 16 + q) * 2] - m_use);
-        lsum += wgt * ml[(w * 16 + q) * 2 + 1];
-        o += lds[(w * 4 + (dq >> 2)) * 64 + q + 16 * (dq & 3)] * wgt;
-      }
-      const int qrow = (qg * NQ + t) * 16 + q;
-      if (qrow < RG) {
-        if (p.NS == 1) {
-          const int mm = b * p.R + qrow / p.G;
-          const int k = (hk * p.G + qrow % p.G) * 64 + dq * 4;
-          const float inv = 1.0f / lsum;
-          bf16_t hi[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) hi[e] = to_f16(o[e] * inv);      // (this unit serves wide passes only: fp16 activations)
-          st_u64(att_out + b_off<MT>(k, mm), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
-        } else {
-          const int64_t pb = ((int64_t)(b * p.Hkv + hk) * p.NS + s) * (p.QT * 16) + qrow;
-          if (dq == 0) st_u64(part_ml + pb * 2, pack_f32x2(mmax, lsum));
-          st_f32x4(part_o + pb * 64 + dq * 4, o);
-        }
-      }
-    }
-    wg_barrier();
-  }
-  stamp(p, ph, 1);
-  // ---- append the keys and values computed in this pass for later passes, from their LDS copies: the row's private
-  // suffix slot (branch) or its trunk position (extend)
-  if (n_fb > 0) {
-    for (int it = threadIdx.x; it < nf8; it += kFusedThreads) {
-      const int f = it >> 3, q8 = it & 7;
-      int m_o;
-      bool valid, stored;
-      fresh_row(f, m_o, valid, stored);
-      if (!valid || stored) continue;
-      const u32x2 k_lo = *(const u32x2*)(kf_s + f * 72 + q8 * 4), k_hi = *(const u32x2*)(kf_s + f * 72 + 32 + q8 * 4);
-      Bf8 vv;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vv.u[e] = vf_s[(q8 * 8 + e) * VS + f];
-      if (is_branch) {
-        const int64_t row = (((int64_t)m_o * p.suffix_cap + (p.suffix_len - 1)) * p.Hkv + hk) * 64;
-        *(gu32x2*)(L.suffix_k + row + q8 * 4) = k_lo;
-        *(gu32x2*)(L.suffix_k + row + 32 + q8 * 4) = k_hi;
-        *(gbf16x8*)(L.suffix_v + row + q8 * 8) = vv.v;
-      } else {
-        const int slot = p.rows[m_o].kv_slot;
-        const int64_t bb = PG ? ((int64_t)p.pages[(int64_t)b * p.page_stride + (slot >> 5)] * p.Hkv + hk) * 2048
-                              : (int64_t)(b * p.Hkv + hk) * p.vt_stride * 64 + (int64_t)(slot >> 5) * 2048;
-        const int64_t row = bb + (int64_t)(slot & 31) * 64;
-        *(gu32x2*)(L.trunk_k + row + q8 * 4) = k_lo;
-        *(gu32x2*)(L.trunk_k + row + 32 + q8 * 4) = k_hi;
-        gbf16* vcol = (gbf16*)L.trunk_vt + bb + (q8 * 8) * 32 + (slot & 31);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) vcol[e * 32] = vv.u[e];
-      }
-    }
-  }
-  wg_barrier();
-}
-
 // Merge unit (only when the trunk is split over several units): one wavefront per (row, query head), lane = head
 // dimension, merges the NS partial softmaxes and writes the attention output planes.
 template <int MT, int MP, int NPT>
@@ -1476,21 +1143,30 @@ __device__ __forceinline__ void attn_merge_unit(const FusedParams& p, int unit, 
 // per clock) and the latency of each pull, so the work of a layer is cut in two dimensions and every phase is a kernel
 // of its own, shaped for its work (a wide step takes milliseconds: the dozens of launches cost little beside it).
 //
-// Linear layers (wide_gemm_kernel).  A "pair" = (4 feature tiles, one group of kWideGroup row tiles) over the whole
+// What bounds them, measured with 256 workgroups that only load: data in an XCD's L2 reach a compute unit at 110-125 GB/s,
+// a stream from memory shared by 8 workgroups of one XCD at 86-104, but everything that misses the L2s together, from HBM
+// and the memory-side cache alike, at 6-7.4 TB/s (24-29 GB/s per compute unit).  So a layer's cost is what crosses into the
+// L2s: the weights once, and the activations once per XCD that needs them.
+//
+// Linear layers (wide_gemm_kernel).  A "pair" = (4 feature tiles, one group of MTG row tiles) over one of S slices of the
 // reduction dimension.  A workgroup is 4 wavefronts, ONE per SIMD, so each may use all 512 vector registers: 96 hold
 // the 24 accumulator tiles, the rest a ring of kWideRing register chunks, 7 of them (70 KiB per wavefront) in flight
-// while one is multiplied: a compute unit has to keep about 200 KiB in flight to pull at L2 rate.  The wavefronts
-// split the reduction dimension; each streams its own weight tiles (A operands, straight from the stream-order
-// layout: two of its eight wavefront runs, and a k-slice of a K-split layer is just another piece of the range) and
-// the matching activation tiles of the row group (B operands, one fp16 plane): 24 MFMAs per 10 KiB pulled.  The row
-// groups of one set of feature tiles run on workgroups of ONE XCD (workgroup w runs on XCD w % 8), so the weights
-// leave HBM once and the other row groups find them in that XCD's L2.  The four partial tiles meet in LDS (96 KiB) and
-// are added in wavefront order.
+// while one is multiplied.  The wavefronts split the slice; each streams its own weight tiles (A operands, straight from
+// the stream-order layout, in which the k-tiles of a tile group are one contiguous run) and the matching activation tiles
+// of the row group (B operands, one fp16 plane): 24 MFMAs per 10 KiB pulled.  The four partial tiles meet in LDS (96 KiB)
+// and are added in wavefront order.
+// The o- and down-projections have few features (32 sets of 4 tiles at the 1B shape) under a long reduction dimension:
+// they are cut S ways so that every compute unit has a pair, XCD x working on slice x mod S, so that an XCD's L2 takes in
+// only that slice of the activations and, among the XCDs of a slice, only its own sets' weights.  Their fp32 partial sums
+// go to memory, and wide_resid_kernel, a workgroup per row, adds them to the residual stream in slice order and normalises
+// the row: the linear layers that follow find finished operands and need no row scales.  (Small row groups instead of
+// slices, S = 1 and the residual in the epilogue, pulled every set's weights once per row group and the whole activation
+// matrix into every XCD: the down-projection took 23 / 28 / 33 us at 96 / 170 / 384 rows; now 15.8 / 18.5 / 28 and 5 to 6
+// for the residual kernel, and the kernels behind it 1.5 to 2.5 us less each.)
 constexpr int kWideTiles = kFusedWideRows / 16;
 constexpr int kWideGroup = 6;
 constexpr int kWideRing = 8;
 constexpr int kWideThreads = 256, kWideWaves = 4;
-constexpr int kWideQueryTiles = kFusedWideQueryTiles;   // query tiles that share a unit's pull of the stored keys
 
 // plain stores the compiler does not count (see st_f32x4_uncounted)
 __device__ __forceinline__ void st_u64_uncounted(void* p, uint64_t v) {
@@ -1500,44 +1176,6 @@ __device__ __forceinline__ void st_f32_uncounted(float* p, float v) {
   asm volatile("global_store_dword %0, %1, off" : : "v"(p), "v"(v));
 }
 
-// 1/rms of rows m_lo .. m_hi-1 of a wide pass into r_s[m] (LDS).  Wide passes keep the sums of squares of the residual
-// stream per 64 features (the 4 feature tiles a workgroup of the producing kernel owns): ssq[feature quad][row].  All
-// loads of a thread go out together (one memory round trip); 4 wavefronts; tmp: 4 x 64 floats of LDS.
-template <int MP>
-__device__ __forceinline__ void wide_row_scales(const FusedParams& p, const float* ssq, float* r_s, float* tmp, int m_lo, int m_hi) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n_quads = p.d >> 6;
-  const gfloat* src = (const gfloat*)ssq;
-  for (int m0 = m_lo; m0 < m_hi; m0 += 128) {
-    float sum[2] = {0.f, 0.f};
-    for (int j0 = wave; j0 < n_quads; j0 += 4 * 8) {
-      float v[2][8];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int m = m0 + 64 * h + lane;
-        const int mc = m < m_hi ? m : m_hi - 1;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int j = j0 + 4 * i;
-          v[h][i] = src[(int64_t)(j < n_quads ? j : j0) * MP + mc];
-        }
-      }
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) sum[h] += j0 + 4 * i < n_quads ? v[h][i] : 0.f;
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int m = m0 + 64 * h + lane;
-      tmp[wave * 64 + lane] = sum[h];
-      wg_barrier();
-      if (wave == 0 && m < m_hi) r_s[m] = 1.0f / sqrtf((tmp[lane] + tmp[64 + lane] + tmp[128 + lane] + tmp[192 + lane]) / (float)p.d + p.eps);
-      wg_barrier();
-    }
-  }
-}
-
 template <int MTG>
 struct WideChunk {
   bf16x8 a[4];
@@ -1545,41 +1183,35 @@ struct WideChunk {
 };
 
 struct WideEpi {
-  float* out;          // QKV: [M][ld] projections with the norm's row scale applied; LOGITS: [M][ld] logits
+  float* out;          // QKV: [M][ld] projections; LOGITS: [M][ld] logits; PART: [slice][M][ld] partial sums
   int64_t ld;
-  const float* h_in;   // RESID
-  float* h_out;
-  const bf16_t* gain;
-  bf16_t* xn_out;
-  float* ssq_out;
   bf16_t* act_out;     // SWIGLU
-  const float* ssq_in; // QKV, SWIGLU, LOGITS: per-feature-tile sums of squares of the input's residual stream
+  int S;               // k-slices (PART; 1 otherwise)
   int ph;              // phase id (for the optional clocks)
 };
 
-// ATW: feature tiles per unit of the layer's stream-order layout (2: qkv, o, down; 4: gate/up, LM head).
-// D: chunks of the ring (kWideRing; half of it for reduction dimensions too short for whole turns of the full ring).
-// MTG: row tiles per row group: kWideGroup, or half of it where that gives every workgroup of the grid a pair (the
-// o- and down-projections have few feature tiles; smaller groups pull more bytes per MFMA but idle no compute unit).
+// ATW: feature tiles per unit of the layer's stream-order layout (2: qkv, o, down; 4: gate/up).
+// D: chunks of the ring (kWideRing; half of it for slices too short for whole turns of the full ring).
+// MTG: row tiles per row group: kWideGroup, or fewer where that gives every workgroup of the grid a pair.
 template <int ATW, int EPI, int D, int MTG>
 __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
-  constexpr int MP = kFusedWideRows, MTOT = kWideTiles, NT = 4 * MTG;
+  constexpr int MTOT = kWideTiles, NT = 4 * MTG;
   extern __shared__ f32x4 red[];
-  __shared__ float r_s[MP];
-  __shared__ float ssq_s[NT * 16];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int KTW = g.KTW, KS = g.KS;
-  const int NCH8 = KS * KTW;                        // k-tiles per pair in one of the layout's 8 wavefront runs
-  const int NCH = 2 * NCH8;                         // k-tiles per pair of this wavefront (a multiple of D: host check)
-  const int n_groups = g.n_units / KS;
+  const int NKT = g.KS * kFusedWaves * g.KTW;       // k-tiles of the reduction dimension
+  const int S = EPI == FE_PART ? e.S : 1;
+  const int NCH = NKT / (kWideWaves * S);           // k-tiles per pair of this wavefront (a multiple of D: host check)
+  const int n_groups = g.n_units / g.KS;
   const int nq = ATW == 4 ? n_groups : n_groups >> 1;
   const int n_rg = (((p.M + 15) >> 4) + MTG - 1) / MTG;
-  // the pairs of this workgroup: XCD x = blockIdx.x % 8 serves the tile sets q = x, x + 8, ..; its workgroups take
-  // (set, row group) pairs t = wx, wx + per_xcd, .. with the row group running fastest
+  // the pairs of this workgroup: XCD x = blockIdx.x % 8 works on slice x % S and, among the XCDs of that slice, on the tile
+  // sets q = y, y + ys, ..; its workgroups take (set, row group) pairs t = wx, wx + per_xcd, .. with the row group running
+  // fastest
   const int x = (int)blockIdx.x & 7, wx = (int)blockIdx.x >> 3, per_xcd = (int)gridDim.x >> 3;
-  const int nqx = x < nq ? (nq - x + 7) >> 3 : 0;
-  const int tx = nqx * n_rg;
-  const int n_my = wx < tx ? (tx - wx + per_xcd - 1) / per_xcd : 0;
+  const int slice = x % S, y = x / S, ys = 8 / S;   // S is 1, 2, 4 or 8
+  const int nqy = y < nq ? (nq - y + ys - 1) / ys : 0;
+  const int ty = nqy * n_rg;
+  const int n_my = wx < ty ? (ty - wx + per_xcd - 1) / per_xcd : 0;
   stamp(p, e.ph, 0);
   if (n_my == 0) return;
 
@@ -1589,35 +1221,27 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
 #pragma unroll
     for (int t = 0; t < MTG; ++t) acc[j][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-  // The load cursor walks the chunks of this wavefront: pair after pair, in a pair the two wavefront runs of the
-  // layout it covers, in a run the k-slices, in a slice KTW consecutive k-tiles.  Inside such a segment both operand
-  // addresses advance by a constant; only a segment change (every KTW chunks) costs index arithmetic: scalar
-  // divisions per chunk would take longer than the chunk's MFMAs.
+  // The load cursor walks the chunks of this wavefront, pair after pair (clamped to the last one)
   struct Cursor {
-    const bf16_t* a;     // this wavefront's A tiles of the chunk (feature tile 0 of the set; ATW == 2: of its first unit)
+    const bf16_t* a;     // this wavefront's A tiles of the chunk (feature tile 0 of the set; ATW == 2: of its first tile group)
     const bf16_t* b;     // B tile 0 of the row group at the chunk's k-tile
-    int i, seg, n;       // k-tile in the segment, segment in the pair (run * KS + k-slice), pair ordinal
+    int i, n;            // chunk in the pair, pair ordinal
   };
-  const int64_t a_step = (int64_t)ATW * 512;                     // next k-tile of a segment
-  const int64_t a_unit2 = (int64_t)KS * kFusedWaves * KTW * 2 * 512;   // ATW == 2: from the set's first unit to its second
-  const int64_t b_step = (int64_t)MTOT * 512;
-  auto place = [&](Cursor& cu) {   // operand addresses at the start of segment cu.seg of pair cu.n (clamped to the last pair)
+  const int64_t a_group2 = (int64_t)NKT * 2 * 512;               // ATW == 2: from the set's first tile group to its second
+  const int kt0 = (slice * kWideWaves + wave) * NCH;
+  auto place = [&](Cursor& cu) {
     const int t = wx + (cu.n < n_my ? cu.n : n_my - 1) * per_xcd;
     const int qh = t / n_rg;
-    const int q = qh * 8 + x, rg = t - qh * n_rg;
-    const int half = cu.seg >= KS ? 1 : 0;
-    const int ks = cu.seg - half * KS;
-    const int run = 2 * wave + half;                // which of the layout's 8 wavefront runs
-    const int64_t unit = ATW == 4 ? (int64_t)q : (int64_t)(2 * q) * KS + ks;
-    cu.a = g.w + ((unit * kFusedWaves + run) * KTW) * ATW * 512;
-    cu.b = bsrc + ((int64_t)((ks * kFusedWaves + run) * KTW) * MTOT + rg * MTG) * 512;
+    const int q = qh * ys + y, rg = t - qh * n_rg;
+    cu.a = g.w + (int64_t)(ATW == 4 ? q : 2 * q) * NKT * ATW * 512 + (int64_t)kt0 * ATW * 512;
+    cu.b = bsrc + ((int64_t)kt0 * MTOT + rg * MTG) * 512;
   };
   auto advance = [&](Cursor& cu) {
-    cu.a += a_step;
-    cu.b += b_step;
-    if (++cu.i == KTW) {
+    cu.a += ATW * 512;
+    cu.b += MTOT * 512;
+    if (++cu.i == NCH) {
       cu.i = 0;
-      if (++cu.seg == 2 * KS) { cu.seg = 0; ++cu.n; }
+      ++cu.n;
       place(cu);
     }
   };
@@ -1629,7 +1253,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
 #pragma unroll
       for (int j = 0; j < 4; ++j) ck.a[j] = ap[j * 64];
     } else {
-      const gbf16x8* ap2 = (const gbf16x8*)(cu.a + a_unit2) + lane;
+      const gbf16x8* ap2 = (const gbf16x8*)(cu.a + a_group2) + lane;
       ck.a[0] = ap[0];
       ck.a[1] = ap[64];
       ck.a[2] = ap2[0];
@@ -1646,25 +1270,15 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
       for (int t = 0; t < MTG; ++t) acc[j][t] = mfma16_f16(ck.a[j], ck.b[t], acc[j][t]);
   };
 
-  // 1/rms of the rows this workgroup's pairs cover: one row group if per_xcd is a multiple of n_rg, else all rows
-  // (before the ring's loads, which fill the load counter)
-  if (EPI != FE_RESID) {
-    const bool one_group = per_xcd % n_rg == 0;
-    const int m_lo = one_group ? (wx % n_rg) * MTG * 16 : 0;
-    wide_row_scales<MP>(p, e.ssq_in, r_s, (float*)red, m_lo, min(p.M, one_group ? m_lo + MTG * 16 : p.M));
-  }
-
   WideChunk<MTG> ring[D];
-  Cursor cu{nullptr, nullptr, 0, 0, 0};
+  Cursor cu{nullptr, nullptr, 0, 0};
   place(cu);
 #pragma unroll
   for (int s = 0; s < D - 1; ++s) { load_chunk(ring[s], cu); advance(cu); }
-  stamp(p, e.ph, 1);
-
   stamp(p, e.ph, 3);
   for (int n = 0; n < n_my; ++n) {
     const int t = wx + n * per_xcd;
-    const int q = (t / n_rg) * 8 + x, rg = t - (t / n_rg) * n_rg;
+    const int q = (t / n_rg) * ys + y, rg = t - (t / n_rg) * n_rg;
     for (int c = 0; c < NCH; c += D) {
 #pragma unroll
       for (int s = 0; s < D; ++s) {
@@ -1674,7 +1288,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
       }
     }
     if (n == 0) stamp(p, e.ph, 4);
-    // ---- end of a pair: the 4 wavefronts' partial tiles meet in LDS; every wavefront sums its 6 of the 24 tiles in
+    // ---- end of a pair: the 4 wavefronts' partial tiles meet in LDS; every wavefront sums its share of the tiles in
     // wavefront order and runs their epilogue
 #pragma unroll
     for (int j = 0; j < 4; ++j)
@@ -1698,67 +1312,120 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
         const f32x4 gv = total(idx), uv = total(idx + 2 * MTG);
         const int m = (rg * MTG + tt) * 16 + (lane & 15);
         if (m < p.M) {
-          const float rs = r_s[m];
           bf16_t hi[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const float gg = gv[i] * rs, uu = uv[i] * rs;
-            hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
-          }
+          for (int i = 0; i < 4; ++i) hi[i] = to_f16(gv[i] / (1.0f + __expf(-gv[i])) * uv[i]);
           const int k = q * 32 + j * 16 + f4;      // input index of the down-projection
           st_u64_uncounted(e.act_out + b_off<MTOT>(k, m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
         }
       }
     } else {
+      float* out = e.out + (EPI == FE_PART ? (int64_t)slice * p.M * e.ld : 0);
       for (int idx = wave; idx < NT; idx += kWideWaves) {
         const int j = idx / MTG, tt = idx - j * MTG;
         const f32x4 v = total(idx);
         const int m = (rg * MTG + tt) * 16 + (lane & 15);
         const int tile = q * 4 + j;
-        const int nn = tile * 16 + f4;
-        if (tile >= g.NT) continue;
-        if constexpr (EPI == FE_QKV || EPI == FE_LOGITS) {
-          if (m < p.M) st_f32x4_uncounted(e.out + (int64_t)m * e.ld + nn, v * r_s[m]);
-        } else {
-          // residual stream: new h, (h * gain) as one fp16 plane for the next linear layer, this tile's sum of squares
-          f32x4 hn = v;
-          float ss = 0.f;
-          if (m < p.M) {
-            hn += *(const gf32x4*)(e.h_in + (int64_t)m * p.d + nn);
-            const u32x2 gb = *(const gu32x2*)(e.gain + nn);
-            st_f32x4_uncounted(e.h_out + (int64_t)m * p.d + nn, hn);
-            const float gg[4] = {__uint_as_float(gb.x << 16), __uint_as_float(gb.x & 0xffff0000u), __uint_as_float(gb.y << 16),
-                                 __uint_as_float(gb.y & 0xffff0000u)};
-            bf16_t hi[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              hi[i] = to_f16(hn[i] * gg[i]);
-              ss += hn[i] * hn[i];
-            }
-            st_u64_uncounted(e.xn_out + b_off<MTOT>(nn, m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
-          }
-          ss += __shfl_xor(ss, 16);
-          ss += __shfl_xor(ss, 32);
-          if (lane < 16) ssq_s[idx * 16 + lane] = ss;     // this feature tile's sum of squares per row
-        }
+        if (tile < g.NT && m < p.M) st_f32x4_uncounted(out + (int64_t)m * e.ld + tile * 16 + f4, v);
       }
     }
     wg_barrier();
-    if constexpr (EPI == FE_RESID) {
-      // the set's 4 feature tiles, added in tile order: one sum per (64 features, row)
-      const int tt = (int)threadIdx.x >> 4, r = (int)threadIdx.x & 15;
-      const int m = (rg * MTG + tt) * 16 + r;
-      if (tt < MTG && m < p.M && q * 4 < g.NT) {
-        float ss = 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) ss += q * 4 + j < g.NT ? ssq_s[(j * MTG + tt) * 16 + r] : 0.f;
-        st_f32_uncounted(e.ssq_out + q * MP + m, ss);
-      }
-      wg_barrier();
-    }
     if (n == 0) stamp(p, e.ph, 5);
   }
   stamp(p, e.ph, 2);
+}
+
+// The residual stream of a wide pass: a workgroup per row.  EMBED: h = the token's embedding; otherwise h += the row's
+// partial sums of the linear layer before, slice after slice.  Then the RMSNorm with `gain`, as the fp16 B operand of the
+// next linear layer (8 consecutive features per thread are one lane's 16 bytes of it) and, where asked for, as fp32
+// hidden states.  Reads S + 1 rows of d floats: at 96 rows of the 1B shape (S = 4 and 8) 4.9 us, at 384 (S = 2)
+// 6.0 us, of which launch and two memory round trips are about 4.
+template <bool EMBED>
+__global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p, const float* part, int S, const bf16_t* gain,
+                                                                  float* hidden, int ph) {
+  constexpr int kHeld = 2;                       // 8-feature chunks per thread kept in registers (d <= 4096); others are re-read
+  __shared__ float sum_s[kWideWaves];
+  const int m = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  stamp(p, ph, 0);
+  gfloat* h = (gfloat*)p.h + (int64_t)m * p.d;
+  int tok = 0;
+  if (EMBED) {
+    tok = p.tokens[m];
+    tok = tok < 0 ? 0 : (tok >= p.V ? p.V - 1 : tok);
+  }
+  f32x4 held[kHeld][2];
+  u32x4 gheld[kHeld];
+  float ss = 0.f;
+  auto chunk = [&](int c, f32x4 v[2]) {
+    if (EMBED) {
+      Bf8 eb;
+      eb.v = *(const gbf16x8*)((const gbf16*)p.embed + (int64_t)tok * p.d + c);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i >> 2][i & 3] = bf16_to_f32(eb.u[i]);
+    } else {
+      const gfloat* pp = (const gfloat*)part + (int64_t)m * p.d + c;
+      v[0] = *(const gf32x4*)(h + c);
+      v[1] = *(const gf32x4*)(h + c + 4);
+      for (int s0 = 0; s0 < S; s0 += 4) {
+        f32x4 pv[4][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const gfloat* q = pp + (int64_t)min(s0 + i, S - 1) * p.M * p.d;
+          pv[i][0] = *(const gf32x4*)q;
+          pv[i][1] = *(const gf32x4*)(q + 4);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (s0 + i < S) { v[0] += pv[i][0]; v[1] += pv[i][1]; }
+      }
+    }
+    *(gf32x4*)(h + c) = v[0];
+    *(gf32x4*)(h + c + 4) = v[1];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ss += v[i >> 2][i & 3] * v[i >> 2][i & 3];
+  };
+  const int step = kWideThreads * 8;
+#pragma unroll
+  for (int i = 0; i < kHeld; ++i) {
+    const int c = (int)threadIdx.x * 8 + i * step;
+    if (c < p.d) {
+      gheld[i] = *(const u32x4*)(gain + c);
+      chunk(c, held[i]);
+    }
+  }
+  for (int c = (int)threadIdx.x * 8 + kHeld * step; c < p.d; c += step) {
+    f32x4 v[2];
+    chunk(c, v);
+  }
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+  if (lane == 0) sum_s[wave] = ss;
+  __syncthreads();
+  const float rs = 1.0f / sqrtf(((sum_s[0] + sum_s[1]) + (sum_s[2] + sum_s[3])) / (float)p.d + p.eps);
+  auto put = [&](int c, const f32x4 v[2], u32x4 gw) {
+    Bf8 gb, x;
+    gb.w = gw;
+    f32x4 n[2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      n[i >> 2][i & 3] = v[i >> 2][i & 3] * rs * bf16_to_f32(gb.u[i]);
+      x.u[i] = to_f16(n[i >> 2][i & 3]);
+    }
+    *(gbf16x8*)((gbf16*)p.xn + b_off<kWideTiles>(c, m)) = x.v;
+    if (hidden) {
+      *(gf32x4*)((gfloat*)hidden + (int64_t)m * p.hidden_ld + c) = n[0];
+      *(gf32x4*)((gfloat*)hidden + (int64_t)m * p.hidden_ld + c + 4) = n[1];
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < kHeld; ++i) {
+    const int c = (int)threadIdx.x * 8 + i * step;
+    if (c < p.d) put(c, held[i], gheld[i]);
+  }
+  for (int c = (int)threadIdx.x * 8 + kHeld * step; c < p.d; c += step) {
+    f32x4 v[2] = {*(const gf32x4*)(h + c), *(const gf32x4*)(h + c + 4)};   // this thread's own stores
+    put(c, v, *(const u32x4*)(gain + c));
+  }
+  stamp(p, ph, 2);
 }
 
 // The two large linear layers of a wide pass (gate/up + SwiGLU, LM head; stream-order units of 4 feature tiles, no
@@ -1776,11 +1443,10 @@ constexpr int kWideStage = 8;   // k-tiles per LDS stage of the activation opera
 
 template <int EPI>
 __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
-  constexpr int MP = kFusedWideRows, MTOT = kWideTiles, MTG = kWideGroup, KC = kWideStage;
+  constexpr int MTOT = kWideTiles, MTG = kWideGroup, KC = kWideStage;
   constexpr int STAGE = KC * MTG * 64;               // 16-byte vectors per stage
   constexpr int BL = STAGE / kWideThreads;           // staging loads per thread and stage (12)
   extern __shared__ f32x4 lds[];                     // [2][KC][MTG][64] B-operand vectors
-  __shared__ float r_s[MP];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int NKT = g.KTW * kFusedWaves;               // k-tiles of the reduction dimension
   const int NST = NKT / KC;                          // stages per pair
@@ -1792,14 +1458,6 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
   const int n_my = wx < tx ? (tx - wx + per_xcd - 1) / per_xcd : 0;
   stamp(p, e.ph, 0);
   if (n_my == 0) return;
-
-  // ---- 1/rms of the rows this workgroup's pairs cover (one row group if per_xcd is a multiple of n_rg, else all rows)
-  {
-    const bool one_group = per_xcd % n_rg == 0;
-    const int m_lo = one_group ? (wx % n_rg) * MTG * 16 : 0;
-    wide_row_scales<MP>(p, e.ssq_in, r_s, (float*)lds, m_lo, min(p.M, one_group ? m_lo + MTG * 16 : p.M));
-  }
-  stamp(p, e.ph, 1);
 
   constexpr int MT32 = MTG / 2;                      // 32-row tiles of a row group
   static_assert(MTG % 2 == 0, "row tiles pair up into 32-row MFMA operands");
@@ -1922,7 +1580,6 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
       for (int t = 0; t < MT32; ++t) {
         const int m = (rg * MTG + 2 * t) * 16 + (lane & 31);
         if (m < p.M) {
-          const float rs = r_s[m];
           if constexpr (EPI == FE_SWIGLU) {
             // feature tiles 0, 1 of the unit are gate, 2, 3 the matching up tiles
 #pragma unroll
@@ -1930,7 +1587,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
               bf16_t hi[4];
 #pragma unroll
               for (int i = 0; i < 4; ++i) {
-                const float gg = acc[0][t][4 * q + i] * rs, uu = acc[1][t][4 * q + i] * rs;
+                const float gg = acc[0][t][4 * q + i], uu = acc[1][t][4 * q + i];
                 hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
               }
               const int k = unit * 32 + 8 * q + f4;       // input index of the down-projection
@@ -1943,7 +1600,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
               for (int q = 0; q < 4; ++q) {
                 const int n0 = unit * 64 + f * 32 + 8 * q + f4;
                 const f32x4 v = (f32x4){acc[f][t][4 * q], acc[f][t][4 * q + 1], acc[f][t][4 * q + 2], acc[f][t][4 * q + 3]};
-                if ((n0 >> 4) < g.NT) st_f32x4_uncounted(e.out + (int64_t)m * e.ld + n0, v * rs);
+                if ((n0 >> 4) < g.NT) st_f32x4_uncounted(e.out + (int64_t)m * e.ld + n0, v);
               }
           }
         }
@@ -1958,76 +1615,424 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
   stamp(p, e.ph, 2);
 }
 
-// The other phases of a wide pass (embedding, attention, merge of key splits, final hidden states), one launch each:
-// the narrow pass's units over a workspace of kFusedWideRows rows, one fp16 plane per tensor.
-template <class PL, bool PG>
-__global__ __launch_bounds__(kFusedThreads) void wide_kernel(FusedParams p, int ph) {
-  constexpr int MP = kFusedWideRows, MTOT = kWideTiles;
-  extern __shared__ f32x4 red[];
-  __shared__ float r_s[MP];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lm_phase = fused_last_phase(p.L);
-  const int l = ph == 0 ? 0 : (ph == lm_phase ? p.L - 1 : (ph - 1) / 6);
-  const int sub = ph == 0 ? -1 : (ph == lm_phase ? 6 : (ph - 1) % 6);
-  const FusedLayer L = p.layers[l];
+// The attention unit of the wide passes, a workgroup: NQ query tiles of one (sequence, KV head, key split) share every
+// stored key and value block the unit pulls (a wide pass has 6 and more query tiles per sequence and head: units of one
+// tile would pull the same trunk once per tile).  Same method and same layouts as attn_unit; the qkv projections are
+// finished here (no row scale).  What shapes it, measured on 384 rows over 2048 keys of the 1B shape:
+// - order of the loads: they return in order, and the first ring of stored keys is a burst of 32 MB over the chip, so the
+//   queries and the fresh keys are requested before it and staged under it;
+// - every query tile is rotated once, by one wavefront, and reaches the others through LDS;
+// - vector instructions per score (they, not the MFMAs, fill the SIMDs): a row's reference maximum enters the score MFMAs as
+//   their C operand, so scores come out ready for the exponential; the reference moves only when a score exceeds it by
+//   2^8 (probabilities up to 256 are as exact as those up to 1), which one comparison per lane tests, instead of a maximum
+//   across lanes per block; visibility is tested only in blocks that reach past a tile's shortest row;
+// - the eight wavefronts' partial softmaxes of all NQ tiles meet in LDS at once, after the new keys have been appended.
+// 26.5 us (36.1 before), 16.5 for 170 prompt tokens (22), 19 for 96 rows over 4 sequences of up to 1500 (26.8).
+constexpr int kMultiFreshKeys = kFusedWideFreshKeys;   // LDS room: NQ x (rows per tile x slots per row) for NQ = 3, or the tokens of an extend
+constexpr int kMultiVs = kMultiFreshKeys + 8;          // V^T row of the fresh keys
+constexpr int kMultiQ = kFusedWideQueryTiles;
+constexpr float kMultiSlack = 8.0f;                    // log2 of how far scores may exceed the reference
+// LDS: fresh keys [f][72], fresh values^T [64][kMultiVs]; then the query operands, later (same place) the partial outputs
+// [NQ][wave][4][64] f32x4; then the partial (reference, sum) [NQ][wave][16][2]
+constexpr size_t kMultiFreshBytes = (size_t)(kMultiFreshKeys * 72 + 64 * kMultiVs) * 2;
+constexpr size_t kMultiRedBytes = (size_t)kMultiQ * kFusedWaves * 4 * 64 * 16;
+constexpr size_t kMultiLdsBytes = kMultiFreshBytes + kMultiRedBytes + (size_t)kMultiQ * kFusedWaves * 16 * 2 * 4;
+static_assert(kMultiFreshBytes % 16 == 0 && kMultiLdsBytes <= 160 * 1024, "LDS of the wide attention unit");
+
+template <int NPQ, int NPP, bool PG>
+__global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p, bf16_t* trunk_k, bf16_t* trunk_vt, bf16_t* suffix_k,
+                                                                  bf16_t* suffix_v, int ph) {
+  constexpr int NQ = kMultiQ, MT = kWideTiles;
+  extern __shared__ f32x4 lds[];
+  bf16_t* kf_s = (bf16_t*)lds;
+  bf16_t* vf_s = kf_s + kMultiFreshKeys * 72;
+  f32x4* red = (f32x4*)((char*)lds + kMultiFreshBytes);
+  bf16x8* q_s = (bf16x8*)red;                                  // [NQ][2 k-steps][NPQ planes][64]
+  float* ml = (float*)((char*)red + kMultiRedBytes);
   stamp(p, ph, 0);
-  if (sub == -1) {
-    // embedding gather: residual stream version 0, (h * gain) as one fp16 plane, sums of squares per 64 features
-    for (int u = blockIdx.x; u < (p.d >> 6); u += gridDim.x) {
-      for (int t = wave; t < ((p.M + 15) >> 4); t += kFusedWaves) {
-        const int m = t * 16 + (lane & 15);
-        int tok = p.tokens[min(m, p.M - 1)];
-        tok = tok < 0 ? 0 : (tok >= p.V ? p.V - 1 : tok);
-        float ss = 0.f;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, g4 = lane >> 4;
+  const int QG = (p.QT + NQ - 1) / NQ;        // groups of query tiles per (sequence, KV head)
+  const int unit = blockIdx.x;
+  const int hk = unit % p.Hkv;
+  int rem = unit / p.Hkv;
+  const int qg = rem % QG;
+  rem /= QG;
+  const int s = rem % p.NS, b = rem / p.NS;
+  const int g_log = 31 - __builtin_clz(p.G), sl_log = p.SL == 8 ? 3 : 4;   // G and SL are powers of two
+  const int RG = p.R << g_log;
+  const bool is_branch = p.is_branch != 0;
+  const gfloat* gq = (const gfloat*)p.qkv;
+  const gfloat* gcs = (const gfloat*)p.cos_sin;
+  const int rpt = 16 >> g_log;                                // rows per query tile
+  // query row of a lane in tile t (clamped: rows past the last are computed like it and never stored)
+  auto row_of = [&](int t) { return min((qg * NQ + t) * 16 + li, RG - 1); };
+
+  // ---- issue: row descriptors, the raw queries (wavefront t: tile t), the first fresh keys
+  int tv[NQ];                                                 // stored keys this lane's query rows see
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int n = (u * 4 + j) * 16 + (lane >> 4) * 4;
-          const u32x2 eb = *(const gu32x2*)(p.embed + (int64_t)tok * p.d + n);
-          const u32x2 gb = *(const gu32x2*)(L.attn_norm + n);
-          const float hv[4] = {__uint_as_float(eb.x << 16), __uint_as_float(eb.x & 0xffff0000u), __uint_as_float(eb.y << 16),
-                               __uint_as_float(eb.y & 0xffff0000u)};
-          const float gg[4] = {__uint_as_float(gb.x << 16), __uint_as_float(gb.x & 0xffff0000u), __uint_as_float(gb.y << 16),
-                               __uint_as_float(gb.y & 0xffff0000u)};
-          if (m < p.M) {
-            *(gf32x4*)(p.h + (int64_t)m * p.d + n) = (f32x4){hv[0], hv[1], hv[2], hv[3]};
-            bf16_t hi[4];
+  for (int t = 0; t < NQ; ++t) {
+    const int m = b * p.R + (row_of(t) >> g_log);
+    tv[t] = trunk_visible(p.rows[m], m, p.R);
+  }
+  f32x4 qraw[4], qcs[4];
+  if (wave < NQ) {
+    const int qr = row_of(wave), m = b * p.R + (qr >> g_log);
+    const gfloat* qp = gq + (int64_t)m * p.qkvd + (hk * p.G + (qr & (p.G - 1))) * 64 + g4 * 8;
+    qraw[0] = *(const gf32x4*)qp;
+    qraw[1] = *(const gf32x4*)(qp + 4);
+    qraw[2] = *(const gf32x4*)(qp + 32);
+    qraw[3] = *(const gf32x4*)(qp + 36);
+    const gfloat* cp = gcs + ((int64_t)m * 32 + g4 * 8) * 2;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              hi[i] = to_f16(hv[i] * gg[i]);
-              ss += hv[i] * hv[i];
-            }
-            *(uint64_t*)(p.xn + b_off<MTOT>(n, m)) = pack_bf16x4(hi[0], hi[1], hi[2], hi[3]);
-          }
-        }
-        ss += __shfl_xor(ss, 16);
-        ss += __shfl_xor(ss, 32);
-        if (m < p.M && lane < 16) p.ssq[(int64_t)u * MP + m] = ss;
-      }
+    for (int i = 0; i < 4; ++i) qcs[i] = *(const gf32x4*)(cp + 4 * i);
+  }
+  // fresh keys: item = (key f, rotary quad / 8-dim group q8)
+  const int n_fresh_keys = is_branch ? (NQ * rpt) << sl_log : p.R;
+  const int n_fb = s == 0 ? (n_fresh_keys + 31) >> 5 : 0;
+  const int nf8 = n_fb * 32 * 8;
+  auto fresh_row = [&](int f, int& m_o, bool& valid, bool& stored) {
+    if (is_branch) {
+      const int rt = qg * NQ * rpt + (f >> sl_log), j = f & (p.SL - 1);
+      m_o = b * p.R + min(rt, p.R - 1);
+      valid = rt < p.R && j < p.suffix_len;
+      stored = j < p.suffix_len - 1;
+    } else {
+      m_o = b * p.R + min(f, p.R - 1);
+      valid = f < p.R;
+      stored = false;
     }
-  } else if (sub == 1) {
-    for (int u = blockIdx.x; u < p.n_attn_units; u += gridDim.x)
-      attn_unit_multi<MTOT, MP, PL::q, PL::p, kWideQueryTiles, PG>(p, L, p.qkv, u, red, p.att, p.part_o, p.part_ml, ph);
-  } else if (sub == 2) {
-    for (int u = blockIdx.x; u < p.n_pair_units; u += gridDim.x) attn_merge_unit<MTOT, MP, 1>(p, u, p.part_o, p.part_ml, p.att);
-  } else if (sub == 6 && p.hidden) {
-    // final-norm hidden states: workgroup per row, the row's scale from the tile sums
-    const gfloat* hv = (const gfloat*)p.h;
-    const gfloat* sq = (const gfloat*)p.ssq;
-    float* tmp = (float*)red;
-    for (int m = blockIdx.x; m < p.M; m += gridDim.x) {
-      float s = 0.f;
-      for (int j = threadIdx.x; j < (p.d >> 6); j += kFusedThreads) s += sq[(int64_t)j * MP + m];
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-      if (lane == 0) tmp[wave] = s;
-      wg_barrier();
-      float tot = 0.f;
-      for (int w = 0; w < kFusedWaves; ++w) tot += tmp[w];
-      const float rs = 1.0f / sqrtf(tot / (float)p.d + p.eps);
-      for (int c = threadIdx.x; c < p.d; c += kFusedThreads)
-        p.hidden[(int64_t)m * p.hidden_ld + c] = hv[(int64_t)m * p.d + c] * bf16_to_f32(p.final_norm[c]) * rs;
-      wg_barrier();
+  };
+  struct Fresh {
+    bool valid, stored;
+    u32x2 k_lo, k_hi;              // stored: 4 + 4 key elements
+    bf16x8 v;                      // stored: 8 value elements
+    f32x4 a, bb, c0, c1, v0, v1;   // computed: raw projections and rotary table
+  };
+  auto load_fresh = [&](Fresh& x, int it) {
+    const int f = it >> 3, q8 = it & 7;
+    int m_o;
+    x.valid = x.stored = false;
+    if (it >= nf8) return;
+    fresh_row(f, m_o, x.valid, x.stored);
+    if (x.valid && x.stored) {
+      const int64_t row = (((int64_t)m_o * p.suffix_cap + (f & (p.SL - 1))) * p.Hkv + hk) * 64;
+      x.k_lo = *(const gu32x2*)(suffix_k + row + q8 * 4);
+      x.k_hi = *(const gu32x2*)(suffix_k + row + 32 + q8 * 4);
+      x.v = *(const gbf16x8*)(suffix_v + row + q8 * 8);
+    } else if (x.valid) {
+      const gfloat* kp = gq + (int64_t)m_o * p.qkvd + p.qd + hk * 64 + q8 * 4;
+      x.a = *(const gf32x4*)kp;
+      x.bb = *(const gf32x4*)(kp + 32);
+      const gfloat* cs = gcs + ((int64_t)m_o * 32 + q8 * 4) * 2;
+      x.c0 = *(const gf32x4*)cs;
+      x.c1 = *(const gf32x4*)(cs + 4);
+      const gfloat* vp = gq + (int64_t)m_o * p.qkvd + p.qd + p.kvd + hk * 64 + q8 * 8;
+      x.v0 = *(const gf32x4*)vp;
+      x.v1 = *(const gf32x4*)(vp + 4);
+    }
+  };
+  auto stage_fresh = [&](const Fresh& x, int it) {   // rotated, to LDS (zeros where there is no key)
+    if (it >= nf8) return;
+    const int f = it >> 3, q8 = it & 7;
+    u32x2 k_lo = (u32x2){0u, 0u}, k_hi = (u32x2){0u, 0u};
+    Bf8 vv;
+    vv.w = (u32x4){0u, 0u, 0u, 0u};
+    if (x.valid && x.stored) {
+      k_lo = x.k_lo;
+      k_hi = x.k_hi;
+      vv.v = x.v;
+    } else if (x.valid) {
+      const float cc[8] = {x.c0[0], x.c0[1], x.c0[2], x.c0[3], x.c1[0], x.c1[1], x.c1[2], x.c1[3]};
+      bf16_t x0[4], x1[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float c = cc[2 * e], sn = cc[2 * e + 1];
+        x0[e] = to_bf16(x.a[e] * c - x.bb[e] * sn);
+        x1[e] = to_bf16(x.bb[e] * c + x.a[e] * sn);
+        vv.u[e] = to_bf16(x.v0[e]);
+        vv.u[4 + e] = to_bf16(x.v1[e]);
+      }
+      const uint64_t p0 = pack_bf16x4(x0[0], x0[1], x0[2], x0[3]), p1 = pack_bf16x4(x1[0], x1[1], x1[2], x1[3]);
+      k_lo = (u32x2){(uint32_t)p0, (uint32_t)(p0 >> 32)};
+      k_hi = (u32x2){(uint32_t)p1, (uint32_t)(p1 >> 32)};
+    }
+    *(u32x2*)(kf_s + f * 72 + q8 * 4) = k_lo;
+    *(u32x2*)(kf_s + f * 72 + 32 + q8 * 4) = k_hi;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) vf_s[(q8 * 8 + e) * kMultiVs + f] = vv.u[e];
+  };
+  Fresh fr[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) load_fresh(fr[i], (int)threadIdx.x + i * kFusedThreads);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // ---- issue: the first trunk blocks of this wavefront (block counts from the host's bound)
+  const int kb0 = s * p.KPU;
+  const int kend_ub = min(kb0 + p.KPU, p.tv_ub);
+  const int n_tb = kend_ub > kb0 ? (kend_ub - kb0 + 31) >> 5 : 0;
+  const int n_mine = n_tb > wave ? (n_tb - wave + kFusedWaves - 1) / kFusedWaves : 0;
+  const int krow = (li >> 2) * 8 + (li & 3);                  // key of this lane's A-operand row in a block (tile 0)
+  // PG (paged trunk, App. B "PagedAttention"): block j of sequence b is page p.pages[b][j] of a pool shared by all
+  // sequences, a page = the same 4 KiB per head and operand as a block of the contiguous layouts.  Lane i of a wavefront
+  // fetches the page of the wavefront's i-th block up front (one load), so the block loop itself stays free of
+  // dependent loads; entries behind a sequence's allocation name page 0, which exists and holds zeros.
+  const int64_t head0 = PG ? 0 : ((int64_t)(b * p.Hkv + hk) * p.vt_stride) * 64;
+  const gbf16* kbase = (const gbf16*)trunk_k + head0 + g4 * 8;
+  const gbf16* vbase = (const gbf16*)trunk_vt + head0 + li * 32 + g4 * 8;
+  int pgs = 0;
+  if constexpr (PG) pgs = p.pages[(int64_t)b * p.page_stride + min((kb0 >> 5) + wave + kFusedWaves * lane, p.page_stride - 1)];
+  struct KvBlock {
+    bf16x8 k[2][2];
+    bf16x8 vt[4];
+  };
+  constexpr int RING = 2;
+  KvBlock ring[RING];
+  auto load_trunk = [&](KvBlock& tb, int i) {   // i-th block of this wavefront, clamped to its last one
+    const int ic = max(min(i, n_mine - 1), 0);
+    const int blk = wave + kFusedWaves * ic;
+    const int kb = min(kb0 + blk * 32, p.vt_stride - 32);
+    const int64_t bo = PG ? ((int64_t)__builtin_amdgcn_readlane(pgs, ic) * p.Hkv + hk) * 2048 : (int64_t)kb * 64;
+#pragma unroll
+    for (int tile = 0; tile < 2; ++tile) {
+      const gbf16* kp = kbase + bo + (krow + tile * 4) * 64;
+      tb.k[tile][0] = *(const gbf16x8*)kp;
+      tb.k[tile][1] = *(const gbf16x8*)(kp + 32);
+    }
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) tb.vt[dt] = *(const gbf16x8*)(vbase + bo + dt * 16 * 32);
+  };
+#pragma unroll
+  for (int i = 0; i < RING; ++i) load_trunk(ring[i], i);   // unconditional (a wavefront without blocks re-reads block 0)
+  __builtin_amdgcn_sched_barrier(0);
+  stamp(p, ph, 3);
+
+  // ---- query operands: dims g4*8..+7 (k-step 0) and 32+g4*8..+7 (k-step 1) of the rows, rotated and scaled
+  if (wave < NQ) {
+    const float scale = 0.125f * kLog2e;
+    Bf8 qh[2], ql[2];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float a = qraw[e >> 2][e & 3], bb = qraw[2 + (e >> 2)][e & 3];
+      const float c = qcs[e >> 1][2 * (e & 1)], sn = qcs[e >> 1][2 * (e & 1) + 1];
+      const float x0 = (a * c - bb * sn) * scale, x1 = (bb * c + a * sn) * scale;
+      qh[0].u[e] = to_bf16(x0);
+      qh[1].u[e] = to_bf16(x1);
+      ql[0].u[e] = to_bf16(x0 - bf16_to_f32(qh[0].u[e]));
+      ql[1].u[e] = to_bf16(x1 - bf16_to_f32(qh[1].u[e]));
+    }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      q_s[((wave * 2 + ks) * NPQ) * 64 + lane] = qh[ks].v;
+      if (NPQ == 2) q_s[((wave * 2 + ks) * NPQ + 1) * 64 + lane] = ql[ks].v;
     }
   }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) stage_fresh(fr[i], (int)threadIdx.x + i * kFusedThreads);
+  for (int it = threadIdx.x + 2 * kFusedThreads; it < nf8; it += kFusedThreads) {
+    load_fresh(fr[0], it);
+    stage_fresh(fr[0], it);
+  }
+  wg_barrier();
+  bf16x8 q[NQ][2][NPQ];
+#pragma unroll
+  for (int t = 0; t < NQ; ++t)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int pl = 0; pl < NPQ; ++pl) q[t][ks][pl] = q_s[((t * 2 + ks) * NPQ + pl) * 64 + lane];
+  stamp(p, ph, 5);
+
+  // running softmax per tile: negref = minus the reference (all four elements), thr = how far above the reference a score
+  // moves it (-inf before the row's first visible key), sum of this lane's share, outputs
+  f32x4 negref[NQ], acc[NQ][4];
+  float thr[NQ], l_run[NQ];
+  int vmin[NQ];                                               // stored keys every row of the tile sees
+#pragma unroll
+  for (int t = 0; t < NQ; ++t) {
+    negref[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    thr[t] = -INFINITY;
+    l_run[t] = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) acc[t][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    int v = tv[t];
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o));
+    vmin[t] = __builtin_amdgcn_readfirstlane(v);
+  }
+  // one 32-key block against tile t: scores of this lane's row for keys g4*8..+7 of the block
+  auto tile_step = [&](int t, const bf16x8 (&k)[2][2], const bf16x8 (&vt)[4], bool masked, auto visible) {
+    f32x4 S[2];
+#pragma unroll
+    for (int tile = 0; tile < 2; ++tile) {
+      S[tile] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[tile][0], q[t][0][0], negref[t], 0, 0, 0);
+      S[tile] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[tile][1], q[t][1][0], S[tile], 0, 0, 0);
+      if (NPQ == 2) {
+        S[tile] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[tile][0], q[t][0][NPQ - 1], S[tile], 0, 0, 0);
+        S[tile] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k[tile][1], q[t][1][NPQ - 1], S[tile], 0, 0, 0);
+      }
+    }
+    float sv[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sv[e] = S[e >> 2][e & 3];
+    if (masked) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sv[e] = visible(e) ? sv[e] : -INFINITY;
+    }
+    const float mx = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
+    if (__any(mx > thr[t])) {
+      const float mr = max_over_rows(mx);
+      const bool move = mr > thr[t];                          // (the same for the four lanes of a row)
+      const float shift = move ? mr : 0.f;
+      const float corr = thr[t] == -INFINITY ? 1.0f : exp2_fast(-shift);
+      l_run[t] *= corr;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt) acc[t][dt] = acc[t][dt] * corr;
+      const float nr = negref[t][0] - shift;
+      negref[t] = (f32x4){nr, nr, nr, nr};
+      if (move) thr[t] = kMultiSlack;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sv[e] -= shift;
+    }
+    Bf8 phi, plo;
+    float psum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float pe = exp2_fast(sv[e]);
+      psum += pe;
+      phi.u[e] = to_bf16(pe);
+      if (NPP == 2) plo.u[e] = to_bf16(pe - bf16_to_f32(phi.u[e]));
+    }
+    l_run[t] += psum;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) {
+      acc[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[dt], phi.v, acc[t][dt], 0, 0, 0);
+      if (NPP == 2) acc[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt[dt], plo.v, acc[t][dt], 0, 0, 0);
+    }
+  };
+
+  // ---- stored trunk keys: RING blocks in flight, every block scored against all NQ query tiles.  The last turn of the
+  // ring loads nothing new that is used (clamped duplicates of the last block)
+  for (int i0 = 0; i0 < n_mine; i0 += RING) {
+#pragma unroll
+    for (int r = 0; r < RING; ++r) {
+      if (i0 + r < n_mine) {
+        const int kb = kb0 + (wave + kFusedWaves * (i0 + r)) * 32;
+#pragma unroll
+        for (int t = 0; t < NQ; ++t)
+          tile_step(t, ring[r].k, ring[r].vt, kb + 32 > vmin[t], [&](int e) { return kb + g4 * 8 + e < tv[t]; });
+      }
+      load_trunk(ring[r], i0 + r + RING);
+    }
+  }
+  stamp(p, ph, 6);
+  // ---- fresh blocks continue the round-robin after the trunk blocks; a tile skips blocks none of its rows can see
+  for (int blk = n_tb + ((wave - n_tb) & (kFusedWaves - 1)); blk < n_tb + n_fb; blk += kFusedWaves) {
+    const int f0 = (blk - n_tb) * 32;
+    bf16x8 kk[2][2], vt[4];
+#pragma unroll
+    for (int tile = 0; tile < 2; ++tile) {
+      const bf16_t* kp = kf_s + (f0 + krow + tile * 4) * 72 + g4 * 8;
+      kk[tile][0] = *(const bf16x8*)kp;
+      kk[tile][1] = *(const bf16x8*)(kp + 32);
+    }
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) vt[dt] = *(const bf16x8*)(vf_s + (dt * 16 + li) * kMultiVs + f0 + g4 * 8);
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) {
+      const bool any = is_branch ? f0 < ((t + 1) * rpt) << sl_log && f0 + 32 > (t * rpt) << sl_log
+                                 : f0 <= ((qg * NQ + t) * 16 + 15) >> g_log;
+      if (!any) continue;
+      const int rloc = row_of(t) >> g_log;                    // row of the sequence; its keys as (row in the unit, slot)
+      const int own = rloc - qg * NQ * rpt;
+      tile_step(t, kk, vt, true, [&](int e) {
+        const int f = f0 + g4 * 8 + e;
+        return is_branch ? (f >> sl_log) == own && (f & (p.SL - 1)) < p.suffix_len : f <= rloc;
+      });
+    }
+  }
+  stamp(p, ph, 7);
+  // ---- append the keys and values computed in this pass for later passes, from their LDS copies: the row's private
+  // suffix slot (branch) or its trunk position (extend)
+  for (int it = threadIdx.x; it < nf8; it += kFusedThreads) {
+    const int f = it >> 3, q8 = it & 7;
+    int m_o;
+    bool valid, stored;
+    fresh_row(f, m_o, valid, stored);
+    if (!valid || stored) continue;
+    const u32x2 k_lo = *(const u32x2*)(kf_s + f * 72 + q8 * 4), k_hi = *(const u32x2*)(kf_s + f * 72 + 32 + q8 * 4);
+    Bf8 vv;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) vv.u[e] = vf_s[(q8 * 8 + e) * kMultiVs + f];
+    if (is_branch) {
+      const int64_t row = (((int64_t)m_o * p.suffix_cap + (p.suffix_len - 1)) * p.Hkv + hk) * 64;
+      *(gu32x2*)(suffix_k + row + q8 * 4) = k_lo;
+      *(gu32x2*)(suffix_k + row + 32 + q8 * 4) = k_hi;
+      *(gbf16x8*)(suffix_v + row + q8 * 8) = vv.v;
+    } else {
+      const int slot = p.rows[m_o].kv_slot;
+      const int64_t bb = PG ? ((int64_t)p.pages[(int64_t)b * p.page_stride + (slot >> 5)] * p.Hkv + hk) * 2048
+                            : (int64_t)(b * p.Hkv + hk) * p.vt_stride * 64 + (int64_t)(slot >> 5) * 2048;
+      const int64_t row = bb + (int64_t)(slot & 31) * 64;
+      *(gu32x2*)(trunk_k + row + q8 * 4) = k_lo;
+      *(gu32x2*)(trunk_k + row + 32 + q8 * 4) = k_hi;
+      gbf16* vcol = (gbf16*)trunk_vt + bb + (q8 * 8) * 32 + (slot & 31);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) vcol[e * 32] = vv.u[e];
+    }
+  }
+  // ---- the 8 wavefronts' partial softmaxes meet in LDS (every wavefront read its queries before the barrier above and has
+  // passed it, but another may still be on its way there: a barrier before their place is written)
+  wg_barrier();
+#pragma unroll
+  for (int t = 0; t < NQ; ++t) {
+    l_run[t] = sum_over_rows(l_run[t]);
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) red[((t * kFusedWaves + wave) * 4 + dt) * 64 + lane] = acc[t][dt];
+    if (g4 == 0) {
+      ml[((t * kFusedWaves + wave) * 16 + li) * 2] = thr[t] == -INFINITY ? -INFINITY : -negref[t][0];
+      ml[((t * kFusedWaves + wave) * 16 + li) * 2 + 1] = l_run[t];
+    }
+  }
+  wg_barrier();
+  for (int idx = threadIdx.x; idx < NQ * 256; idx += kFusedThreads) {
+    const int t = idx >> 8, qi = idx & 15, dq = (idx >> 4) & 15;       // query row of tile t, dims 4 dq .. 4 dq + 3
+    const float* mlt = ml + (t * kFusedWaves * 16 + qi) * 2;
+    float mmax = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kFusedWaves; ++w) mmax = fmaxf(mmax, mlt[w * 32]);
+    const float m_use = mmax == -INFINITY ? 0.f : mmax;
+    float lsum = 0.f;
+    f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kFusedWaves; ++w) {
+      const float wgt = exp2_fast(mlt[w * 32] - m_use);
+      lsum += wgt * mlt[w * 32 + 1];
+      o += red[((t * kFusedWaves + w) * 4 + (dq >> 2)) * 64 + qi + 16 * (dq & 3)] * wgt;
+    }
+    const int qrow = (qg * NQ + t) * 16 + qi;
+    if (qrow >= RG) continue;
+    if (p.NS == 1) {
+      const int mm = b * p.R + (qrow >> g_log);
+      const int k = (hk * p.G + (qrow & (p.G - 1))) * 64 + dq * 4;
+      const float inv = 1.0f / lsum;
+      bf16_t hi[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) hi[e] = to_f16(o[e] * inv);
+      *(uint64_t*)(p.att + b_off<MT>(k, mm)) = pack_bf16x4(hi[0], hi[1], hi[2], hi[3]);
+    } else {
+      const int64_t pb = ((int64_t)(b * p.Hkv + hk) * p.NS + s) * (p.QT * 16) + qrow;
+      if (dq == 0) *(uint64_t*)(p.part_ml + pb * 2) = pack_f32x2(mmax, lsum);
+      *(gf32x4*)((gfloat*)p.part_o + pb * 64 + dq * 4) = o;
+    }
+  }
+  stamp(p, ph, 2);
+}
+
+// Merge of a wide pass's key splits.
+__global__ __launch_bounds__(kFusedThreads) void wide_merge_kernel(FusedParams p, int ph) {
+  stamp(p, ph, 0);
+  attn_merge_unit<kWideTiles, kFusedWideRows, 1>(p, blockIdx.x, p.part_o, p.part_ml, p.att);
   stamp(p, ph, 2);
 }
 
@@ -2410,6 +2415,8 @@ int check_residency_pl(int nwg, int cus) {
   return SSD_OK;
 }
 
+int wide_k_tiles(const FusedGemm& g) { return g.KS * kFusedWaves * g.KTW; }
+
 template <int ATW, int EPI, int D, int MTG>
 int launch_wide_gemm_dm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
   static bool configured = false;
@@ -2420,22 +2427,6 @@ int launch_wide_gemm_dm(const FusedParams& p, const FusedGemm& g, const bf16_t* 
   wide_gemm_kernel<ATW, EPI, D, MTG><<<p.nwg, kWideThreads, kFusedLdsBytes, s>>>(p, g, bsrc, e);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
-}
-
-template <int ATW, int EPI, int D>
-int launch_wide_gemm_d(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
-  // Row groups as small as still give every pair a workgroup of its own: what bounds these kernels is what one compute
-  // unit pulls (4 KiB of weights + 1 KiB per row tile of the group, per k-tile), and with few rows or few feature tiles
-  // the full-size groups leave most of the grid without a pair while the busy workgroups pull as much as ever.
-  const int nq = ATW == 4 ? g.n_units / g.KS : (g.n_units / g.KS) >> 1;
-  const int tiles = (p.M + 15) >> 4;
-  auto fits = [&](int mtg) { return nq * ((tiles + mtg - 1) / mtg) <= p.nwg; };
-  if constexpr (ATW == 2) {
-    if (fits(1)) return launch_wide_gemm_dm<ATW, EPI, D, 1>(p, g, bsrc, e, s);
-    if (fits(2)) return launch_wide_gemm_dm<ATW, EPI, D, 2>(p, g, bsrc, e, s);
-    if (fits(kWideGroup / 2)) return launch_wide_gemm_dm<ATW, EPI, D, kWideGroup / 2>(p, g, bsrc, e, s);
-  }
-  return launch_wide_gemm_dm<ATW, EPI, D, kWideGroup>(p, g, bsrc, e, s);
 }
 
 template <int EPI>
@@ -2450,58 +2441,90 @@ int launch_wide_gemm_lds(const FusedParams& p, const FusedGemm& g, const bf16_t*
   return SSD_OK;
 }
 
-template <int ATW, int EPI>
+template <int ATW, int EPI, int MTG>
 int launch_wide_gemm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
   // a wavefront's k-tiles per pair must be whole turns of the ring
-  if ((2 * g.KS * g.KTW) % kWideRing == 0) return launch_wide_gemm_d<ATW, EPI, kWideRing>(p, g, bsrc, e, s);
-  return launch_wide_gemm_d<ATW, EPI, kWideRing / 2>(p, g, bsrc, e, s);
+  if (wide_k_tiles(g) / (kWideWaves * e.S) % kWideRing == 0) return launch_wide_gemm_dm<ATW, EPI, kWideRing, MTG>(p, g, bsrc, e, s);
+  return launch_wide_gemm_dm<ATW, EPI, kWideRing / 2, MTG>(p, g, bsrc, e, s);
 }
 
-// One wide pass: phases [first, last] as one launch each.  layers_host: the pass's layer table in host memory.
+// qkv: row groups as small as still give every pair a workgroup of its own (with few rows the full-size groups leave most
+// of the grid without a pair while the busy workgroups pull as much as ever).
+int launch_wide_qkv(const FusedParams& p, const FusedGemm& g, const WideEpi& e, hipStream_t s) {
+  const int nq = (g.n_units / g.KS) >> 1, tiles = (p.M + 15) >> 4;
+  auto fits = [&](int mtg) { return nq * ((tiles + mtg - 1) / mtg) <= p.nwg; };
+  if (fits(1)) return launch_wide_gemm<2, FE_QKV, 1>(p, g, p.xn, e, s);
+  if (fits(2)) return launch_wide_gemm<2, FE_QKV, 2>(p, g, p.xn, e, s);
+  if (fits(kWideGroup / 2)) return launch_wide_gemm<2, FE_QKV, kWideGroup / 2>(p, g, p.xn, e, s);
+  return launch_wide_gemm<2, FE_QKV, kWideGroup>(p, g, p.xn, e, s);
+}
+
+// o and down: the largest row groups, and as many k-slices as give every pair a workgroup of its own; *slices = how many
+int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
+  const int nq = (g.n_units / g.KS) >> 1, tiles = (p.M + 15) >> 4;
+  const int mtg = tiles >= 4 ? kWideGroup : tiles;
+  const int n_rg = (tiles + mtg - 1) / mtg;
+  e.S = 1;
+  for (int S = kFusedWideSlices; S > 1; S >>= 1)
+    if (nq * n_rg * S <= p.nwg && wide_k_tiles(g) % (kWideWaves * S * (kWideRing / 2)) == 0) { e.S = S; break; }
+  switch (mtg) {
+    case 1: return launch_wide_gemm<2, FE_PART, 1>(p, g, bsrc, e, s);
+    case 2: return launch_wide_gemm<2, FE_PART, 2>(p, g, bsrc, e, s);
+    case 3: return launch_wide_gemm<2, FE_PART, 3>(p, g, bsrc, e, s);
+    default: return launch_wide_gemm<2, FE_PART, kWideGroup>(p, g, bsrc, e, s);
+  }
+}
+
+// One wide pass: phases [first, last] as one launch each (two for o and down).  layers_host: the pass's layer table in host
+// memory.
 template <class PL, bool PG>
 int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int first, int last, hipStream_t s) {
-  static bool configured = false;
-  if (!configured) {
-    SSD_HIP(hipFuncSetAttribute((const void*)wide_kernel<PL, PG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes));
-    configured = true;
-  }
+  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_attn_kernel<PL::q, PL::p, PG>,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMultiLdsBytes);
+  SSD_HIP(configured);
   const int lm_phase = fused_last_phase(p.L);
   for (int ph = first; ph <= last; ++ph) {
-    const int l = ph == 0 ? 0 : (ph == lm_phase ? p.L - 1 : (ph - 1) / 6);
-    const int sub = ph == 0 ? -1 : (ph == lm_phase ? 6 : (ph - 1) % 6);
-    if (sub == 2 && p.NS == 1) continue;             // no merge phase with one key split
-    const FusedLayer& L = layers_host[l];
+    if (ph == 0) {
+      wide_resid_kernel<true><<<p.M, kWideThreads, 0, s>>>(p, nullptr, 0, layers_host[0].attn_norm, nullptr, ph);
+      SSD_HIP(hipGetLastError());
+      continue;
+    }
     WideEpi e{};
     e.ph = ph;
+    e.S = 1;
+    if (ph == lm_phase) {
+      if (p.logits) {
+        e.out = p.logits; e.ld = p.logits_ld;
+        SSD_TRY((launch_wide_gemm_lds<FE_LOGITS>(p, p.lm, p.xn, e, s)));
+      }
+      continue;
+    }
+    const int l = (ph - 1) / 6, sub = (ph - 1) % 6;
+    const FusedLayer& L = layers_host[l];
     if (sub == 0) {
-      e.out = p.qkv; e.ld = p.qkvd; e.ssq_in = p.ssq;
-      SSD_TRY((launch_wide_gemm<2, FE_QKV>(p, L.qkv, p.xn, e, s)));
+      e.out = p.qkv; e.ld = p.qkvd;
+      SSD_TRY(launch_wide_qkv(p, L.qkv, e, s));
     } else if (sub == 3 || sub == 5) {
-      e.h_in = e.h_out = p.h;     // every element is read and rewritten by one lane
-      e.gain = sub == 3 ? L.mlp_norm : (l + 1 < p.L ? layers_host[l + 1].attn_norm : p.final_norm);
-      e.xn_out = p.xn;
-      e.ssq_out = p.ssq;
-      SSD_TRY((launch_wide_gemm<2, FE_RESID>(p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s)));
+      e.out = p.fix_buf; e.ld = p.d;
+      SSD_TRY(launch_wide_part(p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s));
+      const bool fin = sub == 5 && l + 1 == p.L;
+      wide_resid_kernel<false><<<p.M, kWideThreads, 0, s>>>(p, p.fix_buf, e.S, sub == 3 ? L.mlp_norm : (fin ? p.final_norm : layers_host[l + 1].attn_norm),
+                                                            fin ? p.hidden : nullptr, ph);
+      SSD_HIP(hipGetLastError());
     } else if (sub == 4) {
-      e.act_out = p.act; e.ssq_in = p.ssq;
+      e.act_out = p.act;
       // one row group (up to 96 rows): a workgroup per unit of 4 feature tiles, the reduction dimension over its
       // wavefronts, instead of 16 feature tiles per workgroup on a quarter of the grid
       if (((p.M + 15) >> 4) <= kWideGroup && L.gu.n_units <= p.nwg) {
-        SSD_TRY((launch_wide_gemm<4, FE_SWIGLU>(p, L.gu, p.xn, e, s)));
+        SSD_TRY((launch_wide_gemm<4, FE_SWIGLU, kWideGroup>(p, L.gu, p.xn, e, s)));
       } else {
         SSD_TRY((launch_wide_gemm_lds<FE_SWIGLU>(p, L.gu, p.xn, e, s)));
       }
-    } else {
-      if (sub == 6 && p.logits) {
-        e.out = p.logits; e.ld = p.logits_ld; e.ssq_in = p.ssq;
-        SSD_TRY((launch_wide_gemm_lds<FE_LOGITS>(p, p.lm, p.xn, e, s)));
-      }
-      if (sub == 6 && !p.hidden) continue;
-      int grid = p.nwg;
-      if (sub == 1) grid = p.n_attn_units;
-      else if (sub == 2) grid = p.n_pair_units;
-      else if (sub == 6) grid = p.M;
-      wide_kernel<PL, PG><<<grid, kFusedThreads, kFusedLdsBytes, s>>>(p, ph);
+    } else if (sub == 1) {
+      wide_attn_kernel<PL::q, PL::p, PG><<<p.n_attn_units, kFusedThreads, kMultiLdsBytes, s>>>(p, L.trunk_k, L.trunk_vt, L.suffix_k, L.suffix_v, ph);
+      SSD_HIP(hipGetLastError());
+    } else if (p.NS > 1) {                           // (no merge phase with one key split)
+      wide_merge_kernel<<<p.n_pair_units, kFusedThreads, 0, s>>>(p, ph);
       SSD_HIP(hipGetLastError());
     }
   }

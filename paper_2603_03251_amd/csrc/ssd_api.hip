@@ -747,7 +747,7 @@ int fused_setup(ssd_ctx* c) {
       };
       carve(&w.h, MW * p.d * 4);
       carve(&w.xn, MW * p.d * 2);
-      carve(&w.ssq, (size_t)(p.d / 64) * MW * 4);
+      carve(&w.fix_buf, (size_t)kFusedWideSlices * MW * p.d * 4);
       carve(&w.qkv, MW * p.qkvd * 4);
       carve(&w.att, MW * p.qd * 2);
       carve(&w.act, MW * p.ffn * 2);
