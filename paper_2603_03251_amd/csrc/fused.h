@@ -14,7 +14,7 @@ constexpr int kFusedThreads = 512;  // 8 wavefronts; they split the reduction di
 constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxRows = 48;   // rows of one narrow pass (three 16-row MFMA tiles)
 constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles): contexts with more than kFusedMaxRows rows
-constexpr int kFusedWideQueryTiles = 3;   // wide passes: query tiles per attention unit (n_attn_units counts such units)
+constexpr int kFusedWideQueryTiles = 3;   // wide passes: most query tiles per attention unit
 constexpr int kFusedWideFreshKeys = 192;  // wide passes: tokens of one sequence an extend pass takes (LDS room of the attention unit)
 constexpr int kFusedWideSlices = 8;       // wide passes: most k-slices of the o- and down-projections (one per XCD)
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())
@@ -65,6 +65,7 @@ struct FusedParams {
   int KPU;                                 // stored trunk keys per split (multiple of 32)
   int NS;                                  // key splits; 1 = the attention phase writes the final output
   int QT;                                  // query tiles per (sequence, KV head) = ceil(R G / 16)
+  int NQ;                                  // wide passes: query tiles per attention unit (n_attn_units counts such units)
   int SL;                                  // fresh-key slots per branch row (8 or 16)
   int is_branch;                           // 1: branch rows (private suffix), 0: extend rows (causal among themselves)
   int suffix_len;                          // branch rows: private positions a row sees, its own token included

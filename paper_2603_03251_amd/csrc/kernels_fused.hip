@@ -1627,10 +1627,11 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
 //   2^8 (probabilities up to 256 are as exact as those up to 1), which one comparison per lane tests, instead of a maximum
 //   across lanes per block; visibility is tested only in blocks that reach past a tile's shortest row;
 // - the eight wavefronts' partial softmaxes of all NQ tiles meet in LDS at once, after the new keys have been appended.
-// 26.5 us (36.1 before), 16.5 for 170 prompt tokens (22), 19 for 96 rows over 4 sequences of up to 1500 (26.8).
+// 26.0 us (36.1 with a unit that did none of this), 15.1 for 170 prompt tokens (22), 14.4 for 96 rows over 4 sequences of up
+// to 1500 keys (26.8).
 constexpr int kMultiFreshKeys = kFusedWideFreshKeys;   // LDS room: NQ x (rows per tile x slots per row) for NQ = 3, or the tokens of an extend
 constexpr int kMultiVs = kMultiFreshKeys + 8;          // V^T row of the fresh keys
-constexpr int kMultiQ = kFusedWideQueryTiles;
+constexpr int kMultiQ = kFusedWideQueryTiles;          // most query tiles of a unit
 constexpr float kMultiSlack = 8.0f;                    // log2 of how far scores may exceed the reference
 // LDS: fresh keys [f][72], fresh values^T [64][kMultiVs]; then the query operands, later (same place) the partial outputs
 // [NQ][wave][4][64] f32x4; then the partial (reference, sum) [NQ][wave][16][2]
@@ -1639,10 +1640,10 @@ constexpr size_t kMultiRedBytes = (size_t)kMultiQ * kFusedWaves * 4 * 64 * 16;
 constexpr size_t kMultiLdsBytes = kMultiFreshBytes + kMultiRedBytes + (size_t)kMultiQ * kFusedWaves * 16 * 2 * 4;
 static_assert(kMultiFreshBytes % 16 == 0 && kMultiLdsBytes <= 160 * 1024, "LDS of the wide attention unit");
 
-template <int NPQ, int NPP, bool PG>
+template <int NPQ, int NPP, int NQ, bool PG>
 __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p, bf16_t* trunk_k, bf16_t* trunk_vt, bf16_t* suffix_k,
                                                                   bf16_t* suffix_v, int ph) {
-  constexpr int NQ = kMultiQ, MT = kWideTiles;
+  constexpr int MT = kWideTiles;
   extern __shared__ f32x4 lds[];
   bf16_t* kf_s = (bf16_t*)lds;
   bf16_t* vf_s = kf_s + kMultiFreshKeys * 72;
@@ -1668,12 +1669,17 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
   // query row of a lane in tile t (clamped: rows past the last are computed like it and never stored)
   auto row_of = [&](int t) { return min((qg * NQ + t) * 16 + li, RG - 1); };
 
+  const int kb0 = s * p.KPU;
+  int pgs = 0;
+  if constexpr (PG) pgs = p.pages[(int64_t)b * p.page_stride + min((kb0 >> 5) + wave + kFusedWaves * lane, p.page_stride - 1)];
   // ---- issue: row descriptors, the raw queries (wavefront t: tile t), the first fresh keys
   int tv[NQ];                                                 // stored keys this lane's query rows see
 #pragma unroll
   for (int t = 0; t < NQ; ++t) {
-    const int m = b * p.R + (row_of(t) >> g_log);
-    tv[t] = trunk_visible(p.rows[m], m, p.R);
+    // (an extend's descriptor counts the pass's own tokens, here fresh keys, up to the row itself.  The pass's kind comes
+    // from the launch: tested per row it would put a round trip to memory between these loads and the next)
+    const int rloc = row_of(t) >> g_log;
+    tv[t] = p.rows[b * p.R + rloc].vis - (is_branch ? 0 : 1 + rloc);
   }
   f32x4 qraw[4], qcs[4];
   if (wave < NQ) {
@@ -1712,24 +1718,25 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
   auto load_fresh = [&](Fresh& x, int it) {
     const int f = it >> 3, q8 = it & 7;
     int m_o;
-    x.valid = x.stored = false;
-    if (it >= nf8) return;
     fresh_row(f, m_o, x.valid, x.stored);
-    if (x.valid && x.stored) {
+    x.valid = x.valid && it < nf8;
+    if (!x.valid) return;
+    // both sources in one stretch of loads (a branch on `stored` made the second wait for the first); the slots of a row
+    // up to its own are inside its suffix
+    const gfloat* kp = gq + (int64_t)m_o * p.qkvd + p.qd + hk * 64 + q8 * 4;
+    x.a = *(const gf32x4*)kp;
+    x.bb = *(const gf32x4*)(kp + 32);
+    const gfloat* cs = gcs + ((int64_t)m_o * 32 + q8 * 4) * 2;
+    x.c0 = *(const gf32x4*)cs;
+    x.c1 = *(const gf32x4*)(cs + 4);
+    const gfloat* vp = gq + (int64_t)m_o * p.qkvd + p.qd + p.kvd + hk * 64 + q8 * 8;
+    x.v0 = *(const gf32x4*)vp;
+    x.v1 = *(const gf32x4*)(vp + 4);
+    if (is_branch) {
       const int64_t row = (((int64_t)m_o * p.suffix_cap + (f & (p.SL - 1))) * p.Hkv + hk) * 64;
       x.k_lo = *(const gu32x2*)(suffix_k + row + q8 * 4);
       x.k_hi = *(const gu32x2*)(suffix_k + row + 32 + q8 * 4);
       x.v = *(const gbf16x8*)(suffix_v + row + q8 * 8);
-    } else if (x.valid) {
-      const gfloat* kp = gq + (int64_t)m_o * p.qkvd + p.qd + hk * 64 + q8 * 4;
-      x.a = *(const gf32x4*)kp;
-      x.bb = *(const gf32x4*)(kp + 32);
-      const gfloat* cs = gcs + ((int64_t)m_o * 32 + q8 * 4) * 2;
-      x.c0 = *(const gf32x4*)cs;
-      x.c1 = *(const gf32x4*)(cs + 4);
-      const gfloat* vp = gq + (int64_t)m_o * p.qkvd + p.qd + p.kvd + hk * 64 + q8 * 8;
-      x.v0 = *(const gf32x4*)vp;
-      x.v1 = *(const gf32x4*)(vp + 4);
     }
   };
   auto stage_fresh = [&](const Fresh& x, int it) {   // rotated, to LDS (zeros where there is no key)
@@ -1768,20 +1775,17 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- issue: the first trunk blocks of this wavefront (block counts from the host's bound)
-  const int kb0 = s * p.KPU;
   const int kend_ub = min(kb0 + p.KPU, p.tv_ub);
   const int n_tb = kend_ub > kb0 ? (kend_ub - kb0 + 31) >> 5 : 0;
   const int n_mine = n_tb > wave ? (n_tb - wave + kFusedWaves - 1) / kFusedWaves : 0;
   const int krow = (li >> 2) * 8 + (li & 3);                  // key of this lane's A-operand row in a block (tile 0)
   // PG (paged trunk, App. B "PagedAttention"): block j of sequence b is page p.pages[b][j] of a pool shared by all
   // sequences, a page = the same 4 KiB per head and operand as a block of the contiguous layouts.  Lane i of a wavefront
-  // fetches the page of the wavefront's i-th block up front (one load), so the block loop itself stays free of
+  // fetched the page of the wavefront's i-th block first of all (one load), so the block loop itself stays free of
   // dependent loads; entries behind a sequence's allocation name page 0, which exists and holds zeros.
   const int64_t head0 = PG ? 0 : ((int64_t)(b * p.Hkv + hk) * p.vt_stride) * 64;
   const gbf16* kbase = (const gbf16*)trunk_k + head0 + g4 * 8;
   const gbf16* vbase = (const gbf16*)trunk_vt + head0 + li * 32 + g4 * 8;
-  int pgs = 0;
-  if constexpr (PG) pgs = p.pages[(int64_t)b * p.page_stride + min((kb0 >> 5) + wave + kFusedWaves * lane, p.page_stride - 1)];
   struct KvBlock {
     bf16x8 k[2][2];
     bf16x8 vt[4];
@@ -2475,13 +2479,28 @@ int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
   }
 }
 
+// The attention units of a pass, p.NQ query tiles each (host: as few as leave no compute unit with two units)
+template <class PL, bool PG, int NQ>
+int launch_wide_attn_nq(const FusedParams& p, const FusedLayer& L, int ph, hipStream_t s) {
+  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_attn_kernel<PL::q, PL::p, NQ, PG>,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMultiLdsBytes);
+  SSD_HIP(configured);
+  wide_attn_kernel<PL::q, PL::p, NQ, PG><<<p.n_attn_units, kFusedThreads, kMultiLdsBytes, s>>>(p, L.trunk_k, L.trunk_vt, L.suffix_k, L.suffix_v, ph);
+  SSD_HIP(hipGetLastError());
+  return SSD_OK;
+}
+template <class PL, bool PG>
+int launch_wide_attn(const FusedParams& p, const FusedLayer& L, int ph, hipStream_t s) {
+  static_assert(kMultiQ == 3, "an instance per number of query tiles");
+  if (p.NQ == 1) return launch_wide_attn_nq<PL, PG, 1>(p, L, ph, s);
+  if (p.NQ == 2) return launch_wide_attn_nq<PL, PG, 2>(p, L, ph, s);
+  return launch_wide_attn_nq<PL, PG, 3>(p, L, ph, s);
+}
+
 // One wide pass: phases [first, last] as one launch each (two for o and down).  layers_host: the pass's layer table in host
 // memory.
 template <class PL, bool PG>
 int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int first, int last, hipStream_t s) {
-  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_attn_kernel<PL::q, PL::p, PG>,
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMultiLdsBytes);
-  SSD_HIP(configured);
   const int lm_phase = fused_last_phase(p.L);
   for (int ph = first; ph <= last; ++ph) {
     if (ph == 0) {
@@ -2521,8 +2540,7 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
         SSD_TRY((launch_wide_gemm_lds<FE_SWIGLU>(p, L.gu, p.xn, e, s)));
       }
     } else if (sub == 1) {
-      wide_attn_kernel<PL::q, PL::p, PG><<<p.n_attn_units, kFusedThreads, kMultiLdsBytes, s>>>(p, L.trunk_k, L.trunk_vt, L.suffix_k, L.suffix_v, ph);
-      SSD_HIP(hipGetLastError());
+      SSD_TRY((launch_wide_attn<PL, PG>(p, L, ph, s)));
     } else if (p.NS > 1) {                           // (no merge phase with one key split)
       wide_merge_kernel<<<p.n_pair_units, kFusedThreads, 0, s>>>(p, ph);
       SSD_HIP(hipGetLastError());
@@ -2575,6 +2593,7 @@ int launch_fused_wide(const FusedParams& p, const FusedLayer* layers_host, int f
   SSD_CHECK_ARG(p.KPU >= 32 && p.KPU % 32 == 0 && p.NS >= 1 && p.QT >= 1 && (p.SL == 8 || p.SL == 16) && 16 % p.G == 0 &&
                     (16 / p.G) * p.SL <= 64,
                 "bad attention split");
+  SSD_CHECK_ARG(p.NQ >= 1 && p.NQ <= kMultiQ && p.n_attn_units == p.B * p.Hkv * ((p.QT + p.NQ - 1) / p.NQ) * p.NS, "bad attention units");
   SSD_CHECK_ARG(first >= 0 && last <= fused_last_phase(p.L) && first <= last && layers_host, "bad phase range");
   if (p.pages) {
     SSD_CHECK_ARG((p.planes & 24) != 24, "a paged trunk takes the default planes of the attention unit only");

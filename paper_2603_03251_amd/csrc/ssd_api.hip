@@ -448,7 +448,12 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
   // on the 1B shape; the choice only affects speed.
   {
     const int seqs = n_seq < per_pass ? n_seq : (per_pass > 0 ? per_pass : 1);
-    const int pairs = seqs * p.Hkv * (wide ? (p.QT + kFusedWideQueryTiles - 1) / kFusedWideQueryTiles : p.QT);
+    // Wide passes: units of as few query tiles as give every compute unit at most one, so that few rows still fill the
+    // chip (24 rows x 4 sequences: 14.4 us as 192 units of one tile, 19 as 64 of three, whose sharing of the stored keys
+    // pays only when there are units enough)
+    p.NQ = 1;
+    while (wide && p.NQ < kFusedWideQueryTiles && seqs * p.Hkv * ((p.QT + p.NQ - 1) / p.NQ) > p.nwg) ++p.NQ;
+    const int pairs = seqs * p.Hkv * ((p.QT + p.NQ - 1) / p.NQ);
     int best = 1;
     float best_cost = 0.f;
     const int ns_cap = part.ns_max;                     // what the partial-softmax buffers were sized for
@@ -493,7 +498,7 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
     p.logits_ld = logits_ld;
     p.hidden = hidden ? hidden + row0 * hidden_ld : nullptr;
     p.hidden_ld = hidden_ld;
-    p.n_attn_units = p.B * p.Hkv * (wide ? (p.QT + kFusedWideQueryTiles - 1) / kFusedWideQueryTiles : p.QT) * p.NS;
+    p.n_attn_units = p.B * p.Hkv * ((p.QT + p.NQ - 1) / p.NQ) * p.NS;
     p.n_pair_units = (p.M * p.Hq + kFusedWaves - 1) / kFusedWaves;
     if (p.NS > 1 && (int64_t)p.B * p.Hkv * p.NS * p.QT * 16 > part.entries) {
       set_error("fused pass: attention partial buffer too small (%d splits, %d query tiles)", p.NS, p.QT);
