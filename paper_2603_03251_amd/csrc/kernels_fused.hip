@@ -1191,11 +1191,17 @@ struct WideEpi {
 };
 
 // ATW: feature tiles per unit of the layer's stream-order layout (2: qkv, o, down; 4: gate/up).
-// D: chunks of the ring (kWideRing; half of it for slices too short for whole turns of the full ring).
-// MTG: row tiles per row group: kWideGroup, or fewer where that gives every workgroup of the grid a pair.
+// D: chunks of the ring (kWideRing; half of it for slices too short for whole turns of the full ring, and for MTG = 12).
+// MTG: row tiles per row group.  Even: the MFMAs are 32x32x16, which a wavefront alone on its SIMD issues back to back (a
+// 16x16x32 every 28 clocks: the same time at 6 row tiles, but at 12 the 48 of a chunk would outlast its loads); both
+// operands stay in their 16x16x32 tile order, see wide_gemm_lds_kernel.
 template <int ATW, int EPI, int D, int MTG>
 __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
-  constexpr int MTOT = kWideTiles, NT = 4 * MTG;
+  constexpr int MTOT = kWideTiles;
+  constexpr bool BIG = MTG % 2 == 0;
+  constexpr int MT32 = MTG / 2;
+  constexpr int ROUNDS = MTG > kWideGroup ? 2 : 1;   // the partial tiles meet in LDS (at most 96 KiB) in this many parts
+  constexpr int NT = 4 * MTG / ROUNDS;               // 1 KiB blocks of a wavefront in a part
   extern __shared__ f32x4 red[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int NKT = g.KS * kFusedWaves * g.KTW;       // k-tiles of the reduction dimension
@@ -1215,11 +1221,27 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
   stamp(p, e.ph, 0);
   if (n_my == 0) return;
 
-  f32x4 acc[4][MTG];
+  // accumulators: BIG [32 features: tiles 0-1 / 2-3 of the set][32 rows], else [feature tile][row tile]
+  f32x16 accb[2][BIG ? MT32 : 1];
+  f32x4 acc[4][BIG ? 1 : MTG];
+  auto zero_acc = [&]() {
+    if constexpr (BIG) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j)
+      for (int f = 0; f < 2; ++f)
 #pragma unroll
-    for (int t = 0; t < MTG; ++t) acc[j][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < MT32; ++t)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) accb[f][t][i] = 0.f;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < MTG; ++t) acc[j][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  zero_acc();
+  // operand vector of this lane in a tile (BIG: in two neighbouring tiles, k-half 0; k-half 1 is 32 vectors further)
+  const int lsrc = BIG ? ((lane >> 4) & 1) * 64 + (lane & 15) + ((lane >> 5) << 4) : lane;
 
   // The load cursor walks the chunks of this wavefront, pair after pair (clamped to the last one)
   struct Cursor {
@@ -1245,29 +1267,34 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
       place(cu);
     }
   };
-  // (plain, cached loads also for the weights: the other row groups of the same feature tiles, on this XCD, find them
-  // in its L2; a streaming hint would make every row group fetch them from memory again)
+  // (plain, cached loads also for the weights: the other row groups of the same feature tiles, on this XCD, find them in
+  // its L2; a streaming hint would make every row group fetch them from memory again, and with one row group it measured
+  // slower too: down 17.6 instead of 15.8 us at 96 rows)
   auto load_chunk = [&](WideChunk<MTG>& ck, const Cursor& cu) {
-    const gbf16x8* ap = (const gbf16x8*)cu.a + lane;
-    if constexpr (ATW == 4) {
+    const gbf16x8* ap = (const gbf16x8*)cu.a + lsrc;
+    const gbf16x8* ap2 = ATW == 4 ? ap + 128 : (const gbf16x8*)(cu.a + a_group2) + lsrc;
+    ck.a[0] = ap[0];                         // BIG: [2 f + h], features 32 f .. 32 f + 31 of the set, k-half h
+    ck.a[1] = ap[BIG ? 32 : 64];
+    ck.a[2] = ap2[0];
+    ck.a[3] = ap2[BIG ? 32 : 64];
+    const gbf16x8* bp = (const gbf16x8*)cu.b + lsrc;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) ck.a[j] = ap[j * 64];
-    } else {
-      const gbf16x8* ap2 = (const gbf16x8*)(cu.a + a_group2) + lane;
-      ck.a[0] = ap[0];
-      ck.a[1] = ap[64];
-      ck.a[2] = ap2[0];
-      ck.a[3] = ap2[64];
-    }
-    const gbf16x8* bp = (const gbf16x8*)cu.b + lane;
-#pragma unroll
-    for (int t = 0; t < MTG; ++t) ck.b[t] = bp[t * 64];
+    for (int t = 0; t < MTG; ++t) ck.b[t] = BIG ? bp[(t >> 1) * 128 + (t & 1) * 32] : bp[t * 64];   // BIG: [2 t + h]
   };
   auto mfma_chunk = [&](const WideChunk<MTG>& ck) {
+    if constexpr (BIG) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int t = 0; t < MTG; ++t) acc[j][t] = mfma16_f16(ck.a[j], ck.b[t], acc[j][t]);
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int t = 0; t < MT32; ++t) accb[f][t] = mfma32_f16(ck.a[2 * f + h], ck.b[2 * t + h], accb[f][t]);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < MTG; ++t) acc[j][t] = mfma16_f16(ck.a[j], ck.b[t], acc[j][t]);
+    }
   };
 
   WideChunk<MTG> ring[D];
@@ -1288,48 +1315,65 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
       }
     }
     if (n == 0) stamp(p, e.ph, 4);
-    // ---- end of a pair: the 4 wavefronts' partial tiles meet in LDS; every wavefront sums its share of the tiles in
-    // wavefront order and runs their epilogue
+    // ---- end of a pair: the 4 wavefronts' partial tiles meet in LDS; every wavefront sums its share of the 1 KiB blocks in
+    // wavefront order and runs their epilogue.  Block idx of a part: BIG (f, t, q) = registers 4 q .. 4 q + 3 of accb[f][t]:
+    // features 32 f + 8 q + 4 (lane >> 5) .. + 3, row 32 t + (lane & 31); else (j, t): features 16 j + 4 (lane >> 4) .. + 3,
+    // row 16 t + (lane & 15)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int rd = 0; rd < ROUNDS; ++rd) {
+      constexpr int TR = (BIG ? MT32 : MTG) / ROUNDS;          // row tiles of a part
+      if constexpr (BIG) {
 #pragma unroll
-      for (int tt = 0; tt < MTG; ++tt) {
-        red[(wave * NT + j * MTG + tt) * 64 + lane] = acc[j][tt];
-        acc[j][tt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int tt = 0; tt < TR; ++tt)
+#pragma unroll
+            for (int qq = 0; qq < 4; ++qq) {
+              const f32x16& v = accb[f][rd * TR + tt];
+              red[(wave * NT + (f * TR + tt) * 4 + qq) * 64 + lane] = (f32x4){v[4 * qq], v[4 * qq + 1], v[4 * qq + 2], v[4 * qq + 3]};
+            }
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int tt = 0; tt < TR; ++tt) red[(wave * NT + j * TR + tt) * 64 + lane] = acc[j][tt];
       }
-    wg_barrier();
-    auto total = [&](int idx) {
-      f32x4 v = red[idx * 64 + lane];
+      wg_barrier();
+      auto total = [&](int idx) {
+        f32x4 v = red[idx * 64 + lane];
 #pragma unroll
-      for (int w = 1; w < kWideWaves; ++w) v += red[(w * NT + idx) * 64 + lane];
-      return v;
-    };
-    const int f4 = (lane >> 4) * 4;
-    if constexpr (EPI == FE_SWIGLU) {
-      // feature tiles 0, 1 of the set are gate, 2, 3 the matching up tiles
-      for (int idx = wave; idx < 2 * MTG; idx += kWideWaves) {
-        const int j = idx / MTG, tt = idx - j * MTG;
-        const f32x4 gv = total(idx), uv = total(idx + 2 * MTG);
-        const int m = (rg * MTG + tt) * 16 + (lane & 15);
-        if (m < p.M) {
-          bf16_t hi[4];
+        for (int w = 1; w < kWideWaves; ++w) v += red[(w * NT + idx) * 64 + lane];
+        return v;
+      };
+      // features (of the set of 64) and row (of the pass) of block idx
+      auto feature_of = [&](int idx) { return BIG ? (idx / (4 * TR)) * 32 + (idx & 3) * 8 + (lane >> 5) * 4 : (idx / TR) * 16 + (lane >> 4) * 4; };
+      auto row_of = [&](int idx) {
+        return rg * MTG * 16 + (BIG ? (rd * TR + (idx >> 2) % TR) * 32 + (lane & 31) : (idx % TR) * 16 + (lane & 15));
+      };
+      if constexpr (EPI == FE_SWIGLU) {
+        // features 0..31 of the set are gate, 32..63 the matching up features: blocks idx and idx + NT / 2
+        for (int idx = wave; idx < NT / 2; idx += kWideWaves) {
+          const f32x4 gv = total(idx), uv = total(idx + NT / 2);
+          const int m = row_of(idx);
+          if (m < p.M) {
+            bf16_t hi[4];
 #pragma unroll
-          for (int i = 0; i < 4; ++i) hi[i] = to_f16(gv[i] / (1.0f + __expf(-gv[i])) * uv[i]);
-          const int k = q * 32 + j * 16 + f4;      // input index of the down-projection
-          st_u64_uncounted(e.act_out + b_off<MTOT>(k, m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
+            for (int i = 0; i < 4; ++i) hi[i] = to_f16(gv[i] / (1.0f + __expf(-gv[i])) * uv[i]);
+            // input index of the down-projection
+            st_u64_uncounted(e.act_out + b_off<MTOT>(q * 32 + feature_of(idx), m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
+          }
+        }
+      } else {
+        float* out = e.out + (EPI == FE_PART ? (int64_t)slice * p.M * e.ld : 0);
+        for (int idx = wave; idx < NT; idx += kWideWaves) {
+          const f32x4 v = total(idx);
+          const int m = row_of(idx), n0 = q * 64 + feature_of(idx);
+          if ((n0 >> 4) < g.NT && m < p.M) st_f32x4_uncounted(out + (int64_t)m * e.ld + n0, v);
         }
       }
-    } else {
-      float* out = e.out + (EPI == FE_PART ? (int64_t)slice * p.M * e.ld : 0);
-      for (int idx = wave; idx < NT; idx += kWideWaves) {
-        const int j = idx / MTG, tt = idx - j * MTG;
-        const f32x4 v = total(idx);
-        const int m = (rg * MTG + tt) * 16 + (lane & 15);
-        const int tile = q * 4 + j;
-        if (tile < g.NT && m < p.M) st_f32x4_uncounted(out + (int64_t)m * e.ld + tile * 16 + f4, v);
-      }
+      wg_barrier();
     }
-    wg_barrier();
+    zero_acc();
     if (n == 0) stamp(p, e.ph, 5);
   }
   stamp(p, e.ph, 2);
@@ -1441,7 +1485,8 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
 // takes its 16 bytes from lane (l & 15) + 16 (l >> 5) + 32 h of tile (l >> 4) & 1, a fixed offset per lane.
 constexpr int kWideStage = 8;   // k-tiles per LDS stage of the activation operand
 
-template <int EPI>
+// NTW (one row group): the weights are read once and take the non-temporal path (LM head at 96 rows: 117 -> 108 us)
+template <int EPI, bool NTW>
 __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
   constexpr int MTOT = kWideTiles, MTG = kWideGroup, KC = kWideStage;
   constexpr int STAGE = KC * MTG * 64;               // 16-byte vectors per stage
@@ -1512,7 +1557,11 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
   auto load_a = [&](const Cursor& cu, int j) {       // ring[j][2 f + h]: features 32 f .. 32 f + 31 of the unit, k-half h
     const gbf16x8* ap = (const gbf16x8*)(cu.a + (int64_t)j * 4 * 512) + lsrc;
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) ring[j][jj] = ap[(jj >> 1) * 128 + (jj & 1) * 32];
+    for (int jj = 0; jj < 4; ++jj) {
+      const gbf16x8* q = ap + (jj >> 1) * 128 + (jj & 1) * 32;
+      if constexpr (NTW) ring[j][jj] = __builtin_nontemporal_load(q);
+      else ring[j][jj] = *q;
+    }
   };
 
   // ---- prologue: stage 0 of the first pair
@@ -2423,24 +2472,20 @@ int wide_k_tiles(const FusedGemm& g) { return g.KS * kFusedWaves * g.KTW; }
 
 template <int ATW, int EPI, int D, int MTG>
 int launch_wide_gemm_dm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
-  static bool configured = false;
-  if (!configured) {
-    SSD_HIP(hipFuncSetAttribute((const void*)wide_gemm_kernel<ATW, EPI, D, MTG>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes));
-    configured = true;
-  }
+  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_gemm_kernel<ATW, EPI, D, MTG>,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes);
+  SSD_HIP(configured);
   wide_gemm_kernel<ATW, EPI, D, MTG><<<p.nwg, kWideThreads, kFusedLdsBytes, s>>>(p, g, bsrc, e);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }
 
-template <int EPI>
+template <int EPI, bool NTW>
 int launch_wide_gemm_lds(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
-  static bool configured = false;
-  if (!configured) {
-    SSD_HIP(hipFuncSetAttribute((const void*)wide_gemm_lds_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes));
-    configured = true;
-  }
-  wide_gemm_lds_kernel<EPI><<<p.nwg, kWideThreads, kFusedLdsBytes, s>>>(p, g, bsrc, e);
+  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_gemm_lds_kernel<EPI, NTW>,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes);
+  SSD_HIP(configured);
+  wide_gemm_lds_kernel<EPI, NTW><<<p.nwg, kWideThreads, kFusedLdsBytes, s>>>(p, g, bsrc, e);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }
@@ -2448,7 +2493,8 @@ int launch_wide_gemm_lds(const FusedParams& p, const FusedGemm& g, const bf16_t*
 template <int ATW, int EPI, int MTG>
 int launch_wide_gemm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
   // a wavefront's k-tiles per pair must be whole turns of the ring
-  if (wide_k_tiles(g) / (kWideWaves * e.S) % kWideRing == 0) return launch_wide_gemm_dm<ATW, EPI, kWideRing, MTG>(p, g, bsrc, e, s);
+  if (MTG <= kWideGroup && wide_k_tiles(g) / (kWideWaves * e.S) % kWideRing == 0)
+    return launch_wide_gemm_dm<ATW, EPI, MTG <= kWideGroup ? kWideRing : kWideRing / 2, MTG>(p, g, bsrc, e, s);
   return launch_wide_gemm_dm<ATW, EPI, kWideRing / 2, MTG>(p, g, bsrc, e, s);
 }
 
@@ -2463,7 +2509,7 @@ int launch_wide_qkv(const FusedParams& p, const FusedGemm& g, const WideEpi& e, 
   return launch_wide_gemm<2, FE_QKV, kWideGroup>(p, g, p.xn, e, s);
 }
 
-// o and down: the largest row groups, and as many k-slices as give every pair a workgroup of its own; *slices = how many
+// o and down: the largest row groups, and as many k-slices as give every pair a workgroup of its own; e.S = how many
 int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
   const int nq = (g.n_units / g.KS) >> 1, tiles = (p.M + 15) >> 4;
   const int mtg = tiles >= 4 ? kWideGroup : tiles;
@@ -2477,6 +2523,21 @@ int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
     case 3: return launch_wide_gemm<2, FE_PART, 3>(p, g, bsrc, e, s);
     default: return launch_wide_gemm<2, FE_PART, kWideGroup>(p, g, bsrc, e, s);
   }
+}
+
+// gate/up + SwiGLU.  Up to 12 row tiles (192 rows) in one row group: a workgroup per unit of 4 feature tiles, the reduction
+// dimension over its wavefronts, every weight read once, instead of 16 feature tiles per workgroup on a quarter (up to
+// 96 rows) or half of the grid (170 rows: 27 us against 30; 32 rows: 18 against 20.9 in groups of 6).  With more rows 16 feature tiles per workgroup fill the
+// grid and pull less.
+int launch_wide_gate_up(const FusedParams& p, const FusedGemm& g, const WideEpi& e, hipStream_t s) {
+  const int tiles = (p.M + 15) >> 4;
+  if (g.n_units <= p.nwg && tiles <= 2 * kWideGroup) {
+    if (tiles <= 2) return launch_wide_gemm<4, FE_SWIGLU, 2>(p, g, p.xn, e, s);
+    if (tiles <= kWideGroup) return launch_wide_gemm<4, FE_SWIGLU, kWideGroup>(p, g, p.xn, e, s);
+    return launch_wide_gemm<4, FE_SWIGLU, 2 * kWideGroup>(p, g, p.xn, e, s);
+  }
+  if (tiles <= kWideGroup) return launch_wide_gemm_lds<FE_SWIGLU, true>(p, g, p.xn, e, s);
+  return launch_wide_gemm_lds<FE_SWIGLU, false>(p, g, p.xn, e, s);
 }
 
 // The attention units of a pass, p.NQ query tiles each (host: as few as leave no compute unit with two units)
@@ -2514,7 +2575,8 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
     if (ph == lm_phase) {
       if (p.logits) {
         e.out = p.logits; e.ld = p.logits_ld;
-        SSD_TRY((launch_wide_gemm_lds<FE_LOGITS>(p, p.lm, p.xn, e, s)));
+        if (((p.M + 15) >> 4) <= kWideGroup) SSD_TRY((launch_wide_gemm_lds<FE_LOGITS, true>(p, p.lm, p.xn, e, s)));
+        else SSD_TRY((launch_wide_gemm_lds<FE_LOGITS, false>(p, p.lm, p.xn, e, s)));
       }
       continue;
     }
@@ -2532,13 +2594,7 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
       SSD_HIP(hipGetLastError());
     } else if (sub == 4) {
       e.act_out = p.act;
-      // one row group (up to 96 rows): a workgroup per unit of 4 feature tiles, the reduction dimension over its
-      // wavefronts, instead of 16 feature tiles per workgroup on a quarter of the grid
-      if (((p.M + 15) >> 4) <= kWideGroup && L.gu.n_units <= p.nwg) {
-        SSD_TRY((launch_wide_gemm<4, FE_SWIGLU, kWideGroup>(p, L.gu, p.xn, e, s)));
-      } else {
-        SSD_TRY((launch_wide_gemm_lds<FE_SWIGLU>(p, L.gu, p.xn, e, s)));
-      }
+      SSD_TRY(launch_wide_gate_up(p, L.gu, e, s));
     } else if (sub == 1) {
       SSD_TRY((launch_wide_attn<PL, PG>(p, L, ph, s)));
     } else if (p.NS > 1) {                           // (no merge phase with one key split)
