@@ -15,8 +15,10 @@ constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxRows = 48;   // rows of one narrow pass (three 16-row MFMA tiles)
 constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles): contexts with more than kFusedMaxRows rows
 constexpr int kFusedWideQueryTiles = 3;   // wide passes: most query tiles per attention unit
-constexpr int kFusedWideFreshKeys = 192;  // wide passes: tokens of one sequence an extend pass takes (LDS room of the attention unit)
+constexpr int kFusedWideFreshKeys = 192;  // wide passes: keys of the pass itself an attention unit has LDS room for
+constexpr int kFusedWideAppendRows = 64;  // wide extends of more tokens of a sequence append their keys before the attention
 constexpr int kFusedWideSlices = 8;       // wide passes: most k-slices of the o- and down-projections (one per XCD)
+constexpr int kFusedWideRowGroup = 96;    // wide passes: rows of a full row group of a linear layer
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())
 constexpr int kFusedMaxSlices = 4;   // most k-slices of a linear layer
 constexpr unsigned kFusedSpinLimit = 4000000u;   // polls of a bounded wait (seconds of wall time) before it gives up
@@ -69,18 +71,19 @@ struct FusedParams {
   int SL;                                  // fresh-key slots per branch row (8 or 16)
   int is_branch;                           // 1: branch rows (private suffix), 0: extend rows (causal among themselves)
   int suffix_len;                          // branch rows: private positions a row sees, its own token included
+  int appended;                            // wide extends: 1 = the pass's keys are in the trunk before its attention runs
   int tv_ub;                               // host bound of the stored trunk keys any row sees (loop counts only)
   int n_attn_units, n_pair_units;          // B Hkv QT NS attention units; ceil(M Hq / 8) merge units (wide passes)
   // workspace, every address written at most once per launch
   float* h;        // [2L+1][48][d]    residual stream after embed / each o-proj / each down-proj
   bf16_t* xn;      // [2L+1][2][48*d]  (h * gain of the next norm) as fp16 planes (head, remainder) in B-operand order
-  float* ssq;      // [2L+1][d/16][48] per-feature-tile partial sums of h^2
+  float* ssq;      // [2L+1][d/16][48] per-feature-tile partial sums of h^2; wide passes: [rows] 1/rms of h
   float* qkv;      // [L][48][qkvd]    raw projections (before the norm's row scale and the rotary embedding)
   bf16_t* att;     // [L][2][48*qd]    attention output planes, B-operand order
   bf16_t* act;     // [L][planes][48*ffn]
   float* fix_buf;  // [L][3][fix_stride]  partial tiles of K-split linear layers (qkv, o, down); every word holds
                    // 0xffffffff ("not written yet") between launches: the reader of a tile puts that value back.
-                   // Wide passes: [kFusedWideSlices][M][d] partial sums of the o- and down-projections' k-slices
+                   // Wide passes: [slice][M][d] partial sums of the o- and down-projections' k-slices, fix_stride rows
   int64_t fix_stride;
   float* part_o;   // [L][B][Hkv][NS][QT*16][64]  partial softmaxes of the key splits (NS > 1 only)
   float* part_ml;  // [L][B][Hkv][NS][QT*16][2]

@@ -1158,13 +1158,13 @@ __device__ __forceinline__ void attn_merge_unit(const FusedParams& p, int unit, 
 // The o- and down-projections have few features (32 sets of 4 tiles at the 1B shape) under a long reduction dimension:
 // they are cut S ways so that every compute unit has a pair, XCD x working on slice x mod S, so that an XCD's L2 takes in
 // only that slice of the activations and, among the XCDs of a slice, only its own sets' weights.  Their fp32 partial sums
-// go to memory, and wide_resid_kernel, a workgroup per row, adds them to the residual stream in slice order and normalises
-// the row: the linear layers that follow find finished operands and need no row scales.  (Small row groups instead of
+// go to memory, and wide_resid_kernel, a workgroup per row, adds them to the residual stream in slice order and leaves the
+// row's 1/rms: the linear layers that follow load one number per row where they had to add up partial sums of squares.  (Small row groups instead of
 // slices, S = 1 and the residual in the epilogue, pulled every set's weights once per row group and the whole activation
 // matrix into every XCD: the down-projection took 23 / 28 / 33 us at 96 / 170 / 384 rows; now 15.8 / 18.5 / 28 and 5 to 6
 // for the residual kernel, and the kernels behind it 1.5 to 2.5 us less each.)
 constexpr int kWideTiles = kFusedWideRows / 16;
-constexpr int kWideGroup = 6;
+constexpr int kWideGroup = kFusedWideRowGroup / 16;
 constexpr int kWideRing = 8;
 constexpr int kWideThreads = 256, kWideWaves = 4;
 
@@ -1183,7 +1183,7 @@ struct WideChunk {
 };
 
 struct WideEpi {
-  float* out;          // QKV: [M][ld] projections; LOGITS: [M][ld] logits; PART: [slice][M][ld] partial sums
+  float* out;          // QKV: [M][ld] projections, row scale applied; LOGITS: [M][ld] logits; PART: [slice][M][ld] partial sums
   int64_t ld;
   bf16_t* act_out;     // SWIGLU
   int S;               // k-slices (PART; 1 otherwise)
@@ -1203,6 +1203,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
   constexpr int ROUNDS = MTG > kWideGroup ? 2 : 1;   // the partial tiles meet in LDS (at most 96 KiB) in this many parts
   constexpr int NT = 4 * MTG / ROUNDS;               // 1 KiB blocks of a wavefront in a part
   extern __shared__ f32x4 red[];
+  __shared__ float r_s[EPI == FE_PART ? 1 : kFusedWideRows];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int NKT = g.KS * kFusedWaves * g.KTW;       // k-tiles of the reduction dimension
   const int S = EPI == FE_PART ? e.S : 1;
@@ -1297,11 +1298,20 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
     }
   };
 
+  float rs0, rs1;                                   // the rows' 1/rms: requested first, in LDS under the ring's loads
+  if constexpr (EPI != FE_PART) {
+    rs0 = ((const gfloat*)p.ssq)[min((int)threadIdx.x, p.M - 1)];
+    rs1 = ((const gfloat*)p.ssq)[min((int)threadIdx.x + kWideThreads, p.M - 1)];
+  }
   WideChunk<MTG> ring[D];
   Cursor cu{nullptr, nullptr, 0, 0};
   place(cu);
 #pragma unroll
   for (int s = 0; s < D - 1; ++s) { load_chunk(ring[s], cu); advance(cu); }
+  if constexpr (EPI != FE_PART) {                   // (read behind the barriers of the reduction)
+    r_s[threadIdx.x] = rs0;
+    if ((int)threadIdx.x < kFusedWideRows - kWideThreads) r_s[threadIdx.x + kWideThreads] = rs1;
+  }
   stamp(p, e.ph, 3);
   for (int n = 0; n < n_my; ++n) {
     const int t = wx + n * per_xcd;
@@ -1356,9 +1366,13 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
           const f32x4 gv = total(idx), uv = total(idx + NT / 2);
           const int m = row_of(idx);
           if (m < p.M) {
+            const float rs = r_s[m];
             bf16_t hi[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) hi[i] = to_f16(gv[i] / (1.0f + __expf(-gv[i])) * uv[i]);
+            for (int i = 0; i < 4; ++i) {
+              const float gg = gv[i] * rs, uu = uv[i] * rs;
+              hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
+            }
             // input index of the down-projection
             st_u64_uncounted(e.act_out + b_off<MTOT>(q * 32 + feature_of(idx), m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
           }
@@ -1368,7 +1382,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
         for (int idx = wave; idx < NT; idx += kWideWaves) {
           const f32x4 v = total(idx);
           const int m = row_of(idx), n0 = q * 64 + feature_of(idx);
-          if ((n0 >> 4) < g.NT && m < p.M) st_f32x4_uncounted(out + (int64_t)m * e.ld + n0, v);
+          if ((n0 >> 4) < g.NT && m < p.M) st_f32x4_uncounted(out + (int64_t)m * e.ld + n0, EPI == FE_PART ? v : v * r_s[m]);
         }
       }
       wg_barrier();
@@ -1380,9 +1394,9 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
 }
 
 // The residual stream of a wide pass: a workgroup per row.  EMBED: h = the token's embedding; otherwise h += the row's
-// partial sums of the linear layer before, slice after slice.  Then the RMSNorm with `gain`, as the fp16 B operand of the
-// next linear layer (8 consecutive features per thread are one lane's 16 bytes of it) and, where asked for, as fp32
-// hidden states.  Reads S + 1 rows of d floats: at 96 rows of the 1B shape (S = 4 and 8) 4.9 us, at 384 (S = 2)
+// partial sums of the linear layer before, slice after slice.  Then (h * gain) as the fp16 B operand of the next linear
+// layer (8 consecutive features per thread are one lane's 16 bytes of it), the row's 1/rms, which that layer's epilogue
+// multiplies in, and, where asked for, the normalised row as fp32 hidden states.  Reads S + 1 rows of d floats: at 96 rows of the 1B shape (S = 4 and 8) 4.9 us, at 384 (S = 2)
 // 6.0 us, of which launch and two memory round trips are about 4.
 template <bool EMBED>
 __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p, const float* part, int S, const bf16_t* gain,
@@ -1445,14 +1459,16 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
   if (lane == 0) sum_s[wave] = ss;
   __syncthreads();
   const float rs = 1.0f / sqrtf(((sum_s[0] + sum_s[1]) + (sum_s[2] + sum_s[3])) / (float)p.d + p.eps);
+  if (threadIdx.x == 0) ((gfloat*)p.ssq)[m] = rs;
   auto put = [&](int c, const f32x4 v[2], u32x4 gw) {
     Bf8 gb, x;
     gb.w = gw;
     f32x4 n[2];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      n[i >> 2][i & 3] = v[i >> 2][i & 3] * rs * bf16_to_f32(gb.u[i]);
-      x.u[i] = to_f16(n[i >> 2][i & 3]);
+      const float xg = v[i >> 2][i & 3] * bf16_to_f32(gb.u[i]);
+      x.u[i] = to_f16(xg);
+      n[i >> 2][i & 3] = xg * rs;
     }
     *(gbf16x8*)((gbf16*)p.xn + b_off<kWideTiles>(c, m)) = x.v;
     if (hidden) {
@@ -1492,6 +1508,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
   constexpr int STAGE = KC * MTG * 64;               // 16-byte vectors per stage
   constexpr int BL = STAGE / kWideThreads;           // staging loads per thread and stage (12)
   extern __shared__ f32x4 lds[];                     // [2][KC][MTG][64] B-operand vectors
+  __shared__ float r_s[kFusedWideRows];              // the rows' 1/rms
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int NKT = g.KTW * kFusedWaves;               // k-tiles of the reduction dimension
   const int NST = NKT / KC;                          // stages per pair
@@ -1564,7 +1581,9 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
     }
   };
 
-  // ---- prologue: stage 0 of the first pair
+  // ---- prologue: the rows' scales (requested first, read in the epilogue), stage 0 of the first pair
+  const float rs0 = ((const gfloat*)p.ssq)[min((int)threadIdx.x, p.M - 1)];
+  const float rs1 = ((const gfloat*)p.ssq)[min((int)threadIdx.x + kWideThreads, p.M - 1)];
   Cursor cu{0, 0, nullptr, nullptr};
   place(cu);
   load_b(cu);
@@ -1576,6 +1595,8 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
     load_a(cu, j);
   }
   __builtin_amdgcn_sched_barrier(0);
+  r_s[threadIdx.x] = rs0;
+  if ((int)threadIdx.x < kFusedWideRows - kWideThreads) r_s[threadIdx.x + kWideThreads] = rs1;
   store_b(0);
   wg_barrier();
   stamp(p, e.ph, 3);
@@ -1629,6 +1650,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
       for (int t = 0; t < MT32; ++t) {
         const int m = (rg * MTG + 2 * t) * 16 + (lane & 31);
         if (m < p.M) {
+          const float rs = r_s[m];
           if constexpr (EPI == FE_SWIGLU) {
             // feature tiles 0, 1 of the unit are gate, 2, 3 the matching up tiles
 #pragma unroll
@@ -1636,7 +1658,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
               bf16_t hi[4];
 #pragma unroll
               for (int i = 0; i < 4; ++i) {
-                const float gg = acc[0][t][4 * q + i], uu = acc[1][t][4 * q + i];
+                const float gg = acc[0][t][4 * q + i] * rs, uu = acc[1][t][4 * q + i] * rs;
                 hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
               }
               const int k = unit * 32 + 8 * q + f4;       // input index of the down-projection
@@ -1649,7 +1671,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
               for (int q = 0; q < 4; ++q) {
                 const int n0 = unit * 64 + f * 32 + 8 * q + f4;
                 const f32x4 v = (f32x4){acc[f][t][4 * q], acc[f][t][4 * q + 1], acc[f][t][4 * q + 2], acc[f][t][4 * q + 3]};
-                if ((n0 >> 4) < g.NT) st_f32x4_uncounted(e.out + (int64_t)m * e.ld + n0, v);
+                if ((n0 >> 4) < g.NT) st_f32x4_uncounted(e.out + (int64_t)m * e.ld + n0, v * rs);
               }
           }
         }
@@ -1666,8 +1688,8 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
 
 // The attention unit of the wide passes, a workgroup: NQ query tiles of one (sequence, KV head, key split) share every
 // stored key and value block the unit pulls (a wide pass has 6 and more query tiles per sequence and head: units of one
-// tile would pull the same trunk once per tile).  Same method and same layouts as attn_unit; the qkv projections are
-// finished here (no row scale).  What shapes it, measured on 384 rows over 2048 keys of the 1B shape:
+// tile would pull the same trunk once per tile).  Same method and same layouts as attn_unit; the qkv projections
+// arrive with the norm's row scale applied.  What shapes it, measured on 384 rows over 2048 keys of the 1B shape:
 // - order of the loads: they return in order, and the first ring of stored keys is a burst of 32 MB over the chip, so the
 //   queries and the fresh keys are requested before it and staged under it;
 // - every query tile is rotated once, by one wavefront, and reaches the others through LDS;
@@ -1728,7 +1750,7 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
     // (an extend's descriptor counts the pass's own tokens, here fresh keys, up to the row itself.  The pass's kind comes
     // from the launch: tested per row it would put a round trip to memory between these loads and the next)
     const int rloc = row_of(t) >> g_log;
-    tv[t] = p.rows[b * p.R + rloc].vis - (is_branch ? 0 : 1 + rloc);
+    tv[t] = p.rows[b * p.R + rloc].vis - (is_branch || p.appended ? 0 : 1 + rloc);
   }
   f32x4 qraw[4], qcs[4];
   if (wave < NQ) {
@@ -1744,7 +1766,7 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
   }
   // fresh keys: item = (key f, rotary quad / 8-dim group q8)
   const int n_fresh_keys = is_branch ? (NQ * rpt) << sl_log : p.R;
-  const int n_fb = s == 0 ? (n_fresh_keys + 31) >> 5 : 0;
+  const int n_fb = s == 0 && !p.appended ? (n_fresh_keys + 31) >> 5 : 0;
   const int nf8 = n_fb * 32 * 8;
   auto fresh_row = [&](int f, int& m_o, bool& valid, bool& stored) {
     if (is_branch) {
@@ -1824,7 +1846,8 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
   __builtin_amdgcn_sched_barrier(0);
 
   // ---- issue: the first trunk blocks of this wavefront (block counts from the host's bound)
-  const int kend_ub = min(kb0 + p.KPU, p.tv_ub);
+  // (appended: the rows of the pass before the unit's last one are stored keys too)
+  const int kend_ub = min(kb0 + p.KPU, p.tv_ub + (p.appended ? min(((qg + 1) * NQ * 16 - 1) >> g_log, p.R - 1) + 1 : 0));
   const int n_tb = kend_ub > kb0 ? (kend_ub - kb0 + 31) >> 5 : 0;
   const int n_mine = n_tb > wave ? (n_tb - wave + kFusedWaves - 1) / kFusedWaves : 0;
   const int krow = (li >> 2) * 8 + (li & 3);                  // key of this lane's A-operand row in a block (tile 0)
@@ -2080,6 +2103,37 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
     }
   }
   stamp(p, ph, 2);
+}
+
+// The keys (rotated) and values of an extend of many tokens, into the trunk ahead of its attention, which then finds every
+// key in one place: units of a prompt chunk would each rotate and stage all of its keys (170 tokens: 1360 items per unit)
+// and have LDS room for kFusedWideFreshKeys of them.  Thread = (row, KV head, rotary quad / 8-dim group).  5.0 us at 340 rows.
+template <bool PG>
+__global__ __launch_bounds__(256) void wide_append_kernel(FusedParams p, bf16_t* trunk_k, bf16_t* trunk_vt) {
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  const int q8 = idx & 7, hk = (idx >> 3) % p.Hkv, m = (idx >> 3) / p.Hkv;
+  if (m >= p.M) return;
+  const int slot = p.rows[m].kv_slot, b = m / p.R;
+  const gfloat* src = (const gfloat*)p.qkv + (int64_t)m * p.qkvd + p.qd + hk * 64;
+  const f32x4 a = *(const gf32x4*)(src + q8 * 4), bb = *(const gf32x4*)(src + 32 + q8 * 4);
+  const gfloat* cs = (const gfloat*)p.cos_sin + ((int64_t)m * 32 + q8 * 4) * 2;
+  const f32x4 c0 = *(const gf32x4*)cs, c1 = *(const gf32x4*)(cs + 4);
+  const f32x4 v0 = *(const gf32x4*)(src + p.kvd + q8 * 8), v1 = *(const gf32x4*)(src + p.kvd + q8 * 8 + 4);
+  const int64_t base = PG ? ((int64_t)p.pages[(int64_t)b * p.page_stride + (slot >> 5)] * p.Hkv + hk) * 2048
+                          : (int64_t)(b * p.Hkv + hk) * p.vt_stride * 64 + (int64_t)(slot >> 5) * 2048;
+  bf16_t x0[4], x1[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const float c = e < 2 ? c0[2 * e] : c1[2 * e - 4], sn = e < 2 ? c0[2 * e + 1] : c1[2 * e - 3];
+    x0[e] = to_bf16(a[e] * c - bb[e] * sn);
+    x1[e] = to_bf16(bb[e] * c + a[e] * sn);
+  }
+  const int64_t row = base + (int64_t)(slot & 31) * 64 + q8 * 4;
+  *(uint64_t*)(trunk_k + row) = pack_bf16x4(x0[0], x0[1], x0[2], x0[3]);
+  *(uint64_t*)(trunk_k + row + 32) = pack_bf16x4(x1[0], x1[1], x1[2], x1[3]);
+  gbf16* vcol = (gbf16*)trunk_vt + base + (q8 * 8) * 32 + (slot & 31);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) vcol[e * 32] = to_bf16(e < 4 ? v0[e & 3] : v1[e & 3]);
 }
 
 // Merge of a wide pass's key splits.
@@ -2516,7 +2570,7 @@ int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
   const int n_rg = (tiles + mtg - 1) / mtg;
   e.S = 1;
   for (int S = kFusedWideSlices; S > 1; S >>= 1)
-    if (nq * n_rg * S <= p.nwg && wide_k_tiles(g) % (kWideWaves * S * (kWideRing / 2)) == 0) { e.S = S; break; }
+    if (nq * n_rg * S <= p.nwg && (int64_t)S * p.M <= p.fix_stride && wide_k_tiles(g) % (kWideWaves * S * (kWideRing / 2)) == 0) { e.S = S; break; }
   switch (mtg) {
     case 1: return launch_wide_gemm<2, FE_PART, 1>(p, g, bsrc, e, s);
     case 2: return launch_wide_gemm<2, FE_PART, 2>(p, g, bsrc, e, s);
@@ -2596,6 +2650,11 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
       e.act_out = p.act;
       SSD_TRY(launch_wide_gate_up(p, L.gu, e, s));
     } else if (sub == 1) {
+      if (p.appended) {
+        wide_append_kernel<PG><<<(p.M * p.Hkv * 8 + 255) / 256, 256, 0, s>>>(p, L.trunk_k, L.trunk_vt);
+        SSD_HIP(hipGetLastError());
+        if (ph == last) continue;                    // (a pass without outputs: stored, that was all)
+      }
       SSD_TRY((launch_wide_attn<PL, PG>(p, L, ph, s)));
     } else if (p.NS > 1) {                           // (no merge phase with one key split)
       wide_merge_kernel<<<p.n_pair_units, kFusedThreads, 0, s>>>(p, ph);
@@ -2650,6 +2709,9 @@ int launch_fused_wide(const FusedParams& p, const FusedLayer* layers_host, int f
                     (16 / p.G) * p.SL <= 64,
                 "bad attention split");
   SSD_CHECK_ARG(p.NQ >= 1 && p.NQ <= kMultiQ && p.n_attn_units == p.B * p.Hkv * ((p.QT + p.NQ - 1) / p.NQ) * p.NS, "bad attention units");
+  SSD_CHECK_ARG(p.M <= p.fix_stride, "no room for the partial sums of %d rows", p.M);
+  SSD_CHECK_ARG(!p.is_branch || !p.appended, "branch rows keep their own keys");
+  SSD_CHECK_ARG(p.is_branch || p.appended || p.R <= kFusedWideFreshKeys, "an extend of %d tokens must append its keys first", p.R);
   SSD_CHECK_ARG(first >= 0 && last <= fused_last_phase(p.L) && first <= last && layers_host, "bad phase range");
   if (p.pages) {
     SSD_CHECK_ARG((p.planes & 24) != 24, "a paged trunk takes the default planes of the attention unit only");

@@ -439,7 +439,9 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
   const int RG = p.R * p.G;
   p.QT = (RG + 15) / 16;
   p.SL = c->K + 1 <= 8 ? 8 : 16;
-  const int p_ub = max_vis > 1 ? max_vis : 1;
+  p.appended = wide && !p.is_branch && rows_per_seq > kFusedWideAppendRows;
+  const int stored_ub = max_vis + (p.appended ? rows_per_seq : 0);
+  const int p_ub = stored_ub > 1 ? stored_ub : 1;
   const int n_seq = M / rows_per_seq;
   const int per_pass = cap / rows_per_seq;
   // Key splits of the stored trunk: the attention phase lasts (rounds of units over the grid) x (a unit's 32-key blocks
@@ -585,7 +587,7 @@ int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset,
 // KV of positions 0 .. max(len)-1 of sequences [b0, b0 + nb) (their trunk_len is 0): extend passes over d_tokens
 // [nb][stride].  In contexts that prefill in wide passes a pass takes as many tokens of a sequence as a wide pass has room
 // for, and several sequences where their prompts are short: a pass streams every weight once, so what a prompt costs is its
-// number of passes (a 1020-token prompt of the 1B shape: 6 passes of 170 rows instead of 170 passes of K+1 = 6 rows).
+// number of passes (a 1020-token prompt of the 1B shape: 3 passes of 340 rows instead of 170 passes of K+1 = 6 rows).
 // Otherwise chunks of K+1 tokens of all sequences.
 int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t* lens, int b0, int nb, hipStream_t s) {
   const int K1 = c->K + 1;
@@ -596,7 +598,7 @@ int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t*
       // a group: the next sequences that fit one pass with the whole chunk of each
       T = 0;
       for (gn = 0; g0 + gn < nb; ++gn) {
-        const int want = std::max(T, std::min<int>(lens[g0 + gn], kFusedWideFreshKeys));
+        const int want = std::max(T, std::min<int>(lens[g0 + gn], kFusedWideRows));
         if (gn > 0 && want * (gn + 1) > kFusedWideRows) break;
         T = want;
       }
@@ -741,6 +743,10 @@ int fused_setup(ssd_ctx* c) {
     // query rows of a pass: whole 16-row tiles per sequence
     c->part_wide.ns_max = (c->max_trunk + 2047) / 2048 + 1;
     c->part_wide.entries = (int64_t)p.Hkv * c->part_wide.ns_max * (kFusedWideRows * p.G + 16 * std::min(c->B, kFusedWideRows));
+    // partial sums of o and down: eight slices of a row group of 96, two of 384 rows (which is what gives every pair of 64
+    // features x 96 rows a workgroup at the 1B shape).  They lie where the qkv projections were: written after the
+    // attention has read those, read before the next layer's are written
+    w.fix_stride = kFusedWideSlices * kFusedWideRowGroup;
     // one allocation, carved up
     char* base = nullptr;
     size_t used = 0;
@@ -752,8 +758,9 @@ int fused_setup(ssd_ctx* c) {
       };
       carve(&w.h, MW * p.d * 4);
       carve(&w.xn, MW * p.d * 2);
-      carve(&w.fix_buf, (size_t)kFusedWideSlices * MW * p.d * 4);
-      carve(&w.qkv, MW * p.qkvd * 4);
+      carve(&w.ssq, MW * 4);
+      carve(&w.fix_buf, std::max((size_t)w.fix_stride * p.d * 4, MW * p.qkvd * 4));
+      w.qkv = w.fix_buf;
       carve(&w.att, MW * p.qd * 2);
       carve(&w.act, MW * p.ffn * 2);
       carve(&w.part_o, (size_t)c->part_wide.entries * 64 * 4);

@@ -36,7 +36,7 @@ def _trunk(B, ctx, lens, max_trunk):
     return ks, vs
 
 
-@pytest.mark.parametrize("lens", [[1], [6], [191], [192], [193], [385], [700], [40, 300, 7], [33] * 15],
+@pytest.mark.parametrize("lens", [[1], [6], [64], [65], [191], [192], [193], [384], [385], [700], [129, 130], [40, 300, 7], [33] * 15],
                          ids=lambda x: "-".join(map(str, x[:3])) + ("x%d" % len(x) if len(x) > 3 else ""))
 def test_wide_prefill_equals_narrow_chunks(B, lens):
     nb, max_trunk, seed = len(lens), max(lens) + 2 * K + 8, 7 + sum(lens)
