@@ -226,20 +226,34 @@ __global__ __launch_bounds__(kSelBlock) void sample_kernel(const float* __restri
     // per token of a 128256-token row cost more than the rest of the sampler together, so the scan runs in fp32 and
     // only the tokens that can still win are scored in fp64: with |s32 - s64| <= delta for every token near the top,
     // the fp64 winner t* has s32(t*) >= s64(t*) - delta >= s64(t32) - delta >= max32 - 2 delta.  delta: z / T in
-    // fp32 is within 2^-22 |z / T|; u is exact in fp32 (a 24-bit odd integer times 2^-24); logf is good to 2 ulp, so
-    // g = -log(-log u) (at most 16.7 in magnitude) to 5e-6; near the top |z / T| <= |s| + 17.  The bound used is
-    // twice that.
+    // fp32 is within 2^-22 |z / T|; u is exact in fp32 (a 24-bit odd integer times 2^-24); the hardware's base-2 logarithm
+    // times ln 2 is good to 3 ulp, so g = -log(-log u) (at most 16.7 in magnitude) to 1e-5; near the top
+    // |z / T| <= |s| + 17.  The bound used is more than four times that.
     const int t_begin = q_begin * 4, t_end = min(V, q_end * 4);
     const float inv_t = 1.0f / (float)T;
-    auto s32 = [&](int t) {
-      const float zt = z[t];
+    auto s32 = [&](int t, float zt) {
       if (zt != zt) return -INFINITY;
-      const uint64_t m = mix64(prefix + (uint64_t)t) >> 41;
+      const uint32_t m = (uint32_t)(mix64(prefix + (uint64_t)t) >> 41);   // (32 bits: a 64-bit conversion is a dozen instructions)
       const float u = ((float)m + 0.5f) * (1.0f / 8388608.0f);
-      return zt * inv_t - logf(-logf(u));
+      constexpr float kLn2 = 0.69314718f;
+      return zt * inv_t - __builtin_amdgcn_logf(__builtin_amdgcn_logf(u) * -kLn2) * kLn2;
     };
-    float mx = -INFINITY;
-    for (int t = t_begin + threadIdx.x; t < t_end; t += kSelBlock) mx = fmaxf(mx, s32(t));
+    // The logits are requested four at a time ahead of the hashes and logarithms; each thread remembers its own maximum,
+    // and only threads whose maximum can still win go over their tokens again (a second scan by all of them, with 64-bit
+    // conversions and library logarithms: 61 us for 96 rows of 128256, now 48).
+    constexpr int kAhead = 4;
+    float mine = -INFINITY;
+    for (int t0 = t_begin + (int)threadIdx.x; t0 < t_end; t0 += kSelBlock * kAhead) {
+      float zv[kAhead];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) zv[u] = z[min(t0 + u * kSelBlock, t_end - 1)];
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        const float sc = s32(t0 + u * kSelBlock, zv[u]);
+        mine = t0 + u * kSelBlock < t_end ? fmaxf(mine, sc) : mine;
+      }
+    }
+    float mx = mine;
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     __shared__ float fmx[kSelWaves];
     if ((threadIdx.x & 63) == 0) fmx[threadIdx.x >> 6] = mx;
@@ -248,8 +262,8 @@ __global__ __launch_bounds__(kSelBlock) void sample_kernel(const float* __restri
     for (int i = 1; i < kSelWaves; ++i) mx = fmaxf(mx, fmx[i]);
     // an infinite or empty maximum: score everything in fp64
     const float thr = mx > -INFINITY && mx < INFINITY ? mx - 2.0f * (2e-6f * (fabsf(mx) + 40.0f) + 2e-5f) : -INFINITY;
-    for (int t = t_begin + threadIdx.x; t < t_end; t += kSelBlock) {
-      if (s32(t) >= thr) {
+    for (int t = mine >= thr ? t_begin + (int)threadIdx.x : t_end; t < t_end; t += kSelBlock) {
+      if (s32(t, z[t]) >= thr) {
         ScoreId c;
         c.id = t;
         c.s = score_of(z[t]) / T + gumbel_from_u(draw_u(prefix, (uint64_t)t));
