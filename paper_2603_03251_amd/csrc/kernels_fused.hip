@@ -624,11 +624,6 @@ __device__ __forceinline__ float sum_over_rows(float x) {
   const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
-__device__ __forceinline__ int trunk_visible(const RowDesc& r, int m, int R) {
-  // stored trunk keys the row sees; the tokens of this very pass are handled as fresh keys
-  return r.is_branch ? r.vis : r.vis - 1 - (m % R);
-}
-
 struct OnlineSoftmax {
   float m_run, l_run;   // running maximum (base-2 exponent) and this lane's share of the running sum
   f32x4 acc[4];         // O^T: dims dt*16 + (lane>>4)*4 + r of query row lane & 15
@@ -816,18 +811,14 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
         x.m_o = b * p.R + min(rt, p.R - 1);
         x.valid = rt < p.R && j < p.suffix_len;
         x.stored = j < p.suffix_len - 1;
-        if (x.valid && x.stored) {
-          const int64_t row = (((int64_t)x.m_o * p.suffix_cap + j) * p.Hkv + hk) * 64;
-          x.k_lo = *(const gu32x2*)(L.suffix_k + row + x.q8 * 4);
-          x.k_hi = *(const gu32x2*)(L.suffix_k + row + 32 + x.q8 * 4);
-          x.v = *(const gbf16x8*)(L.suffix_v + row + x.q8 * 8);
-        }
       } else {
         x.m_o = b * p.R + min(x.f, p.R - 1);
         x.valid = x.f < p.R;
         fresh_slot = p.rows[x.m_o].kv_slot;
       }
-      if (x.valid && !x.stored) {
+      if (x.valid) {
+        // both sources in one stretch of loads: a branch on `stored` makes the second wait for the first (the slots of a
+        // row up to its own are inside its suffix)
         const gfloat* kp = gq + (int64_t)x.m_o * p.qkvd + p.qd + hk * 64 + x.q8 * 4;
         x.a = *(const gf32x4*)kp;
         x.bb = *(const gf32x4*)(kp + 32);
@@ -837,12 +828,20 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
         const gfloat* vp = gq + (int64_t)x.m_o * p.qkvd + p.qd + p.kvd + hk * 64 + x.q8 * 8;
         x.v0 = *(const gf32x4*)vp;
         x.v1 = *(const gf32x4*)(vp + 4);
+        if (is_branch) {
+          const int64_t row = (((int64_t)x.m_o * p.suffix_cap + (x.f & (p.SL - 1))) * p.Hkv + hk) * 64;
+          x.k_lo = *(const gu32x2*)(L.suffix_k + row + x.q8 * 4);
+          x.k_hi = *(const gu32x2*)(L.suffix_k + row + 32 + x.q8 * 4);
+          x.v = *(const gbf16x8*)(L.suffix_v + row + x.q8 * 8);
+        }
       }
     }
   }
 
   // ---- Q operand: dims g4*8..+7 (k-step 0) and 32+g4*8..+7 (k-step 1) of this lane's query row, rotated, scaled
-  const int tv = vq ? trunk_visible(rd, m, p.R) : 0;
+  // stored trunk keys the row sees (an extend's descriptor counts the pass's own tokens, here fresh keys, up to itself; the
+  // kind of the pass comes from the launch: a test of the descriptor would wait for it)
+  const int tv = vq ? rd.vis - (is_branch ? 0 : 1 + rloc) : 0;
   Bf8 qh[2], ql[2];
   {
     float a[8] = {qa0[0], qa0[1], qa0[2], qa0[3], qa1[0], qa1[1], qa1[2], qa1[3]};
