@@ -1399,11 +1399,10 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
 // 6.0 us, of which launch and two memory round trips are about 4.
 template <bool EMBED>
 __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p, const float* part, int S, const bf16_t* gain,
-                                                                  float* hidden, int ph) {
+                                                                  float* hidden) {
   constexpr int kHeld = 2;                       // 8-feature chunks per thread kept in registers (d <= 4096); others are re-read
   __shared__ float sum_s[kWideWaves];
   const int m = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  stamp(p, ph, 0);
   gfloat* h = (gfloat*)p.h + (int64_t)m * p.d;
   int tok = 0;
   if (EMBED) {
@@ -1484,7 +1483,6 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
     f32x4 v[2] = {*(const gf32x4*)(h + c), *(const gf32x4*)(h + c + 4)};   // this thread's own stores
     put(c, v, *(const u32x4*)(gain + c));
   }
-  stamp(p, ph, 2);
 }
 
 // The two large linear layers of a wide pass (gate/up + SwiGLU, LM head; stream-order units of 4 feature tiles, no
@@ -2618,7 +2616,7 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
   const int lm_phase = fused_last_phase(p.L);
   for (int ph = first; ph <= last; ++ph) {
     if (ph == 0) {
-      wide_resid_kernel<true><<<p.M, kWideThreads, 0, s>>>(p, nullptr, 0, layers_host[0].attn_norm, nullptr, ph);
+      wide_resid_kernel<true><<<p.M, kWideThreads, 0, s>>>(p, nullptr, 0, layers_host[0].attn_norm, nullptr);
       SSD_HIP(hipGetLastError());
       continue;
     }
@@ -2643,7 +2641,7 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
       SSD_TRY(launch_wide_part(p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s));
       const bool fin = sub == 5 && l + 1 == p.L;
       wide_resid_kernel<false><<<p.M, kWideThreads, 0, s>>>(p, p.fix_buf, e.S, sub == 3 ? L.mlp_norm : (fin ? p.final_norm : layers_host[l + 1].attn_norm),
-                                                            fin ? p.hidden : nullptr, ph);
+                                                            fin ? p.hidden : nullptr);
       SSD_HIP(hipGetLastError());
     } else if (sub == 4) {
       e.act_out = p.act;
