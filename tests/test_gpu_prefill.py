@@ -93,3 +93,30 @@ def test_wide_prefill_against_the_oracle(B, pages):
     finally:
         B.ssd_ctx_destroy(ctx)
         B.ssd_model_destroy(model)
+
+
+@pytest.mark.parametrize("heads,lens", [(16, [384]), (16, [340, 1]), (32, [770]), (32, [90] * 4)])
+def test_wide_attention_units_of_two_and_three_query_tiles(B, heads, lens):
+    """8 KV heads and groups of 2 and 4: 384 and 768 query tiles per pass, more than there are compute units, so that a unit
+    takes two or three of them (the last unit of a head an incomplete set); appended prompts and, 90 rows of 4 sequences,
+    their last chunk.  Against the narrow passes, whose units take one tile each."""
+    shape = I.ModelShape(n_layers=2, d_model=512, n_q_heads=heads, n_kv_heads=8, head_dim=64, d_ffn=1024, vocab=2064, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    nb, seed = len(lens), 3 + heads
+    print(f"[case] prefill of {lens} with {heads} query heads", flush=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, 12))
+    prompt = dev_i32(I.make_prompt(shape, nb, max(lens), seed))
+    pending, temps = dev_i32(I.make_pending(shape, nb, K, seed)), dev_f32(np.zeros(nb))
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, max(lens) + 2 * K + 8, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
+    try:
+        got = []
+        for ctx in ctxs:
+            B.ssd_ctx_prefill(ctx, prompt, lens)
+            B.ssd_prespeculate(ctx, pending, temps, 1)
+            got.append(B.read_cache(ctx)["glue_logits"].cpu().numpy())
+        # each side is within TOL_BF16_OWN_PREFILL of the exact logits
+        assert row_rel_err(got[0], got[1]) < 2 * TOL_BF16_OWN_PREFILL
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
