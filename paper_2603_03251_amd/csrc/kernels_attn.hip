@@ -391,6 +391,24 @@ __global__ __launch_bounds__(256) void attention_extend_kernel(const float* __re
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
   for (; kb < j_end; kb += kExtKeys) {
+    // A row must not feel a key it does not see, and weight 0 does not keep an infinite or NaN value out of a product.  So
+    // where some row of the sequence does not see all 32 keys (the last block or two of a row's trunk), values that are not
+    // finite leave the operand (exponent all ones: the carry out of it lands in the sign bit), and rows that do see their
+    // keys get them added after the product, one by one.
+    bool odd = false;
+    if (kb + 32 > last.vis - (R - 1)) {
+      uint32_t ones = 0u;
+#pragma unroll
+      for (int k = 0; k < 32; ++k) ones |= (vr[k] & 0x7f807f80u) + 0x00800080u;
+      odd = __any((ones & 0x80008000u) != 0u);
+      if (odd) {
+#pragma unroll
+        for (int k = 0; k < 32; ++k) {
+          if ((vr[k] & 0x7f80u) == 0x7f80u) vr[k] &= 0xffff0000u;
+          if ((vr[k] & 0x7f800000u) == 0x7f800000u) vr[k] &= 0x0000ffffu;
+        }
+      }
+    }
     // V^T of the wavefront's 32 keys through LDS (its own part: no barrier)
 #pragma unroll
     for (int e = 0; e < NE; ++e)
@@ -441,6 +459,24 @@ __global__ __launch_bounds__(256) void attention_extend_kernel(const float* __re
       const bf16x8 vt = *(const bf16x8*)(vt_s + (dt * 16 + li) * kExtVt + g4 * 8);
 #pragma unroll
       for (int pl = 2; pl >= 0; --pl) acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, pp[pl].v, acc[dt], 0, 0, 0);
+    }
+    if (odd) {
+      for (int k8 = 0; k8 < 4; ++k8)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float pk = __shfl(((float)pp[2].e[e] + (float)pp[1].e[e]) + (float)pp[0].e[e], k8 * 16 + li);
+          const int key = kb + k8 * 8 + e;
+          if (key < min(vis, j_end)) {
+            const bf16_t* vp = tv + (int64_t)key * kv_stride + g4 * 4;
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const bf16_t v = vp[dt * 16 + r];
+                if ((v & 0x7f80u) == 0x7f80u) acc[dt][r] = fmaf(pk, bf16_to_f32(v), acc[dt][r]);
+              }
+          }
+        }
     }
   }
   // ---- the wavefronts' partial softmaxes meet in LDS, where V^T was

@@ -155,3 +155,35 @@ def test_round_with_sampled_verification_on_the_targets_logits(B):
         B.ssd_ctx_destroy(dctx)
         B.ssd_model_destroy(target)
         B.ssd_model_destroy(draft)
+
+
+@pytest.mark.parametrize("head_dim,P", [(64, 20), (64, 125), (128, 61), (128, 300)])
+def test_extend_rows_do_not_feel_a_later_token_without_values(B, head_dim, P):
+    """A token whose embedding is NaN has NaN keys and values.  The rows of an extend that come before it do not see it: their
+    logits are, bit for bit, those beside an ordinary token.  The rows from it on are NaN.  Prefixes that put the token in a
+    32-key block of its own rows, across two blocks and across two splits; groups of 4 and 1 query heads per KV head."""
+    shape = I.ModelShape(n_layers=2, d_model=512, n_q_heads=8 if head_dim == 64 else 4, n_kv_heads=2 if head_dim == 64 else 4,
+                         head_dim=head_dim, d_ffn=1024, vocab=2064, dtype="bf16", rope_theta=500000.0, tie_embeddings=False)
+    K, seed, bad = 5, 5 + P, 7
+    print(f"[case] NaN token in an extend: head_dim {head_dim}, prefix {P}", flush=True)
+    w = I.make_weights(shape, seed)
+    w["embed"][bad] = np.nan
+    model = B.ssd_model_create(shape, w)
+    ctx = B.ssd_ctx_create(model, 2, K, 1, P + 2 * K + 2, B.SSD_CTX_PER_OPERATOR)
+    try:
+        k, v = I.make_prefix_kv(shape, 2, P, seed)
+        B.ssd_ctx_load_trunk(ctx, kv_to_device(k, "bf16"), kv_to_device(v, "bf16"), P)
+        pending = I.make_pending(shape, 2, K, seed)
+        pending[pending == bad] = bad + 1
+        out = []
+        for token in (bad + 2, bad):
+            pending[0, 3] = token
+            logits = torch.empty((2, K + 1, shape.vocab), dtype=torch.float32, device="cuda")
+            B.ssd_ctx_extend(ctx, dev_i32(pending), 0, logits)
+            out.append(logits.cpu().numpy())
+        assert np.isfinite(out[0]).all()
+        assert np.array_equal(out[1][0, :3], out[0][0, :3]) and np.array_equal(out[1][1], out[0][1])
+        assert np.isnan(out[1][0, 3:]).all()
+    finally:
+        B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
