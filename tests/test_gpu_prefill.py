@@ -71,6 +71,34 @@ def test_wide_prefill_equals_narrow_chunks(B, lens):
         B.ssd_model_destroy(model)
 
 
+@pytest.mark.parametrize("lens", [[1], [K], [K + 1], [K + 1, 1], [2, K, 1]], ids=lambda x: "-".join(map(str, x)))
+def test_prompts_of_one_chunk_take_the_narrow_pass(B, lens):
+    """Where the rounds are narrow passes and a chunk of K+1 tokens holds the prompts, the prefill is that one narrow pass, to
+    the bit: for the whole batch and for a slot of its own."""
+    nb, max_trunk, seed = len(lens), 2 * K + 12, 9 + sum(lens)
+    print(f"[case] prefill of {lens}", flush=True)
+    model = B.ssd_model_create(SHAPE, I.make_weights(SHAPE, 13))
+    prompt = dev_i32(I.make_prompt(SHAPE, nb, max(lens), seed))
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
+    try:
+        for alone in (False, True):
+            got = []
+            for ctx in ctxs:
+                if alone:
+                    B.ssd_ctx_prefill_sequence(ctx, nb - 1, prompt[nb - 1, :lens[-1]].contiguous())
+                else:
+                    B.ssd_ctx_prefill(ctx, prompt, lens)
+                got.append(_trunk(B, ctx, lens, max_trunk))
+            for part in (0, 1):
+                for l in range(SHAPE.n_layers):
+                    for b in range(nb):
+                        assert np.array_equal(got[0][part][l][b], got[1][part][l][b]), (alone, part, l, b)
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
 @pytest.mark.parametrize("pages", [0, 16])
 def test_wide_prefill_against_the_oracle(B, pages):
     lens, max_trunk, seed = [210, 60], 240, 5
