@@ -156,7 +156,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_kernel(const bf16_t* __
 
 // fp32 models.  A pass is a handful of rows over matrices of a few hundred KiB that sit in L2, so a layer costs its memory
 // round trips, not its bytes: a wavefront takes one output feature (or, PAIR, two: gate and up of SwiGLU, or the two
-// members of a rotary pair) over 1 / WPF of the reduction dimension and up to kRowsF32 rows, requests 16 bytes per lane of
+// members of a rotary pair; TWO: two neighbours) over 1 / WPF of the reduction dimension and up to kRowsF32 rows, requests 16 bytes per lane of
 // the weights and of every row at a time, kStepsF32 such steps together, and adds the lanes up with a butterfly that
 // halves the number of rows it carries at each step (10 exchanges for 8 rows instead of 48).  WPF = 4 (few features, long
 // reduction dimension): the four wavefronts of a block share a feature.  NORM: the input is the residual stream, the RMSNorm
@@ -204,15 +204,15 @@ struct GemmF32 {
   int qd, kvd, half, max_trunk, suffix_cap;
 };
 
-template <int EPI, bool NORM, int WPF>
+template <int EPI, bool NORM, int WPF, bool TWO>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 a) {
-  constexpr bool PAIR = EPI == F32_SWIGLU || EPI == F32_ROPE;
+  constexpr bool PAIR = EPI == F32_SWIGLU || EPI == F32_ROPE || TWO;
   __shared__ float part[3][4][kRowsF32];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int u = WPF == 4 ? (int)blockIdx.x : (int)blockIdx.x * 4 + wave;   // feature, or feature pair (ROPE)
-  const int n_units = EPI == F32_ROPE ? a.N >> 1 : a.N;
+  const int n_units = EPI == F32_ROPE ? a.N >> 1 : (TWO ? (a.N + 1) >> 1 : a.N);
   if (WPF == 1 && u >= n_units) return;
-  int n = u, n2 = u;
+  int n = TWO ? 2 * u : u, n2 = TWO ? min(2 * u + 1, a.N - 1) : u;
   if (EPI == F32_ROPE) {
     const int head = u / a.half;
     n = head * 2 * a.half + (u - head * a.half);
@@ -275,9 +275,11 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 a) {
     y *= rs;
     if (PAIR) y2 *= rs;
   }
-  if (EPI == F32_STORE) a.out[(int64_t)m * a.ld + n] = y;
-  else if (EPI == F32_RESIDUAL) a.out[(int64_t)m * a.ld + n] += y;
-  else if (EPI == F32_SWIGLU) a.out[(int64_t)m * a.ld + n] = (y / (1.0f + expf(-y))) * y2;
+  if (EPI == F32_STORE || EPI == F32_RESIDUAL) {
+    float* dst = a.out + (int64_t)m * a.ld + n;
+    dst[0] = EPI == F32_STORE ? y : dst[0] + y;
+    if (TWO && n2 > n) dst[1] = EPI == F32_STORE ? y2 : dst[1] + y2;
+  } else if (EPI == F32_SWIGLU) a.out[(int64_t)m * a.ld + n] = (y / (1.0f + expf(-y))) * y2;
   else {
     const int i = u % a.half;
     if (n < a.qd + a.kvd) {
@@ -329,17 +331,26 @@ int launch_bf16(const void* x, int64_t x_plane, const void* w, const void* w2, v
 // Four wavefronts per feature where that still leaves at most four blocks per compute unit and a wavefront has at least
 // one full step of 256 inputs: down of the 256-wide configuration (K = 1024) takes 4.6 us in 256 blocks, hardly more than
 // o (K = 256, 64 blocks of one wavefront per feature, 4.2 us), where its reduction would be four steps in a row.
+// Two features per wavefront (o, down, LM head) where the rows make several groups and the halved number of blocks is still
+// three per compute unit: with many rows the loads of the rows, once per feature, are what a layer pays for.  4 layers of
+// width 2048 and a head of 32000: 384 rows 15.5 -> 12.5 ms (14.3 with 16 rows of 4-byte elements per wavefront), 18 rows
+// (768 blocks) 1.20 -> 1.17, 16 rows (512 blocks) 0.94 -> 1.03; width 1024: 48 rows (768) 0.81 -> 0.78, 30 rows (512)
+// 0.59 -> 0.63.
 template <int EPI, bool NORM>
 int launch_f32(GemmF32 a, hipStream_t s) {
   const int n_units = EPI == F32_ROPE ? a.N / 2 : a.N;
   const int gy = (a.M + kRowsF32 - 1) / kRowsF32;
   a.rows = (a.M + gy - 1) / gy;
   constexpr int kMaxGridY = 65535;
+  constexpr bool kPlain = EPI == F32_STORE || EPI == F32_RESIDUAL;
+  const int blocks2 = ((n_units + 1) / 2 + 3) / 4;
+  const bool two = kPlain && gy > 1 && (int64_t)blocks2 * gy >= 768;
   for (int y0 = 0; y0 < gy; y0 += kMaxGridY) {
     const int ny = gy - y0 < kMaxGridY ? gy - y0 : kMaxGridY;
     if ((a.m_base = y0 * a.rows) >= a.M) break;
-    if (n_units <= 1024 && a.Kd >= 1024) gemm_f32_kernel<EPI, NORM, 4><<<dim3(n_units, ny), 256, 0, s>>>(a);
-    else gemm_f32_kernel<EPI, NORM, 1><<<dim3((n_units + 3) / 4, ny), 256, 0, s>>>(a);
+    if (two) gemm_f32_kernel<EPI, NORM, 1, kPlain><<<dim3(blocks2, ny), 256, 0, s>>>(a);
+    else if (n_units <= 1024 && a.Kd >= 1024) gemm_f32_kernel<EPI, NORM, 4, false><<<dim3(n_units, ny), 256, 0, s>>>(a);
+    else gemm_f32_kernel<EPI, NORM, 1, false><<<dim3((n_units + 3) / 4, ny), 256, 0, s>>>(a);
     SSD_HIP(hipGetLastError());
   }
   return SSD_OK;

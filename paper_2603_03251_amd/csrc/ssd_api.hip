@@ -589,8 +589,8 @@ int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset,
 // for, and several sequences where their prompts are short: a pass streams every weight once, so what a prompt costs is its
 // number of passes (a 1020-token prompt of the 1B shape: 3 passes of 340 rows instead of 170 passes of K+1 = 6 rows).
 // Otherwise chunks of K+1 tokens of all sequences.  Contexts whose rounds are narrow passes also take such a chunk where it
-// holds the whole prompts of a group: one persistent launch is shorter than a wide pass of as few rows (1B shape, 6 rows 0.68
-// against 0.90 ms, 48 rows 0.82 against 1.03), two of them are not (7 tokens in chunks of 6: 1.36 against 0.90 ms).
+// holds the whole prompts of a group: one persistent launch is shorter than a wide pass of as few rows (1B shape, 6 rows 0.65
+// against 0.90 ms, 48 rows 0.78 against 1.03), two of them are not (7 tokens in chunks of 6: 1.3 against 0.89 ms).
 int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t* lens, int b0, int nb, hipStream_t s) {
   const int K1 = c->K + 1;
   for (int g0 = 0, gn = 0; g0 < nb; g0 += gn) {

@@ -165,6 +165,33 @@ def test_f32_odd_sizes(B, shape, kw):
     assert worst < 2e-6          # measured 3e-7 on the 2-layer tiny pair; fp32 sums of up to 1100 terms in another order
 
 
+@pytest.mark.parametrize("batch,T", [(4, 2), (3, 3), (25, 6)])
+def test_f32_linear_layers_of_two_features_per_wavefront(B, batch, T):
+    """Up to 8 rows one feature per wavefront everywhere; with 9 rows the head of 6147 features takes two (769 blocks in two row
+    groups, an odd last feature); with 150 rows o and down (width 516: 65 blocks in 19 groups) do too.  Extends of every
+    sequence against the oracle, fp32 bound."""
+    shape = I.ModelShape(n_layers=2, d_model=516, n_q_heads=4, n_kv_heads=2, head_dim=64, d_ffn=1036, vocab=6147, dtype="f32",
+                         rope_theta=10000.0, tie_embeddings=False)
+    P, K, seed = 40, 5, 61
+    print(f"[case] fp32 extend of {batch} x {T} rows", flush=True)
+    w = I.make_weights(shape, seed)
+    om, model = O.Model.from_weights(shape, w), B.ssd_model_create(shape, w)
+    ctx = B.ssd_ctx_create(model, batch, K, 1, P + 2 * K + 2)
+    try:
+        k, v = I.make_prefix_kv(shape, batch, P, seed)
+        B.ssd_ctx_load_trunk(ctx, kv_to_device(k, "f32"), kv_to_device(v, "f32"), P)
+        tokens = I.make_pending(shape, batch, K, seed)[:, :T]
+        logits = torch.empty((batch, T, shape.vocab), dtype=torch.float32, device="cuda")
+        B.ssd_ctx_extend(ctx, dev_i32(tokens), 0, logits)
+        got = logits.cpu().numpy()
+        for b in range(batch):
+            want, _, _ = O.glue_extend(om, oracle_trunk_from_arrays(om, k, v, b), tokens[b])
+            assert row_rel_err(got[b], want) < TOL["f32"], b
+    finally:
+        B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
 def test_small_bf16_ragged_rows_synthetic_prefix(B):
     # M = 2 * 4 * 3 = 24 rows, prefix 203 (not a multiple of anything), GQA group 4
     _run_round_parity(B, SMALL_BF16, batch=2, P=203, K=3, F=3, seed=7, synthetic_kv=True)
