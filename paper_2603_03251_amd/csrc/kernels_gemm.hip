@@ -382,7 +382,7 @@ int launch_gemm(int dtype, int epi, const void* x, int64_t x_plane, const void* 
   switch (epi) {
     case EPI_STORE_F32: return launch_f32<F32_STORE, false>(a, s);
     case EPI_RESIDUAL_ADD: return launch_f32<F32_RESIDUAL, false>(a, s);
-    default: return launch_f32<F32_SWIGLU, false>(a, s);
+    default: set_error("fp32 gate/up layers run with their norm (launch_norm_swiglu_f32)"); return SSD_EINVAL;
   }
 }
 

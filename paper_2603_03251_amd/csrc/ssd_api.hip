@@ -444,29 +444,30 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
   const int p_ub = stored_ub > 1 ? stored_ub : 1;
   const int n_seq = M / rows_per_seq;
   const int per_pass = cap / rows_per_seq;
-  // Key splits of the stored trunk: the attention phase lasts (rounds of units over the grid) x (a unit's 32-key blocks
-  // per wavefront + its fixed part), and more than one split adds a merge (a phase of its own in wide passes, the last
-  // unit of a tile to arrive in narrow ones).  Costs in microseconds as measured
-  // on the 1B shape; the choice only affects speed.
+  // Key splits of the stored trunk, and in wide passes query tiles per unit: the attention phase lasts (rounds of units over
+  // the grid) x (a unit's 32-key blocks per wavefront + its fixed part, which grows with its tiles), and more than one split
+  // adds a merge (a phase of its own in wide passes, the last unit of a tile to arrive in narrow ones: its arrival count and
+  // the other splits' partial results each cost a memory round trip).  Costs in microseconds as measured on the 1B shape; the
+  // choice only affects speed.  Few rows over a short trunk fill the chip with units of one tile (24 rows x 4 sequences, 1500
+  // keys: 14.4 us, 17.8 with three); over a long one they are shorter as three-tile units with the keys split (8000 keys: 16.6
+  // us less, 3000: 1.4 less), and tiles beyond one per compute unit share a unit before they wait for a second round (24 rows
+  // x 16 sequences, 8000 keys: two and one tiles 33 and 66 us more than three).
   {
     const int seqs = n_seq < per_pass ? n_seq : (per_pass > 0 ? per_pass : 1);
-    // Wide passes: units of as few query tiles as give every compute unit at most one, so that few rows still fill the
-    // chip (24 rows x 4 sequences: 14.4 us as 192 units of one tile, 19 as 64 of three, whose sharing of the stored keys
-    // pays only when there are units enough)
-    p.NQ = 1;
-    while (wide && p.NQ < kFusedWideQueryTiles && seqs * p.Hkv * ((p.QT + p.NQ - 1) / p.NQ) > p.nwg) ++p.NQ;
-    const int pairs = seqs * p.Hkv * ((p.QT + p.NQ - 1) / p.NQ);
     int best = 1;
     float best_cost = 0.f;
     const int ns_cap = part.ns_max;                     // what the partial-softmax buffers were sized for
-    const float merge_cost = wide ? 5.0f : 4.0f;  // a phase of its own / the last unit of a tile to arrive (its arrival
-                                                           // count and the other splits' partial results each cost a memory round trip)
-    for (int ns = 1; ns <= ns_cap && ns <= 16; ++ns) {
-      const int keys = (p_ub + ns - 1) / ns;
-      const int blocks = ((keys + 31) / 32 + kFusedWaves - 1) / kFusedWaves;
-      const int rounds = (pairs * ns + p.nwg - 1) / p.nwg;
-      const float cost = rounds * (0.9f * blocks + 3.0f) + (ns > 1 ? merge_cost : 0.f);
-      if (ns == 1 || cost < best_cost) { best = ns; best_cost = cost; }
+    const float merge_cost = wide ? 5.0f : 4.0f;
+    p.NQ = 0;
+    for (int nq = 1; nq <= (wide ? kFusedWideQueryTiles : 1); ++nq) {
+      const int pairs = seqs * p.Hkv * ((p.QT + nq - 1) / nq);
+      for (int ns = 1; ns <= ns_cap && ns <= 16; ++ns) {
+        const int keys = (p_ub + ns - 1) / ns;
+        const int blocks = ((keys + 31) / 32 + kFusedWaves - 1) / kFusedWaves;
+        const int rounds = (pairs * ns + p.nwg - 1) / p.nwg;
+        const float cost = rounds * (0.9f * blocks + 3.0f + 1.5f * (nq - 1)) + (ns > 1 ? merge_cost : 0.f);
+        if (p.NQ == 0 || cost < best_cost) { p.NQ = nq; best = ns; best_cost = cost; }
+      }
     }
     p.KPU = ((p_ub + best - 1) / best + 31) / 32 * 32;
     p.NS = (p_ub + p.KPU - 1) / p.KPU;

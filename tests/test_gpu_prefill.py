@@ -7,7 +7,7 @@ import torch
 
 import ssd_inputs as I
 from oracle import ssd_oracle as O
-from tests.gpu_util import TOL_BF16_OWN_PREFILL, dev_f32, dev_i32, row_rel_err
+from tests.gpu_util import TOL_BF16_OWN_PREFILL, TOL_WIDE_BF16, dev_f32, dev_i32, row_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -22,12 +22,12 @@ def B():
     return binding
 
 
-def _trunk(B, ctx, lens, max_trunk):
+def _trunk(B, ctx, lens, max_trunk, shape=SHAPE):
     """Keys and values of the verified positions, [layer][sequence] arrays [len][Hkv][64]."""
     v = B.ssd_ctx_views(ctx)
-    T, hkv = (max_trunk + 63) // 64 * 64, SHAPE.n_kv_heads
+    T, hkv = (max_trunk + 63) // 64 * 64, shape.n_kv_heads
     ks, vs = [], []
-    for l in range(SHAPE.n_layers):
+    for l in range(shape.n_layers):
         k = B.device_copy(v.h_trunk_k[l], (len(lens), hkv, T, 64), torch.bfloat16).float().cpu().numpy()
         vt = B.device_copy(v.h_trunk_v[l], (len(lens), hkv, T // 32, 64, 32), torch.bfloat16).float().cpu().numpy()
         vt = vt.transpose(0, 1, 2, 4, 3).reshape(len(lens), hkv, T, 64)
@@ -148,3 +148,73 @@ def test_wide_attention_units_of_two_and_three_query_tiles(B, heads, lens):
         for ctx in ctxs:
             B.ssd_ctx_destroy(ctx)
         B.ssd_model_destroy(model)
+
+
+@pytest.mark.parametrize("pages", [0, 420])
+@pytest.mark.parametrize("kv_heads,lens", [(1, [6000]), (2, [4100, 2500]), (1, [2600])])
+def test_appended_prompts_with_key_splits(B, kv_heads, lens, pages):
+    """8 query heads on one or two KV heads: some 190 query tiles per pass of up to 384 tokens, which over thousands of stored
+    keys run as units of two or three tiles with the keys in two to four splits.  The last splits hold no keys for the first tiles of a pass, and a merge
+    launch follows.  Keys, values and glue logits against the narrow passes' chunks of K+1 tokens."""
+    shape = I.ModelShape(n_layers=2, d_model=512, n_q_heads=8, n_kv_heads=kv_heads, head_dim=64, d_ffn=1024, vocab=2064,
+                         dtype="bf16", rope_theta=500000.0, tie_embeddings=True)
+    nb, seed, max_trunk = len(lens), 5 + kv_heads, max(lens) + 2 * K + 8
+    print(f"[case] prefill of {lens}, {kv_heads} KV heads, {pages} pages", flush=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, 14))
+    prompt = dev_i32(I.make_prompt(shape, nb, max(lens), seed))
+    pending, temps = dev_i32(I.make_pending(shape, nb, K, seed)), dev_f32(np.zeros(nb))
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags, pages) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
+    try:
+        got, kv = [], []
+        for ctx in ctxs:
+            B.ssd_ctx_prefill(ctx, prompt, lens)
+            if not pages:
+                kv.append(_trunk(B, ctx, lens, max_trunk, shape))
+            B.ssd_prespeculate(ctx, pending, temps, 1)
+            got.append(B.read_cache(ctx)["glue_logits"].cpu().numpy())
+        for part in (0, 1) if kv else ():
+            for l in range(shape.n_layers):
+                for b in range(nb):
+                    e = row_rel_err(kv[0][part][l][b], kv[1][part][l][b])
+                    assert e < 2 * TOL_BF16_OWN_PREFILL, (part, l, b, e)
+        e = row_rel_err(got[0], got[1])
+        print(f"[splits] glue logits {e:.2e}", flush=True)
+        assert e < 2 * TOL_BF16_OWN_PREFILL
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
+@pytest.mark.parametrize("pages", [0, 700])
+@pytest.mark.parametrize("lens", [[6000, 3500, 6000, 100], [700] * 4, [3000] * 3])
+def test_wide_rounds_over_long_trunks(B, lens, pages):
+    """24 branch rows of 3 or 4 sequences, 8 KV heads: 144 and 192 query tiles.  Over a short trunk a unit takes one of them;
+    over thousands of keys units of three with the keys split are the shorter ones.  Against the narrow passes."""
+    shape = I.ModelShape(n_layers=2, d_model=512, n_q_heads=32, n_kv_heads=8, head_dim=64, d_ffn=1024, vocab=2064, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    nb, k5, f4, seed = len(lens), 5, 4, 15
+    print(f"[case] wide rounds over {lens} keys, {pages} pages", flush=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, seed))
+    pending, temps = dev_i32(I.make_pending(shape, nb, k5, seed)), dev_f32(np.zeros(nb))
+    keys = dev_i32(np.arange(nb * 24).reshape(nb, 6, 4))
+    toks = dev_i32(I.make_prompt(shape, nb * 24, k5, seed).reshape(nb, 6, 4, k5))
+    got = []
+    try:
+        for flags in (0, B.SSD_CTX_NARROW_PASSES):
+            ctx = B.ssd_ctx_create(model, nb, k5, f4, max(lens) + 2 * k5 + 8, flags, pages)
+            try:
+                assert B.ssd_ctx_views(ctx).pass_rows == (48 if flags else 384)
+                B.ssd_ctx_fill_synthetic_kv(ctx, lens, seed)
+                B.ssd_ctx_set_forced(ctx, keys, toks)
+                B.ssd_prespeculate(ctx, pending, temps, 1)
+                c = B.read_cache(ctx)
+                got.append([c[n].cpu().numpy() for n in ("glue_logits", "logits", "hidden")])
+            finally:
+                B.ssd_ctx_destroy(ctx)
+    finally:
+        B.ssd_model_destroy(model)
+    for name, a, b in zip(("glue_logits", "logits", "hidden"), *got):
+        e = row_rel_err(a, b)
+        print(f"[wide] {name} {e:.2e}", flush=True)
+        assert e < 2 * TOL_WIDE_BF16
