@@ -81,7 +81,7 @@ def print_phase_clocks(B, ctx, one_round, shape):
     w = sys.stderr.write
     if B.ssd_ctx_views(ctx).pass_rows > 48:
         # wide passes: every phase is a launch of its own; slots 0 entry, 3 operands of the first stage requested,
-        # 4 last MFMA of the first pair, 2 end (the attention kernel records entry and end only)
+        # 4 last MFMA of the first pair, 2 end; the residual launches behind o and down record entry and end in 6 and 7
         w("phase clocks of one wide decode step (us after the phase's first workgroup entered; mean over layers of the mean / "
           "slowest workgroup)\n")
         names = {0: "qkv", 1: "attention", 2: "merge of key splits", 3: "o-proj", 4: "gate/up", 5: "down"}
@@ -101,6 +101,16 @@ def print_phase_clocks(B, ctx, one_round, shape):
                 f_ = lambda v: "    -" if v is None else f"{v:5.1f}"
                 w(f"  {name:19s} workgroups {int(r_[4]):3d}  first operands requested {f_(r_[0])}  MFMAs done {f_(r_[1])}  "
                   f"end {f_(r_[2])}  slowest {f_(r_[3])}\n")
+        for name, phases, first, end in (("embedding", [0], 0, 2), ("residual after o", [1 + 6 * l + 3 for l in range(L)], 6, 7),
+                                         ("residual after down", [1 + 6 * l + 5 for l in range(L)], 6, 7)):
+            spans = []
+            for x in (t[p_] / 100.0 for p_ in phases):
+                busy = x[end] > 0
+                if busy.any():
+                    spans.append([(x[end][busy] - x[first][busy].min()).mean(), x[end][busy].max() - x[first][busy].min(), busy.sum()])
+            if spans:
+                m_ = np.mean(spans, axis=0)
+                w(f"  {name:19s} workgroups {int(m_[2]):3d}  end {m_[0]:5.1f}  slowest {m_[1]:5.1f}\n")
         return
     us = (t - t[0, 0].min()) / 100.0
     entry, after, end = us[:, 0], us[:, 1], us[:, 2]

@@ -146,7 +146,8 @@ __device__ __forceinline__ f32x16 mfma32_f16(bf16x8 a, bf16x8 b, f32x16 c) {
 }
 
 // Optional phase clocks (a measurement aid): [phase][slot][workgroup] ticks of the 100 MHz real-time counter; slot 0
-// phase entry, 1 after the grid barrier, 2 end of the phase's work, 3.. probes inside a phase.
+// phase entry, 1 after the grid barrier, 2 end of the phase's work, 3.. probes inside a phase (wide passes: 6 and 7 of the
+// o- and down-projections are entry and end of the residual launch behind them).
 __device__ __forceinline__ void stamp(const FusedParams& p, int ph, int which) {
   // (launches of more workgroups than the grid of the persistent kernel - the attention, merge and hidden-state launches
   // of a wide pass - record their first p.nwg workgroups: the table has p.nwg columns)
@@ -1397,12 +1398,14 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
 // layer (8 consecutive features per thread are one lane's 16 bytes of it), the row's 1/rms, which that layer's epilogue
 // multiplies in, and, where asked for, the normalised row as fp32 hidden states.  Reads S + 1 rows of d floats: at 96 rows of the 1B shape (S = 4 and 8) 4.9 us, at 384 (S = 2)
 // 6.0 us, of which launch and two memory round trips are about 4.
-template <bool EMBED>
+// CLOCKS: with phase clocks (an instance of its own: the test of p.prof alone cost a wide round 1 %).
+template <bool EMBED, bool CLOCKS>
 __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p, const float* part, int S, const bf16_t* gain,
-                                                                  float* hidden) {
+                                                                  float* hidden, int ph) {
   constexpr int kHeld = 2;                       // 8-feature chunks per thread kept in registers (d <= 4096); others are re-read
   __shared__ float sum_s[kWideWaves];
   const int m = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (CLOCKS) stamp(p, ph, EMBED ? 0 : 6);       // (the phase's other slots are the linear layer's)
   gfloat* h = (gfloat*)p.h + (int64_t)m * p.d;
   int tok = 0;
   if (EMBED) {
@@ -1483,6 +1486,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
     f32x4 v[2] = {*(const gf32x4*)(h + c), *(const gf32x4*)(h + c + 4)};   // this thread's own stores
     put(c, v, *(const u32x4*)(gain + c));
   }
+  if (CLOCKS) stamp(p, ph, EMBED ? 2 : 7);
 }
 
 // The two large linear layers of a wide pass (gate/up + SwiGLU, LM head; stream-order units of 4 feature tiles, no
@@ -2609,6 +2613,15 @@ int launch_wide_attn(const FusedParams& p, const FusedLayer& L, int ph, hipStrea
   return launch_wide_attn_nq<PL, PG, 3>(p, L, ph, s);
 }
 
+int launch_wide_resid(const FusedParams& p, bool embed, const float* part, int S, const bf16_t* gain, float* hidden, int ph, hipStream_t s) {
+  if (embed && p.prof) wide_resid_kernel<true, true><<<p.M, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
+  else if (embed) wide_resid_kernel<true, false><<<p.M, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
+  else if (p.prof) wide_resid_kernel<false, true><<<p.M, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
+  else wide_resid_kernel<false, false><<<p.M, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
+  SSD_HIP(hipGetLastError());
+  return SSD_OK;
+}
+
 // One wide pass: phases [first, last] as one launch each (two for o and down).  layers_host: the pass's layer table in host
 // memory.
 template <class PL, bool PG>
@@ -2616,8 +2629,7 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
   const int lm_phase = fused_last_phase(p.L);
   for (int ph = first; ph <= last; ++ph) {
     if (ph == 0) {
-      wide_resid_kernel<true><<<p.M, kWideThreads, 0, s>>>(p, nullptr, 0, layers_host[0].attn_norm, nullptr);
-      SSD_HIP(hipGetLastError());
+      SSD_TRY(launch_wide_resid(p, true, nullptr, 0, layers_host[0].attn_norm, nullptr, ph, s));
       continue;
     }
     WideEpi e{};
@@ -2640,9 +2652,8 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
       e.out = p.fix_buf; e.ld = p.d;
       SSD_TRY(launch_wide_part(p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s));
       const bool fin = sub == 5 && l + 1 == p.L;
-      wide_resid_kernel<false><<<p.M, kWideThreads, 0, s>>>(p, p.fix_buf, e.S, sub == 3 ? L.mlp_norm : (fin ? p.final_norm : layers_host[l + 1].attn_norm),
-                                                            fin ? p.hidden : nullptr);
-      SSD_HIP(hipGetLastError());
+      const bf16_t* gain = sub == 3 ? L.mlp_norm : (fin ? p.final_norm : layers_host[l + 1].attn_norm);
+      SSD_TRY(launch_wide_resid(p, false, p.fix_buf, e.S, gain, fin ? p.hidden : nullptr, ph, s));
     } else if (sub == 4) {
       e.act_out = p.act;
       SSD_TRY(launch_wide_gate_up(p, L.gu, e, s));

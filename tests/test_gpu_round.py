@@ -345,6 +345,30 @@ def test_wide_passes_agree_with_narrow_passes_and_repeat_bit_for_bit(B):
     assert e < TOL["bf16"]
 
 
+def test_phase_clocks_of_a_wide_pass_cover_every_launch(B):
+    """Wide passes: the embedding, and the residual launches behind o and down, record entry and end like the other launches."""
+    shape, seed, nb, P, K, F = SMALL_BF16, 24, 3, 50, 4, 5
+    model = B.ssd_model_create(shape, I.make_weights(shape, seed))
+    ctx = B.ssd_ctx_create(model, nb, K, F, P + 4 * K + 8)
+    try:
+        B.ssd_ctx_fill_synthetic_kv(ctx, [P] * nb, seed)
+        B.ssd_ctx_enable_phase_clocks(ctx, True)
+        B.ssd_prespeculate(ctx, dev_i32(I.make_pending(shape, nb, K, seed)), dev_f32(np.zeros(nb)), seed)
+        t = B.ssd_ctx_read_phase_clocks(ctx).astype(np.int64)          # [phase][slot][workgroup], the last decode step's
+        rows = nb * (K + 1) * F
+        spans = [(0, 0, 2)] + [(1 + 6 * l + sub, 6, 7) for l in range(shape.n_layers) for sub in (3, 5)]
+        before = 0
+        for ph, first, end in spans:
+            assert (t[ph, first, :rows] > before).all() and (t[ph, end, :rows] >= t[ph, first, :rows]).all(), ph
+            before = t[ph, end, :rows].max()
+        for l in range(shape.n_layers):                                # the residual launch follows its linear layer
+            for sub in (3, 5):
+                assert t[1 + 6 * l + sub, 6, :rows].min() > t[1 + 6 * l + sub, 2].max()
+    finally:
+        B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
 def test_small_bf16_ragged_prompt_lengths_in_one_batch(B):
     # five sequences whose prompts differ in length (one a single token): three fused passes of 2 + 2 + 1 sequences,
     # every row with its own visible trunk length
