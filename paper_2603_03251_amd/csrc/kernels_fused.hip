@@ -2720,6 +2720,12 @@ int launch_fused_wide(const FusedParams& p, const FusedLayer* layers_host, int f
   SSD_CHECK_ARG(p.M <= p.fix_stride, "no room for the partial sums of %d rows", p.M);
   SSD_CHECK_ARG(!p.is_branch || !p.appended, "branch rows keep their own keys");
   SSD_CHECK_ARG(p.is_branch || p.appended || p.R <= kFusedWideFreshKeys, "an extend of %d tokens must append its keys first", p.R);
+  // What the attention and append kernels index with: trunk slots (a row's own included), the lane that holds a wavefront's
+  // n-th page, private slots.  The units' LDS extents follow from NQ, G, SL and R above.
+  static_assert(kMultiQ * 64 <= kMultiFreshKeys, "fresh keys of a unit of branch rows");
+  SSD_CHECK_ARG(p.tv_ub >= 0 && p.tv_ub + (p.is_branch ? 0 : p.R) <= p.vt_stride, "trunk positions up to %d + %d, room for %d", p.tv_ub, p.R, p.vt_stride);
+  SSD_CHECK_ARG(!p.pages || (p.page_stride * 32 == p.vt_stride && p.KPU <= 64 * kFusedWaves * 32), "%d keys per unit in a paged trunk", p.KPU);
+  SSD_CHECK_ARG(!p.is_branch || (p.suffix_len >= 1 && p.suffix_len <= p.suffix_cap && p.suffix_cap <= p.SL), "private slot %d of %d", p.suffix_len, p.suffix_cap);
   SSD_CHECK_ARG(first >= 0 && last <= fused_last_phase(p.L) && first <= last && layers_host, "bad phase range");
   if (p.pages) {
     SSD_CHECK_ARG((p.planes & 24) != 24, "a paged trunk takes the default planes of the attention unit only");
