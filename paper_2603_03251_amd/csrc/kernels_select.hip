@@ -542,7 +542,7 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_decide_kernel(const float
   ScoreId best;
   double mass;
   // once for the residual and, where this part of it has no mass (its candidate counts only if no part has any, and is then
-  // p's), once more for p
+  // p's), once more for p (without qinv, which is no number where the draft's row has no distribution)
   for (bool residual = k < K;; residual = false) {
     best = {-1.0, 0x7fffffff};
     mass = 0.0;
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_decide_kernel(const float
       for (int u = 0; u < U; ++u) {
         const int t = t0 + u * kVerifyBlock;
         double r = residual_of(exp_rel(logit_score(vp[u]), pmax, inv_t, table), pinv,
-                               residual ? exp_rel(logit_score(vq[u]), qmax, inv_t, table) : 0.0, qinv);
+                               residual ? exp_rel(logit_score(vq[u]), qmax, inv_t, table) : 0.0, residual ? qinv : 0.0);
         r = t < hi && r > 0.0 ? r : 0.0;
         mass += r;
         const ScoreId c = {t < hi ? r / -log(draw_u(prefix, (uint64_t)t)) : -1.0, t};

@@ -1,5 +1,5 @@
 """The two verification kernels where their cuts can go wrong: vocabularies around the sizes at which a row is cut into one more
-part, parts of the bonus row whose residual has no mass, a residual without any mass, infinite and NaN logits."""
+part, parts of the bonus row whose residual has no mass, a residual without any mass, NaN logits and infinite ones of either sign."""
 import numpy as np
 import pytest
 import torch
@@ -63,3 +63,24 @@ def test_verify_residual_without_mass_falls_back_to_the_target(B):
     k, t = _verify(B, zt, zt[:, :K].copy(), np.array([[-1, 5]], np.int32), np.ones(1, np.float32), 7)   # a token outside: rejected
     score = np.log(O.softmax_T(zt[0, 0], 1.0)) + O.gumbel(7, O.STREAM_BONUS, 0, 0, V)
     assert k[0] == 0 and t[0] == int(np.argmax(score))
+
+
+def test_verify_with_rows_that_have_no_distribution(B):
+    """Greedy: +infinity is the row's argmax.  Sampled: such a row has no distribution (every probability is 0/0), so its token
+    is rejected; a target row without a distribution gives token 0, beside a draft row without one (also one of NaN only) the
+    bonus token comes from the target's own distribution."""
+    V, K, T, seed = 3000, 3, 0.8, 21
+    g = np.random.default_rng(8)
+    zt = np.tile(g.standard_normal((1, K + 1, V)).astype(np.float32), (5, 1, 1))
+    zd = zt[:, :K].copy()                                     # equal distributions: every token is accepted
+    spec = np.tile(np.array([[5, 6, 7]], np.int32), (5, 1))
+    zt[0, 1, 2999] = np.inf                                   # greedy, position 1
+    spec[0, 0], spec[0, 1] = zt[0, 0].argmax(), 2999
+    spec[0, 2] = (zt[0, 2].argmax() + 1) % V                  # rejected: the bonus is the argmax of row 2
+    zt[1, 1, 2999] = np.inf                                   # sampled, target row 1
+    zd[2, 1, 17] = np.inf                                     # sampled, draft row 1
+    zd[3, 1] = np.nan                                         # a draft row without any probability
+    k, t = _verify(B, zt, zd, spec, np.array([0.0, T, T, T, T], np.float32), seed)
+    from_p = lambda b, i: int(np.argmax(np.log(O.softmax_T(zt[b, i], T)) + O.gumbel(seed, O.STREAM_BONUS, b, i, V)))
+    assert k.tolist() == [2, 1, 1, 1, 3]
+    assert t.tolist() == [int(zt[0, 2].argmax()), 0, from_p(2, 1), from_p(3, 1), from_p(4, K)]
