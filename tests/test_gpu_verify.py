@@ -30,8 +30,6 @@ def _verify(B, zt, zd, spec, temps, seed):
 @pytest.mark.parametrize("V", [2, 1023, 1024, 2047, 2049, 4097, 32771, 65536])
 @pytest.mark.parametrize("nb,K", [(1, 1), (1, 15), (7, 3), (70, 2)])
 def test_verify_at_the_edges_of_its_parts(B, V, nb, K):
-    if nb * V > 2 ** 20 and K > 2:
-        pytest.skip("covered by the smaller batch")
     print(f"[case] verify B={nb} K={K} V={V}", flush=True)
     g = np.random.default_rng(V + nb + K)
     zd = (g.standard_normal((nb, K, V)) * 2).astype(np.float32)
@@ -53,7 +51,8 @@ def test_verify_at_the_edges_of_its_parts(B, V, nb, K):
             if want.bonus_margin > MARGIN:
                 assert t[b] == want.bonus, b
                 checked += 1
-    assert checked > 0 or nb < 7
+    # (with these seeds every sequence of the small batches is decided by more than the margin)
+    assert checked == nb if nb <= 7 else checked >= 0.9 * nb
 
 
 def test_verify_residual_without_mass_falls_back_to_the_target(B):
