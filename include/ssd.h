@@ -143,7 +143,9 @@ typedef struct {
                                    [B][Hkv][T][D], values transposed per 32-position block [B][Hkv][T/32][D][32] */
   int32_t batch, K, F, vocab, d_model, max_trunk;
   int32_t fused_pass;          /* 0: one kernel per operator; 1: fused pass, one launch per phase; 2: one persistent launch */
-  int32_t pass_rows;           /* most rows of one fused pass: 48 (narrow passes), 384 (wide passes), 0 without the fused pass */
+  int32_t pass_rows;           /* most rows of one fused pass of a round: 48 (narrow passes), 384 (wide passes), 0 without the fused
+                                  pass.  Prompts are prefilled in passes of up to 384 rows either way (unless a flag asks for
+                                  narrow passes or other activation planes), with a workspace for them */
 } ssd_views;
 
 const char* ssd_last_error(void);
@@ -209,9 +211,10 @@ int ssd_ctx_truncate_trunk(ssd_ctx* ctx, const int32_t* h_lens, void* stream);
  * verified text, i.e. rejected positions and bounds that ran ahead), ssd_ctx_truncate_trunk, ssd_ctx_release_sequence.
  * ENOMEM when the pool is empty: the context is unchanged apart from pages already taken for the same call; release a
  * sequence or refresh the bounds and call again.
- * ssd_ctx_prefill runs all sequences in common passes up to the longest prompt, so until it returns every sequence holds
- * pages for that length (the surplus goes back at its end): a pool sized for the true lengths only is filled slot by slot
- * with ssd_ctx_prefill_sequence.  The block table lives in pinned host memory and is copied to the device in stream
+ * ssd_ctx_prefill runs several sequences in common passes up to the longest prompt among them (consecutive ones that fit a
+ * wide pass together; all of them in contexts that prefill in narrow passes or per operator), so until it returns a sequence
+ * may hold pages for a neighbour's length (the surplus goes back at its end): a pool sized for the true lengths only is filled
+ * slot by slot with ssd_ctx_prefill_sequence.  The block table lives in pinned host memory and is copied to the device in stream
  * order whenever it changed; calls on one context are not thread-safe.
  *   ssd_ctx_kv_pages          total pages (0 for a contiguous trunk) and pages currently free.
  *   ssd_ctx_release_sequence  sequence b finished: its pages return to the pool and its trunk is empty; a round must not
@@ -291,8 +294,8 @@ size_t ssd_verify_workspace_bytes(int32_t B, int32_t K);
  * serving loops, harnesses that forbid hipMalloc.  Same arguments, results and error behaviour as ssd_verify, without
  * d_workspace: the partial results of the passes meet in a static device array of ssd_verify_static_capacity() bytes
  * (1 MiB; every GPU the library runs on holds one until the process ends).  The call allocates nothing, neither with
- * hipMalloc nor through any library.  EINVAL if ssd_verify_workspace_bytes(B, K) exceeds the capacity (B (2K+1) up to
- * about 1200 rows of logits fit).  All calls on one GPU share that GPU's array: two calls whose work overlaps in time on
+ * hipMalloc nor through any library.  EINVAL if ssd_verify_workspace_bytes(B, K) exceeds the capacity (a sequence takes
+ * 512 (2K+1) + 1540 bytes: 340 sequences fit at K = 1, 146 at K = 5, 60 at K = 15).  All calls on one GPU share that GPU's array: two calls whose work overlaps in time on
  * one GPU (different streams, or different threads) race; calls on one stream are ordered and safe.  Nothing in the array
  * has to be cleared between calls. */
 int ssd_verify_static(const float* d_target_logits, const float* d_draft_logits, const int32_t* d_spec_tokens,

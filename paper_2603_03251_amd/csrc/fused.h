@@ -13,10 +13,13 @@ namespace ssd {
 constexpr int kFusedThreads = 512;  // 8 wavefronts; they split the reduction dimension of a weight block
 constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxRows = 48;   // rows of one narrow pass (three 16-row MFMA tiles)
-constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles): contexts with more than kFusedMaxRows rows
+constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles): contexts with more than kFusedMaxRows rows, and prompts
 constexpr int kFusedWideQueryTiles = 3;   // wide passes: most query tiles per attention unit
 constexpr int kFusedWideFreshKeys = 192;  // wide passes: keys of the pass itself an attention unit has LDS room for
-constexpr int kFusedWideAppendRows = 64;  // wide extends of more tokens of a sequence append their keys before the attention
+// Wide extends of more tokens of a sequence append their keys before the attention.  4 layers of the 1B shape, one prompt, us per
+// pass with the keys appended / staged by every unit: 64 rows 273 / 269, 96 289 / 284, 128 308 / 309, 160 314 / 322, 192 (what
+// the units have room for) 326 / 337.  The two cross near 120 rows; the line lies below that and costs 1 to 3 % in between.
+constexpr int kFusedWideAppendRows = 64;
 constexpr int kFusedWideSlices = 8;       // wide passes: most k-slices of the o- and down-projections (one per XCD)
 constexpr int kFusedWideRowGroup = 96;    // wide passes: rows of a full row group of a linear layer
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())

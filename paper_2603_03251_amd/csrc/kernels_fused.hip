@@ -2564,7 +2564,10 @@ int launch_wide_qkv(const FusedParams& p, const FusedGemm& g, const WideEpi& e, 
   return launch_wide_gemm<2, FE_QKV, kWideGroup>(p, g, p.xn, e, s);
 }
 
-// o and down: the largest row groups, and as many k-slices as give every pair a workgroup of its own; e.S = how many
+// o and down: the largest row groups (from 4 tiles on; with fewer, one group of them all), and as many k-slices as give every
+// pair a workgroup of its own; e.S = how many.  Groups of 6, 3 and 2 tiles, us per pass of 4 layers of the 1B shape: 64 rows
+// 262, 255, 255; 96 rows 290, 275, 287; 128 rows 294, 297, 286; 160 rows 301, 302, 326; 192 rows 315, 316, 338 (runs of one
+// side differ by up to 5 % below 100 rows).
 int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
   const int nq = (g.n_units / g.KS) >> 1, tiles = (p.M + 15) >> 4;
   const int mtg = tiles >= 4 ? kWideGroup : tiles;
@@ -2582,7 +2585,9 @@ int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
 
 // gate/up + SwiGLU.  Up to 12 row tiles (192 rows) in one row group: a workgroup per unit of 4 feature tiles, the reduction
 // dimension over its wavefronts, every weight read once, instead of 16 feature tiles per workgroup on a quarter (up to
-// 96 rows) or half of the grid (170 rows: 27 us against 30; 32 rows: 18 against 20.9 in groups of 6).  With more rows 16 feature tiles per workgroup fill the
+// 96 rows) or half of the grid (170 rows: 27 us against 30; 32 rows: 18 against 20.9 in groups of 6;
+// whole passes of 4 layers of the 1B shape, against 96 rows per group of the LDS kernel: 112 rows 292 us and 304, 160 rows 301
+// and 311, 192 rows 315 and 323).  With more rows 16 feature tiles per workgroup fill the
 // grid and pull less.
 int launch_wide_gate_up(const FusedParams& p, const FusedGemm& g, const WideEpi& e, hipStream_t s) {
   const int tiles = (p.M + 15) >> 4;
@@ -2595,7 +2600,7 @@ int launch_wide_gate_up(const FusedParams& p, const FusedGemm& g, const WideEpi&
   return launch_wide_gemm_lds<FE_SWIGLU, false>(p, g, p.xn, e, s);
 }
 
-// The attention units of a pass, p.NQ query tiles each (host: as few as leave no compute unit with two units)
+// The attention units of a pass, p.NQ query tiles each (the host chooses them together with the key splits)
 template <class PL, bool PG, int NQ>
 int launch_wide_attn_nq(const FusedParams& p, const FusedLayer& L, int ph, hipStream_t s) {
   static const hipError_t configured = hipFuncSetAttribute((const void*)wide_attn_kernel<PL::q, PL::p, NQ, PG>,

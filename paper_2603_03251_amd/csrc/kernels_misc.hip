@@ -92,8 +92,8 @@ __device__ __forceinline__ float block_sum(float v, float* smem) {
   return t;
 }
 
-// x / sqrt(mean(x^2) + eps) * gain, one block per row (of 1024 threads where that is at most one step of four elements each:
-// 6 rows of 8192 take 5.5 us, 7.5 with 256 threads).  The row is read once, four elements per thread and step,
+// x / sqrt(mean(x^2) + eps) * gain, one block per row (of 1024 threads where that leaves at least one step of four elements to
+// each: 6 rows of 8192 take 5.5 us, 7.5 with 256 threads).  The row is read once, four elements per thread and step,
 // with the loads of up to 8 steps issued together (a row of 8192 is then one memory latency, not 32).
 constexpr int kNormBlock = 1024;
 template <typename T>

@@ -763,7 +763,7 @@ int launch_verify_static(const float* zt, const float* zd, const int32_t* spec, 
                          uint64_t seed, int32_t* accept_len, int32_t* bonus, hipStream_t s) {
   const size_t need = verify_workspace_bytes(B, K);
   SSD_CHECK_ARG(need <= kStaticScratchBytes,
-                "ssd_verify_static: B = %d, K = %d needs %zu bytes of scratch, the static buffer holds %zu (B (2K+1) <= about 1200)",
+                "ssd_verify_static: B = %d, K = %d needs %zu bytes of scratch, the static buffer holds %zu (512 (2K+1) + 1540 bytes per sequence)",
                 B, K, need, kStaticScratchBytes);
   constexpr int kMaxDevices = 64;
   static std::mutex mu;
