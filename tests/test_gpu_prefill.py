@@ -151,10 +151,10 @@ def test_wide_attention_units_of_two_and_three_query_tiles(B, heads, lens):
 
 
 @pytest.mark.parametrize("pages", [0, 420])
-@pytest.mark.parametrize("kv_heads,lens", [(1, [6000]), (2, [4100, 2500]), (1, [2600])])
+@pytest.mark.parametrize("kv_heads,lens", [(1, [6000]), (2, [4100, 2500]), (1, [4500])])
 def test_appended_prompts_with_key_splits(B, kv_heads, lens, pages):
-    """8 query heads on one or two KV heads: some 190 query tiles per pass of up to 384 tokens, which over thousands of stored
-    keys run as units of two or three tiles with the keys in two to four splits.  The last splits hold no keys for the first tiles of a pass, and a merge
+    """8 query heads on one or two KV heads: some 190 query tiles per pass of up to 384 tokens, which from about 3500 stored
+    keys on run as units of two or three tiles with the keys in two to four splits.  The last splits hold no keys for the first tiles of a pass, and a merge
     launch follows.  Keys, values and glue logits against the narrow passes' chunks of K+1 tokens."""
     shape = I.ModelShape(n_layers=2, d_model=512, n_q_heads=8, n_kv_heads=kv_heads, head_dim=64, d_ffn=1024, vocab=2064,
                          dtype="bf16", rope_theta=500000.0, tie_embeddings=True)
@@ -190,7 +190,8 @@ def test_appended_prompts_with_key_splits(B, kv_heads, lens, pages):
 @pytest.mark.parametrize("lens", [[6000, 3500, 6000, 100], [700] * 4, [3000] * 3])
 def test_wide_rounds_over_long_trunks(B, lens, pages):
     """24 branch rows of 3 or 4 sequences, 8 KV heads: 144 and 192 query tiles.  Over a short trunk a unit takes one of them;
-    over thousands of keys units of three with the keys split are the shorter ones.  Against the narrow passes."""
+    over thousands of keys units of two (3000) and three (6000) with the keys split are the shorter ones.  Against the narrow
+    passes."""
     shape = I.ModelShape(n_layers=2, d_model=512, n_q_heads=32, n_kv_heads=8, head_dim=64, d_ffn=1024, vocab=2064, dtype="bf16",
                          rope_theta=500000.0, tie_embeddings=True)
     nb, k5, f4, seed = len(lens), 5, 4, 15
