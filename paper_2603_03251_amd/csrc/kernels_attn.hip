@@ -305,7 +305,8 @@ __global__ __launch_bounds__(D) void attention_merge_kernel(const float* __restr
 // is, again, with weight 0).
 // What bounds it is latency, not bytes (16.8 MB of a 4096-token prefix of the 70B shape): everything a step loads is
 // requested before the queries are staged, and the planner gives a block one step where the chip has room.  6 rows x 64
-// heads x 4096 keys: 17.5 us (55.1 with a block per row, keys and values through the vector units).  One block for three
+// heads x 4096 keys: 17.9 us, 0.5 of them the test for values that are not finite (55.1 with a block per row, keys and values
+// through the vector units).  One block for three
 // query tiles, which pulls the trunk once, took 27: twice the code, run once by every wavefront, and a third of the
 // wavefronts to hide its latencies behind.
 constexpr int kExtWaves = 4, kExtKeys = 32 * kExtWaves;   // keys of a block's step
@@ -542,7 +543,7 @@ int choose_splits(const AttnArgs& a, int* keys_per_split) {
 }
 
 // The extend kernel's launch: splits of whole steps, as many as give the chip four blocks per compute unit (6 rows x 64
-// heads x 4096 keys: 33 splits of one step, 17.5 us), no more than the merge and the scratch hold.
+// heads x 4096 keys: 33 splits of one step, 17.9 us), no more than the merge and the scratch hold.
 template <int D>
 int launch_extend(const AttnArgs& a, hipStream_t s) {
   const int group = a.n_q_heads / a.n_kv_heads, n_seq = a.M / a.rows_per_seq;
