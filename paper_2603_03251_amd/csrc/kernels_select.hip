@@ -303,8 +303,8 @@ __global__ __launch_bounds__(64) void sample_merge_kernel(const ScoreId* __restr
 // decides, and scores its share of the bonus row for the residual; the block of a sequence that finishes last merges the
 // shares.  A row and the bonus row are shared among `parts` blocks, so that the few rows of one verification occupy the chip;
 // partial results are merged in a fixed order (the result does not depend on timing).  Measured (V = 128256, K = 5,
-// temperature 1): B = 1 55.0 -> 18.6 us a call (rows 7.2, decisions 12.3: six dependent memory round trips and three
-// reductions), B = 16 half of it greedy 104.9 -> 48.6 us (28.6 + 24.4).
+// temperature 1): B = 1 18.0 us a call (rows 7, decisions 10.5: five dependent memory round trips and three reductions), B = 16
+// half of it greedy 42 us (25 + 17; rows without their exponentials 18, of which 70 MB at the rate of a copy are 10).
 constexpr int kVerifyBlock = 256, kVerifyWaves = kVerifyBlock / 64;
 constexpr int kVerifyMaxParts = 32;     // blocks that share a row (one lane of a wavefront merges one of them)
 constexpr int kVerifyMaxBonusParts = 64;
@@ -348,12 +348,11 @@ __device__ __forceinline__ bool better_logit(float v, int t, float m, int id) { 
 __device__ __forceinline__ void exp_table_init(double* table) {
   if (threadIdx.x < 32) table[threadIdx.x] = exp2((double)threadIdx.x * (1.0 / 32.0));
 }
-__device__ __forceinline__ double exp_rel(float x, float m, double inv_t, const double* table) {
+__device__ __forceinline__ double exp_core(double a, const double* table) {
   constexpr double kMagic = 6755399441055744.0;            // 1.5 2^52: adding it leaves round(a 32 / ln 2) in the low bits
   constexpr double kLn2 = 0.693147180559945309417232121458, kLn2Tail = 2.3190468138462996e-17;   // ln 2 = their sum
   constexpr double kStepHi = (float)(kLn2 / 32.0);         // 24 bits: n kStepHi is exact
   constexpr double kStepLo = (kLn2 / 32.0 - kStepHi) + kLn2Tail / 32.0;
-  const double a = ((double)x - (double)m) * inv_t;
   const double biased = fma(a, 32.0 / kLn2, kMagic);
   const int n = (int)(uint32_t)__double_as_longlong(biased);
   const double nd = biased - kMagic;
@@ -365,7 +364,11 @@ __device__ __forceinline__ double exp_rel(float x, float m, double inv_t, const 
   q = fma(r, q, 1.0);
   const double t = table[n & 31];
   const double y = fma(t * r, q, t);                       // in [1, 2] (1 + 2^-6)
-  const double scaled = __hiloint2double(__double2hiint(y) + ((n >> 5) << 20), __double2loint(y));
+  return __hiloint2double(__double2hiint(y) + ((n >> 5) << 20), __double2loint(y));
+}
+__device__ __forceinline__ double exp_rel(float x, float m, double inv_t, const double* table) {
+  const double a = ((double)x - (double)m) * inv_t;
+  const double scaled = exp_core(a, table);
   // below e^-700 (and for "no probability"): 0; NaN (an infinite maximum) stays NaN
   return x == -INFINITY || a < -700.0 ? 0.0 : (a == a ? scaled : a);
 }
@@ -378,6 +381,28 @@ __device__ __forceinline__ double residual_of(double ep, double pinv, double eq,
   const double p = ep * pinv, q = eq * qinv;
   return fmax(p - q, 0.0);
 }
+
+// Bounds in fp32 of a token's score in the race, r / -log(u).  The race in fp64 costs two exponentials, a logarithm and a
+// division per token, and only the tokens whose upper bound reaches the highest lower bound found so far can win it: the
+// others are left out (V = 128256: decisions of B = 1 12.5 -> 10.5 us, of B = 16 half of it greedy 24 -> 17, with the loads of the
+// next tokens ahead of the scores and without U copies of the fp64 code, which the first wavefronts have to fetch).
+// Relative error of p = exp2(e) pinv: the argument e is a difference, a product and two rounded factors, 4 2^-24 |e|, times ln 2;
+// the hardware exponential and the two products add 2^-22.  Terms below 2^-126 may have been flushed: 1e-37 absolute, also after
+// the subtraction (pinv <= 1).  -logf(u) and the reciprocal: below 2^-21 together.
+struct Fp32Race {
+  float pmax, qmax, scale, pinv, qinv;
+  __device__ __forceinline__ void bounds(float zp, float zq, bool residual, uint64_t prefix, uint64_t t, float& lo, float& hi) const {
+    const float ep = (zp - pmax) * scale, eq = (zq - qmax) * scale;
+    const float p = __builtin_amdgcn_exp2f(ep) * pinv, q = residual ? __builtin_amdgcn_exp2f(eq) * qinv : 0.f;
+    // (an exponent of -infinity: the probability is 0 and so is its share of the error)
+    float err = p * (fabsf(fmaxf(ep, -150.f)) * 2.5e-7f + 1e-6f) + 2e-37f;
+    if (residual) err += q * (fabsf(fmaxf(eq, -150.f)) * 2.5e-7f + 1e-6f);
+    const float m = (float)(uint32_t)(mix64(prefix + t) >> 41) + 0.5f;              // 24 significant bits: exact
+    const float inv_e = __builtin_amdgcn_rcpf(-logf(m * (1.0f / 8388608.0f)));
+    lo = (p - q - err) * inv_e * (1.0f - 2e-6f);
+    hi = (p - q + err) * inv_e * (1.0f + 2e-6f);
+  }
+};
 
 // (best logit, its token, sum relative to it) over groups of W lanes; every lane returns its group's result
 template <int W>
@@ -402,51 +427,66 @@ __device__ __forceinline__ VerifyPart lanes_merge(VerifyPart v, double inv_t, bo
 __global__ __launch_bounds__(kVerifyBlock) void verify_rows_kernel(const float* __restrict__ zt, const float* __restrict__ zd,
                                                                    const float* __restrict__ temperature, int K, int V,
                                                                    int rows_per_seq, VerifyWs ws) {
-  constexpr int U = 16;   // loads in flight per thread
+  constexpr int U = 8;    // tokens of a thread scored side by side (as many again are on their way)
   __shared__ VerifyPart wave_part[kVerifyWaves];
   __shared__ double table[32];
   const int b = blockIdx.x / rows_per_seq, r = blockIdx.x % rows_per_seq;
   if (r == 0 && blockIdx.y == 0 && threadIdx.x == 0) ws.done[b] = 0;    // for the next kernel
+  const float* z = r <= K ? zt + ((int64_t)b * (K + 1) + r) * V : zd + ((int64_t)b * K + (r - K - 1)) * V;
+  int lo, hi;
+  verify_share(V, lo, hi);
+  const int last = (hi > lo ? hi : V) - 1;
+  float ahead[U];
+  auto load = [&](int t0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) ahead[u] = z[(uint32_t)min(t0 + u * kVerifyBlock, last)];
+  };
+  load(lo + threadIdx.x);                                               // (on its way while the temperature is read)
   const double T = zd ? (double)temperature[b] : 0.0;
   const bool sampled = T > 0.0;
   if (r > K && !sampled) return;                                        // a draft row of a greedy sequence
-  const float* z = r <= K ? zt + ((int64_t)b * (K + 1) + r) * V : zd + ((int64_t)b * K + (r - K - 1)) * V;
   const double inv_t = sampled ? 1.0 / T : 0.0;
   if (sampled) {
     exp_table_init(table);
     __syncthreads();
   }
-  int lo, hi;
-  verify_share(V, lo, hi);
   VerifyPart best = {-INFINITY, 0x7fffffff, 0.0};
   for (int t0 = lo + threadIdx.x; t0 < hi; t0 += kVerifyBlock * U) {
     float v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * kVerifyBlock;
-      v[u] = z[t < hi ? t : t0];
-    }
-    // (a thread's tokens come in rising order: an equal logit later on does not replace the one found first)
+    for (int u = 0; u < U; ++u) v[u] = ahead[u];
+    if (t0 + kVerifyBlock * U < hi) load(t0 + kVerifyBlock * U);
+    // (a thread's tokens come in rising order, past the end its last one again: an equal logit does not replace one found
+    // before it)
     const float before = best.max;
     float top = -INFINITY;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      v[u] = t0 + u * kVerifyBlock < hi ? logit_score(v[u]) : -INFINITY;
+      v[u] = logit_score(v[u]);
       top = fmaxf(top, v[u]);
     }
     if (top > before || best.id == 0x7fffffff) {
       best.max = top;
 #pragma unroll
-      for (int u = U - 1; u >= 0; --u) best.id = v[u] == top && t0 + u * kVerifyBlock < hi ? t0 + u * kVerifyBlock : best.id;
+      for (int u = U - 1; u >= 0; --u) best.id = v[u] == top ? min(t0 + u * kVerifyBlock, last) : best.id;
       if (sampled) best.sum *= exp_rel(before, top, inv_t, table);
     }
     if (sampled) {
+      // Every term is at most 1 and the thread's largest is 1: terms below e^-708, "no probability" (-infinity) among them, are
+      // held at e^-708, which leaves the sum as it is and saves the tests (32 -> 25 instructions a term)
+      const double m = best.max;
       double part[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int u = 0; u < U; ++u) part[u & 3] += exp_rel(v[u], best.max, inv_t, table);
+      for (int u = 0; u < U; ++u) {
+        const float x = t0 + u * kVerifyBlock < hi ? v[u] : -INFINITY;
+        part[u & 3] += exp_core(fmax(((double)x - m) * inv_t, -708.0), table);
+      }
       best.sum += (part[0] + part[1]) + (part[2] + part[3]);
     }
   }
+  // a row without any probability, and one whose maximum is infinite (no distribution)
+  if (best.max == -INFINITY) best.sum = 0.0;
+  if (best.max == INFINITY) best.sum = __longlong_as_double(0x7ff8000000000000ll);
   best = lanes_merge<64>(best, inv_t, sampled, table);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) wave_part[wave] = best;
@@ -468,42 +508,47 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_decide_kernel(const float
                                                                      const float* __restrict__ temperature, int K, int V,
                                                                      uint64_t seed, int rows_per_seq, int row_parts, VerifyWs ws,
                                                                      int32_t* __restrict__ accept_len, int32_t* __restrict__ bonus) {
-  constexpr int U = 8;    // tokens in flight per thread
+  constexpr int U = 4;    // tokens of a thread scored side by side (as many again are on their way)
+  constexpr int H = 2;    // rows of a half wavefront whose partial results are requested at once
   __shared__ double table[32];
   __shared__ VerifyPart row_s[2 * SSD_MAX_K + 1];
   __shared__ int k_s, last_s;
   __shared__ double mass_s[kVerifyWaves];
   __shared__ ScoreId best_s[kVerifyWaves];
   const int b = blockIdx.x, parts = gridDim.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // ---- requested together: the temperature, the drafted tokens, the first rows' partial results (rows of draft logits of a
+  // greedy sequence hold nothing and are not used)
+  int tok = -1;
+  if ((int)threadIdx.x < K) tok = spec[(int64_t)b * K + threadIdx.x];
+  static_assert(kVerifyMaxParts <= 32, "half a wavefront merges a row");
+  VerifyPart v[H];
+  auto load_parts = [&](int r0) {
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+      const int r = r0 + 2 * kVerifyWaves * i;
+      v[i] = {-INFINITY, 0x7fffffff, 0.0};
+      if (r < rows_per_seq && (lane & 31) < row_parts) v[i] = ws.part[((int64_t)b * rows_per_seq + r) * row_parts + (lane & 31)];
+    }
+  };
+  load_parts(2 * wave + (lane >> 5));
   const double T = zd ? (double)temperature[b] : 0.0;
   const bool sampled = T > 0.0;
   if (!sampled && blockIdx.y > 0) return;
   const double inv_t = sampled ? 1.0 / T : 0.0;
-  if (sampled) exp_table_init(table);
   // ---- the drafted tokens' logits, requested ahead of the merge
-  int tok = -1;
   float zt_s = 0.f, zd_s = 0.f;
-  if ((int)threadIdx.x < K) {
-    tok = spec[(int64_t)b * K + threadIdx.x];
-    if (sampled && tok >= 0 && tok < V) {
-      zt_s = zt[((int64_t)b * (K + 1) + threadIdx.x) * V + tok];
-      zd_s = zd[((int64_t)b * K + threadIdx.x) * V + tok];
-    }
+  if (sampled && tok >= 0 && tok < V) {
+    zt_s = zt[((int64_t)b * (K + 1) + threadIdx.x) * V + tok];
+    zd_s = zd[((int64_t)b * K + threadIdx.x) * V + tok];
   }
+  if (sampled) exp_table_init(table);
   // ---- the rows' maxima and denominators: half a wavefront per row, a lane per part, two rows' chains side by side
   const int n_rows = sampled ? 2 * K + 1 : K + 1;
   __syncthreads();
-  static_assert(kVerifyMaxParts <= 32, "half a wavefront merges a row");
-  for (int r0 = 2 * wave + (lane >> 5); r0 < n_rows; r0 += 4 * kVerifyWaves) {
-    VerifyPart v[2];
+  for (int r0 = 2 * wave + (lane >> 5); r0 < n_rows; r0 += 2 * H * kVerifyWaves) {
+    if (r0 >= 2 * H * kVerifyWaves) load_parts(r0);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int r = r0 + 2 * kVerifyWaves * i;
-      v[i] = {-INFINITY, 0x7fffffff, 0.0};
-      if (r < n_rows && (lane & 31) < row_parts) v[i] = ws.part[((int64_t)b * rows_per_seq + r) * row_parts + (lane & 31)];
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < H; ++i) {
       const int r = r0 + 2 * kVerifyWaves * i;
       v[i] = lanes_merge<32>(v[i], inv_t, sampled, table);
       if (r < n_rows && (lane & 31) == 0) row_s[r] = v[i];
@@ -541,30 +586,69 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_decide_kernel(const float
   const uint64_t prefix = draw_prefix(seed, STREAM_BONUS, (uint64_t)b, (uint64_t)k);
   int lo, hi;
   verify_share(V, lo, hi);
+  const Fp32Race race{pmax, qmax, (float)inv_t * 1.44269504f, (float)pinv, (float)qinv};
   ScoreId best;
-  double mass;
+  double mass;     // only its sign is used: above 0 where some token of this part has residual mass
   // once for the residual and, where this part of it has no mass (its candidate counts only if no part has any, and is then
   // p's), once more for p (without qinv, which is no number where the draft's row has no distribution)
   for (bool residual = k < K;; residual = false) {
     best = {-1.0, 0x7fffffff};
     mass = 0.0;
-    for (int t0 = lo + threadIdx.x; t0 < hi; t0 += kVerifyBlock * U) {
-      float vp[U], vq[U];
+    float floor_s = -INFINITY;             // a score that some token of this wavefront is known to reach
+    float ahead_p[U], ahead_q[U];
+    auto load = [&](int t0) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int t = t0 + u * kVerifyBlock;
-        vp[u] = zp[t < hi ? t : t0];
-        vq[u] = zq[t < hi ? t : t0];
+        const uint32_t t = max(min(t0 + u * kVerifyBlock, hi - 1), 0);
+        ahead_p[u] = zp[t];
+        ahead_q[u] = zq[t];
       }
+    };
+    load(lo + threadIdx.x);
+    for (int t0 = lo + threadIdx.x; __any(t0 < hi); t0 += kVerifyBlock * U) {
+      float vp[U], vq[U], most[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int t = t0 + u * kVerifyBlock;
-        double r = residual_of(exp_rel(logit_score(vp[u]), pmax, inv_t, table), pinv,
-                               residual ? exp_rel(logit_score(vq[u]), qmax, inv_t, table) : 0.0, residual ? qinv : 0.0);
-        r = t < hi && r > 0.0 ? r : 0.0;
-        mass += r;
-        const ScoreId c = {t < hi ? r / -log(draw_u(prefix, (uint64_t)t)) : -1.0, t};
-        if (better(c, best)) best = c;
+        vp[u] = ahead_p[u];
+        vq[u] = ahead_q[u];
+      }
+      load(t0 + kVerifyBlock * U);
+      float least = -INFINITY;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        float lo_s;
+        race.bounds(logit_score(vp[u]), logit_score(vq[u]), residual, prefix, (uint64_t)(t0 + u * kVerifyBlock), lo_s, most[u]);
+        const bool in = t0 + u * kVerifyBlock < hi;
+        least = fmaxf(least, in ? lo_s : -INFINITY);
+        most[u] = in ? most[u] : -INFINITY;
+      }
+      for (int o = 32; o > 0; o >>= 1) least = fmaxf(least, __shfl_xor(least, o));
+      floor_s = fmaxf(floor_s, least);
+      // in fp64, the tokens that may win (all of them where none is known to have mass; a bound that is no number excludes
+      // nothing).  A loop over a lane's tokens rather than U copies of its body: most wavefronts take it once, and every
+      // copy would be fetched
+      uint32_t open = 0;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (t0 + u * kVerifyBlock < hi && !(floor_s > 0.f && most[u] < floor_s)) open |= 1u << u;
+      while (__any(open != 0)) {
+        const int u1 = open ? __ffs((int)open) - 1 : 0;
+        float xp = vp[0], xq = vq[0];
+#pragma unroll
+        for (int u = 1; u < U; ++u) {
+          xp = u1 == u ? vp[u] : xp;
+          xq = u1 == u ? vq[u] : xq;
+        }
+        if (open) {
+          const int t = t0 + u1 * kVerifyBlock;
+          double r = residual_of(exp_rel(logit_score(xp), pmax, inv_t, table), pinv,
+                                 residual ? exp_rel(logit_score(xq), qmax, inv_t, table) : 0.0, residual ? qinv : 0.0);
+          r = r > 0.0 ? r : 0.0;
+          mass += r;
+          const ScoreId c = {r / -log(draw_u(prefix, (uint64_t)t)), t};
+          if (better(c, best)) best = c;
+        }
+        open &= open - 1;
       }
     }
     for (int o = 32; o > 0; o >>= 1) {

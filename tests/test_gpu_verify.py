@@ -55,6 +55,35 @@ def test_verify_at_the_edges_of_its_parts(B, V, nb, K):
     assert checked == nb if nb <= 7 else checked >= 0.9 * nb
 
 
+@pytest.mark.parametrize("V", [257, 2050, 40011])
+@pytest.mark.parametrize("T,spread,apart", [(1.0, 3.0, 0.5), (0.02, 3.0, 0.5), (9.0, 40.0, 2.0), (0.7, 90.0, 30.0), (1.0, 3.0, 1e-4), (1.0, 1e-3, 1e-6)])
+def test_verify_bonus_token_of_residuals_that_fp32_can_and_cannot_order(B, V, T, spread, apart):
+    """The race for the bonus token leaves out, by bounds in fp32, the tokens that cannot win.  Peaked and flat distributions,
+    exponents past the fp32 range, and residuals that are differences of almost equal probabilities (`apart`: how far draft and
+    target logits lie apart), where fp32 excludes little or nothing."""
+    nb, K, seed = 6, 2, V + int(100 * T)
+    print(f"[case] verify bonus V={V} T={T} spread={spread} apart={apart}", flush=True)
+    g = np.random.default_rng(seed)
+    zt = (g.standard_normal((nb, K + 1, V)) * spread).astype(np.float32)
+    zd = (zt[:, :K] + apart * g.standard_normal((nb, K, V))).astype(np.float32)
+    spec = np.full((nb, K), -1, np.int32)                     # tokens outside the vocabulary: rejected at position 0
+    k, t = _verify(B, zt, zd, spec, np.full(nb, T, np.float32), seed)
+    checked = 0
+    for b in range(nb):
+        p, q = O.softmax_T(zt[b, 0], T), O.softmax_T(zd[b, 0], T)
+        r = np.maximum(p - q, 0.0)
+        with np.errstate(divide="ignore"):
+            score = np.log(r) + O.gumbel(seed, O.STREAM_BONUS, b, 0, V)
+        order = np.argsort(-score)
+        assert k[b] == 0
+        # (r is off by the rounding of p and q, 1e-14 of them: it moves a score by that over r)
+        best = order[0]
+        if score[best] - score[order[1]] > MARGIN and r[best] > 1e-9 * p[best]:
+            assert t[b] == best, b
+            checked += 1
+    assert checked >= nb // 2
+
+
 def test_verify_residual_without_mass_falls_back_to_the_target(B):
     V, K = 5000, 2
     g = np.random.default_rng(3)
