@@ -151,6 +151,7 @@ struct ssd_ctx {
   int fused_mode = 0;
   bool fused_wide = false;     // rounds and extends run as wide passes (up to kFusedWideRows rows, one launch per phase)
   bool wide_prefill = false;   // prompts are prefilled in wide passes (also in contexts whose rounds are narrow passes)
+  bool small_passes = false;   // extends of at most kFusedMaxRows rows take the persistent narrow pass also where wide passes serve the rest
   int fused_cap = 0;           // rows of one pass of a round: kFusedMaxRows or kFusedWideRows
   int vt_stride = 0;
   FusedParams fp{};            // everything that does not change between passes: of narrow passes,
@@ -479,7 +480,7 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
   // without outputs (a prefill) the pass ends where the last layer's keys and values are stored: its attention phase
   const int last = (logits || hidden) ? fused_last_phase(p.L) : fused_last_phase(p.L) - 5;
   const bool timed = c->timing && branch_depth >= 0 && 2 * branch_depth + 1 < (int)c->kernel_events.size();
-  const bool persistent = !wide && c->fused_mode == 2;
+  const bool persistent = !wide && (c->fused_mode == 2 || c->small_passes);
   std::unique_lock<std::mutex> serial(g_fused_mu, std::defer_lock);
   if (persistent) {
     serial.lock();
@@ -575,6 +576,15 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
   return SSD_OK;
 }
 
+// A pass of few rows in a context that runs wide passes: one persistent launch is shorter than seven launches per layer for as
+// long as it takes the rows (1B shape, 1500 keys, extends of 6, 12, 24 and 48 rows: ... against ... us).  Not into a graph that is
+// being captured: persistent launches take turns by events, which a replay would not see.
+bool takes_small_pass(const ssd_ctx* c, int M, hipStream_t s) {
+  if (!c->small_passes || M > kFusedMaxRows) return false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+}
+
 // Extend of sequences [b0, b0 + nb): tokens [nb][T], outputs [nb][T][..]
 int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset, float* logits, float* hidden, int b0, int nb, hipStream_t s) {
   const Dims& d = c->model->dims;
@@ -582,6 +592,7 @@ int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset,
   SSD_TRY(launch_setup_extend_rows(c->rows, c->cos_sin, c->trunk_len, nb, T, offset, d.head_dim / 2, d.rope_theta, b0, s));
   int ub = 0;
   for (int b = b0; b < b0 + nb; ++b) ub = c->ub_of[b] > ub ? c->ub_of[b] : ub;
+  if (wide && takes_small_pass(c, nb * T, s)) wide = false;
   return forward_rows(c, wide, nb * T, tokens, T, ub + offset, -1, logits, d.vocab, hidden, d.d_model, b0, s);
 }
 
@@ -646,7 +657,8 @@ int fused_setup(ssd_ctx* c) {
   p.vt_stride = c->vt_stride;
   p.suffix_cap = c->K;
   // ---- narrow passes: every exchange buffer once per (layer, phase), written at most once per launch
-  const size_t MPr = c->fused_wide ? 0 : (size_t)kFusedMaxRows;
+  const bool narrow = !c->fused_wide || c->small_passes;
+  const size_t MPr = narrow ? (size_t)kFusedMaxRows : 0;
   const size_t nv = 2 * (size_t)L + 1;
   int st = SSD_OK;
   auto A = [&](void** q, size_t bytes) { if (st == SSD_OK && bytes) st = c->arena.alloc(q, bytes); };
@@ -659,15 +671,18 @@ int fused_setup(ssd_ctx* c) {
   // attention partials (used only when the trunk is split over several units)
   const int r_max = c->rows_per_seq > c->K + 1 ? c->rows_per_seq : c->K + 1;
   const int qt_max = (r_max * p.G + 15) / 16;
-  if (!c->fused_wide) {
+  // query tiles of a pass: whole ones per sequence; passes of rounds, and extends of any shape of up to kFusedMaxRows rows
+  const int64_t small_tiles = c->small_passes ? (int64_t)kFusedMaxRows * p.G / 16 + std::min(c->B, kFusedMaxRows) : 0;
+  const int64_t tiles = std::max<int64_t>(c->fused_wide ? 0 : (int64_t)p.B * qt_max, small_tiles);
+  if (narrow) {
     // narrow passes split short trunks too (their units merge the splits themselves, at no barrier)
     c->part.ns_max = std::max((c->max_trunk + 2047) / 2048 + 1, 8);
-    c->part.entries = (int64_t)p.B * p.Hkv * c->part.ns_max * qt_max * 16;
+    c->part.entries = p.Hkv * c->part.ns_max * tiles * 16;
     p.part_layer_stride = c->part.entries;
     A((void**)&p.part_o, (size_t)L * c->part.entries * 64 * 4);
     A((void**)&p.part_ml, (size_t)L * c->part.entries * 2 * 4);
   }
-  p.arrivals_stride = (int64_t)p.B * p.Hkv * qt_max;
+  p.arrivals_stride = std::max<int64_t>(tiles, 1) * p.Hkv;
   A((void**)&p.arrivals, (size_t)L * p.arrivals_stride * 4);
   A((void**)&p.qkv_flags, (size_t)L * 128 * 4);
   // K-split scratch: per (layer, qkv / o / down) partial tiles.  A word of 0xffffffff means "not written in this
@@ -686,7 +701,7 @@ int fused_setup(ssd_ctx* c) {
   // every workgroup of a persistent launch has to be resident at once
   // xn, att, act as one fp16 plane unless two planes are asked for; q, p as asked
   p.planes = ((c->flags >> 8) & 31) | (c->flags & SSD_CTX_TWO_PLANES ? 0 : 7);
-  if (!c->fused_wide && !fused_planes_supported(p.planes)) { set_error("fused pass: plane configuration %d is not compiled in", p.planes); return SSD_EINVAL; }
+  if (narrow && !fused_planes_supported(p.planes)) { set_error("fused pass: plane configuration %d is not compiled in", p.planes); return SSD_EINVAL; }
   if (c->fused_mode == 2) SSD_TRY(fused_check_residency(p.nwg, p.planes, c->kv_pages ? 1 : 0));
   {
     void* host_word = nullptr;
@@ -708,7 +723,7 @@ int fused_setup(ssd_ctx* c) {
   p.qkv_ug = 0;
   {
     const int ug = 2 * p.G + 4;
-    bool fits = c->fused_mode == 2 && !c->fused_wide && p.Hkv <= 8 && 8 % p.Hkv == 0 && ug <= 16 && 8 * ug <= p.nwg;
+    bool fits = (c->fused_mode == 2 || c->small_passes) && p.Hkv <= 8 && 8 % p.Hkv == 0 && ug <= 16 && 8 * ug <= p.nwg;
     for (int l = 0; l < L && fits; ++l)
       fits = m->fused_layers[l].qkv.KS == 1 && m->fused_layers[l].qkv.n_units == 2 * p.Hq + 4 * p.Hkv;
     if (fits) p.qkv_ug = ug;
@@ -926,6 +941,10 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
     c->wide_prefill = c->fused_mode != 0 && model->wide_ok && attn_ok &&
                       !(cfg->flags & (SSD_CTX_NARROW_PASSES | SSD_CTX_TWO_PLANES | SSD_CTX_ONE_PLANE_ALL));
     if (c->wide_prefill) c->max_rows = std::max(c->max_rows, kFusedWideRows);
+    // (a context whose workgroups could not all be resident keeps the wide passes)
+    int grid = 0;
+    c->small_passes = c->wide_prefill && model->fused_ok && !(cfg->flags & SSD_CTX_FUSED_PHASES) && fused_grid_size(&grid) == SSD_OK &&
+                      (c->fused_mode == 2 || fused_check_residency(grid, 7, cfg->kv_pages ? 1 : 0) == SSD_OK);
   }
   const int R = c->max_rows;
   if (!c->fused_mode) {
