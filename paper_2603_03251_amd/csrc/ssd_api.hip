@@ -577,8 +577,9 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
 }
 
 // A pass of few rows in a context that runs wide passes: one persistent launch is shorter than seven launches per layer for as
-// long as it takes the rows (1B shape, 1500 keys, extends of 6, 12, 24 and 48 rows: ... against ... us).  Not into a graph that is
-// being captured: persistent launches take turns by events, which a replay would not see.
+// long as it takes the rows (1B shape, one extend with logits over 1500 keys: 12 rows 0.89 against 1.14 ms, 24 rows 0.91 against
+// 1.17; 48 rows, which four and six row tiles of that kernel would extend: 54 rows 6 % shorter than a wide pass, 72 and 96 rows 10 %
+// longer).  Not into a graph that is being captured: persistent launches take turns by events, which a replay would not see.
 bool takes_small_pass(const ssd_ctx* c, int M, hipStream_t s) {
   if (!c->small_passes || M > kFusedMaxRows) return false;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -941,9 +942,11 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
     c->wide_prefill = c->fused_mode != 0 && model->wide_ok && attn_ok &&
                       !(cfg->flags & (SSD_CTX_NARROW_PASSES | SSD_CTX_TWO_PLANES | SSD_CTX_ONE_PLANE_ALL));
     if (c->wide_prefill) c->max_rows = std::max(c->max_rows, kFusedWideRows);
-    // (a context whose workgroups could not all be resident keeps the wide passes)
+    // Few-row extends on the persistent pass: from a width of 1024 on (16 to 48 rows, 100 and 4000 keys: width 1024, 8 layers,
+    // 283..463 us against 327..498 as wide passes; width 512, 4 layers, 142..189 against 131..192).  A context whose workgroups
+    // could not all be resident keeps the wide passes.
     int grid = 0;
-    c->small_passes = c->wide_prefill && model->fused_ok && !(cfg->flags & SSD_CTX_FUSED_PHASES) && fused_grid_size(&grid) == SSD_OK &&
+    c->small_passes = c->wide_prefill && d.d_model >= 1024 && !(cfg->flags & SSD_CTX_FUSED_PHASES) && fused_grid_size(&grid) == SSD_OK &&
                       (c->fused_mode == 2 || fused_check_residency(grid, 7, cfg->kv_pages ? 1 : 0) == SSD_OK);
   }
   const int R = c->max_rows;

@@ -219,3 +219,41 @@ def test_wide_rounds_over_long_trunks(B, lens, pages):
         e = row_rel_err(a, b)
         print(f"[wide] {name} {e:.2e}", flush=True)
         assert e < 2 * TOL_WIDE_BF16
+
+
+@pytest.mark.parametrize("nb,T", [(16, 1), (16, 3), (12, 4), (13, 4)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_extends_of_few_rows_in_a_context_of_wide_passes(B, nb, T, paged):
+    """Up to 48 rows such a context takes the persistent pass of the narrow contexts: the same bits, also between rounds of wide
+    passes; beyond (13 x 4 rows) it stays with wide passes."""
+    print(f"[case] {nb} sequences, extend of {T} tokens, paged {paged}", flush=True)
+    P, seed = 75, 5 + nb
+    pages = 1 + nb * 4 if paged else 0
+    SHAPE = I.ModelShape(n_layers=2, d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=64, d_ffn=2048, vocab=4112, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)     # (narrower models keep the wide passes)
+    model = B.ssd_model_create(SHAPE, I.make_weights(SHAPE, 3))
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, P + 4 * K + 8, flags, pages) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
+    try:
+        assert [B.ssd_ctx_views(c).pass_rows for c in ctxs] == [384, 48]
+        g = np.random.default_rng(seed)
+        tokens = dev_i32(g.integers(0, SHAPE.vocab, (nb, T)))
+        pending, temps = dev_i32(I.make_pending(SHAPE, nb, K, seed)), dev_f32(np.zeros(nb))
+        got = []
+        for ctx in ctxs:
+            z = [torch.zeros((nb, T, SHAPE.vocab), dtype=torch.float32, device="cuda") for _ in range(2)]
+            B.ssd_ctx_fill_synthetic_kv(ctx, [P - b for b in range(nb)], seed)
+            B.ssd_ctx_extend(ctx, tokens, 0, z[0])
+            B.ssd_prespeculate(ctx, pending, temps, 1)
+            B.ssd_ctx_extend(ctx, tokens, 0, z[1])
+            torch.cuda.synchronize()
+            B.ssd_ctx_status(ctx)
+            got.append([x.cpu().numpy() for x in z])
+        assert np.array_equal(got[0][0], got[0][1])
+        if nb * T <= 48:
+            assert np.array_equal(got[0][0], got[1][0])
+        else:
+            assert row_rel_err(got[0][0], got[1][0]) < 2 * TOL_WIDE_BF16
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
