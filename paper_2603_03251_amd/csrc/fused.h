@@ -14,6 +14,8 @@ constexpr int kFusedThreads = 512;  // 8 wavefronts; they split the reduction di
 constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxRows = 48;   // rows of one narrow pass (three 16-row MFMA tiles)
 constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles): contexts with more than kFusedMaxRows rows, and prompts
+constexpr int kFusedPromptRows = 1024;     // rows of a pass that only fills the trunk (prompts): eight row groups of
+constexpr int kFusedPromptRowGroup = 128;  // this many rows
 constexpr int kFusedWideQueryTiles = 3;   // wide passes: most query tiles per attention unit
 constexpr int kFusedWideFreshKeys = 192;  // wide passes: keys of the pass itself an attention unit has LDS room for
 // Wide extends of more tokens of a sequence append their keys before the attention.  4 layers of the 1B shape, one prompt, us per
@@ -74,6 +76,7 @@ struct FusedParams {
   int SL;                                  // fresh-key slots per branch row (8 or 16)
   int is_branch;                           // 1: branch rows (private suffix), 0: extend rows (causal among themselves)
   int suffix_len;                          // branch rows: private positions a row sees, its own token included
+  int row_tiles;                           // wide passes: 16-row tiles an operand plane has room for (24; prompt passes 64)
   int appended;                            // wide extends: 1 = the pass's keys are in the trunk before its attention runs
   int tv_ub;                               // host bound of the stored trunk keys any row sees (loop counts only)
   int n_attn_units, n_pair_units;          // B Hkv QT NS attention units; ceil(M Hq / 8) merge units (wide passes)

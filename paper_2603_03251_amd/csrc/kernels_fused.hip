@@ -157,9 +157,12 @@ __device__ __forceinline__ void stamp(const FusedParams& p, int ph, int which) {
 
 // Offset of element (row m, input k) in a B-operand-ordered activation plane with MT row tiles:
 // [k / 32][m / 16][lane = m % 16 + 16 ((k % 32) / 8)][k % 8].
+__device__ __forceinline__ int64_t b_off_of(int mt, int k, int m) {
+  return ((int64_t)((k >> 5) * mt + (m >> 4)) * 64 + (m & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
 template <int MT>
 __device__ __forceinline__ int64_t b_off(int k, int m) {
-  return ((int64_t)((k >> 5) * MT + (m >> 4)) * 64 + (m & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+  return b_off_of(MT, k, m);
 }
 
 union Bf8 {
@@ -1097,8 +1100,8 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
 
 // Merge unit (only when the trunk is split over several units): one wavefront per (row, query head), lane = head
 // dimension, merges the NS partial softmaxes and writes the attention output planes.
-template <int MT, int MP, int NPT>
-__device__ __forceinline__ void attn_merge_unit(const FusedParams& p, int unit, const float* part_o, const float* part_ml,
+template <int MP, int NPT>
+__device__ __forceinline__ void attn_merge_unit(const FusedParams& p, int mt, int unit, const float* part_o, const float* part_ml,
                                                 bf16_t* att_out) {
   const int d = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int pair = unit * kFusedWaves + wave;
@@ -1128,7 +1131,7 @@ __device__ __forceinline__ void attn_merge_unit(const FusedParams& p, int unit, 
   uint32_t w1 = __shfl_down(w, 1), w2 = __shfl_down(w, 2), w3 = __shfl_down(w, 3);
   if ((d & 3) == 0) {
     const int k = hq * 64 + d;
-    const int64_t off = b_off<MT>(k, m);
+    const int64_t off = b_off_of(mt, k, m);
     st_u64(att_out + off, pack_bf16x4((bf16_t)w, (bf16_t)w1, (bf16_t)w2, (bf16_t)w3));
     if (NPT == 2)
       st_u64(att_out + (int64_t)MP * p.qd + off,
@@ -1471,7 +1474,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
       x.u[i] = to_f16(xg);
       n[i >> 2][i & 3] = xg * rs;
     }
-    *(gbf16x8*)((gbf16*)p.xn + b_off<kWideTiles>(c, m)) = x.v;
+    *(gbf16x8*)((gbf16*)p.xn + b_off_of(p.row_tiles, c, m)) = x.v;
     if (hidden) {
       *(gf32x4*)((gfloat*)hidden + (int64_t)m * p.hidden_ld + c) = n[0];
       *(gf32x4*)((gfloat*)hidden + (int64_t)m * p.hidden_ld + c + 4) = n[1];
@@ -1687,6 +1690,197 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams
   stamp(p, e.ph, 2);
 }
 
+// Every linear layer of a prompt pass (more than kFusedWideRows rows; no logits).  With so many rows the layers are contractions:
+// what bounds them is the matrix cores (32x32x16 on data that are not constant: 1.4 PFLOP/s, one wavefront per SIMD) and the
+// operands a compute unit pulls (about 100 GB/s), which must run side by side.  A workgroup = 4 wavefronts x (NF x 32 features) x
+// 128 rows: per k-tile it pulls 8 NF KiB of weights straight into registers (a ring of 8 k-tiles) and 8 KiB of activations,
+// which all four wavefronts read from LDS (stages of 4 k-tiles, double buffered, requested two stages ahead), for 8 NF MFMAs of each
+// wavefront.  What the kernel for 96 rows does not have: every LDS read, load and LDS write sits between two MFMAs
+// (sched_barrier), where a burst of them blocks the one wavefront of a SIMD until the memory pipeline has taken it in.  1024 rows
+// of the 1B shape, gate/up: 66 us (three passes of 340 rows: 3 x 35); tiles of 128 features x 192 rows measured 74 for 768 rows, of
+// 256 x 192 spill.
+// Tiles of 32 features: NF = 2: two per wavefront; ATW = 2 (qkv, o, down): the tile groups of the layout; ATW = 4 (gate/up): gate
+// tiles and up tiles of the wavefront's unit.  PART: S slices of the reduction dimension, XCD x on slice x % S, as in
+// wide_gemm_kernel.
+constexpr int kTileRows = kFusedPromptRowGroup, kTileStage = 4, kTileRing = 8;
+template <int ATW, int EPI, int NF>
+__global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
+  constexpr int RT = kTileRows / 16, KC = kTileStage, R32 = RT / 2;
+  constexpr int STAGE = KC * RT * 64, BL = STAGE / kWideThreads, BJ = BL / KC, NM = NF * R32;
+  static_assert(ATW == 2 || NF == 2, "a wavefront owns whole units of 4 feature tiles");
+  static_assert(kTileRing == 2 * KC && 2 * BJ <= NM && NF + 1 < NM, "a turn of the ring is two stages; memory operations between MFMAs");
+  extern __shared__ f32x4 lds[];                     // [2][KC][RT][64] B-operand vectors
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int NKT = g.KS * kFusedWaves * g.KTW;        // k-tiles of the reduction dimension
+  const int S = EPI == FE_PART ? e.S : 1;
+  const int NST = NKT / (KC * S);                    // stages per pair (even: host check)
+  const int n_groups = g.n_units / g.KS;             // units of ATW feature tiles
+  constexpr int SG = 4 * NF * 2 / ATW;               // ... of a set
+  const int n_sets = (n_groups + SG - 1) / SG;
+  const int n_rg = (p.M + kTileRows - 1) / kTileRows;
+  const int x = (int)blockIdx.x & 7, wx = (int)blockIdx.x >> 3, per_xcd = (int)gridDim.x >> 3;
+  const int slice = x % S, y = x / S, ys = 8 / S;    // S is 1, 2, 4 or 8
+  const int nqy = y < n_sets ? (n_sets - y + ys - 1) / ys : 0;
+  const int ty = nqy * n_rg;
+  const int n_my = wx < ty ? (ty - wx + per_xcd - 1) / per_xcd : 0;
+  stamp(p, e.ph, 0);
+  if (n_my == 0) return;
+
+  const int lpos = (lane & 15) + ((lane >> 5) << 4), ltile = (lane >> 4) & 1;
+  const int lsrc = ltile * 64 + lpos;                // operand vector of this lane in two neighbouring tiles, k-half 0
+  const int64_t fstep = ATW == 4 ? 128 : (int64_t)NKT * 128;   // vectors from a wavefront's first 32 features to its second
+  f32x16 acc[NF][R32];
+  auto zero_acc = [&]() {
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+      for (int t = 0; t < R32; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[f][t][i] = 0.f;
+  };
+  zero_acc();
+  auto pair_of = [&](int n, int& set, int& rg) {
+    const int t = wx + (n < n_my ? n : n_my - 1) * per_xcd;
+    const int qh = t / n_rg;
+    set = qh * ys + y;
+    rg = t - qh * n_rg;
+  };
+  // this wavefront's first unit of set `set` (past the last: the last units again, computed and never stored)
+  auto group_of = [&](int set) { return min((set * 4 + wave) * (NF * 2 / ATW), n_groups - NF * 2 / ATW); };
+  int b_rel[BL];
+#pragma unroll
+  for (int i = 0; i < BL; ++i) {
+    const int v = (int)threadIdx.x + kWideThreads * i;
+    const int kt = v / (RT * 64);
+    b_rel[i] = (kt * p.row_tiles * 64 + v - kt * (RT * 64)) * 8;
+  }
+  struct Cursor { int n, s; const bf16_t* q; };      // pair ordinal, stage; operand address of that stage
+  auto place_a = [&](Cursor& c) {
+    int set, rg;
+    pair_of(c.n, set, rg);
+    c.q = g.w + ((int64_t)group_of(set) * NKT + (slice * NST + c.s) * KC) * (ATW * 512);
+  };
+  auto place_b = [&](Cursor& c) {
+    int set, rg;
+    pair_of(c.n, set, rg);
+    c.q = bsrc + ((int64_t)((slice * NST + c.s) * KC) * p.row_tiles + rg * RT) * 512;
+  };
+  auto step = [&](Cursor& c) { if (++c.s == NST) { c.s = 0; ++c.n; } };
+  bf16x8 ring[kTileRing][2 * NF], breg[2][BL], bt[2][R32];
+  Cursor ca{0, 0, nullptr}, cb{0, 0, nullptr};
+  place_b(cb);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {                      // stages 0 and 1
+#pragma unroll
+    for (int i = 0; i < BL; ++i) breg[u][i] = *(const gbf16x8*)(cb.q + b_rel[i]);
+    step(cb);
+    place_b(cb);
+  }
+  place_a(ca);
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+#pragma unroll
+    for (int j = 0; j < KC; ++j) {
+      __builtin_amdgcn_sched_barrier(0);             // (requested in the order in which the loop refills them)
+      const gbf16x8* ap = (const gbf16x8*)(ca.q + j * (ATW * 512)) + lsrc;
+#pragma unroll
+      for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) ring[u * KC + j][2 * f + h] = ap[f * fstep + h * 32];
+    }
+    step(ca);
+    place_a(ca);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < BL; ++i) *(bf16x8*)&lds[(int)threadIdx.x + kWideThreads * i] = breg[0][i];
+  wg_barrier();
+  stamp(p, e.ph, 3);
+
+  for (int n = 0; n < n_my; ++n) {
+    int set, rg;
+    pair_of(n, set, rg);
+    float rs[R32];                                   // the rows' 1/rms
+#pragma unroll
+    for (int t = 0; t < R32; ++t)
+      rs[t] = EPI == FE_PART ? 1.0f : ((const gfloat*)p.ssq)[min((rg * RT + 2 * t) * 16 + (lane & 31), p.M - 1)];
+    for (int st = 0; st < NST; st += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        // stage st + u is in LDS (buffer u), the one after it in breg[u ^ 1]; the loads of this turn are for two stages on
+        const bf16x8* bs = (const bf16x8*)&lds[u * STAGE] + lsrc;
+#pragma unroll
+        for (int t = 0; t < R32; ++t) bt[0][t] = bs[t * 128];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < KC; ++j) {
+          const gbf16x8* ap = (const gbf16x8*)(ca.q + j * (ATW * 512)) + lsrc;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int nx = 2 * j + h + 1;            // the k-half to come
+#pragma unroll
+            for (int i = 0; i < NM; ++i) {
+              const int f = i / R32, t = i % R32;
+              acc[f][t] = mfma32_f16(ring[u * KC + j][2 * f + h], bt[h][t], acc[f][t]);
+              // between two MFMAs: an LDS read of the coming half and one of the k-tile's other memory operations
+              if (nx < 2 * KC && i < R32) bt[nx & 1][i] = bs[(nx >> 1) * (RT * 64) + i * 128 + (nx & 1) * 32];
+              if (h == 0 && (i & 1) == 0 && i / 2 < BJ) breg[u][j * BJ + i / 2] = *(const gbf16x8*)(cb.q + b_rel[j * BJ + i / 2]);
+              if (h == 0 && (i & 1) == 1 && i / 2 < BJ)
+                *(bf16x8*)&lds[(u ^ 1) * STAGE + (int)threadIdx.x + kWideThreads * (j * BJ + i / 2)] = breg[u ^ 1][j * BJ + i / 2];
+              if (h == 1 && i >= 1 && i - 1 < NF) ring[u * KC + j][2 * (i - 1)] = ap[(i - 1) * fstep];
+              if (h == 1 && i + 1 == NM) {
+#pragma unroll
+                for (int ff = 0; ff < NF; ++ff) ring[u * KC + j][2 * ff + 1] = ap[ff * fstep + 32];
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
+        }
+        step(ca);
+        place_a(ca);
+        step(cb);
+        place_b(cb);
+        wg_barrier();
+      }
+    }
+    if (n == 0) stamp(p, e.ph, 4);
+    // ---- epilogue from the accumulators.  Registers 4 q .. 4 q + 3 of a 32x32 tile: features 8 q + 4 (lane >> 5) .. + 3, row lane & 31
+    const int f4 = (lane >> 5) * 4;
+    const int first = (set * 4 + wave) * (NF * 2 / ATW);             // this wavefront's first unit
+    if (first < n_groups) {
+#pragma unroll
+      for (int t = 0; t < R32; ++t) {
+        const int m = (rg * RT + 2 * t) * 16 + (lane & 31);
+        if (m < p.M) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if constexpr (EPI == FE_SWIGLU) {
+              bf16_t hi[4];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const float gg = acc[0][t][4 * q + i] * rs[t], uu = acc[1][t][4 * q + i] * rs[t];
+                hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
+              }
+              st_u64_uncounted(e.act_out + b_off_of(p.row_tiles, first * 32 + 8 * q + f4, m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
+            } else {
+              float* out = e.out + (EPI == FE_PART ? (int64_t)slice * p.M * e.ld : 0) + (int64_t)m * e.ld;
+#pragma unroll
+              for (int f = 0; f < NF; ++f) {
+                const int n0 = (first + f) * 32 + 8 * q + f4;
+                const f32x4 v = (f32x4){acc[f][t][4 * q], acc[f][t][4 * q + 1], acc[f][t][4 * q + 2], acc[f][t][4 * q + 3]};
+                if ((n0 >> 4) < g.NT) st_f32x4_uncounted(out + n0, EPI == FE_PART ? v : v * rs[t]);
+              }
+            }
+          }
+        }
+      }
+    }
+    zero_acc();
+    if (n == 0) stamp(p, e.ph, 5);
+  }
+  stamp(p, e.ph, 2);
+}
+
 // The attention unit of the wide passes, a workgroup: NQ query tiles of one (sequence, KV head, key split) share every
 // stored key and value block the unit pulls (a wide pass has 6 and more query tiles per sequence and head: units of one
 // tile would pull the same trunk once per tile).  Same method and same layouts as attn_unit; the qkv projections
@@ -1715,7 +1909,6 @@ static_assert(kMultiFreshBytes % 16 == 0 && kMultiLdsBytes <= 160 * 1024, "LDS o
 template <int NPQ, int NPP, int NQ, bool PG>
 __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p, bf16_t* trunk_k, bf16_t* trunk_vt, bf16_t* suffix_k,
                                                                   bf16_t* suffix_v, int ph) {
-  constexpr int MT = kWideTiles;
   extern __shared__ f32x4 lds[];
   bf16_t* kf_s = (bf16_t*)lds;
   bf16_t* vf_s = kf_s + kMultiFreshKeys * 72;
@@ -2096,7 +2289,7 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
       bf16_t hi[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) hi[e] = to_f16(o[e] * inv);
-      *(uint64_t*)(p.att + b_off<MT>(k, mm)) = pack_bf16x4(hi[0], hi[1], hi[2], hi[3]);
+      *(uint64_t*)(p.att + b_off_of(p.row_tiles, k, mm)) = pack_bf16x4(hi[0], hi[1], hi[2], hi[3]);
     } else {
       const int64_t pb = ((int64_t)(b * p.Hkv + hk) * p.NS + s) * (p.QT * 16) + qrow;
       if (dq == 0) *(uint64_t*)(p.part_ml + pb * 2) = pack_f32x2(mmax, lsum);
@@ -2140,7 +2333,7 @@ __global__ __launch_bounds__(256) void wide_append_kernel(FusedParams p, bf16_t*
 // Merge of a wide pass's key splits.
 __global__ __launch_bounds__(kFusedThreads) void wide_merge_kernel(FusedParams p, int ph) {
   stamp(p, ph, 0);
-  attn_merge_unit<kWideTiles, kFusedWideRows, 1>(p, blockIdx.x, p.part_o, p.part_ml, p.att);
+  attn_merge_unit<kFusedWideRows, 1>(p, p.row_tiles, blockIdx.x, p.part_o, p.part_ml, p.att);
   stamp(p, ph, 2);
 }
 
@@ -2304,7 +2497,7 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedParams p, int
       float* part_ml = p.part_ml + (int64_t)l * p.part_layer_stride * 2;
       if (do_wait && !grid_wait(grid)) return;
       stamp(p, ph, 1);
-      for (int u = blockIdx.x; u < p.n_pair_units; u += p.nwg) attn_merge_unit<MT, MP, PL::att>(p, u, part_o, part_ml, att);
+      for (int u = blockIdx.x; u < p.n_pair_units; u += p.nwg) attn_merge_unit<MP, PL::att>(p, MT, u, part_o, part_ml, att);
     }
     stamp(p, ph, 2);
     if (ph < last && !(gs && sub == 0)) grid_arrive(grid);
@@ -2553,9 +2746,22 @@ int launch_wide_gemm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
   return launch_wide_gemm_dm<ATW, EPI, kWideRing / 2, MTG>(p, g, bsrc, e, s);
 }
 
+template <int ATW, int EPI, int NF>
+int launch_wide_tile(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
+  constexpr int kLds = 2 * kTileStage * (kTileRows / 16) * 1024;
+  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_tile_kernel<ATW, EPI, NF>,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  SSD_HIP(configured);
+  SSD_CHECK_ARG(wide_k_tiles(g) % (kTileRing * e.S) == 0 && (g.n_units / g.KS) * ATW % (2 * NF) == 0, "prompt pass: layer does not cut into tiles");
+  wide_tile_kernel<ATW, EPI, NF><<<p.nwg, kWideThreads, kLds, s>>>(p, g, bsrc, e);
+  SSD_HIP(hipGetLastError());
+  return SSD_OK;
+}
+
 // qkv: row groups as small as still give every pair a workgroup of its own (with few rows the full-size groups leave most
 // of the grid without a pair while the busy workgroups pull as much as ever).
 int launch_wide_qkv(const FusedParams& p, const FusedGemm& g, const WideEpi& e, hipStream_t s) {
+  if (p.M > kFusedWideRows) return launch_wide_tile<2, FE_QKV, 1>(p, g, p.xn, e, s);
   const int nq = (g.n_units / g.KS) >> 1, tiles = (p.M + 15) >> 4;
   auto fits = [&](int mtg) { return nq * ((tiles + mtg - 1) / mtg) <= p.nwg; };
   if (fits(1)) return launch_wide_gemm<2, FE_QKV, 1>(p, g, p.xn, e, s);
@@ -2569,12 +2775,19 @@ int launch_wide_qkv(const FusedParams& p, const FusedGemm& g, const WideEpi& e, 
 // 262, 255, 255; 96 rows 290, 275, 287; 128 rows 294, 297, 286; 160 rows 301, 302, 326; 192 rows 315, 316, 338 (runs of one
 // side differ by up to 5 % below 100 rows).
 int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
+  if (p.M > kFusedWideRows) {
+    const int pairs = (g.n_units / g.KS + 7) / 8 * ((p.M + kTileRows - 1) / kTileRows);
+    e.S = 1;
+    for (int S = kFusedWideSlices; S > 1; S >>= 1)
+      if (pairs * S <= p.nwg && (int64_t)S * p.M <= p.fix_stride && wide_k_tiles(g) % (kTileRing * S) == 0) { e.S = S; break; }
+    return launch_wide_tile<2, FE_PART, 2>(p, g, bsrc, e, s);
+  }
   const int nq = (g.n_units / g.KS) >> 1, tiles = (p.M + 15) >> 4;
   const int mtg = tiles >= 4 ? kWideGroup : tiles;
   const int n_rg = (tiles + mtg - 1) / mtg;
   e.S = 1;
   for (int S = kFusedWideSlices; S > 1; S >>= 1)
-    if (nq * n_rg * S <= p.nwg && (int64_t)S * p.M <= p.fix_stride && wide_k_tiles(g) % (kWideWaves * S * (kWideRing / 2)) == 0) { e.S = S; break; }
+    if (nq * n_rg * S <= p.nwg && S * p.M <= kFusedWideSlices * kFusedWideRowGroup && wide_k_tiles(g) % (kWideWaves * S * (kWideRing / 2)) == 0) { e.S = S; break; }
   switch (mtg) {
     case 1: return launch_wide_gemm<2, FE_PART, 1>(p, g, bsrc, e, s);
     case 2: return launch_wide_gemm<2, FE_PART, 2>(p, g, bsrc, e, s);
@@ -2590,6 +2803,7 @@ int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
 // and 311, 192 rows 315 and 323).  With more rows 16 feature tiles per workgroup fill the
 // grid and pull less.
 int launch_wide_gate_up(const FusedParams& p, const FusedGemm& g, const WideEpi& e, hipStream_t s) {
+  if (p.M > kFusedWideRows) return launch_wide_tile<4, FE_SWIGLU, 2>(p, g, p.xn, e, s);
   const int tiles = (p.M + 15) >> 4;
   if (g.n_units <= p.nwg && tiles <= 2 * kWideGroup) {
     if (tiles <= 2) return launch_wide_gemm<4, FE_SWIGLU, 2>(p, g, p.xn, e, s);
@@ -2716,7 +2930,9 @@ int fused_check_residency(int nwg, int planes, int paged) {
 // 16 layers, measured); the attention unit's queries and probabilities keep two bf16 planes unless both of their bits
 // are set in p.planes.
 int launch_fused_wide(const FusedParams& p, const FusedLayer* layers_host, int first, int last, hipStream_t s) {
-  SSD_CHECK_ARG(p.M >= 1 && p.M <= kFusedWideRows, "wide fused pass of %d rows (1..%d supported)", p.M, kFusedWideRows);
+  const int max_rows = p.is_branch || p.logits || p.hidden ? kFusedWideRows : kFusedPromptRows;
+  SSD_CHECK_ARG(p.M >= 1 && p.M <= max_rows, "wide fused pass of %d rows (1..%d supported)", p.M, max_rows);
+  SSD_CHECK_ARG(p.row_tiles == (p.M > kFusedWideRows ? kFusedPromptRows : kFusedWideRows) / 16, "row tiles %d of an operand plane", p.row_tiles);
   SSD_CHECK_ARG(p.nwg >= 8 && p.nwg % 8 == 0, "fused grid of %d workgroups must be a multiple of 8", p.nwg);
   SSD_CHECK_ARG(p.KPU >= 32 && p.KPU % 32 == 0 && p.NS >= 1 && p.QT >= 1 && (p.SL == 8 || p.SL == 16) && 16 % p.G == 0 &&
                     (16 / p.G) * p.SL <= 64,

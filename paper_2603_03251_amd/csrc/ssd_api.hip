@@ -432,7 +432,9 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
                   int64_t logits_ld, float* hidden, int64_t hidden_ld, int seq_base, hipStream_t s) {
   FusedParams p = wide ? c->fpw : c->fp;
   const ssd_ctx::PartCap& part = wide ? c->part_wide : c->part;
-  const int cap = wide ? kFusedWideRows : kFusedMaxRows;
+  // passes that only fill the trunk (prompts) may be larger than those of a round
+  const bool fills = c->wide_prefill && !logits && !hidden && branch_depth < 0;
+  const int cap = wide ? (fills ? kFusedPromptRows : kFusedWideRows) : kFusedMaxRows;
   p.R = rows_per_seq;
   p.is_branch = branch_depth >= 0;
   p.suffix_len = branch_depth >= 0 ? branch_depth + 1 : 0;
@@ -492,6 +494,7 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
     const int64_t row0 = (int64_t)s0 * rows_per_seq;
     p.B = nb;
     p.M = nb * rows_per_seq;
+    p.row_tiles = (p.M > kFusedWideRows ? kFusedPromptRows : kFusedWideRows) / 16;
     p.layers = c->fused_layers_dev + (size_t)(seq_base + s0) * p.L;
     p.pages = c->kv_pages ? c->page_table_dev + (size_t)(seq_base + s0) * c->page_stride : nullptr;
     p.page_stride = c->page_stride;
@@ -613,18 +616,16 @@ int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t*
       // a group: the next sequences that fit one pass with the whole chunk of each
       T = 0;
       for (gn = 0; g0 + gn < nb; ++gn) {
-        const int want = std::max(T, std::min<int>(lens[g0 + gn], kFusedWideRows));
-        if (gn > 0 && want * (gn + 1) > kFusedWideRows) break;
+        const int want = std::max(T, std::min<int>(lens[g0 + gn], kFusedPromptRows));
+        if (gn > 0 && want * (gn + 1) > kFusedPromptRows) break;
         T = want;
       }
     }
     for (int b = g0; b < g0 + gn; ++b) max_len = std::max<int>(max_len, lens[b]);
     const bool wide = c->wide_prefill && (c->fused_wide || max_len > K1);
     if (wide) {
-      // of equal size.  (4 layers of the 1B shape, against full passes and a short last one: 1020 tokens 1.24 and 1.22 ms, 700
-      // both 0.83, 1152 both 1.26; but 400, 600 and 900 tokens 5 to 8 % longer, whose parts fill their groups of 96 rows worse)
-      const int chunks = (max_len + T - 1) / T;
-      T = (max_len + chunks - 1) / chunks;
+      // full passes and a shorter last one
+      T = std::min(max_len, kFusedPromptRows);
     } else {
       T = K1;
     }
@@ -763,14 +764,15 @@ int fused_setup(ssd_ctx* c) {
   if (c->fused_wide || c->wide_prefill) {
     FusedParams& w = c->fpw;
     w = p;
-    const size_t MW = (size_t)kFusedWideRows;
+    const size_t MW = c->wide_prefill ? (size_t)kFusedPromptRows : (size_t)kFusedWideRows;
     // query rows of a pass: whole 16-row tiles per sequence
     c->part_wide.ns_max = (c->max_trunk + 2047) / 2048 + 1;
-    c->part_wide.entries = (int64_t)p.Hkv * c->part_wide.ns_max * (kFusedWideRows * p.G + 16 * std::min(c->B, kFusedWideRows));
+    c->part_wide.entries = (int64_t)p.Hkv * c->part_wide.ns_max * ((int64_t)MW * p.G + 16 * std::min(c->B, (int)MW));
     // partial sums of o and down: eight slices of a row group of 96, two of 384 rows (which is what gives every pair of 64
     // features x 96 rows a workgroup at the 1B shape).  They lie where the qkv projections were: written after the
     // attention has read those, read before the next layer's are written
-    w.fix_stride = kFusedWideSlices * kFusedWideRowGroup;
+    // (prompt passes: four slices of 1024 rows, eight of 512)
+    w.fix_stride = c->wide_prefill ? 4 * kFusedPromptRows : kFusedWideSlices * kFusedWideRowGroup;
     // one allocation, carved up
     char* base = nullptr;
     size_t used = 0;
@@ -941,7 +943,7 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
     // (wide passes carry one fp16 plane per activation: not where the configuration asks for two)
     c->wide_prefill = c->fused_mode != 0 && model->wide_ok && attn_ok &&
                       !(cfg->flags & (SSD_CTX_NARROW_PASSES | SSD_CTX_TWO_PLANES | SSD_CTX_ONE_PLANE_ALL));
-    if (c->wide_prefill) c->max_rows = std::max(c->max_rows, kFusedWideRows);
+    if (c->wide_prefill) c->max_rows = std::max(c->max_rows, kFusedPromptRows);
     // Few-row extends on the persistent pass: from a width of 1024 on (16 to 48 rows, 100 and 4000 keys: width 1024, 8 layers,
     // 283..463 us against 327..498 as wide passes; width 512, 4 layers, 142..189 against 131..192).  A context whose workgroups
     // could not all be resident keeps the wide passes.
