@@ -1922,7 +1922,8 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
   const int unit = blockIdx.x;
   const int hk = unit % p.Hkv;
   int rem = unit / p.Hkv;
-  const int qg = rem % QG;
+  // (a prompt's later rows see more keys: their units go first, so that the last ones to start are the short ones)
+  const int qg = p.appended ? QG - 1 - rem % QG : rem % QG;
   rem /= QG;
   const int s = rem % p.NS, b = rem / p.NS;
   const int g_log = 31 - __builtin_clz(p.G), sl_log = p.SL == 8 ? 3 : 4;   // G and SL are powers of two
