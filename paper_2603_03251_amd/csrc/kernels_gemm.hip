@@ -45,8 +45,8 @@ __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g));
 // PACK (at most 8 rows): the two planes of the activations share one B operand, the head of row r in column r, its
 // remainder in column r + 8, and the columns are added at the end: one activation load and one MFMA per weight tile instead
 // of two.  The loads go through the same vector memory path as the weight stream and its rows are 16 strided segments, so
-// they, not HBM, set the pace: 6 rows of the 70B shape take 38 us for qkv (168 MB), 28 for o, 84 for down and 158 for
-// gate/up instead of 42, 32, 94 and 166.
+// they, not HBM, set the pace: 6 rows of the 70B shape take 34 us for qkv (168 MB), 25 for o, 76 for down and 151 for
+// gate/up (38, 28, 85 and 162 while the activations of a group were requested behind the next group's weights).
 template <int EPI, int MT, int U, bool PACK>
 __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_kernel(const bf16_t* __restrict__ x, int64_t x_plane,
                                                                  const bf16_t* __restrict__ w,
@@ -103,6 +103,46 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_kernel(const bf16_t* __
       }
     }
   };
+  if constexpr (MT <= 2) {
+    // Up to 32 rows: the activations of a group travel with its weights.  Requested where they are used, behind the next group's
+    // weights, they made every group wait for those (loads return in order).  4 layers of the 70B shape with a head of 16384: 6 rows
+    // 1476 -> 1360 us, 10 rows 1771 -> 1566, 16 rows 2127 -> 1877, 24 rows 2826 -> 2424 (groups of 4 tiles; at 6 rows they
+    // measured 1393).  More row tiles do not fit the registers.
+    constexpr int NX = PACK ? 1 : 2;
+    bf16x8 wr[2][U], wr2[2][EPI == EPI_SWIGLU ? U : 1], xr[2][U][MT][NX];
+    auto load = [&](int set, int kt) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        wr[set][u] = __builtin_nontemporal_load(wp + (int64_t)(kt + u) * 64);
+        if (EPI == EPI_SWIGLU) wr2[set][u] = __builtin_nontemporal_load(wp2 + (int64_t)(kt + u) * 64);
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+          for (int i = 0; i < NX; ++i) xr[set][u][t][i] = *(const bf16x8*)(xrow[t] + i * x_plane + (kt + u) * 32);
+      }
+    };
+    auto mul = [&](int set) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+          for (int i = 0; i < NX; ++i) {
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[set][u], xr[set][u][t][i], acc[t], 0, 0, 0);
+            if (EPI == EPI_SWIGLU) acc2[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr2[set][u], xr[set][u][t][i], acc2[t], 0, 0, 0);
+          }
+    };
+    const int n_groups = kt_per_wave / U;            // kt_per_wave is a multiple of U (host check)
+    if (n_groups > 0) load(0, 0);
+    int g = 0;
+    for (; g + 2 <= n_groups; g += 2) {
+      load(1, (g + 1) * U);
+      mul(0);
+      if (g + 2 < n_groups) load(0, (g + 2) * U);
+      mul(1);
+    }
+    if (g < n_groups) mul(0);                        // odd number of groups
+  } else {
   bf16x8 wa[U], wa2[U], wb[U], wb2[U];
   const int n_groups = kt_per_wave / U;            // kt_per_wave is a multiple of U (host check)
   if (n_groups > 0) load_group(wa, wa2, 0);
@@ -114,6 +154,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_kernel(const bf16_t* __
     mfma_group(wb, wb2, (g + 1) * U);
   }
   if (g < n_groups) mfma_group(wa, wa2, g * U);    // odd number of groups: the last one is already in wa
+  }
 
 #pragma unroll
   for (int t = 0; t < MT; ++t) {
@@ -310,7 +351,7 @@ int launch_bf16(const void* x, int64_t x_plane, const void* w, const void* w2, v
   const bool deep = EPI != EPI_SWIGLU && (Kd / 32 / kWaves) % 8 == 0;
 #define SSD_GEMM_LAUNCH(MTV, PACK)                                                                                        \
   do {                                                                                                                   \
-    if (deep) gemm_bf16_kernel<EPI, MTV, 8, PACK><<<grid, kWaves * 64, 0, s>>>(xb, x_plane, wb, w2b, out, ld, out_plane, M, N, Kd); \
+    if (deep && (MTV) != 2) gemm_bf16_kernel<EPI, MTV, (MTV) == 2 ? 4 : 8, PACK><<<grid, kWaves * 64, 0, s>>>(xb, x_plane, wb, w2b, out, ld, out_plane, M, N, Kd); \
     else gemm_bf16_kernel<EPI, MTV, 4, PACK><<<grid, kWaves * 64, 0, s>>>(xb, x_plane, wb, w2b, out, ld, out_plane, M, N, Kd);      \
   } while (0)
   if (M <= 8) {
