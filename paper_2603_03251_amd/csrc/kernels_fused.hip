@@ -1285,22 +1285,6 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
 #pragma unroll
     for (int t = 0; t < MTG; ++t) ck.b[t] = BIG ? bp[(t >> 1) * 128 + (t & 1) * 32] : bp[t * 64];   // BIG: [2 t + h]
   };
-  auto mfma_chunk = [&](const WideChunk<MTG>& ck) {
-    if constexpr (BIG) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-          for (int t = 0; t < MT32; ++t) accb[f][t] = mfma32_f16(ck.a[2 * f + h], ck.b[2 * t + h], accb[f][t]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int t = 0; t < MTG; ++t) acc[j][t] = mfma16_f16(ck.a[j], ck.b[t], acc[j][t]);
-    }
-  };
-
   float rs0, rs1;                                   // the rows' 1/rms: requested first, in LDS under the ring's loads
   if constexpr (EPI != FE_PART) {
     rs0 = ((const gfloat*)p.ssq)[min((int)threadIdx.x, p.M - 1)];
@@ -1316,16 +1300,37 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
     if ((int)threadIdx.x < kFusedWideRows - kWideThreads) r_s[threadIdx.x + kWideThreads] = rs1;
   }
   stamp(p, e.ph, 3);
+  // One load of a chunk to come behind each MFMA (two where a chunk has fewer MFMAs than loads): a burst of them blocks the one
+  // wavefront of a SIMD until the vector memory path has taken it in, 640 clocks per chunk of six row tiles and four wavefronts,
+  // with the matrix cores idle behind it
+  constexpr int NM = 4 * (BIG ? MT32 : MTG), NL = 4 + MTG;
+  auto turn = [&](const WideChunk<MTG>& ck, WideChunk<MTG>& to) {
+    const gbf16x8* ap = (const gbf16x8*)cu.a + lsrc;
+    const gbf16x8* ap2 = ATW == 4 ? ap + 128 : (const gbf16x8*)(cu.a + a_group2) + lsrc;
+    const gbf16x8* bp = (const gbf16x8*)cu.b + lsrc;
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      if constexpr (BIG) {
+        const int h = i / (2 * MT32), f = i / MT32 % 2, t = i % MT32;
+        accb[f][t] = mfma32_f16(ck.a[2 * f + h], ck.b[2 * t + h], accb[f][t]);
+      } else {
+        acc[i / MTG][i % MTG] = mfma16_f16(ck.a[i / MTG], ck.b[i % MTG], acc[i / MTG][i % MTG]);
+      }
+#pragma unroll
+      for (int l = i * NL / NM; l < (i + 1) * NL / NM; ++l) {
+        if (l < 4) to.a[l] = l < 2 ? ap[l * (BIG ? 32 : 64)] : ap2[(l - 2) * (BIG ? 32 : 64)];
+        else to.b[l - 4] = BIG ? bp[((l - 4) >> 1) * 128 + ((l - 4) & 1) * 32] : bp[(l - 4) * 64];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    advance(cu);
+  };
   for (int n = 0; n < n_my; ++n) {
     const int t = wx + n * per_xcd;
     const int q = (t / n_rg) * ys + y, rg = t - (t / n_rg) * n_rg;
     for (int c = 0; c < NCH; c += D) {
 #pragma unroll
-      for (int s = 0; s < D; ++s) {
-        load_chunk(ring[(s + D - 1) % D], cu);
-        advance(cu);
-        mfma_chunk(ring[s]);
-      }
+      for (int s = 0; s < D; ++s) turn(ring[s], ring[(s + D - 1) % D]);
     }
     if (n == 0) stamp(p, e.ph, 4);
     // ---- end of a pair: the 4 wavefronts' partial tiles meet in LDS; every wavefront sums its share of the 1 KiB blocks in
