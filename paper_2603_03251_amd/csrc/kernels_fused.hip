@@ -1197,7 +1197,7 @@ struct WideEpi {
 // D: chunks of the ring (kWideRing; half of it for slices too short for whole turns of the full ring, and for MTG = 12).
 // MTG: row tiles per row group.  Even: the MFMAs are 32x32x16, which a wavefront alone on its SIMD issues back to back (a
 // 16x16x32 every 28 clocks: the same time at 6 row tiles, but at 12 the 48 of a chunk would outlast its loads); both
-// operands stay in their 16x16x32 tile order, see wide_gemm_lds_kernel.
+// operands stay in their 16x16x32 tile order, see wide_tile_kernel.
 template <int ATW, int EPI, int D, int MTG>
 __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
   constexpr int MTOT = kWideTiles;
@@ -1497,223 +1497,31 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
   if (CLOCKS) stamp(p, ph, EMBED ? 2 : 7);
 }
 
-// The two large linear layers of a wide pass (gate/up + SwiGLU, LM head; stream-order units of 4 feature tiles, no
-// K-split).  Here the feature dimension is long enough to give every workgroup 16 feature tiles: the 4 wavefronts take
-// one unit each over the WHOLE reduction dimension (a unit's weight tiles are one contiguous run of memory), and the
-// activation tiles of the row group, which all four need, come through LDS: staged 8 k-tiles (48 KiB) at a time, double
-// buffered, one workgroup barrier per stage.  Per k-tile a workgroup pulls 16 KiB of weights and 6 KiB of activations
-// for 96 MFMAs (the split-K kernel above: 40 KiB), and nothing has to be reduced across wavefronts: the epilogue runs
-// from the accumulators.  Weights ride a ring of 8 register chunks that is refilled one stage ahead.
-// The MFMAs are 32x32x16: a wavefront that has its SIMD to itself issues one 16x16x32 per 28 clocks (measured: 1.44 of
-// 2.5 PFLOP/s over the chip) but 32x32x16, twice the work per instruction, back to back (2.23).  Both operands stay in
-// their 16x16x32 tile order in memory and LDS: a 32x32x16 operand is the k-half h of two neighbouring tiles, and lane l
-// takes its 16 bytes from lane (l & 15) + 16 (l >> 5) + 32 h of tile (l >> 4) & 1, a fixed offset per lane.
-constexpr int kWideStage = 8;   // k-tiles per LDS stage of the activation operand
-
-// NTW (one row group): the weights are read once and take the non-temporal path (LM head at 96 rows: 117 -> 108 us)
-template <int EPI, bool NTW>
-__global__ __launch_bounds__(kWideThreads) void wide_gemm_lds_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
-  constexpr int MTOT = kWideTiles, MTG = kWideGroup, KC = kWideStage;
-  constexpr int STAGE = KC * MTG * 64;               // 16-byte vectors per stage
-  constexpr int BL = STAGE / kWideThreads;           // staging loads per thread and stage (12)
-  extern __shared__ f32x4 lds[];                     // [2][KC][MTG][64] B-operand vectors
-  __shared__ float r_s[kFusedWideRows];              // the rows' 1/rms
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int NKT = g.KTW * kFusedWaves;               // k-tiles of the reduction dimension
-  const int NST = NKT / KC;                          // stages per pair
-  const int n_sets = (g.n_units + 3) >> 2;
-  const int n_rg = (((p.M + 15) >> 4) + MTG - 1) / MTG;
-  const int x = (int)blockIdx.x & 7, wx = (int)blockIdx.x >> 3, per_xcd = (int)gridDim.x >> 3;
-  const int nqx = x < n_sets ? (n_sets - x + 7) >> 3 : 0;
-  const int tx = nqx * n_rg;
-  const int n_my = wx < tx ? (tx - wx + per_xcd - 1) / per_xcd : 0;
-  stamp(p, e.ph, 0);
-  if (n_my == 0) return;
-
-  constexpr int MT32 = MTG / 2;                      // 32-row tiles of a row group
-  static_assert(MTG % 2 == 0, "row tiles pair up into 32-row MFMA operands");
-  const int lsrc = ((lane >> 4) & 1) * 64 + (lane & 15) + ((lane >> 5) << 4);   // operand vector of this lane (k-half 0)
-  auto zero_acc = [](f32x16& a) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) a[i] = 0.f;
-  };
-  f32x16 acc[2][MT32];                               // [32 features: tiles 0-1 / 2-3 of the unit][32 rows]
-#pragma unroll
-  for (int f = 0; f < 2; ++f)
-#pragma unroll
-    for (int t = 0; t < MT32; ++t) zero_acc(acc[f][t]);
-
-  auto pair_of = [&](int n, int& set, int& rg) {
-    const int t = wx + (n < n_my ? n : n_my - 1) * per_xcd;
-    const int qh = t / n_rg;
-    set = qh * 8 + x;
-    rg = t - qh * n_rg;
-  };
-  // this thread's BL vectors of a stage: vector v = tid + 256 i of [KC][MTG][64] sits at k-tile v / (MTG 64), row tile
-  // (v / 64) % MTG, lane v % 64 of the activation matrix [k-tile][MTOT][64]
-  int64_t b_rel[BL];
-#pragma unroll
-  for (int i = 0; i < BL; ++i) {
-    const int v = (int)threadIdx.x + kWideThreads * i;
-    const int kt = v / (MTG * 64), r2 = v - kt * (MTG * 64);
-    b_rel[i] = ((int64_t)kt * MTOT * 64 + r2) * 8;
-  }
-  struct Cursor { int n, s; const bf16_t* a; const bf16_t* b; };   // pair ordinal, stage; operand addresses of that stage
-  auto place = [&](Cursor& cu) {
-    int set, rg;
-    pair_of(cu.n, set, rg);
-    const int unit = min(set * 4 + wave, g.n_units - 1);
-    cu.a = g.w + ((int64_t)unit * NKT + cu.s * KC) * 4 * 512;
-    cu.b = bsrc + ((int64_t)(cu.s * KC) * MTOT + rg * MTG) * 512;
-  };
-  auto next_stage = [&](Cursor& cu) {
-    if (++cu.s == NST) { cu.s = 0; ++cu.n; }
-    place(cu);
-  };
-  bf16x8 ring[KC][4];
-  bf16x8 breg[BL];
-  auto load_b = [&](const Cursor& cu) {
-#pragma unroll
-    for (int i = 0; i < BL; ++i) breg[i] = *(const gbf16x8*)(cu.b + b_rel[i]);
-  };
-  auto store_b = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < BL; ++i) *(bf16x8*)&lds[buf * STAGE + (int)threadIdx.x + kWideThreads * i] = breg[i];
-  };
-  auto load_a = [&](const Cursor& cu, int j) {       // ring[j][2 f + h]: features 32 f .. 32 f + 31 of the unit, k-half h
-    const gbf16x8* ap = (const gbf16x8*)(cu.a + (int64_t)j * 4 * 512) + lsrc;
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const gbf16x8* q = ap + (jj >> 1) * 128 + (jj & 1) * 32;
-      if constexpr (NTW) ring[j][jj] = __builtin_nontemporal_load(q);
-      else ring[j][jj] = *q;
-    }
-  };
-
-  // ---- prologue: the rows' scales (requested first, read in the epilogue), stage 0 of the first pair
-  const float rs0 = ((const gfloat*)p.ssq)[min((int)threadIdx.x, p.M - 1)];
-  const float rs1 = ((const gfloat*)p.ssq)[min((int)threadIdx.x + kWideThreads, p.M - 1)];
-  Cursor cu{0, 0, nullptr, nullptr};
-  place(cu);
-  load_b(cu);
-  // the ring is requested in the order the loop refills it: the wait for chunk j inside the loop is computed from BOTH
-  // ways into the loop, and a prologue that had requested chunk 0 last would make every stage wait for the whole ring
-#pragma unroll
-  for (int j = 0; j < KC; ++j) {
-    __builtin_amdgcn_sched_barrier(0);
-    load_a(cu, j);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  r_s[threadIdx.x] = rs0;
-  if ((int)threadIdx.x < kFusedWideRows - kWideThreads) r_s[threadIdx.x + kWideThreads] = rs1;
-  store_b(0);
-  wg_barrier();
-  stamp(p, e.ph, 3);
-
-  int buf = 0;
-  for (int n = 0; n < n_my; ++n) {
-    int set, rg;
-    pair_of(n, set, rg);
-    for (int st = 0; st < NST; ++st) {
-      next_stage(cu);                                // the stage after this one (clamped past the end: loaded, never used)
-      load_b(cu);
-      __builtin_amdgcn_sched_barrier(0);
-      const bf16x8* bs = (const bf16x8*)&lds[buf * STAGE] + lsrc;
-      // the activation tiles of k-tile j + 1 leave LDS while the MFMAs of k-tile j run: one wavefront per SIMD has no
-      // neighbour to hide an LDS round trip behind.  bt[..][2 t + h]: rows 32 t .. 32 t + 31 of the group, k-half h
-      bf16x8 bt[2][MTG];
-#pragma unroll
-      for (int t = 0; t < MTG; ++t) bt[0][t] = bs[(t >> 1) * 128 + (t & 1) * 32];
-#pragma unroll
-      for (int j = 0; j < KC; ++j) {
-        if (j + 1 < KC) {
-#pragma unroll
-          for (int t = 0; t < MTG; ++t) bt[(j + 1) & 1][t] = bs[((j + 1) * MTG + (t >> 1) * 2) * 64 + (t & 1) * 32];
-        }
-        // (pinned in front of the MFMAs: the scheduler otherwise issues these reads behind them, into the registers the
-        // MFMAs have just released, and every k-tile starts with an LDS round trip)
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int f = 0; f < 2; ++f)
-#pragma unroll
-            for (int t = 0; t < MT32; ++t)
-              acc[f][t] = mfma32_f16(ring[j][2 * f + h], bt[j & 1][2 * t + h], acc[f][t]);
-        load_a(cu, j);
-        // the refill stays here, a whole stage ahead of its use: left alone, the instruction scheduler sinks it to just
-        // before that use to save registers, and every k-tile then waits a full memory latency
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      store_b(buf ^ 1);
-      wg_barrier();
-      buf ^= 1;
-    }
-    if (n == 0) stamp(p, e.ph, 4);
-    // ---- epilogue straight from the accumulators: this wavefront's unit (4 feature tiles) x the row group.  Registers
-    // 4 q .. 4 q + 3 of a 32x32 accumulator: features 8 q + 4 (lane >> 5) .. + 3 of the 32, row lane & 31
-    const int unit = set * 4 + wave;
-    const int f4 = (lane >> 5) * 4;
-    if (unit < g.n_units) {
-#pragma unroll
-      for (int t = 0; t < MT32; ++t) {
-        const int m = (rg * MTG + 2 * t) * 16 + (lane & 31);
-        if (m < p.M) {
-          const float rs = r_s[m];
-          if constexpr (EPI == FE_SWIGLU) {
-            // feature tiles 0, 1 of the unit are gate, 2, 3 the matching up tiles
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              bf16_t hi[4];
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const float gg = acc[0][t][4 * q + i] * rs, uu = acc[1][t][4 * q + i] * rs;
-                hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
-              }
-              const int k = unit * 32 + 8 * q + f4;       // input index of the down-projection
-              st_u64_uncounted(e.act_out + b_off<MTOT>(k, m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
-            }
-          } else {
-#pragma unroll
-            for (int f = 0; f < 2; ++f)
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                const int n0 = unit * 64 + f * 32 + 8 * q + f4;
-                const f32x4 v = (f32x4){acc[f][t][4 * q], acc[f][t][4 * q + 1], acc[f][t][4 * q + 2], acc[f][t][4 * q + 3]};
-                if ((n0 >> 4) < g.NT) st_f32x4_uncounted(e.out + (int64_t)m * e.ld + n0, v * rs);
-              }
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int f = 0; f < 2; ++f)
-#pragma unroll
-      for (int t = 0; t < MT32; ++t) zero_acc(acc[f][t]);
-    if (n == 0) stamp(p, e.ph, 5);
-  }
-  stamp(p, e.ph, 2);
-}
-
-// Every linear layer of a prompt pass (more than kFusedWideRows rows; no logits).  With so many rows the layers are contractions:
-// what bounds them is the matrix cores (32x32x16 on data that are not constant: 1.4 PFLOP/s, one wavefront per SIMD) and the
-// operands a compute unit pulls (about 100 GB/s), which must run side by side.  A workgroup = 4 wavefronts x (NF x 32 features) x
-// 128 rows: per k-tile it pulls 8 NF KiB of weights straight into registers (a ring of 8 k-tiles) and 8 KiB of activations,
-// which all four wavefronts read from LDS (stages of 4 k-tiles, double buffered, requested two stages ahead), for 8 NF MFMAs of each
-// wavefront.  What the kernel for 96 rows does not have: every LDS read, load and LDS write sits between two MFMAs
-// (sched_barrier), where a burst of them blocks the one wavefront of a SIMD until the memory pipeline has taken it in.  1024 rows
-// of the 1B shape, gate/up: 66 us (three passes of 340 rows: 3 x 35); tiles of 128 features x 192 rows measured 74 for 768 rows, of
-// 256 x 192 spill.
-// Tiles of 32 features: NF = 2: two per wavefront; ATW = 2 (qkv, o, down): the tile groups of the layout; ATW = 4 (gate/up): gate
-// tiles and up tiles of the wavefront's unit.  PART: S slices of the reduction dimension, XCD x on slice x % S, as in
-// wide_gemm_kernel.
-constexpr int kTileRows = kFusedPromptRowGroup, kTileStage = 4, kTileRing = 8;
-template <int ATW, int EPI, int NF>
+// The linear layers with many outputs (rows x features): the LM head, gate/up + SwiGLU beyond 192 rows, and every layer of a prompt
+// pass (more than kFusedWideRows rows).  They are contractions: what bounds them is the matrix cores (32x32x16 on data that are not
+// constant: 1.4 PFLOP/s with one wavefront per SIMD) and the operands a compute unit pulls (about 100 GB/s), which must run side by
+// side.  A workgroup = 4 wavefronts x (NF x 32 features) x RT row tiles over the whole reduction dimension (PART: a slice of it, XCD
+// x on slice x % S, as in wide_gemm_kernel).  The weights of a wavefront's own features go straight into registers (a ring of
+// 8 k-tiles); the activations, which all four need, through LDS (stages of 4 k-tiles, double buffered, requested two stages
+// ahead); nothing has to be reduced across wavefronts.  Every LDS read, load and LDS write sits between two MFMAs
+// (sched_barrier): a burst of them blocks the one wavefront of a SIMD until the memory pipeline has taken it in, and left to itself
+// the scheduler sinks the loads to just before their use.
+// The MFMAs are 32x32x16 (a 16x16x32 has 28 clocks from issue to issue for a wavefront alone on its SIMD, 32x32x16 twice the work in
+// 34).  Both operands stay in their 16x16x32 tile order in memory and LDS: a 32x32x16 operand is the k-half h of two neighbouring
+// tiles, and lane l takes its 16 bytes from lane (l & 15) + 16 (l >> 5) + 32 h of tile (l >> 4) & 1, a fixed offset per lane.
+// NF = 2: 64 features per wavefront: two tile groups of the layout (ATW = 2: o, down), or gate tiles and up tiles, or four tiles of
+// the head, of one unit (ATW = 4).  NTW (one row group): the weights are read once and take the non-temporal path.
+// Against stages of 8 k-tiles with the memory operations in bursts: rounds of the 1B shape of 384 rows 13.67 -> 13.29 ms, 288 rows
+// 12.19 -> 12.09, 96 rows (head only) 8.22 -> 8.14.  1024 prompt rows, gate/up: 66 us (three passes of 340 rows before: 3 x 35); tiles of
+// 128 features x 192 rows measured 74 for 768 rows, tiles of 256 x 192 spill.
+constexpr int kTileRows = kFusedPromptRowGroup;      // rows of a full row group
+constexpr int kTileStage = 4, kTileRing = 8;         // k-tiles of an LDS stage, of the weight ring
+template <int ATW, int EPI, int NF, int RT, bool NTW>
 __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
-  constexpr int RT = kTileRows / 16, KC = kTileStage, R32 = RT / 2;
-  constexpr int STAGE = KC * RT * 64, BL = STAGE / kWideThreads, BJ = BL / KC, NM = NF * R32;
+  constexpr int KC = kTileStage, R32 = RT / 2;
+  constexpr int STAGE = KC * RT * 64, BL = STAGE / kWideThreads, NM = NF * R32;
   static_assert(ATW == 2 || NF == 2, "a wavefront owns whole units of 4 feature tiles");
-  static_assert(kTileRing == 2 * KC && 2 * BJ <= NM && NF + 1 < NM, "a turn of the ring is two stages; memory operations between MFMAs");
+  static_assert(kTileRing == 2 * KC && 2 * ((BL + KC - 1) / KC) <= NM && NF + 1 < NM, "a turn of the ring is two stages; memory operations between MFMAs");
   extern __shared__ f32x4 lds[];                     // [2][KC][RT][64] B-operand vectors
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int NKT = g.KS * kFusedWaves * g.KTW;        // k-tiles of the reduction dimension
@@ -1722,7 +1530,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
   const int n_groups = g.n_units / g.KS;             // units of ATW feature tiles
   constexpr int SG = 4 * NF * 2 / ATW;               // ... of a set
   const int n_sets = (n_groups + SG - 1) / SG;
-  const int n_rg = (p.M + kTileRows - 1) / kTileRows;
+  const int n_rg = (((p.M + 15) >> 4) + RT - 1) / RT;
   const int x = (int)blockIdx.x & 7, wx = (int)blockIdx.x >> 3, per_xcd = (int)gridDim.x >> 3;
   const int slice = x % S, y = x / S, ys = 8 / S;    // S is 1, 2, 4 or 8
   const int nqy = y < n_sets ? (n_sets - y + ys - 1) / ys : 0;
@@ -1771,6 +1579,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
     c.q = bsrc + ((int64_t)((slice * NST + c.s) * KC) * p.row_tiles + rg * RT) * 512;
   };
   auto step = [&](Cursor& c) { if (++c.s == NST) { c.s = 0; ++c.n; } };
+  auto weight = [](const gbf16x8* q) { return NTW ? __builtin_nontemporal_load(q) : *q; };
   bf16x8 ring[kTileRing][2 * NF], breg[2][BL], bt[2][R32];
   Cursor ca{0, 0, nullptr}, cb{0, 0, nullptr};
   place_b(cb);
@@ -1791,7 +1600,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
 #pragma unroll
       for (int f = 0; f < NF; ++f)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) ring[u * KC + j][2 * f + h] = ap[f * fstep + h * 32];
+        for (int h = 0; h < 2; ++h) ring[u * KC + j][2 * f + h] = weight(ap + f * fstep + h * 32);
     }
     step(ca);
     place_a(ca);
@@ -1820,6 +1629,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
 #pragma unroll
         for (int j = 0; j < KC; ++j) {
           const gbf16x8* ap = (const gbf16x8*)(ca.q + j * (ATW * 512)) + lsrc;
+          const int b0 = j * BL / KC, b1 = (j + 1) * BL / KC;         // the k-tile's share of a thread's staging
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             const int nx = 2 * j + h + 1;            // the k-half to come
@@ -1829,13 +1639,13 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
               acc[f][t] = mfma32_f16(ring[u * KC + j][2 * f + h], bt[h][t], acc[f][t]);
               // between two MFMAs: an LDS read of the coming half and one of the k-tile's other memory operations
               if (nx < 2 * KC && i < R32) bt[nx & 1][i] = bs[(nx >> 1) * (RT * 64) + i * 128 + (nx & 1) * 32];
-              if (h == 0 && (i & 1) == 0 && i / 2 < BJ) breg[u][j * BJ + i / 2] = *(const gbf16x8*)(cb.q + b_rel[j * BJ + i / 2]);
-              if (h == 0 && (i & 1) == 1 && i / 2 < BJ)
-                *(bf16x8*)&lds[(u ^ 1) * STAGE + (int)threadIdx.x + kWideThreads * (j * BJ + i / 2)] = breg[u ^ 1][j * BJ + i / 2];
-              if (h == 1 && i >= 1 && i - 1 < NF) ring[u * KC + j][2 * (i - 1)] = ap[(i - 1) * fstep];
+              if (h == 0 && (i & 1) == 0 && b0 + i / 2 < b1) breg[u][b0 + i / 2] = *(const gbf16x8*)(cb.q + b_rel[b0 + i / 2]);
+              if (h == 0 && (i & 1) == 1 && b0 + i / 2 < b1)
+                *(bf16x8*)&lds[(u ^ 1) * STAGE + (int)threadIdx.x + kWideThreads * (b0 + i / 2)] = breg[u ^ 1][b0 + i / 2];
+              if (h == 1 && i >= 1 && i - 1 < NF) ring[u * KC + j][2 * (i - 1)] = weight(ap + (i - 1) * fstep);
               if (h == 1 && i + 1 == NM) {
 #pragma unroll
-                for (int ff = 0; ff < NF; ++ff) ring[u * KC + j][2 * ff + 1] = ap[ff * fstep + 32];
+                for (int ff = 0; ff < NF; ++ff) ring[u * KC + j][2 * ff + 1] = weight(ap + ff * fstep + 32);
               }
               __builtin_amdgcn_sched_barrier(0);
             }
@@ -1871,7 +1681,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
               float* out = e.out + (EPI == FE_PART ? (int64_t)slice * p.M * e.ld : 0) + (int64_t)m * e.ld;
 #pragma unroll
               for (int f = 0; f < NF; ++f) {
-                const int n0 = (first + f) * 32 + 8 * q + f4;
+                const int n0 = first * (ATW * 16) + f * 32 + 8 * q + f4;
                 const f32x4 v = (f32x4){acc[f][t][4 * q], acc[f][t][4 * q + 1], acc[f][t][4 * q + 2], acc[f][t][4 * q + 3]};
                 if ((n0 >> 4) < g.NT) st_f32x4_uncounted(out + n0, EPI == FE_PART ? v : v * rs[t]);
               }
@@ -2734,16 +2544,6 @@ int launch_wide_gemm_dm(const FusedParams& p, const FusedGemm& g, const bf16_t* 
   return SSD_OK;
 }
 
-template <int EPI, bool NTW>
-int launch_wide_gemm_lds(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
-  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_gemm_lds_kernel<EPI, NTW>,
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes);
-  SSD_HIP(configured);
-  wide_gemm_lds_kernel<EPI, NTW><<<p.nwg, kWideThreads, kFusedLdsBytes, s>>>(p, g, bsrc, e);
-  SSD_HIP(hipGetLastError());
-  return SSD_OK;
-}
-
 template <int ATW, int EPI, int MTG>
 int launch_wide_gemm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
   // a wavefront's k-tiles per pair must be whole turns of the ring
@@ -2752,14 +2552,14 @@ int launch_wide_gemm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
   return launch_wide_gemm_dm<ATW, EPI, kWideRing / 2, MTG>(p, g, bsrc, e, s);
 }
 
-template <int ATW, int EPI, int NF>
+template <int ATW, int EPI, int NF, int RT = kTileRows / 16, bool NTW = false>
 int launch_wide_tile(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
-  constexpr int kLds = 2 * kTileStage * (kTileRows / 16) * 1024;
-  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_tile_kernel<ATW, EPI, NF>,
+  constexpr int kLds = 2 * kTileStage * RT * 1024;
+  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_tile_kernel<ATW, EPI, NF, RT, NTW>,
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   SSD_HIP(configured);
   SSD_CHECK_ARG(wide_k_tiles(g) % (kTileRing * e.S) == 0 && (g.n_units / g.KS) * ATW % (2 * NF) == 0, "prompt pass: layer does not cut into tiles");
-  wide_tile_kernel<ATW, EPI, NF><<<p.nwg, kWideThreads, kLds, s>>>(p, g, bsrc, e);
+  wide_tile_kernel<ATW, EPI, NF, RT, NTW><<<p.nwg, kWideThreads, kLds, s>>>(p, g, bsrc, e);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }
@@ -2805,7 +2605,7 @@ int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
 // gate/up + SwiGLU.  Up to 12 row tiles (192 rows) in one row group: a workgroup per unit of 4 feature tiles, the reduction
 // dimension over its wavefronts, every weight read once, instead of 16 feature tiles per workgroup on a quarter (up to
 // 96 rows) or half of the grid (170 rows: 27 us against 30; 32 rows: 18 against 20.9 in groups of 6;
-// whole passes of 4 layers of the 1B shape, against 96 rows per group of the LDS kernel: 112 rows 292 us and 304, 160 rows 301
+// whole passes of 4 layers of the 1B shape, against 96 rows per group and 16 feature tiles per workgroup: 112 rows 292 us and 304, 160 rows 301
 // and 311, 192 rows 315 and 323).  With more rows 16 feature tiles per workgroup fill the
 // grid and pull less.
 int launch_wide_gate_up(const FusedParams& p, const FusedGemm& g, const WideEpi& e, hipStream_t s) {
@@ -2816,8 +2616,8 @@ int launch_wide_gate_up(const FusedParams& p, const FusedGemm& g, const WideEpi&
     if (tiles <= kWideGroup) return launch_wide_gemm<4, FE_SWIGLU, kWideGroup>(p, g, p.xn, e, s);
     return launch_wide_gemm<4, FE_SWIGLU, 2 * kWideGroup>(p, g, p.xn, e, s);
   }
-  if (tiles <= kWideGroup) return launch_wide_gemm_lds<FE_SWIGLU, true>(p, g, p.xn, e, s);
-  return launch_wide_gemm_lds<FE_SWIGLU, false>(p, g, p.xn, e, s);
+  if (tiles <= kWideGroup) return launch_wide_tile<4, FE_SWIGLU, 2, kWideGroup, true>(p, g, p.xn, e, s);
+  return launch_wide_tile<4, FE_SWIGLU, 2, kWideGroup>(p, g, p.xn, e, s);
 }
 
 // The attention units of a pass, p.NQ query tiles each (the host chooses them together with the key splits)
@@ -2836,6 +2636,16 @@ int launch_wide_attn(const FusedParams& p, const FusedLayer& L, int ph, hipStrea
   if (p.NQ == 1) return launch_wide_attn_nq<PL, PG, 1>(p, L, ph, s);
   if (p.NQ == 2) return launch_wide_attn_nq<PL, PG, 2>(p, L, ph, s);
   return launch_wide_attn_nq<PL, PG, 3>(p, L, ph, s);
+}
+
+// LM head.  Up to 96 rows one row group.  Beyond: row groups of 128 where they pad no more rows than groups of 96 do (rounds of the 1B shape, ms: 384 rows
+// 13.23 with 128, 13.36 with 96; 288 rows 12.16, 12.11; 180 rows 9.55, 9.52).
+int launch_wide_logits(const FusedParams& p, const WideEpi& e, hipStream_t s) {
+  constexpr int kSmall = kWideGroup * 16;
+  if (p.M <= kSmall) return launch_wide_tile<4, FE_LOGITS, 2, kWideGroup, true>(p, p.lm, p.xn, e, s);
+  if ((p.M + kTileRows - 1) / kTileRows * kTileRows <= (p.M + kSmall - 1) / kSmall * kSmall)
+    return launch_wide_tile<4, FE_LOGITS, 2>(p, p.lm, p.xn, e, s);
+  return launch_wide_tile<4, FE_LOGITS, 2, kWideGroup>(p, p.lm, p.xn, e, s);
 }
 
 int launch_wide_resid(const FusedParams& p, bool embed, const float* part, int S, const bf16_t* gain, float* hidden, int ph, hipStream_t s) {
@@ -2863,8 +2673,7 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
     if (ph == lm_phase) {
       if (p.logits) {
         e.out = p.logits; e.ld = p.logits_ld;
-        if (((p.M + 15) >> 4) <= kWideGroup) SSD_TRY((launch_wide_gemm_lds<FE_LOGITS, true>(p, p.lm, p.xn, e, s)));
-        else SSD_TRY((launch_wide_gemm_lds<FE_LOGITS, false>(p, p.lm, p.xn, e, s)));
+        SSD_TRY(launch_wide_logits(p, e, s));
       }
       continue;
     }

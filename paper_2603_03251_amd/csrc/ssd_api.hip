@@ -151,6 +151,7 @@ struct ssd_ctx {
   int fused_mode = 0;
   bool fused_wide = false;     // rounds and extends run as wide passes (up to kFusedWideRows rows, one launch per phase)
   bool wide_prefill = false;   // prompts are prefilled in wide passes (also in contexts whose rounds are narrow passes)
+  int prompt_rows = 0;         // most rows of a pass that only fills the trunk
   bool small_passes = false;   // extends of at most kFusedMaxRows rows take the persistent narrow pass also where wide passes serve the rest
   int fused_cap = 0;           // rows of one pass of a round: kFusedMaxRows or kFusedWideRows
   int vt_stride = 0;
@@ -433,8 +434,8 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
   FusedParams p = wide ? c->fpw : c->fp;
   const ssd_ctx::PartCap& part = wide ? c->part_wide : c->part;
   // passes that only fill the trunk (prompts) may be larger than those of a round
-  const bool fills = c->wide_prefill && !logits && !hidden && branch_depth < 0;
-  const int cap = wide ? (fills ? kFusedPromptRows : kFusedWideRows) : kFusedMaxRows;
+  const bool fills = !logits && !hidden && branch_depth < 0;
+  const int cap = wide ? (fills ? c->prompt_rows : kFusedWideRows) : kFusedMaxRows;
   p.R = rows_per_seq;
   p.is_branch = branch_depth >= 0;
   p.suffix_len = branch_depth >= 0 ? branch_depth + 1 : 0;
@@ -616,8 +617,8 @@ int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t*
       // a group: the next sequences that fit one pass with the whole chunk of each
       T = 0;
       for (gn = 0; g0 + gn < nb; ++gn) {
-        const int want = std::max(T, std::min<int>(lens[g0 + gn], kFusedPromptRows));
-        if (gn > 0 && want * (gn + 1) > kFusedPromptRows) break;
+        const int want = std::max(T, std::min<int>(lens[g0 + gn], c->prompt_rows));
+        if (gn > 0 && want * (gn + 1) > c->prompt_rows) break;
         T = want;
       }
     }
@@ -625,7 +626,7 @@ int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t*
     const bool wide = c->wide_prefill && (c->fused_wide || max_len > K1);
     if (wide) {
       // full passes and a shorter last one
-      T = std::min(max_len, kFusedPromptRows);
+      T = std::min(max_len, c->prompt_rows);
     } else {
       T = K1;
     }
@@ -764,7 +765,7 @@ int fused_setup(ssd_ctx* c) {
   if (c->fused_wide || c->wide_prefill) {
     FusedParams& w = c->fpw;
     w = p;
-    const size_t MW = c->wide_prefill ? (size_t)kFusedPromptRows : (size_t)kFusedWideRows;
+    const size_t MW = (size_t)c->prompt_rows;
     // query rows of a pass: whole 16-row tiles per sequence
     c->part_wide.ns_max = (c->max_trunk + 2047) / 2048 + 1;
     c->part_wide.entries = (int64_t)p.Hkv * c->part_wide.ns_max * ((int64_t)MW * p.G + 16 * std::min(c->B, (int)MW));
@@ -772,7 +773,7 @@ int fused_setup(ssd_ctx* c) {
     // features x 96 rows a workgroup at the 1B shape).  They lie where the qkv projections were: written after the
     // attention has read those, read before the next layer's are written
     // (prompt passes: four slices of 1024 rows, eight of 512)
-    w.fix_stride = c->wide_prefill ? 4 * kFusedPromptRows : kFusedWideSlices * kFusedWideRowGroup;
+    w.fix_stride = c->prompt_rows > kFusedWideRows ? 4 * kFusedPromptRows : kFusedWideSlices * kFusedWideRowGroup;
     // one allocation, carved up
     char* base = nullptr;
     size_t used = 0;
@@ -943,7 +944,9 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
     // (wide passes carry one fp16 plane per activation: not where the configuration asks for two)
     c->wide_prefill = c->fused_mode != 0 && model->wide_ok && attn_ok &&
                       !(cfg->flags & (SSD_CTX_NARROW_PASSES | SSD_CTX_TWO_PLANES | SSD_CTX_ONE_PLANE_ALL));
-    if (c->wide_prefill) c->max_rows = std::max(c->max_rows, kFusedPromptRows);
+    // (no more than the trunks have room for)
+    c->prompt_rows = c->wide_prefill && (int64_t)c->B * c->max_trunk > kFusedWideRows ? kFusedPromptRows : kFusedWideRows;
+    if (c->wide_prefill) c->max_rows = std::max(c->max_rows, c->prompt_rows);
     // Few-row extends on the persistent pass: from a width of 1024 on (16 to 48 rows, 100 and 4000 keys: width 1024, 8 layers,
     // 283..463 us against 327..498 as wide passes; width 512, 4 layers, 142..189 against 131..192).  A context whose workgroups
     // could not all be resident keeps the wide passes.
