@@ -71,6 +71,42 @@ def test_wide_prefill_equals_narrow_chunks(B, lens):
         B.ssd_model_destroy(model)
 
 
+@pytest.mark.parametrize("width,lens", [(1024, [512]), (1024, [513]), (512, [896]), (1024, [897]), (512, [1024]), (1024, [1025]),
+                                        (512, [1409]), (1024, [500, 512, 30])], ids=lambda x: str(x) if isinstance(x, int) else "-".join(map(str, x)))
+@pytest.mark.parametrize("paged", [False, True])
+def test_prompt_passes_at_the_edges_of_their_row_groups(B, width, lens, paged):
+    """Passes of 385 to 1024 rows, in row groups of 128: whole ones, one row more, the most a pass takes and what is left behind
+    it (1 row; 385), the row count from which o and down have room for fewer slices (512 | 513), a pass of two sequences."""
+    print(f"[case] width {width}, prefill of {lens}, paged {paged}", flush=True)
+    nb, max_trunk, seed = len(lens), max(lens) + 2 * K + 8, 3 + sum(lens)
+    shape = I.ModelShape(n_layers=2, d_model=width, n_q_heads=width // 64, n_kv_heads=width // 256, head_dim=64, d_ffn=2 * width, vocab=4112,
+                         dtype="bf16", rope_theta=500000.0, tie_embeddings=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, 17))
+    prompt = dev_i32(I.make_prompt(shape, nb, max(lens), seed))
+    pending, temps = dev_i32(I.make_pending(shape, nb, K, seed)), dev_f32(np.zeros(nb))
+    pages = 1 + nb * ((max_trunk + 63) // 64 * 2) if paged else 0
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags, n) for flags, n in ((0, pages), (B.SSD_CTX_NARROW_PASSES, 0))]
+    try:
+        got = []
+        for ctx in ctxs:
+            B.ssd_ctx_prefill(ctx, prompt, lens)
+            kv = None if paged else _trunk(B, ctx, lens, max_trunk, shape)
+            B.ssd_prespeculate(ctx, pending, temps, 1)
+            torch.cuda.synchronize()
+            B.ssd_ctx_status(ctx)
+            got.append((kv, B.read_cache(ctx)["glue_logits"].cpu().numpy()))
+        # each side is within TOL_BF16_OWN_PREFILL of the exact keys, values and logits
+        for part in (0, 1) if not paged else ():
+            for l in range(shape.n_layers):
+                for b in range(nb):
+                    assert row_rel_err(got[0][0][part][l][b], got[1][0][part][l][b]) < 2 * TOL_BF16_OWN_PREFILL, (part, l, b)
+        assert row_rel_err(got[0][1], got[1][1]) < 2 * TOL_BF16_OWN_PREFILL
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
 @pytest.mark.parametrize("lens", [[1], [K], [K + 1], [K + 1, 1], [2, K, 1]], ids=lambda x: "-".join(map(str, x)))
 def test_prompts_of_one_chunk_take_the_narrow_pass(B, lens):
     """Where the rounds are narrow passes and a chunk of K+1 tokens holds the prompts, the prefill is that one narrow pass, to
