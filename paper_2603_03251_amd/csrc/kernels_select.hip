@@ -147,10 +147,16 @@ struct ScoreId {
   double s;
   int id;
 };
-constexpr int kSampleMaxParts = 64;   // blocks that share one row of the sampler
+// The sampler's rows are shared among small blocks: a block of 1024 threads waits with all 16 wavefronts for the slowest of them, and
+// only two fit a compute unit.  About 2048 blocks, of 1024 and 256 threads, us with the merge: 24 rows of 128256 at temperature
+// 0.7 15.9 and 15.0, 48 rows 25.8 and 17.8 (greedy 16.9 and 10.2), 96 rows 41.0 and 25.4 (23.9 and 13.5), 384 rows 74 and 63 (37.4
+// and 35.3); 512 threads lie between, 1024 or 4096 blocks of 256 measure 0 to 4 us more from 48 rows on.  A row of one block takes 1024.
+constexpr int kSampleBlock = 256;
+constexpr int kSampleMaxParts = 128;  // blocks that share one row of the sampler
 __device__ __forceinline__ bool better(const ScoreId& a, const ScoreId& b) {
   return a.s > b.s || (a.s == b.s && a.id < b.id);
 }
+template <int WAVES>
 __device__ __forceinline__ ScoreId block_argmax(ScoreId v, ScoreId* smem) {
   for (int o = 32; o > 0; o >>= 1) {
     ScoreId t;
@@ -162,7 +168,7 @@ __device__ __forceinline__ ScoreId block_argmax(ScoreId v, ScoreId* smem) {
   if (lane == 0) smem[wave] = v;
   __syncthreads();
   ScoreId r = smem[0];
-  for (int i = 1; i < kSelWaves; ++i)
+  for (int i = 1; i < WAVES; ++i)
     if (better(smem[i], r)) r = smem[i];
   __syncthreads();
   return r;
@@ -173,12 +179,13 @@ __device__ __forceinline__ double score_of(float z) { return z != z ? -INFINITY 
 // part of its row's vocabulary; with one part it writes the token, otherwise its best (score, id) goes to `scratch`
 // [row][part] and sample_merge_kernel picks the row's winner (the order `better` defines is total, so any grouping
 // gives the same token).
-__global__ __launch_bounds__(kSelBlock) void sample_kernel(const float* __restrict__ logits, int64_t ld,
-                                                           const float* __restrict__ temperature, int rows_per_seq,
-                                                           int V, uint64_t seed, int row_base, int step,
-                                                           int32_t* __restrict__ out, int64_t out_stride,
-                                                           ScoreId* __restrict__ scratch, int exact_scan) {
-  __shared__ ScoreId smem[kSelWaves];
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void sample_kernel(const float* __restrict__ logits, int64_t ld,
+                                                       const float* __restrict__ temperature, int rows_per_seq,
+                                                       int V, uint64_t seed, int row_base, int step,
+                                                       int32_t* __restrict__ out, int64_t out_stride,
+                                                       ScoreId* __restrict__ scratch, int exact_scan) {
+  __shared__ ScoreId smem[BLOCK / 64];
   const int row = blockIdx.x, part = blockIdx.y, parts = gridDim.y;
   const float* z = logits + (int64_t)row * ld;
   const double T = (double)temperature[row / rows_per_seq];
@@ -193,16 +200,16 @@ __global__ __launch_bounds__(kSelBlock) void sample_kernel(const float* __restri
     // would cost a memory latency each)
     typedef __attribute__((ext_vector_type(4))) float f4;
     const f4* z4 = (const f4*)z;
-    for (int t0 = q_begin + threadIdx.x; t0 < q_end; t0 += kSelBlock * 8) {
+    for (int t0 = q_begin + threadIdx.x; t0 < q_end; t0 += BLOCK * 8) {
       f4 v[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        int t = t0 + u * kSelBlock;
+        int t = t0 + u * BLOCK;
         v[u] = z4[t < q_end ? t : t0];
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        int t = t0 + u * kSelBlock;
+        int t = t0 + u * BLOCK;
         if (t < q_end) {
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
@@ -214,7 +221,7 @@ __global__ __launch_bounds__(kSelBlock) void sample_kernel(const float* __restri
     }
   } else if (T <= 0.0 || exact_scan) {
     const int t_end = min(V, q_end * 4);
-    for (int t = q_begin * 4 + threadIdx.x; t < t_end; t += kSelBlock) {
+    for (int t = q_begin * 4 + threadIdx.x; t < t_end; t += BLOCK) {
       ScoreId c;
       c.id = t;
       c.s = score_of(z[t]);
@@ -238,40 +245,55 @@ __global__ __launch_bounds__(kSelBlock) void sample_kernel(const float* __restri
       constexpr float kLn2 = 0.69314718f;
       return zt * inv_t - __builtin_amdgcn_logf(__builtin_amdgcn_logf(u) * -kLn2) * kLn2;
     };
-    // The logits are requested four at a time ahead of the hashes and logarithms; each thread remembers its own maximum,
-    // and only threads whose maximum can still win go over their tokens again (a second scan by all of them, with 64-bit
-    // conversions and library logarithms: 61 us for 96 rows of 128256, now 48).
+    // Hashes and logarithms set the pace (two 64-bit products and two quarter-rate logarithms a token), so the next four logits
+    // are on their way while four are scored.  Each thread remembers its best token and the second best score: only where
+    // both can win does it go over its tokens again, a chain of a memory round trip per token that somebody in every block
+    // used to walk (96 rows of 128256: 48 -> 41 us).
     constexpr int kAhead = 4;
-    float mine = -INFINITY;
-    for (int t0 = t_begin + (int)threadIdx.x; t0 < t_end; t0 += kSelBlock * kAhead) {
+    float mine = -INFINITY, second = -INFINITY;
+    int at = t_begin + (int)threadIdx.x;
+    float ahead[kAhead];
+    auto load = [&](int t0) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) ahead[u] = z[min(t0 + u * BLOCK, t_end - 1)];
+    };
+    if (at < t_end) load(at);
+    for (int t0 = at; t0 < t_end; t0 += BLOCK * kAhead) {
       float zv[kAhead];
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u) zv[u] = z[min(t0 + u * kSelBlock, t_end - 1)];
+      for (int u = 0; u < kAhead; ++u) zv[u] = ahead[u];
+      if (t0 + BLOCK * kAhead < t_end) load(t0 + BLOCK * kAhead);
 #pragma unroll
       for (int u = 0; u < kAhead; ++u) {
-        const float sc = s32(t0 + u * kSelBlock, zv[u]);
-        mine = t0 + u * kSelBlock < t_end ? fmaxf(mine, sc) : mine;
+        const int t = t0 + u * BLOCK;
+        const float sc = t < t_end ? s32(t, zv[u]) : -INFINITY;
+        second = fmaxf(second, fminf(mine, sc));     // (an equal score, or one that is not a number, counts as a second one)
+        at = sc > mine ? t : at;
+        mine = fmaxf(mine, sc);
       }
     }
     float mx = mine;
     for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    __shared__ float fmx[kSelWaves];
+    __shared__ float fmx[BLOCK / 64];
     if ((threadIdx.x & 63) == 0) fmx[threadIdx.x >> 6] = mx;
     __syncthreads();
     mx = fmx[0];
-    for (int i = 1; i < kSelWaves; ++i) mx = fmaxf(mx, fmx[i]);
+    for (int i = 1; i < BLOCK / 64; ++i) mx = fmaxf(mx, fmx[i]);
     // an infinite or empty maximum: score everything in fp64
     const float thr = mx > -INFINITY && mx < INFINITY ? mx - 2.0f * (2e-6f * (fabsf(mx) + 40.0f) + 2e-5f) : -INFINITY;
-    for (int t = mine >= thr ? t_begin + (int)threadIdx.x : t_end; t < t_end; t += kSelBlock) {
-      if (s32(t, z[t]) >= thr) {
-        ScoreId c;
-        c.id = t;
-        c.s = score_of(z[t]) / T + gumbel_from_u(draw_u(prefix, (uint64_t)t));
-        if (better(c, best)) best = c;
-      }
+    auto score = [&](int t) {
+      ScoreId c;
+      c.id = t;
+      c.s = score_of(z[t]) / T + gumbel_from_u(draw_u(prefix, (uint64_t)t));
+      if (better(c, best)) best = c;
+    };
+    if (mine >= thr) {
+      const bool one = second < thr;
+      for (int t = one ? at : t_begin + (int)threadIdx.x; t < t_end; t += one ? V : BLOCK)
+        if (one || s32(t, z[t]) >= thr) score(t);
     }
   }
-  best = block_argmax(best, smem);
+  best = block_argmax<BLOCK / 64>(best, smem);
   if (threadIdx.x == 0) {
     if (parts == 1) out[(int64_t)row * out_stride] = best.id;
     else scratch[(int64_t)row * parts + part] = best;
@@ -794,17 +816,22 @@ int launch_sample(const float* logits, int64_t ld, const float* temperature, int
                   hipStream_t s) {
   if (rows <= 0) return SSD_OK;
   int parts = 1;
-  if (scratch) {
+  if (scratch && V > 4096) {                                            // (fewer tokens: a block has them in 4 loads a thread)
     parts = (2048 + rows - 1) / rows;                                   // about 2048 blocks
-    const int by_len = (V + kSelBlock * 4 - 1) / (kSelBlock * 4);       // at least 4 tokens per thread
+    const int by_len = (V + kSampleBlock * 4 - 1) / (kSampleBlock * 4); // at least 4 tokens per thread
     parts = parts < by_len ? parts : by_len;
     parts = parts < kSampleMaxParts ? parts : kSampleMaxParts;
     parts = parts < 1 ? 1 : parts;
   }
   // exact_scan: score every token of a sampled row in fp64 instead of pre-selecting in fp32 (a test aid: both give the
   // same token)
-  sample_kernel<<<dim3(rows, parts), kSelBlock, 0, s>>>(logits, ld, temperature, rows_per_seq, V, seed, row_base, step, out,
-                                                        out_stride, (ScoreId*)scratch, exact_scan);
+  const dim3 grid(rows, parts);
+  if (parts > 1)
+    sample_kernel<kSampleBlock><<<grid, kSampleBlock, 0, s>>>(logits, ld, temperature, rows_per_seq, V, seed, row_base, step, out,
+                                                              out_stride, (ScoreId*)scratch, exact_scan);
+  else
+    sample_kernel<kSelBlock><<<grid, kSelBlock, 0, s>>>(logits, ld, temperature, rows_per_seq, V, seed, row_base, step, out, out_stride,
+                                                        (ScoreId*)scratch, exact_scan);
   SSD_HIP(hipGetLastError());
   if (parts > 1) {
     sample_merge_kernel<<<rows, 64, 0, s>>>((const ScoreId*)scratch, parts, out, out_stride);

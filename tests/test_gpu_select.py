@@ -122,6 +122,27 @@ def test_sampler_fp32_preselection_gives_the_fp64_token(B, V, rows, scale, temp)
     assert (outs[1][0] != outs[1][1]).any() or rows <= 7
 
 
+@pytest.mark.parametrize("V", [1023, 1025, 5121, 40003])
+@pytest.mark.parametrize("stride", [0, 1, 1024, 4096, 5120])
+def test_sampler_candidates_that_fp32_cannot_order(B, V, stride):
+    """A thread of the sampler takes every 1024th token.  All tokens (stride 0), or one token and its neighbour at `stride` (the
+    same thread's, or another's), have scores that differ only by the rounding of the logits."""
+    seed, T, rows, g = 11, 0.5, 5, np.random.default_rng(V + stride)
+    z = np.empty((rows, V), np.float32)
+    for r in range(rows):
+        level = np.full(V, 3.0 if stride == 0 else -3.0)
+        if stride:
+            t = int(g.integers(0, max(1, V - stride)))
+            level[[t, min(t + stride, V - 1)]] = 3.0
+        z[r] = (level - O.gumbel(seed, O.STREAM_DRAFT, r, 2, V)) * T
+    temps, zd, outs = dev_f32(np.full(rows, T, np.float32)), dev_f32(z), []
+    for sample in (B.ssd_sample_fp64_scan, B.ssd_sample):
+        out = torch.full((rows,), -5, dtype=torch.int32, device="cuda")
+        sample(zd, temps, seed=seed, row_base=0, step=2, out=out)
+        outs.append(out.cpu().numpy())
+    assert np.array_equal(outs[0], outs[1])
+
+
 def _verify_case(B, V, K, nb, seed, temps, close_draft):
     g = np.random.default_rng(seed)
     zt = (g.standard_normal((nb, K + 1, V)) * 2.0).astype(np.float32)
