@@ -78,7 +78,8 @@ struct RowDesc {
   int32_t pos;        // absolute position of the row's token (rotary angle)
   int32_t vis;        // number of trunk positions the row sees (for extend rows this includes itself)
   int32_t suffix_len; // number of private suffix positions the row sees (includes itself); 0 for extend rows
-  int32_t kv_slot;    // where the row's own K/V goes: trunk position (extend) or suffix depth (branch)
+  int32_t kv_slot;    // where the row's own K/V goes: trunk position (extend; -1: nowhere, a row that only pads a wide pass) or
+                      // suffix depth (branch)
   int32_t is_branch;  // 1: KV goes to the row's private suffix, 0: to the trunk
 };
 
@@ -106,7 +107,7 @@ int launch_setup_branch_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk
                              int half_dim, float theta, int32_t* step_tokens, const int32_t* keys,
                              const int32_t* cache_tokens, const int32_t* forced_keys, const int32_t* forced_tokens,
                              hipStream_t s);
-int launch_setup_extend_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, int B, int T, int offset,
+int launch_setup_extend_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, const int32_t* limit, int B, int T, int offset,
                              int half_dim, float theta, int seq_base, hipStream_t s);
 int launch_embed(int dtype, const void* embed, const int32_t* tokens, float* h, int M, int d, int vocab, hipStream_t s);
 int launch_rmsnorm(int dtype, const float* h, const void* gain, void* xn, int64_t xn_plane, float* copy_out,

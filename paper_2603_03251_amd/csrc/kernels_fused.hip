@@ -2057,6 +2057,7 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
       *(gbf16x8*)(suffix_v + row + q8 * 8) = vv.v;
     } else {
       const int slot = p.rows[m_o].kv_slot;
+      if (slot < 0) continue;                                 // a row that only pads
       const int64_t bb = PG ? ((int64_t)p.pages[(int64_t)b * p.page_stride + (slot >> 5)] * p.Hkv + hk) * 2048
                             : (int64_t)(b * p.Hkv + hk) * p.vt_stride * 64 + (int64_t)(slot >> 5) * 2048;
       const int64_t row = bb + (int64_t)(slot & 31) * 64;
@@ -2123,7 +2124,7 @@ __global__ __launch_bounds__(256) void wide_append_kernel(FusedParams p, bf16_t*
   const int idx = blockIdx.x * 256 + threadIdx.x;
   const int q8 = idx & 7, hk = (idx >> 3) % p.Hkv, m = (idx >> 3) / p.Hkv;
   if (m >= p.M) return;
-  const int slot = p.rows[m].kv_slot, b = m / p.R;
+  const int stored_at = p.rows[m].kv_slot, slot = max(stored_at, 0), b = m / p.R;
   const gfloat* src = (const gfloat*)p.qkv + (int64_t)m * p.qkvd + p.qd + hk * 64;
   const f32x4 a = *(const gf32x4*)(src + q8 * 4), bb = *(const gf32x4*)(src + 32 + q8 * 4);
   const gfloat* cs = (const gfloat*)p.cos_sin + ((int64_t)m * 32 + q8 * 4) * 2;
@@ -2138,6 +2139,7 @@ __global__ __launch_bounds__(256) void wide_append_kernel(FusedParams p, bf16_t*
     x0[e] = to_bf16(a[e] * c - bb[e] * sn);
     x1[e] = to_bf16(bb[e] * c + a[e] * sn);
   }
+  if (stored_at < 0) return;                                  // a row that only pads (tested behind the loads)
   const int64_t row = base + (int64_t)(slot & 31) * 64 + q8 * 4;
   *(uint64_t*)(trunk_k + row) = pack_bf16x4(x0[0], x0[1], x0[2], x0[3]);
   *(uint64_t*)(trunk_k + row + 32) = pack_bf16x4(x1[0], x1[1], x1[2], x1[3]);

@@ -48,7 +48,8 @@ __global__ void setup_branch_rows_kernel(RowDesc* rows, float* cos_sin, const in
 
 // Extend rows: token t of sequence b at position trunk_len+offset+t, causal (sees itself after the append).
 // rows of sequences seq_base .. seq_base + B - 1 (row m of the pass = token m % T of sequence seq_base + m / T)
-__global__ void setup_extend_rows_kernel(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, int B, int T,
+// limit (or null): sequence b stores the keys of its first limit[b] trunk positions only, rows behind them pad
+__global__ void setup_extend_rows_kernel(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, const int32_t* limit, int B, int T,
                                          int offset, int half_dim, float theta, int seq_base) {
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= B * T * half_dim) return;
@@ -57,7 +58,8 @@ __global__ void setup_extend_rows_kernel(RowDesc* rows, float* cos_sin, const in
   int pos = trunk_len[b] + offset + t;
   if (i == 0) {
     RowDesc r;
-    r.seq = b; r.pos = pos; r.vis = pos + 1; r.suffix_len = 0; r.kv_slot = pos; r.is_branch = 0;
+    r.seq = b; r.pos = pos; r.vis = pos + 1; r.suffix_len = 0; r.is_branch = 0;
+    r.kv_slot = limit && pos >= limit[b] ? -1 : pos;
     rows[m] = r;
   }
   write_cos_sin(cos_sin, m, half_dim, i, pos, theta);
@@ -280,9 +282,9 @@ int launch_setup_branch_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk
   return SSD_OK;
 }
 
-int launch_setup_extend_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, int B, int T, int offset,
+int launch_setup_extend_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, const int32_t* limit, int B, int T, int offset,
                              int half_dim, float theta, int seq_base, hipStream_t s) {
-  setup_extend_rows_kernel<<<grid_for((int64_t)B * T * half_dim), kBlock, 0, s>>>(rows, cos_sin, trunk_len, B, T,
+  setup_extend_rows_kernel<<<grid_for((int64_t)B * T * half_dim), kBlock, 0, s>>>(rows, cos_sin, trunk_len, limit, B, T,
                                                                                  offset, half_dim, theta, seq_base);
   SSD_HIP(hipGetLastError());
   return SSD_OK;

@@ -111,6 +111,7 @@ struct ssd_ctx {
   bool have_cache = false;
   // state
   int32_t* trunk_len;
+  int32_t* prompt_len = nullptr;         // lengths of the prompts a prefill is working on
   std::vector<void*> trunk_k, trunk_v;   // per layer [B][max_trunk][Hkv][D]
   std::vector<void*> suffix_k, suffix_v; // per layer [M][K][Hkv][D]
   // speculation cache
@@ -408,11 +409,13 @@ int pages_upload(ssd_ctx* c, hipStream_t s) {
   return SSD_OK;
 }
 
-// Before a pass that writes trunk positions up to (bound of sequence b) + extra of sequences [b0, b0 + nb)
-int pages_for_pass(ssd_ctx* c, int b0, int nb, int extra, hipStream_t s) {
+// Before a pass that writes trunk positions up to (bound of sequence b) + extra of sequences [b0, b0 + nb), and with limit
+// (nb lengths) none from limit[b - b0] on
+int pages_for_pass(ssd_ctx* c, int b0, int nb, int extra, const int32_t* limit, hipStream_t s) {
   if (!c->kv_pages) return SSD_OK;
   bool dirty = false;
-  for (int b = b0; b < b0 + nb; ++b) SSD_TRY(pages_ensure(c, b, c->ub_of[b] + extra, &dirty));
+  for (int b = b0; b < b0 + nb; ++b)
+    SSD_TRY(pages_ensure(c, b, limit ? std::min(c->ub_of[b] + extra, limit[b - b0]) : c->ub_of[b] + extra, &dirty));
   return dirty ? pages_upload(c, s) : SSD_OK;
 }
 
@@ -590,52 +593,72 @@ bool takes_small_pass(const ssd_ctx* c, int M, hipStream_t s) {
   return hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
 }
 
-// Extend of sequences [b0, b0 + nb): tokens [nb][T], outputs [nb][T][..]
-int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset, float* logits, float* hidden, int b0, int nb, hipStream_t s) {
+// Extend of sequences [b0, b0 + nb): tokens [nb][T], outputs [nb][T][..].  h_limit: the sequences' lengths, also in prompt_len on the
+// device: rows behind them pad a wide pass, take no pages and leave nothing in the trunk.
+int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset, float* logits, float* hidden, int b0, int nb, hipStream_t s,
+                const int32_t* h_limit = nullptr) {
   const Dims& d = c->model->dims;
-  SSD_TRY(pages_for_pass(c, b0, nb, offset + T, s));
-  SSD_TRY(launch_setup_extend_rows(c->rows, c->cos_sin, c->trunk_len, nb, T, offset, d.head_dim / 2, d.rope_theta, b0, s));
+  SSD_TRY(pages_for_pass(c, b0, nb, offset + T, h_limit, s));
+  SSD_TRY(launch_setup_extend_rows(c->rows, c->cos_sin, c->trunk_len, h_limit ? c->prompt_len : nullptr, nb, T, offset, d.head_dim / 2,
+                                   d.rope_theta, b0, s));
   int ub = 0;
   for (int b = b0; b < b0 + nb; ++b) ub = c->ub_of[b] > ub ? c->ub_of[b] : ub;
   if (wide && takes_small_pass(c, nb * T, s)) wide = false;
   return forward_rows(c, wide, nb * T, tokens, T, ub + offset, -1, logits, d.vocab, hidden, d.d_model, b0, s);
 }
 
+// What a prompt pass of `rows` rows costs, in rows: the weights it streams, its launches, and one more step where the row groups
+// of 128 begin (1B shape, ms: 64 rows 1.13, 128 1.32, 256 1.69, 384 1.91, 385 2.21, 512 2.38, 768 2.98, 1024 3.43; as a persistent
+// pass 10 rows 0.66, 48 rows 0.80.  Narrower models pay more for a pass and less for a row).
+int prompt_pass_cost(const ssd_ctx* c, int rows) {
+  if (rows <= kFusedMaxRows && c->small_passes) return 300;
+  return 450 + rows + (rows > kFusedWideRows ? 80 : 0);
+}
+
+// The next sequences whose prompts share passes (wide_prefill), all padded to the longest of them: as many as fit kFusedWideRows
+// padded rows, and further such groups as long as all fit the largest pass and it is cheaper with them than with a pass for each
+// of the two parts (1B shape, ms: lengths 300 and 200 2.70 in one pass, 3.29 in two; 340, 10 and 10 3.15 in one, 2.49 in two).
+int next_prompt_group(const ssd_ctx* c, const int32_t* lens, int n) {
+  auto rows = [&](int i0, int count) { return std::min<int>(*std::max_element(lens + i0, lens + i0 + count), c->prompt_rows) * count; };
+  auto small_group = [&](int i0) {
+    int count = 1;
+    while (i0 + count < n && rows(i0, count + 1) <= kFusedWideRows) ++count;
+    return count;
+  };
+  int count = small_group(0);
+  while (count < n) {
+    const int more = small_group(count), all = rows(0, count + more);
+    const int apart = prompt_pass_cost(c, rows(0, count)) + prompt_pass_cost(c, rows(count, more));
+    if (all > c->prompt_rows || prompt_pass_cost(c, all) >= apart) break;
+    count += more;
+  }
+  return count;
+}
+
 // KV of positions 0 .. max(len)-1 of sequences [b0, b0 + nb) (their trunk_len is 0): extend passes over d_tokens
-// [nb][stride].  In contexts that prefill in wide passes a pass takes as many tokens of a sequence as a wide pass has room
-// for, and several sequences where their prompts are short: a pass streams every weight once, so what a prompt costs is its
-// number of passes (a 1020-token prompt of the 1B shape: 3 passes of 340 rows instead of 170 passes of K+1 = 6 rows).
-// Otherwise chunks of K+1 tokens of all sequences.  Contexts whose rounds are narrow passes also take such a chunk where it
-// holds the whole prompts of a group: one persistent launch is shorter than a wide pass of as few rows (1B shape, 6 rows 0.65
-// against 0.90 ms, 48 rows 0.78 against 1.03), two of them are not (7 tokens in chunks of 6: 1.3 against 0.89 ms).
+// [nb][stride].  In contexts that prefill in wide passes a pass takes as many tokens of a sequence as prompt_rows allows, and
+// several sequences where their prompts are short: a pass streams every weight once, so what a prompt costs is above all its
+// number of passes.  Otherwise chunks of K+1 tokens of all sequences.  Contexts whose rounds are narrow passes also take such a
+// chunk where it holds the whole prompts of a group: one persistent launch is shorter than a wide pass of as few rows (1B shape,
+// 6 rows 0.65 against 0.90 ms, 48 rows 0.80 against 1.05).
 int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t* lens, int b0, int nb, hipStream_t s) {
   const int K1 = c->K + 1;
   for (int g0 = 0, gn = 0; g0 < nb; g0 += gn) {
-    int max_len = 0, T = K1;
-    gn = nb;
-    if (c->wide_prefill) {
-      // a group: the next sequences that fit one pass with the whole chunk of each
-      T = 0;
-      for (gn = 0; g0 + gn < nb; ++gn) {
-        const int want = std::max(T, std::min<int>(lens[g0 + gn], c->prompt_rows));
-        if (gn > 0 && want * (gn + 1) > c->prompt_rows) break;
-        T = want;
-      }
-    }
+    gn = c->wide_prefill ? next_prompt_group(c, lens + g0, nb - g0) : nb;
+    int max_len = 0;
     for (int b = g0; b < g0 + gn; ++b) max_len = std::max<int>(max_len, lens[b]);
     const bool wide = c->wide_prefill && (c->fused_wide || max_len > K1);
-    if (wide) {
-      // full passes and a shorter last one
-      T = std::min(max_len, c->prompt_rows);
-    } else {
-      T = K1;
-    }
+    // wide: full passes and a shorter last one
+    const int T = wide ? std::min(max_len, c->prompt_rows) : K1;
+    // The padding of several prompts in one large pass is not stored: it would take pages of a pool that holds the prompts
+    const bool bounded = wide && gn > 1 && gn * T > kFusedWideRows;
+    if (bounded) SSD_HIP(hipMemcpyAsync(c->prompt_len + b0 + g0, lens + g0, sizeof(int32_t) * gn, hipMemcpyHostToDevice, s));
     for (int start = 0; start < max_len; start += T) {
       const int Tn = wide ? std::min(T, max_len - start) : T;
       const int n = gn * Tn;
       gather_chunk_tokens_kernel<<<(n + 255) / 256, 256, 0, s>>>(c->step_tokens, d_tokens + (int64_t)g0 * stride, stride, gn, Tn, start);
       SSD_HIP(hipGetLastError());
-      SSD_TRY(extend_rows(c, wide || c->fused_wide, c->step_tokens, Tn, start, nullptr, nullptr, b0 + g0, gn, s));
+      SSD_TRY(extend_rows(c, wide || c->fused_wide, c->step_tokens, Tn, start, nullptr, nullptr, b0 + g0, gn, s, bounded ? lens + g0 : nullptr));
     }
   }
   return SSD_OK;
@@ -919,6 +942,7 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
   int st = SSD_OK;
   auto A = [&](void** p, size_t bytes) { if (st == SSD_OK) st = c->arena.alloc(p, bytes); };
   A((void**)&c->trunk_len, sizeof(int32_t) * c->B);
+  A((void**)&c->prompt_len, sizeof(int32_t) * c->B);
   c->trunk_k.resize(d.n_layers); c->trunk_v.resize(d.n_layers);
   c->suffix_k.resize(d.n_layers); c->suffix_v.resize(d.n_layers);
   // the fused pass serves every pass of a context it fits, unless the configuration's flags say otherwise
@@ -1149,7 +1173,10 @@ int ssd_ctx_prefill(ssd_ctx* c, const int32_t* d_tokens, int32_t stride, const i
       for (int b = 0; b < c->B; ++b) pages_release_beyond(c, b, 0, &dirty);
     }
   }
-  SSD_TRY(prefill_rows(c, d_tokens, stride, h_lens, 0, c->B, s));
+  if (const int st = prefill_rows(c, d_tokens, stride, h_lens, 0, c->B, s); st != SSD_OK) {
+    (void)hipStreamSynchronize(s);    // (copies of h_lens may be under way)
+    return st;
+  }
   SSD_HIP(hipMemcpyAsync(c->trunk_len, h_lens, sizeof(int32_t) * c->B, hipMemcpyHostToDevice, s));
   SSD_HIP(hipStreamSynchronize(s));   // h_lens is caller-owned pageable memory
   set_bounds(c, h_lens);

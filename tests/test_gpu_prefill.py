@@ -107,6 +107,35 @@ def test_prompt_passes_at_the_edges_of_their_row_groups(B, width, lens, paged):
         B.ssd_model_destroy(model)
 
 
+@pytest.mark.parametrize("lens,pages", [([340, 10, 10], 13), ([250, 1, 1, 1], 11), ([500, 300], 26), ([470, 510], 31), ([190, 180, 10, 12], 14),
+                                        ([60] * 6 + [20], 13)],
+                         ids=lambda x: "-".join(map(str, x[:4])) if isinstance(x, list) else str(x))
+def test_unequal_prompts_take_no_pages_for_rows_that_only_pad(B, lens, pages):
+    """Prompts of different lengths in a pool that holds them and no more: rows that pad a large pass to its longest prompt are not
+    stored (attention units that append themselves, up to 64 rows per sequence, and the pass that appends first)."""
+    print(f"[case] prefill of {lens} in {pages} pages", flush=True)
+    nb, max_trunk, seed = len(lens), max(lens) + 2 * K + 8, 13 + sum(lens)
+    assert pages == sum((n + 31) // 32 for n in lens)
+    model = B.ssd_model_create(SHAPE, I.make_weights(SHAPE, 11))
+    prompt, last = dev_i32(I.make_prompt(SHAPE, nb, max(lens), seed)), dev_i32(np.arange(nb).reshape(nb, 1))
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags, n) for flags, n in ((0, 1 + pages), (B.SSD_CTX_NARROW_PASSES, 0))]
+    try:
+        got = []
+        for ctx in ctxs:
+            B.ssd_ctx_prefill(ctx, prompt, lens)
+            z = torch.zeros((nb, 1, SHAPE.vocab), dtype=torch.float32, device="cuda")
+            B.ssd_ctx_extend(ctx, last, 0, z)
+            torch.cuda.synchronize()
+            B.ssd_ctx_status(ctx)
+            got.append(z.cpu().numpy())
+        assert B.ssd_ctx_kv_pages(ctxs[0]) == (1 + pages, 0)
+        assert row_rel_err(got[0], got[1]) < 2 * TOL_BF16_OWN_PREFILL
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
 @pytest.mark.parametrize("lens", [[1], [K], [K + 1], [K + 1, 1], [2, K, 1]], ids=lambda x: "-".join(map(str, x)))
 def test_prompts_of_one_chunk_take_the_narrow_pass(B, lens):
     """Where the rounds are narrow passes and a chunk of K+1 tokens holds the prompts, the prefill is that one narrow pass, to
