@@ -463,10 +463,15 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_rows_kernel(const float* 
 #pragma unroll
     for (int u = 0; u < U; ++u) ahead[u] = z[(uint32_t)min(t0 + u * kVerifyBlock, last)];
   };
-  load(lo + threadIdx.x);                                               // (on its way while the temperature is read)
+  // (a target row is on its way while the temperature is read; a draft row waits for it: that of a greedy sequence is not read.
+  // 16 greedy sequences of K = 5 with draft logits 17.3 -> 15.4 us, half of them sampled 42.4 -> 41.9)
+  if (r <= K) load(lo + threadIdx.x);
   const double T = zd ? (double)temperature[b] : 0.0;
   const bool sampled = T > 0.0;
-  if (r > K && !sampled) return;                                        // a draft row of a greedy sequence
+  if (r > K) {
+    if (!sampled) return;                                               // a draft row of a greedy sequence
+    load(lo + threadIdx.x);
+  }
   const double inv_t = sampled ? 1.0 / T : 0.0;
   if (sampled) {
     exp_table_init(table);
