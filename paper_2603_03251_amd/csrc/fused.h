@@ -26,6 +26,7 @@ constexpr int kFusedWideSlices = 8;       // wide passes: most k-slices of the o
 constexpr int kFusedWideRowGroup = 96;    // wide passes: rows of a full row group of a linear layer
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())
 constexpr int kFusedMaxSlices = 4;   // most k-slices of a linear layer
+constexpr int kFusedMaxSplits = 16;  // most key splits of an attention pass
 constexpr unsigned kFusedSpinLimit = 4000000u;   // polls of a bounded wait (seconds of wall time) before it gives up
 
 // A linear layer in "stream order".  The [N][Kd] matrix is cut into 1 KiB MFMA tiles (16 features x 32 inputs,

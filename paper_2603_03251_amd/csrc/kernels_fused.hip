@@ -1062,7 +1062,7 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
       const int q = threadIdx.x & 15, dq = threadIdx.x >> 4;
       const int qrow = qt * 16 + q;
       if (qrow < RG) {
-        constexpr int kMaxSplits = 16;
+        constexpr int kMaxSplits = kFusedMaxSplits;
         const int64_t pb0 = ((int64_t)(b * p.Hkv + hk) * p.NS) * (p.QT * 16) + qrow, pstep = p.QT * 16;
         uint64_t mlv[kMaxSplits];
 #pragma unroll

@@ -468,7 +468,7 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
     p.NQ = 0;
     for (int nq = 1; nq <= (wide ? kFusedWideQueryTiles : 1); ++nq) {
       const int pairs = seqs * p.Hkv * ((p.QT + nq - 1) / nq);
-      for (int ns = 1; ns <= ns_cap && ns <= 16; ++ns) {
+      for (int ns = 1; ns <= ns_cap; ++ns) {
         const int keys = (p_ub + ns - 1) / ns;
         const int blocks = ((keys + 31) / 32 + kFusedWaves - 1) / kFusedWaves;
         const int rounds = (pairs * ns + p.nwg - 1) / p.nwg;
@@ -702,7 +702,7 @@ int fused_setup(ssd_ctx* c) {
   const int64_t tiles = std::max<int64_t>(c->fused_wide ? 0 : (int64_t)p.B * qt_max, small_tiles);
   if (narrow) {
     // narrow passes split short trunks too (their units merge the splits themselves, at no barrier)
-    c->part.ns_max = std::max((c->max_trunk + 2047) / 2048 + 1, 8);
+    c->part.ns_max = std::min(std::max((c->max_trunk + 2047) / 2048 + 1, 8), kFusedMaxSplits);
     c->part.entries = p.Hkv * c->part.ns_max * tiles * 16;
     p.part_layer_stride = c->part.entries;
     A((void**)&p.part_o, (size_t)L * c->part.entries * 64 * 4);
@@ -790,7 +790,7 @@ int fused_setup(ssd_ctx* c) {
     w = p;
     const size_t MW = (size_t)c->prompt_rows;
     // query rows of a pass: whole 16-row tiles per sequence
-    c->part_wide.ns_max = (c->max_trunk + 2047) / 2048 + 1;
+    c->part_wide.ns_max = std::min((c->max_trunk + 2047) / 2048 + 1, kFusedMaxSplits);
     c->part_wide.entries = (int64_t)p.Hkv * c->part_wide.ns_max * ((int64_t)MW * p.G + 16 * std::min(c->B, (int)MW));
     // partial sums of o and down: eight slices of a row group of 96, two of 384 rows (which is what gives every pair of 64
     // features x 96 rows a workgroup at the 1B shape).  They lie where the qkv projections were: written after the

@@ -806,3 +806,26 @@ def test_two_fused_contexts_on_two_streams_take_turns(B):
             B.ssd_ctx_destroy(c)
         for m in models:
             B.ssd_model_destroy(m)
+
+
+@pytest.mark.parametrize("flags", [0, 4], ids=["wide", "narrow"])
+def test_workspace_of_long_trunks_stays_bounded(B, flags):
+    """A pass splits its keys at most 16 ways: beyond the trunks it was made for (32768 positions) a context grows by its KV store
+    only, not by room for partial results of splits that are never made."""
+    shape = I.ModelShape(n_layers=2, d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=64, d_ffn=2048, vocab=4112, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    nb, K, F, sizes, taken = 4, 3, 4, (32768, 98304), []
+    model = B.ssd_model_create(shape, I.make_weights(shape, 3))
+    try:
+        for max_trunk in sizes:
+            torch.cuda.synchronize()
+            before = torch.cuda.mem_get_info()[0]
+            ctx = B.ssd_ctx_create(model, nb, K, F, max_trunk, flags)
+            taken.append(before - torch.cuda.mem_get_info()[0])
+            B.ssd_ctx_destroy(ctx)
+    finally:
+        B.ssd_model_destroy(model)
+    kv = (sizes[1] - sizes[0]) * nb * shape.n_layers * 2 * shape.n_kv_heads * 64 * 2
+    print(f"[memory] {taken[0] >> 20} and {taken[1] >> 20} MiB, KV store {kv >> 20} MiB more", flush=True)
+    # (allocations come in pieces of up to 2 MiB, two KV arrays per layer)
+    assert taken[1] - taken[0] - kv <= 6 << 20
