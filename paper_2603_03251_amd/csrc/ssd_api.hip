@@ -427,6 +427,38 @@ void set_bounds(ssd_ctx* c, const int32_t* lens) {
   }
 }
 
+// Attention work of a pass: how many key splits of the stored trunk, and in wide passes query tiles per unit, its units take.
+struct AttnPlan {
+  int nq, ns;
+  float cost;   // us of the phase, as estimated
+};
+
+// The attention phase lasts (rounds of units over the grid) x (a unit's 32-key blocks per wavefront + its fixed part, which grows
+// with its tiles), and more than one split adds a merge (a phase of its own in wide passes, the last unit of a tile to arrive in
+// narrow ones: its arrival count and the other splits' partial results each cost a memory round trip).  Costs in microseconds as
+// measured on the 1B shape; the choice only affects speed.  Few rows over a short trunk fill the chip with units of one tile (24
+// rows x 4 sequences, 1500 keys: 14.4 us, 17.8 with three); over a long one they are shorter as three-tile units with the keys
+// split (8000 keys: 16.6 us less, 3000: 1.4 less), and tiles beyond one per compute unit share a unit before they wait for a
+// second round (24 rows x 16 sequences, 8000 keys: two and one tiles 33 and 66 us more than three).
+// seqs: sequences of a pass; tiles: 16-row query tiles of a sequence and KV head; keys: stored keys a row sees at most.
+AttnPlan plan_attention(const ssd_ctx* c, bool wide, int seqs, int tiles, int keys) {
+  const FusedParams& p = wide ? c->fpw : c->fp;
+  const int ns_cap = (wide ? c->part_wide : c->part).ns_max;   // what the partial-softmax buffers were sized for
+  const float merge_cost = wide ? 5.0f : 4.0f;
+  AttnPlan best = {0, 1, 0.f};
+  for (int nq = 1; nq <= (wide ? kFusedWideQueryTiles : 1); ++nq) {
+    const int pairs = seqs * p.Hkv * ((tiles + nq - 1) / nq);
+    for (int ns = 1; ns <= ns_cap; ++ns) {
+      const int keys_each = (keys + ns - 1) / ns;
+      const int blocks = ((keys_each + 31) / 32 + kFusedWaves - 1) / kFusedWaves;
+      const int rounds = (pairs * ns + p.nwg - 1) / p.nwg;
+      const float cost = rounds * (0.9f * blocks + 3.0f + 1.5f * (nq - 1)) + (ns > 1 ? merge_cost : 0.f);
+      if (best.nq == 0 || cost < best.cost) best = {nq, ns, cost};
+    }
+  }
+  return best;
+}
+
 // The same pass through the fused kernel: attention work split for this pass's shape, then one launch per group of
 // whole sequences that fits kFusedMaxRows rows (one launch for the few-row workloads the kernel is built for; a batch
 // with more rows streams the weights once per group).
@@ -451,32 +483,10 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
   const int p_ub = stored_ub > 1 ? stored_ub : 1;
   const int n_seq = M / rows_per_seq;
   const int per_pass = cap / rows_per_seq;
-  // Key splits of the stored trunk, and in wide passes query tiles per unit: the attention phase lasts (rounds of units over
-  // the grid) x (a unit's 32-key blocks per wavefront + its fixed part, which grows with its tiles), and more than one split
-  // adds a merge (a phase of its own in wide passes, the last unit of a tile to arrive in narrow ones: its arrival count and
-  // the other splits' partial results each cost a memory round trip).  Costs in microseconds as measured on the 1B shape; the
-  // choice only affects speed.  Few rows over a short trunk fill the chip with units of one tile (24 rows x 4 sequences, 1500
-  // keys: 14.4 us, 17.8 with three); over a long one they are shorter as three-tile units with the keys split (8000 keys: 16.6
-  // us less, 3000: 1.4 less), and tiles beyond one per compute unit share a unit before they wait for a second round (24 rows
-  // x 16 sequences, 8000 keys: two and one tiles 33 and 66 us more than three).
   {
-    const int seqs = n_seq < per_pass ? n_seq : (per_pass > 0 ? per_pass : 1);
-    int best = 1;
-    float best_cost = 0.f;
-    const int ns_cap = part.ns_max;                     // what the partial-softmax buffers were sized for
-    const float merge_cost = wide ? 5.0f : 4.0f;
-    p.NQ = 0;
-    for (int nq = 1; nq <= (wide ? kFusedWideQueryTiles : 1); ++nq) {
-      const int pairs = seqs * p.Hkv * ((p.QT + nq - 1) / nq);
-      for (int ns = 1; ns <= ns_cap; ++ns) {
-        const int keys = (p_ub + ns - 1) / ns;
-        const int blocks = ((keys + 31) / 32 + kFusedWaves - 1) / kFusedWaves;
-        const int rounds = (pairs * ns + p.nwg - 1) / p.nwg;
-        const float cost = rounds * (0.9f * blocks + 3.0f + 1.5f * (nq - 1)) + (ns > 1 ? merge_cost : 0.f);
-        if (p.NQ == 0 || cost < best_cost) { p.NQ = nq; best = ns; best_cost = cost; }
-      }
-    }
-    p.KPU = ((p_ub + best - 1) / best + 31) / 32 * 32;
+    const AttnPlan a = plan_attention(c, wide, n_seq < per_pass ? n_seq : (per_pass > 0 ? per_pass : 1), p.QT, p_ub);
+    p.NQ = a.nq;
+    p.KPU = ((p_ub + a.ns - 1) / a.ns + 31) / 32 * 32;
     p.NS = (p_ub + p.KPU - 1) / p.KPU;
   }
   if (per_pass < 1 || n_seq * rows_per_seq != M) {
@@ -586,9 +596,19 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
 // A pass of few rows in a context that runs wide passes: one persistent launch is shorter than seven launches per layer for as
 // long as it takes the rows (1B shape, one extend with logits over 1500 keys: 12 rows 0.89 against 1.14 ms, 24 rows 0.91 against
 // 1.17; 48 rows, which four and six row tiles of that kernel would extend: 54 rows 6 % shorter than a wide pass, 72 and 96 rows 10 %
-// longer).  Not into a graph that is being captured: persistent launches take turns by events, which a replay would not see.
-bool takes_small_pass(const ssd_ctx* c, int M, hipStream_t s) {
-  if (!c->small_passes || M > kFusedMaxRows) return false;
+// longer) and its attention units, which take one query tile where those of a wide pass take up to three, do not pull the
+// same keys too often.  What the launches and the earlier weight loads save was measured as 0.18 us per layer and million
+// weights of it, what the units cost more is what the plans of the two say (ms, 1B shape: 3 x 16 rows over 8192 keys 1.33
+// against 1.47 as a wide pass, over 16384 1.68 against 1.63, 131072 5.5 against 4.1; 6 x 8 rows 1.42, 1.54; 1.83, 1.81; 6.3, 5.5;
+// width 1024, 6 x 8 rows: 0.48, 0.53; 0.58, 0.59; 2.3, 1.5; sequences of one query tile stay shorter to the last length).
+// Not into a graph that is being captured: persistent launches take turns by events, which a replay would not see.
+// seqs x T rows, the longest trunk with stored keys a row sees.
+bool takes_small_pass(const ssd_ctx* c, int seqs, int T, int stored, hipStream_t s) {
+  if (!c->small_passes || seqs * T > kFusedMaxRows) return false;
+  const FusedParams& p = c->fp;
+  const int tiles = (T * p.G + 15) / 16, keys = stored > 1 ? stored : 1;
+  const float weights = (float)p.d * (p.qkvd + p.qd + 3.0f * p.ffn);
+  if (plan_attention(c, false, seqs, tiles, keys).cost > plan_attention(c, true, seqs, tiles, keys).cost + 0.18e-6f * weights) return false;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
 }
@@ -603,7 +623,7 @@ int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset,
                                    d.rope_theta, b0, s));
   int ub = 0;
   for (int b = b0; b < b0 + nb; ++b) ub = c->ub_of[b] > ub ? c->ub_of[b] : ub;
-  if (wide && takes_small_pass(c, nb * T, s)) wide = false;
+  if (wide && takes_small_pass(c, nb, T, ub + offset, s)) wide = false;
   return forward_rows(c, wide, nb * T, tokens, T, ub + offset, -1, logits, d.vocab, hidden, d.d_model, b0, s);
 }
 

@@ -322,3 +322,32 @@ def test_extends_of_few_rows_in_a_context_of_wide_passes(B, nb, T, paged):
         for ctx in ctxs:
             B.ssd_ctx_destroy(ctx)
         B.ssd_model_destroy(model)
+
+
+@pytest.mark.parametrize("nb,T,P,small", [(8, 6, 1500, True), (8, 6, 32768, False), (3, 16, 1500, True), (3, 16, 65536, False), (16, 3, 32768, True)])
+def test_few_rows_over_long_trunks_take_the_pass_that_reads_their_keys_once(B, nb, T, P, small):
+    """Sequences of several query tiles pull the same keys once per tile in the persistent pass: over long trunks they stay with the
+    wide pass (the bits of a context without the persistent kernel), over short ones and with one query tile (16 x 3 rows) they
+    take the persistent pass (the bits of a context of narrow passes)."""
+    print(f"[case] {nb} sequences of {P} keys, extend of {T} tokens", flush=True)
+    K, F, seed = max(T - 1, 3), 2, 5 + nb
+    shape = I.ModelShape(n_layers=2, d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=64, d_ffn=2048, vocab=4112, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, 3))
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, P + 2 * K + 8, flags) for flags in (0, B.SSD_CTX_FUSED_PHASES, B.SSD_CTX_NARROW_PASSES)]
+    try:
+        tokens, got = dev_i32(np.random.default_rng(seed).integers(0, shape.vocab, (nb, T))), []
+        for ctx in ctxs:
+            z = torch.zeros((nb, T, shape.vocab), dtype=torch.float32, device="cuda")
+            B.ssd_ctx_fill_synthetic_kv(ctx, [P - b for b in range(nb)], seed)
+            B.ssd_ctx_extend(ctx, tokens, 0, z)
+            torch.cuda.synchronize()
+            B.ssd_ctx_status(ctx)
+            got.append(z.cpu().numpy())
+        assert row_rel_err(got[1], got[2]) < 2 * TOL_WIDE_BF16
+        assert np.array_equal(got[0], got[2 if small else 1])
+        assert not np.array_equal(got[1], got[2])
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
