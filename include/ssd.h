@@ -327,6 +327,12 @@ int ssd_sample(const float* d_logits, int64_t ld, const float* d_temperature, in
  * only the tokens within the fp32 error bound of the maximum; both must give the same token). */
 int ssd_sample_fp64_scan(const float* d_logits, int64_t ld, const float* d_temperature, int32_t rows, int32_t V,
                          uint64_t seed, int32_t row_base, int32_t step, int32_t* d_out, void* stream);
+/* Test aid: the same draw as a round makes it, a row of more than 4096 tokens shared among several workgroups (ssd_sample takes
+ * one per row); fp64_scan != 0: every token scored in fp64.  d_workspace: ssd_sample_split_workspace_bytes(rows) bytes of device
+ * memory, 8-byte aligned, private to the call until `stream` has passed it.  Same token as ssd_sample. */
+int ssd_sample_split(const float* d_logits, int64_t ld, const float* d_temperature, int32_t rows, int32_t V, uint64_t seed,
+                     int32_t row_base, int32_t step, int32_t* d_out, void* d_workspace, int32_t fp64_scan, void* stream);
+size_t ssd_sample_split_workspace_bytes(int32_t rows);
 
 /* ---- generic extend (the glue step on its own; also how a target model is run) ------------------ */
 

@@ -91,6 +91,9 @@ EXPORTS = {
                              C.c_int32, C.c_void_p, C.c_void_p]),
     "ssd_sample_fp64_scan": (C.c_int, [C.c_void_p, C.c_int64, C.c_void_p, C.c_int32, C.c_int32, C.c_uint64, C.c_int32,
                                        C.c_int32, C.c_void_p, C.c_void_p]),
+    "ssd_sample_split": (C.c_int, [C.c_void_p, C.c_int64, C.c_void_p, C.c_int32, C.c_int32, C.c_uint64, C.c_int32,
+                                   C.c_int32, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p]),
+    "ssd_sample_split_workspace_bytes": (C.c_size_t, [C.c_int32]),
     "ssd_ctx_status": (C.c_int, [C.c_void_p]),
     "ssd_ctx_recover": (C.c_int, [C.c_void_p]),
     "ssd_ctx_debug_set": (C.c_int, [C.c_void_p, C.c_int32, C.c_uint32]),
@@ -356,6 +359,17 @@ def ssd_sample_fp64_scan(logits: torch.Tensor, temperature: torch.Tensor, seed: 
     rows, V = logits.shape
     _check(lib.ssd_sample_fp64_scan(_ptr(logits), V, _ptr(temperature), rows, V, seed, row_base, step, _ptr(out),
                                     _stream(stream)))
+
+
+def ssd_sample_split(logits: torch.Tensor, temperature: torch.Tensor, seed: int, row_base: int, step: int, out: torch.Tensor,
+                     workspace: torch.Tensor, fp64_scan: bool = False, vocab: Optional[int] = None, stream=None) -> None:
+    rows, ld = logits.shape
+    _check(lib.ssd_sample_split(_ptr(logits), ld, _ptr(temperature), rows, ld if vocab is None else vocab, seed, row_base, step, _ptr(out),
+                                _ptr(workspace), int(fp64_scan), _stream(stream)))
+
+
+def ssd_sample_split_workspace_bytes(rows: int) -> int:
+    return int(lib.ssd_sample_split_workspace_bytes(rows))
 
 
 def ssd_ctx_status(ctx: int) -> None:

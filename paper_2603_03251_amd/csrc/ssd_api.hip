@@ -1593,6 +1593,16 @@ int ssd_sample_fp64_scan(const float* d_logits, int64_t ld, const float* d_tempe
   return launch_sample(d_logits, ld, d_temperature, 1, rows, V, seed, row_base, step, d_out, 1, nullptr, 1, (hipStream_t)stream);
 }
 
+int ssd_sample_split(const float* d_logits, int64_t ld, const float* d_temperature, int32_t rows, int32_t V, uint64_t seed, int32_t row_base,
+                     int32_t step, int32_t* d_out, void* d_workspace, int32_t fp64_scan, void* stream) {
+  SSD_CHECK_ARG(d_logits && d_temperature && d_out && d_workspace, "ssd_sample_split: null argument");
+  SSD_CHECK_ARG(rows >= 0 && V >= 2 && ld >= V, "ssd_sample_split: rows >= 0, V >= 2, ld >= V required");
+  return launch_sample(d_logits, ld, d_temperature, 1, rows, V, seed, row_base, step, d_out, 1, d_workspace, fp64_scan != 0,
+                       (hipStream_t)stream);
+}
+
+size_t ssd_sample_split_workspace_bytes(int32_t rows) { return rows > 0 ? sample_scratch_bytes(rows) : 0; }
+
 int ssd_backup_random(uint64_t seed, int32_t B, int32_t K, int32_t V, int32_t* d_tokens, void* stream) {
   SSD_CHECK_ARG(d_tokens, "ssd_backup_random: null argument");
   SSD_CHECK_ARG(B >= 0 && K >= 0 && V >= 1 && (int64_t)B * K <= (1 << 24), "ssd_backup_random: B, K >= 0, V >= 1 required");

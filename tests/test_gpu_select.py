@@ -89,6 +89,22 @@ def test_sampler_greedy_and_gumbel(B, V, rows):
     assert (got != greedy).any()
 
 
+def _samplers(B, rows):
+    """Every route of the sampler, the fp64 scan of a row by one workgroup first (what the others have to give): a row as one
+    workgroup, and shared among several as a round does it."""
+    ws = torch.full((B.ssd_sample_split_workspace_bytes(rows),), 0xff, dtype=torch.uint8, device="cuda")
+    return (B.ssd_sample_fp64_scan, B.ssd_sample, lambda *a, **k: B.ssd_sample_split(*a, **k, workspace=ws),
+            lambda *a, **k: B.ssd_sample_split(*a, **k, workspace=ws, fp64_scan=True))
+
+
+def _part_starts(rows, V):
+    """First tokens of the workgroups that share a row (about 2048 in all, at most 128 per row, at least 1024 tokens each, whole
+    groups of four)."""
+    parts = max(1, min(-(-2048 // rows), -(-V // 1024), 128)) if V > 4096 else 1
+    per = -(-(-(-V // 4)) // parts)
+    return [4 * per * i for i in range(1, parts) if 4 * per * i < V]
+
+
 @pytest.mark.parametrize("V,rows,scale,temp", [(128256, 24, 1.0, 1.0), (128256, 48, 3.0, 0.3), (4099, 7, 50.0, 0.05),
                                                (128256, 6, 0.01, 2.0), (1024, 300, 1.0, 0.7)])
 def test_sampler_fp32_preselection_gives_the_fp64_token(B, V, rows, scale, temp):
@@ -107,7 +123,7 @@ def test_sampler_fp32_preselection_gives_the_fp64_token(B, V, rows, scale, temp)
     temps = dev_f32(np.full(rows, temp, np.float32))
     zd = dev_f32(z)
     outs = []
-    for sample in (B.ssd_sample_fp64_scan, B.ssd_sample):
+    for sample in _samplers(B, rows):
         per_step = []
         for step in range(3):
             out = torch.full((rows,), -5, dtype=torch.int32, device="cuda")
@@ -115,32 +131,73 @@ def test_sampler_fp32_preselection_gives_the_fp64_token(B, V, rows, scale, temp)
             torch.cuda.synchronize()
             per_step.append(out.cpu().numpy())
         outs.append(np.stack(per_step))
-    assert np.array_equal(outs[0], outs[1])
+    assert all(np.array_equal(outs[0], o) for o in outs[1:])
     if rows > 3:
         assert (outs[1][:, 3] == 11).all()
     # and it is a sample, not the argmax: steps differ somewhere
     assert (outs[1][0] != outs[1][1]).any() or rows <= 7
 
 
-@pytest.mark.parametrize("V", [1023, 1025, 5121, 40003])
-@pytest.mark.parametrize("stride", [0, 1, 1024, 4096, 5120])
-def test_sampler_candidates_that_fp32_cannot_order(B, V, stride):
-    """A thread of the sampler takes every 1024th token.  All tokens (stride 0), or one token and its neighbour at `stride` (the
-    same thread's, or another's), have scores that differ only by the rounding of the logits."""
-    seed, T, rows, g = 11, 0.5, 5, np.random.default_rng(V + stride)
+@pytest.mark.parametrize("V,rows,stride", [(V, rows, s) for V, rows in ((1023, 5), (1025, 5), (4097, 5), (5121, 5), (40003, 5), (128256, 2))
+                                           for s in (0, 1, 256, 512, 768, 1024, 4096, 5120, -1)] +
+                         [(V, rows, s) for V, rows in ((40003, 800), (128256, 700)) for s in (0, 256, -1)])
+def test_sampler_candidates_that_fp32_cannot_order(B, V, rows, stride):
+    """A thread of the sampler takes every 1024th token, or every 256th of its workgroup's part of the row.  All tokens (stride 0),
+    or one token and its neighbour at `stride` (the same thread's, another's, another workgroup's; -1: the tokens on both sides of
+    a boundary between parts), have scores that differ only by the rounding of the logits.  128 to 3 parts per row, the last one short."""
+    seed, T, g = 11, 0.5, np.random.default_rng(V + stride + 1)
+    starts, distinct = _part_starts(rows, V), min(rows, 5)
     z = np.empty((rows, V), np.float32)
     for r in range(rows):
+        if r >= distinct:                                       # (the same logits under other noise: far apart)
+            z[r] = z[r % distinct]
+            continue
         level = np.full(V, 3.0 if stride == 0 else -3.0)
-        if stride:
+        if stride > 0:
             t = int(g.integers(0, max(1, V - stride)))
             level[[t, min(t + stride, V - 1)]] = 3.0
+        elif stride < 0:
+            t = int(g.choice(starts)) if starts else V // 2
+            level[[t - 1, t]] = 3.0
         z[r] = (level - O.gumbel(seed, O.STREAM_DRAFT, r, 2, V)) * T
     temps, zd, outs = dev_f32(np.full(rows, T, np.float32)), dev_f32(z), []
-    for sample in (B.ssd_sample_fp64_scan, B.ssd_sample):
+    for sample in _samplers(B, rows):
         out = torch.full((rows,), -5, dtype=torch.int32, device="cuda")
         sample(zd, temps, seed=seed, row_base=0, step=2, out=out)
         outs.append(out.cpu().numpy())
-    assert np.array_equal(outs[0], outs[1])
+    assert all(np.array_equal(outs[0], o) for o in outs[1:])
+
+
+@pytest.mark.parametrize("V,rows,gap", [(V, rows, gap) for V, rows in ((4096, 3), (4097, 3), (5121, 7), (40003, 1), (128256, 24)) for gap in (0, 4, 5)] +
+                         [(128256, 1024, 0), (131072, 2100, 0)])
+def test_sampler_rows_shared_among_workgroups(B, V, rows, gap):
+    """Greedy and sampled rows side by side, from 128 workgroups per row to one, row strides that allow 16-byte loads and such
+    that do not; maxima that tie across parts, infinite and NaN logits, rows without any."""
+    g = torch.Generator(device="cuda").manual_seed(V + rows)
+    padded = torch.randn((rows, V + gap), generator=g, device="cuda")
+    padded[:, V:] = 20.0                                        # not part of any row
+    z = padded[:, :V]
+    starts = _part_starts(rows, V)
+    for t in [0, V - 1] + ([starts[0], starts[0] - 1, starts[-1]] if starts else []):
+        z[0, t] = 9.0                                           # the lowest id wins a greedy row
+    z[1 % rows, V // 2:] = float("nan")
+    if rows > 4:
+        z[2] = float("-inf")
+        z[3] = float("nan")
+        z[4, [V - 2, V // 3]] = float("inf")
+    temps = dev_f32(np.where(np.arange(rows) % 2 == 0, 0.0, 0.8))
+    for shift in (0, 1):                                        # every row greedy once and sampled once
+        temps, outs = temps.roll(shift), []
+        for i, sample in enumerate(_samplers(B, rows)):         # (the calls without a workspace take whole rows)
+            out = torch.full((rows,), -5, dtype=torch.int32, device="cuda")
+            if i < 2:
+                sample(z.contiguous(), temps, seed=3, row_base=5, step=1, out=out)
+            else:
+                sample(padded, temps, seed=3, row_base=5, step=1, out=out, vocab=V)
+            outs.append(out)
+        assert all(torch.equal(outs[0], o) for o in outs[1:])
+        if shift == 0:
+            assert int(outs[0][0]) == 0
 
 
 def _verify_case(B, V, K, nb, seed, temps, close_draft):
