@@ -351,3 +351,116 @@ def test_few_rows_over_long_trunks_take_the_pass_that_reads_their_keys_once(B, n
         for ctx in ctxs:
             B.ssd_ctx_destroy(ctx)
         B.ssd_model_destroy(model)
+
+
+@pytest.mark.parametrize("heads_kv,base,F,paged", [(4, 1024, 2, False), (4, 1024, 16, True), (4, 4096, 2, True), (8, 4096, 16, False), (1, 4096, 2, False), (1, 1024, 16, True)])
+def test_remainders_of_prompts_on_the_persistent_pass(B, heads_kv, base, F, paged):
+    """What full passes of 1024 rows leave of a prompt, 16 to 48 rows of ONE sequence, in one persistent launch: one and two blocks of
+    the pass's own keys, 2 to 48 query tiles per head, key splits over the longer prompts; 49 rows are a wide pass.  In contexts of
+    narrow and of wide rounds, against chunks of K+1 tokens."""
+    shape = I.ModelShape(n_layers=2, d_model=1024, n_q_heads=16, n_kv_heads=heads_kv, head_dim=64, d_ffn=2048, vocab=4112, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    model, max_trunk = B.ssd_model_create(shape, I.make_weights(shape, 17)), base + 49 + 2 * K + 8
+    prompt, last = dev_i32(I.make_prompt(shape, 1, base + 49, 23)), dev_i32([[7]])
+    pages = 1 + (max_trunk + 31) // 32 if paged else 0
+    ctxs = [B.ssd_ctx_create(model, 1, K, f, max_trunk, flags, n)
+            for flags, f, n in ((0, F, pages), (B.SSD_CTX_FUSED_PHASES, F, pages), (B.SSD_CTX_NARROW_PASSES, 2, 0))]
+    try:
+        for r in (16, 17, 32, 33, 47, 48, 49):
+            print(f"[case] {base} + {r} tokens, {heads_kv} KV heads, F {F}, paged {paged}", flush=True)
+            got = []
+            for ctx in ctxs:
+                B.ssd_ctx_prefill(ctx, prompt, [base + r])
+                z = torch.zeros((1, 1, shape.vocab), dtype=torch.float32, device="cuda")
+                B.ssd_ctx_extend(ctx, last, 0, z)
+                torch.cuda.synchronize()
+                B.ssd_ctx_status(ctx)
+                ks, vs = ([], []) if paged else _trunk(B, ctx, [base + r], max_trunk, shape)
+                got.append((z.cpu().numpy(), [x[0][base:] for x in ks + vs]))
+            assert row_rel_err(got[0][0], got[2][0]) < 2 * TOL_BF16_OWN_PREFILL, r
+            for a, b in zip(got[0][1], got[2][1]):
+                assert row_rel_err(a, b) < 2 * TOL_BF16_OWN_PREFILL, r
+            if not paged:                                      # the pass that the remainder takes: its keys' bits
+                same = all(np.array_equal(a, b) for a, b in zip(got[0][1], got[1][1]))
+                assert same == (r > 48), r
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
+def test_expired_wait_and_recovery_in_a_context_of_wide_passes(B):
+    """The glue extend of a small batch is a persistent launch also where the rounds are wide passes: with a limit of one poll its
+    bounded waits expire and every workgroup leaves the kernel.  The context reports it, refuses the hot calls, and computes the
+    same bits again after ssd_ctx_recover."""
+    nb, P, F, seed = 4, 75, 4, 9
+    shape = I.ModelShape(n_layers=2, d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=64, d_ffn=2048, vocab=4112, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, 3))
+    ctx = B.ssd_ctx_create(model, nb, K, F, P + 4 * K + 8)
+    try:
+        assert B.ssd_ctx_views(ctx).pass_rows == 384
+        pending, temps = dev_i32(I.make_pending(shape, nb, K, seed)), dev_f32(np.zeros(nb))
+        B.ssd_ctx_fill_synthetic_kv(ctx, [P] * nb, seed)
+        B.ssd_prespeculate(ctx, pending, temps, 1)
+        good = {k: v.cpu().numpy() for k, v in B.read_cache(ctx).items()}
+        B.ssd_ctx_status(ctx)
+        B.ssd_ctx_debug_set(ctx, B.SSD_DEBUG_SPIN_LIMIT, 1)
+        print("[fault] launching one extend whose bounded waits expire after one poll", flush=True)
+        B.ssd_ctx_extend(ctx, pending, 0, None)
+        torch.cuda.synchronize()
+        for call in (lambda: B.ssd_ctx_status(ctx), lambda: B.ssd_prespeculate(ctx, pending, temps, 1), lambda: B.ssd_ctx_extend(ctx, pending, 0, None)):
+            with pytest.raises(B.SsdError) as e:
+                call()
+            assert e.value.status == B.SSD_EHIP
+        B.ssd_ctx_debug_set(ctx, B.SSD_DEBUG_SPIN_LIMIT, 0)
+        B.ssd_ctx_recover(ctx)
+        B.ssd_ctx_fill_synthetic_kv(ctx, [P] * nb, seed)
+        B.ssd_prespeculate(ctx, pending, temps, 1)
+        again = {k: v.cpu().numpy() for k, v in B.read_cache(ctx).items()}
+        B.ssd_ctx_refresh_bounds(ctx)
+        for name in ("keys", "tokens", "logits", "hidden", "glue_logits"):
+            assert np.array_equal(good[name], again[name]), name
+    finally:
+        B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
+def test_captured_extend_of_few_rows_takes_the_wide_pass(B):
+    """Persistent launches take turns by events, which a replay would not see: inside a stream capture the extend of a context of wide
+    passes is wide launches (the bits of a context without the persistent kernel).  Replayed with eager work in between."""
+    nb, T, P, F, seed = 4, 4, 200, 4, 9
+    shape = I.ModelShape(n_layers=2, d_model=1024, n_q_heads=16, n_kv_heads=4, head_dim=64, d_ffn=2048, vocab=4112, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, 3))
+    ctx, wide = (B.ssd_ctx_create(model, nb, K, F, P + 4 * K + 8, flags) for flags in (0, B.SSD_CTX_FUSED_PHASES))
+    try:
+        sets = [dev_i32(np.random.default_rng(i).integers(0, shape.vocab, (nb, T))) for i in range(4)]
+        tokens, z = sets[0].clone(), torch.zeros((nb, T, shape.vocab), dtype=torch.float32, device="cuda")
+        eager = torch.zeros_like(z)
+        for c in (ctx, wide):
+            B.ssd_ctx_fill_synthetic_kv(c, [P - b for b in range(nb)], seed)
+        want = []
+        for t in sets:
+            B.ssd_ctx_extend(wide, t, 0, z)
+            want.append(z.clone())
+        B.ssd_ctx_extend(ctx, tokens, 0, eager)                # (first launches outside the capture)
+        torch.cuda.synchronize()
+        graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(graph, stream=stream):
+            B.ssd_ctx_extend(ctx, tokens, 0, z, stream=stream)
+        for t, w in zip(sets, want):
+            tokens.copy_(t)
+            z.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(z, w)
+            B.ssd_ctx_extend(ctx, t, 0, eager)                 # eager work between the replays: the persistent pass
+            torch.cuda.synchronize()
+            assert not torch.equal(eager, w)
+            assert row_rel_err(eager.cpu().numpy(), w.cpu().numpy()) < 2 * TOL_WIDE_BF16
+        B.ssd_ctx_status(ctx)
+    finally:
+        for c in (ctx, wide):
+            B.ssd_ctx_destroy(c)
+        B.ssd_model_destroy(model)
