@@ -671,7 +671,7 @@ int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t*
     // wide: full passes and a shorter last one
     const int T = wide ? std::min(max_len, c->prompt_rows) : K1;
     // The padding of several prompts in one large pass is not stored: it would take pages of a pool that holds the prompts
-    const bool bounded = wide && gn > 1 && gn * T > kFusedWideRows;
+    const bool bounded = wide && gn * T > kFusedWideRows && *std::min_element(lens + g0, lens + g0 + gn) < T;
     if (bounded) SSD_HIP(hipMemcpyAsync(c->prompt_len + b0 + g0, lens + g0, sizeof(int32_t) * gn, hipMemcpyHostToDevice, s));
     for (int start = 0; start < max_len; start += T) {
       const int Tn = wide ? std::min(T, max_len - start) : T;
@@ -961,8 +961,8 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
   const size_t kvd = (size_t)d.kv_dim();
   int st = SSD_OK;
   auto A = [&](void** p, size_t bytes) { if (st == SSD_OK) st = c->arena.alloc(p, bytes); };
-  A((void**)&c->trunk_len, sizeof(int32_t) * c->B);
-  A((void**)&c->prompt_len, sizeof(int32_t) * c->B);
+  A((void**)&c->trunk_len, 2 * sizeof(int32_t) * c->B);
+  if (st == SSD_OK) c->prompt_len = c->trunk_len + c->B;
   c->trunk_k.resize(d.n_layers); c->trunk_v.resize(d.n_layers);
   c->suffix_k.resize(d.n_layers); c->suffix_v.resize(d.n_layers);
   // the fused pass serves every pass of a context it fits, unless the configuration's flags say otherwise
