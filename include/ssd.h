@@ -107,7 +107,8 @@ typedef struct {
 enum {
   SSD_CTX_PER_OPERATOR = 1, /* never the fused pass: one kernel per operator */
   SSD_CTX_FUSED_PHASES = 2, /* the fused pass as one launch per phase instead of one persistent launch: no grid barrier, so
-                               no need for all its workgroups to be resident at once; same bits as the persistent launch */
+                               no need for all its workgroups to be resident at once; same bits as the persistent launch.  A
+                               context of wide passes (below) then runs its few-row extends as wide passes too: same to rounding */
   SSD_CTX_NARROW_PASSES = 4, /* a context with more than 48 rows in a batched forward runs them as passes of whole sequences
                                 of at most 48 rows (the weights are then streamed once per pass) instead of wide passes of
                                 up to 384 rows; a comparison aid */
@@ -144,9 +145,16 @@ typedef struct {
   int32_t batch, K, F, vocab, d_model, max_trunk;
   int32_t fused_pass;          /* 0: one kernel per operator; 1: fused pass, one launch per phase; 2: one persistent launch */
   int32_t pass_rows;           /* most rows of one fused pass of a round: 48 (narrow passes), 384 (wide passes), 0 without the fused
-                                  pass.  Prompts are prefilled in passes of up to 384 rows either way (unless a flag asks for
-                                  narrow passes or other activation planes), with a workspace for them */
+                                  pass.  Prompts are prefilled in passes of up to 1024 rows either way (unless a flag asks for
+                                  narrow passes or other activation planes; 384 where the trunks hold no more positions), with a
+                                  workspace for them */
 } ssd_views;
+/* Contexts of wide passes (fused_pass 1, pass_rows 384) of models at least 1024 wide launch the persistent kernel as well: for
+ * extends of at most 48 rows in all (the glue extend of a small batch, ssd_ctx_extend, what full passes leave of a prompt; not over
+ * trunks so long that a wide pass reads their keys sooner).  What is said below of persistent launches, residency, turns
+ * between streams and expired waits, holds for them; the context keeps to wide passes if the workgroups could not all be resident,
+ * or with SSD_CTX_FUSED_PHASES.  Inside a stream capture such an extend is wide launches (persistent launches take turns by events
+ * that a replay would not see), so its results differ from the eager call's by rounding. */
 
 const char* ssd_last_error(void);
 
@@ -347,7 +355,8 @@ int ssd_ctx_extend(ssd_ctx* ctx, const int32_t* d_tokens, int32_t T, int32_t off
  * (see ssd_ctx_status). */
 int ssd_ctx_refresh_bounds(ssd_ctx* ctx, void* stream);
 
-/* Health of a context served by the persistent fused pass.  That kernel separates its phases by grid barriers, which
+/* Health of a context that launches the persistent fused pass (ssd_views.fused_pass 2, and few-row extends of contexts of wide
+ * passes).  That kernel separates its phases by grid barriers, which
  * complete only while all its workgroups are resident at once.  The library checks at ssd_ctx_create that they fit the
  * device and makes every persistent launch of the process wait (on the device) for the previous one wherever that ran on
  * another stream; a kernel of the caller's own that occupies compute units for seconds could still starve a barrier.

@@ -13,8 +13,8 @@ namespace ssd {
 constexpr int kFusedThreads = 512;  // 8 wavefronts; they split the reduction dimension of a weight block
 constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxRows = 48;   // rows of one narrow pass (three 16-row MFMA tiles)
-constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles): contexts with more than kFusedMaxRows rows, and prompts
-constexpr int kFusedPromptRows = 1024;     // rows of a pass that only fills the trunk (prompts): eight row groups of
+constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles) of a round or extend: contexts with more than kFusedMaxRows rows
+constexpr int kFusedPromptRows = 1024;     // rows of a wide pass that only fills the trunk (prompts): eight row groups of
 constexpr int kFusedPromptRowGroup = 128;  // this many rows
 constexpr int kFusedWideQueryTiles = 3;   // wide passes: most query tiles per attention unit
 constexpr int kFusedWideFreshKeys = 192;  // wide passes: keys of the pass itself an attention unit has LDS room for

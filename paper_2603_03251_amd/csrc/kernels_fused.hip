@@ -1511,8 +1511,9 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
 // tiles, and lane l takes its 16 bytes from lane (l & 15) + 16 (l >> 5) + 32 h of tile (l >> 4) & 1, a fixed offset per lane.
 // NF = 2: 64 features per wavefront: two tile groups of the layout (ATW = 2: o, down), or gate tiles and up tiles, or four tiles of
 // the head, of one unit (ATW = 4).  NTW (one row group): the weights are read once and take the non-temporal path.
-// Against stages of 8 k-tiles with the memory operations in bursts: rounds of the 1B shape of 384 rows 13.67 -> 13.29 ms, 288 rows
-// 12.19 -> 12.09, 96 rows (head only) 8.22 -> 8.14.  1024 prompt rows, gate/up: 66 us (three passes of 340 rows before: 3 x 35); tiles of
+// Against stages of 8 k-tiles with the memory operations in bursts (1B shape, median us of a launch, both kernels on one machine):
+// 384 rows gate/up 37.5 -> 34.5, head 253 -> 232; 288 rows 31.9 -> 32.0, 204 -> 198; 96 rows head 109 -> 107 to 110.  A round of
+// 384 rows with all that came beside it 13.38 -> 13.17 ms.  1024 prompt rows, gate/up: 66 us (three passes of 340 rows before: 3 x 35); tiles of
 // 128 features x 192 rows measured 74 for 768 rows, tiles of 256 x 192 spill.
 constexpr int kTileRows = kFusedPromptRowGroup;      // rows of a full row group
 constexpr int kTileStage = 4, kTileRing = 8;         // k-tiles of an LDS stage, of the weight ring
@@ -1737,7 +1738,8 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
   const int unit = blockIdx.x;
   const int hk = unit % p.Hkv;
   int rem = unit / p.Hkv;
-  // (a prompt's later rows see more keys: their units go first, so that the last ones to start are the short ones)
+  // (a prompt's later rows see more keys: their units go first, so that the last ones to start are the short ones.  Prefill of 700
+  // tokens 2880 -> 2851 us, 1000 3325 -> 3306, 3000 10803 -> 10737, four runs a side in turn that do not overlap)
   const int qg = p.appended ? QG - 1 - rem % QG : rem % QG;
   rem /= QG;
   const int s = rem % p.NS, b = rem / p.NS;
@@ -2560,7 +2562,7 @@ int launch_wide_tile(const FusedParams& p, const FusedGemm& g, const bf16_t* bsr
   static const hipError_t configured = hipFuncSetAttribute((const void*)wide_tile_kernel<ATW, EPI, NF, RT, NTW>,
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   SSD_HIP(configured);
-  SSD_CHECK_ARG(wide_k_tiles(g) % (kTileRing * e.S) == 0 && (g.n_units / g.KS) * ATW % (2 * NF) == 0, "prompt pass: layer does not cut into tiles");
+  SSD_CHECK_ARG(wide_k_tiles(g) % (kTileRing * e.S) == 0 && (g.n_units / g.KS) * ATW % (2 * NF) == 0, "wide pass: layer does not cut into tiles");
   wide_tile_kernel<ATW, EPI, NF, RT, NTW><<<p.nwg, kWideThreads, kLds, s>>>(p, g, bsrc, e);
   SSD_HIP(hipGetLastError());
   return SSD_OK;

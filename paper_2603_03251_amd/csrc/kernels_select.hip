@@ -149,8 +149,8 @@ struct ScoreId {
 };
 // The sampler's rows are shared among small blocks: a block of 1024 threads waits with all 16 wavefronts for the slowest of them, and
 // only two fit a compute unit.  About 2048 blocks, of 1024 and 256 threads, us with the merge: 24 rows of 128256 at temperature
-// 0.7 15.9 and 15.0, 48 rows 25.8 and 17.8 (greedy 16.9 and 10.2), 96 rows 41.0 and 25.4 (23.9 and 13.5), 384 rows 74 and 63 (37.4
-// and 35.3); 512 threads lie between, 1024 or 4096 blocks of 256 measure 0 to 4 us more from 48 rows on.  A row of one block takes 1024.
+// 0.7 15.9 and 15.0, 48 rows 25.8 and 17.8 (greedy 16.9 and 10.2), 96 rows 41.0 and 25.4 (23.9 and 13.5), 384 rows 74 and 63 (greedy,
+// logits not in the caches, 46.5 and 47.7); 512 threads lie between, 1024 or 4096 blocks of 256 measure 0 to 4 us more from 48 rows on.  A row of one block takes 1024.
 constexpr int kSampleBlock = 256;
 constexpr int kSampleMaxParts = 128;  // blocks that share one row of the sampler
 __device__ __forceinline__ bool better(const ScoreId& a, const ScoreId& b) {
@@ -325,8 +325,8 @@ __global__ __launch_bounds__(64) void sample_merge_kernel(const ScoreId* __restr
 // decides, and scores its share of the bonus row for the residual; the block of a sequence that finishes last merges the
 // shares.  A row and the bonus row are shared among `parts` blocks, so that the few rows of one verification occupy the chip;
 // partial results are merged in a fixed order (the result does not depend on timing).  Measured (V = 128256, K = 5,
-// temperature 1): B = 1 18.0 us a call (rows 7, decisions 10.5: five dependent memory round trips and three reductions), B = 16
-// half of it greedy 42 us (25 + 17; rows without their exponentials 18, of which 70 MB at the rate of a copy are 10).
+// temperature 1): B = 1 17.9 us a call (rows 7, decisions 10.5: five dependent memory round trips and three reductions), B = 16
+// half of it greedy 41 us (24 + 17; rows without their exponentials 18, of which 70 MB at the rate of a copy are 10).
 constexpr int kVerifyBlock = 256, kVerifyWaves = kVerifyBlock / 64;
 constexpr int kVerifyMaxParts = 32;     // blocks that share a row (one lane of a wavefront merges one of them)
 constexpr int kVerifyMaxBonusParts = 64;
