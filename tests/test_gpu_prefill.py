@@ -118,7 +118,7 @@ def test_unequal_prompts_take_no_pages_for_rows_that_only_pad(B, lens, pages):
     assert pages == sum((n + 31) // 32 for n in lens)
     model = B.ssd_model_create(SHAPE, I.make_weights(SHAPE, 11))
     prompt, last = dev_i32(I.make_prompt(SHAPE, nb, max(lens), seed)), dev_i32(np.arange(nb).reshape(nb, 1))
-    ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags, n) for flags, n in ((0, 1 + pages), (B.SSD_CTX_NARROW_PASSES, 0))]
+    ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags, n) for flags, n in ((0, 1 + pages), (B.SSD_CTX_NARROW_PASSES, 0), (0, 0))]
     try:
         got = []
         for ctx in ctxs:
@@ -129,6 +129,7 @@ def test_unequal_prompts_take_no_pages_for_rows_that_only_pad(B, lens, pages):
             B.ssd_ctx_status(ctx)
             got.append(z.cpu().numpy())
         assert B.ssd_ctx_kv_pages(ctxs[0]) == (1 + pages, 0)
+        assert np.array_equal(got[0], got[2])                  # the same passes as over a contiguous trunk
         assert row_rel_err(got[0], got[1]) < 2 * TOL_BF16_OWN_PREFILL
     finally:
         for ctx in ctxs:
