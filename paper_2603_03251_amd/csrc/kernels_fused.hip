@@ -273,6 +273,30 @@ __device__ __forceinline__ void compute_row_scales(const FusedParams& p, const f
   wg_barrier();
 }
 
+// The same in two halves around other work: the first 128 feature tiles' sums are requested, and met later.  The caller's
+// next workgroup barrier publishes r_s.  tid: the thread index, read afresh by the caller.
+template <int MP>
+__device__ __forceinline__ void row_scales_issue(const FusedParams& p, const float* ssq, float (&v)[16], int tid) {
+  const int n_tiles = p.d >> 4;   // a multiple of 32
+  const unsigned off = ((tid >> 3) < p.M ? tid >> 3 : 0) + (tid & 7) * MP;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = ((const gfloat*)ssq + (8 * i < n_tiles ? 8 * i * MP : 0))[off];
+}
+template <int MP>
+__device__ __forceinline__ void row_scales_finish(const FusedParams& p, const float* ssq, const float (&v)[16], float* r_s, int tid) {
+  const int n_tiles = p.d >> 4;
+  const int m = tid >> 3;
+  const unsigned off = (m < p.M ? m : 0) + (tid & 7) * MP;
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) s += 8 * i < n_tiles ? v[i] : 0.f;
+  for (int j = 128; j < n_tiles; j += 8) s += ((const gfloat*)ssq + j * MP)[off];
+  s += __shfl_xor(s, 1);
+  s += __shfl_xor(s, 2);
+  s += __shfl_xor(s, 4);
+  if (m < p.M && (tid & 7) == 0) r_s[m] = 1.0f / sqrtf(s / (float)p.d + p.eps);
+}
+
 // Residual-stream epilogue shared by the embedding, the o-projection and the down-projection: store the new h
 // (4 consecutive features n..n+3 of row m per lane), (h * gain) as fp16 head/remainder planes for the next linear
 // layer, and this feature tile's sum of squares per row.
@@ -317,6 +341,9 @@ struct EpiArgs {
   float* fix_buf;      // K-split: [tile group][slice][tile][64 lanes][4] partial tiles of this phase instance
 };
 
+// Gate/up takes the loop that requests a whole unit ahead where a wavefront's share of it is this many k-tiles (d_model 2048):
+// as many as fit its registers (4 tiles each, 128 of 256).  Fewer leave less to request, more do not fit; both stay with the ring.
+constexpr int kGuTiles = 8;
 template <int AT, int MT, int NP>
 struct Chunk {
   bf16x8 a[AT];
@@ -467,7 +494,68 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
   };
 
 
-  if constexpr (PRE) {
+  if constexpr (PRE && AT == 4) {
+    // ---- gate/up with at most one unit per workgroup: ALL of a wavefront's weight tiles are requested before the workgroup
+    // waits at the barrier (the ring below: 3 of 8 k-tiles), activation tiles through a ring behind it, and the row scales, which
+    // only the epilogue wants, are requested with the first activation tiles and met after the MFMAs.  Bound by the 67 MB of
+    // weights of a layer, 9.3 of the 13 us the phase now takes with its barrier (16 before), and by the exchange before it: the
+    // flood slows the o-projection's last workgroups, so more of it, earlier, loses (requested under the o-projection: 24-row
+    // rounds over 1024 keys 4.97 -> 5.8 ms; a part held back until the barrier: 5.0 to 5.2).  Against the ring, 24 rows over 1024
+    // keys 5057 -> 4968 us per round, 8 rows over 211 keys 3044 -> 2971, single-token drafting 4000 -> 3945, 48 rows over 8192 keys
+    // 7429 -> 7415.
+    if (my_unit >= g.n_units) {
+      if (do_wait && !grid_wait(grid)) return false;
+      stamp(p, ph, 1);
+      return true;
+    }
+    constexpr int DA = kGuTiles, DB = MT * NP > 2 ? 2 : 4;
+    static_assert(DA % DB == 0, "static ring indices");
+    const gbf16x8* a_next = (const gbf16x8*)(g.w + (((int64_t)my_unit * kFusedWaves + wave) * DA * AT) * 512);
+    bf16x8 a[DA][AT], b[DB][MT * NP];
+    auto load_a = [&](bf16x8 (&dst)[AT]) {
+#pragma unroll
+      for (int j = 0; j < AT; ++j) dst[j] = __builtin_nontemporal_load(a_next + j * 64 + (unsigned)lane);
+      a_next += AT * 64;
+    };
+#pragma unroll
+    for (int c = 0; c < DA; ++c) load_a(a[c]);
+    if (do_wait && !grid_wait(grid)) return false;
+    stamp(p, ph, 1);
+    unsigned b_lane[MT];   // rows beyond M (padding of the last row tile) are not fetched: their lanes re-read row 0
+#pragma unroll
+    for (int t = 0; t < MT; ++t) b_lane[t] = lane - (t * 16 + (lane & 15) < p.M ? 0 : (lane & 15));
+    const gbf16x8* b_next = (const gbf16x8*)(bsrc + (int64_t)(wave * DA) * MT * 512);
+    auto load_b = [&](bf16x8 (&dst)[MT * NP]) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int pl = 0; pl < NP; ++pl) dst[t * NP + pl] = (b_next + pl * bplane_v + t * 64)[b_lane[t]];
+      b_next += MT * 64;
+    };
+    auto mfma_chunk = [&](const bf16x8 (&ca)[AT], const bf16x8 (&cb)[MT * NP]) {
+#pragma unroll
+      for (int j = 0; j < AT; ++j)
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+          for (int pl = 0; pl < NP; ++pl) acc[j][t] = mfma16_f16(ca[j], cb[t * NP + pl], acc[j][t]);
+    };
+#pragma unroll
+    for (int c = 0; c < DB - 1; ++c) load_b(b[c]);
+    float ssq_v[16];
+    row_scales_issue<MP>(p, ssq_in, ssq_v, ids.tid);
+    stamp(p, ph, 3);
+#pragma unroll
+    for (int c = 0; c < DA; ++c) {
+      if (c + DB - 1 < DA) load_b(b[(c + DB - 1) % DB]);
+      mfma_chunk(a[c], b[c % DB]);
+    }
+    stamp(p, ph, 4);
+    row_scales_finish<MP>(p, ssq_in, ssq_v, r_s, ids.tid);
+    stamp(p, ph, 5);
+    finish_unit(my_unit);
+    return true;
+  } else if constexpr (PRE) {
     // ---- at most one unit per workgroup (the host checks n_units <= grid): ALL of the wavefront's weight tiles are
     // requested before the workgroup waits at the barrier, so the weight stream of the phase runs under the barrier
     // latency, the activation fetch and the row scales; after the barrier only the activation tiles (L2) are loaded,
@@ -2286,6 +2374,9 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedParams p, int
       // (the unit's stores have left: it ended with a drain and a workgroup barrier)
       if (qkv_flag >= 0 && threadIdx.x == 0)
         __hip_atomic_store(p.qkv_flags + qkv_flag, grid.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (PL::xn == 1 && sub == 4 && g.KTW == kGuTiles && g.n_units <= p.nwg) {
+      if (!gemm_phase<4, MT, PL::xn, 2, true, MP, PL::xn, PL::act>(p, g, bsrc, bplane, FE_SWIGLU, e, grid, do_wait, red, r_s, ssq_in, ph,
+                                                                   (int)blockIdx.x)) return;
     } else if (sub == 4 || sub == 6) {
       const bool ok = gemm_phase<4, MT, PL::xn, Depth<MT, DEEP, PL::xn>::a4, false, MP, PL::xn, PL::act>(p, g, bsrc, bplane, epi, e, grid, do_wait, red, r_s, ssq_in, ph, my_unit);
       if (!ok) return;
