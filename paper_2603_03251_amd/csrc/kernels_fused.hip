@@ -110,7 +110,9 @@ __device__ __forceinline__ void st_f32x4_uncounted(float* p, f32x4 v) {
 // global addresses) is then local to the phase that computes it.  Derived from the kernel-wide threadIdx they would be
 // hoisted out of the phase loop, stay live through every phase and be spilled where registers are short.  (With the linear
 // layers and the row scales on fresh indices the instances use at most 28 bytes of scratch, up to 120 before: a
-// 24-row round over 1024 keys of the 1B shape 5162 -> 5057 us, 8 rows over 211 keys 3098 -> 3044.)
+// 24-row round over 1024 keys of the 1B shape 5162 -> 5057 us, 8 rows over 211 keys 3098 -> 3044.  With the attention unit
+// on fresh indices as well, beside the gate/up loop that holds all its weights: 4968 -> 4941, 2965 -> 2939, and 48 rows
+// over 8192 keys 7429 -> 7310, but single-token drafting 3950 -> 3985.)
 struct ThreadIds { int tid, lane, wave; };
 __device__ __forceinline__ ThreadIds fresh_thread_ids() {
   int t = threadIdx.x;
@@ -846,6 +848,8 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
     bf16x8 k[2][2];
     bf16x8 vt[4];
   };
+  // (3 or 4 blocks fit the registers but lose: 24 rows over 1024 keys 4941 -> 5183 or 5193 us per round, 48 rows over 8192 keys
+  // 7310 -> 7559 or 7434: what a wavefront polls for returns behind its K/V loads, and a compute unit ingests no more of them)
   constexpr int RING = 2;
   TrunkBlock ring[RING];
   auto load_trunk = [&](TrunkBlock& tb, int i) {   // i-th block of this wavefront, clamped to its last one
@@ -895,7 +899,7 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
 #pragma unroll
   for (int t = 0; t < 1; ++t) {
     Fresh& x = fr[t];
-    const int it = threadIdx.x + t * kFusedThreads;
+    const int it = ids.tid + t * kFusedThreads;
     x.f = it >> 3;
     x.q8 = it & 7;
     x.valid = false;
@@ -964,7 +968,7 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
 #pragma unroll
     for (int t = 0; t < 1; ++t) {
       Fresh& x = fr[t];
-      if (threadIdx.x + t * kFusedThreads < nf8) {
+      if (ids.tid + t * kFusedThreads < nf8) {
         u32x2 k_lo = (u32x2){0u, 0u}, k_hi = (u32x2){0u, 0u};
         Bf8 vv;
         vv.w = (u32x4){0u, 0u, 0u, 0u};
@@ -1070,6 +1074,7 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
     st_u64(att_out + off, pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
     if (NPT == 2) st_u64(att_out + (int64_t)MP * p.qd + off, pack_bf16x4(lo[0], lo[1], lo[2], lo[3]));
   };
+  const int tid = fresh_thread_ids().tid;
   // ---- the 8 wavefronts' partial softmaxes meet in LDS: acc [wave][dt][lane], (m, l) [wave][16]
   float* ml = (float*)(lds + kFusedWaves * 4 * 64);
 #pragma unroll
@@ -1079,8 +1084,8 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
     ml[(wave * 16 + li) * 2 + 1] = st.l_run;
   }
   wg_barrier();
-  if (threadIdx.x < 256) {
-    const int q = threadIdx.x & 15, dq = threadIdx.x >> 4;       // query row of the tile, dims 4 dq .. 4 dq + 3
+  if (tid < 256) {
+    const int q = tid & 15, dq = tid >> 4;       // query row of the tile, dims 4 dq .. 4 dq + 3
     float mmax = -INFINITY;
 #pragma unroll
     for (int w = 0; w < kFusedWaves; ++w) mmax = fmaxf(mmax, ml[(w * 16 + q) * 2]);
@@ -1111,7 +1116,7 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
   if (SM && p.NS > 1) {
     __builtin_amdgcn_s_waitcnt(0);
     wg_barrier();
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       unsigned* cnt = arrivals + (b * p.Hkv + hk) * p.QT + qt;
       const unsigned old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int is_last = old + 1 == (unsigned)p.NS;
@@ -1123,7 +1128,7 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
   // suffix slot (branch) or its trunk position (extend).  Last, so that the stores are not in the way of any load.
   {
     const Fresh& x = fr[0];
-    if (n_fb > 0 && (int)threadIdx.x < nf8 && x.valid && !x.stored) {
+    if (n_fb > 0 && tid < nf8 && x.valid && !x.stored) {
       const u32x2 k_lo = *(const u32x2*)(kf_s + x.f * 72 + x.q8 * 4), k_hi = *(const u32x2*)(kf_s + x.f * 72 + 32 + x.q8 * 4);
       Bf8 vv;
 #pragma unroll
@@ -1150,8 +1155,8 @@ __device__ __forceinline__ bool attn_unit(const FusedParams& p, const FusedLayer
   // XCDs); the other splits' stores were complete before their arrivals were counted.
   if (SM && p.NS > 1) {
     wg_barrier();
-    if (*last_s != 0 && threadIdx.x < 256) {
-      const int q = threadIdx.x & 15, dq = threadIdx.x >> 4;
+    if (*last_s != 0 && tid < 256) {
+      const int q = tid & 15, dq = tid >> 4;
       const int qrow = qt * 16 + q;
       if (qrow < RG) {
         constexpr int kMaxSplits = kFusedMaxSplits;
@@ -1966,6 +1971,8 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
     bf16x8 k[2][2];
     bf16x8 vt[4];
   };
+  // (3 or 4 blocks fit the registers but lose: 24 rows over 1024 keys 4941 -> 5183 or 5193 us per round, 48 rows over 8192 keys
+  // 7310 -> 7559 or 7434: what a wavefront polls for returns behind its K/V loads, and a compute unit ingests no more of them)
   constexpr int RING = 2;
   KvBlock ring[RING];
   auto load_trunk = [&](KvBlock& tb, int i) {   // i-th block of this wavefront, clamped to its last one
