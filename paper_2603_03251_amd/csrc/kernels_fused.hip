@@ -152,12 +152,13 @@ __device__ __forceinline__ f32x16 mfma32_f16(bf16x8 a, bf16x8 b, f32x16 c) {
 // Optional phase clocks (a measurement aid): [phase][slot][workgroup] ticks of the 100 MHz real-time counter; slot 0
 // phase entry, 1 after the grid barrier, 2 end of the phase's work, 3.. probes inside a phase (wide passes: 6 and 7 of the
 // o- and down-projections are entry and end of the residual launch behind them).
-__device__ __forceinline__ void stamp(const FusedParams& p, int ph, int which) {
+__device__ __forceinline__ void stamp(const FusedParams& p, int ph, int which, int column) {
   // (launches of more workgroups than the grid of the persistent kernel - the attention, merge and hidden-state launches
   // of a wide pass - record their first p.nwg workgroups: the table has p.nwg columns)
-  if (p.prof && threadIdx.x == 0 && (int)blockIdx.x < p.nwg)
-    p.prof[((int64_t)ph * kFusedClockSlots + which) * p.nwg + blockIdx.x] = __builtin_amdgcn_s_memrealtime();
+  if (p.prof && threadIdx.x == 0 && column < p.nwg)
+    p.prof[((int64_t)ph * kFusedClockSlots + which) * p.nwg + column] = __builtin_amdgcn_s_memrealtime();
 }
+__device__ __forceinline__ void stamp(const FusedParams& p, int ph, int which) { stamp(p, ph, which, (int)blockIdx.x); }
 
 // Offset of element (row m, input k) in a B-operand-ordered activation plane with MT row tiles:
 // [k / 32][m / 16][lane = m % 16 + 16 ((k % 32) / 8)][k % 8].
@@ -1514,7 +1515,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int m = ((int)blockIdx.x & 7) * (int)(gridDim.x >> 3) + ((int)blockIdx.x >> 3);
   if (m >= p.M) return;
-  if (CLOCKS) stamp(p, ph, EMBED ? 0 : 6);       // (the phase's other slots are the linear layer's)
+  if (CLOCKS) stamp(p, ph, EMBED ? 0 : 6, m);       // (the phase's other slots are the linear layer's)
   gfloat* h = (gfloat*)p.h + (int64_t)m * p.d;
   int tok = 0;
   if (EMBED) {
@@ -1595,7 +1596,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
     f32x4 v[2] = {*(const gf32x4*)(h + c), *(const gf32x4*)(h + c + 4)};   // this thread's own stores
     put(c, v, *(const u32x4*)(gain + c));
   }
-  if (CLOCKS) stamp(p, ph, EMBED ? 2 : 7);
+  if (CLOCKS) stamp(p, ph, EMBED ? 2 : 7, m);
 }
 
 // The linear layers with many outputs (rows x features): the LM head, gate/up + SwiGLU beyond 192 rows, and every layer of a prompt
