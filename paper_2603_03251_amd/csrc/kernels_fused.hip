@@ -276,24 +276,20 @@ __device__ __forceinline__ void compute_row_scales(const FusedParams& p, const f
   wg_barrier();
 }
 
-// The same in two halves around other work: the first 128 feature tiles' sums are requested, and met later.  The caller's
-// next workgroup barrier publishes r_s.  tid: the thread index, read afresh by the caller.
+// The same in two halves around other work, for the model width of gate/up with its weights ahead (kGuTiles below: 128 feature
+// tiles): the sums are requested, and met later.  The caller's next workgroup barrier publishes r_s.  tid: the thread index, read
+// afresh by the caller.
 template <int MP>
 __device__ __forceinline__ void row_scales_issue(const FusedParams& p, const float* ssq, float (&v)[16], int tid) {
-  const int n_tiles = p.d >> 4;   // a multiple of 32
   const unsigned off = ((tid >> 3) < p.M ? tid >> 3 : 0) + (tid & 7) * MP;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = ((const gfloat*)ssq + (8 * i < n_tiles ? 8 * i * MP : 0))[off];
+  for (int i = 0; i < 16; ++i) v[i] = ((const gfloat*)ssq + 8 * i * MP)[off];
 }
-template <int MP>
-__device__ __forceinline__ void row_scales_finish(const FusedParams& p, const float* ssq, const float (&v)[16], float* r_s, int tid) {
-  const int n_tiles = p.d >> 4;
+__device__ __forceinline__ void row_scales_finish(const FusedParams& p, const float (&v)[16], float* r_s, int tid) {
   const int m = tid >> 3;
-  const unsigned off = (m < p.M ? m : 0) + (tid & 7) * MP;
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) s += 8 * i < n_tiles ? v[i] : 0.f;
-  for (int j = 128; j < n_tiles; j += 8) s += ((const gfloat*)ssq + j * MP)[off];
+  for (int i = 0; i < 16; ++i) s += v[i];
   s += __shfl_xor(s, 1);
   s += __shfl_xor(s, 2);
   s += __shfl_xor(s, 4);
@@ -347,6 +343,7 @@ struct EpiArgs {
 // Gate/up takes the loop that requests a whole unit ahead where a wavefront's share of it is this many k-tiles (d_model 2048):
 // as many as fit its registers (4 tiles each, 128 of 256).  Fewer leave less to request, more do not fit; both stay with the ring.
 constexpr int kGuTiles = 8;
+static_assert(kGuTiles * kFusedWaves * 2 == 16 * 8, "row_scales_issue: 16 feature tiles for each of a row's 8 threads");
 template <int AT, int MT, int NP>
 struct Chunk {
   bf16x8 a[AT];
@@ -511,8 +508,10 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
       stamp(p, ph, 1);
       return true;
     }
-    constexpr int DA = kGuTiles, DB = MT * NP > 2 ? 2 : 4;
-    static_assert(DA % DB == 0, "static ring indices");
+    // chunks of activation tiles in flight, as the registers allow: 1 row tile 8 (single-token drafting 3999 -> 3973 us with 8
+    // instead of 4), 2 row tiles 4 (6 use scratch and gain nothing), 3 row tiles 3 (48 rows over 8192 keys 7222 -> 7140 us with 3
+    // instead of 2; 4 use scratch: 7205)
+    constexpr int DA = kGuTiles, DB = MT * NP > 2 ? 3 : MT * NP > 1 ? 4 : 8;
     const gbf16x8* a_next = (const gbf16x8*)(g.w + (((int64_t)my_unit * kFusedWaves + wave) * DA * AT) * 512);
     bf16x8 a[DA][AT], b[DB][MT * NP];
     auto load_a = [&](bf16x8 (&dst)[AT]) {
@@ -554,7 +553,7 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
       mfma_chunk(a[c], b[c % DB]);
     }
     stamp(p, ph, 4);
-    row_scales_finish<MP>(p, ssq_in, ssq_v, r_s, ids.tid);
+    row_scales_finish(p, ssq_v, r_s, ids.tid);
     stamp(p, ph, 5);
     finish_unit(my_unit);
     return true;
@@ -596,16 +595,19 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
 #pragma unroll
         for (int pl = 0; pl < NP; ++pl) dst[t * NP + pl] = bp[pl * bplane_v + t * 64 + row_fix[t]];
     };
-    // the activation tiles of KC chunks through a ring of DB, straight-line code with static register indices
+    // the activation tiles of KC chunks through a ring of DB (DB = KC: all requested at once), straight-line code with static
+    // register indices
     auto run = [&](auto kc_tag) {
       constexpr int KC = decltype(kc_tag)::value;
-      constexpr int DB = KC < 4 ? KC : 4;
+      // (three row tiles of one plane: all at once, 48 rows over 8192 keys 7306 -> 7222 us per round; fewer rows gain nothing,
+      // 24 rows over 1024 keys 4930 -> 4950, 8 rows over 211 keys 2940 -> 2939)
+      constexpr int DB = KC < 4 || (MT == 3 && NP == 1) ? KC : 4;
       bf16x8 b[DB][MT * NP];
 #pragma unroll
-      for (int c = 0; c < DB - 1; ++c) load_b(b[c], c);
+      for (int c = 0; c < (DB == KC ? DB : DB - 1); ++c) load_b(b[c], c);
 #pragma unroll
       for (int c = 0; c < KC; ++c) {
-        if (c + DB - 1 < KC) load_b(b[(c + DB - 1) % DB], c + DB - 1);
+        if (DB < KC && c + DB - 1 < KC) load_b(b[(c + DB - 1) % DB], c + DB - 1);
 #pragma unroll
         for (int j = 0; j < AT; ++j)
 #pragma unroll

@@ -432,6 +432,20 @@ def test_small_bf16_corner_shapes(B, name, shape, kw):
     _run_round_parity(B, shape, **kw)
 
 
+@pytest.mark.parametrize("batch,P,K,F", [
+    (1, 37, 1, 1),      # one row tile: 2 rows
+    (1, 300, 3, 4),     # 16 rows, a full tile
+    (1, 300, 3, 5),     # two tiles, the second with 4 rows
+    (2, 130, 3, 5),     # three tiles: 40 rows of two sequences
+    (1, 2100, 5, 8),    # 48 rows, key splits merged by their last unit
+])
+def test_bf16_gate_up_with_all_weights_ahead(B, batch, P, K, F):
+    """Model width 2048: gate/up requests a wavefront's whole unit before the barrier and meets the row scales after its MFMAs;
+    with 48 units most workgroups have none."""
+    shape = _small(n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=4, d_ffn=1536)
+    _run_round_parity(B, shape, batch=batch, P=P, K=K, F=F, seed=51, synthetic_kv=True)
+
+
 def test_small_bf16_head_dim_128_untied(B):
     _run_round_parity(B, SMALL_BF16_D128, batch=1, P=70, K=2, F=2, seed=9, synthetic_kv=True)
 
