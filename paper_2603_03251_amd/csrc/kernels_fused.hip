@@ -7,9 +7,10 @@
 // does not depend on timing.  The 8 wavefronts of a workgroup split its reduction range; each streams its own
 // contiguous run of 1 KiB weight tiles (MFMA 16x16x32 A operands, fp16) and reads the matching activation tiles (B
 // operands: 16 rows x 32 inputs, written by the producing phase as fp16 head/remainder planes in exactly the lane
-// order the MFMA wants).  Two loop shapes: where a workgroup has at most one unit (qkv, o, down) ALL its weight
-// tiles are requested before it waits at the grid barrier in front of the phase; gate/up and the LM head stream
-// weights and activations together through a ring of register chunks whose first chunks go out before the barrier.
+// order the MFMA wants).  Two loop shapes: where a workgroup has at most one unit (qkv, o, down, and gate/up of the
+// width whose unit fits the registers) ALL its weight tiles are requested before it waits at the grid barrier in front
+// of the phase; the LM head and gate/up of other widths stream weights and activations together through a ring of
+// register chunks whose first chunks go out before the barrier.
 // Weights depend on nothing, so HBM keeps streaming while the barrier and the activation exchange take their latency.
 // One exchange needs less than the grid: an attention unit reads the projections of its KV head's group only, so the
 // qkv units of a group announce themselves in a line of flags that the group's attention units poll (group_wait), and
@@ -340,7 +341,7 @@ struct EpiArgs {
   float* fix_buf;      // K-split: [tile group][slice][tile][64 lanes][4] partial tiles of this phase instance
 };
 
-// Gate/up takes the loop that requests a whole unit ahead where a wavefront's share of it is this many k-tiles (d_model 2048):
+// Gate/up takes the loop that requests a whole unit ahead (see gemm_phase) where a wavefront's share of it is this many k-tiles (d_model 2048):
 // as many as fit its registers (4 tiles each, 128 of 256).  Fewer leave less to request, more do not fit; both stay with the ring.
 constexpr int kGuTiles = 8;
 static_assert(kGuTiles * kFusedWaves * 2 == 16 * 8, "row_scales_issue: 16 feature tiles for each of a row's 8 threads");
@@ -1507,7 +1508,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
 // partial sums of the linear layer before, slice after slice.  Then (h * gain) as the fp16 B operand of the next linear
 // layer (8 consecutive features per thread are one lane's 16 bytes of it), the row's 1/rms, which that layer's epilogue
 // multiplies in, and, where asked for, the normalised row as fp32 hidden states.  Reads S + 1 rows of d floats: at 96 rows of the 1B shape (S = 4 and 8) 4.9 us, at 384 (S = 2)
-// 6.0 us, of which launch and two memory round trips are about 4.
+// 5.3 us (5.9 with the rows dealt round-robin), at 1020 10.4 (11.4), of which launch and two memory round trips are about 4.
 // CLOCKS: with phase clocks (an instance of its own: the test of p.prof alone cost a wide round 1 %).
 template <bool EMBED, bool CLOCKS>
 __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p, const float* part, int S, const bf16_t* gain,
