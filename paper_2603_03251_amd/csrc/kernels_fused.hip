@@ -34,6 +34,7 @@
 #include <vector>
 
 #include "fused.h"
+#include "wide_rows.h"
 
 namespace ssd {
 
@@ -1502,13 +1503,17 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
   stamp(p, e.ph, 2);
 }
 
-// The residual stream of a wide pass: a workgroup per row, an eighth of the rows in whole 16-row tiles per XCD: the 16 rows whose
-// 16-byte pieces share a 256-byte line of the operand plane then meet in one L2 (rows dealt round-robin sent every line to memory
-// in eight parts: rounds of 16 sequences over 2048 keys 13.34 -> 13.26 ms, a 1020-token prompt 4.15 -> 4.11).  EMBED: h = the token's embedding; otherwise h += the row's
-// partial sums of the linear layer before, slice after slice.  Then (h * gain) as the fp16 B operand of the next linear
-// layer (8 consecutive features per thread are one lane's 16 bytes of it), the row's 1/rms, which that layer's epilogue
-// multiplies in, and, where asked for, the normalised row as fp32 hidden states.  Reads S + 1 rows of d floats: at 96 rows of the 1B shape (S = 4 and 8) 4.9 us, at 384 (S = 2)
-// 5.3 us (5.9 with the rows dealt round-robin), at 1020 10.4 (11.4), of which launch and two memory round trips are about 4.
+// The residual stream of a wide pass: a workgroup per row, the rows dealt to the XCDs in pieces of 8 (wide_rows.h).  EMBED: h =
+// the token's embedding; otherwise h += the row's partial sums of the linear layer before, slice after slice.  Then (h * gain) as
+// the fp16 B operand of the next linear layer (8 consecutive features per thread are one lane's 16 bytes of it), the row's 1/rms,
+// which that layer's epilogue multiplies in, and, where asked for, the normalised row as fp32 hidden states.  Reads S + 1 rows of
+// d floats; launch and two memory round trips are about 4 us of what it takes.  1B shape, us per launch, mean of those behind o and
+// down, with pieces of 8 rows / single rows / an eighth of the rows per XCD: 8 rows 3.8 / 4.0 / 3.7, 16 rows 3.8 / 4.1 / 3.9,
+// 54 rows 4.6 / 4.6 / 4.5, 64 rows 4.5 / 4.6 / 4.5, 80 rows 4.8 / 4.8 / 4.6, 96 rows 4.8 / 4.9 / 4.5, 130 rows 4.9 / 5.0 / 5.1,
+// 160 rows 5.0 / 5.0 / 5.1, 260 rows 5.1 / 5.4 / 5.4, 384 rows 5.3 / 6.0 / 5.3, 1020 rows 10.3 / 11.5 / 10.2.  Where the launch
+// itself is no shorter the one behind it is: 8-layer passes, us, 16 rows 586 / 588 / 591, 54 rows 695 / 698 / 698, 80 rows 706 /
+// 710 / 708, 96 rows 727 / 731 / 729, 130 rows 836 / 842 / 850, 260 rows 1149 / 1157 / 1156, 384 rows 1233 / 1249 / 1241, 299 prompt tokens
+// 862 / 884 / 880, 1020 tokens 1622 / 1646 / 1625.  (Pieces of 4 rows: as pieces of 8, prompts of 200 and 299 tokens 1 % longer.)
 // CLOCKS: with phase clocks (an instance of its own: the test of p.prof alone cost a wide round 1 %).
 template <bool EMBED, bool CLOCKS>
 __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p, const float* part, int S, const bf16_t* gain,
@@ -1516,7 +1521,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
   constexpr int kHeld = 2;                       // 8-feature chunks per thread kept in registers (d <= 4096); others are re-read
   __shared__ float sum_s[kWideWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = ((int)blockIdx.x & 7) * (int)(gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+  const int m = wide_resid_row((int)blockIdx.x);
   if (m >= p.M) return;
   if (CLOCKS) stamp(p, ph, EMBED ? 0 : 6, m);       // (the phase's other slots are the linear layer's)
   gfloat* h = (gfloat*)p.h + (int64_t)m * p.d;
@@ -2763,7 +2768,7 @@ int launch_wide_logits(const FusedParams& p, const WideEpi& e, hipStream_t s) {
 }
 
 int launch_wide_resid(const FusedParams& p, bool embed, const float* part, int S, const bf16_t* gain, float* hidden, int ph, hipStream_t s) {
-  const int grid = (p.M + 127) / 128 * 128;   // 8 XCDs x whole 16-row tiles
+  const int grid = wide_resid_grid(p.M);
   if (embed && p.prof) wide_resid_kernel<true, true><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
   else if (embed) wide_resid_kernel<true, false><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
   else if (p.prof) wide_resid_kernel<false, true><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
