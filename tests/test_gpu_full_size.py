@@ -71,6 +71,7 @@ def test_full_size_round_on_sampled_branches(B, draft_1b, name, seqs, rows, ragg
         v_dev[:, b, lens[b]:] = I.round_to_bf16(np.float32(3.0e4))
     ctx = B.ssd_ctx_create(model, nb, K, F, P + TAIL + 2 * K + 2, B.SSD_CTX_TWO_PLANES if two_planes else 0)
     try:
+        assert B.ssd_ctx_views(ctx).fused_pass == (2 if nb * (K + 1) * F <= 48 else 1)
         B.ssd_ctx_load_trunk(ctx, kv_to_device(k_dev, "bf16"), kv_to_device(v_dev, "bf16"), P + TAIL)
         B.ssd_ctx_truncate_trunk(ctx, lens)
         del k_dev, v_dev
@@ -177,6 +178,7 @@ def test_full_size_rows_are_blind_to_what_they_must_not_see(B, draft_1b, name, P
         lens[b0] = 1999
     ctx = B.ssd_ctx_create(model, nb, K, F, P + 2 * K + 2)
     try:
+        assert B.ssd_ctx_views(ctx).fused_pass == (2 if nb * (K + 1) * F <= 48 else 1)
         B.ssd_ctx_load_trunk(ctx, kv_to_device(k, "bf16"), kv_to_device(v, "bf16"), P)
         if ragged:
             B.ssd_ctx_truncate_trunk(ctx, lens)
@@ -241,6 +243,7 @@ def test_full_size_round_with_the_geometric_cache_shape(B, draft_1b):
     k, v = I.make_prefix_kv(shape, 1, P, wl.seed)
     ctx = B.ssd_ctx_create_fanout(model, 1, K, fan, P + 2 * K + 2)
     try:
+        assert B.ssd_ctx_views(ctx).fused_pass == 2
         B.ssd_ctx_load_trunk(ctx, kv_to_device(k, "bf16"), kv_to_device(v, "bf16"), P)
         pending = I.make_pending(shape, 1, K, wl.seed)
         trunk = oracle_trunk_from_arrays(om, k, v, 0)

@@ -40,6 +40,7 @@ def test_device_generated_model_and_prefix_equal_the_host_twin(B, shape):
         model = B.ssd_model_create_random(shape, seed) if on_device else B.ssd_model_create(shape, twin)
         ctx = B.ssd_ctx_create(model, nb, K, F, 96)
         try:
+            assert (B.ssd_ctx_views(ctx).fused_pass == 2) == (shape is SHAPES[0])
             if on_device:
                 B.ssd_ctx_fill_synthetic_kv(ctx, lens, seed + 1)
             else:

@@ -46,6 +46,7 @@ def test_wide_prefill_equals_narrow_chunks(B, lens):
     pending, temps = dev_i32(I.make_pending(SHAPE, nb, K, seed)), dev_f32(np.zeros(nb))
     ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in ctxs)
         got = []
         for ctx in ctxs:
             B.ssd_ctx_prefill(ctx, prompt, lens)
@@ -58,6 +59,7 @@ def test_wide_prefill_equals_narrow_chunks(B, lens):
                 for b in range(nb):
                     assert row_rel_err(got[0][0][part][l][b], got[1][0][part][l][b]) < 2 * TOL_BF16_OWN_PREFILL, (part, l, b)
         assert row_rel_err(got[0][1], got[1][1]) < 2 * TOL_BF16_OWN_PREFILL
+        assert max(lens) <= K + 1 or not np.array_equal(got[0][1], got[1][1])      # (the prompts did go through another pass)
         # one slot prefilled alone gives what it gets beside the others
         b = nb - 1
         B.ssd_ctx_prefill_sequence(ctxs[0], b, prompt[b, :lens[b]].contiguous())
@@ -87,6 +89,7 @@ def test_prompt_passes_at_the_edges_of_their_row_groups(B, width, lens, paged):
     pages = 1 + nb * ((max_trunk + 63) // 64 * 2) if paged else 0
     ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags, n) for flags, n in ((0, pages), (B.SSD_CTX_NARROW_PASSES, 0))]
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in ctxs)
         got = []
         for ctx in ctxs:
             B.ssd_ctx_prefill(ctx, prompt, lens)
@@ -101,6 +104,7 @@ def test_prompt_passes_at_the_edges_of_their_row_groups(B, width, lens, paged):
                 for b in range(nb):
                     assert row_rel_err(got[0][0][part][l][b], got[1][0][part][l][b]) < 2 * TOL_BF16_OWN_PREFILL, (part, l, b)
         assert row_rel_err(got[0][1], got[1][1]) < 2 * TOL_BF16_OWN_PREFILL
+        assert not np.array_equal(got[0][1], got[1][1])
     finally:
         for ctx in ctxs:
             B.ssd_ctx_destroy(ctx)
@@ -120,6 +124,7 @@ def test_unequal_prompts_take_no_pages_for_rows_that_only_pad(B, lens, pages):
     prompt, last = dev_i32(I.make_prompt(SHAPE, nb, max(lens), seed)), dev_i32(np.arange(nb).reshape(nb, 1))
     ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags, n) for flags, n in ((0, 1 + pages), (B.SSD_CTX_NARROW_PASSES, 0), (0, 0))]
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in ctxs)
         got = []
         for ctx in ctxs:
             B.ssd_ctx_prefill(ctx, prompt, lens)
@@ -147,6 +152,7 @@ def test_prompts_of_one_chunk_take_the_narrow_pass(B, lens):
     prompt = dev_i32(I.make_prompt(SHAPE, nb, max(lens), seed))
     ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in ctxs)
         for alone in (False, True):
             got = []
             for ctx in ctxs:
@@ -175,6 +181,7 @@ def test_wide_prefill_against_the_oracle(B, pages):
     pending = I.make_pending(SHAPE, 2, K, seed)
     ctx = B.ssd_ctx_create(model, 2, K, F, max_trunk, 0, pages)
     try:
+        assert B.ssd_ctx_views(ctx).fused_pass
         B.ssd_ctx_prefill(ctx, dev_i32(prompt), lens)
         B.ssd_prespeculate(ctx, dev_i32(pending), dev_f32(np.zeros(2)), 1)
         got = B.read_cache(ctx)["glue_logits"].cpu().numpy()
@@ -203,6 +210,7 @@ def test_wide_attention_units_of_two_and_three_query_tiles(B, heads, lens):
     pending, temps = dev_i32(I.make_pending(shape, nb, K, seed)), dev_f32(np.zeros(nb))
     ctxs = [B.ssd_ctx_create(model, nb, K, F, max(lens) + 2 * K + 8, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in ctxs)
         got = []
         for ctx in ctxs:
             B.ssd_ctx_prefill(ctx, prompt, lens)
@@ -231,6 +239,7 @@ def test_appended_prompts_with_key_splits(B, kv_heads, lens, pages):
     pending, temps = dev_i32(I.make_pending(shape, nb, K, seed)), dev_f32(np.zeros(nb))
     ctxs = [B.ssd_ctx_create(model, nb, K, F, max_trunk, flags, pages) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in ctxs)
         got, kv = [], []
         for ctx in ctxs:
             B.ssd_ctx_prefill(ctx, prompt, lens)
@@ -337,6 +346,7 @@ def test_few_rows_over_long_trunks_take_the_pass_that_reads_their_keys_once(B, n
     model = B.ssd_model_create(shape, I.make_weights(shape, 3))
     ctxs = [B.ssd_ctx_create(model, nb, K, F, P + 2 * K + 8, flags) for flags in (0, B.SSD_CTX_FUSED_PHASES, B.SSD_CTX_NARROW_PASSES)]
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in ctxs)
         tokens, got = dev_i32(np.random.default_rng(seed).integers(0, shape.vocab, (nb, T))), []
         for ctx in ctxs:
             z = torch.zeros((nb, T, shape.vocab), dtype=torch.float32, device="cuda")
@@ -367,6 +377,7 @@ def test_remainders_of_prompts_on_the_persistent_pass(B, heads_kv, base, F, page
     ctxs = [B.ssd_ctx_create(model, 1, K, f, max_trunk, flags, n)
             for flags, f, n in ((0, F, pages), (B.SSD_CTX_FUSED_PHASES, F, pages), (B.SSD_CTX_NARROW_PASSES, 2, 0))]
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in ctxs)
         for r in (16, 17, 32, 33, 47, 48, 49):
             print(f"[case] {base} + {r} tokens, {heads_kv} KV heads, F {F}, paged {paged}", flush=True)
             got = []
@@ -436,6 +447,7 @@ def test_captured_extend_of_few_rows_takes_the_wide_pass(B):
     model = B.ssd_model_create(shape, I.make_weights(shape, 3))
     ctx, wide = (B.ssd_ctx_create(model, nb, K, F, P + 4 * K + 8, flags) for flags in (0, B.SSD_CTX_FUSED_PHASES))
     try:
+        assert all(B.ssd_ctx_views(c).fused_pass for c in (ctx, wide))
         sets = [dev_i32(np.random.default_rng(i).integers(0, shape.vocab, (nb, T))) for i in range(4)]
         tokens, z = sets[0].clone(), torch.zeros((nb, T, shape.vocab), dtype=torch.float32, device="cuda")
         eager = torch.zeros_like(z)
