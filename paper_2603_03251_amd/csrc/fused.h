@@ -107,7 +107,7 @@ struct FusedParams {
   unsigned spin_limit;                     // polls a bounded wait may take before it gives up
   unsigned long long* prof;                // optional [phases][kFusedClockSlots][nwg] real-time-counter ticks, or null
   int nwg;
-  int deep;                                // 1: every linear layer has a multiple of 4 k-tiles per wavefront and unit
+  int kt;                                  // k-tiles per wavefront and unit of the linear layers over the model width: d / 256 = 2, 4, 8
   int planes;                              // bit i set: tensor i travels as one 16-bit plane instead of head + remainder
                                            // (0 xn, 1 att, 2 act, 3 q, 4 p); see Planes in kernels_fused.hip
 };
@@ -139,8 +139,9 @@ bool fused_wide_gemm_ok(const FusedGemm& g, int at);
 // dst[i] = fp16(src[i]) over a stream-order weight buffer (the fused passes multiply in fp16; dst may be src); n a multiple of 8
 int launch_bf16_to_f16(const bf16_t* src, bf16_t* dst, int64_t n, hipStream_t s);
 int fused_grid_size(int* out);
-// EINVAL unless `nwg` workgroups of every instance of the persistent kernel can be resident at once on the current device
-int fused_check_residency(int nwg, int planes, int paged);
+// EINVAL unless `nwg` workgroups of every instance of the persistent kernel for this width (FusedParams::kt) can be resident at once
+// on the current device
+int fused_check_residency(int nwg, int kt, int planes, int paged);
 bool fused_planes_supported(int planes);
 // Barrier words (kFusedSyncWords of them + the error word behind) as a finished barrier number `epoch0` leaves them;
 // 0 for a new context.  The epoch counts on from launch to launch and wraps after 2^32 barriers.

@@ -7,10 +7,10 @@
 // does not depend on timing.  The 8 wavefronts of a workgroup split its reduction range; each streams its own
 // contiguous run of 1 KiB weight tiles (MFMA 16x16x32 A operands, fp16) and reads the matching activation tiles (B
 // operands: 16 rows x 32 inputs, written by the producing phase as fp16 head/remainder planes in exactly the lane
-// order the MFMA wants).  Two loop shapes: where a workgroup has at most one unit (qkv, o, down, and gate/up of the
-// width whose unit fits the registers) ALL its weight tiles are requested before it waits at the grid barrier in front
-// of the phase; the LM head and gate/up of other widths stream weights and activations together through a ring of
-// register chunks whose first chunks go out before the barrier.
+// order the MFMA wants).  Two loop shapes: where a workgroup has at most one unit (qkv, o, down, and with one activation
+// plane gate/up) ALL its weight tiles are requested before it waits at the grid barrier in front of the phase; the LM head,
+// and gate/up with two planes, stream weights and activations together through a ring of register chunks whose first
+// chunks go out before the barrier.
 // Weights depend on nothing, so HBM keeps streaming while the barrier and the activation exchange take their latency.
 // One exchange needs less than the grid: an attention unit reads the projections of its KV head's group only, so the
 // qkv units of a group announce themselves in a line of flags that the group's attention units poll (group_wait), and
@@ -278,20 +278,21 @@ __device__ __forceinline__ void compute_row_scales(const FusedParams& p, const f
   wg_barrier();
 }
 
-// The same in two halves around other work, for the model width of gate/up with its weights ahead (kGuTiles below: 128 feature
-// tiles): the sums are requested, and met later.  The caller's next workgroup barrier publishes r_s.  tid: the thread index, read
-// afresh by the caller.
-template <int MP>
-__device__ __forceinline__ void row_scales_issue(const FusedParams& p, const float* ssq, float (&v)[16], int tid) {
+// The same in two halves around other work, for gate/up with its weights ahead (see gemm_phase): the sums are requested, and met
+// later.  N: feature tiles of the model width for each of a row's 8 threads.  The caller's next workgroup barrier publishes r_s.
+// tid: the thread index, read afresh by the caller.
+template <int MP, int N>
+__device__ __forceinline__ void row_scales_issue(const FusedParams& p, const float* ssq, float (&v)[N], int tid) {
   const unsigned off = ((tid >> 3) < p.M ? tid >> 3 : 0) + (tid & 7) * MP;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) v[i] = ((const gfloat*)ssq + 8 * i * MP)[off];
+  for (int i = 0; i < N; ++i) v[i] = ((const gfloat*)ssq + 8 * i * MP)[off];
 }
-__device__ __forceinline__ void row_scales_finish(const FusedParams& p, const float (&v)[16], float* r_s, int tid) {
+template <int N>
+__device__ __forceinline__ void row_scales_finish(const FusedParams& p, const float (&v)[N], float* r_s, int tid) {
   const int m = tid >> 3;
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) s += v[i];
+  for (int i = 0; i < N; ++i) s += v[i];
   s += __shfl_xor(s, 1);
   s += __shfl_xor(s, 2);
   s += __shfl_xor(s, 4);
@@ -342,10 +343,6 @@ struct EpiArgs {
   float* fix_buf;      // K-split: [tile group][slice][tile][64 lanes][4] partial tiles of this phase instance
 };
 
-// Gate/up takes the loop that requests a whole unit ahead (see gemm_phase) where a wavefront's share of it is this many k-tiles (d_model 2048):
-// as many as fit its registers (4 tiles each, 128 of 256).  Fewer leave less to request, more do not fit; both stay with the ring.
-constexpr int kGuTiles = 8;
-static_assert(kGuTiles * kFusedWaves * 2 == 16 * 8, "row_scales_issue: 16 feature tiles for each of a row's 8 threads");
 template <int AT, int MT, int NP>
 struct Chunk {
   bf16x8 a[AT];
@@ -355,10 +352,11 @@ struct Chunk {
 // One linear layer over the workgroup's units.  bsrc: activation planes in B-operand order, `bplane` elements apart.
 // ssq_in: if not null, row scales are computed into r_s after the barrier (SWIGLU and LOGITS need them).
 // AT = 2 serves the qkv, o and down projections (epilogue FE_QKV / FE_RESID), AT = 4 the gate/up projection and the
-// LM head (FE_SWIGLU / FE_LOGITS).  The epilogue kind is a run-time argument so that each of the two streaming loops
-// exists once in the kernel: its code has to stay resident in the instruction cache across the layers.
+// LM head (FE_SWIGLU / FE_LOGITS).  The epilogue kind is a run-time argument so that the loop of qkv, o and down, and the ring,
+// exist once each in the kernel, beside gate/up's: the code has to stay resident in the instruction cache across the layers.
 // MP: row capacity of the workspace; NPX / NPC: planes of the (h * gain) / SwiGLU outputs the epilogues write.
-template <int AT, int MT, int NP, int D, bool PRE, int MP, int NPX, int NPC>
+// KT: k-tiles per wavefront and unit of gate/up with its weights ahead.
+template <int AT, int MT, int NP, int D, bool PRE, int MP, int NPX, int NPC, int KT = 0>
 __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm g, const bf16_t* bsrc, int64_t bplane,
                                            const int EPI, const EpiArgs& e, Grid& grid, bool do_wait, f32x4* red, float* r_s,
                                            const float* ssq_in, int ph, int my_unit) {
@@ -500,11 +498,13 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
     // ---- gate/up with at most one unit per workgroup: ALL of a wavefront's weight tiles are requested before the workgroup
     // waits at the barrier (the ring below: 3 of 8 k-tiles), activation tiles through a ring behind it, and the row scales, which
     // only the epilogue wants, are requested with the first activation tiles and met after the MFMAs.  Bound by the 67 MB of
-    // weights of a layer, 9.3 of the 13 us the phase now takes with its barrier (16 before), and by the exchange before it: the
-    // flood slows the o-projection's last workgroups, so more of it, earlier, loses (requested under the o-projection: 24-row
+    // weights of a layer of the 1B shape, 9.3 of the 13 us the phase now takes with its barrier (16 before), and by the exchange before
+    // it: the flood slows the o-projection's last workgroups, so more of it, earlier, loses (requested under the o-projection: 24-row
     // rounds over 1024 keys 4.97 -> 5.8 ms; a part held back until the barrier: 5.0 to 5.2).  Against the ring, 24 rows over 1024
     // keys 5057 -> 4968 us per round, 8 rows over 211 keys 3044 -> 2971, single-token drafting 4000 -> 3945, 48 rows over 8192 keys
-    // 7429 -> 7415.
+    // 7429 -> 7415.  16 layers of width 1024 (d_ffn 4096) and
+    // 512 (2048), rounds: 8 rows over 211 keys 2215 -> 2083 and 2078 -> 1975, 24 rows over 1024 keys 3666 -> 3472 and 3443 -> 3263, 48 rows
+    // over 8192 keys 4771 -> 4563 and 4131 -> 3941; five single tokens over 1024 keys 2794 -> 2639 and 2633 -> 2463.
     if (my_unit >= g.n_units) {
       if (do_wait && !grid_wait(grid)) return false;
       stamp(p, ph, 1);
@@ -512,8 +512,8 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
     }
     // chunks of activation tiles in flight, as the registers allow: 1 row tile 8 (single-token drafting 3999 -> 3973 us with 8
     // instead of 4), 2 row tiles 4 (6 use scratch and gain nothing), 3 row tiles 3 (48 rows over 8192 keys 7222 -> 7140 us with 3
-    // instead of 2; 4 use scratch: 7205)
-    constexpr int DA = kGuTiles, DB = MT * NP > 2 ? 3 : MT * NP > 1 ? 4 : 8;
+    // instead of 2, of 28 bytes of scratch; 4 use more: 7205)
+    constexpr int DA = KT, DB_MAX = MT * NP > 2 ? 3 : MT * NP > 1 ? 4 : 8, DB = DB_MAX < DA ? DB_MAX : DA;
     const gbf16x8* a_next = (const gbf16x8*)(g.w + (((int64_t)my_unit * kFusedWaves + wave) * DA * AT) * 512);
     bf16x8 a[DA][AT], b[DB][MT * NP];
     auto load_a = [&](bf16x8 (&dst)[AT]) {
@@ -546,7 +546,7 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
     };
 #pragma unroll
     for (int c = 0; c < DB - 1; ++c) load_b(b[c]);
-    float ssq_v[16];
+    float ssq_v[2 * KT];   // KT k-tiles of 32 inputs in each of 8 wavefronts: 16 KT feature tiles, 2 KT for each of a row's 8 threads
     row_scales_issue<MP>(p, ssq_in, ssq_v, ids.tid);
     stamp(p, ph, 3);
 #pragma unroll
@@ -2270,13 +2270,14 @@ __global__ __launch_bounds__(kFusedThreads) void wide_merge_kernel(FusedParams p
 }
 
 // ---------------------------------------------------------------------------------------------- the kernel
-// Register chunks in flight per wavefront.  DEEP needs the k-tiles per wavefront of every linear layer to be a
-// multiple of 8 (one feature tile per unit) / 4 (four per unit); the shallow set needs multiples of 2.
-template <int MT, bool DEEP, int NP> struct Depth {
-  static constexpr int a4 = !DEEP ? 2 : (MT * NP > 4 ? 2 : 4);   // four feature tiles per unit
+// Register chunks in flight per wavefront in the ring: a divisor of the KT k-tiles a wavefront takes of a unit.
+template <int MT, int KT, int NP> struct Depth {
+  static constexpr int a4 = KT == 2 ? 2 : (MT * NP > 4 ? 2 : 4);   // four feature tiles per unit
 };
 
-template <int MT, bool DEEP, class PL, bool PG, bool SM>
+// KT: k-tiles per wavefront of a unit over the model width (d / 256: 8, 4 or 2, what the host admits).  An instance for each: the loop of
+// gate/up holds that many in registers, and two such loops in one kernel spill.
+template <int MT, int KT, class PL, bool PG, bool SM>
 __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedParams p, int first, int last, int persistent) {
   constexpr int MP = kFusedMaxRows;
   extern __shared__ f32x4 red[];
@@ -2394,11 +2395,13 @@ __global__ __launch_bounds__(kFusedThreads) void fused_kernel(FusedParams p, int
       // (the unit's stores have left: it ended with a drain and a workgroup barrier)
       if (qkv_flag >= 0 && threadIdx.x == 0)
         __hip_atomic_store(p.qkv_flags + qkv_flag, grid.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else if (PL::xn == 1 && sub == 4 && g.KTW == kGuTiles && g.n_units <= p.nwg) {
-      if (!gemm_phase<4, MT, PL::xn, 2, true, MP, PL::xn, PL::act>(p, g, bsrc, bplane, FE_SWIGLU, e, grid, do_wait, red, r_s, ssq_in, ph,
-                                                                   (int)blockIdx.x)) return;
+    } else if (PL::xn == 1 && sub == 4 && g.n_units <= p.nwg) {
+      // (more units than workgroups exist only on a device of fewer than 256 compute units: the down-projection admits a d_ffn of
+      // at most 8192; they stream through the ring)
+      if (!gemm_phase<4, MT, PL::xn, 2, true, MP, PL::xn, PL::act, KT>(p, g, bsrc, bplane, FE_SWIGLU, e, grid, do_wait, red, r_s, ssq_in, ph,
+                                                                       (int)blockIdx.x)) return;
     } else if (sub == 4 || sub == 6) {
-      const bool ok = gemm_phase<4, MT, PL::xn, Depth<MT, DEEP, PL::xn>::a4, false, MP, PL::xn, PL::act>(p, g, bsrc, bplane, epi, e, grid, do_wait, red, r_s, ssq_in, ph, my_unit);
+      const bool ok = gemm_phase<4, MT, PL::xn, Depth<MT, KT, PL::xn>::a4, false, MP, PL::xn, PL::act>(p, g, bsrc, bplane, epi, e, grid, do_wait, red, r_s, ssq_in, ph, my_unit);
       if (!ok) return;
       if (sub == 6 && p.hidden) {
         // final-norm hidden states (the row scales are in LDS)
@@ -2496,39 +2499,39 @@ __global__ void copy_kv_fused_kernel(bf16_t* trunk_k, bf16_t* trunk_vt, const bf
 
 constexpr size_t kFusedLdsBytes = 96 * 1024;   // reduction tiles (<= 8 wavefronts x 12 tiles x 1 KiB); also keeps one workgroup per CU
 
-template <int MT, bool DEEP, class PL, bool PG, bool SM>
+template <int MT, int KT, class PL, bool PG, bool SM>
 int check_residency_sm(int nwg, int cus) {
-  SSD_HIP(hipFuncSetAttribute((const void*)fused_kernel<MT, DEEP, PL, PG, SM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes));
+  SSD_HIP(hipFuncSetAttribute((const void*)fused_kernel<MT, KT, PL, PG, SM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes));
   int per_cu = 0;
-  SSD_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fused_kernel<MT, DEEP, PL, PG, SM>, kFusedThreads, kFusedLdsBytes));
+  SSD_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fused_kernel<MT, KT, PL, PG, SM>, kFusedThreads, kFusedLdsBytes));
   SSD_CHECK_ARG((int64_t)per_cu * cus >= nwg,
                 "fused pass: %d workgroups cannot be resident at once (%d per compute unit x %d compute units): the grid barrier "
                 "would never complete", nwg, per_cu, cus);
   return SSD_OK;
 }
 
-template <int MT, bool DEEP, class PL, bool PG>
+template <int MT, int KT, class PL, bool PG>
 int check_residency_mt(int nwg, int cus) {
-  SSD_TRY((check_residency_sm<MT, DEEP, PL, PG, false>(nwg, cus)));
-  return check_residency_sm<MT, DEEP, PL, PG, true>(nwg, cus);
+  SSD_TRY((check_residency_sm<MT, KT, PL, PG, false>(nwg, cus)));
+  return check_residency_sm<MT, KT, PL, PG, true>(nwg, cus);
 }
 
-template <int MT, bool DEEP, class PL, bool PG, bool SM>
+template <int MT, int KT, class PL, bool PG, bool SM>
 int launch_sm(const FusedParams& p, int first, int last, int persistent, hipStream_t s) {
   const size_t lds = kFusedLdsBytes;
   static bool configured = false;
   if (!configured) {
-    SSD_HIP(hipFuncSetAttribute((const void*)fused_kernel<MT, DEEP, PL, PG, SM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    SSD_HIP(hipFuncSetAttribute((const void*)fused_kernel<MT, KT, PL, PG, SM>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     configured = true;
   }
   if (persistent) {
-    fused_kernel<MT, DEEP, PL, PG, SM><<<p.nwg, kFusedThreads, lds, s>>>(p, first, last, 1);
+    fused_kernel<MT, KT, PL, PG, SM><<<p.nwg, kFusedThreads, lds, s>>>(p, first, last, 1);
     SSD_HIP(hipGetLastError());
   } else {
     const int lm_phase = fused_last_phase(p.L);
     for (int ph = first; ph <= last; ++ph) {
       if ((SM || p.NS == 1) && ph > 0 && ph < lm_phase && (ph - 1) % 6 == 2) continue;   // no merge phase
-      fused_kernel<MT, DEEP, PL, PG, SM><<<p.nwg, kFusedThreads, lds, s>>>(p, ph, ph, 0);
+      fused_kernel<MT, KT, PL, PG, SM><<<p.nwg, kFusedThreads, lds, s>>>(p, ph, ph, 0);
       SSD_HIP(hipGetLastError());
     }
   }
@@ -2536,10 +2539,10 @@ int launch_sm(const FusedParams& p, int first, int last, int persistent, hipStre
 }
 
 // Passes with several key splits take the kernel whose attention units merge them.
-template <int MT, bool DEEP, class PL, bool PG>
+template <int MT, int KT, class PL, bool PG>
 int launch_mt(const FusedParams& p, int first, int last, int persistent, hipStream_t s) {
-  if (p.NS > 1) return launch_sm<MT, DEEP, PL, PG, true>(p, first, last, persistent, s);
-  return launch_sm<MT, DEEP, PL, PG, false>(p, first, last, persistent, s);
+  if (p.NS > 1) return launch_sm<MT, KT, PL, PG, true>(p, first, last, persistent, s);
+  return launch_sm<MT, KT, PL, PG, false>(p, first, last, persistent, s);
 }
 
 }  // namespace
@@ -2640,15 +2643,20 @@ constexpr int kFusedDefaultPlanes = 7;
 template <int MASK>
 using PlanesOf = Planes<(MASK & 1) ? 1 : 2, (MASK & 2) ? 1 : 2, (MASK & 4) ? 1 : 2, (MASK & 8) ? 1 : 2, (MASK & 16) ? 1 : 2>;
 
+// The instance of a model width: with two planes gate/up streams through the ring, which takes 4 k-tiles as it takes 8.
+template <class PL> constexpr int kt_of(int kt) { return PL::xn == 2 && kt == 4 ? 8 : kt; }
+
+template <int KT, class PL, bool PG>
+int check_residency_kt(int nwg, int cus) {
+  SSD_TRY((check_residency_mt<1, KT, PL, PG>(nwg, cus)));
+  SSD_TRY((check_residency_mt<2, KT, PL, PG>(nwg, cus)));
+  return check_residency_mt<3, KT, PL, PG>(nwg, cus);
+}
 template <class PL, bool PG>
-int check_residency_pl(int nwg, int cus) {
-  SSD_TRY((check_residency_mt<1, true, PL, PG>(nwg, cus)));
-  SSD_TRY((check_residency_mt<2, true, PL, PG>(nwg, cus)));
-  SSD_TRY((check_residency_mt<3, true, PL, PG>(nwg, cus)));
-  SSD_TRY((check_residency_mt<1, false, PL, PG>(nwg, cus)));
-  SSD_TRY((check_residency_mt<2, false, PL, PG>(nwg, cus)));
-  SSD_TRY((check_residency_mt<3, false, PL, PG>(nwg, cus)));
-  return SSD_OK;
+int check_residency_pl(int nwg, int cus, int kt) {
+  if (kt == 2) return check_residency_kt<2, PL, PG>(nwg, cus);
+  if (kt == 4) return check_residency_kt<kt_of<PL>(4), PL, PG>(nwg, cus);
+  return check_residency_kt<8, PL, PG>(nwg, cus);
 }
 
 int wide_k_tiles(const FusedGemm& g) { return g.KS * kFusedWaves * g.KTW; }
@@ -2826,17 +2834,18 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
   return SSD_OK;
 }
 
+template <int KT, class PL, bool PG>
+int launch_kt(const FusedParams& p, int first, int last, int persistent, hipStream_t s) {
+  const int mt = (p.M + 15) / 16;
+  if (mt == 1) return launch_mt<1, KT, PL, PG>(p, first, last, persistent, s);
+  if (mt == 2) return launch_mt<2, KT, PL, PG>(p, first, last, persistent, s);
+  return launch_mt<3, KT, PL, PG>(p, first, last, persistent, s);
+}
 template <class PL, bool PG>
 int launch_pl(const FusedParams& p, int first, int last, int persistent, hipStream_t s) {
-  const int mt = (p.M + 15) / 16;
-  if (p.deep != 0) {
-    if (mt == 1) return launch_mt<1, true, PL, PG>(p, first, last, persistent, s);
-    if (mt == 2) return launch_mt<2, true, PL, PG>(p, first, last, persistent, s);
-    return launch_mt<3, true, PL, PG>(p, first, last, persistent, s);
-  }
-  if (mt == 1) return launch_mt<1, false, PL, PG>(p, first, last, persistent, s);
-  if (mt == 2) return launch_mt<2, false, PL, PG>(p, first, last, persistent, s);
-  return launch_mt<3, false, PL, PG>(p, first, last, persistent, s);
+  if (p.kt == 2) return launch_kt<2, PL, PG>(p, first, last, persistent, s);
+  if (p.kt == 4) return launch_kt<kt_of<PL>(4), PL, PG>(p, first, last, persistent, s);
+  return launch_kt<8, PL, PG>(p, first, last, persistent, s);
 }
 
 bool fused_planes_supported(int mask) {
@@ -2846,15 +2855,15 @@ bool fused_planes_supported(int mask) {
   return false;
 }
 
-int fused_check_residency(int nwg, int planes, int paged) {
+int fused_check_residency(int nwg, int kt, int planes, int paged) {
   int dev = 0, cus = 0;
   SSD_HIP(hipGetDevice(&dev));
   SSD_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
   if (paged) {
     SSD_CHECK_ARG(planes == kFusedDefaultPlanes, "a paged trunk takes the default activation planes only");
-    return check_residency_pl<PlanesOf<kFusedDefaultPlanes>, true>(nwg, cus);
+    return check_residency_pl<PlanesOf<kFusedDefaultPlanes>, true>(nwg, cus, kt);
   }
-#define X(m) if (planes == (m)) return check_residency_pl<PlanesOf<(m)>, false>(nwg, cus);
+#define X(m) if (planes == (m)) return check_residency_pl<PlanesOf<(m)>, false>(nwg, cus, kt);
   SSD_FUSED_PLANE_MASKS
 #undef X
   set_error("fused pass: plane configuration %d is not compiled in", planes);
@@ -2906,6 +2915,7 @@ int launch_fused(const FusedParams& p, int first, int last, int persistent, hipS
                     (16 / p.G) * p.SL <= 64,
                 "bad attention split");
   SSD_CHECK_ARG(first >= 0 && last <= fused_last_phase(p.L) && first <= last, "bad phase range");
+  SSD_CHECK_ARG((p.kt == 2 || p.kt == 4 || p.kt == 8) && p.kt * 256 == p.d && p.lm.KTW == p.kt, "fused pass: no kernel for a width of %d", p.d);
   SSD_CHECK_ARG(p.NS <= 16 && (p.NS == 1 || p.arrivals), "fused pass: %d key splits (at most 16, with arrival counters)", p.NS);
   SSD_CHECK_ARG(p.qkv_ug == 0 || (p.qkv_flags && p.qkv_ug <= 16 && p.qkv_ug == 2 * p.G + 4 && p.Hkv <= 8 && 8 % p.Hkv == 0 &&
                                   8 * p.qkv_ug <= p.nwg && (!persistent || first == 0)),

@@ -693,6 +693,7 @@ int fused_setup(ssd_ctx* c) {
   SSD_TRY(fused_grid_size(&p.nwg));
   p.L = L; p.d = d.d_model; p.qd = d.q_dim(); p.kvd = d.kv_dim(); p.qkvd = d.qkv_dim(); p.ffn = d.d_ffn; p.V = d.vocab;
   p.Hq = d.n_q_heads; p.Hkv = d.n_kv_heads; p.G = d.n_q_heads / d.n_kv_heads; p.eps = d.rms_eps;
+  p.kt = d.d_model / 256;
   p.embed = (const bf16_t*)m->embed;
   p.final_norm = (const bf16_t*)m->final_norm;
   p.lm = m->fused_lm;
@@ -748,7 +749,7 @@ int fused_setup(ssd_ctx* c) {
   // xn, att, act as one fp16 plane unless two planes are asked for; q, p as asked
   p.planes = ((c->flags >> 8) & 31) | (c->flags & SSD_CTX_TWO_PLANES ? 0 : 7);
   if (narrow && !fused_planes_supported(p.planes)) { set_error("fused pass: plane configuration %d is not compiled in", p.planes); return SSD_EINVAL; }
-  if (c->fused_mode == 2) SSD_TRY(fused_check_residency(p.nwg, p.planes, c->kv_pages ? 1 : 0));
+  if (c->fused_mode == 2) SSD_TRY(fused_check_residency(p.nwg, p.kt, p.planes, c->kv_pages ? 1 : 0));
   {
     void* host_word = nullptr;
     hipError_t e = hipHostMalloc(&host_word, 64, hipHostMallocMapped);
@@ -774,10 +775,6 @@ int fused_setup(ssd_ctx* c) {
       fits = m->fused_layers[l].qkv.KS == 1 && m->fused_layers[l].qkv.n_units == 2 * p.Hq + 4 * p.Hkv;
     if (fits) p.qkv_ug = ug;
   }
-  p.deep = 1;   // ring depth of the gate/up and LM-head streaming loops
-  for (int l = 0; l < L; ++l)
-    if (m->fused_layers[l].gu.KTW % 4) p.deep = 0;
-  if (m->fused_lm.KTW % 4) p.deep = 0;
   // Layer tables, one per first sequence of a pass: a pass takes as many whole sequences as fit kFusedMaxRows rows, and
   // the kernel numbers sequences and rows from 0, so the KV pointers of table s start at sequence s (and at its first
   // branch row).
@@ -996,7 +993,7 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
     // could not all be resident keeps the wide passes.
     int grid = 0;
     c->small_passes = c->wide_prefill && d.d_model >= 1024 && !(cfg->flags & SSD_CTX_FUSED_PHASES) && fused_grid_size(&grid) == SSD_OK &&
-                      (c->fused_mode == 2 || fused_check_residency(grid, 7, cfg->kv_pages ? 1 : 0) == SSD_OK);
+                      (c->fused_mode == 2 || fused_check_residency(grid, d.d_model / 256, 7, cfg->kv_pages ? 1 : 0) == SSD_OK);
   }
   const int R = c->max_rows;
   if (!c->fused_mode) {

@@ -449,11 +449,11 @@ def test_small_bf16_corner_shapes(B, name, shape, kw):
     (2, 130, 3, 5),     # three tiles: 40 rows of two sequences
     (1, 2100, 5, 8),    # 48 rows, key splits merged by their last unit
 ])
-def test_bf16_gate_up_with_all_weights_ahead(B, batch, P, K, F):
-    """Model width 2048: gate/up requests a wavefront's whole unit before the barrier and meets the row scales after its MFMAs;
-    with 64 units most workgroups have none.  (The 1B shape has one for each of 256.  More units than workgroups do not exist:
-    the down-projection of such a d_ffn does not fit the persistent pass.)"""
-    shape = _small(n_layers=2, d_model=2048, n_q_heads=16, n_kv_heads=4, d_ffn=2048)
+@pytest.mark.parametrize("width,heads,d_ffn", [(512, 8, 1024), (1024, 16, 2048), (2048, 16, 2048)])
+def test_bf16_gate_up_with_all_weights_ahead(B, width, heads, d_ffn, batch, P, K, F):
+    """Gate/up requests a wavefront's whole unit (2, 4 and 8 k-tiles) before the barrier and meets the row scales after its MFMAs;
+    with 32 and 64 units most workgroups have none.  (The 1B shape has one for each of 256.)"""
+    shape = _small(n_layers=2, d_model=width, n_q_heads=heads, n_kv_heads=heads // 4, d_ffn=d_ffn)
     _run_round_parity(B, shape, batch=batch, P=P, K=K, F=F, seed=51, synthetic_kv=True)
 
 
