@@ -1503,26 +1503,27 @@ __global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, 
   stamp(p, e.ph, 2);
 }
 
-// The residual stream of a wide pass: a workgroup per row, the rows dealt to the XCDs in pieces of 8 (wide_rows.h).  EMBED: h =
-// the token's embedding; otherwise h += the row's partial sums of the linear layer before, slice after slice.  Then (h * gain) as
-// the fp16 B operand of the next linear layer (8 consecutive features per thread are one lane's 16 bytes of it), the row's 1/rms,
-// which that layer's epilogue multiplies in, and, where asked for, the normalised row as fp32 hidden states.  Reads S + 1 rows of
-// d floats; launch and two memory round trips are about 4 us of what it takes.  1B shape, us per launch, mean of those behind o and
-// down, with pieces of 8 rows / single rows / an eighth of the rows per XCD: 8 rows 3.8 / 4.0 / 3.7, 16 rows 3.8 / 4.1 / 3.9,
-// 54 rows 4.6 / 4.6 / 4.5, 64 rows 4.5 / 4.6 / 4.5, 80 rows 4.8 / 4.8 / 4.6, 96 rows 4.8 / 4.9 / 4.5, 130 rows 4.9 / 5.0 / 5.1,
-// 160 rows 5.0 / 5.0 / 5.1, 260 rows 5.1 / 5.4 / 5.4, 384 rows 5.3 / 6.0 / 5.3, 1020 rows 10.3 / 11.5 / 10.2.  Where the launch
-// itself is no shorter the one behind it is: 8-layer passes, us, 16 rows 586 / 588 / 591, 54 rows 695 / 698 / 698, 80 rows 706 /
-// 710 / 708, 96 rows 727 / 731 / 729, 130 rows 836 / 842 / 850, 260 rows 1149 / 1157 / 1156, 384 rows 1233 / 1249 / 1241, 299 prompt tokens
-// 862 / 884 / 880, 1020 tokens 1622 / 1646 / 1625.  (Pieces of 4 rows: as pieces of 8, prompts of 200 and 299 tokens 1 % longer.)
+// The residual stream of a wide pass: a workgroup per row.  EMBED: h = the token's embedding; otherwise h += the row's partial sums of
+// the linear layer before, slice after slice.  Then (h * gain) as the fp16 B operand of the next linear layer (8 consecutive
+// features per thread are one lane's 16 bytes of it), the row's 1/rms, which that layer's epilogue multiplies in, and, where
+// asked for, the normalised row as fp32 hidden states.  Reads S + 1 rows of d floats: at 96 rows of the 1B shape (S = 4 and 8)
+// 4.9 us, at 384 (S = 2) 5.3, at 1020 10.3, of which launch and two memory round trips are about 4.
+// PIECES: rows go to the XCDs in pieces of 8 (wide_rows.h) instead of singly; see launch_wide_resid.
 // CLOCKS: with phase clocks (an instance of its own: the test of p.prof alone cost a wide round 1 %).
-template <bool EMBED, bool CLOCKS>
+template <bool EMBED, bool PIECES, bool CLOCKS>
 __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p, const float* part, int S, const bf16_t* gain,
                                                                   float* hidden, int ph) {
   constexpr int kHeld = 2;                       // 8-feature chunks per thread kept in registers (d <= 4096); others are re-read
   __shared__ float sum_s[kWideWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int m = wide_resid_row((int)blockIdx.x);
-  if (m >= p.M) return;
+  const int m = PIECES ? (int)wide_resid_row(blockIdx.x) : (int)blockIdx.x;
+  if (PIECES) {
+    // What the row's first loads need comes in one batch of scalar loads with the number of rows; left to itself the compiler loads
+    // that alone, waits, and asks for the rest behind the branch.
+    if (EMBED) asm volatile("" ::"s"(p.M), "s"(p.d), "s"(p.V), "s"(p.tokens), "s"(p.embed), "s"(gain));
+    else asm volatile("" ::"s"(p.M), "s"(p.d), "s"(p.h), "s"(part), "s"(S), "s"(gain));
+    if (m >= p.M) return;
+  }
   if (CLOCKS) stamp(p, ph, EMBED ? 0 : 6, m);       // (the phase's other slots are the linear layer's)
   gfloat* h = (gfloat*)p.h + (int64_t)m * p.d;
   int tok = 0;
@@ -2775,14 +2776,28 @@ int launch_wide_logits(const FusedParams& p, const WideEpi& e, hipStream_t s) {
   return launch_wide_tile<4, FE_LOGITS, 2, kWideGroup>(p, p.lm, p.xn, e, s);
 }
 
-int launch_wide_resid(const FusedParams& p, bool embed, const float* part, int S, const bf16_t* gain, float* hidden, int ph, hipStream_t s) {
-  const int grid = wide_resid_grid(p.M);
-  if (embed && p.prof) wide_resid_kernel<true, true><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
-  else if (embed) wide_resid_kernel<true, false><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
-  else if (p.prof) wide_resid_kernel<false, true><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
-  else wide_resid_kernel<false, false><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
+template <bool EMBED>
+int launch_wide_resid_e(const FusedParams& p, const float* part, int S, const bf16_t* gain, float* hidden, int ph, bool pieces, hipStream_t s) {
+  const unsigned grid = pieces ? wide_resid_grid((unsigned)p.M) : (unsigned)p.M;
+  if (pieces && p.prof) wide_resid_kernel<EMBED, true, true><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
+  else if (pieces) wide_resid_kernel<EMBED, true, false><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
+  else if (p.prof) wide_resid_kernel<EMBED, false, true><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
+  else wide_resid_kernel<EMBED, false, false><<<grid, kWideThreads, 0, s>>>(p, part, S, gain, hidden, ph);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
+}
+
+// Single rows send every 128-byte line of the operand to memory in eight parts, one from each die; pieces of 8 rows send it whole, but
+// leave the few rows of a small launch on few dies, whose L2s then take longer to write back than eight would (the launch itself is
+// shorter, the one behind it starts later).  Whole passes of 8 layers of the 1B shape, us, single rows / pieces: 8 rows 571 / 577, 32
+// rows 600 / 604, 64 rows 688 / 687, 96 rows 724 / 725, 130 rows 838 / 835, 160 rows 845 / 841, 260 rows 1144 / 1137, 384 rows 1240 /
+// 1225, prompts of 299 tokens 871 / 861, 450 tokens 1090 / 1078, 1020 tokens 1622 / 1602.  16 layers of width 1024: 16 rows 669 / 677, 130 rows
+// 941 / 942, 260 rows 1149 / 1153, 384 rows 1200 / 1206, prompts of 450 tokens 1403 / 1393, 1020 tokens 1805 / 1787; of width 512: 16 rows 500
+// / 503, 130 rows 715 / 716, 260 rows 868 / 875, 384 rows 893 / 897, prompts of 450 tokens 1086 / 1064, 1020 tokens 1312 / 1216.
+int launch_wide_resid(const FusedParams& p, bool embed, const float* part, int S, const bf16_t* gain, float* hidden, int ph, hipStream_t s) {
+  const bool pieces = p.M > kFusedWideRows || (p.d >= 2048 && p.M >= 128);
+  return embed ? launch_wide_resid_e<true>(p, part, S, gain, hidden, ph, pieces, s)
+               : launch_wide_resid_e<false>(p, part, S, gain, hidden, ph, pieces, s);
 }
 
 // One wide pass: phases [first, last] as one launch each (two for o and down).  layers_host: the pass's layer table in host

@@ -16,8 +16,8 @@ def lib(tmp_path_factory):
     d = tmp_path_factory.mktemp("wide_rows")
     src, so = d / "rows.cpp", d / "rows.so"
     src.write_text('#include "wide_rows.h"\n'
-                   'extern "C" int grid_of(int rows) { return ssd::wide_resid_grid(rows); }\n'
-                   'extern "C" void rows_of(int grid, int* out) { for (int b = 0; b < grid; ++b) out[b] = ssd::wide_resid_row(b); }\n')
+                   'extern "C" int grid_of(int rows) { return (int)ssd::wide_resid_grid((unsigned)rows); }\n'
+                   'extern "C" void rows_of(int grid, int* out) { for (int b = 0; b < grid; ++b) out[b] = (int)ssd::wide_resid_row((unsigned)b); }\n')
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(so), str(src)], check=True)
     return ctypes.CDLL(str(so))
 
