@@ -502,7 +502,8 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
     // it: the flood slows the o-projection's last workgroups, so more of it, earlier, loses (requested under the o-projection: 24-row
     // rounds over 1024 keys 4.97 -> 5.8 ms; a part held back until the barrier: 5.0 to 5.2).  Against the ring, 24 rows over 1024
     // keys 5057 -> 4968 us per round, 8 rows over 211 keys 3044 -> 2971, single-token drafting 4000 -> 3945, 48 rows over 8192 keys
-    // 7429 -> 7415.  16 layers of width 1024 (d_ffn 4096) and
+    // 7429 -> 7415.  (The scales behind the MFMAs alone: 4988 -> 4960, 2990 -> 2957, single-token drafting 3980 -> 4007, 48 rows over 8192
+    // keys 7139 -> 7131.)  16 layers of width 1024 (d_ffn 4096) and
     // 512 (2048), rounds: 8 rows over 211 keys 2215 -> 2083 and 2078 -> 1975, 24 rows over 1024 keys 3666 -> 3472 and 3443 -> 3263, 48 rows
     // over 8192 keys 4771 -> 4563 and 4131 -> 3941; five single tokens over 1024 keys 2794 -> 2639 and 2633 -> 2463.
     if (my_unit >= g.n_units) {
@@ -1985,8 +1986,6 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
     bf16x8 k[2][2];
     bf16x8 vt[4];
   };
-  // (3 or 4 blocks fit the registers but lose: 24 rows over 1024 keys 4941 -> 5183 or 5193 us per round, 48 rows over 8192 keys
-  // 7310 -> 7559 or 7434: what a wavefront polls for returns behind its K/V loads, and a compute unit ingests no more of them)
   constexpr int RING = 2;
   KvBlock ring[RING];
   auto load_trunk = [&](KvBlock& tb, int i) {   // i-th block of this wavefront, clamped to its last one

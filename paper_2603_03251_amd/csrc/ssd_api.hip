@@ -594,13 +594,15 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
 }
 
 // A pass of few rows in a context that runs wide passes: one persistent launch is shorter than seven launches per layer for as
-// long as it takes the rows (1B shape, one extend with logits over 1500 keys: 12 rows 0.89 against 1.14 ms, 24 rows 0.91 against
-// 1.17; 48 rows, which four and six row tiles of that kernel would extend: 54 rows 6 % shorter than a wide pass, 72 and 96 rows 10 %
+// long as it takes the rows (1B shape, one extend with logits over 1500 keys: 12 rows 0.86 against 1.15 ms, 24 rows 0.87 against
+// 1.18, 48 rows 0.92 against 1.28; four and six row tiles, tried once: 54 rows 6 % shorter than a wide pass, 72 and 96 rows 10 %
 // longer) and its attention units, which take one query tile where those of a wide pass take up to three, do not pull the
-// same keys too often.  What the launches and the earlier weight loads save was measured as 0.18 us per layer and million
-// weights of it, what the units cost more is what the plans of the two say (ms, 1B shape: 3 x 16 rows over 8192 keys 1.33
-// against 1.47 as a wide pass, over 16384 1.68 against 1.63, 131072 5.5 against 4.1; 6 x 8 rows 1.42, 1.54; 1.83, 1.81; 6.3, 5.5;
-// width 1024, 6 x 8 rows: 0.48, 0.53; 0.58, 0.59; 2.3, 1.5; sequences of one query tile stay shorter to the last length).
+// same keys too often.  What the launches and the earlier weight loads save is taken as 0.18 us per layer and million
+// weights of it, what the units cost more is what the plans of the two say (ms, 1B shape: 3 x 16 rows over 8192 keys 1.26
+// against 1.46 as a wide pass, over 16384 1.61 against 1.64, 32768 2.21 against 2.00, 131072 5.4 against 4.1; 6 x 8 rows 1.34, 1.54;
+// 1.75, 1.81; 2.43, 2.37; 6.3, 5.5; width 1024, 6 x 8 rows over 8192 keys 0.86, 1.04, 16384 1.08, 1.17, 131072 4.2, 3.0; sequences of
+// one query tile stay shorter to the last length).  The line falls between 12000 and 16384 keys; the persistent pass, which has
+// become 3 to 7 % shorter since the 0.18 was fitted, would now be 2 to 13 % shorter at 16384 too.
 // Not into a graph that is being captured: persistent launches take turns by events, which a replay would not see.
 // seqs x T rows, the longest trunk with stored keys a row sees.
 bool takes_small_pass(const ssd_ctx* c, int seqs, int T, int stored, hipStream_t s) {
@@ -628,8 +630,8 @@ int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset,
 }
 
 // What a prompt pass of `rows` rows costs, in rows: the weights it streams, its launches, and one more step where the row groups
-// of 128 begin (1B shape, ms: 64 rows 1.13, 128 1.32, 256 1.69, 384 1.91, 385 2.21, 512 2.38, 768 2.98, 1024 3.43; as a persistent
-// pass 10 rows 0.66, 48 rows 0.80.  Narrower models pay more for a pass and less for a row).
+// of 128 begin (1B shape, ms: 64 rows 1.10, 128 1.31, 256 1.69, 384 1.77, 385 2.08, 512 2.21, 768 2.84, 1024 3.27; as a persistent
+// pass 10 rows 0.64, 48 rows 0.73.  Narrower models pay more for a pass and less for a row).
 int prompt_pass_cost(const ssd_ctx* c, int rows) {
   if (rows <= kFusedMaxRows && c->small_passes) return 300;
   return 450 + rows + (rows > kFusedWideRows ? 80 : 0);
@@ -660,7 +662,7 @@ int next_prompt_group(const ssd_ctx* c, const int32_t* lens, int n) {
 // several sequences where their prompts are short: a pass streams every weight once, so what a prompt costs is above all its
 // number of passes.  Otherwise chunks of K+1 tokens of all sequences.  Contexts whose rounds are narrow passes also take such a
 // chunk where it holds the whole prompts of a group: one persistent launch is shorter than a wide pass of as few rows (1B shape,
-// 6 rows 0.65 against 0.90 ms, 48 rows 0.80 against 1.05).
+// 10 rows 0.64 against 0.91 ms, 48 rows 0.73 against 1.03).
 int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t* lens, int b0, int nb, hipStream_t s) {
   const int K1 = c->K + 1;
   for (int g0 = 0, gn = 0; g0 < nb; g0 += gn) {
@@ -989,7 +991,8 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
     c->prompt_rows = c->wide_prefill && (int64_t)c->B * c->max_trunk > kFusedWideRows ? kFusedPromptRows : kFusedWideRows;
     if (c->wide_prefill) c->max_rows = std::max(c->max_rows, c->prompt_rows);
     // Few-row extends on the persistent pass: from a width of 1024 on (16 to 48 rows, 100 and 4000 keys: width 1024, 8 layers,
-    // 283..463 us against 327..498 as wide passes; width 512, 4 layers, 142..189 against 131..192).  A context whose workgroups
+    // 268..431 us against 328..514 as wide passes; width 512, 4 layers, 141..187 against 141..202, 16 layers 476..675 against 485..818;
+    // the line was drawn when width 512 took 152..196 and 520..710).  A context whose workgroups
     // could not all be resident keeps the wide passes.
     int grid = 0;
     c->small_passes = c->wide_prefill && d.d_model >= 1024 && !(cfg->flags & SSD_CTX_FUSED_PHASES) && fused_grid_size(&grid) == SSD_OK &&
