@@ -350,9 +350,13 @@ def test_wide_passes_agree_with_narrow_passes_and_repeat_bit_for_bit(B):
     assert e < TOL["bf16"]
 
 
-def test_phase_clocks_of_a_wide_pass_cover_every_launch(B):
-    """Wide passes: the embedding, and the residual launches behind o and down, record entry and end like the other launches."""
-    shape, seed, nb, P, K, F = SMALL_BF16, 24, 3, 50, 4, 5
+@pytest.mark.parametrize("wide_rows", [dict(width=512, nb=3, F=5), dict(width=2048, nb=4, F=7)], ids=["single rows", "rows in pieces"])
+def test_phase_clocks_of_a_wide_pass_cover_every_launch(B, wide_rows):
+    """Wide passes: the embedding, and the residual launches behind o and down, record entry and end like the other launches, row by
+    row (75 rows of width 512; 140 rows of width 2048, which the dies take in pieces of 8)."""
+    width, nb, F = wide_rows["width"], wide_rows["nb"], wide_rows["F"]
+    shape = SMALL_BF16 if width == 512 else _small(d_model=width, n_q_heads=16, n_kv_heads=4, d_ffn=width)
+    seed, P, K = 24, 50, 4
     model = B.ssd_model_create(shape, I.make_weights(shape, seed))
     ctx = B.ssd_ctx_create(model, nb, K, F, P + 4 * K + 8)
     try:
@@ -433,6 +437,8 @@ def _small(**over):
     # (6 k-tiles of the down-projection per wavefront: not a number the persistent pass unrolls)
     ("a width of d_ffn the fused passes do not take", _small(d_model=1024, n_q_heads=16, n_kv_heads=4, d_ffn=1536),
      dict(batch=1, P=90, K=4, F=4, seed=8, synthetic_kv=True, expect_pass=0)),
+    ("140 rows of width 2048: residual rows in pieces, the last of 4", _small(n_layers=1, d_model=2048, n_q_heads=16, n_kv_heads=4, d_ffn=2048),
+     dict(batch=4, P=50, K=4, F=7, seed=15, synthetic_kv=True)),
     ("56 rows per sequence: wide passes", _small(n_layers=1), dict(batch=1, P=50, K=6, F=8, seed=11, synthetic_kv=True)),
     ("seven sequences of different lengths", _small(n_layers=1),
      dict(batch=7, P=12, K=2, F=2, seed=14, synthetic_kv=False, lens=[12, 1, 5, 9, 2, 12, 7])),
