@@ -14,8 +14,7 @@ constexpr int kFusedThreads = 512;  // 8 wavefronts; they split the reduction di
 constexpr int kFusedWaves = 8;
 constexpr int kFusedMaxRows = 48;   // rows of one narrow pass (three 16-row MFMA tiles)
 constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles) of a round or extend: contexts with more than kFusedMaxRows rows
-constexpr int kFusedPromptRows = 1024;     // rows of a wide pass that only fills the trunk (prompts): eight row groups of
-constexpr int kFusedPromptRowGroup = 128;  // this many rows
+constexpr int kFusedPromptRows = 1024;    // rows of a wide pass that only fills the trunk (prompts)
 constexpr int kFusedWideQueryTiles = 3;   // wide passes: most query tiles per attention unit
 constexpr int kFusedWideFreshKeys = 192;  // wide passes: keys of the pass itself an attention unit has LDS room for
 // Wide extends of more tokens of a sequence append their keys before the attention.  4 layers of the 1B shape, one prompt, us per
@@ -23,7 +22,6 @@ constexpr int kFusedWideFreshKeys = 192;  // wide passes: keys of the pass itsel
 // the units have room for) 326 / 337.  The two cross near 120 rows; the line lies below that and costs 1 to 3 % in between.
 constexpr int kFusedWideAppendRows = 64;
 constexpr int kFusedWideSlices = 8;       // wide passes: most k-slices of the o- and down-projections (one per XCD)
-constexpr int kFusedWideRowGroup = 96;    // wide passes: rows of a full row group of a linear layer
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())
 constexpr int kFusedMaxSlices = 4;   // most k-slices of a linear layer
 constexpr int kFusedMaxSplits = 16;  // most key splits of an attention pass

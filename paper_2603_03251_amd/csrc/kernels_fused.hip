@@ -34,6 +34,7 @@
 #include <vector>
 
 #include "fused.h"
+#include "wide_blocks.h"
 #include "wide_rows.h"
 
 namespace ssd {
@@ -103,10 +104,11 @@ __device__ __forceinline__ f32x4 fix_empty() {
 // for loads degrade to "wait for everything", which would empty the weight pipeline at every unit of the LM head.
 // Hidden, the store only makes a later counted wait err on the safe side: loads complete in order among themselves,
 // so "at most N operations outstanding" still implies that every load older than the N youngest has arrived.
-// (the s_nop: a store of more than 8 bytes must not be followed at once by a VALU write of its data registers, a
-// hazard the compiler covers for its own stores and cannot see inside this one)
+// (the s_nop: a VALU write of its data registers has to stay two instructions behind a store of more than 8 bytes, a hazard the
+// compiler covers for its own stores and cannot see inside this one; and v must come from a VALU instruction, not straight from an
+// MFMA, whose latency it would not wait out either)
 __device__ __forceinline__ void st_f32x4_uncounted(float* p, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 0" : : "v"(p), "v"(v));
+  asm volatile("global_store_dwordx4 %0, %1, off\n\ts_nop 1" : : "v"(p), "v"(v));
 }
 // Thread coordinates read afresh where they are called: everything derived from them (row and tile indices, LDS and
 // global addresses) is then local to the phase that computes it.  Derived from the kernel-wide threadIdx they would be
@@ -1254,39 +1256,12 @@ __device__ __forceinline__ void attn_merge_unit(const FusedParams& p, int mt, in
 // and the memory-side cache alike, at 6-7.4 TB/s (24-29 GB/s per compute unit).  So a layer's cost is what crosses into the
 // L2s: the weights once, and the activations once per XCD that needs them.
 //
-// Linear layers (wide_gemm_kernel).  A "pair" = (4 feature tiles, one group of MTG row tiles) over one of S slices of the
-// reduction dimension.  A workgroup is 4 wavefronts, ONE per SIMD, so each may use all 512 vector registers: 96 hold
-// the 24 accumulator tiles, the rest a ring of kWideRing register chunks, 7 of them (70 KiB per wavefront) in flight
-// while one is multiplied.  The wavefronts split the slice; each streams its own weight tiles (A operands, straight from
-// the stream-order layout, in which the k-tiles of a tile group are one contiguous run) and the matching activation tiles
-// of the row group (B operands, one fp16 plane): 24 MFMAs per 10 KiB pulled.  The four partial tiles meet in LDS (96 KiB)
-// and are added in wavefront order.
-// The o- and down-projections have few features (32 sets of 4 tiles at the 1B shape) under a long reduction dimension:
-// they are cut S ways so that every compute unit has a pair, XCD x working on slice x mod S, so that an XCD's L2 takes in
-// only that slice of the activations and, among the XCDs of a slice, only its own sets' weights.  Their fp32 partial sums
-// go to memory, and wide_resid_kernel, a workgroup per row, adds them to the residual stream in slice order and leaves the
-// row's 1/rms: the linear layers that follow load one number per row where they had to add up partial sums of squares.  (Small row groups instead of
-// slices, S = 1 and the residual in the epilogue, pulled every set's weights once per row group and the whole activation
-// matrix into every XCD: the down-projection took 23 / 28 / 33 us at 96 / 170 / 384 rows; now 15.8 / 18.5 / 28 and 5 to 6
-// for the residual kernel, and the kernels behind it 1.5 to 2.5 us less each.)
-constexpr int kWideTiles = kFusedWideRows / 16;
-constexpr int kWideGroup = kFusedWideRowGroup / 16;
-constexpr int kWideRing = 8;
+// Linear layers: wide_block_kernel, below.  The o- and down-projections have few features under a long reduction dimension: they are
+// cut into up to 8 k-slices, XCD x working on slice x mod S, so that an XCD's L2 takes in only that slice of the activations and, among
+// the XCDs of a slice, only its own features' weights.  Their fp32 partial sums go to memory, and wide_resid_kernel, a workgroup per
+// row, adds them to the residual stream in slice order and leaves the row's 1/rms: the linear layers that follow load one number per
+// row where they had to add up partial sums of squares.
 constexpr int kWideThreads = 256, kWideWaves = 4;
-
-// plain stores the compiler does not count (see st_f32x4_uncounted)
-__device__ __forceinline__ void st_u64_uncounted(void* p, uint64_t v) {
-  asm volatile("global_store_dwordx2 %0, %1, off" : : "v"(p), "v"(v));
-}
-__device__ __forceinline__ void st_f32_uncounted(float* p, float v) {
-  asm volatile("global_store_dword %0, %1, off" : : "v"(p), "v"(v));
-}
-
-template <int MTG>
-struct WideChunk {
-  bf16x8 a[4];
-  bf16x8 b[MTG];
-};
 
 struct WideEpi {
   float* out;          // QKV: [M][ld] projections, row scale applied; LOGITS: [M][ld] logits; PART: [slice][M][ld] partial sums
@@ -1296,211 +1271,198 @@ struct WideEpi {
   int ph;              // phase id (for the optional clocks)
 };
 
-// ATW: feature tiles per unit of the layer's stream-order layout (2: qkv, o, down; 4: gate/up).
-// D: chunks of the ring (kWideRing; half of it for slices too short for whole turns of the full ring, and for MTG = 12).
-// MTG: row tiles per row group.  Even: the MFMAs are 32x32x16, which a wavefront alone on its SIMD issues back to back (a
-// 16x16x32 every 28 clocks: the same time at 6 row tiles, but at 12 the 48 of a chunk would outlast its loads); both
-// operands stay in their 16x16x32 tile order, see wide_tile_kernel.
-template <int ATW, int EPI, int D, int MTG>
-__global__ __launch_bounds__(kWideThreads) void wide_gemm_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
-  constexpr int MTOT = kWideTiles;
-  constexpr bool BIG = MTG % 2 == 0;
-  constexpr int MT32 = MTG / 2;
-  constexpr int ROUNDS = MTG > kWideGroup ? 2 : 1;   // the partial tiles meet in LDS (at most 96 KiB) in this many parts
-  constexpr int NT = 4 * MTG / ROUNDS;               // 1 KiB blocks of a wavefront in a part
-  extern __shared__ f32x4 red[];
-  __shared__ float r_s[EPI == FE_PART ? 1 : kFusedWideRows];
+// Memory to LDS without a register in between: 64 lanes x 16 (4) bytes, lane i at the wavefront's LDS address + 16 i (4 i).
+__device__ __forceinline__ void dma16(const bf16_t* src, uint32_t lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)(uintptr_t)lds, 16, 0, 0);
+}
+__device__ __forceinline__ void dma4(const float* src, uint32_t lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)(uintptr_t)lds, 4, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+// The linear layers of a wide pass.  A workgroup computes a block of FT feature tiles x RT row tiles (16 each) over the whole reduction
+// dimension (PART: over one of S slices of it); WN x WM wavefronts hold FT / WN x RT / WM tiles of it each.  Both operands go from memory
+// to LDS without passing registers, a k-tile (FT + RT KiB) to a buffer (G of them, one for each of G groups of wavefronts, where steps are
+// short), NB buffers in flight; in memory a tile already has the lane order of
+// the MFMA, so a tile is one load, its LDS image the same 1 KiB, and reading it back free of bank conflicts.  A step is one k-tile: wait
+// until the next one has landed, barrier, then the MFMAs of this one with the LDS reads of the next and the loads for the buffer that
+// has just become free between them (sched_barrier: a burst of memory operations would hold up the MFMAs behind it).
+// What bounds it: with many rows the power the chip may draw (under 32x32x16 MFMAs on random data the clock falls to 1.6 GHz: 1.7 PFLOP/s;
+// 16x16x32, taken here, 1.9), so operands are moved as few times as possible: large blocks; with few rows the weight stream and the steps'
+// latency (0.2 us each).  us of a launch at 2048 inputs, 16384 gate/up features, one machine, against the kernels it replaces (64 features
+// with the reduction dimension over the wavefronts, and 256 features x 96 or 128 rows with the weights in registers): 96 rows 18.0 and
+// 21.8 + 2.4 (gap), 192 rows 22.9 and 27 + 2.4, 384 rows 31.3 and 35.1, 1020 rows 61 and 77.  2048 features, 8192 inputs in slices: 96 rows
+// 11.9 and 13.1, 384 rows 22.5 and 28.0.
+// Past its last block a workgroup goes on loading the last k-tile (the waits count loads), and it leaves when everything has landed.
+template <int ATW, int EPI, int FT, int RT, int WN, int G, int NB, int TH>
+__global__ __launch_bounds__(TH) void wide_block_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
+  constexpr int W = TH / 64, WG = W / G, WM = WG / WN, FTW = FT / WN, RTW = RT / WM;
+  constexpr int NTILE = G * (FT + RT), STAGE = NTILE * 64;   // tiles and 16-byte vectors of a buffer
+  constexpr int LPW = (NTILE + W - 1) / W;                   // loads of a wavefront per step (the last tile again where they do not divide)
+  constexpr int NM = FTW * RTW, NF = FTW + RTW, NO = NF + LPW;
+  static_assert(W % G == 0 && WG % WN == 0 && FT % WN == 0 && RT % WM == 0 && FT % ATW == 0 && NB >= 3 && (NB - 1) * LPW < 64, "block shape");
+  static_assert(EPI != FE_SWIGLU || FTW == 2 || FTW % 4 == 0, "a wavefront holds gate tiles together with their up tiles");
+  extern __shared__ f32x4 lds[];                             // [NB][NTILE][64], the rows' 1/rms, then (G > 1) partial tiles
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int NKT = g.KS * kFusedWaves * g.KTW;       // k-tiles of the reduction dimension
-  const int S = EPI == FE_PART ? e.S : 1;
-  const int NCH = NKT / (kWideWaves * S);           // k-tiles per pair of this wavefront (a multiple of D: host check)
-  const int n_groups = g.n_units / g.KS;
-  const int nq = ATW == 4 ? n_groups : n_groups >> 1;
-  const int n_rg = (((p.M + 15) >> 4) + MTG - 1) / MTG;
-  // the pairs of this workgroup: XCD x = blockIdx.x % 8 works on slice x % S and, among the XCDs of that slice, on the tile
-  // sets q = y, y + ys, ..; its workgroups take (set, row group) pairs t = wx, wx + per_xcd, .. with the row group running
-  // fastest
+  const int grp = wave / WG, wn = wave % WG % WN, wm = wave % WG / WN;
+  const int NKT = g.KS * kFusedWaves * g.KTW;                // k-tiles of the reduction dimension
+  const int S = EPI == FE_PART ? e.S : 1, steps = NKT / (S * G);   // (even: host check)
+  const int n_groups = g.n_units / g.KS;                     // units of ATW feature tiles
+  const int n_sets = (n_groups * ATW + FT - 1) / FT;
+  const int n_rg = (((p.M + 15) >> 4) + RT - 1) / RT;
+  // XCD x = blockIdx.x % 8 works on slice x % S and, among the XCDs of that slice, on the sets q = y, y + ys, ..; its workgroups take
+  // (set, row group) pairs t = wx, wx + per_xcd, .. with the row group running fastest
   const int x = (int)blockIdx.x & 7, wx = (int)blockIdx.x >> 3, per_xcd = (int)gridDim.x >> 3;
-  const int slice = x % S, y = x / S, ys = 8 / S;   // S is 1, 2, 4 or 8
-  const int nqy = y < nq ? (nq - y + ys - 1) / ys : 0;
+  const int slice = x % S, y = x / S, ys = 8 / S;            // S is 1, 2, 4 or 8
+  const int nqy = y < n_sets ? (n_sets - y + ys - 1) / ys : 0;
   const int ty = nqy * n_rg;
   const int n_my = wx < ty ? (ty - wx + per_xcd - 1) / per_xcd : 0;
   stamp(p, e.ph, 0);
   if (n_my == 0) return;
-
-  // accumulators: BIG [32 features: tiles 0-1 / 2-3 of the set][32 rows], else [feature tile][row tile]
-  f32x16 accb[2][BIG ? MT32 : 1];
-  f32x4 acc[4][BIG ? 1 : MTG];
-  auto zero_acc = [&]() {
-    if constexpr (BIG) {
-#pragma unroll
-      for (int f = 0; f < 2; ++f)
-#pragma unroll
-        for (int t = 0; t < MT32; ++t)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) accb[f][t][i] = 0.f;
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int t = 0; t < MTG; ++t) acc[j][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    }
-  };
-  zero_acc();
-  // operand vector of this lane in a tile (BIG: in two neighbouring tiles, k-half 0; k-half 1 is 32 vectors further)
-  const int lsrc = BIG ? ((lane >> 4) & 1) * 64 + (lane & 15) + ((lane >> 5) << 4) : lane;
-
-  // The load cursor walks the chunks of this wavefront, pair after pair (clamped to the last one)
-  struct Cursor {
-    const bf16_t* a;     // this wavefront's A tiles of the chunk (feature tile 0 of the set; ATW == 2: of its first tile group)
-    const bf16_t* b;     // B tile 0 of the row group at the chunk's k-tile
-    int i, n;            // chunk in the pair, pair ordinal
-  };
-  const int64_t a_group2 = (int64_t)NKT * 2 * 512;               // ATW == 2: from the set's first tile group to its second
-  const int kt0 = (slice * kWideWaves + wave) * NCH;
-  auto place = [&](Cursor& cu) {
-    const int t = wx + (cu.n < n_my ? cu.n : n_my - 1) * per_xcd;
-    const int qh = t / n_rg;
-    const int q = qh * ys + y, rg = t - qh * n_rg;
-    cu.a = g.w + (int64_t)(ATW == 4 ? q : 2 * q) * NKT * ATW * 512 + (int64_t)kt0 * ATW * 512;
-    cu.b = bsrc + ((int64_t)kt0 * MTOT + rg * MTG) * 512;
-  };
-  auto advance = [&](Cursor& cu) {
-    cu.a += ATW * 512;
-    cu.b += MTOT * 512;
-    if (++cu.i == NCH) {
-      cu.i = 0;
-      ++cu.n;
-      place(cu);
-    }
-  };
-  // (plain, cached loads also for the weights: the other row groups of the same feature tiles, on this XCD, find them in
-  // its L2; a streaming hint would make every row group fetch them from memory again, and with one row group it measured
-  // slower too: down 17.6 instead of 15.8 us at 96 rows)
-  auto load_chunk = [&](WideChunk<MTG>& ck, const Cursor& cu) {
-    const gbf16x8* ap = (const gbf16x8*)cu.a + lsrc;
-    const gbf16x8* ap2 = ATW == 4 ? ap + 128 : (const gbf16x8*)(cu.a + a_group2) + lsrc;
-    ck.a[0] = ap[0];                         // BIG: [2 f + h], features 32 f .. 32 f + 31 of the set, k-half h
-    ck.a[1] = ap[BIG ? 32 : 64];
-    ck.a[2] = ap2[0];
-    ck.a[3] = ap2[BIG ? 32 : 64];
-    const gbf16x8* bp = (const gbf16x8*)cu.b + lsrc;
-#pragma unroll
-    for (int t = 0; t < MTG; ++t) ck.b[t] = BIG ? bp[(t >> 1) * 128 + (t & 1) * 32] : bp[t * 64];   // BIG: [2 t + h]
-  };
-  float rs0, rs1;                                   // the rows' 1/rms: requested first, in LDS under the ring's loads
-  if constexpr (EPI != FE_PART) {
-    rs0 = ((const gfloat*)p.ssq)[min((int)threadIdx.x, p.M - 1)];
-    rs1 = ((const gfloat*)p.ssq)[min((int)threadIdx.x + kWideThreads, p.M - 1)];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+  float* r_s = (float*)(lds + NB * STAGE);
+  if (EPI != FE_PART) {
+    for (int r = wave * 64; r < p.M; r += TH) dma4(p.ssq + min(r + lane, p.M - 1), lds0 + NB * STAGE * 16 + r * 4);
   }
-  WideChunk<MTG> ring[D];
-  Cursor cu{nullptr, nullptr, 0, 0};
-  place(cu);
+  // feature tile of the block that is this wavefront's f-th: whole units, or (two tiles a wavefront) a gate tile and its up tile
+  auto tile_of = [&](int f) { return EPI == FE_SWIGLU && FTW == 2 ? (wn >> 1) * 4 + (wn & 1) + 2 * f : wn * FTW + f; };
+  auto pair_of = [&](int n, int& set, int& rg) {
+    const int t = wx + min(n, n_my - 1) * per_xcd, qh = t / n_rg;
+    set = qh * ys + y;
+    rg = t - qh * n_rg;
+  };
+  // the loads: step ld_k of pair ld_n to buffer ld_buf
+  int ld_n = 0, ld_k = 0, ld_buf = 0;
+  const bf16_t* src[LPW];
+  int step_a = G * ATW * 512, step_b = G * p.row_tiles * 512;
+  auto place = [&]() {
+    int set, rg;
+    pair_of(ld_n, set, rg);
+    const bool past = ld_n >= n_my;
+    const int kt0 = (slice * steps + (past ? steps - 1 : 0)) * G;
+    if (past) step_a = step_b = 0;
 #pragma unroll
-  for (int s = 0; s < D - 1; ++s) { load_chunk(ring[s], cu); advance(cu); }
-  if constexpr (EPI != FE_PART) {                   // (read behind the barriers of the reduction)
-    r_s[threadIdx.x] = rs0;
-    if ((int)threadIdx.x < kFusedWideRows - kWideThreads) r_s[threadIdx.x + kWideThreads] = rs1;
+    for (int n = 0; n < LPW; ++n) {
+      // (units behind the last and row tiles behind the last row: the last one again, computed and not stored)
+      const int i = min(wave * LPW + n, NTILE - 1), kt = kt0 + i / (FT + RT), t = i % (FT + RT);
+      src[n] = t < FT ? g.w + (((int64_t)min(set * (FT / ATW) + t / ATW, n_groups - 1) * NKT + kt) * ATW + t % ATW) * 512
+                      : bsrc + ((int64_t)kt * p.row_tiles + min(rg * RT + t - FT, (p.M - 1) >> 4)) * 512;
+    }
+  };
+  auto load = [&](int n) {
+    const int i = min(wave * LPW + n, NTILE - 1);
+    dma16(src[n] + lane * 8, lds0 + (ld_buf * STAGE + i * 64) * 16);
+    src[n] += i % (FT + RT) < FT ? step_a : step_b;
+  };
+  auto next_load = [&]() {
+    ld_buf = ld_buf + 1 == NB ? 0 : ld_buf + 1;
+    if (++ld_k == steps) {
+      ld_k = 0;
+      ++ld_n;
+      place();
+    }
+  };
+  place();
+  for (int s = 0; s < NB; ++s) {
+#pragma unroll
+    for (int n = 0; n < LPW; ++n) load(n);
+    next_load();
   }
   stamp(p, e.ph, 3);
-  // One load of a chunk to come behind each MFMA (two where a chunk has fewer MFMAs than loads): a burst of them blocks the one
-  // wavefront of a SIMD until the vector memory path has taken it in, 640 clocks per chunk of six row tiles and four wavefronts,
-  // with the matrix cores idle behind it
-  constexpr int NM = 4 * (BIG ? MT32 : MTG), NL = 4 + MTG;
-  auto turn = [&](const WideChunk<MTG>& ck, WideChunk<MTG>& to) {
-    const gbf16x8* ap = (const gbf16x8*)cu.a + lsrc;
-    const gbf16x8* ap2 = ATW == 4 ? ap + 128 : (const gbf16x8*)(cu.a + a_group2) + lsrc;
-    const gbf16x8* bp = (const gbf16x8*)cu.b + lsrc;
+  bf16x8 a[2][FTW], b[2][RTW];
+  f32x4 acc[FTW][RTW];
 #pragma unroll
-    for (int i = 0; i < NM; ++i) {
-      if constexpr (BIG) {
-        const int h = i / (2 * MT32), f = i / MT32 % 2, t = i % MT32;
-        accb[f][t] = mfma32_f16(ck.a[2 * f + h], ck.b[2 * t + h], accb[f][t]);
-      } else {
-        acc[i / MTG][i % MTG] = mfma16_f16(ck.a[i / MTG], ck.b[i % MTG], acc[i / MTG][i % MTG]);
-      }
+  for (int f = 0; f < FTW; ++f)
 #pragma unroll
-      for (int l = i * NL / NM; l < (i + 1) * NL / NM; ++l) {
-        if (l < 4) to.a[l] = l < 2 ? ap[l * (BIG ? 32 : 64)] : ap2[(l - 2) * (BIG ? 32 : 64)];
-        else to.b[l - 4] = BIG ? bp[((l - 4) >> 1) * 128 + ((l - 4) & 1) * 32] : bp[(l - 4) * 64];
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    advance(cu);
+    for (int t = 0; t < RTW; ++t) acc[f][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  auto fragment = [&](int i, int to, const bf16x8* buf) {
+    if (i < RTW) b[to][i] = buf[(FT + wm * RTW + i) * 64];
+    else a[to][i - RTW] = buf[tile_of(i - RTW) * 64];
   };
-  for (int n = 0; n < n_my; ++n) {
-    const int t = wx + n * per_xcd;
-    const int q = (t / n_rg) * ys + y, rg = t - (t / n_rg) * n_rg;
-    for (int c = 0; c < NCH; c += D) {
+  // loads return in order: the first buffer has landed when only those of the others are outstanding
+  wait_loads<(NB - 1) * LPW>();
+  wg_barrier();
 #pragma unroll
-      for (int s = 0; s < D; ++s) turn(ring[s], ring[(s + D - 1) % D]);
+  for (int i = 0; i < NF; ++i) fragment(i, 0, (const bf16x8*)lds + grp * (FT + RT) * 64 + lane);
+  int rd = 0;
+  for (int n = 0; n < n_my; ++n) {
+    for (int k = 0; k < steps; k += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        // the next k-tile has landed here, behind the barrier everywhere; and everyone has read this one's buffer
+        wait_loads<(NB - 2) * LPW>();
+        wg_barrier();
+        rd = rd + 1 == NB ? 0 : rd + 1;
+        const bf16x8* buf = (const bf16x8*)lds + rd * STAGE + grp * (FT + RT) * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+          const int f = i / RTW, t = i % RTW;
+          acc[f][t] = mfma16_f16(a[u][f], b[u][t], acc[f][t]);
+#pragma unroll
+          for (int o = i * NO / NM; o < (i + 1) * NO / NM; ++o) {
+            if (o < NF) fragment(o, u ^ 1, buf);
+            else load(o - NF);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        next_load();
+      }
     }
     if (n == 0) stamp(p, e.ph, 4);
-    // ---- end of a pair: the 4 wavefronts' partial tiles meet in LDS; every wavefront sums its share of the 1 KiB blocks in
-    // wavefront order and runs their epilogue.  Block idx of a part: BIG (f, t, q) = registers 4 q .. 4 q + 3 of accb[f][t]:
-    // features 32 f + 8 q + 4 (lane >> 5) .. + 3, row 32 t + (lane & 31); else (j, t): features 16 j + 4 (lane >> 4) .. + 3,
-    // row 16 t + (lane & 15)
+    if constexpr (G > 1) {                                   // the groups' partial tiles meet in LDS: group 0 adds them in order
+      f32x4* red = lds + NB * STAGE + kFusedPromptRows / 4;
+      if (grp > 0) {
 #pragma unroll
-    for (int rd = 0; rd < ROUNDS; ++rd) {
-      constexpr int TR = (BIG ? MT32 : MTG) / ROUNDS;          // row tiles of a part
-      if constexpr (BIG) {
-#pragma unroll
-        for (int f = 0; f < 2; ++f)
-#pragma unroll
-          for (int tt = 0; tt < TR; ++tt)
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-              const f32x16& v = accb[f][rd * TR + tt];
-              red[(wave * NT + (f * TR + tt) * 4 + qq) * 64 + lane] = (f32x4){v[4 * qq], v[4 * qq + 1], v[4 * qq + 2], v[4 * qq + 3]};
-            }
-      } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int tt = 0; tt < TR; ++tt) red[(wave * NT + j * TR + tt) * 64 + lane] = acc[j][tt];
+        for (int i = 0; i < NM; ++i) red[((wave - WG) * NM + i) * 64 + lane] = acc[i / RTW][i % RTW];
       }
       wg_barrier();
-      auto total = [&](int idx) {
-        f32x4 v = red[idx * 64 + lane];
+      if (grp == 0) {
 #pragma unroll
-        for (int w = 1; w < kWideWaves; ++w) v += red[(w * NT + idx) * 64 + lane];
-        return v;
-      };
-      // features (of the set of 64) and row (of the pass) of block idx
-      auto feature_of = [&](int idx) { return BIG ? (idx / (4 * TR)) * 32 + (idx & 3) * 8 + (lane >> 5) * 4 : (idx / TR) * 16 + (lane >> 4) * 4; };
-      auto row_of = [&](int idx) {
-        return rg * MTG * 16 + (BIG ? (rd * TR + (idx >> 2) % TR) * 32 + (lane & 31) : (idx % TR) * 16 + (lane & 15));
-      };
-      if constexpr (EPI == FE_SWIGLU) {
-        // features 0..31 of the set are gate, 32..63 the matching up features: blocks idx and idx + NT / 2
-        for (int idx = wave; idx < NT / 2; idx += kWideWaves) {
-          const f32x4 gv = total(idx), uv = total(idx + NT / 2);
-          const int m = row_of(idx);
-          if (m < p.M) {
-            const float rs = r_s[m];
+        for (int o = 1; o < G; ++o)
+#pragma unroll
+          for (int i = 0; i < NM; ++i) acc[i / RTW][i % RTW] += red[(((o - 1) * WG + wave) * NM + i) * 64 + lane];
+      }
+      if (n + 1 < n_my) wg_barrier();
+    }
+    // ---- epilogue from the accumulators: tile (f, t) holds features 4 (lane >> 4) .. + 3 of row lane & 15
+    int set, rg;
+    pair_of(n, set, rg);
+    const int f4 = (lane >> 4) * 4;
+#pragma unroll
+    for (int t = 0; t < RTW; ++t) {
+      const int m = (rg * RT + wm * RTW + t) * 16 + (lane & 15);
+      if (m < p.M && grp == 0) {
+        const float rs = EPI == FE_PART ? 1.0f : r_s[m];
+        if constexpr (EPI == FE_SWIGLU) {
+#pragma unroll
+          for (int i = 0; i < FTW / 2; ++i) {
+            const int f = FTW == 2 ? 0 : (i >> 1) * 4 + (i & 1), tile = set * FT + tile_of(f);   // gate; its up tile is two further in the unit
+            if (tile / 4 >= n_groups) continue;
             bf16_t hi[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const float gg = gv[i] * rs, uu = uv[i] * rs;
-              hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
+            for (int c = 0; c < 4; ++c) {
+              const float gg = acc[f][t][c] * rs, uu = acc[FTW == 2 ? 1 : f + 2][t][c] * rs;
+              hi[c] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
             }
             // input index of the down-projection
-            st_u64_uncounted(e.act_out + b_off<MTOT>(q * 32 + feature_of(idx), m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
+            *(uint64_t*)(e.act_out + b_off_of(p.row_tiles, (tile / 4) * 32 + (tile & 1) * 16 + f4, m)) = pack_bf16x4(hi[0], hi[1], hi[2], hi[3]);
+          }
+        } else {
+          float* out = e.out + ((int64_t)slice * p.M + m) * e.ld;
+#pragma unroll
+          for (int f = 0; f < FTW; ++f) {
+            const int tile = set * FT + tile_of(f);
+            if (tile < g.NT) *(gf32x4*)((gfloat*)out + tile * 16 + f4) = EPI == FE_PART ? acc[f][t] : acc[f][t] * rs;
           }
         }
-      } else {
-        float* out = e.out + (EPI == FE_PART ? (int64_t)slice * p.M * e.ld : 0);
-        for (int idx = wave; idx < NT; idx += kWideWaves) {
-          const f32x4 v = total(idx);
-          const int m = row_of(idx), n0 = q * 64 + feature_of(idx);
-          if ((n0 >> 4) < g.NT && m < p.M) st_f32x4_uncounted(out + (int64_t)m * e.ld + n0, EPI == FE_PART ? v : v * r_s[m]);
-        }
       }
-      wg_barrier();
+#pragma unroll
+      for (int f = 0; f < FTW; ++f) acc[f][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
-    zero_acc();
     if (n == 0) stamp(p, e.ph, 5);
   }
+  wait_loads<0>();
   stamp(p, e.ph, 2);
 }
 
@@ -1609,52 +1571,34 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
   if (CLOCKS) stamp(p, ph, EMBED ? 2 : 7, m);
 }
 
-// The linear layers with many outputs (rows x features): the LM head, gate/up + SwiGLU beyond 192 rows, and every layer of a prompt
-// pass (more than kFusedWideRows rows).  They are contractions: what bounds them is the matrix cores (32x32x16 on data that are not
-// constant: 1.4 PFLOP/s with one wavefront per SIMD) and the operands a compute unit pulls (about 100 GB/s), which must run side by
-// side.  A workgroup = 4 wavefronts x (NF x 32 features) x RT row tiles over the whole reduction dimension (PART: a slice of it, XCD
-// x on slice x % S, as in wide_gemm_kernel).  The weights of a wavefront's own features go straight into registers (a ring of
-// 8 k-tiles); the activations, which all four need, through LDS (stages of 4 k-tiles, double buffered, requested two stages
-// ahead); nothing has to be reduced across wavefronts.  Every LDS read, load and LDS write sits between two MFMAs
-// (sched_barrier): a burst of them blocks the one wavefront of a SIMD until the memory pipeline has taken it in, and left to itself
-// the scheduler sinks the loads to just before their use.
-// The MFMAs are 32x32x16 (a 16x16x32 has 28 clocks from issue to issue for a wavefront alone on its SIMD, 32x32x16 twice the work in
-// 34).  Both operands stay in their 16x16x32 tile order in memory and LDS: a 32x32x16 operand is the k-half h of two neighbouring
-// tiles, and lane l takes its 16 bytes from lane (l & 15) + 16 (l >> 5) + 32 h of tile (l >> 4) & 1, a fixed offset per lane.
-// NF = 2: 64 features per wavefront: two tile groups of the layout (ATW = 2: o, down), or gate tiles and up tiles, or four tiles of
-// the head, of one unit (ATW = 4).  NTW (one row group): the weights are read once and take the non-temporal path.
-// Against stages of 8 k-tiles with the memory operations in bursts (1B shape, median us of a launch, both kernels on one machine):
-// 384 rows gate/up 37.5 -> 34.5, head 253 -> 232; 288 rows 31.9 -> 32.0, 204 -> 198; 96 rows head 109 -> 107 to 110.  A round of
-// 384 rows with all that came beside it 13.38 -> 13.17 ms.  1024 prompt rows, gate/up: 66 us (three passes of 340 rows before: 3 x 35); tiles of
-// 128 features x 192 rows measured 74 for 768 rows, tiles of 256 x 192 spill.
-constexpr int kTileRows = kFusedPromptRowGroup;      // rows of a full row group
+// The LM head of up to 96 rows: a stream of weights, each read once.  A workgroup = 4 wavefronts x 64 features x 96 rows over the whole
+// reduction dimension.  The weights of a wavefront's own features go straight into registers (a ring of 8 k-tiles, non-temporal); the
+// activations, which all four need, through LDS (stages of 4 k-tiles, double buffered, requested two stages ahead); nothing has to be
+// reduced across wavefronts.  Every LDS read, load and LDS write sits between two MFMAs (sched_barrier): a burst of them blocks the one
+// wavefront of a SIMD until the memory pipeline has taken it in, and left to itself the scheduler sinks the loads to just before their
+// use.  The MFMAs are 32x32x16.  Both operands stay in their 16x16x32 tile order in memory and LDS: a 32x32x16 operand is the k-half h of
+// two neighbouring tiles, and lane l takes its 16 bytes from lane (l & 15) + 16 (l >> 5) + 32 h of tile (l >> 4) & 1, a fixed offset per
+// lane.  96 rows of the 1B shape 107 to 110 us, 525 MB of weights and 49 MB of logits (stages of 8 k-tiles with the memory operations in
+// bursts 109; wide_block_kernel 117).
+constexpr int kTileRows = 96;
 constexpr int kTileStage = 4, kTileRing = 8;         // k-tiles of an LDS stage, of the weight ring
-template <int ATW, int EPI, int NF, int RT, bool NTW>
 __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
-  constexpr int KC = kTileStage, R32 = RT / 2;
+  constexpr int KC = kTileStage, RT = kTileRows / 16, R32 = RT / 2, NF = 2, ATW = 4;   // (64 features of a wavefront: one unit)
   constexpr int STAGE = KC * RT * 64, BL = STAGE / kWideThreads, NM = NF * R32;
-  static_assert(ATW == 2 || NF == 2, "a wavefront owns whole units of 4 feature tiles");
   static_assert(kTileRing == 2 * KC && 2 * ((BL + KC - 1) / KC) <= NM && NF + 1 < NM, "a turn of the ring is two stages; memory operations between MFMAs");
   extern __shared__ f32x4 lds[];                     // [2][KC][RT][64] B-operand vectors
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int NKT = g.KS * kFusedWaves * g.KTW;        // k-tiles of the reduction dimension
-  const int S = EPI == FE_PART ? e.S : 1;
-  const int NST = NKT / (KC * S);                    // stages per pair (even: host check)
-  const int n_groups = g.n_units / g.KS;             // units of ATW feature tiles
-  constexpr int SG = 4 * NF * 2 / ATW;               // ... of a set
-  const int n_sets = (n_groups + SG - 1) / SG;
-  const int n_rg = (((p.M + 15) >> 4) + RT - 1) / RT;
-  const int x = (int)blockIdx.x & 7, wx = (int)blockIdx.x >> 3, per_xcd = (int)gridDim.x >> 3;
-  const int slice = x % S, y = x / S, ys = 8 / S;    // S is 1, 2, 4 or 8
-  const int nqy = y < n_sets ? (n_sets - y + ys - 1) / ys : 0;
-  const int ty = nqy * n_rg;
-  const int n_my = wx < ty ? (ty - wx + per_xcd - 1) / per_xcd : 0;
+  const int NST = NKT / KC;                          // stages per set (even: host check)
+  const int n_groups = g.n_units;                    // units of ATW feature tiles
+  const int n_sets = (n_groups + 3) / 4;
+  const int n_my = (int)blockIdx.x < n_sets ? (n_sets - 1 - (int)blockIdx.x) / (int)gridDim.x + 1 : 0;
   stamp(p, e.ph, 0);
   if (n_my == 0) return;
 
   const int lpos = (lane & 15) + ((lane >> 5) << 4), ltile = (lane >> 4) & 1;
   const int lsrc = ltile * 64 + lpos;                // operand vector of this lane in two neighbouring tiles, k-half 0
-  const int64_t fstep = ATW == 4 ? 128 : (int64_t)NKT * 128;   // vectors from a wavefront's first 32 features to its second
+  constexpr int fstep = 128;                         // vectors from a wavefront's first 32 features to its second
   f32x16 acc[NF][R32];
   auto zero_acc = [&]() {
 #pragma unroll
@@ -1665,14 +1609,8 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
         for (int i = 0; i < 16; ++i) acc[f][t][i] = 0.f;
   };
   zero_acc();
-  auto pair_of = [&](int n, int& set, int& rg) {
-    const int t = wx + (n < n_my ? n : n_my - 1) * per_xcd;
-    const int qh = t / n_rg;
-    set = qh * ys + y;
-    rg = t - qh * n_rg;
-  };
-  // this wavefront's first unit of set `set` (past the last: the last units again, computed and never stored)
-  auto group_of = [&](int set) { return min((set * 4 + wave) * (NF * 2 / ATW), n_groups - NF * 2 / ATW); };
+  // this wavefront's unit of the workgroup's n-th set (past the last: the last unit again, computed and never stored)
+  auto unit_of = [&](int n) { return min(((int)blockIdx.x + min(n, n_my - 1) * (int)gridDim.x) * 4 + wave, n_groups - 1); };
   int b_rel[BL];
 #pragma unroll
   for (int i = 0; i < BL; ++i) {
@@ -1680,19 +1618,11 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
     const int kt = v / (RT * 64);
     b_rel[i] = (kt * p.row_tiles * 64 + v - kt * (RT * 64)) * 8;
   }
-  struct Cursor { int n, s; const bf16_t* q; };      // pair ordinal, stage; operand address of that stage
-  auto place_a = [&](Cursor& c) {
-    int set, rg;
-    pair_of(c.n, set, rg);
-    c.q = g.w + ((int64_t)group_of(set) * NKT + (slice * NST + c.s) * KC) * (ATW * 512);
-  };
-  auto place_b = [&](Cursor& c) {
-    int set, rg;
-    pair_of(c.n, set, rg);
-    c.q = bsrc + ((int64_t)((slice * NST + c.s) * KC) * p.row_tiles + rg * RT) * 512;
-  };
+  struct Cursor { int n, s; const bf16_t* q; };      // set ordinal, stage; operand address of that stage
+  auto place_a = [&](Cursor& c) { c.q = g.w + ((int64_t)unit_of(c.n) * NKT + c.s * KC) * (ATW * 512); };
+  auto place_b = [&](Cursor& c) { c.q = bsrc + (int64_t)(c.s * KC) * p.row_tiles * 512; };
   auto step = [&](Cursor& c) { if (++c.s == NST) { c.s = 0; ++c.n; } };
-  auto weight = [](const gbf16x8* q) { return NTW ? __builtin_nontemporal_load(q) : *q; };
+  auto weight = [](const gbf16x8* q) { return __builtin_nontemporal_load(q); };
   bf16x8 ring[kTileRing][2 * NF], breg[2][BL], bt[2][R32];
   Cursor ca{0, 0, nullptr}, cb{0, 0, nullptr};
   place_b(cb);
@@ -1725,12 +1655,10 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
   stamp(p, e.ph, 3);
 
   for (int n = 0; n < n_my; ++n) {
-    int set, rg;
-    pair_of(n, set, rg);
     float rs[R32];                                   // the rows' 1/rms
 #pragma unroll
     for (int t = 0; t < R32; ++t)
-      rs[t] = EPI == FE_PART ? 1.0f : ((const gfloat*)p.ssq)[min((rg * RT + 2 * t) * 16 + (lane & 31), p.M - 1)];
+      rs[t] = ((const gfloat*)p.ssq)[min(t * 32 + (lane & 31), p.M - 1)];
     for (int st = 0; st < NST; st += 2) {
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
@@ -1774,32 +1702,20 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
     if (n == 0) stamp(p, e.ph, 4);
     // ---- epilogue from the accumulators.  Registers 4 q .. 4 q + 3 of a 32x32 tile: features 8 q + 4 (lane >> 5) .. + 3, row lane & 31
     const int f4 = (lane >> 5) * 4;
-    const int first = (set * 4 + wave) * (NF * 2 / ATW);             // this wavefront's first unit
-    if (first < n_groups) {
+    const int unit = ((int)blockIdx.x + n * (int)gridDim.x) * 4 + wave;
+    if (unit < n_groups) {
 #pragma unroll
       for (int t = 0; t < R32; ++t) {
-        const int m = (rg * RT + 2 * t) * 16 + (lane & 31);
+        const int m = t * 32 + (lane & 31);
         if (m < p.M) {
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if constexpr (EPI == FE_SWIGLU) {
-              bf16_t hi[4];
+          for (int q = 0; q < 4; ++q)
 #pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                const float gg = acc[0][t][4 * q + i] * rs[t], uu = acc[1][t][4 * q + i] * rs[t];
-                hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
-              }
-              st_u64_uncounted(e.act_out + b_off_of(p.row_tiles, first * 32 + 8 * q + f4, m), pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
-            } else {
-              float* out = e.out + (EPI == FE_PART ? (int64_t)slice * p.M * e.ld : 0) + (int64_t)m * e.ld;
-#pragma unroll
-              for (int f = 0; f < NF; ++f) {
-                const int n0 = first * (ATW * 16) + f * 32 + 8 * q + f4;
-                const f32x4 v = (f32x4){acc[f][t][4 * q], acc[f][t][4 * q + 1], acc[f][t][4 * q + 2], acc[f][t][4 * q + 3]};
-                if ((n0 >> 4) < g.NT) st_f32x4_uncounted(out + n0, EPI == FE_PART ? v : v * rs[t]);
-              }
+            for (int f = 0; f < NF; ++f) {
+              const int n0 = unit * (ATW * 16) + f * 32 + 8 * q + f4;
+              const f32x4 v = (f32x4){acc[f][t][4 * q], acc[f][t][4 * q + 1], acc[f][t][4 * q + 2], acc[f][t][4 * q + 3]};
+              if ((n0 >> 4) < g.NT) st_f32x4_uncounted(e.out + (int64_t)m * e.ld + n0, v * rs[t]);
             }
-          }
         }
       }
     }
@@ -2661,90 +2577,45 @@ int check_residency_pl(int nwg, int cus, int kt) {
 
 int wide_k_tiles(const FusedGemm& g) { return g.KS * kFusedWaves * g.KTW; }
 
-template <int ATW, int EPI, int D, int MTG>
-int launch_wide_gemm_dm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
-  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_gemm_kernel<ATW, EPI, D, MTG>,
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFusedLdsBytes);
-  SSD_HIP(configured);
-  wide_gemm_kernel<ATW, EPI, D, MTG><<<p.nwg, kWideThreads, kFusedLdsBytes, s>>>(p, g, bsrc, e);
-  SSD_HIP(hipGetLastError());
-  return SSD_OK;
-}
-
-template <int ATW, int EPI, int MTG>
-int launch_wide_gemm(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
-  // a wavefront's k-tiles per pair must be whole turns of the ring
-  if (MTG <= kWideGroup && wide_k_tiles(g) / (kWideWaves * e.S) % kWideRing == 0)
-    return launch_wide_gemm_dm<ATW, EPI, MTG <= kWideGroup ? kWideRing : kWideRing / 2, MTG>(p, g, bsrc, e, s);
-  return launch_wide_gemm_dm<ATW, EPI, kWideRing / 2, MTG>(p, g, bsrc, e, s);
-}
-
-template <int ATW, int EPI, int NF, int RT = kTileRows / 16, bool NTW = false>
-int launch_wide_tile(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
-  constexpr int kLds = 2 * kTileStage * RT * 1024;
-  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_tile_kernel<ATW, EPI, NF, RT, NTW>,
+template <int ATW, int EPI, int FT, int RT, int WN, int G, int NB, int TH>
+int launch_wide_block_of(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
+  constexpr int kLds = (NB * G * (FT + RT) + (G - 1) * FT * RT) * 1024 + kFusedPromptRows * 4;
+  static_assert(kLds <= 160 * 1024, "LDS of a block");
+  static const hipError_t configured = hipFuncSetAttribute((const void*)wide_block_kernel<ATW, EPI, FT, RT, WN, G, NB, TH>,
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   SSD_HIP(configured);
-  SSD_CHECK_ARG(wide_k_tiles(g) % (kTileRing * e.S) == 0 && (g.n_units / g.KS) * ATW % (2 * NF) == 0, "wide pass: layer does not cut into tiles");
-  wide_tile_kernel<ATW, EPI, NF, RT, NTW><<<p.nwg, kWideThreads, kLds, s>>>(p, g, bsrc, e);
+  SSD_CHECK_ARG(wide_k_tiles(g) % (2 * e.S * G) == 0 && (ATW == 2 || ATW == 4) && p.M <= kFusedPromptRows && p.row_tiles * 16 >= p.M,
+                "wide pass: layer does not cut into blocks");
+  wide_block_kernel<ATW, EPI, FT, RT, WN, G, NB, TH><<<p.nwg, TH, kLds, s>>>(p, g, bsrc, e);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }
 
-// qkv: row groups as small as still give every pair a workgroup of its own (with few rows the full-size groups leave most
-// of the grid without a pair while the busy workgroups pull as much as ever).
-int launch_wide_qkv(const FusedParams& p, const FusedGemm& g, const WideEpi& e, hipStream_t s) {
-  if (p.M > kFusedWideRows) return launch_wide_tile<2, FE_QKV, 1>(p, g, p.xn, e, s);
-  const int nq = (g.n_units / g.KS) >> 1, tiles = (p.M + 15) >> 4;
-  auto fits = [&](int mtg) { return nq * ((tiles + mtg - 1) / mtg) <= p.nwg; };
-  if (fits(1)) return launch_wide_gemm<2, FE_QKV, 1>(p, g, p.xn, e, s);
-  if (fits(2)) return launch_wide_gemm<2, FE_QKV, 2>(p, g, p.xn, e, s);
-  if (fits(kWideGroup / 2)) return launch_wide_gemm<2, FE_QKV, kWideGroup / 2>(p, g, p.xn, e, s);
-  return launch_wide_gemm<2, FE_QKV, kWideGroup>(p, g, p.xn, e, s);
-}
-
-// o and down: the largest row groups (from 4 tiles on; with fewer, one group of them all), and as many k-slices as give every
-// pair a workgroup of its own; e.S = how many.  Groups of 6, 3 and 2 tiles, us per pass of 4 layers of the 1B shape: 64 rows
-// 262, 255, 255; 96 rows 290, 275, 287; 128 rows 294, 297, 286; 160 rows 301, 302, 326; 192 rows 315, 316, 338 (runs of one
-// side differ by up to 5 % below 100 rows).
-int launch_wide_part(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
-  if (p.M > kFusedWideRows) {
-    const int pairs = (g.n_units / g.KS + 7) / 8 * ((p.M + kTileRows - 1) / kTileRows);
-    e.S = 1;
-    for (int S = kFusedWideSlices; S > 1; S >>= 1)
-      if (pairs * S <= p.nwg && (int64_t)S * p.M <= p.fix_stride && wide_k_tiles(g) % (kTileRing * S) == 0) { e.S = S; break; }
-    return launch_wide_tile<2, FE_PART, 2>(p, g, bsrc, e, s);
+// One linear layer of a wide pass in the blocks chosen for it; e.S = the k-slices (PART).  Four wavefronts where their share of a block
+// fits their registers, eight for more (and for 8 x 8 and 8 x 12: 25.2 against 26.1 and 22.5 against 22.6 us); buffers: five or six are as
+// good as more (96 rows of gate/up 18.0 us with six, 18.3 with eight, 20 with sixteen).  Two groups of wavefronts where a block is small and
+// its steps many: qkv of 96 rows 10.3 us in blocks of 4 x 2, 11.3 with one; gate/up of 96 rows (4 x 6) 19.6, 18.4 with one.
+template <int ATW, int EPI>
+int launch_wide_block(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
+  constexpr bool kSlices = EPI == FE_PART;
+  const WideChoice c = choose_wide_block(g.n_units / g.KS * ATW, wide_k_tiles(g), p.M, p.nwg, kNumWideBlocks - (EPI == FE_LOGITS ? 0 : 1),
+                                         kFusedWideSlices, kSlices ? p.fix_stride : 0, p.d);
+  e.S = c.S;
+  switch (c.block) {
+    case 0: return launch_wide_block_of<ATW, EPI, 4, 2, 2, kSlices ? 1 : 2, 6, 256>(p, g, bsrc, e, s);
+    case 1: return launch_wide_block_of<ATW, EPI, 4, 4, 2, 1, 6, 256>(p, g, bsrc, e, s);
+    case 2: return launch_wide_block_of<ATW, EPI, 4, 6, 2, 1, 6, 256>(p, g, bsrc, e, s);
+    case 3: return launch_wide_block_of<ATW, EPI, 4, 8, 2, 1, 6, 256>(p, g, bsrc, e, s);
+    case 4: return launch_wide_block_of<ATW, EPI, 8, 6, 2, 1, 6, 256>(p, g, bsrc, e, s);
+    case 5: return launch_wide_block_of<ATW, EPI, 8, 8, 4, 1, 5, 512>(p, g, bsrc, e, s);
+    case 6: return launch_wide_block_of<ATW, EPI, 8, 12, 4, 1, 5, 512>(p, g, bsrc, e, s);
+    case 7: return launch_wide_block_of<ATW, EPI, 16, 8, 2, 1, 5, 512>(p, g, bsrc, e, s);
+    case 8: return launch_wide_block_of<ATW, EPI, 16, 12, 2, 1, 5, 256>(p, g, bsrc, e, s);
+    case 9: return launch_wide_block_of<ATW, EPI, 16, 16, 2, 1, 4, 512>(p, g, bsrc, e, s);
+    default:
+      if constexpr (EPI == FE_LOGITS) return launch_wide_block_of<ATW, EPI, 16, 6, 4, 1, 5, 256>(p, g, bsrc, e, s);
+      return SSD_EINVAL;
   }
-  const int nq = (g.n_units / g.KS) >> 1, tiles = (p.M + 15) >> 4;
-  const int mtg = tiles >= 4 ? kWideGroup : tiles;
-  const int n_rg = (tiles + mtg - 1) / mtg;
-  e.S = 1;
-  for (int S = kFusedWideSlices; S > 1; S >>= 1)
-    if (nq * n_rg * S <= p.nwg && S * p.M <= kFusedWideSlices * kFusedWideRowGroup && wide_k_tiles(g) % (kWideWaves * S * (kWideRing / 2)) == 0) { e.S = S; break; }
-  switch (mtg) {
-    case 1: return launch_wide_gemm<2, FE_PART, 1>(p, g, bsrc, e, s);
-    case 2: return launch_wide_gemm<2, FE_PART, 2>(p, g, bsrc, e, s);
-    case 3: return launch_wide_gemm<2, FE_PART, 3>(p, g, bsrc, e, s);
-    default: return launch_wide_gemm<2, FE_PART, kWideGroup>(p, g, bsrc, e, s);
-  }
-}
-
-// gate/up + SwiGLU.  Up to 12 row tiles (192 rows) in one row group: a workgroup per unit of 4 feature tiles, the reduction
-// dimension over its wavefronts, every weight read once, instead of 16 feature tiles per workgroup on a quarter (up to
-// 96 rows) or half of the grid (170 rows: 27 us against 30; 32 rows: 18 against 20.9 in groups of 6;
-// whole passes of 4 layers of the 1B shape, against 96 rows per group and 16 feature tiles per workgroup: 112 rows 292 us and 304, 160 rows 301
-// and 311, 192 rows 315 and 323).  With more rows 16 feature tiles per workgroup fill the
-// grid and pull less.
-int launch_wide_gate_up(const FusedParams& p, const FusedGemm& g, const WideEpi& e, hipStream_t s) {
-  if (p.M > kFusedWideRows) return launch_wide_tile<4, FE_SWIGLU, 2>(p, g, p.xn, e, s);
-  const int tiles = (p.M + 15) >> 4;
-  if (g.n_units <= p.nwg && tiles <= 2 * kWideGroup) {
-    if (tiles <= 2) return launch_wide_gemm<4, FE_SWIGLU, 2>(p, g, p.xn, e, s);
-    if (tiles <= kWideGroup) return launch_wide_gemm<4, FE_SWIGLU, kWideGroup>(p, g, p.xn, e, s);
-    return launch_wide_gemm<4, FE_SWIGLU, 2 * kWideGroup>(p, g, p.xn, e, s);
-  }
-  if (tiles <= kWideGroup) return launch_wide_tile<4, FE_SWIGLU, 2, kWideGroup, true>(p, g, p.xn, e, s);
-  return launch_wide_tile<4, FE_SWIGLU, 2, kWideGroup>(p, g, p.xn, e, s);
 }
 
 // The attention units of a pass, p.NQ query tiles each (the host chooses them together with the key splits)
@@ -2765,14 +2636,15 @@ int launch_wide_attn(const FusedParams& p, const FusedLayer& L, int ph, hipStrea
   return launch_wide_attn_nq<PL, PG, 3>(p, L, ph, s);
 }
 
-// LM head.  Up to 96 rows one row group.  Beyond: row groups of 128 where they pad no more rows than groups of 96 do (rounds of the 1B shape, ms: 384 rows
-// 13.23 with 128, 13.36 with 96; 288 rows 12.16, 12.11; 180 rows 9.55, 9.52).
-int launch_wide_logits(const FusedParams& p, const WideEpi& e, hipStream_t s) {
-  constexpr int kSmall = kWideGroup * 16;
-  if (p.M <= kSmall) return launch_wide_tile<4, FE_LOGITS, 2, kWideGroup, true>(p, p.lm, p.xn, e, s);
-  if ((p.M + kTileRows - 1) / kTileRows * kTileRows <= (p.M + kSmall - 1) / kSmall * kSmall)
-    return launch_wide_tile<4, FE_LOGITS, 2>(p, p.lm, p.xn, e, s);
-  return launch_wide_tile<4, FE_LOGITS, 2, kWideGroup>(p, p.lm, p.xn, e, s);
+// LM head.  Up to 96 rows it is a stream of weights, each read once, which goes faster straight into registers and past the caches
+// (96 rows 109 us, 117 in blocks of 256 features x 96 rows).
+int launch_wide_logits(const FusedParams& p, WideEpi& e, hipStream_t s) {
+  if (p.M > kTileRows) return launch_wide_block<4, FE_LOGITS>(p, p.lm, p.xn, e, s);
+  SSD_CHECK_ARG(p.lm.KS == 1 && wide_k_tiles(p.lm) % kTileRing == 0, "wide pass: the LM head does not cut into tiles");
+  constexpr int kLds = 2 * kTileStage * kTileRows / 16 * 1024;
+  wide_tile_kernel<<<p.nwg, kWideThreads, kLds, s>>>(p, p.lm, p.xn, e);
+  SSD_HIP(hipGetLastError());
+  return SSD_OK;
 }
 
 template <bool EMBED>
@@ -2823,16 +2695,16 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
     const FusedLayer& L = layers_host[l];
     if (sub == 0) {
       e.out = p.qkv; e.ld = p.qkvd;
-      SSD_TRY(launch_wide_qkv(p, L.qkv, e, s));
+      SSD_TRY((launch_wide_block<2, FE_QKV>(p, L.qkv, p.xn, e, s)));
     } else if (sub == 3 || sub == 5) {
       e.out = p.fix_buf; e.ld = p.d;
-      SSD_TRY(launch_wide_part(p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s));
+      SSD_TRY((launch_wide_block<2, FE_PART>(p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s)));
       const bool fin = sub == 5 && l + 1 == p.L;
       const bf16_t* gain = sub == 3 ? L.mlp_norm : (fin ? p.final_norm : layers_host[l + 1].attn_norm);
       SSD_TRY(launch_wide_resid(p, false, p.fix_buf, e.S, gain, fin ? p.hidden : nullptr, ph, s));
     } else if (sub == 4) {
       e.act_out = p.act;
-      SSD_TRY(launch_wide_gate_up(p, L.gu, e, s));
+      SSD_TRY((launch_wide_block<4, FE_SWIGLU>(p, L.gu, p.xn, e, s)));
     } else if (sub == 1) {
       if (p.appended) {
         wide_append_kernel<PG><<<(p.M * p.Hkv * 8 + 255) / 256, 256, 0, s>>>(p, L.trunk_k, L.trunk_vt);
@@ -2917,7 +2789,7 @@ int launch_fused_wide(const FusedParams& p, const FusedLayer* layers_host, int f
 // Shapes the wide pass takes: every layer's stream-order layout must cut into sets of 4 feature tiles over whole
 // k-ranges of an even number of k-tiles per wavefront.
 bool fused_wide_gemm_ok(const FusedGemm& g, int at) {
-  if ((2 * g.KS * g.KTW) % (kWideRing / 2)) return false;     // a wavefront's k-tiles per pair, in whole turns of the (half) ring
+  if (g.KS * g.KTW % 2) return false;                        // k-tiles in whole turns of 8 slices of two steps
   if (at == 4) return g.KS == 1;
   return at == 2 && (g.n_units / g.KS) % 2 == 0;
 }

@@ -811,11 +811,10 @@ int fused_setup(ssd_ctx* c) {
     // query rows of a pass: whole 16-row tiles per sequence
     c->part_wide.ns_max = std::min((c->max_trunk + 2047) / 2048 + 1, kFusedMaxSplits);
     c->part_wide.entries = (int64_t)p.Hkv * c->part_wide.ns_max * ((int64_t)MW * p.G + 16 * std::min(c->B, (int)MW));
-    // partial sums of o and down: eight slices of a row group of 96, two of 384 rows (which is what gives every pair of 64
-    // features x 96 rows a workgroup at the 1B shape).  They lie where the qkv projections were: written after the
+    // partial sums of o and down: eight slices of a round's rows, four of a prompt pass's (what eight would write and read again costs
+    // more than the larger blocks of a slice save).  They lie where the qkv projections were: written after the
     // attention has read those, read before the next layer's are written
-    // (prompt passes: four slices of 1024 rows, eight of 512)
-    w.fix_stride = c->prompt_rows > kFusedWideRows ? 4 * kFusedPromptRows : kFusedWideSlices * kFusedWideRowGroup;
+    w.fix_stride = std::max(kFusedWideSlices * kFusedWideRows, c->prompt_rows > kFusedWideRows ? 4 * kFusedPromptRows : 0);
     // one allocation, carved up
     char* base = nullptr;
     size_t used = 0;

@@ -1,0 +1,46 @@
+// Which block of a linear layer a workgroup of a wide pass computes (plain C++: no HIP types).
+#pragma once
+
+#include <cstdint>
+
+namespace ssd {
+
+// The blocks that wide_block_kernel is compiled for, feature tiles x row tiles, and what a workgroup is expected to take (us): a step of
+// 32 inputs 0.18 and 0.0027 more per tile product (measured at full grids: 4 x 6 tiles 0.20, 8 x 6 0.28 to 0.33, 8 x 8 0.33, 8 x 12 0.42,
+// 16 x 12 0.74, 16 x 16 0.85 to 0.95), 1.5 per block, and each k-slice 0.1 and what writing and reading its partial sums costs at 6 TB/s,
+// beyond four slices 0.4 more (the residual kernel loads four at a time; with 1 instead, which takes down of 384 rows of the 1B shape from
+// eight slices in blocks of 8 x 12 to four in blocks of 8 x 6, rounds of 384 rows take 3 % longer).
+// Taken is the cheapest; with one slice and few enough rows that is the smallest block that leaves no workgroup a second one.  Best
+// and second best of a sweep (us of a launch; 2048 inputs, 16384 features): 64 rows 4 x 4 15.6, 4 x 6 17.9; 128 rows 4 x 8 19.5, 8 x 6 22.9;
+// 192 rows 8 x 6 22.9, 8 x 8 25.2; 256 rows 8 x 8 25.2, 8 x 12 33.2; 384 rows 8 x 12 32.9, 16 x 8 35.0; 512 rows 16 x 8 40.0, 8 x 8 44.0;
+// 768 rows 16 x 12 56.3, 16 x 16 58.6; 1020 rows 16 x 16 66.7, 16 x 8 82.3.
+struct WideBlock { int ft, rt; };
+constexpr WideBlock kWideBlocks[] = {{4, 2}, {4, 4}, {4, 6}, {4, 8}, {8, 6}, {8, 8}, {8, 12}, {16, 8}, {16, 12}, {16, 16}, {16, 6}};
+constexpr int kNumWideBlocks = sizeof(kWideBlocks) / sizeof(kWideBlocks[0]);   // the last one for the LM head only (288 rows: three groups)
+
+struct WideChoice { int block, S; };
+
+// tiles: 16-feature tiles of the layer; k_tiles: of its reduction dimension; blocks: how many of the list it may take; room: rows of
+// partial sums there is memory for (0: no k-slices); out_width: features of such a row.
+inline WideChoice choose_wide_block(int tiles, int k_tiles, int rows, int workgroups, int blocks, int max_slices, int64_t room, int out_width) {
+  const int per_xcd = workgroups / 8, row_tiles = (rows + 15) / 16;
+  WideChoice best{0, 1};
+  float best_us = 0.0f;
+  for (int S = 1; S <= (room > 0 ? max_slices : 1); S *= 2) {
+    if (k_tiles % (2 * S) != 0 || (S > 1 && (int64_t)S * rows > room)) break;   // whole pairs of steps per slice
+    for (int i = 0; i < blocks; ++i) {
+      const int area = kWideBlocks[i].ft * kWideBlocks[i].rt, ys = 8 / S;       // dies that share a slice
+      const int sets = (tiles + kWideBlocks[i].ft - 1) / kWideBlocks[i].ft, groups = (row_tiles + kWideBlocks[i].rt - 1) / kWideBlocks[i].rt;
+      const int turns = ((sets + ys - 1) / ys * groups + per_xcd - 1) / per_xcd;
+      float us = (float)turns * ((float)(k_tiles / S) * (0.18f + 0.0027f * (float)area) + 1.5f);
+      if (room > 0) us += (float)S * (0.1f + (float)rows * (float)out_width * 8.0f / 6e6f) + (S > 4 ? 0.4f : 0.0f);
+      if ((S == 1 && i == 0) || us < best_us) {
+        best_us = us;
+        best = WideChoice{i, S};
+      }
+    }
+  }
+  return best;
+}
+
+}  // namespace ssd

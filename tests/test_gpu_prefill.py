@@ -477,3 +477,69 @@ def test_captured_extend_of_few_rows_takes_the_wide_pass(B):
         for c in (ctx, wide):
             B.ssd_ctx_destroy(c)
         B.ssd_model_destroy(model)
+
+
+# (width, d_ffn, prompt rows): gate/up takes another block at each, with whole and with partly filled row groups, and o and down
+# one, two, four and eight slices
+BLOCK_PROMPTS = [(512, 8192, 20), (512, 8192, 32), (512, 8192, 64), (512, 8192, 65), (512, 8192, 96), (512, 8192, 128), (512, 8192, 190),
+                 (512, 8192, 250), (512, 8192, 256), (512, 8192, 384), (512, 8192, 500), (512, 8192, 513), (512, 8192, 768), (512, 8192, 1000),
+                 (2048, 2048, 300)]
+# (vocabulary, sequences, F) with K = 2: the LM head's blocks, the last of them with features behind the vocabulary
+BLOCK_ROUNDS = [(66016, 16, 3), (66016, 16, 4), (66016, 16, 6), (66016, 16, 8), (20016, 16, 8), (4112, 11, 3), (4112, 16, 8)]
+
+
+@pytest.mark.parametrize("width,ffn,rows", BLOCK_PROMPTS)
+def test_blocks_of_prompt_passes(B, width, ffn, rows):
+    """Every block that the linear layers of wide passes are cut into, against the narrow passes' own kernels."""
+    print(f"[case] width {width}, d_ffn {ffn}, {rows} rows", flush=True)
+    max_trunk, seed, lens = rows + 2 * K + 8, 5 + rows, [rows]
+    shape = I.ModelShape(n_layers=2, d_model=width, n_q_heads=width // 64, n_kv_heads=2, head_dim=64, d_ffn=ffn, vocab=4112, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, 17))
+    prompt = dev_i32(I.make_prompt(shape, 1, rows, seed))
+    ctxs = [B.ssd_ctx_create(model, 1, K, F, max_trunk, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
+    try:
+        got = []
+        for ctx in ctxs:
+            B.ssd_ctx_prefill(ctx, prompt, lens)
+            got.append(_trunk(B, ctx, lens, max_trunk, shape))
+        # each side is within TOL_BF16_OWN_PREFILL of the exact keys and values
+        for part in (0, 1):
+            for l in range(shape.n_layers):
+                assert row_rel_err(got[0][part][l][0], got[1][part][l][0]) < 2 * TOL_BF16_OWN_PREFILL, (part, l)
+        assert not np.array_equal(got[0][0][1][0], got[1][0][1][0])          # (the prompt did go through another pass)
+    finally:
+        for ctx in ctxs:
+            B.ssd_ctx_destroy(ctx)
+        B.ssd_model_destroy(model)
+
+
+@pytest.mark.parametrize("vocab,nb,F_", BLOCK_ROUNDS)
+def test_blocks_of_the_head(B, vocab, nb, F_):
+    print(f"[case] vocabulary {vocab}, {nb} sequences, F {F_}", flush=True)
+    K_, P = 2, 40
+    shape = I.ModelShape(n_layers=1, d_model=512, n_q_heads=8, n_kv_heads=2, head_dim=64, d_ffn=1024, vocab=vocab, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    model = B.ssd_model_create_random(shape, 3)
+    R = (K_ + 1) * F_
+    pending = dev_i32(I.make_pending(shape, nb, K_, 3))
+    rng = np.random.default_rng(vocab + nb)
+    keys = dev_i32(np.stack([rng.permutation(vocab)[:R] for _ in range(nb)]))
+    tokens, temps = dev_i32(rng.integers(0, vocab, (nb, R, K_))), dev_f32(np.zeros(nb))
+    out = []
+    try:
+        for flags in (0, B.SSD_CTX_NARROW_PASSES):
+            ctx = B.ssd_ctx_create(model, nb, K_, F_, P + 2 * K_ + 8, flags)
+            try:
+                B.ssd_ctx_fill_synthetic_kv(ctx, [P] * nb, 4)
+                B.ssd_ctx_set_forced(ctx, keys, tokens)
+                B.ssd_prespeculate(ctx, pending, temps, 1)
+                out.append(B.read_cache(ctx)["logits"].reshape(-1, vocab).float())
+                B.ssd_ctx_refresh_bounds(ctx)
+            finally:
+                B.ssd_ctx_destroy(ctx)
+        err = ((out[0] - out[1]).abs().amax(dim=1) / out[1].abs().amax(dim=1)).max().item()
+        print(f"[head] {err:.2e}", flush=True)
+        assert err < 2 * TOL_WIDE_BF16                         # each side is within TOL_WIDE_BF16 of the exact logits
+    finally:
+        B.ssd_model_destroy(model)
