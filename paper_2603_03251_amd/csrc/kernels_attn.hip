@@ -2,6 +2,7 @@
 // up to its fork point and only its own path).  No mask is materialised: a row is described by the number of
 // trunk positions it sees and the number of private suffix positions it sees.
 #include "common.h"
+#include "lanes.h"
 
 namespace ssd {
 
@@ -91,16 +92,16 @@ __global__ __launch_bounds__(256) void attention_rowwise_kernel(const float* __r
     }
     // merge the 64 lanes
     float m_all = m_run;
-    for (int o = 32; o > 0; o >>= 1) m_all = fmaxf(m_all, __shfl_xor(m_all, o));
+    m_all = lanes_max(m_all);
     float w = m_run == -INFINITY ? 0.f : expf(m_run - m_all);
     float l_all = l_run * w;
-    for (int o = 32; o > 0; o >>= 1) l_all += __shfl_xor(l_all, o);
+    l_all = lanes_sum(l_all);
     float inv = 1.0f / l_all;
     const int64_t obase = ((int64_t)m * n_q_heads + hq) * D;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
       float v = acc[d] * w;
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+      v = lanes_sum(v);
       if (lane == (d & 63)) Act<T>::store(out, out_plane, obase + d, v * inv);
     }
     __builtin_amdgcn_wave_barrier();
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     float v = have ? sc[g] : -INFINITY;
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    v = lanes_max(v);
     if (lane == 0) mx_s[g][wave] = v;
   }
   __syncthreads();
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
     const float pe = have ? expf(sc[g] - m_use) : 0.f;
     p_s[g][tid] = pe;
     float v = pe;
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    v = lanes_sum(v);
     if (lane == 0) sum_s[g][wave] = v;
   }
   __syncthreads();
@@ -242,8 +243,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
       float v = acc[g][e];
-#pragma unroll
-      for (int o = LPR; o < 64; o <<= 1) v += __shfl_xor(v, o);
+      if constexpr (LPR < 64) v = lanes_sum<32, LPR>(v);
       if (lane < LPR) red_s[wave][g][d0 + e] = v;
     }
   __syncthreads();
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(D) void attention_merge_kernel(const float* __restr
   const float* pp = partial + pair * n_splits * (D + 2);
   const float ms = lane < n_splits ? pp[lane * (D + 2)] : -INFINITY, ls = lane < n_splits ? pp[lane * (D + 2) + 1] : 0.f;
   float m_max = ms;
-  for (int o = 32; o > 0; o >>= 1) m_max = fmaxf(m_max, __shfl_xor(m_max, o));
+  m_max = lanes_max(m_max);
   const float w = ms == -INFINITY ? 0.f : expf(ms - m_max);
   float l = 0.f, o = 0.f;
   for (int s0 = 0; s0 < n_splits; s0 += 16) {
@@ -440,8 +440,7 @@ __global__ __launch_bounds__(256) void attention_extend_kernel(const float* __re
       sv[e] = key < min(vis, j_end) ? (e < 4 ? S[0][e & 3] : S[1][e & 3]) : -INFINITY;
       mx = fmaxf(mx, sv[e]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    mx = lanes_max<32, 16>(mx);
     const float m_new = fmaxf(m_run, mx), m_use = m_new == -INFINITY ? 0.f : m_new;
     const float corr = expf(m_run - m_use);
     m_run = m_new;
@@ -483,8 +482,7 @@ __global__ __launch_bounds__(256) void attention_extend_kernel(const float* __re
   // ---- the wavefronts' partial softmaxes meet in LDS, where V^T was
   f32x4* mrg = (f32x4*)vt_all;                                           // [wave][DT][64]
   static_assert((size_t)DT * 64 * 16 <= (size_t)D * kExtVt * 2, "a wavefront's tile fits where its V^T was");
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+  l_run = lanes_sum<32, 16>(l_run);
   __syncthreads();
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) mrg[(wave * DT + dt) * 64 + lane] = acc[dt];

@@ -34,6 +34,7 @@
 #include <vector>
 
 #include "fused.h"
+#include "lanes.h"
 #include "wide_blocks.h"
 #include "wide_rows.h"
 
@@ -273,9 +274,7 @@ __device__ __forceinline__ void compute_row_scales(const FusedParams& p, const f
 #pragma unroll
     for (int i = 0; i < 16; ++i) s += j0 + 8 * i < n_tiles ? v[i] : 0.f;
   }
-  s += __shfl_xor(s, 1);
-  s += __shfl_xor(s, 2);
-  s += __shfl_xor(s, 4);
+  s = lanes_sum<4>(s);
   if (m < p.M && part == 0) r_s[m] = 1.0f / sqrtf(s / (float)p.d + p.eps);
   wg_barrier();
 }
@@ -295,9 +294,7 @@ __device__ __forceinline__ void row_scales_finish(const FusedParams& p, const fl
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < N; ++i) s += v[i];
-  s += __shfl_xor(s, 1);
-  s += __shfl_xor(s, 2);
-  s += __shfl_xor(s, 4);
+  s = lanes_sum<4>(s);
   if (m < p.M && (tid & 7) == 0) r_s[m] = 1.0f / sqrtf(s / (float)p.d + p.eps);
 }
 
@@ -325,8 +322,7 @@ __device__ __forceinline__ void resid_store(const FusedParams& p, f32x4 hn, int 
     st_u64(xn_out + off, pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
     if (NPX == 2) st_u64(xn_out + (int64_t)MP * p.d + off, pack_bf16x4(lo[0], lo[1], lo[2], lo[3]));
   }
-  s += __shfl_xor(s, 16);
-  s += __shfl_xor(s, 32);
+  s = lanes_sum<32, 16>(s);
   if (ok && lane < 16) st_f32(ssq_out + tile * MP + m, s);
 }
 
@@ -713,23 +709,9 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
 }
 
 // ---------------------------------------------------------------------------------------------- attention
-// Reductions over the four 16-lane rows of a wavefront (lanes l, l^16, l^32, l^48 hold values of one query row) with
-// the row-swap instructions of gfx950: a swap of a register with itself leaves "mine" in one result and "my
-// partner's" in the other, a few cycles instead of a trip through the LDS crossbar.
-__device__ __forceinline__ float max_over_rows(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned v = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-__device__ __forceinline__ float sum_over_rows(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  const unsigned v = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
+// Reductions over the four 16-lane rows of a wavefront (lanes l, l^16, l^32, l^48 hold values of one query row)
+__device__ __forceinline__ float max_over_rows(float x) { return lanes_max<32, 16>(x); }
+__device__ __forceinline__ float sum_over_rows(float x) { return lanes_sum<32, 16>(x); }
 struct OnlineSoftmax {
   float m_run, l_run;   // running maximum (base-2 exponent) and this lane's share of the running sum
   f32x4 acc[4];         // O^T: dims dt*16 + (lane>>4)*4 + r of query row lane & 15
@@ -1538,7 +1520,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_resid_kernel(FusedParams p,
     f32x4 v[2];
     chunk(c, v);
   }
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+  ss = lanes_sum(ss);
   if (lane == 0) sum_s[wave] = ss;
   __syncthreads();
   const float rs = 1.0f / sqrtf(((sum_s[0] + sum_s[1]) + (sum_s[2] + sum_s[3])) / (float)p.d + p.eps);
@@ -1972,8 +1954,7 @@ __global__ __launch_bounds__(kFusedThreads) void wide_attn_kernel(FusedParams p,
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) acc[t][dt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     int v = tv[t];
-#pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o));
+    v = lanes_reduce<8>(v, [](int a, int b) { return min(a, b); });
     vmin[t] = __builtin_amdgcn_readfirstlane(v);
   }
   // one 32-key block against tile t: scores of this lane's row for keys g4*8..+7 of the block

@@ -11,6 +11,7 @@
 // and of the KV cache.  With a handful of rows the extra MFMAs are free: the kernel is bound by the weight stream.
 // fp32 models (the small correctness configuration): plain FMA dot products.
 #include "common.h"
+#include "lanes.h"
 
 namespace ssd {
 
@@ -168,7 +169,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_kernel(const bf16_t* __
     for (int v = 1; v < kWaves; ++v) sum += red[(v * MT + t) * 64 + lane];
     if (PACK) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sum[r] += __shfl_xor(sum[r], 8);
+      for (int r = 0; r < 4; ++r) sum[r] = lanes_sum<8, 8>(sum[r]);
     }
     int m = m0 + t * 16 + (lane & 15);
     int n = nt * 16 + (lane >> 4) * 4;
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_kernel(const bf16_t* __
       for (int v = 1; v < kWaves; ++v) up += red[kWaves * MT * 64 + (v * MT + t) * 64 + lane];
       if (PACK) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) up[r] += __shfl_xor(up[r], 8);
+        for (int r = 0; r < 4; ++r) up[r] = lanes_sum<8, 8>(up[r]);
       }
     }
     if (m >= M) continue;
@@ -210,21 +211,11 @@ enum F32Epilogue { F32_STORE = 0, F32_RESIDUAL = 1, F32_SWIGLU = 2, F32_ROPE = 3
 
 // v[r] summed over the 64 lanes; lane l ends up with the sum of row l >> 3.
 __device__ __forceinline__ float rows_sum(float v[kRowsF32]) {
-  const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int half = kRowsF32 / 2, o = 32; half >= 1; half >>= 1, o >>= 1) {
+  for (int i = 0; i < 4; ++i) v[i] = lanes_split_sum<32>(v[i], v[i + 4]);
 #pragma unroll
-    for (int i = 0; i < kRowsF32 / 2; ++i)
-      if (i < half) {
-        const bool hi = (lane & o) != 0;
-        const float send = hi ? v[i] : v[i + half], keep = hi ? v[i + half] : v[i];
-        v[i] = keep + __shfl_xor(send, o);
-      }
-  }
-  float s = v[0];
-#pragma unroll
-  for (int o = 4; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-  return s;
+  for (int i = 0; i < 2; ++i) v[i] = lanes_split_sum<16>(v[i], v[i + 2]);
+  return lanes_sum<4>(lanes_split_sum<8>(v[0], v[1]));
 }
 static_assert(kRowsF32 == 8, "rows_sum leaves row lane >> 3 in a lane");
 
@@ -264,6 +255,21 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 a) {
   const float* w2 = EPI == F32_SWIGLU ? a.w2 + (int64_t)n * a.Kd : a.w + (int64_t)n2 * a.Kd;
   const int kq = (a.Kd / 4 + WPF - 1) / WPF * 4;                    // inputs per wavefront
   const int k_begin = WPF == 4 ? wave * kq : 0, k_end = min(a.Kd, k_begin + kq);
+  // what the lane that ends a row's sum will want beside it, requested first: behind the sum it would cost a memory round trip
+  const int r = lane >> 3, m = m0 + r, i_rope = EPI == F32_ROPE ? u % a.half : 0;
+  float old[2] = {0.f, 0.f}, cos_v = 1.f, sin_v = 0.f;
+  RowDesc d = {};
+  if ((lane & 7) == 0 && r < rows && (WPF == 1 || wave == 0)) {
+    if (EPI == F32_RESIDUAL) {
+      old[0] = a.out[(int64_t)m * a.ld + n];
+      if (TWO) old[1] = a.out[(int64_t)m * a.ld + n2];
+    }
+    if (EPI == F32_ROPE) {
+      cos_v = a.cos_sin[((int64_t)m * a.half + i_rope) * 2];
+      sin_v = a.cos_sin[((int64_t)m * a.half + i_rope) * 2 + 1];
+      if (n >= a.qd) d = a.desc[m];
+    }
+  }
   float acc[kRowsF32], acc2[kRowsF32], ssq[kRowsF32];
 #pragma unroll
   for (int r = 0; r < kRowsF32; ++r) { acc[r] = 0.f; acc2[r] = 0.f; ssq[r] = 0.f; }
@@ -296,7 +302,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 a) {
   float y = rows_sum(acc), y2 = 0.f, ss = 0.f;
   if (PAIR) y2 = rows_sum(acc2);
   if (NORM) ss = rows_sum(ssq);
-  const int r = lane >> 3, m = m0 + r;
   if (WPF == 4) {
     if ((lane & 7) == 0) {
       part[0][wave][r] = y;
@@ -318,20 +323,17 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 a) {
   }
   if (EPI == F32_STORE || EPI == F32_RESIDUAL) {
     float* dst = a.out + (int64_t)m * a.ld + n;
-    dst[0] = EPI == F32_STORE ? y : dst[0] + y;
-    if (TWO && n2 > n) dst[1] = EPI == F32_STORE ? y2 : dst[1] + y2;
+    dst[0] = EPI == F32_STORE ? y : old[0] + y;
+    if (TWO && n2 > n) dst[1] = EPI == F32_STORE ? y2 : old[1] + y2;
   } else if (EPI == F32_SWIGLU) a.out[(int64_t)m * a.ld + n] = (y / (1.0f + expf(-y))) * y2;
   else {
-    const int i = u % a.half;
     if (n < a.qd + a.kvd) {
-      const float c = a.cos_sin[((int64_t)m * a.half + i) * 2], sn = a.cos_sin[((int64_t)m * a.half + i) * 2 + 1];
-      const float ra = y * c - y2 * sn, rb = y2 * c + y * sn;
+      const float ra = y * cos_v - y2 * sin_v, rb = y2 * cos_v + y * sin_v;
       y = ra;
       y2 = rb;
     }
     float* dst = a.out + (int64_t)m * a.qd + n;
     if (n >= a.qd) {
-      const RowDesc d = a.desc[m];
       const int64_t row = (d.is_branch ? ((int64_t)m * a.suffix_cap + d.kv_slot) : ((int64_t)d.seq * a.max_trunk + d.kv_slot)) * a.kvd;
       if (n < a.qd + a.kvd) dst = (d.is_branch ? a.suffix_k : a.trunk_k) + row + (n - a.qd);
       else dst = (d.is_branch ? a.suffix_v : a.trunk_v) + row + (n - a.qd - a.kvd);

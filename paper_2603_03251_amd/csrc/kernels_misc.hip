@@ -1,6 +1,7 @@
 // Small kernels of the round: row descriptors and rotary tables, embedding gather, RMSNorm,
 // rotary embedding + KV append, step-token gather, cache lookup, trunk commit.
 #include "common.h"
+#include "lanes.h"
 
 namespace ssd {
 
@@ -84,7 +85,7 @@ __global__ void embed_kernel(const T* embed, const int32_t* tokens, float* h, in
 }
 
 __device__ __forceinline__ float block_sum(float v, float* smem) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  v = lanes_sum(v);
   int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   if ((threadIdx.x & 63) == 0) smem[w] = v;
   __syncthreads();

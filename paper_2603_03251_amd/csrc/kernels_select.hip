@@ -4,6 +4,7 @@
 #include <mutex>
 
 #include "common.h"
+#include "lanes.h"
 #include "rng.h"
 
 namespace ssd {
@@ -27,11 +28,7 @@ __device__ __forceinline__ uint64_t make_key(float f, int id) {
 __device__ __forceinline__ int key_id(uint64_t k) { return (int)(~(uint32_t)k); }
 
 __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    uint64_t t = __shfl_xor((unsigned long long)v, o);
-    v = t > v ? t : v;
-  }
-  return v;
+  return lanes_reduce(v, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
 }
 
 // One block per row.  Every thread keeps the best FMAX keys of its strided share in sorted registers; then F
@@ -156,14 +153,14 @@ constexpr int kSampleMaxParts = 128;  // blocks that share one row of the sample
 __device__ __forceinline__ bool better(const ScoreId& a, const ScoreId& b) {
   return a.s > b.s || (a.s == b.s && a.id < b.id);
 }
+__device__ __forceinline__ ScoreId lanes_best(ScoreId v) {
+  struct Packed { double s; int id, pad; };          // (whole registers)
+  const Packed r = lanes_reduce(Packed{v.s, v.id, 0}, [](Packed a, Packed b) { return a.s > b.s || (a.s == b.s && a.id < b.id) ? a : b; });
+  return {r.s, r.id};
+}
 template <int WAVES>
 __device__ __forceinline__ ScoreId block_argmax(ScoreId v, ScoreId* smem) {
-  for (int o = 32; o > 0; o >>= 1) {
-    ScoreId t;
-    t.s = __shfl_xor(v.s, o);
-    t.id = __shfl_xor(v.id, o);
-    if (better(t, v)) v = t;
-  }
+  v = lanes_best(v);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (lane == 0) smem[wave] = v;
   __syncthreads();
@@ -273,7 +270,7 @@ __global__ __launch_bounds__(BLOCK) void sample_kernel(const float* __restrict__
       }
     }
     float mx = mine;
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    mx = lanes_max(mx);
     __shared__ float fmx[BLOCK / 64];
     if ((threadIdx.x & 63) == 0) fmx[threadIdx.x >> 6] = mx;
     __syncthreads();
@@ -308,12 +305,7 @@ __global__ __launch_bounds__(64) void sample_merge_kernel(const ScoreId* __restr
     const ScoreId c = scratch[(int64_t)row * parts + i];
     if (better(c, best)) best = c;
   }
-  for (int o = 32; o > 0; o >>= 1) {
-    ScoreId t;
-    t.s = __shfl_xor(best.s, o);
-    t.id = __shfl_xor(best.id, o);
-    if (better(t, best)) best = t;
-  }
+  best = lanes_best(best);
   if (threadIdx.x == 0) out[(int64_t)row * out_stride] = best.id;
 }
 
@@ -325,8 +317,9 @@ __global__ __launch_bounds__(64) void sample_merge_kernel(const ScoreId* __restr
 // decides, and scores its share of the bonus row for the residual; the block of a sequence that finishes last merges the
 // shares.  A row and the bonus row are shared among `parts` blocks, so that the few rows of one verification occupy the chip;
 // partial results are merged in a fixed order (the result does not depend on timing).  Measured (V = 128256, K = 5,
-// temperature 1): B = 1 17.9 us a call (rows 7, decisions 10.5: five dependent memory round trips and three reductions), B = 16
-// half of it greedy 41 us (24 + 17; rows without their exponentials 18, of which 70 MB at the rate of a copy are 10).
+// temperature 1): B = 1 16.5 us a call (rows 6.5, decisions 9.5: five dependent memory round trips and three reductions; 18.1 with the
+// reductions through the LDS crossbar), B = 16 half of it greedy 39.4 us (23 + 16; 40.9; rows without their exponentials 18, of which
+// 70 MB at the rate of a copy are 10).
 constexpr int kVerifyBlock = 256, kVerifyWaves = kVerifyBlock / 64;
 constexpr int kVerifyMaxParts = 32;     // blocks that share a row (one lane of a wavefront merges one of them)
 constexpr int kVerifyMaxBonusParts = 64;
@@ -429,18 +422,11 @@ struct Fp32Race {
 // (best logit, its token, sum relative to it) over groups of W lanes; every lane returns its group's result
 template <int W>
 __device__ __forceinline__ VerifyPart lanes_merge(VerifyPart v, double inv_t, bool sampled, const double* table) {
-  const float own = v.max;
-#pragma unroll
-  for (int o = W / 2; o > 0; o >>= 1) {
-    const float m = __shfl_xor(v.max, o);
-    const int id = __shfl_xor(v.id, o);
-    if (better_logit(m, id, v.max, v.id)) { v.max = m; v.id = id; }
-  }
-  if (sampled) {
-    v.sum *= exp_rel(own, v.max, inv_t, table);
-#pragma unroll
-    for (int o = W / 2; o > 0; o >>= 1) v.sum += __shfl_xor(v.sum, o);
-  }
+  struct Top { float max; int32_t id; };
+  const Top top = lanes_reduce<W / 2>(Top{v.max, v.id}, [](Top a, Top b) { return better_logit(a.max, a.id, b.max, b.id) ? a : b; });
+  if (sampled) v.sum = lanes_sum<W / 2>(v.sum * exp_rel(v.max, top.max, inv_t, table));
+  v.max = top.max;
+  v.id = top.id;
   return v;
 }
 
@@ -649,7 +635,7 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_decide_kernel(const float
         least = fmaxf(least, in ? lo_s : -INFINITY);
         most[u] = in ? most[u] : -INFINITY;
       }
-      for (int o = 32; o > 0; o >>= 1) least = fmaxf(least, __shfl_xor(least, o));
+      least = lanes_max(least);
       floor_s = fmaxf(floor_s, least);
       // in fp64, the tokens that may win (all of them where none is known to have mass; a bound that is no number excludes
       // nothing).  A loop over a lane's tokens rather than U copies of its body: most wavefronts take it once, and every
@@ -678,13 +664,8 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_decide_kernel(const float
         open &= open - 1;
       }
     }
-    for (int o = 32; o > 0; o >>= 1) {
-      mass += __shfl_xor(mass, o);
-      ScoreId t;
-      t.s = __shfl_xor(best.s, o);
-      t.id = __shfl_xor(best.id, o);
-      if (better(t, best)) best = t;
-    }
+    mass = lanes_sum(mass);
+    best = lanes_best(best);
     __syncthreads();
     if (lane == 0) { mass_s[wave] = mass; best_s[wave] = best; }
     __syncthreads();
@@ -722,12 +703,7 @@ __global__ __launch_bounds__(kVerifyBlock) void verify_decide_kernel(const float
     m = __longlong_as_double((long long)__hip_atomic_load(&c->mass, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   }
   if (k < K && __any(m > 0.0) && !(m > 0.0)) mine = {-1.0, 0x7fffffff};
-  for (int o = 32; o > 0; o >>= 1) {
-    ScoreId t;
-    t.s = __shfl_xor(mine.s, o);
-    t.id = __shfl_xor(mine.id, o);
-    if (better(t, mine)) mine = t;
-  }
+  mine = lanes_best(mine);
   if (lane == 0) bonus[b] = mine.id;
 }
 
