@@ -814,7 +814,9 @@ int fused_setup(ssd_ctx* c) {
     // partial sums of o and down: eight slices of a round's rows, four of a prompt pass's (what eight would write and read again costs
     // more than the larger blocks of a slice save).  They lie where the qkv projections were: written after the
     // attention has read those, read before the next layer's are written
-    w.fix_stride = std::max(kFusedWideSlices * kFusedWideRows, c->prompt_rows > kFusedWideRows ? 4 * kFusedPromptRows : 0);
+    // (most_rows: of any wide pass, a round's or one over tokens that fit the trunk)
+    const int64_t most_rows = std::min<int64_t>(MW, std::max((int64_t)c->M, (int64_t)c->B * std::max(c->max_trunk, c->K + 1)));
+    w.fix_stride = std::max(kFusedWideSlices * std::min<int64_t>(most_rows, kFusedWideRows), most_rows > kFusedWideRows ? 4 * most_rows : 0);
     // one allocation, carved up
     char* base = nullptr;
     size_t used = 0;
