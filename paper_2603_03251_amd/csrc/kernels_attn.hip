@@ -127,6 +127,17 @@ __device__ __forceinline__ void load_elems(const T* p, float* o) {
   }
 }
 
+// the same from a register
+template <typename T, int VEC>
+__device__ __forceinline__ void unpack_elems(uint4 v, float* o) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    if constexpr (sizeof(T) == 4) o[e] = __uint_as_float(w[e & 3]);
+    else o[e] = __uint_as_float(e & 1 ? w[e / 2 & 3] & 0xffff0000u : w[e / 2 & 3] << 16);
+  }
+}
+
 // Passes with few rows (an extend, a verification forward, a small decode batch): one block per (row, KV head, split
 // of at most 256 keys), all query heads of the group (at most G) at once.  Scores: one key per thread against the group's
 // queries (in LDS); softmax over the block; weighted values: every wavefront takes a quarter of the keys the split really
@@ -146,7 +157,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
   // heads x 8 dimensions of accumulators and their exchange across lanes cost a 70B-shaped row more than they saved:
   // 55 -> 70 us for 6 rows x 8 heads x 4096 keys)
   constexpr int KV = Vec16<T>::N, VEC = G * KV <= 32 ? KV : D / 64, LPR = D / VEC, KPI = 64 / LPR;
-  constexpr int kPvBatch = 8;
+  constexpr int kPvBatch = 8, kPvAhead = G * VEC <= 8 ? 12 : 8;
   __shared__ float q_s[G][D];
   __shared__ float p_s[G][kSplitKeys];
   __shared__ float red_s[4][G][D];
@@ -165,6 +176,17 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
   const T* sk = suffix_k + ((int64_t)m * suffix_cap) * kv_stride + hk * D;
   const T* sv = suffix_v + ((int64_t)m * suffix_cap) * kv_stride + hk * D;
 
+  // ---- the first values of this wavefront's quarter of the keys (addresses only: they are on their way while the scores are taken)
+  const int n_here = max(j_end - j_begin, 0), quarter = (n_here + 3) >> 2;
+  const int jq0 = wave * quarter, jq1 = min(jq0 + quarter, n_here);
+  const int sub = lane / LPR, d0 = (lane & (LPR - 1)) * VEC;
+  auto value_row = [&](int jk) { return (jk < r.vis ? tv + (int64_t)jk * kv_stride : sv + (int64_t)(jk - r.vis) * kv_stride) + d0; };
+  constexpr int kAhead = VEC * sizeof(T) == 16 ? kPvAhead : 0;
+  uint4 ahead[kAhead > 0 ? kAhead : 1];
+  if (kAhead > 0 && jq0 < jq1) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) ahead[u] = *(const uint4*)value_row(j_begin + min(jq0 + u * KPI + sub, jq1 - 1));
+  }
   for (int i = tid; i < group * D; i += 256) {
     const int g = i / D, d = i - g * D;
     q_s[g][d] = q[((int64_t)m * n_q_heads + hk * group + g) * D + d] * scale;
@@ -218,16 +240,27 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
   for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[g][e] = 0.f;
-  const int n_here = max(j_end - j_begin, 0), quarter = (n_here + 3) >> 2;
-  const int jq0 = wave * quarter, jq1 = min(jq0 + quarter, n_here);
-  const int sub = lane / LPR, d0 = (lane & (LPR - 1)) * VEC;
-  for (int jj0 = jq0; jj0 < jq1; jj0 += KPI * kPvBatch) {
+  if (kAhead > 0 && jq0 < jq1) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int jj = jq0 + u * KPI + sub;
+      float vv[VEC];
+      unpack_elems<T, VEC>(ahead[u], vv);
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const float pe = jj < jq1 ? p_s[g][min(jj, jq1 - 1)] : 0.f;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[g][e] = fmaf(pe, vv[e], acc[g][e]);
+      }
+    }
+  }
+  for (int jj0 = jq0 + kAhead * KPI; jj0 < jq1; jj0 += KPI * kPvBatch) {
     float vv[kPvBatch][VEC], pe[kPvBatch][G];
 #pragma unroll
     for (int u = 0; u < kPvBatch; ++u) {
       const int jj = jj0 + u * KPI + sub, jc = min(jj, jq1 - 1);   // past the end: the last row again, with weight 0
       const int jk = j_begin + jc;
-      load_elems<T, VEC>((jk < r.vis ? tv + (int64_t)jk * kv_stride : sv + (int64_t)(jk - r.vis) * kv_stride) + d0, vv[u]);
+      load_elems<T, VEC>(value_row(jk), vv[u]);
 #pragma unroll
       for (int g = 0; g < G; ++g) pe[u][g] = jj < jq1 ? p_s[g][jc] : 0.f;
     }

@@ -232,6 +232,8 @@ struct GemmF32 {
   // ROPE: out = the rotated queries [M][qd]; rotated keys and values go to the row's KV slot
   const RowDesc* desc;
   const float* cos_sin;
+  float* hidden;      // STORE behind a norm: the normalised rows [M][hidden_ld], or null
+  int64_t hidden_ld;
   float *trunk_k, *trunk_v, *suffix_k, *suffix_v;
   int qd, kvd, half, max_trunk, suffix_cap;
 };
@@ -314,6 +316,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 a) {
     y = total(0);
     if (PAIR) y2 = total(1);
     if (NORM) ss = total(2);
+  }
+  if (EPI == F32_STORE && NORM && a.hidden && u < rows) {               // (the grid has a unit for each of a group's 8 rows: host check)
+    const float rs = 1.0f / sqrtf(__shfl(ss, u * 8) / (float)a.Kd + a.eps);
+    for (int k = lane * 4; k < a.Kd; k += 256) {
+      const float4 x = *(const float4*)(a.x + (int64_t)(m0 + u) * a.Kd + k), g = *(const float4*)(a.gain + k);
+      *(float4*)(a.hidden + (int64_t)(m0 + u) * a.hidden_ld + k) = make_float4(x.x * rs * g.x, x.y * rs * g.y, x.z * rs * g.z, x.w * rs * g.w);
+    }
   }
   if ((lane & 7) != 0 || r >= rows) return;
   if (NORM) {
@@ -427,6 +436,15 @@ int launch_gemm(int dtype, int epi, const void* x, int64_t x_plane, const void* 
     case EPI_RESIDUAL_ADD: return launch_f32<F32_RESIDUAL, false>(a, s);
     default: set_error("fp32 gate/up layers run with their norm (launch_norm_swiglu_f32)"); return SSD_EINVAL;
   }
+}
+
+int launch_norm_head_f32(const float* h, const float* gain, const float* w, float* logits, int64_t ld, float* hidden, int64_t hidden_ld,
+                         int M, int V, int d_model, float eps, hipStream_t s) {
+  if (M <= 0) return SSD_OK;
+  SSD_CHECK_ARG(V >= 2 * kRowsF32 && hidden_ld % 4 == 0 && (uintptr_t)hidden % 16 == 0, "fp32 head of %d features", V);
+  GemmF32 a{};
+  a.x = h; a.gain = gain; a.w = w; a.out = logits; a.ld = ld; a.M = M; a.N = V; a.Kd = d_model; a.eps = eps; a.hidden = hidden; a.hidden_ld = hidden_ld;
+  return launch_f32<F32_STORE, true>(a, s);
 }
 
 int launch_norm_swiglu_f32(const float* h, const float* gain, const float* w_gate, const float* w_up, float* act, int M, int d_ffn,

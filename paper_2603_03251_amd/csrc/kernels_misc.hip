@@ -17,6 +17,24 @@ __device__ __forceinline__ void write_cos_sin(float* cos_sin, int row, int half_
   cos_sin[((int64_t)row * half_dim + i) * 2 + 1] = (float)sin(ang);
 }
 
+// Block `block` of an embedding gather: kBlock x 4 elements of a row (d is a multiple of 4).
+__device__ __forceinline__ int embed_blocks_per_row(int d) { return (d / 4 + kBlock - 1) / kBlock; }
+__device__ __forceinline__ void embed_part(const EmbedGather& e, int m, int part, int tok) {
+  const int c = (part * kBlock + (int)threadIdx.x) * 4;
+  if (c >= e.d) return;
+  tok = tok < 0 ? 0 : (tok >= e.vocab ? e.vocab - 1 : tok);
+  const int64_t at = (int64_t)tok * e.d + c;
+  float4 v;
+  if (e.dtype == SSD_BF16) {
+    const uint2 w = *(const uint2*)((const bf16_t*)e.table + at);
+    v = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
+                    __uint_as_float(w.y & 0xffff0000u));
+  } else {
+    v = *(const float4*)((const float*)e.table + at);
+  }
+  *(float4*)(e.h + (int64_t)m * e.d + c) = v;
+}
+
 // Branch rows at depth `step` (App. B): row (b,k,j) sits at position trunk_len+1+k+step, sees the trunk up to
 // the glue position of accept length k, and its own step+1 private positions.
 // Everything a branch-decode step needs before its forward pass, in one launch: the row descriptors and rotary tables
@@ -25,7 +43,16 @@ __device__ __forceinline__ void write_cos_sin(float* cos_sin, int row, int half_
 __global__ void setup_branch_rows_kernel(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, int M, int K,
                                          FanTable fan, int step, int half_dim, float theta, int32_t* step_tokens, const int32_t* keys,
                                          const int32_t* cache_tokens, const int32_t* forced_keys,
-                                         const int32_t* forced_tokens) {
+                                         const int32_t* forced_tokens, EmbedGather embed, int setup_blocks) {
+  auto token_of = [&](int m) {
+    if (step == 0) return forced_keys ? forced_keys[m] : keys[m];
+    return forced_tokens ? forced_tokens[(int64_t)m * K + step - 1] : cache_tokens[(int64_t)m * K + step - 1];
+  };
+  if ((int)blockIdx.x >= setup_blocks) {                       // blocks behind the set-up's: the embedding gather
+    const int part = (int)blockIdx.x - setup_blocks, per_row = embed_blocks_per_row(embed.d);
+    embed_part(embed, part / per_row, part % per_row, token_of(part / per_row));
+    return;
+  }
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= M * half_dim) return;
   int m = idx / half_dim, i = idx % half_dim;
@@ -39,10 +66,7 @@ __global__ void setup_branch_rows_kernel(RowDesc* rows, float* cos_sin, const in
     RowDesc r;
     r.seq = b; r.pos = pos; r.vis = tl + k + 1; r.suffix_len = step + 1; r.kv_slot = step; r.is_branch = 1;
     rows[m] = r;
-    if (step_tokens) {
-      if (step == 0) step_tokens[m] = forced_keys ? forced_keys[m] : keys[m];
-      else step_tokens[m] = forced_tokens ? forced_tokens[(int64_t)m * K + step - 1] : cache_tokens[(int64_t)m * K + step - 1];
-    }
+    if (step_tokens) step_tokens[m] = token_of(m);
   }
   write_cos_sin(cos_sin, m, half_dim, i, pos, theta);
 }
@@ -51,7 +75,13 @@ __global__ void setup_branch_rows_kernel(RowDesc* rows, float* cos_sin, const in
 // rows of sequences seq_base .. seq_base + B - 1 (row m of the pass = token m % T of sequence seq_base + m / T)
 // limit (or null): sequence b stores the keys of its first limit[b] trunk positions only, rows behind them pad
 __global__ void setup_extend_rows_kernel(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, const int32_t* limit, int B, int T,
-                                         int offset, int half_dim, float theta, int seq_base) {
+                                         int offset, int half_dim, float theta, int seq_base, EmbedGather embed,
+                                         const int32_t* tokens, int setup_blocks) {
+  if ((int)blockIdx.x >= setup_blocks) {                       // blocks behind the set-up's: the embedding gather
+    const int part = (int)blockIdx.x - setup_blocks, per_row = embed_blocks_per_row(embed.d);
+    embed_part(embed, part / per_row, part % per_row, tokens[part / per_row]);
+    return;
+  }
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= B * T * half_dim) return;
   int m = idx / half_dim, i = idx % half_dim;
@@ -64,24 +94,6 @@ __global__ void setup_extend_rows_kernel(RowDesc* rows, float* cos_sin, const in
     rows[m] = r;
   }
   write_cos_sin(cos_sin, m, half_dim, i, pos, theta);
-}
-
-template <typename T>
-__global__ void embed_kernel(const T* embed, const int32_t* tokens, float* h, int M, int d, int vocab) {
-  const int m = blockIdx.x, c = ((int)blockIdx.y * kBlock + (int)threadIdx.x) * 4;   // (d is a multiple of 4)
-  if (c >= d) return;
-  int tok = tokens[m];
-  tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);
-  const T* src = embed + (int64_t)tok * d + c;
-  float4 v;
-  if constexpr (sizeof(T) == 2) {
-    const uint2 w = *(const uint2*)src;
-    v = make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
-                    __uint_as_float(w.y & 0xffff0000u));
-  } else {
-    v = *(const float4*)src;
-  }
-  *(float4*)(h + (int64_t)m * d + c) = v;
 }
 
 __device__ __forceinline__ float block_sum(float v, float* smem) {
@@ -271,30 +283,26 @@ inline int grid_for(int64_t n) { return (int)((n + kBlock - 1) / kBlock); }
 
 }  // namespace
 
+static int embed_blocks(const EmbedGather& e, int M) { return e.table ? M * ((e.d / 4 + kBlock - 1) / kBlock) : 0; }
+
 int launch_setup_branch_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, int B, int K, const FanTable& fan, int step,
                              int half_dim, float theta, int32_t* step_tokens, const int32_t* keys,
                              const int32_t* cache_tokens, const int32_t* forced_keys, const int32_t* forced_tokens,
-                             hipStream_t s) {
+                             const EmbedGather& embed, hipStream_t s) {
   const int M = B * fan.off[K + 1];
-  setup_branch_rows_kernel<<<grid_for((int64_t)M * half_dim), kBlock, 0, s>>>(rows, cos_sin, trunk_len, M, K, fan, step,
-                                                                             half_dim, theta, step_tokens, keys,
-                                                                             cache_tokens, forced_keys, forced_tokens);
+  const int blocks = grid_for((int64_t)M * half_dim);
+  setup_branch_rows_kernel<<<blocks + embed_blocks(embed, M), kBlock, 0, s>>>(rows, cos_sin, trunk_len, M, K, fan, step, half_dim, theta,
+                                                                              step_tokens, keys, cache_tokens, forced_keys, forced_tokens,
+                                                                              embed, blocks);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }
 
 int launch_setup_extend_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, const int32_t* limit, int B, int T, int offset,
-                             int half_dim, float theta, int seq_base, hipStream_t s) {
-  setup_extend_rows_kernel<<<grid_for((int64_t)B * T * half_dim), kBlock, 0, s>>>(rows, cos_sin, trunk_len, limit, B, T,
-                                                                                 offset, half_dim, theta, seq_base);
-  SSD_HIP(hipGetLastError());
-  return SSD_OK;
-}
-
-int launch_embed(int dtype, const void* embed, const int32_t* tokens, float* h, int M, int d, int vocab, hipStream_t s) {
-  const dim3 grid(M, (d / 4 + kBlock - 1) / kBlock);
-  if (dtype == SSD_BF16) embed_kernel<bf16_t><<<grid, kBlock, 0, s>>>((const bf16_t*)embed, tokens, h, M, d, vocab);
-  else embed_kernel<float><<<grid, kBlock, 0, s>>>((const float*)embed, tokens, h, M, d, vocab);
+                             int half_dim, float theta, int seq_base, const EmbedGather& embed, const int32_t* tokens, hipStream_t s) {
+  const int blocks = grid_for((int64_t)B * T * half_dim);
+  setup_extend_rows_kernel<<<blocks + embed_blocks(embed, B * T), kBlock, 0, s>>>(rows, cos_sin, trunk_len, limit, B, T, offset, half_dim,
+                                                                                  theta, seq_base, embed, tokens, blocks);
   SSD_HIP(hipGetLastError());
   return SSD_OK;
 }

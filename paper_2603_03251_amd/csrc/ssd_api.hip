@@ -538,8 +538,16 @@ int fused_forward(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_
   return SSD_OK;
 }
 
+// What the set-up launch of a pass gathers: the embeddings, for passes of one kernel per operator (the others do it themselves).
+EmbedGather embed_gather(const ssd_ctx* c) {
+  if (c->fused_mode) return EmbedGather{};
+  const Dims& d = c->model->dims;
+  return EmbedGather{c->model->embed, c->h, d.d_model, d.vocab, d.dtype};
+}
+
 // One batched pass of the decoder over `M` rows whose descriptors and rotary tables are already in ctx->rows /
-// ctx->cos_sin.  Logits (fp32, row stride logits_ld) and final-norm hidden states are optional.
+// ctx->cos_sin (and, where embed_gather says so, whose embeddings are in ctx->h).  Logits (fp32, row stride logits_ld) and final-norm
+// hidden states are optional.
 // max_vis: host bound of the stored trunk positions any row sees; branch_depth: decode step of branch rows, -1 for an extend.
 // wide: fused contexts run the pass as wide passes.
 int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_per_seq, int max_vis, int branch_depth, float* logits,
@@ -550,7 +558,6 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
     return fused_forward(c, wide, M, tokens, rows_per_seq, max_vis, branch_depth, logits, logits_ld, hidden, hidden_ld, seq_base, s);
   const int dt = d.dtype;
   const int64_t R = c->max_rows;     // plane stride of an activation buffer = R * columns
-  SSD_TRY(launch_embed(dt, m->embed, tokens, c->h, M, d.d_model, d.vocab, s));
   for (int l = 0; l < d.n_layers; ++l) {
     const ssd_model::Layer& L = m->layers[l];
     if (dt == SSD_F32) {
@@ -586,6 +593,10 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
                         d.d_ffn, s));
   }
   if (logits || hidden) {
+    // (a head of fewer than 16 features has no 8 units to write the rows' hidden states)
+    if (dt == SSD_F32 && logits && d.vocab >= 16)
+      return launch_norm_head_f32(c->h, (const float*)m->final_norm, (const float*)m->lm_head, logits, logits_ld, hidden, hidden_ld, M,
+                                  d.vocab, d.d_model, d.rms_eps, s);
     SSD_TRY(launch_rmsnorm(dt, c->h, m->final_norm, c->xn, R * d.d_model, hidden, hidden_ld, M, d.d_model, d.rms_eps, s));
     if (logits) SSD_TRY(launch_gemm(dt, EPI_STORE_F32, c->xn, R * d.d_model, m->lm_head, nullptr, logits, logits_ld, 0, M,
                                     d.vocab, d.d_model, s));
@@ -622,7 +633,7 @@ int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset,
   const Dims& d = c->model->dims;
   SSD_TRY(pages_for_pass(c, b0, nb, offset + T, h_limit, s));
   SSD_TRY(launch_setup_extend_rows(c->rows, c->cos_sin, c->trunk_len, h_limit ? c->prompt_len : nullptr, nb, T, offset, d.head_dim / 2,
-                                   d.rope_theta, b0, s));
+                                   d.rope_theta, b0, embed_gather(c), tokens, s));
   int ub = 0;
   for (int b = b0; b < b0 + nb; ++b) ub = c->ub_of[b] > ub ? c->ub_of[b] : ub;
   if (wide && takes_small_pass(c, nb, T, ub + offset, s)) wide = false;
@@ -1393,7 +1404,7 @@ int ssd_prespeculate(ssd_ctx* c, const int32_t* d_pending, const float* d_temper
   // a2/a3: K batched branch-decode steps; logits and tokens land in the cache directly
   for (int i = 0; i < K; ++i) {
     SSD_TRY(launch_setup_branch_rows(c->rows, c->cos_sin, c->trunk_len, B, K, c->fan, i, d.head_dim / 2, d.rope_theta, c->step_tokens,
-                                     c->keys, c->tokens, c->forced_keys, c->forced_tokens, s));
+                                     c->keys, c->tokens, c->forced_keys, c->forced_tokens, embed_gather(c), s));
     SSD_TRY(forward_rows(c, c->fused_wide, M, c->step_tokens, RB, c->trunk_ub + K + 1, i, c->logits + (size_t)i * V, (int64_t)K * V,
                          c->hidden + (size_t)i * d.d_model, (int64_t)K * d.d_model, 0, s));
     if (c->saguaro_c < 1.0f) {
