@@ -13,8 +13,9 @@ constexpr int kBlock = 256;
 __device__ __forceinline__ void write_cos_sin(float* cos_sin, int row, int half_dim, int i, int pos, float theta) {
   double inv = pow((double)theta, -2.0 * (double)i / (double)(2 * half_dim));
   double ang = (double)pos * inv;
-  cos_sin[((int64_t)row * half_dim + i) * 2 + 0] = (float)cos(ang);
-  cos_sin[((int64_t)row * half_dim + i) * 2 + 1] = (float)sin(ang);
+  double sn, cs;
+  sincos(ang, &sn, &cs);
+  *(float2*)(cos_sin + ((int64_t)row * half_dim + i) * 2) = make_float2((float)cs, (float)sn);
 }
 
 // Block `block` of an embedding gather: kBlock x 4 elements of a row (d is a multiple of 4).
