@@ -454,7 +454,7 @@ def main():
         "roofline": {"kernel": ((f"fused_kernel: one batched branch-decode step ({r.rows} rows) in one persistent launch"
                                  if B.ssd_ctx_views(ctx).pass_rows <= 48 else
                                  f"wide pass: one batched branch-decode step ({r.rows} rows), one launch per phase "
-                                 f"(wide_gemm_kernel, wide_tile_kernel, wide_attn_kernel, wide_resid_kernel)") if fused
+                                 f"(wide_block_kernel, wide_tile_kernel, wide_attn_kernel, wide_resid_kernel)") if fused
                                 else f"one batched branch-decode step ({r.rows} rows), one kernel per operator"),
                      "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic_bytes() if headline and fused else None,

@@ -145,7 +145,7 @@ __device__ __forceinline__ void unpack_elems(uint4 v, float* o) {
 // a split of 64 keys is one memory round trip there, where 64 fixed keys per wavefront and one row per load made it eight.
 // Writes the split's partial softmax (max, sum, unnormalised output) to `partial` [row][query head][split][D + 2];
 // attention_merge_kernel adds the splits up in split order.  A single split is the result (partial == nullptr).
-// 10 rows x 4 heads x 138 keys, fp32: 7.0 us (18.5 us and 4.7 us of merge before).
+// 10 rows x 4 heads x 138 keys, fp32: 6.4 us (18.5 us and 4.7 us of merge before; 6.6 with the values requested behind the scores).
 template <typename T, int D, int G>
 __global__ __launch_bounds__(256) void attention_split_kernel(const float* __restrict__ q, const T* __restrict__ trunk_k,
                                                                const T* __restrict__ trunk_v, const T* __restrict__ suffix_k,

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kWaves * 64) void gemm_bf16_kernel(const bf16_t* __
 // halves the number of rows it carries at each step (10 exchanges for 8 rows instead of 48).  WPF = 4 (few features, long
 // reduction dimension): the four wavefronts of a block share a feature.  NORM: the input is the residual stream, the RMSNorm
 // runs along in the same loads (y = 1/rms(x) * sum x gain w): no kernel of its own.  A round of the 2-layer, 256-wide
-// configuration (10 rows, prefix 128): 4.2 (o), 4.6 (down), 6.4 (qkv) and 6.8 us (gate/up); 12.3, 12.3, 7.1 and 9.4 with one 4-byte element
+// configuration (10 rows, prefix 128): 3.4 (o), 3.5 (down), 4.5 (qkv) and 5.3 us (gate/up); 12.3, 12.3, 7.1 and 9.4 with one 4-byte element
 // per lane and step, behind separate norm (4.2 us) and rotary (3.3 us) kernels.
 constexpr int kRowsF32 = 8;
 constexpr int kStepsF32 = 4;

@@ -640,9 +640,10 @@ int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset,
   return forward_rows(c, wide, nb * T, tokens, T, ub + offset, -1, logits, d.vocab, hidden, d.d_model, b0, s);
 }
 
-// What a prompt pass of `rows` rows costs, in rows: the weights it streams, its launches, and one more step where the row groups
-// of 128 begin (1B shape, ms: 64 rows 1.10, 128 1.31, 256 1.69, 384 1.77, 385 2.08, 512 2.21, 768 2.84, 1024 3.27; as a persistent
-// pass 10 rows 0.64, 48 rows 0.73.  Narrower models pay more for a pass and less for a row).
+// What a prompt pass of `rows` rows costs, in rows: the weights it streams, its launches, and one more step behind 384 rows, where o and
+// down have room for half the slices (8 layers of the 1B shape, ms: 60 rows 0.48, 100 0.56, 200 0.67, 299 0.80, 384 0.85, 450 0.94, 700
+// 1.19, 1020 1.44; as a persistent pass
+// of 16 layers 10 rows 0.64, 48 rows 0.73.  Narrower models pay more for a pass and less for a row).
 int prompt_pass_cost(const ssd_ctx* c, int rows) {
   if (rows <= kFusedMaxRows && c->small_passes) return 300;
   return 450 + rows + (rows > kFusedWideRows ? 80 : 0);
