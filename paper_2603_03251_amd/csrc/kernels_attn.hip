@@ -276,7 +276,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
       float v = acc[g][e];
-      if constexpr (LPR < 64) v = lanes_sum<32, LPR>(v);
+      if constexpr (LPR < 64) v = lanes_sum<LPR, 32>(v);
       if (lane < LPR) red_s[wave][g][d0 + e] = v;
     }
   __syncthreads();
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(256) void attention_extend_kernel(const float* __re
       sv[e] = key < min(vis, j_end) ? (e < 4 ? S[0][e & 3] : S[1][e & 3]) : -INFINITY;
       mx = fmaxf(mx, sv[e]);
     }
-    mx = lanes_max<32, 16>(mx);
+    mx = lanes_max<16, 32>(mx);
     const float m_new = fmaxf(m_run, mx), m_use = m_new == -INFINITY ? 0.f : m_new;
     const float corr = expf(m_run - m_use);
     m_run = m_new;
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(256) void attention_extend_kernel(const float* __re
   // ---- the wavefronts' partial softmaxes meet in LDS, where V^T was
   f32x4* mrg = (f32x4*)vt_all;                                           // [wave][DT][64]
   static_assert((size_t)DT * 64 * 16 <= (size_t)D * kExtVt * 2, "a wavefront's tile fits where its V^T was");
-  l_run = lanes_sum<32, 16>(l_run);
+  l_run = lanes_sum<16, 32>(l_run);
   __syncthreads();
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) mrg[(wave * DT + dt) * 64 + lane] = acc[dt];

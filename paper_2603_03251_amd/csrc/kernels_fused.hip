@@ -274,7 +274,7 @@ __device__ __forceinline__ void compute_row_scales(const FusedParams& p, const f
 #pragma unroll
     for (int i = 0; i < 16; ++i) s += j0 + 8 * i < n_tiles ? v[i] : 0.f;
   }
-  s = lanes_sum<4>(s);
+  s = lanes_sum<1, 4>(s);
   if (m < p.M && part == 0) r_s[m] = 1.0f / sqrtf(s / (float)p.d + p.eps);
   wg_barrier();
 }
@@ -294,7 +294,7 @@ __device__ __forceinline__ void row_scales_finish(const FusedParams& p, const fl
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < N; ++i) s += v[i];
-  s = lanes_sum<4>(s);
+  s = lanes_sum<1, 4>(s);
   if (m < p.M && (tid & 7) == 0) r_s[m] = 1.0f / sqrtf(s / (float)p.d + p.eps);
 }
 
@@ -322,7 +322,7 @@ __device__ __forceinline__ void resid_store(const FusedParams& p, f32x4 hn, int 
     st_u64(xn_out + off, pack_bf16x4(hi[0], hi[1], hi[2], hi[3]));
     if (NPX == 2) st_u64(xn_out + (int64_t)MP * p.d + off, pack_bf16x4(lo[0], lo[1], lo[2], lo[3]));
   }
-  s = lanes_sum<32, 16>(s);
+  s = lanes_sum<16, 32>(s);
   if (ok && lane < 16) st_f32(ssq_out + tile * MP + m, s);
 }
 
@@ -710,8 +710,8 @@ __device__ __forceinline__ bool gemm_phase(const FusedParams& p, const FusedGemm
 
 // ---------------------------------------------------------------------------------------------- attention
 // Reductions over the four 16-lane rows of a wavefront (lanes l, l^16, l^32, l^48 hold values of one query row)
-__device__ __forceinline__ float max_over_rows(float x) { return lanes_max<32, 16>(x); }
-__device__ __forceinline__ float sum_over_rows(float x) { return lanes_sum<32, 16>(x); }
+__device__ __forceinline__ float max_over_rows(float x) { return lanes_max<16, 32>(x); }
+__device__ __forceinline__ float sum_over_rows(float x) { return lanes_sum<16, 32>(x); }
 struct OnlineSoftmax {
   float m_run, l_run;   // running maximum (base-2 exponent) and this lane's share of the running sum
   f32x4 acc[4];         // O^T: dims dt*16 + (lane>>4)*4 + r of query row lane & 15

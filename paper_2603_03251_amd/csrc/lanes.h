@@ -1,8 +1,8 @@
 // Exchanges between the lanes of a wavefront on the vector unit.  __shfl_xor goes through the LDS crossbar, some 60 clocks for each
 // 32 bits and step of a chain; within 16 lanes DPP reads another lane's register as an operand, and gfx950 swaps 16- and 32-lane rows in
 // one instruction.  Rounds of the tiny fp32 pair (10 rows, 75 launches) 349 -> 304 us with these and the loads its linear layers want last
-// requested first, a verification of one sequence 18.1 -> 16.5, 24-row rounds of the 1B shape 4969 -> 4898.  The butterflies below take the same partners in the same order as `for (o = 32; o > 0; o >>= 1)` over
-// __shfl_xor(v, o): the same bits.
+// requested first, a verification of one sequence 18.1 -> 16.5, 24-row rounds of the 1B shape 4969 -> 4898.  The butterflies below take the
+// partners that __shfl_xor(v, o) takes, o from FROM to LAST, halved or doubled from step to step: in the same order, the same bits.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -35,11 +35,12 @@ __device__ __forceinline__ void lane_pair(uint32_t v, uint32_t& a, uint32_t& b) 
   }
 }
 
-// op over groups of 2 FROM lanes down to pairs LAST apart (a whole wavefront: 32 and 1); op has to be commutative.  Every lane gets its
-// group's result.
+// op over lanes FROM apart, then half (or, LAST > FROM, twice) as far at each step until LAST apart: a whole wavefront is 32 to 1.  op has
+// to be commutative.  Every lane gets its group's result.  A sum's bits depend on the order: the narrow pass's row scales and the sums
+// over rows of 16 lanes take their nearest lanes first.
 template <int FROM = 32, int LAST = 1, typename T, typename Op>
 __device__ __forceinline__ T lanes_reduce(T v, Op op) {
-  static_assert(sizeof(T) % 4 == 0 && FROM >= LAST, "whole registers, at least one step");
+  static_assert(sizeof(T) % 4 == 0, "whole registers");
   struct Words { uint32_t w[sizeof(T) / 4]; };
   const Words x = __builtin_bit_cast(Words, v);
   Words a, b;
@@ -47,6 +48,7 @@ __device__ __forceinline__ T lanes_reduce(T v, Op op) {
   for (unsigned i = 0; i < sizeof(T) / 4; ++i) lane_pair<FROM>(x.w[i], a.w[i], b.w[i]);
   const T r = op(__builtin_bit_cast(T, a), __builtin_bit_cast(T, b));
   if constexpr (FROM > LAST) return lanes_reduce<FROM / 2, LAST>(r, op);
+  else if constexpr (FROM < LAST) return lanes_reduce<FROM * 2, LAST>(r, op);
   else return r;
 }
 template <int FROM = 32, int LAST = 1, typename T>
