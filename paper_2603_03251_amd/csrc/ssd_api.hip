@@ -16,6 +16,7 @@
 #include <stdlib.h>
 
 #include "common.h"
+#include "f32_head.h"
 #include "fused.h"
 
 namespace ssd {
@@ -593,8 +594,7 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
                         d.d_ffn, s));
   }
   if (logits || hidden) {
-    // (a head of fewer than 16 features has no 8 units to write the rows' hidden states)
-    if (dt == SSD_F32 && logits && d.vocab >= 16)
+    if (dt == SSD_F32 && logits && f32_head_takes_norm(M, d.vocab, d.d_model))
       return launch_norm_head_f32(c->h, (const float*)m->final_norm, (const float*)m->lm_head, logits, logits_ld, hidden, hidden_ld, M,
                                   d.vocab, d.d_model, d.rms_eps, s);
     SSD_TRY(launch_rmsnorm(dt, c->h, m->final_norm, c->xn, R * d.d_model, hidden, hidden_ld, M, d.d_model, d.rms_eps, s));

@@ -170,6 +170,17 @@ def test_f32_odd_sizes(B, shape, kw):
     assert worst < 2e-6          # measured 3e-7 on the 2-layer tiny pair; fp32 sums of up to 1100 terms in another order
 
 
+@pytest.mark.parametrize("vocab,F", [(8100, 4), (8100, 5), (8200, 2)])
+def test_f32_head_on_both_sides_of_its_lines(B, vocab, F):
+    """Width 1032, glue passes of 8 rows (one group) and steps of 16, 32 or 40 (two, four or five): heads of 8100 features take the
+    norm along with one and four groups, not with five; heads of 8200 with two, not with one."""
+    print(f"[case] fp32 head of {vocab} features, F {F}", flush=True)
+    shape = I.ModelShape(n_layers=1, d_model=1032, n_q_heads=4, n_kv_heads=2, head_dim=64, d_ffn=516, vocab=vocab, dtype="f32",
+                         rope_theta=10000.0, tie_embeddings=False)
+    *_, worst = _run_round_parity(B, shape, batch=1, P=40, K=7, F=F, seed=7, synthetic_kv=True)
+    assert worst < 2e-6          # the bound of the odd sizes above, which have the same longest sums
+
+
 @pytest.mark.parametrize("batch,T", [(4, 2), (3, 3), (25, 6)])
 def test_f32_linear_layers_of_two_features_per_wavefront(B, batch, T):
     """Up to 8 rows one feature per wavefront everywhere; with 9 rows the head of 6147 features takes two (769 blocks in two row
