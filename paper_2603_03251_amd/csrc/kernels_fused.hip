@@ -2579,8 +2579,9 @@ int launch_wide_block_of(const FusedParams& p, const FusedGemm& g, const bf16_t*
 template <int ATW, int EPI>
 int launch_wide_block(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
   constexpr bool kSlices = EPI == FE_PART;
-  const WideChoice c = choose_wide_block(g.n_units / g.KS * ATW, wide_k_tiles(g), p.M, p.nwg, kNumWideBlocks - (EPI == FE_LOGITS ? 0 : 1),
-                                         kFusedWideSlices, kSlices ? p.fix_stride : 0, p.d);
+  constexpr int kBlocks = EPI == FE_LOGITS ? kNumWideBlocks : EPI == FE_SWIGLU ? kGateUpBlocks : kLayerBlocks;
+  const WideChoice c = choose_wide_block(g.n_units / g.KS * ATW, wide_k_tiles(g), p.M, p.nwg, kBlocks, kFusedWideSlices,
+                                         kSlices ? p.fix_stride : 0, p.d);
   e.S = c.S;
   switch (c.block) {
     case 0: return launch_wide_block_of<ATW, EPI, 4, 2, 2, kSlices ? 1 : 2, 6, 256>(p, g, bsrc, e, s);
@@ -2591,12 +2592,14 @@ int launch_wide_block(const FusedParams& p, const FusedGemm& g, const bf16_t* bs
     case 5: return launch_wide_block_of<ATW, EPI, 8, 8, 4, 1, 5, 512>(p, g, bsrc, e, s);
     case 6: return launch_wide_block_of<ATW, EPI, 8, 12, 4, 1, 5, 512>(p, g, bsrc, e, s);
     case 7: return launch_wide_block_of<ATW, EPI, 16, 8, 2, 1, 5, 512>(p, g, bsrc, e, s);
-    case 8: return launch_wide_block_of<ATW, EPI, 16, 12, 2, 1, 5, 256>(p, g, bsrc, e, s);
-    case 9: return launch_wide_block_of<ATW, EPI, 16, 16, 2, 1, 4, 512>(p, g, bsrc, e, s);
-    default:
-      if constexpr (EPI == FE_LOGITS) return launch_wide_block_of<ATW, EPI, 16, 6, 4, 1, 5, 256>(p, g, bsrc, e, s);
-      return SSD_EINVAL;
+    default: break;
   }
+  if constexpr (kBlocks > 8) {
+    if (c.block == 8) return launch_wide_block_of<ATW, EPI, 16, 12, 2, 1, 5, 256>(p, g, bsrc, e, s);
+    if (c.block == 9) return launch_wide_block_of<ATW, EPI, 16, 16, 2, 1, 4, 512>(p, g, bsrc, e, s);
+  }
+  if constexpr (kBlocks > 10) return launch_wide_block_of<ATW, EPI, 16, 6, 4, 1, 5, 256>(p, g, bsrc, e, s);
+  return SSD_EINVAL;
 }
 
 // The attention units of a pass, p.NQ query tiles each (the host chooses them together with the key splits)
@@ -2767,10 +2770,10 @@ int launch_fused_wide(const FusedParams& p, const FusedLayer* layers_host, int f
   return launch_wide_pl<Planes<1, 1, 1, 2, 2>, false>(p, layers_host, first, last, s);
 }
 
-// Shapes the wide pass takes: every layer's stream-order layout must cut into sets of 4 feature tiles over whole
-// k-ranges of an even number of k-tiles per wavefront.
+// Shapes the wide pass takes: every layer's stream-order layout must cut into sets of 4 feature tiles, and its reduction dimension into
+// eight slices of an even number of k-tiles (a step of a block is one k-tile and its loop takes two).
 bool fused_wide_gemm_ok(const FusedGemm& g, int at) {
-  if (g.KS * g.KTW % 2) return false;                        // k-tiles in whole turns of 8 slices of two steps
+  if (g.KS * g.KTW % 2) return false;                        // (8 KS KTW k-tiles)
   if (at == 4) return g.KS == 1;
   return at == 2 && (g.n_units / g.KS) % 2 == 0;
 }

@@ -18,6 +18,7 @@
 #include "common.h"
 #include "f32_head.h"
 #include "fused.h"
+#include "wide_blocks.h"
 
 namespace ssd {
 
@@ -823,12 +824,11 @@ int fused_setup(ssd_ctx* c) {
     // query rows of a pass: whole 16-row tiles per sequence
     c->part_wide.ns_max = std::min((c->max_trunk + 2047) / 2048 + 1, kFusedMaxSplits);
     c->part_wide.entries = (int64_t)p.Hkv * c->part_wide.ns_max * ((int64_t)MW * p.G + 16 * std::min(c->B, (int)MW));
-    // partial sums of o and down: eight slices of a round's rows, four of a prompt pass's (what eight would write and read again costs
-    // more than the larger blocks of a slice save).  They lie where the qkv projections were: written after the
-    // attention has read those, read before the next layer's are written
+    // partial sums of o and down lie where the qkv projections were: written after the attention has read those, read before the next
+    // layer's are written
     // (most_rows: of any wide pass, a round's or one over tokens that fit the trunk)
     const int64_t most_rows = std::min<int64_t>(MW, std::max((int64_t)c->M, (int64_t)c->B * std::max(c->max_trunk, c->K + 1)));
-    w.fix_stride = std::max(kFusedWideSlices * std::min<int64_t>(most_rows, kFusedWideRows), most_rows > kFusedWideRows ? 4 * most_rows : 0);
+    w.fix_stride = wide_part_room(most_rows, kFusedWideRows, kFusedWideSlices);
     // one allocation, carved up
     char* base = nullptr;
     size_t used = 0;

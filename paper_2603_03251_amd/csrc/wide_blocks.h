@@ -17,6 +17,16 @@ namespace ssd {
 struct WideBlock { int ft, rt; };
 constexpr WideBlock kWideBlocks[] = {{4, 2}, {4, 4}, {4, 6}, {4, 8}, {8, 6}, {8, 8}, {8, 12}, {16, 8}, {16, 12}, {16, 16}, {16, 6}};
 constexpr int kNumWideBlocks = sizeof(kWideBlocks) / sizeof(kWideBlocks[0]);   // the last one for the LM head only (288 rows: three groups)
+// Gate/up takes all but that one; qkv, o and down no block of 16 x 12 or 16 x 16, which no shape of a fused pass has the features for on
+// 256 workgroups (at most 512 tiles of qkv, 128 of o and down in two or more slices).
+constexpr int kGateUpBlocks = kNumWideBlocks - 1, kLayerBlocks = 8;
+
+// Rows of partial sums a context has room for, whose wide passes have at most `rows` rows: eight slices of a round's (at most
+// `round_rows`), four of a prompt pass's (what eight would write and read again costs more than the larger blocks of a slice save).
+constexpr int64_t wide_part_room(int64_t rows, int64_t round_rows, int max_slices) {
+  const int64_t round = max_slices * (rows < round_rows ? rows : round_rows), prompt = rows > round_rows ? max_slices / 2 * rows : 0;
+  return round > prompt ? round : prompt;
+}
 
 struct WideChoice { int block, S; };
 
