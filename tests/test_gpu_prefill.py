@@ -77,8 +77,8 @@ def test_wide_prefill_equals_narrow_chunks(B, lens):
                                         (512, [1409]), (1024, [500, 512, 30])], ids=lambda x: str(x) if isinstance(x, int) else "-".join(map(str, x)))
 @pytest.mark.parametrize("paged", [False, True])
 def test_prompt_passes_at_the_edges_of_their_row_groups(B, width, lens, paged):
-    """Passes of 385 to 1024 rows, in row groups of 128: whole ones, one row more, the most a pass takes and what is left behind
-    it (1 row; 385), the row count from which o and down have room for fewer slices (512 | 513), a pass of two sequences."""
+    """Passes of 385 to 1024 rows: whole groups of 8 row tiles, one row more, the most a pass takes and what is left behind it (1 row;
+    385), the row count from which o and down have room for fewer slices (512 | 513), a pass of two sequences."""
     print(f"[case] width {width}, prefill of {lens}, paged {paged}", flush=True)
     nb, max_trunk, seed = len(lens), max(lens) + 2 * K + 8, 3 + sum(lens)
     shape = I.ModelShape(n_layers=2, d_model=width, n_q_heads=width // 64, n_kv_heads=width // 256, head_dim=64, d_ffn=2 * width, vocab=4112,
@@ -479,24 +479,45 @@ def test_captured_extend_of_few_rows_takes_the_wide_pass(B):
         B.ssd_model_destroy(model)
 
 
-# (width, d_ffn, prompt rows): gate/up takes another block at each, with whole and with partly filled row groups, and o and down
-# one, two, four and eight slices
+# (width, d_ffn, prompt rows): gate/up takes another block at each, with whole and with partly filled row groups, and o and down two, four
+# and eight slices
 BLOCK_PROMPTS = [(512, 8192, 20), (512, 8192, 32), (512, 8192, 64), (512, 8192, 65), (512, 8192, 96), (512, 8192, 128), (512, 8192, 190),
                  (512, 8192, 250), (512, 8192, 256), (512, 8192, 384), (512, 8192, 500), (512, 8192, 513), (512, 8192, 768), (512, 8192, 1000),
                  (2048, 2048, 300)]
+# (prompt rows, trunk positions) at the layers of the 1B shape: every block and number of slices that qkv, o, gate/up and down of a wide
+# pass take there, row groups whole and partly filled (the trunk's room decides how many rows of partial sums o and down may write)
+BLOCK_PROMPTS_1B = [(58, 0), (64, 0), (74, 0), (128, 0), (160, 0), (256, 0), (384, 0), (450, 1100), (490, 0), (512, 0), (700, 0), (768, 0),
+                    (1003, 0)]
+# prompt rows at a width of 2048 under 64 query and 16 KV heads and a d_ffn of 512: larger blocks of qkv, o and down in one slice
+BLOCK_PROMPTS_64_HEADS = [500, 900, 1003]
 # (vocabulary, sequences, F) with K = 2: the LM head's blocks, the last of them with features behind the vocabulary
-BLOCK_ROUNDS = [(66016, 16, 3), (66016, 16, 4), (66016, 16, 6), (66016, 16, 8), (20016, 16, 8), (4112, 11, 3), (4112, 16, 8)]
+BLOCK_ROUNDS = [(66016, 16, 3), (66016, 16, 4), (66016, 16, 6), (66016, 16, 8), (20016, 16, 8), (4112, 11, 3), (4112, 16, 8),
+                (2000, 5, 7), (2592, 14, 8), (5552, 11, 8), (8512, 13, 8), (10288, 11, 8), (32784, 9, 8), (128256, 14, 5)]
 
 
-@pytest.mark.parametrize("width,ffn,rows", BLOCK_PROMPTS)
-def test_blocks_of_prompt_passes(B, width, ffn, rows):
-    """Every block that the linear layers of wide passes are cut into, against the narrow passes' own kernels."""
-    print(f"[case] width {width}, d_ffn {ffn}, {rows} rows", flush=True)
-    max_trunk, seed, lens = rows + 2 * K + 8, 5 + rows, [rows]
-    shape = I.ModelShape(n_layers=2, d_model=width, n_q_heads=width // 64, n_kv_heads=2, head_dim=64, d_ffn=ffn, vocab=4112, dtype="bf16",
-                         rope_theta=500000.0, tie_embeddings=True)
-    model = B.ssd_model_create(shape, I.make_weights(shape, 17))
-    prompt = dev_i32(I.make_prompt(shape, 1, rows, seed))
+def _layer_shape(q_heads, kv_heads, ffn):
+    return I.ModelShape(n_layers=2, d_model=2048, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=64, d_ffn=ffn, vocab=4112, dtype="bf16",
+                        rope_theta=500000.0, tie_embeddings=True)
+
+
+@pytest.fixture(scope="module")
+def layer_models(B):
+    """Models of two layers of width 2048, made once per shape."""
+    made = {}
+
+    def model_of(*sizes):
+        if sizes not in made:
+            shape = _layer_shape(*sizes)
+            made[sizes] = (shape, B.ssd_model_create(shape, I.make_weights(shape, 17)))
+        return made[sizes]
+    yield model_of
+    for _, model in made.values():
+        B.ssd_model_destroy(model)
+
+
+def _compare_with_narrow_chunks(B, shape, model, rows, max_trunk):
+    """One prompt in a wide pass against the narrow passes' own kernels."""
+    prompt, lens = dev_i32(I.make_prompt(shape, 1, rows, 5 + rows)), [rows]
     ctxs = [B.ssd_ctx_create(model, 1, K, F, max_trunk, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
     try:
         got = []
@@ -511,6 +532,30 @@ def test_blocks_of_prompt_passes(B, width, ffn, rows):
     finally:
         for ctx in ctxs:
             B.ssd_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("rows,trunk", BLOCK_PROMPTS_1B)
+def test_blocks_of_prompt_passes_at_the_1b_layers(B, layer_models, rows, trunk):
+    print(f"[case] 1B layers, {rows} rows, trunk {trunk}", flush=True)
+    _compare_with_narrow_chunks(B, *layer_models(32, 8, 8192), rows, trunk or rows + 2 * K + 8)
+
+
+@pytest.mark.parametrize("rows", BLOCK_PROMPTS_64_HEADS)
+def test_blocks_of_prompt_passes_under_64_heads(B, layer_models, rows):
+    print(f"[case] 64 heads, {rows} rows", flush=True)
+    _compare_with_narrow_chunks(B, *layer_models(64, 16, 512), rows, rows + 2 * K + 8)
+
+
+@pytest.mark.parametrize("width,ffn,rows", BLOCK_PROMPTS)
+def test_blocks_of_prompt_passes(B, width, ffn, rows):
+    """Every block that the linear layers of wide passes are cut into, against the narrow passes' own kernels."""
+    print(f"[case] width {width}, d_ffn {ffn}, {rows} rows", flush=True)
+    shape = I.ModelShape(n_layers=2, d_model=width, n_q_heads=width // 64, n_kv_heads=2, head_dim=64, d_ffn=ffn, vocab=4112, dtype="bf16",
+                         rope_theta=500000.0, tie_embeddings=True)
+    model = B.ssd_model_create(shape, I.make_weights(shape, 17))
+    try:
+        _compare_with_narrow_chunks(B, shape, model, rows, rows + 2 * K + 8)
+    finally:
         B.ssd_model_destroy(model)
 
 

@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from tests.test_gpu_prefill import BLOCK_PROMPTS, BLOCK_ROUNDS
+from tests.test_gpu_prefill import BLOCK_PROMPTS, BLOCK_PROMPTS_1B, BLOCK_PROMPTS_64_HEADS, BLOCK_ROUNDS, K
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2603_03251_amd", "csrc")
 NWG, SLICES, ROUND_ROWS, PROMPT_ROWS = 256, 8, 384, 1024
@@ -94,10 +94,31 @@ def test_blocks_that_are_not_compiled_would_not_be_taken(lib):
     assert taken == {(layer, i) for layer in ("qkv", "o", "down", "gate/up") for i in range(lib.count(layer == "gate/up", 0))}
 
 
-def test_the_gpu_test_reaches_every_block(lib):
+def _reached(lib):
+    """(layer, block, slices) of the prompt passes that the GPU tests compare."""
     seen = set()
     for width, ffn, rows in BLOCK_PROMPTS:
-        seen.add(_choose(lib, 2 * ffn // 16, width // 32, rows, NWG, lib.count(1, 0), 0, width)[0])
-    assert seen == set(range(lib.count(1, 0))), seen
-    heads = {_choose(lib, (vocab + 63) // 64 * 4, 512 // 32, nb * 3 * F, NWG, ANY, 0, 512)[0] for vocab, nb, F in BLOCK_ROUNDS}
-    assert lib.count(0, 1) - 1 in heads and len(heads) >= 4, heads
+        seen |= _prompt_choices(lib, (width, width // 64, 2, ffn), rows, rows + 2 * K + 8)
+    for rows, trunk in BLOCK_PROMPTS_1B:
+        seen |= _prompt_choices(lib, (2048, 32, 8, 8192), rows, trunk or rows + 2 * K + 8)
+    for rows in BLOCK_PROMPTS_64_HEADS:
+        seen |= _prompt_choices(lib, (2048, 64, 16, 512), rows, rows + 2 * K + 8)
+    return seen
+
+
+def test_the_gpu_tests_reach_what_the_1b_shape_takes(lib):
+    """All wide passes of its layers, in contexts of every room (up to 48 rows are passes of another kind)."""
+    wanted = set()
+    for rows in range(49, 1025):
+        for room_rows in {rows, max(rows, 300), max(rows, 384), max(rows, 385), max(rows, 512), max(rows, 700), 1024}:
+            wanted |= _prompt_choices(lib, (2048, 32, 8, 8192), rows, room_rows)
+    assert len(wanted) > 30 and wanted <= _reached(lib), wanted - _reached(lib)
+
+
+def test_the_gpu_tests_reach_every_block(lib):
+    seen = _reached(lib)
+    for layers in (("qkv",), ("o", "down"), ("gate/up",)):        # (o and down share their kernels)
+        assert {block for at, block, _ in seen if at in layers} == set(range(lib.count(layers[0] == "gate/up", 0))), layers
+    assert {S for _, _, S in seen} == {1, 2, 4, 8}
+    heads = {_choose(lib, (vocab + 63) // 64 * 4, 512 // 32, nb * 3 * F, NWG, ANY, 0, 512)[0] for vocab, nb, F in BLOCK_ROUNDS if nb * 3 * F > 96}
+    assert heads == set(range(lib.count(0, 1))), heads
