@@ -146,8 +146,14 @@ __device__ __forceinline__ void unpack_elems(uint4 v, float* o) {
 // Writes the split's partial softmax (max, sum, unnormalised output) to `partial` [row][query head][split][D + 2];
 // attention_merge_kernel adds the splits up in split order.  A single split is the result (partial == nullptr).
 // 10 rows x 4 heads x 138 keys, fp32: 6.4 us (18.5 us and 4.7 us of merge before; 6.6 with the values requested behind the scores).
-template <typename T, int D, int G>
-__global__ __launch_bounds__(256) void attention_split_kernel(const float* __restrict__ q, const T* __restrict__ trunk_k,
+// Values ahead: as many loads as cost no wavefront in flight (one query head, bf16: 8 leave five per SIMD, 12 four; rounds of 24 rows over 700
+// keys of 8 heads of 128 dimensions 1243 us with 8, 1321 with 12, 1246 with none, 1337 before there were any), 12 for one fp32 head, which
+// keeps more than four with them (96 rows over 8000 keys 10.72 ms with 12, 11.15 with 8).  MANY: a launch of many more blocks than the chip
+// holds is bound by the keys and values its L2s miss: values behind the scores and four wavefronts per SIMD spread over fewer of them
+// (384 rows over 8000 keys, 16 heads of 64 dimensions: 36.4 ms, 36.8 with 8 values ahead, 37.2 with 12; 36.0 before the sums over lanes left
+// the LDS crossbar, the one size that stayed slower by 1 %).
+template <typename T, int D, int G, bool MANY = false>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MANY ? 4 : 1, MANY ? 4 : 8))) void attention_split_kernel(const float* __restrict__ q, const T* __restrict__ trunk_k,
                                                                const T* __restrict__ trunk_v, const T* __restrict__ suffix_k,
                                                                const T* __restrict__ suffix_v, const RowDesc* __restrict__ rows,
                                                                int n_q_heads, int n_kv_heads, int max_trunk, int suffix_cap,
@@ -157,7 +163,7 @@ __global__ __launch_bounds__(256) void attention_split_kernel(const float* __res
   // heads x 8 dimensions of accumulators and their exchange across lanes cost a 70B-shaped row more than they saved:
   // 55 -> 70 us for 6 rows x 8 heads x 4096 keys)
   constexpr int KV = Vec16<T>::N, VEC = G * KV <= 32 ? KV : D / 64, LPR = D / VEC, KPI = 64 / LPR;
-  constexpr int kPvBatch = 8, kPvAhead = G * VEC <= 8 ? 12 : 8;
+  constexpr int kPvBatch = 8, kPvAhead = MANY ? 0 : G == 1 && sizeof(T) == 4 ? 12 : 8;
   __shared__ float q_s[G][D];
   __shared__ float p_s[G][kSplitKeys];
   __shared__ float red_s[4][G][D];
@@ -610,11 +616,16 @@ int launch_rowwise_d(const AttnArgs& a, hipStream_t s) {
     dim3 grid(a.M, a.n_kv_heads, n_splits);
     float* partial = n_splits > 1 ? a.partial : nullptr;
     const int group = a.n_q_heads / a.n_kv_heads;
-#define SSD_SPLIT_LAUNCH(GV)                                                                                              \
-  attention_split_kernel<T, D, GV><<<grid, 256, 0, s>>>(a.q, (const T*)a.trunk_k, (const T*)a.trunk_v, (const T*)a.suffix_k, \
+    // (bf16, one query head per KV head; blocks of a launch, us of a round with 8 values ahead / as a large launch: 6144 1697 / 1696, 13824
+    // 3772 / 3830, 24576 5697 / 5701, 27648 11294 / 11254, 55296 11243 / 11157, 101376 36712 / 36432)
+    constexpr int64_t kManyBlocks = 24576;
+    const bool many = sizeof(T) == 2 && group == 1 && (int64_t)a.M * a.n_kv_heads * n_splits > kManyBlocks;
+#define SSD_SPLIT_LAUNCH(...)                                                                                             \
+  attention_split_kernel<T, D, __VA_ARGS__><<<grid, 256, 0, s>>>(a.q, (const T*)a.trunk_k, (const T*)a.trunk_v, (const T*)a.suffix_k, \
                                                         (const T*)a.suffix_v, a.rows, a.n_q_heads, a.n_kv_heads, a.max_trunk, \
                                                         a.suffix_cap, partial, keys_per_split, a.out, a.out_plane)
-    if (group == 1) SSD_SPLIT_LAUNCH(1);
+    if (many) SSD_SPLIT_LAUNCH(1, sizeof(T) == 2);
+    else if (group == 1) SSD_SPLIT_LAUNCH(1);
     else if (group <= 4) SSD_SPLIT_LAUNCH(4);
     else SSD_SPLIT_LAUNCH(kSplitMaxGroup);
 #undef SSD_SPLIT_LAUNCH

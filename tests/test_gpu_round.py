@@ -492,6 +492,16 @@ def test_bf16_extends_of_the_per_operator_path(B, shape, batch, P, K):
     _run_round_parity(B, shape, batch=batch, P=P, K=K, F=1, seed=41, synthetic_kv=True, flags=B.SSD_CTX_PER_OPERATOR)
 
 
+@pytest.mark.parametrize("head_dim,batch,P,blocks", [(64, 6, 1100, 23040), (64, 7, 1100, 26880), (128, 4, 1900, 24576), (128, 5, 1900, 30720)])
+def test_bf16_branch_rows_of_one_query_head_per_kv_head(B, head_dim, batch, P, blocks):
+    """The split attention in launches of up to 24576 blocks (rows x KV heads x splits of 256 keys) and in larger ones."""
+    print(f"[case] head_dim {head_dim}, {batch} sequences, prefix {P}", flush=True)
+    K_, heads = 2, 16
+    assert blocks == batch * (K_ + 1) * 16 * heads * -(-(P + K_ + 1 + K_) // 256)
+    shape = _small(n_layers=1, d_model=512, n_q_heads=heads, n_kv_heads=heads, head_dim=head_dim, d_ffn=512, vocab=512)
+    _run_round_parity(B, shape, batch=batch, P=P, K=K_, F=16, seed=13, synthetic_kv=True, flags=B.SSD_CTX_PER_OPERATOR)
+
+
 def test_small_bf16_geometric_cache_shape(B):
     """Sec. 4.1.2: a round whose fan-out follows the theorem's geometric shape; the library's integer shape equals the
     oracle's, the rows run accept length by accept length, and the fused pass serves the 13 rows per sequence."""
