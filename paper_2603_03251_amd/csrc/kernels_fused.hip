@@ -1245,6 +1245,9 @@ __device__ __forceinline__ void attn_merge_unit(const FusedParams& p, int mt, in
 // row where they had to add up partial sums of squares.
 constexpr int kWideThreads = 256, kWideWaves = 4;
 
+// k-tiles of a layer's reduction dimension
+__host__ __device__ __forceinline__ int wide_k_tiles(const FusedGemm& g) { return g.KS * kFusedWaves * g.KTW; }
+
 struct WideEpi {
   float* out;          // QKV: [M][ld] projections, row scale applied; LOGITS: [M][ld] logits; PART: [slice][M][ld] partial sums
   int64_t ld;
@@ -1288,7 +1291,7 @@ __global__ __launch_bounds__(TH) void wide_block_kernel(FusedParams p, FusedGemm
   extern __shared__ f32x4 lds[];                             // [NB][NTILE][64], the rows' 1/rms, then (G > 1) partial tiles
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = wave / WG, wn = wave % WG % WN, wm = wave % WG / WN;
-  const int NKT = g.KS * kFusedWaves * g.KTW;                // k-tiles of the reduction dimension
+  const int NKT = wide_k_tiles(g);
   const int S = EPI == FE_PART ? e.S : 1, steps = NKT / (S * G);   // (even: host check)
   const int n_groups = g.n_units / g.KS;                     // units of ATW feature tiles
   const int n_sets = (n_groups * ATW + FT - 1) / FT;
@@ -1448,6 +1451,166 @@ __global__ __launch_bounds__(TH) void wide_block_kernel(FusedParams p, FusedGemm
   stamp(p, e.ph, 2);
 }
 
+// The linear layers of the narrowest wide passes: few rows over a short reduction dimension, where the k-tiles of wide_block_kernel's
+// steps (0.2 us each) and its two trips to memory outlast the work.  A workgroup takes 4 feature tiles x a group of MTG row tiles over one of
+// S slices; its four wavefronts, one per SIMD, split the slice, stream their weight tiles and the matching activation tiles into a ring of D
+// register chunks, D - 1 of them in flight, and meet once, in LDS, where the partial tiles are added in wavefront order.  MTG = 2: 32x32x16
+// MFMAs on operands kept in 16x16x32 tile order, see wide_tile_kernel.
+// Graphs of 16 layers of width 512, us, against the blocks alone and the kernels before them: 20 rows 509, 576, 508; 48 rows 560, 592, 564.
+template <int ATW, int EPI, int D, int MTG>
+__global__ __launch_bounds__(kWideThreads) void wide_few_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
+  constexpr int MTOT = kFusedWideRows / 16, NT = 4 * MTG;  // 1 KiB blocks of a wavefront's partial tiles
+  constexpr bool BIG = MTG == 2;
+  extern __shared__ f32x4 red[];
+  __shared__ float r_s[kFewRows];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int NKT = wide_k_tiles(g);
+  const int S = EPI == FE_PART ? e.S : 1;
+  const int NCH = NKT / (kWideWaves * S);           // k-tiles of this wavefront per pair (a multiple of D: host check)
+  const int n_groups = g.n_units / g.KS;
+  const int nq = ATW == 4 ? n_groups : n_groups >> 1;
+  const int n_rg = (((p.M + 15) >> 4) + MTG - 1) / MTG;
+  // the pairs of this workgroup: as in wide_block_kernel
+  const int x = (int)blockIdx.x & 7, wx = (int)blockIdx.x >> 3, per_xcd = (int)gridDim.x >> 3;
+  const int slice = x % S, y = x / S, ys = 8 / S;
+  const int nqy = y < nq ? (nq - y + ys - 1) / ys : 0;
+  const int ty = nqy * n_rg;
+  const int n_my = wx < ty ? (ty - wx + per_xcd - 1) / per_xcd : 0;
+  stamp(p, e.ph, 0);
+  if (n_my == 0) return;
+
+  // operand vector of this lane in a tile (BIG: in two neighbouring tiles, k-half 0; k-half 1 is 32 vectors further)
+  const int lsrc = BIG ? ((lane >> 4) & 1) * 64 + (lane & 15) + ((lane >> 5) << 4) : lane;
+  const int64_t a_group2 = (int64_t)NKT * 2 * 512;  // ATW == 2: from the set's first tile group to its second
+  const int kt0 = (slice * kWideWaves + wave) * NCH;
+  // the load cursor walks the chunks of this wavefront, pair after pair (behind the last: the last one again)
+  const bf16_t *src_a = nullptr, *src_b = nullptr;
+  int ld_i = 0, ld_n = 0;
+  auto place = [&]() {
+    const int t = wx + min(ld_n, n_my - 1) * per_xcd, qh = t / n_rg;
+    const int q = qh * ys + y, rg = t - qh * n_rg;
+    src_a = g.w + ((int64_t)(ATW == 4 ? q : 2 * q) * NKT + kt0) * ATW * 512;
+    src_b = bsrc + ((int64_t)kt0 * MTOT + rg * MTG) * 512;
+  };
+  struct Chunk { bf16x8 a[4], b[MTG]; };
+  auto load = [&](Chunk& ck, int l) {
+    const gbf16x8* ap = (const gbf16x8*)(ATW == 4 || l < 2 ? src_a : src_a + a_group2) + lsrc;
+    const gbf16x8* bp = (const gbf16x8*)src_b + lsrc;
+    // BIG: a[2 f + h] features 32 f .. 32 f + 31 of the set, k-half h; b[h] k-half h
+    if (l < 4) ck.a[l] = ap[(ATW == 4 ? (l >> 1) * 128 : 0) + (l & 1) * (BIG ? 32 : 64)];
+    else ck.b[l - 4] = bp[(l - 4) * (BIG ? 32 : 64)];
+  };
+  auto advance = [&]() {
+    src_a += ATW * 512;
+    src_b += MTOT * 512;
+    if (++ld_i == NCH) {
+      ld_i = 0;
+      ++ld_n;
+      place();
+    }
+  };
+  f32x16 accb[2];
+  f32x4 acc[4][MTG];
+  auto zero_acc = [&]() {
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) accb[f][i] = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int t = 0; t < MTG; ++t) acc[j][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  };
+  zero_acc();
+  // the rows' 1/rms: requested first, in LDS under the ring's loads, read behind the barrier
+  float rs = 0.f;
+  if (EPI != FE_PART) rs = ((const gfloat*)p.ssq)[min((int)threadIdx.x, p.M - 1)];
+  Chunk ring[D];
+  place();
+#pragma unroll
+  for (int s = 0; s < D - 1; ++s) {
+#pragma unroll
+    for (int l = 0; l < 4 + MTG; ++l) load(ring[s], l);
+    advance();
+  }
+  if (EPI != FE_PART && threadIdx.x < kFewRows) r_s[threadIdx.x] = rs;
+  stamp(p, e.ph, 3);
+  // a chunk's loads between the MFMAs of the one before (a burst of them would hold the wavefront up)
+  constexpr int NM = BIG ? 4 : 4 * MTG, NL = 4 + MTG;
+  auto turn = [&](const Chunk& ck, Chunk& to) {
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      if constexpr (BIG) accb[i & 1] = mfma32_f16(ck.a[2 * (i & 1) + (i >> 1)], ck.b[i >> 1], accb[i & 1]);
+      else acc[i / MTG][i % MTG] = mfma16_f16(ck.a[i / MTG], ck.b[i % MTG], acc[i / MTG][i % MTG]);
+#pragma unroll
+      for (int l = i * NL / NM; l < (i + 1) * NL / NM; ++l) load(to, l);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    advance();
+  };
+  for (int n = 0; n < n_my; ++n) {
+    const int t = wx + n * per_xcd;
+    const int q = (t / n_rg) * ys + y, rg = t - (t / n_rg) * n_rg;
+    for (int c = 0; c < NCH; c += D) {
+#pragma unroll
+      for (int s = 0; s < D; ++s) turn(ring[s], ring[(s + D - 1) % D]);
+    }
+    if (n == 0) stamp(p, e.ph, 4);
+    // ---- the four wavefronts' partial tiles meet; every wavefront sums its share of the blocks and runs their epilogue.  Block idx: BIG
+    // (f, c) = registers 4 c .. 4 c + 3 of accb[f]: features 32 f + 8 c + 4 (lane >> 5) .. + 3, row lane & 31; else (j, t): features 16 j + 4
+    // (lane >> 4) .. + 3, row 16 t + (lane & 15)
+    if constexpr (BIG) {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        const f32x16& v = accb[i >> 2];
+        const int c = (i & 3) * 4;
+        red[(wave * NT + i) * 64 + lane] = (f32x4){v[c], v[c + 1], v[c + 2], v[c + 3]};
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NT; ++i) red[(wave * NT + i) * 64 + lane] = acc[i / MTG][i % MTG];
+    }
+    wg_barrier();
+    auto total = [&](int idx) {
+      f32x4 v = red[idx * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < kWideWaves; ++w) v += red[(w * NT + idx) * 64 + lane];
+      return v;
+    };
+    auto feature_of = [&](int idx) { return BIG ? (idx >> 2) * 32 + (idx & 3) * 8 + (lane >> 5) * 4 : (idx / MTG) * 16 + (lane >> 4) * 4; };
+    auto row_of = [&](int idx) { return rg * MTG * 16 + (BIG ? lane & 31 : (idx % MTG) * 16 + (lane & 15)); };
+    if constexpr (EPI == FE_SWIGLU) {
+      // features 0..31 of the set are gate, 32..63 the matching up features: blocks idx and idx + NT / 2
+      for (int idx = wave; idx < NT / 2; idx += kWideWaves) {
+        const f32x4 gv = total(idx), uv = total(idx + NT / 2);
+        const int m = row_of(idx);
+        if (m < p.M) {
+          const float rs = r_s[m];
+          bf16_t hi[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float gg = gv[i] * rs, uu = uv[i] * rs;
+            hi[i] = to_f16(gg / (1.0f + __expf(-gg)) * uu);
+          }
+          // input index of the down-projection
+          *(uint64_t*)(e.act_out + b_off<MTOT>(q * 32 + feature_of(idx), m)) = pack_bf16x4(hi[0], hi[1], hi[2], hi[3]);
+        }
+      }
+    } else {
+      float* out = e.out + (int64_t)slice * p.M * e.ld;
+      for (int idx = wave; idx < NT; idx += kWideWaves) {
+        const f32x4 v = total(idx);
+        const int m = row_of(idx), n0 = q * 64 + feature_of(idx);
+        if ((n0 >> 4) < g.NT && m < p.M) *(gf32x4*)((gfloat*)out + (int64_t)m * e.ld + n0) = EPI == FE_PART ? v : v * r_s[m];
+      }
+    }
+    wg_barrier();
+    zero_acc();
+    if (n == 0) stamp(p, e.ph, 5);
+  }
+  stamp(p, e.ph, 2);
+}
+
 // The residual stream of a wide pass: a workgroup per row.  EMBED: h = the token's embedding; otherwise h += the row's partial sums of
 // the linear layer before, slice after slice.  Then (h * gain) as the fp16 B operand of the next linear layer (8 consecutive
 // features per thread are one lane's 16 bytes of it), the row's 1/rms, which that layer's epilogue multiplies in, and, where
@@ -1570,7 +1733,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_tile_kernel(FusedParams p, 
   static_assert(kTileRing == 2 * KC && 2 * ((BL + KC - 1) / KC) <= NM && NF + 1 < NM, "a turn of the ring is two stages; memory operations between MFMAs");
   extern __shared__ f32x4 lds[];                     // [2][KC][RT][64] B-operand vectors
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int NKT = g.KS * kFusedWaves * g.KTW;        // k-tiles of the reduction dimension
+  const int NKT = wide_k_tiles(g);
   const int NST = NKT / KC;                          // stages per set (even: host check)
   const int n_groups = g.n_units;                    // units of ATW feature tiles
   const int n_sets = (n_groups + 3) / 4;
@@ -2556,8 +2719,6 @@ int check_residency_pl(int nwg, int cus, int kt) {
   return check_residency_kt<8, PL, PG>(nwg, cus);
 }
 
-int wide_k_tiles(const FusedGemm& g) { return g.KS * kFusedWaves * g.KTW; }
-
 template <int ATW, int EPI, int FT, int RT, int WN, int G, int NB, int TH>
 int launch_wide_block_of(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
   constexpr int kLds = (NB * G * (FT + RT) + (G - 1) * FT * RT) * 1024 + kFusedPromptRows * 4;
@@ -2572,16 +2733,22 @@ int launch_wide_block_of(const FusedParams& p, const FusedGemm& g, const bf16_t*
   return SSD_OK;
 }
 
+template <int EPI> constexpr int kBlocksOf = EPI == FE_LOGITS ? kNumWideBlocks : EPI == FE_SWIGLU ? kGateUpBlocks : kLayerBlocks;
+// The blocks a linear layer of the pass is cut into
+template <int ATW, int EPI>
+WideChoice wide_choice(const FusedParams& p, const FusedGemm& g) {
+  return choose_wide_block(g.n_units / g.KS * ATW, wide_k_tiles(g), p.M, p.nwg, kBlocksOf<EPI>, kFusedWideSlices,
+                           EPI == FE_PART ? p.fix_stride : 0, p.d);
+}
+
 // One linear layer of a wide pass in the blocks chosen for it; e.S = the k-slices (PART).  Four wavefronts where their share of a block
 // fits their registers, eight for more (and for 8 x 8 and 8 x 12: 25.2 against 26.1 and 22.5 against 22.6 us); buffers: five or six are as
 // good as more (96 rows of gate/up 18.0 us with six, 18.3 with eight, 20 with sixteen).  Two groups of wavefronts where a block is small and
 // its steps many: qkv of 96 rows 10.3 us in blocks of 4 x 2, 11.3 with one; gate/up of 96 rows (4 x 6) 19.6, 18.4 with one.
 template <int ATW, int EPI>
-int launch_wide_block(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
+int launch_wide_block(const WideChoice& c, const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
+  constexpr int kBlocks = kBlocksOf<EPI>;
   constexpr bool kSlices = EPI == FE_PART;
-  constexpr int kBlocks = EPI == FE_LOGITS ? kNumWideBlocks : EPI == FE_SWIGLU ? kGateUpBlocks : kLayerBlocks;
-  const WideChoice c = choose_wide_block(g.n_units / g.KS * ATW, wide_k_tiles(g), p.M, p.nwg, kBlocks, kFusedWideSlices,
-                                         kSlices ? p.fix_stride : 0, p.d);
   e.S = c.S;
   switch (c.block) {
     case 0: return launch_wide_block_of<ATW, EPI, 4, 2, 2, kSlices ? 1 : 2, 6, 256>(p, g, bsrc, e, s);
@@ -2599,6 +2766,39 @@ int launch_wide_block(const FusedParams& p, const FusedGemm& g, const bf16_t* bs
     if (c.block == 9) return launch_wide_block_of<ATW, EPI, 16, 16, 2, 1, 4, 512>(p, g, bsrc, e, s);
   }
   if constexpr (kBlocks > 10) return launch_wide_block_of<ATW, EPI, 16, 6, 4, 1, 5, 256>(p, g, bsrc, e, s);
+  return SSD_EINVAL;
+}
+
+template <int ATW, int EPI, int D, int MTG>
+int launch_wide_few_of(const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
+  SSD_CHECK_ARG(p.M <= kFewRows && p.row_tiles == kFusedWideRows / 16 && wide_k_tiles(g) % (kWideWaves * e.S * D) == 0 &&
+                    (ATW == 4 || g.n_units / g.KS % 2 == 0), "wide pass: layer does not cut into sets");
+  wide_few_kernel<ATW, EPI, D, MTG><<<p.nwg, kWideThreads, kWideWaves * 4 * MTG * 1024, s>>>(p, g, bsrc, e);
+  SSD_HIP(hipGetLastError());
+  return SSD_OK;
+}
+template <int EPI, int MTG>
+int launch_wide_few(const FewChoice& c, const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, const WideEpi& e, hipStream_t s) {
+  constexpr int ATW = EPI == FE_SWIGLU ? 4 : 2;
+  return c.depth == 8 ? launch_wide_few_of<ATW, EPI, 8, MTG>(p, g, bsrc, e, s) : launch_wide_few_of<ATW, EPI, 4, MTG>(p, g, bsrc, e, s);
+}
+
+// How the layers of a pass are cut (the layers of a model have one shape: once per pass; 0.2 us of the host per layer, and passes of narrow
+// models wait for the host), and one of them launched; e.S = the k-slices (o and down).
+struct WideCut { WideChoice block; FewChoice few; };
+template <int EPI>
+WideCut wide_cut(const FusedParams& p, const FusedGemm& g) {
+  constexpr int ATW = EPI == FE_SWIGLU ? 4 : 2;
+  constexpr FewLayer kLayer = EPI == FE_SWIGLU ? FEW_GATE_UP : EPI == FE_PART ? FEW_PART : FEW_QKV;
+  return {wide_choice<ATW, EPI>(p, g), choose_wide_few(kLayer, g.n_units / g.KS * ATW, wide_k_tiles(g), p.M, p.nwg, kFusedWideSlices, p.fix_stride)};
+}
+template <int EPI>
+int launch_wide_layer(const WideCut& c, const FusedParams& p, const FusedGemm& g, const bf16_t* bsrc, WideEpi& e, hipStream_t s) {
+  if (c.few.depth == 0) return launch_wide_block<EPI == FE_SWIGLU ? 4 : 2, EPI>(c.block, p, g, bsrc, e, s);
+  e.S = c.few.S;
+  if constexpr (EPI != FE_SWIGLU)
+    if (c.few.mtg == 1) return launch_wide_few<EPI, 1>(c.few, p, g, bsrc, e, s);
+  if constexpr (EPI != FE_QKV) return c.few.mtg == 2 ? launch_wide_few<EPI, 2>(c.few, p, g, bsrc, e, s) : launch_wide_few<EPI, 3>(c.few, p, g, bsrc, e, s);
   return SSD_EINVAL;
 }
 
@@ -2623,7 +2823,7 @@ int launch_wide_attn(const FusedParams& p, const FusedLayer& L, int ph, hipStrea
 // LM head.  Up to 96 rows it is a stream of weights, each read once, which goes faster straight into registers and past the caches
 // (96 rows 109 us, 117 in blocks of 256 features x 96 rows).
 int launch_wide_logits(const FusedParams& p, WideEpi& e, hipStream_t s) {
-  if (p.M > kTileRows) return launch_wide_block<4, FE_LOGITS>(p, p.lm, p.xn, e, s);
+  if (p.M > kTileRows) return launch_wide_block<4, FE_LOGITS>(wide_choice<4, FE_LOGITS>(p, p.lm), p, p.lm, p.xn, e, s);
   SSD_CHECK_ARG(p.lm.KS == 1 && wide_k_tiles(p.lm) % kTileRing == 0, "wide pass: the LM head does not cut into tiles");
   constexpr int kLds = 2 * kTileStage * kTileRows / 16 * 1024;
   wide_tile_kernel<<<p.nwg, kWideThreads, kLds, s>>>(p, p.lm, p.xn, e);
@@ -2660,6 +2860,9 @@ int launch_wide_resid(const FusedParams& p, bool embed, const float* part, int S
 template <class PL, bool PG>
 int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int first, int last, hipStream_t s) {
   const int lm_phase = fused_last_phase(p.L);
+  const FusedLayer& any = layers_host[0];
+  const WideCut cut_qkv = wide_cut<FE_QKV>(p, any.qkv), cut_o = wide_cut<FE_PART>(p, any.o), cut_gu = wide_cut<FE_SWIGLU>(p, any.gu),
+                cut_down = wide_cut<FE_PART>(p, any.down);
   for (int ph = first; ph <= last; ++ph) {
     if (ph == 0) {
       SSD_TRY(launch_wide_resid(p, true, nullptr, 0, layers_host[0].attn_norm, nullptr, ph, s));
@@ -2679,16 +2882,16 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
     const FusedLayer& L = layers_host[l];
     if (sub == 0) {
       e.out = p.qkv; e.ld = p.qkvd;
-      SSD_TRY((launch_wide_block<2, FE_QKV>(p, L.qkv, p.xn, e, s)));
+      SSD_TRY(launch_wide_layer<FE_QKV>(cut_qkv, p, L.qkv, p.xn, e, s));
     } else if (sub == 3 || sub == 5) {
       e.out = p.fix_buf; e.ld = p.d;
-      SSD_TRY((launch_wide_block<2, FE_PART>(p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s)));
+      SSD_TRY(launch_wide_layer<FE_PART>(sub == 3 ? cut_o : cut_down, p, sub == 3 ? L.o : L.down, sub == 3 ? p.att : p.act, e, s));
       const bool fin = sub == 5 && l + 1 == p.L;
       const bf16_t* gain = sub == 3 ? L.mlp_norm : (fin ? p.final_norm : layers_host[l + 1].attn_norm);
       SSD_TRY(launch_wide_resid(p, false, p.fix_buf, e.S, gain, fin ? p.hidden : nullptr, ph, s));
     } else if (sub == 4) {
       e.act_out = p.act;
-      SSD_TRY((launch_wide_block<4, FE_SWIGLU>(p, L.gu, p.xn, e, s)));
+      SSD_TRY(launch_wide_layer<FE_SWIGLU>(cut_gu, p, L.gu, p.xn, e, s));
     } else if (sub == 1) {
       if (p.appended) {
         wide_append_kernel<PG><<<(p.M * p.Hkv * 8 + 255) / 256, 256, 0, s>>>(p, L.trunk_k, L.trunk_vt);

@@ -30,6 +30,31 @@ constexpr int64_t wide_part_room(int64_t rows, int64_t round_rows, int max_slice
 
 struct WideChoice { int block, S; };
 
+// Layers that wide_few_kernel takes instead, over whole sets of 4 feature tiles: row tiles of a group, k-slices and chunks of its ring (0: it
+// does not).  Up to 48 rows all of qkv in one turn, and what is short enough of the others.  us that a pass of 8 layers gains (-) or loses
+// with it on that layer, blocks alone 268 to 413: width 512 (d_ffn 512, 2048, 8192; 4 to 48 rows) qkv -9 to -16, o -9 to +2, gate/up -12 to +1,
+// down -19 to 0; width 1024 (1024, 4096, 8192) qkv -3 to -12, o -9 to 0 up to 32 rows and -1 to +5 beyond, gate/up -9 to +1 at a d_ffn of 1024
+// and -2 to +12 above, down -12 to 0 up to 32 rows and -1 to +6 beyond; four layers of width 2048 (2048, 8192) qkv 0 to -8, o -6 to +4, gate/up
+// -3 to +6 and +9 to +13, down -6 to +4 and +1 to +3.
+constexpr int kFewRows = 48;
+enum FewLayer { FEW_QKV, FEW_PART, FEW_GATE_UP };
+struct FewChoice { int mtg, S, depth; };
+inline FewChoice choose_wide_few(FewLayer layer, int tiles, int k_tiles, int rows, int workgroups, int max_slices, int64_t room) {
+  const int row_tiles = (rows + 15) / 16, sets = (tiles + 3) / 4, work = sets * k_tiles;
+  if (rows > kFewRows || k_tiles % 16 != 0) return FewChoice{0, 1, 0};
+  int S = 1;
+  if (layer == FEW_QKV && sets * row_tiles > workgroups) return FewChoice{0, 1, 0};
+  if (layer == FEW_GATE_UP && k_tiles > 16 && sets > 64) return FewChoice{0, 1, 0};
+  if (layer == FEW_PART) {
+    if (work > (rows <= 32 ? 4096 : 2048)) return FewChoice{0, 1, 0};
+    for (S = max_slices; S > 1; S /= 2)                       // as many slices as leave every workgroup one pair
+      if (sets * S <= workgroups && (int64_t)S * rows <= room && k_tiles % (16 * S) == 0) break;
+  }
+  // qkv: a row tile per workgroup, so that more of them share the weights
+  const int mtg = layer == FEW_QKV || (layer == FEW_PART && row_tiles == 1) ? 1 : row_tiles <= 2 ? 2 : 3;
+  return FewChoice{mtg, S, k_tiles / (4 * S) % 8 == 0 ? 8 : 4};   // (a wavefront's quarter of a slice is whole turns of the ring)
+}
+
 // tiles: 16-feature tiles of the layer; k_tiles: of its reduction dimension; blocks: how many of the list it may take; room: rows of
 // partial sums there is memory for (0: no k-slices); out_width: features of such a row.
 inline WideChoice choose_wide_block(int tiles, int k_tiles, int rows, int workgroups, int blocks, int max_slices, int64_t room, int out_width) {

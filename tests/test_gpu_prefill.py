@@ -481,7 +481,7 @@ def test_captured_extend_of_few_rows_takes_the_wide_pass(B):
 
 # (width, d_ffn, prompt rows): gate/up takes another block at each, with whole and with partly filled row groups, and o and down two, four
 # and eight slices
-BLOCK_PROMPTS = [(512, 8192, 20), (512, 8192, 32), (512, 8192, 64), (512, 8192, 65), (512, 8192, 96), (512, 8192, 128), (512, 8192, 190),
+BLOCK_PROMPTS = [(512, 8192, 20), (512, 8192, 32), (512, 2048, 100), (512, 8192, 64), (512, 8192, 65), (512, 8192, 96), (512, 8192, 128), (512, 8192, 190),
                  (512, 8192, 250), (512, 8192, 256), (512, 8192, 384), (512, 8192, 500), (512, 8192, 513), (512, 8192, 768), (512, 8192, 1000),
                  (2048, 2048, 300)]
 # (prompt rows, trunk positions) at the layers of the 1B shape: every block and number of slices that qkv, o, gate/up and down of a wide
@@ -490,19 +490,22 @@ BLOCK_PROMPTS_1B = [(58, 0), (64, 0), (74, 0), (128, 0), (160, 0), (256, 0), (38
                     (1003, 0)]
 # prompt rows at a width of 2048 under 64 query and 16 KV heads and a d_ffn of 512: larger blocks of qkv, o and down in one slice
 BLOCK_PROMPTS_64_HEADS = [500, 900, 1003]
+# (width, query heads, KV heads, d_ffn, prompt rows): the kernel of passes of up to 48 rows, every instance of it and the first that is not
+FEW_ROW_PROMPTS = [(512, 8, 2, 8192, n) for n in (5, 16, 17, 32, 33, 48, 49)] + [(1024, 16, 4, 1024, n) for n in (16, 31, 48)] + [
+    (2048, 32, 8, 2048, 20), (2048, 32, 8, 8192, 48), (2048, 64, 16, 512, 48), (512, 8, 2, 512, 30)]
 # (vocabulary, sequences, F) with K = 2: the LM head's blocks, the last of them with features behind the vocabulary
 BLOCK_ROUNDS = [(66016, 16, 3), (66016, 16, 4), (66016, 16, 6), (66016, 16, 8), (20016, 16, 8), (4112, 11, 3), (4112, 16, 8),
                 (2000, 5, 7), (2592, 14, 8), (5552, 11, 8), (8512, 13, 8), (10288, 11, 8), (32784, 9, 8), (128256, 14, 5)]
 
 
-def _layer_shape(q_heads, kv_heads, ffn):
-    return I.ModelShape(n_layers=2, d_model=2048, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=64, d_ffn=ffn, vocab=4112, dtype="bf16",
+def _layer_shape(q_heads, kv_heads, ffn, width=2048):
+    return I.ModelShape(n_layers=2, d_model=width, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=64, d_ffn=ffn, vocab=4112, dtype="bf16",
                         rope_theta=500000.0, tie_embeddings=True)
 
 
 @pytest.fixture(scope="module")
 def layer_models(B):
-    """Models of two layers of width 2048, made once per shape."""
+    """Models of two layers, made once per shape."""
     made = {}
 
     def model_of(*sizes):
@@ -515,10 +518,10 @@ def layer_models(B):
         B.ssd_model_destroy(model)
 
 
-def _compare_with_narrow_chunks(B, shape, model, rows, max_trunk):
+def _compare_with_narrow_chunks(B, shape, model, rows, max_trunk, flags=0):
     """One prompt in a wide pass against the narrow passes' own kernels."""
     prompt, lens = dev_i32(I.make_prompt(shape, 1, rows, 5 + rows)), [rows]
-    ctxs = [B.ssd_ctx_create(model, 1, K, F, max_trunk, flags) for flags in (0, B.SSD_CTX_NARROW_PASSES)]
+    ctxs = [B.ssd_ctx_create(model, 1, K, F, max_trunk, f) for f in (flags, B.SSD_CTX_NARROW_PASSES)]
     try:
         got = []
         for ctx in ctxs:
@@ -538,6 +541,13 @@ def _compare_with_narrow_chunks(B, shape, model, rows, max_trunk):
 def test_blocks_of_prompt_passes_at_the_1b_layers(B, layer_models, rows, trunk):
     print(f"[case] 1B layers, {rows} rows, trunk {trunk}", flush=True)
     _compare_with_narrow_chunks(B, *layer_models(32, 8, 8192), rows, trunk or rows + 2 * K + 8)
+
+
+@pytest.mark.parametrize("width,heads,kv_heads,ffn,rows", FEW_ROW_PROMPTS)
+def test_wide_passes_of_few_rows(B, layer_models, width, heads, kv_heads, ffn, rows):
+    """(One launch per phase: a context that may launch the persistent kernel takes that for so few rows from a width of 1024 on.)"""
+    print(f"[case] width {width}, {heads} heads, d_ffn {ffn}, {rows} rows", flush=True)
+    _compare_with_narrow_chunks(B, *layer_models(heads, kv_heads, ffn, width), rows, rows + 2 * K + 8, B.SSD_CTX_FUSED_PHASES)
 
 
 @pytest.mark.parametrize("rows", BLOCK_PROMPTS_64_HEADS)

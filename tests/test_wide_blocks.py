@@ -6,7 +6,7 @@ import subprocess
 
 import pytest
 
-from tests.test_gpu_prefill import BLOCK_PROMPTS, BLOCK_PROMPTS_1B, BLOCK_PROMPTS_64_HEADS, BLOCK_ROUNDS, K
+from tests.test_gpu_prefill import BLOCK_PROMPTS, BLOCK_PROMPTS_1B, BLOCK_PROMPTS_64_HEADS, BLOCK_ROUNDS, FEW_ROW_PROMPTS, K
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2603_03251_amd", "csrc")
 NWG, SLICES, ROUND_ROWS, PROMPT_ROWS = 256, 8, 384, 1024
@@ -21,6 +21,8 @@ def lib(tmp_path_factory):
                    'extern "C" int choose(int tiles, int kt, int rows, int nwg, int blocks, int slices, long long room, int width) {\n'
                    '  const auto c = choose_wide_block(tiles, kt, rows, nwg, blocks < kNumWideBlocks ? blocks : kNumWideBlocks, slices, room, width);\n'
                    '  return c.block * 16 + c.S; }\n'
+                   'extern "C" int few(int layer, int tiles, int kt, int rows, int nwg, int slices, long long room) {\n'
+                   '  const auto c = choose_wide_few((FewLayer)layer, tiles, kt, rows, nwg, slices, room); return c.depth ? (c.mtg * 16 + c.S) * 16 + c.depth : 0; }\n'
                    'extern "C" int count(int gate_up, int head) { return head ? kNumWideBlocks : gate_up ? kGateUpBlocks : kLayerBlocks; }\n'
                    'extern "C" long long room(long long rows) { return wide_part_room(rows, %d, %d); }\n'
                    'extern "C" int tile(int i, int rows) { return rows ? kWideBlocks[i].rt : kWideBlocks[i].ft; }\n' % (ROUND_ROWS, SLICES))
@@ -35,6 +37,15 @@ def _choose(lib, tiles, kt, rows, nwg, blocks, room, width):
     return c // 16, c % 16
 
 
+FEW_LAYER = {"qkv": 0, "o": 1, "down": 1, "gate/up": 2}
+
+
+def _few(lib, layer, tiles, kt, rows, room, nwg=NWG):
+    """(row tiles of a group, slices, ring) of the kernel for few rows, or None where it is not taken."""
+    c = lib.few(FEW_LAYER[layer], tiles, kt, rows, nwg, SLICES, ctypes.c_longlong(room))
+    return (c // 256, c // 16 % 16, c % 16) if c else None
+
+
 def _layers(width, q_heads, kv_heads, ffn):
     """(tiles, k-tiles, has slices) of the linear layers of a model."""
     return {"qkv": ((q_heads + 2 * kv_heads) * 4, width // 32, False), "o": (width // 16, q_heads * 2, True),
@@ -45,7 +56,7 @@ def _prompt_choices(lib, model, rows, max_trunk, blocks=None):
     """What the layers of a prompt pass of one sequence take, in a context with max_trunk positions."""
     room = lib.room(ctypes.c_longlong(min(max_trunk, PROMPT_ROWS if max_trunk > ROUND_ROWS else ROUND_ROWS)))
     return {(layer,) + _choose(lib, tiles, kt, rows, NWG, blocks or lib.count(layer == "gate/up", 0), room if slices else 0, model[0])
-            for layer, (tiles, kt, slices) in _layers(*model).items()}
+            for layer, (tiles, kt, slices) in _layers(*model).items() if not _few(lib, layer, tiles, kt, rows, room)}
 
 
 @pytest.mark.parametrize("width,ffn", [(512, 1024), (512, 8192), (1024, 4096), (2048, 8192)])
@@ -92,6 +103,32 @@ def test_blocks_that_are_not_compiled_would_not_be_taken(lib):
                 assert got == _prompt_choices(lib, model, rows, room_rows, 10), (model, rows)
                 taken |= {(layer, block) for layer, block, _ in got}
     assert taken == {(layer, i) for layer in ("qkv", "o", "down", "gate/up") for i in range(lib.count(layer == "gate/up", 0))}
+
+
+def test_few_rows_fit_the_layer_and_its_workspace(lib):
+    """The kernel for few rows: its quarters of a slice are whole turns of its ring, its partial sums fit, qkv is one turn of the grid; and
+    the GPU test reaches every instance that a shape takes."""
+    taken, reached = set(), set()
+    for model in _fused_models():
+        for rows in (1, 4, 16, 17, 32, 33, 48, 49):
+            room = lib.room(ctypes.c_longlong(rows))
+            for layer, (tiles, kt, slices) in _layers(*model).items():
+                for nwg in (NWG, 64, 8):
+                    c = _few(lib, layer, tiles, kt, rows, room, nwg)
+                    if c is None:
+                        continue
+                    mtg, S, depth = c
+                    assert rows <= 48 and kt % (4 * S * depth) == 0 and S * rows <= room and (slices or S == 1), (model, rows, layer)
+                    assert mtg == 1 if layer == "qkv" else mtg >= (rows + 15) // 16 and (mtg, layer) != (1, "gate/up"), (model, rows, layer)
+                    assert layer != "qkv" or (tiles + 3) // 4 * ((rows + 15) // 16) <= nwg
+                    if nwg == NWG:
+                        taken.add((FEW_LAYER[layer], mtg, depth))
+    for width, heads, kv_heads, ffn, rows in FEW_ROW_PROMPTS:
+        for layer, (tiles, kt, _) in _layers(width, heads, kv_heads, ffn).items():
+            c = _few(lib, layer, tiles, kt, rows, lib.room(ctypes.c_longlong(rows)))
+            if c:
+                reached.add((FEW_LAYER[layer], c[0], c[2]))
+    assert reached == taken and len(taken) == 12
 
 
 def _reached(lib):
