@@ -2843,14 +2843,12 @@ int launch_wide_resid_e(const FusedParams& p, const float* part, int S, const bf
 }
 
 // Single rows send every 128-byte line of the operand to memory in eight parts, one from each die; pieces of 8 rows send it whole, but
-// leave the few rows of a small launch on few dies, whose L2s then take longer to write back than eight would (the launch itself is
-// shorter, the one behind it starts later).  Whole passes of 8 layers of the 1B shape, us, single rows / pieces: 8 rows 571 / 577, 32
-// rows 600 / 604, 64 rows 688 / 687, 96 rows 724 / 725, 130 rows 838 / 835, 160 rows 845 / 841, 260 rows 1144 / 1137, 384 rows 1240 /
-// 1225, prompts of 299 tokens 871 / 861, 450 tokens 1090 / 1078, 1020 tokens 1622 / 1602.  16 layers of width 1024: 16 rows 669 / 677, 130 rows
-// 941 / 942, 260 rows 1149 / 1153, 384 rows 1200 / 1206, prompts of 450 tokens 1403 / 1393, 1020 tokens 1805 / 1787; of width 512: 16 rows 500
-// / 503, 130 rows 715 / 716, 260 rows 868 / 875, 384 rows 893 / 897, prompts of 450 tokens 1086 / 1064, 1020 tokens 1312 / 1216.
+// leave the few rows of a small launch on few dies, whose L2s then take longer to write back than eight would.  Whole passes, us, single
+// rows / pieces: 8 layers of the 1B shape 32 rows 498 / 497, 96 rows 589 / 586, 128 rows 600 / 596, 192 rows 744 / 737, 384 rows 989 / 977, prompts of
+// 450 tokens 932 / 921, 1020 tokens 1445 / 1435; of width 1024 32 rows 337 / 336, 96 rows 374 / 374, 160 rows 405 / 398, 384 rows 547 / 538; of
+// width 512 32 rows 255 / 257, 96 rows 303 / 305, 128 rows 304 / 297, 256 rows 326 / 316, 384 rows 350 / 343.
 int launch_wide_resid(const FusedParams& p, bool embed, const float* part, int S, const bf16_t* gain, float* hidden, int ph, hipStream_t s) {
-  const bool pieces = p.M > kFusedWideRows || (p.d >= 2048 && p.M >= 128);
+  const bool pieces = p.M >= 128;
   return embed ? launch_wide_resid_e<true>(p, part, S, gain, hidden, ph, pieces, s)
                : launch_wide_resid_e<false>(p, part, S, gain, hidden, ph, pieces, s);
 }
