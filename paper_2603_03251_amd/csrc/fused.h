@@ -17,10 +17,11 @@ constexpr int kFusedWideRows = 384; // rows of one wide pass (24 row tiles) of a
 constexpr int kFusedPromptRows = 1024;    // rows of a wide pass that only fills the trunk (prompts)
 constexpr int kFusedWideQueryTiles = 3;   // wide passes: most query tiles per attention unit
 constexpr int kFusedWideFreshKeys = 192;  // wide passes: keys of the pass itself an attention unit has LDS room for
-// Wide extends of more tokens of a sequence append their keys before the attention.  4 layers of the 1B shape, one prompt, us per
-// pass with the keys appended / staged by every unit: 64 rows 273 / 269, 96 289 / 284, 128 308 / 309, 160 314 / 322, 192 (what
-// the units have room for) 326 / 337.  The two cross near 120 rows; the line lies below that and costs 1 to 3 % in between.
-constexpr int kFusedWideAppendRows = 64;
+// Wide extends of more tokens of a sequence append their keys before the attention.  8 layers of the 1B shape, prompts, us per pass with the
+// keys appended / staged by every unit: one of 65 tokens 534 / 504, 96 550 / 525, 128 572 / 554, 144 618 / 609, 160 632 / 632, 176 657 / 663, 192
+// (what the units have room for) 663 / 672; two of 96 656 / 647, 128 685 / 685, 160 794 / 796; width 1024 one of 96 373 / 358, 144 402 / 400, 160
+// 410 / 405, 176 414 / 418, two of 160 469 / 475.
+constexpr int kFusedWideAppendRows = 144;
 constexpr int kFusedWideSlices = 8;       // wide passes: most k-slices of the o- and down-projections (one per XCD)
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())
 constexpr int kFusedMaxSlices = 4;   // most k-slices of a linear layer

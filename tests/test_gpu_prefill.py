@@ -36,7 +36,7 @@ def _trunk(B, ctx, lens, max_trunk, shape=SHAPE):
     return ks, vs
 
 
-@pytest.mark.parametrize("lens", [[1], [6], [64], [65], [191], [192], [193], [384], [385], [700], [129, 130], [40, 300, 7], [33] * 15],
+@pytest.mark.parametrize("lens", [[1], [6], [64], [65], [144], [145], [191], [192], [193], [384], [385], [700], [129, 130], [40, 300, 7], [33] * 15],
                          ids=lambda x: "-".join(map(str, x[:3])) + ("x%d" % len(x) if len(x) > 3 else ""))
 def test_wide_prefill_equals_narrow_chunks(B, lens):
     nb, max_trunk, seed = len(lens), max(lens) + 2 * K + 8, 7 + sum(lens)
@@ -112,11 +112,11 @@ def test_prompt_passes_at_the_edges_of_their_row_groups(B, width, lens, paged):
 
 
 @pytest.mark.parametrize("lens,pages", [([340, 10, 10], 13), ([250, 1, 1, 1], 11), ([500, 300], 26), ([470, 510], 31), ([190, 180, 10, 12], 14),
-                                        ([60] * 6 + [20], 13)],
+                                        ([60] * 6 + [20], 13), ([130, 130, 100, 90], 17)],
                          ids=lambda x: "-".join(map(str, x[:4])) if isinstance(x, list) else str(x))
 def test_unequal_prompts_take_no_pages_for_rows_that_only_pad(B, lens, pages):
     """Prompts of different lengths in a pool that holds them and no more: rows that pad a large pass to its longest prompt are not
-    stored (attention units that append themselves, up to 64 rows per sequence, and the pass that appends first)."""
+    stored (attention units that append themselves, up to 144 rows per sequence, and the pass that appends first)."""
     print(f"[case] prefill of {lens} in {pages} pages", flush=True)
     nb, max_trunk, seed = len(lens), max(lens) + 2 * K + 8, 13 + sum(lens)
     assert pages == sum((n + 31) // 32 for n in lens)
