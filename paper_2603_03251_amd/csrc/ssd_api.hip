@@ -606,15 +606,14 @@ int forward_rows(ssd_ctx* c, bool wide, int M, const int32_t* tokens, int rows_p
 }
 
 // A pass of few rows in a context that runs wide passes: one persistent launch is shorter than seven launches per layer for as
-// long as it takes the rows (1B shape, one extend with logits over 1500 keys: 12 rows 0.86 against 1.15 ms, 24 rows 0.87 against
-// 1.18, 48 rows 0.92 against 1.28; four and six row tiles, tried once: 54 rows 6 % shorter than a wide pass, 72 and 96 rows 10 %
-// longer) and its attention units, which take one query tile where those of a wide pass take up to three, do not pull the
-// same keys too often.  What the launches and the earlier weight loads save is taken as 0.18 us per layer and million
-// weights of it, what the units cost more is what the plans of the two say (ms, 1B shape: 3 x 16 rows over 8192 keys 1.26
-// against 1.46 as a wide pass, over 16384 1.61 against 1.64, 32768 2.21 against 2.00, 131072 5.4 against 4.1; 6 x 8 rows 1.34, 1.54;
-// 1.75, 1.81; 2.43, 2.37; 6.3, 5.5; width 1024, 6 x 8 rows over 8192 keys 0.86, 1.04, 16384 1.08, 1.17, 131072 4.2, 3.0; sequences of
-// one query tile stay shorter to the last length).  The line falls between 12000 and 16384 keys; the persistent pass, which has
-// become 3 to 7 % shorter since the 0.18 was fitted, would now be 2 to 13 % shorter at 16384 too.
+// long as it takes the rows (8 layers of the 1B shape, one extend over 1500 keys, us, against the wide pass: 12 rows 391 and 556, 24 rows 475
+// and 577, 48 rows 417 and 559 in three sequences, 611 and 744 in 48; four and six row tiles, tried once: 54 rows 6 % shorter than a wide
+// pass, 72 and 96 rows 10 % longer) and its attention units, which take one query tile where those of a wide pass take up to three, do
+// not pull the same keys too often.  What the launches and the earlier weight loads save is taken as 3.7 us per layer and 0.088 us per
+// million weights of it, what the units cost more is what the plans of the two say.  Measured, persistent / wide: 8 layers of the 1B shape
+// 3 x 16 rows over 8192 keys 591 / 638, 10000 643 / 650, 12288 688 / 676, 16384 764 / 714, 32768 1060 / 876; 6 x 8 rows 629 / 673, 683 / 692, 733 /
+// 732, 821 / 800, 1159 / 1110; 2 x 16 rows 24576 670 / 692, 32768 753 / 741; width 1024, 3 x 16 rows 16384 490 / 536, 24576 555 / 583, 32768 622 / 632; 6 x
+// 8 rows 16384 542 / 550, 20000 596 / 571, 32768 769 / 674; sequences of one query tile stay shorter to the last length.
 // Not into a graph that is being captured: persistent launches take turns by events, which a replay would not see.
 // seqs x T rows, the longest trunk with stored keys a row sees.
 bool takes_small_pass(const ssd_ctx* c, int seqs, int T, int stored, hipStream_t s) {
@@ -622,7 +621,7 @@ bool takes_small_pass(const ssd_ctx* c, int seqs, int T, int stored, hipStream_t
   const FusedParams& p = c->fp;
   const int tiles = (T * p.G + 15) / 16, keys = stored > 1 ? stored : 1;
   const float weights = (float)p.d * (p.qkvd + p.qd + 3.0f * p.ffn);
-  if (plan_attention(c, false, seqs, tiles, keys).cost > plan_attention(c, true, seqs, tiles, keys).cost + 0.18e-6f * weights) return false;
+  if (plan_attention(c, false, seqs, tiles, keys).cost > plan_attention(c, true, seqs, tiles, keys).cost + 3.7f + 0.088e-6f * weights) return false;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   return hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
 }
@@ -641,18 +640,18 @@ int extend_rows(ssd_ctx* c, bool wide, const int32_t* tokens, int T, int offset,
   return forward_rows(c, wide, nb * T, tokens, T, ub + offset, -1, logits, d.vocab, hidden, d.d_model, b0, s);
 }
 
-// What a prompt pass of `rows` rows costs, in rows: the weights it streams, its launches, and one more step behind 384 rows, where o and
-// down have room for half the slices (8 layers of the 1B shape, ms: 60 rows 0.48, 100 0.56, 200 0.67, 299 0.80, 384 0.85, 450 0.94, 700
-// 1.19, 1020 1.44; as a persistent pass
-// of 16 layers 10 rows 0.64, 48 rows 0.73.  Narrower models pay more for a pass and less for a row).
+// What a prompt pass of `rows` rows costs, in rows of its own: the weights it streams and its launches.  16 layers of the 1B shape, ms: 60 rows
+// 0.96, 100 1.13, 200 1.37, 340 1.69, 512 1.99, 768 2.52, 1020 2.98, as a persistent pass 4 rows 0.62, 48 rows 0.72; width 1024 200 rows 0.88, 512
+// 1.07, 1000 1.52, persistent 0.49 to 0.56; width 512 200 rows 0.70, 512 0.77, 1000 0.92: narrower models pay as much for a pass and less for a row.
 int prompt_pass_cost(const ssd_ctx* c, int rows) {
-  if (rows <= kFusedMaxRows && c->small_passes) return 300;
-  return 450 + rows + (rows > kFusedWideRows ? 80 : 0);
+  const int d = c->model->dims.d_model;
+  if (rows <= kFusedMaxRows && c->small_passes) return 320 * 2048 / d;
+  return 480 * 2048 / d + rows;
 }
 
 // The next sequences whose prompts share passes (wide_prefill), all padded to the longest of them: as many as fit kFusedWideRows
 // padded rows, and further such groups as long as all fit the largest pass and it is cheaper with them than with a pass for each
-// of the two parts (1B shape, ms: lengths 300 and 200 2.70 in one pass, 3.29 in two; 340, 10 and 10 3.15 in one, 2.49 in two).
+// of the two parts (1B shape, ms: lengths 300 and 200 2.30 in one pass, 2.97 in two; 340, 150 and 10 2.80, 3.22; 340, 10 and 10 2.98, 2.32).
 int next_prompt_group(const ssd_ctx* c, const int32_t* lens, int n) {
   auto rows = [&](int i0, int count) { return std::min<int>(*std::max_element(lens + i0, lens + i0 + count), c->prompt_rows) * count; };
   auto small_group = [&](int i0) {
@@ -675,7 +674,7 @@ int next_prompt_group(const ssd_ctx* c, const int32_t* lens, int n) {
 // several sequences where their prompts are short: a pass streams every weight once, so what a prompt costs is above all its
 // number of passes.  Otherwise chunks of K+1 tokens of all sequences.  Contexts whose rounds are narrow passes also take such a
 // chunk where it holds the whole prompts of a group: one persistent launch is shorter than a wide pass of as few rows (1B shape,
-// 10 rows 0.64 against 0.91 ms, 48 rows 0.73 against 1.03).
+// ms of a prompt of 4 to 10 tokens 0.62, of 60 tokens, a wide pass, 0.96).
 int prefill_rows(ssd_ctx* c, const int32_t* d_tokens, int stride, const int32_t* lens, int b0, int nb, hipStream_t s) {
   const int K1 = c->K + 1;
   for (int g0 = 0, gn = 0; g0 < nb; g0 += gn) {
@@ -1003,10 +1002,9 @@ static int ctx_create(const ssd_model* model, const ssd_round_config* cfg, const
     // (no more than the trunks have room for)
     c->prompt_rows = c->wide_prefill && (int64_t)c->B * c->max_trunk > kFusedWideRows ? kFusedPromptRows : kFusedWideRows;
     if (c->wide_prefill) c->max_rows = std::max(c->max_rows, c->prompt_rows);
-    // Few-row extends on the persistent pass: from a width of 1024 on (16 to 48 rows, 100 and 4000 keys: width 1024, 8 layers,
-    // 268..431 us against 328..514 as wide passes; width 512, 4 layers, 141..187 against 141..202, 16 layers 476..675 against 485..818;
-    // the line was drawn when width 512 took 152..196 and 520..710).  A context whose workgroups
-    // could not all be resident keeps the wide passes.
+    // Few-row extends on the persistent pass: from a width of 1024 on (12 to 48 rows, 8 layers, 100 and 4000 keys: width 1024 257..565 us
+    // against 308..620 as wide passes, width 512 244..404 against 249..458 with single shapes over 100 keys 1 % longer; the line was drawn
+    // when width 512 gained less).  A context whose workgroups could not all be resident keeps the wide passes.
     int grid = 0;
     c->small_passes = c->wide_prefill && d.d_model >= 1024 && !(cfg->flags & SSD_CTX_FUSED_PHASES) && fused_grid_size(&grid) == SSD_OK &&
                       (c->fused_mode == 2 || fused_check_residency(grid, d.d_model / 256, 7, cfg->kv_pages ? 1 : 0) == SSD_OK);
