@@ -20,7 +20,7 @@ constexpr int kFusedWideFreshKeys = 192;  // wide passes: keys of the pass itsel
 // Wide extends of more tokens of a sequence append their keys before the attention.  8 layers of the 1B shape, prompts, us per pass with the
 // keys appended / staged by every unit: one of 65 tokens 534 / 504, 96 550 / 525, 128 572 / 554, 144 618 / 609, 160 632 / 632, 176 657 / 663, 192
 // (what the units have room for) 663 / 672; two of 96 656 / 647, 128 685 / 685, 160 794 / 796; width 1024 one of 96 373 / 358, 144 402 / 400, 160
-// 410 / 405, 176 414 / 418, two of 160 469 / 475.
+// 410 / 405, 176 414 / 418, two of 160 469 / 475.  (Staged with an attention in the last layer too, which a pass without outputs leaves out.)
 constexpr int kFusedWideAppendRows = 144;
 constexpr int kFusedWideSlices = 8;       // wide passes: most k-slices of the o- and down-projections (one per XCD)
 constexpr int kFusedClockSlots = 8;  // clock probes per phase and workgroup (see stamp())

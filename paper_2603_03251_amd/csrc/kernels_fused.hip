@@ -2891,10 +2891,11 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
       e.act_out = p.act;
       SSD_TRY(launch_wide_layer<FE_SWIGLU>(cut_gu, p, L.gu, p.xn, e, s));
     } else if (sub == 1) {
-      if (p.appended) {
+      // (a pass without outputs ends where the last layer's keys and values are stored: no attention there)
+      if (p.appended || ph == last) {
         wide_append_kernel<PG><<<(p.M * p.Hkv * 8 + 255) / 256, 256, 0, s>>>(p, L.trunk_k, L.trunk_vt);
         SSD_HIP(hipGetLastError());
-        if (ph == last) continue;                    // (a pass without outputs: stored, that was all)
+        if (ph == last) continue;
       }
       SSD_TRY((launch_wide_attn<PL, PG>(p, L, ph, s)));
     } else if (p.NS > 1) {                           // (no merge phase with one key split)
