@@ -147,7 +147,8 @@ typedef struct {
   int32_t pass_rows;           /* most rows of one fused pass of a round: 48 (narrow passes), 384 (wide passes), 0 without the fused
                                   pass.  Prompts are prefilled in passes of up to 1024 rows either way (unless a flag asks for
                                   narrow passes or other activation planes; 384 where the trunks hold no more positions), with a
-                                  workspace for them */
+                                  workspace for them.  Most of a wide pass's workspace are partial sums of d_model floats: eight
+                                  per row of a round (25 MB for 384 rows of width 2048), four per row of a prompt pass */
 } ssd_views;
 /* Contexts of wide passes (fused_pass 1, pass_rows 384) of models at least 1024 wide launch the persistent kernel as well: for
  * extends of at most 48 rows in all (the glue extend of a small batch, ssd_ctx_extend, what full passes leave of a prompt; not over

@@ -101,8 +101,6 @@ struct FanTable {
 };
 
 // ---------------------------------------------------------------- kernels_misc.hip
-// Row descriptors + rotary tables for a branch step / an extend, from device-side trunk lengths.  The branch version
-// also gathers the token every row feeds at this step into step_tokens (null: skipped).
 // The embedding gather of a pass, which the launches that set its rows up do beside that (table null: no gather): row m of h [M][d] =
 // the embedding of its token, kept within the vocabulary.
 struct EmbedGather {
@@ -110,6 +108,8 @@ struct EmbedGather {
   float* h;
   int d, vocab, dtype;
 };
+// Row descriptors + rotary tables for a branch step / an extend, from device-side trunk lengths.  The branch version
+// also gathers the token every row feeds at this step into step_tokens (null: skipped).
 int launch_setup_branch_rows(RowDesc* rows, float* cos_sin, const int32_t* trunk_len, int B, int K, const FanTable& fan, int step,
                              int half_dim, float theta, int32_t* step_tokens, const int32_t* keys,
                              const int32_t* cache_tokens, const int32_t* forced_keys, const int32_t* forced_tokens,
@@ -149,11 +149,11 @@ int launch_tile_weights_bf16(const bf16_t* src, bf16_t* dst, int N, int Kd, hipS
 int launch_gemm(int dtype, int epi, const void* x, int64_t x_plane, const void* w, const void* w2, void* out, int64_t ld,
                 int64_t out_plane, int M, int N, int Kd, hipStream_t s);
 // fp32 models: RMSNorm of the residual stream h [M][d_model] together with the linear layer that reads it.
-// act = silu(xn w_gate^T) * (xn w_up^T); and q (rotated), keys (rotated) and values of xn wqkv^T, the latter two straight
-// into the rows' KV slots.
-// final norm + LM head; hidden (or null): the normalised rows
+// logits = xn w^T; hidden (or null): the normalised rows xn
 int launch_norm_head_f32(const float* h, const float* gain, const float* w, float* logits, int64_t ld, float* hidden, int64_t hidden_ld,
                          int M, int V, int d_model, float eps, hipStream_t s);
+// act = silu(xn w_gate^T) * (xn w_up^T); and q (rotated), keys (rotated) and values of xn wqkv^T, the latter two straight
+// into the rows' KV slots.
 int launch_norm_swiglu_f32(const float* h, const float* gain, const float* w_gate, const float* w_up, float* act, int M, int d_ffn,
                            int d_model, float eps, hipStream_t s);
 int launch_norm_qkv_rope_f32(const float* h, const float* gain, const float* wqkv, float* q, float* trunk_k, float* trunk_v,

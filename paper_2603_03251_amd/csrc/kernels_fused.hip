@@ -1238,7 +1238,7 @@ __device__ __forceinline__ void attn_merge_unit(const FusedParams& p, int mt, in
 // and the memory-side cache alike, at 6-7.4 TB/s (24-29 GB/s per compute unit).  So a layer's cost is what crosses into the
 // L2s: the weights once, and the activations once per XCD that needs them.
 //
-// Linear layers: wide_block_kernel, below.  The o- and down-projections have few features under a long reduction dimension: they are
+// Linear layers: wide_block_kernel, below, and wide_few_kernel for up to 48 rows.  The o- and down-projections have few features under a long reduction dimension: they are
 // cut into up to 8 k-slices, XCD x working on slice x mod S, so that an XCD's L2 takes in only that slice of the activations and, among
 // the XCDs of a slice, only its own features' weights.  Their fp32 partial sums go to memory, and wide_resid_kernel, a workgroup per
 // row, adds them to the residual stream in slice order and leaves the row's 1/rms: the linear layers that follow load one number per
@@ -1273,12 +1273,13 @@ __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)
 // the MFMA, so a tile is one load, its LDS image the same 1 KiB, and reading it back free of bank conflicts.  A step is one k-tile: wait
 // until the next one has landed, barrier, then the MFMAs of this one with the LDS reads of the next and the loads for the buffer that
 // has just become free between them (sched_barrier: a burst of memory operations would hold up the MFMAs behind it).
-// What bounds it: with many rows the power the chip may draw (under 32x32x16 MFMAs on random data the clock falls to 1.6 GHz: 1.7 PFLOP/s;
-// 16x16x32, taken here, 1.9), so operands are moved as few times as possible: large blocks; with few rows the weight stream and the steps'
-// latency (0.2 us each).  us of a launch at 2048 inputs, 16384 gate/up features, one machine, against the kernels it replaces (64 features
-// with the reduction dimension over the wavefronts, and 256 features x 96 or 128 rows with the weights in registers): 96 rows 18.0 and
-// 21.8 + 2.4 (gap), 192 rows 22.9 and 27 + 2.4, 384 rows 31.3 and 35.1, 1020 rows 61 and 77.  2048 features, 8192 inputs in slices: 96 rows
-// 11.9 and 13.1, 384 rows 22.5 and 28.0.
+// What bounds it, by count and counters (1B shape): with many rows the LDS beside the MFMAs.  A step of gate/up takes about 910 clocks at 384
+// rows, in which the LDS moves 84 KiB in 672 and the matrix pipes work 384, and 1950 at 1020 rows (128 KiB in 1024, 1024; the clock falls to 2.15
+// GHz), so operands are moved as few times as possible: large blocks, and 16x16x32 MFMAs, which draw a tenth less power for the same work.
+// With few rows the weight stream and the steps' latency (0.2 us each).  us of a launch at 2048 inputs, 16384 gate/up features, one machine,
+// against the kernels it replaces (64 features with the reduction dimension over the wavefronts, as wide_few_kernel still does, and 256
+// features x 96 or 128 rows with the weights in registers): 96 rows 18.0 and 21.8 + 2.4 (gap), 192 rows 22.9 and 27 + 2.4, 384 rows 31.3 and
+// 35.1, 1020 rows 61 and 77.  2048 features, 8192 inputs in slices: 96 rows 11.9 and 13.1, 384 rows 22.5 and 28.0.
 // Past its last block a workgroup goes on loading the last k-tile (the waits count loads), and it leaves when everything has landed.
 template <int ATW, int EPI, int FT, int RT, int WN, int G, int NB, int TH>
 __global__ __launch_bounds__(TH) void wide_block_kernel(FusedParams p, FusedGemm g, const bf16_t* bsrc, WideEpi e) {
@@ -2891,7 +2892,8 @@ int launch_wide_pl(const FusedParams& p, const FusedLayer* layers_host, int firs
       e.act_out = p.act;
       SSD_TRY(launch_wide_layer<FE_SWIGLU>(cut_gu, p, L.gu, p.xn, e, s));
     } else if (sub == 1) {
-      // (a pass without outputs ends where the last layer's keys and values are stored: no attention there)
+      // (a pass without outputs ends where the last layer's keys and values are stored: no attention there, also where the units would stage
+      // the keys.  Three prompts of 100 tokens, 2 layers of the 1B shape: 139 us, 155 with the last attention, 147 with all keys appended first)
       if (p.appended || ph == last) {
         wide_append_kernel<PG><<<(p.M * p.Hkv * 8 + 255) / 256, 256, 0, s>>>(p, L.trunk_k, L.trunk_vt);
         SSD_HIP(hipGetLastError());

@@ -10,10 +10,10 @@ namespace ssd {
 // 16 x 12 0.74, 16 x 16 0.85 to 0.95), 1.5 per block, and each k-slice 0.1 and what writing and reading its partial sums costs at 6 TB/s,
 // beyond four slices 0.4 more (the residual kernel loads four at a time; with 1 instead, which takes down of 384 rows of the 1B shape from
 // eight slices in blocks of 8 x 12 to four in blocks of 8 x 6, rounds of 384 rows take 3 % longer).
-// Taken is the cheapest; with one slice and few enough rows that is the smallest block that leaves no workgroup a second one.  Best
-// and second best of a sweep (us of a launch; 2048 inputs, 16384 features): 64 rows 4 x 4 15.6, 4 x 6 17.9; 128 rows 4 x 8 19.5, 8 x 6 22.9;
-// 192 rows 8 x 6 22.9, 8 x 8 25.2; 256 rows 8 x 8 25.2, 8 x 12 33.2; 384 rows 8 x 12 32.9, 16 x 8 35.0; 512 rows 16 x 8 40.0, 8 x 8 44.0;
-// 768 rows 16 x 12 56.3, 16 x 16 58.6; 1020 rows 16 x 16 66.7, 16 x 8 82.3.
+// Taken is the cheapest; with one slice and few enough rows that is the smallest block that leaves no workgroup a second one.  Best of a
+// sweep, and how much longer a launch with the second best took (2048 inputs, 16384 features): 64 rows 4 x 4, 4 x 6 15 %; 128 rows 4 x 8, 8 x 6
+// 18 %; 192 rows 8 x 6, 8 x 8 10 %; 256 rows 8 x 8, 8 x 12 32 %; 384 rows 8 x 12, 16 x 8 6 %; 512 rows 16 x 8, 8 x 8 10 %; 768 rows 16 x 12, 16 x 16
+// 4 %; 1020 rows 16 x 16, 16 x 8 23 %.
 struct WideBlock { int ft, rt; };
 constexpr WideBlock kWideBlocks[] = {{4, 2}, {4, 4}, {4, 6}, {4, 8}, {8, 6}, {8, 8}, {8, 12}, {16, 8}, {16, 12}, {16, 16}, {16, 6}};
 constexpr int kNumWideBlocks = sizeof(kWideBlocks) / sizeof(kWideBlocks[0]);   // the last one for the LM head only (288 rows: three groups)

@@ -7,12 +7,12 @@ import torch
 import ssd_inputs as I
 from oracle import ssd_oracle as O
 
-# spec tolerances: relative error of logits / hidden states against the float64 oracle
+# what every path is held to at least: relative error of logits / hidden states against the float64 oracle
 TOL = {"bf16": 2e-2, "f32": 1e-4}
 # What the bf16 paths (bf16 weights and KV, fp32 accumulation; between the phases of the fused pass the activations that
 # meet the weights as one fp16 plane, queries and probabilities as two bf16 planes) are measured at against the float64
 # oracle, with head room of about 2x: a wrongly visible key among thousands shows up here long before it reaches the
-# spec figure above.  Measured: up to 2.6e-3 through the 16 layers of the 1B shape when both sides start from the
+# figure above.  Measured: up to 2.6e-3 through the 16 layers of the 1B shape when both sides start from the
 # same bf16-representable prefix KV (1.1e-3 with SSD_CTX_TWO_PLANES), less on the 2-layer shapes; up to 3.9e-3 when the
 # whole trunk comes from a prefill on the GPU, whose KV is rounded to bf16 while the oracle keeps its own in float64.
 TOL_FUSED_BF16 = 5e-3

@@ -2,7 +2,7 @@
 
 Protocol: (i) selection is compared on the oracle's logits (test_gpu_select.py) and, inside the round,
 wherever the oracle's margin is not a near-tie; (ii) numerics are teacher-forced: the GPU runs every step on
-the oracle's input tokens, so logits and hidden states must agree within the benchmark spec's tolerance
+the oracle's input tokens, so logits and hidden states must agree within the tolerances of gpu_util
 (rel 2e-2 in bf16, 1e-4 in fp32, relative to each row's largest magnitude); (iii) the fp32 tiny workload also
 runs free and must reproduce the oracle's tokens wherever the oracle's top-2 margin exceeds 1e-4."""
 import numpy as np
