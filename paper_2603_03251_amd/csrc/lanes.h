@@ -11,7 +11,8 @@
 
 namespace ssd {
 
-// What a lane and its partner (lane ^ O) hold of `v`, in an order that is the same for both: operands of a commutative operation.
+// What a lane and its partner (lane ^ O) hold of `v`: operands of an operation that gives both the same result whichever comes first (for a
+// choice between two values that means no NaN among them).
 template <int O>
 __device__ __forceinline__ void lane_pair(uint32_t v, uint32_t& a, uint32_t& b) {
   static_assert(O == 1 || O == 2 || O == 4 || O == 8 || O == 16 || O == 32, "a bit of the lane index");

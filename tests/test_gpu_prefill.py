@@ -74,11 +74,11 @@ def test_wide_prefill_equals_narrow_chunks(B, lens):
 
 
 @pytest.mark.parametrize("width,lens", [(1024, [512]), (1024, [513]), (512, [896]), (1024, [897]), (512, [1024]), (1024, [1025]),
-                                        (512, [1409]), (1024, [500, 512, 30])], ids=lambda x: str(x) if isinstance(x, int) else "-".join(map(str, x)))
+                                        (512, [1409]), (512, [1124]), (1024, [1168]), (1024, [500, 512, 30])], ids=lambda x: str(x) if isinstance(x, int) else "-".join(map(str, x)))
 @pytest.mark.parametrize("paged", [False, True])
 def test_prompt_passes_at_the_edges_of_their_row_groups(B, width, lens, paged):
     """Passes of 385 to 1024 rows: whole groups of 8 row tiles, one row more, the most a pass takes and what is left behind it (1 row;
-    385), the row count from which o and down have room for fewer slices (512 | 513), a pass of two sequences."""
+    100, 144, whose keys the units stage beside stored ones; 385), the row count from which o and down have room for fewer slices (512 | 513), a pass of two sequences."""
     print(f"[case] width {width}, prefill of {lens}, paged {paged}", flush=True)
     nb, max_trunk, seed = len(lens), max(lens) + 2 * K + 8, 3 + sum(lens)
     shape = I.ModelShape(n_layers=2, d_model=width, n_q_heads=width // 64, n_kv_heads=width // 256, head_dim=64, d_ffn=2 * width, vocab=4112,
